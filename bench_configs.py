@@ -72,7 +72,7 @@ def main():
         print("| Config | Workload | Projection (h -> d) | T | K | kernels | ms fwd+bwd | useful TFLOP/s | tokens/s | % of 2.5 PFLOP/s |")
         print("|---|---|---|---|---|---|---|---|---|---|")
         for r in rows:
-            kern = "MFMA" if r["kernel_path"] == 0 else "generic (fp32 mode)"
+            kern = "MFMA" if r["kernel_path"] == 0 else "general (fp32 mode)"
             pct = f'{r["pct_of_bf16_mfma_peak"]:.1f}' if r["dtype"] == "bf16" else "-"
             print(f'| {r["config"]} | {r["workload"]} | {r["projection"]} ({r["h"]} -> {r["d"]}) | {r["T"]} | {r["K"]} | {kern} '
                   f'| {r["ms"]:.3f} | {r["tflops"]:.1f} | {r["tokens_per_s"]:.3e} | {pct} |')

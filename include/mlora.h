@@ -165,8 +165,7 @@ mlora_status mlora_lora_bwd_recompute(const mlora_problem* p, const void* X, con
  * with the same T, h, K, dtype and split positions; d, W and the adapters (ranks, scalings,
  * A_k, B_k) are each projection's own.  The forward outputs are Eq. "forward" per projection;
  * the backward writes ONE dX, the sum over the projections of Eq. "grad_output", accumulated
- * in fp32 and rounded once (on the MFMA path; the generic path adds projection by projection
- * in the storage type), and Eq. "grad_lora" per projection.
+ * in fp32 and rounded once, and Eq. "grad_lora" per projection.
  *   ps         HOST array of P pointers to problems
  *   Y, saved   HOST arrays of P DEVICE pointers: Y[p] is [T, d_p]; saved[p] has
  *              mlora_lora_saved_bytes(ps[p]) bytes
@@ -232,12 +231,13 @@ const char* mlora_status_string(mlora_status s);
 int mlora_last_hip_error(void);
 
 /* Which kernels the calls will run for `p` (bit mask), so that a caller can tell the fast path
- * from the fallback before it launches anything:
- *   0      bf16 MFMA kernels everywhere,
- *   bit 0  the two base products run the generic (plain vector ALU, roughly 100 times slower)
- *          kernels,
- *   bit 1  the low-rank products run the generic kernels (3 = generic everywhere).
- * The MFMA kernels take bf16 problems whose h and d are multiples of 64, whose ranks are
+ * from the general one before it launches anything:
+ *   0      aligned bf16 kernels (direct-to-LDS loads) everywhere,
+ *   bit 0  the two base products run the general kernels (any size, alignment and dtype; matrix
+ *          pipes as well, operands through registers: 2 to 3 times the time in bf16, and the fp32
+ *          MFMA rate in fp32),
+ *   bit 1  the low-rank products run the general kernels (3 = general everywhere).
+ * The aligned kernels take bf16 problems whose h and d are multiples of 64, whose ranks are
  * multiples of 8 and whose W, A_k, B_k are 16-byte aligned; the answer assumes that the buffers
  * passed to the calls (X, Y, dY, dX, saved, workspace) are 16-byte aligned too, as device
  * allocations are -- a call handed a misaligned buffer falls back for that call.  Returns -1 if

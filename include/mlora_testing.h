@@ -1,7 +1,7 @@
 /*
  * mlora_testing.h -- test and measurement switches of libmlora.
  *
- * Not part of the operator's interface (mlora.h): a process-wide switch that forces the slower
+ * Not part of the operator's interface (mlora.h): a process-wide switch that forces the general
  * kernels, so that tests can compare every kernel mix on one shape, and a timing aid that
  * brackets the library's kernel launches with HIP events.  Unlike the entry points of mlora.h
  * the timing aid allocates: it creates HIP events (hipEventCreate) on first use and keeps them
@@ -17,11 +17,11 @@ extern "C" {
 #endif
 
 /* Selects which kernels the entry points use (bit mask):
- *   0 (default) fastest applicable path: MFMA kernels when the problem is bf16, h and d are
- *               multiples of 64, every rank is a multiple of 8 and all buffers are 16-byte
- *               aligned; the generic kernels otherwise,
- *   bit 0       generic kernels for the two base products,
- *   bit 1       generic kernels for the low-rank products (3 = generic everywhere).
+ *   0 (default) fastest applicable path: aligned bf16 kernels when the problem is bf16, h and d
+ *               are multiples of 64, every rank is a multiple of 8 and all buffers are 16-byte
+ *               aligned; the general kernels otherwise,
+ *   bit 0       general kernels for the two base products,
+ *   bit 1       general kernels for the low-rank products (3 = general everywhere).
  * Returns the previous value.  Process-wide. */
 int mlora_set_kernel_path(int path);
 

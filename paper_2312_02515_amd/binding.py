@@ -185,7 +185,7 @@ class Problem:
         return int(lib.mlora_lora_validate(ctypes.byref(self.c)))
 
     def kernel_path(self) -> int:
-        """0 = MFMA kernels; bit 0 / bit 1 = generic kernels for the base / low-rank products."""
+        """0 = aligned bf16 kernels; bit 0 / bit 1 = general kernels for the base / low-rank products."""
         return int(lib.mlora_lora_kernel_path(ctypes.byref(self.c)))
 
     def alloc_saved(self) -> torch.Tensor:

@@ -1,0 +1,951 @@
+// General kernels: every shape, segment layout, rank and alignment, in fp32 or bf16 storage, on the
+// matrix pipes with fp32 accumulation.  They carry the fp32 mode and every bf16 problem whose
+// sizes or addresses the direct-to-LDS kernels (gemm_mfma_kernel.h, lowrank_mfma.hip) do not take.
+//
+// Steps (section 3.3.1 of the mLoRA paper, with the scaling s_k folded into the low-rank
+// intermediates):
+//   forward :  Z = s_k x_k A_k            (k_gen_rows)
+//              Y = X W + Z B_k            (k_gen_gemm, W [h,d] read along its rows)
+//   backward:  G = s_k dy_k B_k^T         (k_gen_rows)
+//              dB_k = Z^T dy_k            (k_gen_grad)
+//              dX = dY W^T + G A_k^T      (k_gen_gemm, W [h,d] as the transposed operand)
+//              dA_k = x_k^T G             (k_gen_grad)
+//
+// fp32 products run on v_mfma_f32_32x32x2_f32 / 16x16x4_f32 (IEEE fp32 multiply-adds), bf16 ones on
+// the bf16 MFMAs; any assignment of contraction indices to MFMA slots is correct as long as both
+// operands use the same one, which is what lets a lane feed its four MFMAs from one 16-byte piece.
+#include <type_traits>
+
+#include "mfma_staging.h"
+#include "mlora_common.h"
+
+namespace mlora {
+namespace {
+
+using namespace stage;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+
+// 16 bytes at an address that is only a multiple of the element size (global memory takes them at
+// any alignment; a misaligned piece costs a second cache line)
+template <typename T> struct Piece16;
+template <> struct Piece16<float> {
+  typedef unsigned type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <> struct Piece16<bf16> {
+  typedef unsigned type __attribute__((ext_vector_type(4), aligned(2)));
+};
+template <typename T> constexpr int kV = 16 / (int)sizeof(T);   // elements per 16-byte piece
+
+// Elements i .. i + V - 1 of a row of n elements.  A piece that crosses the row's end is loaded so
+// that it ends there; tail_shift() moves it into place and fills with zeros (rows shorter than one
+// piece are put together element by element, already in place).
+template <typename T>
+__device__ __forceinline__ u32x4 load_piece(const T* row, int i, int n) {
+  constexpr int V = kV<T>;
+  if (n >= V) {
+    const int s = i < n - V ? i : n - V;
+    return *reinterpret_cast<const typename Piece16<T>::type*>(row + s);
+  }
+  union {
+    u32x4 v;
+    T e[V];
+  } u;
+  u.v = u32x4{0, 0, 0, 0};
+#pragma unroll
+  for (int e = 0; e < V; ++e)
+    if (i + e < n) u.e[e] = row[i + e];
+  return u.v;
+}
+template <typename T>
+__device__ __forceinline__ u32x4 tail_shift(u32x4 v, int i, int n) {
+  constexpr int V = kV<T>;
+  if (n < V) return v;
+  const int d = i - (n - V);
+  if (d <= 0) return v;
+  if (d >= V) return u32x4{0, 0, 0, 0};
+  const int bits = d * 8 * (int)sizeof(T);
+  const unsigned __int128 x = __builtin_bit_cast(unsigned __int128, v) >> bits;
+  return __builtin_bit_cast(u32x4, x);
+}
+
+// acc += a x b over one 16-byte piece per lane of each operand (32 rows x 32 columns)
+__device__ __forceinline__ void mma32(f32x16& acc, u32x4 a, u32x4 b, bf16) {
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma32(f32x16& acc, u32x4 a, u32x4 b, float) {
+  const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
+}
+// the same on 16 rows x 16 columns
+__device__ __forceinline__ void mma16(f32x4& acc, u32x4 a, u32x4 b, bf16) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+}
+__device__ __forceinline__ void mma16(f32x4& acc, u32x4 a, u32x4 b, float) {
+  const f32x4 x = __builtin_bit_cast(f32x4, a), y = __builtin_bit_cast(f32x4, b);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], acc, 0, 0, 0);
+}
+
+// 32 consecutive rows of the virtual row axis, on which every row range of the call (before the
+// first task, each task, after the last) is padded to a multiple of 32: a piece never holds rows of
+// two tasks, so no row ever meets another task's adapter, not even multiplied by zero.
+struct RowPiece {
+  int row, n, task;   // first real row, real rows (0 = beyond the last row), task (-1 = none)
+};
+
+// ------------------------------------------------------------------------------------------
+// C[M,N] = sum_g ( A_g[M,Kd_g] * op(W_g) + rows_k( L_g[rows_k, :r_gk] * R_gk ) )
+//   NN = true : W_g [Kd_g, N], R_gk [r_gk, N]      NN = false: W_g [N, Kd_g], R_gk [N, r_gk]
+// ------------------------------------------------------------------------------------------
+template <int NSEG>
+struct GenGemmArgs {
+  void* C;
+  float* part;                           // fp32 partial tiles when parts > 1
+  int M, N, tiles_m, tiles_n, parts;
+  int K;
+  int off[kMaxK + 1];
+  const void* A[NSEG];
+  const void* W[NSEG];
+  const void* L[NSEG];
+  int Kd[NSEG];
+  int ldz[NSEG];
+  unsigned char rank[NSEG][kMaxK];
+  PtrTable R[NSEG];
+};
+
+template <typename Args>
+__device__ __forceinline__ RowPiece find_piece(const Args& a, long long v0) {
+  RowPiece p{a.M - 1, 0, -1};
+  long long vstart = 0;
+  int prev = 0;
+  for (int r = 0; r < a.K + 2; ++r) {
+    const int b1 = r <= a.K ? a.off[r] : a.M;
+    const int len = b1 - prev, vlen = (len + 31) & ~31;
+    if (v0 >= vstart && v0 < vstart + vlen) {
+      const int o = (int)(v0 - vstart);
+      p.row = prev + o;
+      p.n = (len - o) < 32 ? (len - o) : 32;
+      p.task = (r >= 1 && r <= a.K) ? r - 1 : -1;
+    }
+    vstart += vlen;
+    prev = b1;
+  }
+  return p;
+}
+
+// Block id -> (tile, part).  Consecutive ids go round-robin over the 8 XCDs; each XCD takes a
+// contiguous eighth of the order (8 row tiles x all column tiles at a time, column by column), so
+// that the blocks it runs together share operand strips in its L2.
+template <typename Args>
+__device__ __forceinline__ void block_tile(const Args& a, int bid, int* tm, int* tn, int* part) {
+  const int total = a.tiles_m * a.tiles_n * a.parts;
+  const int per = total / 8;
+  int t = bid < per * 8 ? (bid % 8) * per + bid / 8 : bid;
+  *part = t % a.parts;
+  t /= a.parts;
+  constexpr int GM = 8;
+  const int gsize = GM * a.tiles_n;
+  const int group = t / gsize, first = group * GM;
+  const int gm = (a.tiles_m - first) < GM ? (a.tiles_m - first) : GM;
+  const int in_g = t - group * gsize;
+  *tm = first + in_g % gm;
+  *tn = in_g / gm;
+}
+
+// C element store of one 32 x 32 accumulator: lane holds column l32 and rows 8 g + 4 lhi + e
+template <typename T>
+__device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const RowPiece& p, int col, int lhi) {
+  if (col < N) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int o = 8 * g + 4 * lhi + e;
+        if (o < p.n) C[(size_t)(p.row + o) * N + col] = from_f32<T>(acc[4 * g + e]);
+      }
+  }
+}
+
+// Tile BM x BN, 4 waves as 2 x 2, contraction tiles of 128 bytes per row (64 bf16 or 32 fp32).
+// Operands go through registers into two LDS stages: the pieces of tile kt+2 are requested while
+// tile kt is multiplied and written to LDS a tile later, so a load has one whole tile of MFMAs to
+// land, and tails, short rows and odd strides are handled between the load and the LDS write.
+// K-contiguous tiles keep 16-byte piece c of row r at c ^ ((r >> 1) & 7) (conflict-free b128 reads);
+// the NN weight tile keeps its rows as they are in memory (bf16: pieces permuted for the
+// transposing reads; fp32: read element by element, 32 columns of a row at a time).
+// The LoRA term is added from registers at the end, 32-row piece by piece: L and R_k come straight
+// from memory (r_k <= 128 contraction indices against thousands).
+// With parts > 1 a tile's contraction is cut into `parts` ranges, one block each; the partial tiles
+// go to memory in fp32 and k_gen_reduce adds them in order.
+// Bound by the fp32 matrix rate in fp32 (153 TFLOP/s for a large product on this card): T = 2048,
+// 4096 x 4096: 720 us forward, 605 us backward layout (95 and 114 TFLOP/s), against 1714 and 1686 us
+// of a vector-ALU kernel with 64 x 64 tiles; bf16, T = 3072, 4096 x 4096, 240 us (430 TFLOP/s,
+// bound by LDS traffic and the wait for each tile's loads) against 2800 and 3084 us.
+template <typename T, int BM, int BN, bool NN, int NSEG>
+__global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
+  constexpr int V = kV<T>, BK = 8 * V;
+  constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
+  constexpr int NA = BM / 32, NB = BN / 32;          // pieces per thread and tile of each operand
+  constexpr int ABYTES = BM * 128, BBYTES = BN * 128;
+  constexpr int CPR = BN / V;                        // pieces per row of the NN weight tile
+  constexpr bool B16 = sizeof(T) == 2;
+  __shared__ __attribute__((aligned(1024))) char sm[2 * (ABYTES + BBYTES)];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int l32 = lane & 31, lhi = lane >> 5;
+  int tm, tn, part;
+  block_tile(a, blockIdx.x, &tm, &tn, &part);
+  const int col0 = tn * BN, M = a.M, N = a.N;
+
+  RowPiece pc[NA];
+#pragma unroll
+  for (int f = 0; f < NA; ++f) pc[f] = find_piece(a, (long long)tm * BM + 32 * f);
+
+  f32x16 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  // this part's share of the contraction tiles of all operand pairs
+  int total_kt = 0;
+#pragma unroll
+  for (int g = 0; g < NSEG; ++g) total_kt += (a.Kd[g] + BK - 1) / BK;
+  int p0 = (int)((long long)total_kt * part / a.parts), p1 = (int)((long long)total_kt * (part + 1) / a.parts);
+
+  const int ar = tid >> 3, ac = tid & 7;             // K-contiguous: row (of 32) and piece of this thread
+  const bool n_edge = NN && col0 + BN > N;
+  // fragment addresses
+  const int fsw = (l32 >> 1) & 7;
+  const int a_off = (wm * WM + l32) * 128, b_off = (wn * WN + l32) * 128;
+  const int L16 = lane & 15, blk = lane >> 4, kq = L16 >> 2;
+  const int tr_k = 8 * (blk >> 1) + kq, tr_n = 16 * (blk & 1) + 4 * (L16 & 3);
+
+  for (int g = 0; g < NSEG; ++g) {
+    const int Kd = a.Kd[g];
+    const int KT = (Kd + BK - 1) / BK;
+    const int t0 = p0 > 0 ? p0 : 0, t1 = p1 < KT ? p1 : KT;
+    p0 -= KT;
+    p1 -= KT;
+    if (t0 >= t1) continue;
+    const T* A = static_cast<const T*>(a.A[g]);
+    const T* W = static_cast<const T*>(a.W[g]);
+    const T* arow[NA];
+#pragma unroll
+    for (int it = 0; it < NA; ++it) {
+      const int last = pc[it].n > 0 ? pc[it].n - 1 : 0;
+      arow[it] = A + (size_t)(pc[it].row + (ar < last ? ar : last)) * Kd;
+    }
+    const T* brow[NB];
+    if constexpr (!NN) {
+#pragma unroll
+      for (int it = 0; it < NB; ++it) {
+        const int n = col0 + ar + 32 * it;
+        brow[it] = W + (size_t)(n < N ? n : N - 1) * Kd;
+      }
+    }
+    u32x4 ra[NA], rb[NB];
+    auto load = [&](int kt) {
+      const int k0 = kt * BK;
+#pragma unroll
+      for (int it = 0; it < NA; ++it) ra[it] = load_piece<T>(arow[it], k0 + ac * V, Kd);
+#pragma unroll
+      for (int it = 0; it < NB; ++it) {
+        if constexpr (NN) {
+          const int idx = tid + 256 * it;
+          int k = k0 + idx / CPR;
+          k = k < Kd ? k : Kd - 1;
+          rb[it] = load_piece<T>(W + (size_t)k * N, col0 + (idx % CPR) * V, N);
+        } else {
+          rb[it] = load_piece<T>(brow[it], k0 + ac * V, Kd);
+        }
+      }
+    };
+    auto put = [&](int kt, char* st) {
+      const int k0 = kt * BK;
+      const bool tail = k0 + BK > Kd;
+      const int sw = (ac ^ ((ar >> 1) & 7)) << 4;
+#pragma unroll
+      for (int it = 0; it < NA; ++it) {
+        if (tail) ra[it] = tail_shift<T>(ra[it], k0 + ac * V, Kd);
+        *reinterpret_cast<u32x4*>(st + (ar + 32 * it) * 128 + sw) = ra[it];
+      }
+      char* sb = st + ABYTES;
+#pragma unroll
+      for (int it = 0; it < NB; ++it) {
+        if constexpr (NN) {
+          const int idx = tid + 256 * it;
+          const int k = idx / CPR, c = idx % CPR;
+          if (n_edge) rb[it] = tail_shift<T>(rb[it], col0 + c * V, N);
+          if (tail && k0 + k >= Kd) rb[it] = u32x4{0, 0, 0, 0};
+          const int cs = !B16 ? c : (CPR == 16 ? c ^ ((k & 3) << 2) : c ^ (((k >> 1) & 1) << 2));
+          *reinterpret_cast<u32x4*>(sb + (k * CPR + cs) * 16) = rb[it];
+        } else {
+          if (tail) rb[it] = tail_shift<T>(rb[it], k0 + ac * V, Kd);
+          *reinterpret_cast<u32x4*>(sb + (ar + 32 * it) * 128 + sw) = rb[it];
+        }
+      }
+    };
+    auto compute = [&](const char* st) {
+      const char* sb = st + ABYTES;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const int coff = ((2 * ks + lhi) ^ fsw) << 4;
+        u32x4 af[FM], bfr[FN];
+#pragma unroll
+        for (int i = 0; i < FM; ++i) af[i] = *reinterpret_cast<const u32x4*>(st + a_off + i * 4096 + coff);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          if constexpr (!NN) {
+            bfr[j] = *reinterpret_cast<const u32x4*>(sb + b_off + j * 4096 + coff);
+          } else if constexpr (B16) {
+            const int n = wn * WN + 32 * j + tr_n, kk = 16 * ks + tr_k;
+            const int c = CPR == 16 ? (n >> 3) ^ (kq << 2) : (n >> 3) ^ (((kk >> 1) & 1) << 2);
+            const char* q = sb + (kk * CPR + c) * 16 + (n & 7) * 2;
+            bfr[j] = __builtin_bit_cast(u32x4, lds_read_tr_pair(q, q + 4 * CPR * 16));
+          } else {
+            const float* q = reinterpret_cast<const float*>(sb) + (2 * ks + lhi) * 4 * BN + wn * WN + 32 * j + l32;
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = q[e * BN];
+            bfr[j] = __builtin_bit_cast(u32x4, v);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+          for (int j = 0; j < FN; ++j) mma32(acc[i][j], af[i], bfr[j], T{});
+      }
+    };
+    __syncthreads();   // the previous operand pair's last tile has been read
+    load(t0);
+    put(t0, sm);
+    if (t0 + 1 < t1) load(t0 + 1);
+    __syncthreads();
+    for (int kt = t0; kt < t1; ++kt) {
+      const int s = (kt - t0) & 1;
+      compute(sm + s * (ABYTES + BBYTES));
+      if (kt + 1 < t1) put(kt + 1, sm + (s ^ 1) * (ABYTES + BBYTES));
+      if (kt + 2 < t1) load(kt + 2);
+      __syncthreads();
+    }
+  }
+
+  // LoRA term: with the last part
+  if (part == a.parts - 1) {
+    for (int g = 0; g < NSEG; ++g) {
+      const T* L = static_cast<const T*>(a.L[g]);
+      const int ldz = a.ldz[g];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        RowPiece p = pc[i];
+        if (wm == 1) p = pc[NA / 2 + i];
+        const int task = __builtin_amdgcn_readfirstlane(p.task);
+        if (task < 0) continue;
+        const int r = a.rank[g][task];
+        const T* R = static_cast<const T*>(a.R[g].p[task]);
+        const T* lrow = L + (size_t)(p.row + (l32 < p.n ? l32 : p.n - 1)) * ldz;
+        for (int q0 = 0; q0 < r; q0 += 2 * V) {
+          const int q = q0 + lhi * V;                // q + V <= ldz: ldz is a multiple of 16
+          const u32x4 lf = *reinterpret_cast<const typename Piece16<T>::type*>(lrow + q);
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            int n = col0 + wn * WN + 32 * j + l32;
+            n = n < N ? n : N - 1;
+            union {
+              u32x4 v;
+              T e[V];
+            } rf;
+#pragma unroll
+            for (int e = 0; e < V; ++e)
+              rf.e[e] = q + e < r ? (NN ? R[(size_t)(q + e) * N + n] : R[(size_t)n * r + q + e]) : T(0.f);
+            mma32(acc[i][j], lf, rf.v, T{});
+          }
+        }
+      }
+    }
+  }
+
+  if (a.parts > 1) {
+    float* dst = a.part + ((size_t)part * a.tiles_m * a.tiles_n + (size_t)tm * a.tiles_n + tn) * (BM * BN);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+          *reinterpret_cast<f32x4*>(dst + ((wave * FM + i) * FN + j) * 1024 + g * 256 + lane * 4) =
+              f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+    return;
+  }
+  T* C = static_cast<T*>(a.C);
+#pragma unroll
+  for (int i = 0; i < FM; ++i) {
+    RowPiece p = pc[i];
+    if (wm == 1) p = pc[NA / 2 + i];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) store_frag<T>(acc[i][j], C, N, p, col0 + wn * WN + 32 * j + l32, lhi);
+  }
+}
+
+// Adds the parts of k_gen_gemm in order; block = fragment (i, j) of each of a tile's four waves.
+struct GenReduceArgs {
+  void* C;
+  const float* part;
+  int M, N, tiles_m, tiles_n, parts;
+  int K;
+  int off[kMaxK + 1];
+};
+template <typename T, int BM, int BN>
+__global__ __launch_bounds__(256) void k_gen_reduce(const GenReduceArgs a) {
+  constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int j = blockIdx.x % FN, i = blockIdx.x / FN % FM, tile = blockIdx.x / (FM * FN);
+  const int tm = tile / a.tiles_n, tn = tile % a.tiles_n;
+  const RowPiece p = find_piece(a, (long long)tm * BM + wm * WM + 32 * i);
+  if (p.n <= 0) return;
+  const float* src = a.part + (size_t)tile * (BM * BN) + ((wave * FM + i) * FN + j) * 1024 + lane * 4;
+  const size_t step = (size_t)a.tiles_m * a.tiles_n * (BM * BN);
+  f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+#pragma unroll 2
+  for (int s = 0; s < a.parts; ++s)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(src + s * step + g * 256);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[4 * g + e] += v[e];
+    }
+  store_frag<T>(acc, static_cast<T*>(a.C), a.N, p, tn * BN + wn * WN + 32 * j + (lane & 31), lane >> 5);
+}
+
+// ------------------------------------------------------------------------------------------
+// Out[i, 0:ldz] = s_k * In[i, :] * M_k for the rows i of task k; columns >= r_k are zero.
+//   KMAJOR = true : M_k = A_k [inner, r_k]      KMAJOR = false: M_k = B_k^T, B_k [r_k, inner]
+// Block: 16 RM rows of one task; its NW waves split the contraction (each takes every NW-th run of
+// U x 64 bytes per row, no barrier in the loop) and add their sums through LDS in wave order.  Lanes
+// load MFMA operands straight from memory: a row's 64-byte run is shared by four lanes, and enough
+// waves are resident to keep HBM busy without a ring.  Bound by the activation rows' bytes: fp32,
+// T = 2048, 4096 features, rank 16: 14 us (s x A) and 17 us (s dy B^T) for 34 MB, against 553 and
+// 338 us with one thread per output element.
+// ------------------------------------------------------------------------------------------
+struct GenRowsArgs {
+  const void* In;
+  void* Out;
+  int inner, ldz, K, b0;                 // b0: first block of this launch
+  int off[kMaxK + 1];
+  unsigned char rank[kMaxK];
+  float s[kMaxK];
+  PtrTable M;
+};
+
+template <typename T, int NQ, int RM, int NW, bool KMAJOR>
+__global__ __launch_bounds__(NW * 64) void k_gen_rows(const GenRowsArgs a) {
+  constexpr int V = kV<T>, STEP = 4 * V;             // contraction indices per MFMA group (64 bytes)
+  constexpr int U = NQ <= 1 ? 4 : (NQ <= 2 ? 2 : 1);
+  constexpr int TM = 16 * RM;
+  __shared__ float red[NW * RM * NQ * 256];
+  int b = a.b0 + blockIdx.x, k = 0;
+  for (; k < a.K; ++k) {
+    const int nb = (a.off[k + 1] - a.off[k] + TM - 1) / TM;
+    if (b < nb) break;
+    b -= nb;
+  }
+  if (k >= a.K) return;
+  const int lo = a.off[k] + b * TM;
+  const int hi = a.off[k + 1] < lo + TM ? a.off[k + 1] : lo + TM;
+  const int r = a.rank[k], inner = a.inner;
+  const T* Mk = static_cast<const T*>(a.M.p[k]);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kg = lane >> 4;
+  const int nq = (r + 15) / 16;
+
+  const T* x[RM];
+#pragma unroll
+  for (int i = 0; i < RM; ++i) {
+    const int row = lo + 16 * i + l16;
+    x[i] = static_cast<const T*>(a.In) + (size_t)(row < hi ? row : hi - 1) * inner;
+  }
+  f32x4 acc[RM][NQ];
+#pragma unroll
+  for (int i = 0; i < RM; ++i)
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  union Op {
+    u32x4 v;
+    T e[V];
+  };
+  // operand pieces of contraction indices k0 + kg V ..; `tail`: some lie beyond `inner`
+  auto small = [&](int k0, int j, bool tail) {
+    const int kk = k0 + kg * V;
+    int q = 16 * j + l16;
+    q = q < r ? q : r - 1;                           // columns >= r_k are discarded below
+    Op o;
+    if constexpr (KMAJOR) {
+      const T* p = Mk + (size_t)kk * r + q;
+#pragma unroll
+      for (int e = 0; e < V; ++e) o.e[e] = (!tail || kk + e < inner) ? p[(size_t)e * r] : T(0.f);
+    } else {
+      const T* p = Mk + (size_t)q * inner;
+      o.v = load_piece<T>(p, kk, tail ? inner : kk + V);
+      if (tail) o.v = tail_shift<T>(o.v, kk, inner);
+    }
+    return o.v;
+  };
+  auto big = [&](int k0, int i, bool tail) {
+    const int kk = k0 + kg * V;
+    u32x4 v = load_piece<T>(x[i], kk, tail ? inner : kk + V);
+    if (tail) v = tail_shift<T>(v, kk, inner);
+    return v;
+  };
+
+  const int full = inner / (U * STEP);               // runs that need no masks
+  for (int run = wave; run < full; run += NW) {
+    const int k0 = run * U * STEP;
+    u32x4 xf[U][RM], sf[U][NQ];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int i = 0; i < RM; ++i) xf[u][i] = big(k0 + u * STEP, i, false);
+#pragma unroll
+      for (int j = 0; j < NQ; ++j)
+        if (j < nq) sf[u][j] = small(k0 + u * STEP, j, false);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < NQ; ++j)
+        if (j < nq) {
+#pragma unroll
+          for (int i = 0; i < RM; ++i) mma16(acc[i][j], xf[u][i], sf[u][j], T{});
+        }
+  }
+  // what is left of the contraction, in single groups
+  for (int k0 = full * U * STEP + wave * STEP; k0 < inner; k0 += NW * STEP) {
+    u32x4 xf[RM];
+#pragma unroll
+    for (int i = 0; i < RM; ++i) xf[i] = big(k0, i, true);
+#pragma unroll
+    for (int j = 0; j < NQ; ++j)
+      if (j < nq) {
+        const u32x4 sv = small(k0, j, true);
+#pragma unroll
+        for (int i = 0; i < RM; ++i) mma16(acc[i][j], xf[i], sv, T{});
+      }
+  }
+
+  // acc[i][j]: lane holds column q = 16 j + l16 and rows 16 i + 4 kg + e
+#pragma unroll
+  for (int i = 0; i < RM; ++i)
+#pragma unroll
+    for (int j = 0; j < NQ; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[((wave * RM + i) * NQ + j) * 256 + (4 * kg + e) * 16 + l16] = acc[i][j][e];
+  __syncthreads();
+  const float s = a.s[k];
+  T* Out = static_cast<T*>(a.Out);
+  for (int t = tid; t < RM * NQ * 256; t += NW * 64) {
+    float sum = red[t];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) sum += red[w * RM * NQ * 256 + t];
+    const int ij = t >> 8, i = ij / NQ, j = ij % NQ;
+    const int row = lo + 16 * i + ((t >> 4) & 15), q = 16 * j + (t & 15);
+    if (row < hi && q < a.ldz) Out[(size_t)row * a.ldz + q] = from_f32<T>(q < r ? sum * s : 0.f);
+  }
+}
+
+// ------------------------------------------------------------------------------------------
+// Gradients, contraction over a task's tokens:
+//   WIDE_FIRST = true : out_k[c, q] (+)= sum_t Big[t, c] * Small[t, q]   (dA_k = x_k^T G)
+//   WIDE_FIRST = false: out_k[q, c] (+)= sum_t Small[t, q] * Big[t, c]   (dB_k = Z^T dy_k)
+// A wave owns 64 columns of Big as four MFMA fragments of 16: lane i of 16 carries columns
+// 4 i .. 4 i + 3, one for each fragment, so that it loads (and, for dB, stores) them as one piece.
+// splits > 1: a task's tokens are cut into ranges of whole MFMA groups, one block each, whose sums go
+// to `part` ([range][sum of r_k][wide]) for grad_reduce to add in order.  fp32, T = 2048, 4 tasks, 4096
+// columns, rank 16: 13-14 us + 5 us of reduction for 34 MB, against 131 us with a serial sum per
+// output element.
+// ------------------------------------------------------------------------------------------
+struct GenGradArgs {
+  const void* Big;
+  const void* Small;
+  int wide, ldz, K, accumulate, chunks, splits, rtotal;
+  float* part;
+  int off[kMaxK + 1];
+  unsigned char rank[kMaxK];
+  OutTable out;
+};
+
+template <typename T, int NQ, bool WIDE_FIRST>
+__global__ __launch_bounds__(256) void k_gen_grad(const GenGradArgs a) {
+  constexpr int GT = sizeof(T) == 2 ? 32 : 4;        // tokens per MFMA
+  constexpr int TE = GT / 4;                         // ... of which a lane carries TE
+  const int wide = a.wide;
+  const int ch = blockIdx.x % a.chunks;
+  const int sp = blockIdx.x / a.chunks % a.splits;
+  const int k = blockIdx.x / (a.chunks * a.splits);
+  int lo = a.off[k], hi = a.off[k + 1];
+  if (a.splits > 1) {
+    const int len = ((hi - lo + a.splits - 1) / a.splits + 31) / 32 * 32;
+    lo = lo + sp * len < hi ? lo + sp * len : hi;
+    hi = lo + len < hi ? lo + len : hi;
+  }
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kg = lane >> 4;
+  const int c0 = (ch * 4 + wave) * 64;
+  if (c0 >= wide) return;
+  const int r = a.rank[k], nq = (r + 15) / 16;
+  const int col = c0 + 4 * l16;
+  // a piece of four columns that crosses the end is loaded so that it ends there (wide >= 4) and
+  // read with `cs` positions of shift
+  const int cb = wide >= 4 ? (col < wide - 4 ? col : wide - 4) : 0;
+  const int cs = col - cb;
+  const T* Big = static_cast<const T*>(a.Big);
+  const T* Small = static_cast<const T*>(a.Small);
+
+  f32x4 acc[4][NQ];
+#pragma unroll
+  for (int f = 0; f < 4; ++f)
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) acc[f][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  typedef T Vec4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+  const T zero = T(0.f);
+  auto group = [&](int t0, bool tail) {
+    T bv[4][TE], sv[NQ][TE];
+#pragma unroll
+    for (int e = 0; e < TE; ++e) {
+      const int t = t0 + kg * TE + e;
+      const bool in = !tail || t < hi;
+      const T* row = Big + (size_t)(in ? t : hi - 1) * wide;
+      if (wide >= 4) {
+        const Vec4 v = *reinterpret_cast<const Vec4*>(row + cb);
+#pragma unroll
+        for (int f = 0; f < 4; ++f) bv[f][e] = in ? v[f] : zero;
+        if (cs > 0) {                                // columns beyond `wide` are discarded: no fill needed
+          const T w1 = bv[1][e], w2 = bv[2][e], w3 = bv[3][e];
+          bv[0][e] = cs == 1 ? w1 : (cs == 2 ? w2 : w3);
+          bv[1][e] = cs == 1 ? w2 : w3;
+          bv[2][e] = w3;
+        }
+      } else {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) bv[f][e] = (in && col + f < wide) ? row[col + f] : zero;
+      }
+      const T* srow = Small + (size_t)(in ? t : hi - 1) * a.ldz;
+#pragma unroll
+      for (int j = 0; j < NQ; ++j)
+        if (j < nq) sv[j][e] = in ? srow[16 * j + l16] : zero;
+    }
+#pragma unroll
+    for (int j = 0; j < NQ; ++j)
+      if (j < nq) {
+#pragma unroll
+        for (int f = 0; f < 4; ++f) {
+          if constexpr (sizeof(T) == 2) {
+            bf16x8 b8, s8;
+#pragma unroll
+            for (int e = 0; e < TE; ++e) {
+              b8[e] = bv[f][e];
+              s8[e] = sv[j][e];
+            }
+            acc[f][j] = WIDE_FIRST ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b8, s8, acc[f][j], 0, 0, 0)
+                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(s8, b8, acc[f][j], 0, 0, 0);
+          } else {
+            acc[f][j] = WIDE_FIRST ? __builtin_amdgcn_mfma_f32_16x16x4f32(bv[f][0], sv[j][0], acc[f][j], 0, 0, 0)
+                                   : __builtin_amdgcn_mfma_f32_16x16x4f32(sv[j][0], bv[f][0], acc[f][j], 0, 0, 0);
+          }
+        }
+      }
+  };
+  int t = lo;
+  if constexpr (sizeof(T) == 4) {
+    // eight groups' loads in flight at a time
+    for (; t + 8 * GT <= hi; t += 8 * GT) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) group(t + u * GT, false);
+    }
+  }
+  for (; t + GT <= hi; t += GT) group(t, false);
+  if (t < hi) group(t, true);
+
+  float* o = a.out.p[k];
+  int accumulate = a.accumulate;
+  if (a.splits > 1) {
+    int rbase = 0;
+    for (int kk = 0; kk < k; ++kk) rbase += a.rank[kk];
+    o = a.part + ((size_t)sp * a.rtotal + rbase) * wide;
+    accumulate = 0;
+  }
+#pragma unroll
+  for (int j = 0; j < NQ; ++j) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+#pragma unroll
+      for (int f = 0; f < 4; ++f) {
+        // WIDE_FIRST: lane holds q = 16 j + l16 and the columns carried by lane i = 4 kg + e
+        const int c = WIDE_FIRST ? c0 + 4 * (4 * kg + e) + f : col + f;
+        const int q = WIDE_FIRST ? 16 * j + l16 : 16 * j + 4 * kg + e;
+        if (q < r && c < wide) {
+          float* dst = WIDE_FIRST ? o + (size_t)c * r + q : o + (size_t)q * wide + c;
+          *dst = accumulate ? *dst + acc[f][j][e] : acc[f][j][e];
+        }
+      }
+    }
+  }
+}
+
+int row_blocks(const SegTable& st, int tm) {
+  int blocks = 0;
+  for (int k = 0; k < st.K; ++k) blocks += (st.off[k + 1] - st.off[k] + tm - 1) / tm;
+  return blocks;
+}
+
+template <typename T, int NQ, bool KMAJOR>
+void launch_rows(GenRowsArgs& a, const SegTable& st, hipStream_t s) {
+  // 32 rows per block halve the fetches of the small operand once that still leaves two blocks
+  // for every CU
+  const bool two = row_blocks(st, 32) >= 512;
+  const int blocks = row_blocks(st, two ? 32 : 16);
+  constexpr int most = 1 << 22;          // a launch holds fewer than 2^32 threads
+  for (a.b0 = 0; a.b0 < blocks; a.b0 += most) {
+    const dim3 grid((unsigned)(blocks - a.b0 < most ? blocks - a.b0 : most));
+    if (two)
+      hipLaunchKernelGGL((k_gen_rows<T, NQ, 2, NQ <= 4 ? 8 : 4, KMAJOR>), grid, dim3(NQ <= 4 ? 512 : 256), 0, s, a);
+    else
+      hipLaunchKernelGGL((k_gen_rows<T, NQ, 1, 8, KMAJOR>), grid, dim3(512), 0, s, a);
+  }
+}
+
+template <typename T, bool KMAJOR>
+hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const PtrTable& M) {
+  if (c.K == 0 || c.T == 0 || row_blocks(c.st, 16) == 0) return hipSuccess;
+  GenRowsArgs a;
+  a.In = In;
+  a.Out = Out;
+  a.inner = inner;
+  a.ldz = c.ldz;
+  a.K = c.K;
+  for (int k = 0; k <= kMaxK; ++k) a.off[k] = c.st.off[k];
+  for (int k = 0; k < kMaxK; ++k) {
+    a.rank[k] = (unsigned char)c.st.rank[k];
+    a.s[k] = c.st.s[k];
+  }
+  a.M = M;
+  if (c.ldz <= 16) launch_rows<T, 1, KMAJOR>(a, c.st, c.stream);
+  else if (c.ldz <= 32) launch_rows<T, 2, KMAJOR>(a, c.st, c.stream);
+  else if (c.ldz <= 64) launch_rows<T, 4, KMAJOR>(a, c.st, c.stream);
+  else launch_rows<T, 8, KMAJOR>(a, c.st, c.stream);
+  return hipGetLastError();
+}
+
+// rows of the virtual row axis
+long long virtual_rows(const SegTable& st, int M) {
+  long long mv = 0;
+  int prev = 0;
+  for (int r = 0; r < st.K + 2; ++r) {
+    const int b1 = r <= st.K ? st.off[r] : M;
+    mv += (b1 - prev + 31) / 32 * 32;
+    prev = b1;
+  }
+  return mv;
+}
+
+// Tile size and contraction parts of one base product.  128 x 128 tiles once they give every CU a
+// block; below that 64 x 64, and the contraction cut into parts of at least 16 tiles until the
+// blocks fill two thirds of the chip's 512 block slots or the scratch is used up.
+struct GemmPlan {
+  bool small;
+  int tiles_m, tiles_n, parts;
+  size_t part_bytes;
+};
+GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dtype, size_t scratch_limit) {
+  const long long mv = virtual_rows(st, M);
+  GemmPlan p;
+  const long long t128 = ((mv + 127) / 128) * ((N + 127) / 128);
+  p.small = t128 < 256;
+  const int b = p.small ? 64 : 128;
+  p.tiles_m = (int)((mv + b - 1) / b);
+  p.tiles_n = (N + b - 1) / b;
+  p.parts = 1;
+  const size_t tile_bytes = (size_t)p.tiles_m * p.tiles_n * b * b * 4;
+  if (p.small) {
+    const long long kt = Kd_total / (dtype == MLORA_F32 ? 32 : 64);
+    while (p.parts < 16 && (long long)p.tiles_m * p.tiles_n * p.parts < 340 && kt / (p.parts + 1) >= 16 &&
+           tile_bytes * (p.parts + 1) <= scratch_limit)
+      ++p.parts;
+  }
+  p.part_bytes = p.parts > 1 ? align_up(tile_bytes * p.parts, 256) : 0;
+  return p;
+}
+
+template <typename T, bool NN, int NSEG>
+hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch, hipStream_t s) {
+  a.tiles_m = pl.tiles_m;
+  a.tiles_n = pl.tiles_n;
+  a.parts = pl.parts;
+  a.part = scratch;
+  const dim3 grid((unsigned)(pl.tiles_m * pl.tiles_n * pl.parts));
+  if (pl.small)
+    hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG>), grid, dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_gen_gemm<T, 128, 128, NN, NSEG>), grid, dim3(256), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || pl.parts == 1) return e;
+  GenReduceArgs r;
+  r.C = a.C;
+  r.part = scratch;
+  r.M = a.M;
+  r.N = a.N;
+  r.tiles_m = a.tiles_m;
+  r.tiles_n = a.tiles_n;
+  r.parts = a.parts;
+  r.K = a.K;
+  for (int k = 0; k <= kMaxK; ++k) r.off[k] = a.off[k];
+  hipLaunchKernelGGL((k_gen_reduce<T, 64, 64>), dim3((unsigned)(pl.tiles_m * pl.tiles_n)), dim3(256), 0, s, r);
+  return hipGetLastError();
+}
+
+template <int NSEG>
+hipError_t gemm_n(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st, float* scratch,
+                  size_t scratch_bytes, hipStream_t s) {
+  GenGemmArgs<NSEG> a;
+  a.C = C;
+  a.M = M;
+  a.N = N;
+  a.K = st.K;
+  for (int k = 0; k <= kMaxK; ++k) a.off[k] = st.off[k];
+  long long kd = 0;
+  for (int g = 0; g < NSEG; ++g) {
+    const GenOperands& o = ops[g < n ? g : 0];
+    a.A[g] = o.A;
+    a.W[g] = o.W;
+    a.L[g] = o.L;
+    a.Kd[g] = g < n ? o.Kd : 0;
+    a.ldz[g] = o.ldz;
+    for (int k = 0; k < kMaxK; ++k) a.rank[g][k] = (unsigned char)(g < n && k < st.K ? o.rank[k] : 0);
+    a.R[g] = *o.R;
+    kd += a.Kd[g];
+  }
+  const GemmPlan pl = plan_gemm(st, M, N, kd, dtype, scratch != nullptr ? scratch_bytes : 0);
+  const bool f32 = dtype == MLORA_F32;
+  if (!nn) return f32 ? launch_gemm<float, false, NSEG>(a, pl, scratch, s) : launch_gemm<bf16, false, NSEG>(a, pl, scratch, s);
+  if constexpr (NSEG == 1)
+    return f32 ? launch_gemm<float, true, 1>(a, pl, scratch, s) : launch_gemm<bf16, true, 1>(a, pl, scratch, s);
+  return hipErrorInvalidValue;   // only input gradients are summed over projections
+}
+
+// Token ranges per task: about four blocks per CU, at least 64 tokens each, as far as the scratch goes
+int gen_grad_splits(const SegTable& st, int wide, size_t scratch_limit) {
+  const int blocks = st.K * ((wide + 255) / 256);
+  if (st.K == 0) return 1;
+  int longest = 0;
+  size_t rtotal = 0;
+  for (int k = 0; k < st.K; ++k) {
+    longest = st.off[k + 1] - st.off[k] > longest ? st.off[k + 1] - st.off[k] : longest;
+    rtotal += st.rank[k];
+  }
+  int s = (1024 + blocks - 1) / blocks;
+  s = s < 16 ? s : 16;
+  s = s < longest / 64 ? s : longest / 64;
+  while (s > 1 && (size_t)s * rtotal * wide * sizeof(float) > scratch_limit) --s;
+  return s > 1 ? s : 1;
+}
+
+size_t gen_grad_bytes(const SegTable& st, int wide, size_t scratch_limit) {
+  const int s = gen_grad_splits(st, wide, scratch_limit);
+  if (s <= 1) return 0;
+  size_t rtotal = 0;
+  for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
+  return align_up((size_t)s * rtotal * wide * sizeof(float), 256);
+}
+
+template <typename T, bool WIDE_FIRST>
+void launch_grad(const GenGradArgs& a, int ldz, int blocks, hipStream_t s) {
+  if (ldz <= 16) hipLaunchKernelGGL((k_gen_grad<T, 1, WIDE_FIRST>), dim3(blocks), dim3(256), 0, s, a);
+  else if (ldz <= 32) hipLaunchKernelGGL((k_gen_grad<T, 2, WIDE_FIRST>), dim3(blocks), dim3(256), 0, s, a);
+  else if (ldz <= 64) hipLaunchKernelGGL((k_gen_grad<T, 4, WIDE_FIRST>), dim3(blocks), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_gen_grad<T, 8, WIDE_FIRST>), dim3(blocks), dim3(256), 0, s, a);
+}
+
+hipError_t grad_any(const CallCtx& c, const void* Big, int wide, const void* Small, const OutTable& out, int accumulate,
+                    bool wide_first, float* scratch, size_t scratch_bytes) {
+  if (c.K == 0) return hipSuccess;
+  GenGradArgs a;
+  a.Big = Big;
+  a.Small = Small;
+  a.wide = wide;
+  a.ldz = c.ldz;
+  a.K = c.K;
+  a.accumulate = accumulate;
+  a.chunks = (wide + 255) / 256;
+  a.splits = gen_grad_splits(c.st, wide, scratch != nullptr ? scratch_bytes : 0);
+  a.rtotal = 0;
+  for (int k = 0; k < c.K; ++k) a.rtotal += c.st.rank[k];
+  a.part = scratch;
+  for (int k = 0; k <= kMaxK; ++k) a.off[k] = c.st.off[k];
+  for (int k = 0; k < kMaxK; ++k) a.rank[k] = (unsigned char)c.st.rank[k];
+  a.out = out;
+  const int blocks = c.K * a.chunks * a.splits;
+  if (c.dtype == MLORA_F32) {
+    if (wide_first) launch_grad<float, true>(a, c.ldz, blocks, c.stream);
+    else launch_grad<float, false>(a, c.ldz, blocks, c.stream);
+  } else {
+    if (wide_first) launch_grad<bf16, true>(a, c.ldz, blocks, c.stream);
+    else launch_grad<bf16, false>(a, c.ldz, blocks, c.stream);
+  }
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.splits == 1) return e;
+  return grad_reduce(c.st, scratch, a.splits, wide, out, accumulate, c.stream);
+}
+
+}  // namespace
+
+size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype, size_t limit) {
+  size_t b = 0;
+  auto most = [&](size_t v) { b = v > b ? v : b; };
+  most(gen_grad_bytes(st, h, limit));
+  most(gen_grad_bytes(st, d, limit));
+  most(plan_gemm(st, T, d, h, dtype, limit).part_bytes);
+  most(plan_gemm(st, T, h, d, dtype, limit).part_bytes);
+  return b;
+}
+
+hipError_t general_Z(const CallCtx& c, const void* X, void* Z) {
+  return c.dtype == MLORA_F32 ? rows_t<float, true>(c, X, c.h, Z, c.A) : rows_t<bf16, true>(c, X, c.h, Z, c.A);
+}
+
+hipError_t general_G(const CallCtx& c, const void* dY, void* G) {
+  return c.dtype == MLORA_F32 ? rows_t<float, false>(c, dY, c.d, G, c.B) : rows_t<bf16, false>(c, dY, c.d, G, c.B);
+}
+
+hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st,
+                        float* scratch, size_t scratch_bytes, hipStream_t stream) {
+  if (M <= 0) return hipSuccess;
+  if (n < 1 || n > MLORA_MAX_GROUP) return hipErrorInvalidValue;
+  return n == 1 ? gemm_n<1>(n, ops, dtype, C, M, N, nn, st, scratch, scratch_bytes, stream)
+                : gemm_n<MLORA_MAX_GROUP>(n, ops, dtype, C, M, N, nn, st, scratch, scratch_bytes, stream);
+}
+
+hipError_t general_dB(const CallCtx& c, const void* Z, const void* dY, const OutTable& dB, int accumulate, float* scratch,
+                      size_t scratch_bytes) {
+  return grad_any(c, dY, c.d, Z, dB, accumulate, false, scratch, scratch_bytes);
+}
+
+hipError_t general_dA(const CallCtx& c, const void* X, const void* G, const OutTable& dA, int accumulate, float* scratch,
+                      size_t scratch_bytes) {
+  return grad_any(c, X, c.h, G, dA, accumulate, true, scratch, scratch_bytes);
+}
+
+}  // namespace mlora

@@ -915,22 +915,28 @@ hipError_t grad_mfma(const CallCtx& c, const bf16* Big, int wide, const bf16* Sm
   hipError_t e =
       wide_first ? launch_grad<true, 1>(a, nq, blocks, c.stream) : launch_grad<false, 1>(a, nq, blocks, c.stream);
   if (e != hipSuccess || a.splits == 1) return e;
-  ReduceArgs r;
-  r.part = partial;
-  r.splits = a.splits;
-  r.rtotal = a.rtotal;
-  r.wide = wide;
-  r.K = c.K;
-  r.accumulate = accumulate;
-  for (int k = 0; k < kMaxK; ++k) r.rank[k] = (unsigned char)c.st.rank[k];
-  r.out = out;
-  const size_t total = (size_t)a.rtotal * wide;
   // timed with the gradient kernels (its time counts, the launch adds no algorithmic bytes)
   const int slot = profile_begin(kProfileGrad, 0.0, c.stream);
-  hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, c.stream, r);
-  e = hipGetLastError();
+  e = grad_reduce(c.st, partial, a.splits, wide, out, accumulate, c.stream);
   profile_end(slot, c.stream);
   return e;
+}
+
+hipError_t grad_reduce(const SegTable& st, const float* partial, int splits, int wide, const OutTable& out, int accumulate,
+                       hipStream_t stream) {
+  ReduceArgs r;
+  r.part = partial;
+  r.splits = splits;
+  r.rtotal = 0;
+  for (int k = 0; k < st.K; ++k) r.rtotal += st.rank[k];
+  r.wide = wide;
+  r.K = st.K;
+  r.accumulate = accumulate;
+  for (int k = 0; k < kMaxK; ++k) r.rank[k] = (unsigned char)st.rank[k];
+  r.out = out;
+  const size_t total = (size_t)r.rtotal * wide;
+  hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, r);
+  return hipGetLastError();
 }
 
 // Whether np projections whose widest low-rank row stride is max_ldz fit the shared-input kernels

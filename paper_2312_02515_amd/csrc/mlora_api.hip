@@ -107,7 +107,7 @@ bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 
 
 // The MFMA kernels take bf16 problems whose feature sizes are multiples of 64, whose ranks are
 // multiples of 8 (mfma_sizes_ok) and whose buffers are 16-byte aligned; everything else runs the
-// generic kernels.
+// general kernels.
 bool mfma_sizes_ok(const mlora_problem* p) {
   if (p->dtype != MLORA_BF16 || p->T < 1) return false;
   if (!gemm_mfma_ok((int)p->T, (int)p->d, (int)p->h) || !gemm_mfma_ok((int)p->T, (int)p->h, (int)p->d)) return false;
@@ -126,14 +126,32 @@ bool mfma_shapes_ok(const mlora_problem* p) {
 bool mfma_gemm_applies(const mlora_problem* p) { return !(g_kernel_path.load() & 1) && mfma_shapes_ok(p); }
 bool mfma_lowrank_applies(const mlora_problem* p) { return !(g_kernel_path.load() & 2) && mfma_shapes_ok(p); }
 
-// Scratch for the token-split form of the gradient kernels (0 when they do not split).  A
-// function of the sizes alone: a size query must not change its answer with the addresses.
-size_t grad_scratch_bytes(const mlora_problem* p) {
-  if (!mfma_sizes_ok(p) || p->K == 0) return 0;
+// Scratch behind the low-rank intermediates: partial sums of token-split gradient launches and
+// partial tiles of contraction-split base products (0 when nothing splits).  A function of the
+// sizes alone: a size query must not change its answer with the addresses, so it covers whichever
+// kernels the addresses will allow.  `limit` bounds what the general kernels may ask for: splitting
+// is optional there, and a problem whose intermediates fit the static scratch array has to fit it
+// with its partial sums too.
+struct Scratch {
+  size_t limit, bytes;
+};
+Scratch plan_scratch(const mlora_problem* p, const CallCtx& c) {
+  Scratch s{0, 0};
+  if (p->T < 1) return s;
+  if (mfma_sizes_ok(p) && p->K > 0) {
+    const size_t a = grad_partial_bytes(c.st, c.h), b = grad_partial_bytes(c.st, c.d);
+    s.bytes = a > b ? a : b;
+  }
+  const size_t z = lowrank_bytes(p), fixed = (size_t)MLORA_STATIC_SCRATCH_BYTES;
+  s.limit = z + s.bytes <= fixed ? fixed - z : 2 * fixed;
+  const size_t g = general_scratch_bytes(c.st, c.T, c.h, c.d, c.dtype, s.limit);
+  s.bytes = g > s.bytes ? g : s.bytes;
+  return s;
+}
+size_t scratch_bytes(const mlora_problem* p) {
   CallCtx c;
   fill_ctx(p, nullptr, &c);
-  const size_t a = grad_partial_bytes(c.st, c.h), b = grad_partial_bytes(c.st, c.d);
-  return a > b ? a : b;
+  return plan_scratch(p, c).bytes;
 }
 
 mlora_status hip_status(hipError_t e) {
@@ -146,21 +164,24 @@ mlora_status hip_status(hipError_t e) {
 hipError_t compute_Z(const mlora_problem* p, const CallCtx& c, const void* X, void* Z) {
   if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(Z))
     return lowrank_rows_mfma(c, (const bf16*)X, c.h, (bf16*)Z, c.A, true);
-  return generic_Z(c, X, Z);
+  return general_Z(c, X, Z);
 }
 
 // Y = X W + Z B_k, given Z
-hipError_t forward_gemm(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, const void* Z) {
+hipError_t forward_gemm(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, const void* Z, void* scratch) {
   if (mfma_gemm_applies(p) && aligned16(X) && aligned16(Y) && aligned16(Z))
     return gemm_mfma((const bf16*)X, (const bf16*)p->W, (bf16*)Y, c.T, c.d, c.h, true, (const bf16*)Z, c.ldz, c.st, c.B,
                      c.stream);
-  return generic_gemm_fwd(c, X, Y, Z);
+  const GenOperands o{X, p->W, Z, c.h, c.ldz, c.st.rank, &c.B};
+  const Scratch s = plan_scratch(p, c);
+  return general_gemm(1, &o, c.dtype, Y, c.T, c.d, true, c.st, s.bytes ? static_cast<float*>(scratch) : nullptr, s.limit,
+                      c.stream);
 }
 
-hipError_t forward_impl(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, void* Z) {
+hipError_t forward_impl(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, void* Z, void* scratch) {
   hipError_t e = compute_Z(p, c, X, Z);
   if (e != hipSuccess) return e;
-  return forward_gemm(p, c, X, Y, Z);
+  return forward_gemm(p, c, X, Y, Z, scratch);
 }
 
 mlora_status check_grad_tables(const mlora_problem* p, float* const* dA, float* const* dB) {
@@ -175,37 +196,42 @@ mlora_status check_grad_tables(const mlora_problem* p, float* const* dA, float* 
 // G, dB_k and dA_k, given Z
 // (with `skip_dA` the caller computes dA_k itself from G)
 hipError_t adapter_grads_impl(const mlora_problem* p, const CallCtx& c, const void* X, const void* dY, const void* Z,
-                              void* G, float* const* dA, float* const* dB, int accumulate, float* partial,
+                              void* G, float* const* dA, float* const* dB, int accumulate, void* scratch,
                               bool skip_dA = false) {
   OutTable ta, tb;
   for (int k = 0; k < kMaxK; ++k) {
     ta.p[k] = k < p->K ? dA[k] : nullptr;
     tb.p[k] = k < p->K ? dB[k] : nullptr;
   }
+  const Scratch s = plan_scratch(p, c);
+  float* partial = s.bytes ? static_cast<float*>(scratch) : nullptr;
+  accumulate = accumulate ? 1 : 0;
   hipError_t e;
   if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(dY) && aligned16(Z) && aligned16(G)) {
     e = lowrank_rows_mfma(c, (const bf16*)dY, c.d, (bf16*)G, c.B, false);
-    if (e == hipSuccess) e = grad_mfma(c, (const bf16*)dY, c.d, (const bf16*)Z, tb, accumulate ? 1 : 0, false, partial);
+    if (e == hipSuccess) e = grad_mfma(c, (const bf16*)dY, c.d, (const bf16*)Z, tb, accumulate, false, partial);
     if (e == hipSuccess && !skip_dA)
-      e = grad_mfma(c, (const bf16*)X, c.h, (const bf16*)G, ta, accumulate ? 1 : 0, true, partial);
+      e = grad_mfma(c, (const bf16*)X, c.h, (const bf16*)G, ta, accumulate, true, partial);
   } else {
-    e = generic_G(c, dY, G);
-    if (e == hipSuccess) e = generic_dB(c, Z, dY, tb, accumulate ? 1 : 0);
-    if (e == hipSuccess && !skip_dA) e = generic_dA(c, X, G, ta, accumulate ? 1 : 0);
+    e = general_G(c, dY, G);
+    if (e == hipSuccess) e = general_dB(c, Z, dY, tb, accumulate, partial, s.limit);
+    if (e == hipSuccess && !skip_dA) e = general_dA(c, X, G, ta, accumulate, partial, s.limit);
   }
   return e;
 }
 
 // G, dB_k, dA_k and (unless dX is NULL) dX, given Z
 hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X, const void* dY, const void* Z, void* G,
-                         void* dX, float* const* dA, float* const* dB, int accumulate, float* partial) {
-  hipError_t e = adapter_grads_impl(p, c, X, dY, Z, G, dA, dB, accumulate, partial);
+                         void* dX, float* const* dA, float* const* dB, int accumulate, void* scratch) {
+  hipError_t e = adapter_grads_impl(p, c, X, dY, Z, G, dA, dB, accumulate, scratch);
   if (e == hipSuccess && dX != nullptr && p->T > 0) {
     if (mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G))
-      e = gemm_mfma((const bf16*)dY, (const bf16*)p->W, (bf16*)dX, c.T, c.h, c.d, false, (const bf16*)G, c.ldz, c.st, c.A,
-                    c.stream);
-    else
-      e = generic_gemm_bwd(c, dY, dX, G);
+      return gemm_mfma((const bf16*)dY, (const bf16*)p->W, (bf16*)dX, c.T, c.h, c.d, false, (const bf16*)G, c.ldz, c.st,
+                       c.A, c.stream);
+    const GenOperands o{dY, p->W, G, c.d, c.ldz, c.st.rank, &c.A};
+    const Scratch s = plan_scratch(p, c);
+    e = general_gemm(1, &o, c.dtype, dX, c.T, c.h, false, c.st, s.bytes ? static_cast<float*>(scratch) : nullptr, s.limit,
+                     c.stream);
   }
   return e;
 }
@@ -256,13 +282,13 @@ size_t mlora_lora_saved_bytes(const mlora_problem* p) {
 
 size_t mlora_lora_workspace_bytes(const mlora_problem* p) {
   if (validate(p) != MLORA_OK) return 0;
-  size_t b = lowrank_bytes(p) + grad_scratch_bytes(p);  // G, partial sums of split gradient launches
+  size_t b = lowrank_bytes(p) + scratch_bytes(p);  // G, partial sums of split launches
   return b ? b : 256;
 }
 
 size_t mlora_lora_recompute_workspace_bytes(const mlora_problem* p) {
   if (validate(p) != MLORA_OK) return 0;
-  size_t b = 2 * lowrank_bytes(p) + grad_scratch_bytes(p);  // G, Z, partial sums
+  size_t b = 2 * lowrank_bytes(p) + scratch_bytes(p);  // G, Z, partial sums
   return b ? b : 256;
 }
 
@@ -275,7 +301,7 @@ mlora_status mlora_lora_fwd(const mlora_problem* p, const void* X, void* Y, void
   if (workspace == nullptr || workspace_bytes < mlora_lora_workspace_bytes(p)) return MLORA_ERR_WORKSPACE;
   CallCtx c;
   fill_ctx(p, hip_stream, &c);
-  return hip_status(forward_impl(p, c, X, Y, saved));
+  return hip_status(forward_impl(p, c, X, Y, saved, static_cast<char*>(workspace) + lowrank_bytes(p)));
 }
 
 mlora_status mlora_lora_fwd_nosave(const mlora_problem* p, const void* X, void* Y, void* workspace,
@@ -288,7 +314,7 @@ mlora_status mlora_lora_fwd_nosave(const mlora_problem* p, const void* X, void* 
   CallCtx c;
   fill_ctx(p, hip_stream, &c);
   void* Z = static_cast<char*>(workspace) + lowrank_bytes(p);
-  return hip_status(forward_impl(p, c, X, Y, Z));
+  return hip_status(forward_impl(p, c, X, Y, Z, static_cast<char*>(workspace) + 2 * lowrank_bytes(p)));
 }
 
 mlora_status mlora_lora_bwd(const mlora_problem* p, const void* X, const void* dY, const void* saved, void* dX,
@@ -303,8 +329,8 @@ mlora_status mlora_lora_bwd(const mlora_problem* p, const void* X, const void* d
   if (p->T == 0 && accumulate) return MLORA_OK;
   CallCtx c;
   fill_ctx(p, hip_stream, &c);
-  float* partial = grad_scratch_bytes(p) ? reinterpret_cast<float*>(static_cast<char*>(workspace) + lowrank_bytes(p)) : nullptr;
-  return hip_status(backward_impl(p, c, X, dY, saved, workspace, dX, dA, dB, accumulate, partial));
+  return hip_status(backward_impl(p, c, X, dY, saved, workspace, dX, dA, dB, accumulate,
+                                  static_cast<char*>(workspace) + lowrank_bytes(p)));
 }
 
 mlora_status mlora_lora_bwd_static(const mlora_problem* p, const void* X, const void* dY, const void* saved, void* dX,
@@ -339,9 +365,8 @@ mlora_status mlora_lora_bwd_recompute(const mlora_problem* p, const void* X, con
   void* Z = static_cast<char*>(workspace) + lowrank_bytes(p);
   hipError_t e = p->T > 0 ? compute_Z(p, c, X, Z) : hipSuccess;
   if (e != hipSuccess) return hip_status(e);
-  float* partial =
-      grad_scratch_bytes(p) ? reinterpret_cast<float*>(static_cast<char*>(workspace) + 2 * lowrank_bytes(p)) : nullptr;
-  return hip_status(backward_impl(p, c, X, dY, Z, workspace, dX, dA, dB, accumulate, partial));
+  return hip_status(backward_impl(p, c, X, dY, Z, workspace, dX, dA, dB, accumulate,
+                                  static_cast<char*>(workspace) + 2 * lowrank_bytes(p)));
 }
 
 // ---- 8-bit frozen base weight: decode into the head of the workspace, then the plain path ----
@@ -437,7 +462,7 @@ size_t mlora_lora_group_workspace_bytes(const mlora_problem* const* ps, int P) {
   size_t scratch = 0;
   for (int p = 0; p < P; ++p) {
     b += lowrank_bytes(ps[p]);  // every G_p is live until dX is written
-    const size_t g = grad_scratch_bytes(ps[p]);
+    const size_t g = scratch_bytes(ps[p]);
     scratch = g > scratch ? g : scratch;  // shared: the projections' gradient launches run in turn
   }
   b += scratch;
@@ -468,8 +493,11 @@ mlora_status mlora_lora_group_fwd(const mlora_problem* const* ps, int P, const v
     hipError_t e = lowrank_rows_mfma_group(P, it, c[0].st, (const bf16*)X, c[0].h, c[0].stream);
     if (e != hipSuccess) return hip_status(e);
   }
+  char* scratch = static_cast<char*>(workspace);
+  for (int p = 0; p < P; ++p) scratch += lowrank_bytes(ps[p]);
   for (int p = 0; p < P; ++p) {
-    hipError_t e = fused ? forward_gemm(ps[p], c[p], X, Y[p], saved[p]) : forward_impl(ps[p], c[p], X, Y[p], saved[p]);
+    hipError_t e = fused ? forward_gemm(ps[p], c[p], X, Y[p], saved[p], scratch)
+                         : forward_impl(ps[p], c[p], X, Y[p], saved[p], scratch);
     if (e != hipSuccess) return hip_status(e);
   }
   return MLORA_OK;
@@ -510,9 +538,8 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
   bool fused = ps[0]->K > 0 && group_lowrank_applies(ps, P, X);
   for (int p = 0; p < P; ++p) fused = fused && aligned16(dY[p]) && aligned16(saved[p]) && aligned16(G[p]);
   for (int p = 0; p < P; ++p) {
-    float* partial = grad_scratch_bytes(ps[p]) ? reinterpret_cast<float*>(w) : nullptr;  // behind the last G_p
     hipError_t e = adapter_grads_impl(ps[p], c[p], X, dY[p], saved[p], G[p], ps[0]->K > 0 ? dA[p] : nullptr,
-                                      ps[0]->K > 0 ? dB[p] : nullptr, accumulate, partial, fused);
+                                      ps[0]->K > 0 ? dB[p] : nullptr, accumulate, w, fused);  // w: behind the last G_p
     if (e != hipSuccess) return hip_status(e);
   }
   if (fused) {
@@ -542,7 +569,15 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
     }
     e = gemm_mfma_sum_nt(P, ops, (bf16*)dX, c[0].T, c[0].h, c[0].st, c[0].stream);
   } else {
-    for (int p = 0; p < P && e == hipSuccess; ++p) e = generic_gemm_bwd(c[p], dY[p], dX, G[p], p > 0 ? 1 : 0);
+    GenOperands ops[MLORA_MAX_GROUP];
+    size_t scratch = 0;
+    for (int p = 0; p < P; ++p) {
+      ops[p] = GenOperands{dY[p], ps[p]->W, G[p], c[p].d, c[p].ldz, c[p].st.rank, &c[p].A};
+      const size_t b = scratch_bytes(ps[p]);
+      scratch = b > scratch ? b : scratch;
+    }
+    e = general_gemm(P, ops, c[0].dtype, dX, c[0].T, c[0].h, false, c[0].st, scratch ? reinterpret_cast<float*>(w) : nullptr,
+                     scratch, c[0].stream);
   }
   return hip_status(e);
 }

@@ -33,15 +33,6 @@ struct OutTable {
   float* p[kMaxK];
 };
 
-// Adapter that owns `row`, or -1 for rows outside every segment.
-__device__ __forceinline__ int find_segment(const SegTable& st, int row) {
-  int k = -1;
-  for (int i = 0; i < st.K; ++i) {
-    if (row >= st.off[i] && row < st.off[i + 1]) k = i;
-  }
-  return k;
-}
-
 __device__ __forceinline__ float to_f32(float v) { return v; }
 __device__ __forceinline__ float to_f32(bf16 v) { return static_cast<float>(v); }
 template <typename T> __device__ __forceinline__ T from_f32(float v);
@@ -70,14 +61,29 @@ struct CallCtx {
 };
 
 // ---- launchers (each returns a hipError_t; all work goes to c.stream) ----
-// generic_kernels.hip : any shape, fp32 or bf16 storage, plain VALU arithmetic
-hipError_t generic_Z(const CallCtx& c, const void* X, void* Z);                        // Z = s x A
-hipError_t generic_G(const CallCtx& c, const void* dY, void* G);                       // G = s dy B^T
-hipError_t generic_gemm_fwd(const CallCtx& c, const void* X, void* Y, const void* Z);  // Y = X W + Z B
-// dX (+)= dY W^T + G A^T; with `accumulate` the sum is added to what dX holds (in its storage type)
-hipError_t generic_gemm_bwd(const CallCtx& c, const void* dY, void* dX, const void* G, int accumulate = 0);
-hipError_t generic_dB(const CallCtx& c, const void* Z, const void* dY, const OutTable& dB, int accumulate);
-hipError_t generic_dA(const CallCtx& c, const void* X, const void* G, const OutTable& dA, int accumulate);
+// general_mfma.hip : any shape, rank and alignment, fp32 or bf16 storage
+// Scratch: `scratch` holds at least general_scratch_bytes(.., limit) bytes and `limit` is what is
+// passed as scratch_bytes; NULL = no split launches.
+size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype, size_t limit);
+hipError_t general_Z(const CallCtx& c, const void* X, void* Z);      // Z = s x A
+hipError_t general_G(const CallCtx& c, const void* dY, void* G);     // G = s dy B^T
+// One operand pair of a base product: A [M, Kd], W [Kd, N] (nn) or [N, Kd], L [M, ldz] with
+// R_k [rank[k], N] (nn) or [N, rank[k]].
+struct GenOperands {
+  const void* A;
+  const void* W;
+  const void* L;
+  int Kd, ldz;
+  const int* rank;     // K entries
+  const PtrTable* R;
+};
+// C = sum over the n <= MLORA_MAX_GROUP operand pairs of A op(W) + rows_k(L R_k)
+hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st,
+                        float* scratch, size_t scratch_bytes, hipStream_t stream);
+hipError_t general_dB(const CallCtx& c, const void* Z, const void* dY, const OutTable& dB, int accumulate, float* scratch,
+                      size_t scratch_bytes);
+hipError_t general_dA(const CallCtx& c, const void* X, const void* G, const OutTable& dA, int accumulate, float* scratch,
+                      size_t scratch_bytes);
 
 // gemm_mfma.hip : bf16 MFMA GEMM with the LoRA term as extra contraction steps
 bool gemm_mfma_ok(int M, int N, int Kd);
@@ -114,6 +120,9 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
 // do not fill the chip (the tokens of a task are then split over blocks); NULL = never split.
 int grad_splits(const SegTable& st, int wide);
 size_t grad_partial_bytes(const SegTable& st, int wide);
+// adds `splits` ranges of partial sums ([range][sum of ranks][wide]) in order into the tasks' outputs
+hipError_t grad_reduce(const SegTable& st, const float* partial, int splits, int wide, const OutTable& out, int accumulate,
+                       hipStream_t stream);
 hipError_t grad_mfma(const CallCtx& c, const bf16* Big, int wide, const bf16* Small, const OutTable& out,
                      int accumulate, bool wide_first, float* partial);
 

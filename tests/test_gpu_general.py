@@ -1,0 +1,71 @@
+"""The general kernels (fp32, and bf16 sizes or addresses the aligned kernels do not take) at the
+sizes where their tiles, splits and tails change form, against the CPU fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2312_02515_amd import workloads as wl
+from tests.parity_util import TOL, check_full, run_hip
+from tests.test_gpu_groups import _group_inputs, check_group, run_group
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+
+
+def _inputs(T, h, d, tokens, ranks, dtype, lead=0, seed=0):
+    off = [lead]
+    for t in tokens:
+        off.append(off[-1] + t)
+    assert off[-1] <= T
+    return wl.make_inputs(T, h, d, off, ranks, [0.5 + 0.25 * (k % 4) for k in range(len(ranks))], dtype, device=DEV,
+                          seed=seed, sigma_w=1.0 / np.sqrt(h))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("case", [
+    # T, h, d, tokens, ranks, lead
+    (40, 1, 1, [17, 20], [1, 3], 2),                      # rows of one element
+    (70, 3, 5, [33, 30], [2, 8], 1),                      # rows shorter than one 16-byte piece
+    (33, 8, 4, [33], [128], 0),                           # exactly one piece; 8 column groups of 16
+    (65, 31, 33, [31, 34], [16, 17], 0),                  # one element around the fp32 contraction tile
+    (90, 127, 129, [90], [33], 0),                        # one element around a column tile
+    (100, 2050, 70, [60, 37], [5, 20], 2),                # few tiles, deep: forward split over the contraction
+    (100, 70, 3001, [60, 37], [5, 20], 2),                # the same for the input gradient
+    (2200, 136, 2101, [1000, 0, 1150], [7, 64, 32], 25),  # 128 x 128 tiles, odd stride
+    (16500, 41, 24, [9000, 7000], [4, 40], 300),          # 32 rows per low-rank block
+    (700, 70, 514, [640], [9], 13),                       # token ranges; column groups of 64 that end early
+])
+def test_general_kernel_edges(case, dtype):
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, dtype, lead=lead, seed=71)
+    if h == 1:
+        # every gradient is one sum over tokens, sum_t x_t g_t with g_t rounded to 8 bits: its error is
+        # up to 2^-9 sum |x_t g_t|, which is 2^-9 of the result only where the terms do not cancel
+        inp.X.abs_()
+        inp.dY.abs_()
+    check_full(inp, run_hip(inp), TOL[dtype], label=f"general {case}")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_general_kernels_take_misaligned_buffers(dtype):
+    """Activations and weight one element off a 16-byte boundary: same results as aligned copies."""
+    inp = _inputs(300, 128, 192, [100, 150], [8, 16], dtype, lead=5, seed=72)
+
+    def off_by_one(t):
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)
+        buf[1:].copy_(t.reshape(-1))
+        return buf[1:].view(t.shape)
+
+    inp.X, inp.dY, inp.W = off_by_one(inp.X), off_by_one(inp.dY), off_by_one(inp.W)
+    inp.A, inp.B = [off_by_one(t) for t in inp.A], [off_by_one(t) for t in inp.B]
+    check_full(inp, run_hip(inp), TOL[dtype], label="misaligned")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("ds", [[72, 2051], [35, 130, 900, 1]])
+def test_general_group_sum(ds, dtype):
+    """dX of a group in one launch: operand pairs of unequal depth, split over the contraction."""
+    ranks = [[3, 16 + p] for p in range(len(ds))]
+    ins = _group_inputs(150, 52, ds, [80, 61], ranks, dtype, lead=4, seed=73)
+    check_group(ins, run_group(ins), TOL[dtype], label=f"general group {ds}")
