@@ -238,7 +238,8 @@ int mlora_last_hip_error(void);
  *          MFMA rate in fp32),
  *   bit 1  the low-rank products run the general kernels (3 = general everywhere).
  * The aligned kernels take bf16 problems whose h and d are multiples of 64, whose ranks are
- * multiples of 8 and whose W, A_k, B_k are 16-byte aligned; the answer assumes that the buffers
+ * multiples of 8 and whose W, A_k, B_k are 16-byte aligned (with other ranks such a problem runs
+ * forms of its own of the aligned kernels, a little slower, and reports 3); the answer assumes that the buffers
  * passed to the calls (X, Y, dY, dX, saved, workspace) are 16-byte aligned too, as device
  * allocations are -- a call handed a misaligned buffer falls back for that call.  Returns -1 if
  * the problem is invalid.  Honours mlora_set_kernel_path (mlora_testing.h). */

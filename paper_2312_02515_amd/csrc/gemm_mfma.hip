@@ -35,7 +35,13 @@ template <bool NN, int NSEG>
 hipError_t launch(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
   const dim3 grid(a.tiles_m * a.tiles_n);
   const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
-  hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, NN, NSEG>), grid, dim3(512), 0, stream, a);
+  bool rag = false;
+  if constexpr (!NN) {
+    for (int g = 0; g < NSEG; ++g)
+      for (int k = 0; k < a.K; ++k) rag = rag || a.rank[g][k] % 8 != 0;
+    if (rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, false, NSEG, true>), grid, dim3(512), 0, stream, a);
+  }
+  if (!rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, NN, NSEG, false>), grid, dim3(512), 0, stream, a);
   const hipError_t err = hipGetLastError();
   profile_end(slot, stream);
   return err;

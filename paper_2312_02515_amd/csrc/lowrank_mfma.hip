@@ -38,6 +38,23 @@ __device__ __forceinline__ int swizzled_source(int chunk, int w) {
   return row * w + (((seg << 2) | (pc & 3)) << 3);
 }
 
+// A_k's tile (64 contraction indices x r, contiguous in memory) for ranks that are no multiple of 8:
+// its rows are no whole 16-byte chunks, so it is filled in memory order (chunks beyond it re-fetch
+// the first one) and never swizzled.
+__device__ __forceinline__ int ragged_source(int chunk, int r) {
+  if (r % 8 == 0) return swizzled_source(chunk, r);
+  return 8 * chunk < 64 * r ? 8 * chunk : 0;
+}
+// MFMA operand of column n, contraction indices 8 (lane / 32) .. + 7 of step ks, from a tile with
+// rows of r elements that are no multiple of 8 bytes (r % 4 != 0): element by element
+__device__ __forceinline__ bf16x8 ragged_column(const char* ss, int ks, int j, int r, int lane, int zero_off) {
+  asm volatile("" : "+v"(lane));   // addresses worked out here: hoisted out of the tile loop they fill the register file
+  const int n = 32 * j + (lane & 31), k0 = 16 * ks + 8 * (lane >> 5);
+  bf16x8 v;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = *(const bf16*)(ss + (n < r ? ((k0 + e) * r + n) * 2 : zero_off));
+  return v;
+}
 
 // ------------------------------------------------------------------------------------------
 // Arguments of the two kernels, passed by value.  NP > 1 serves projections that share their
@@ -81,8 +98,9 @@ struct GradArgs {
 //   SMALL_KMAJOR = false: M_k = B_k^T, B_k [r_k, inner]
 // Block: TM rows of one task (TM = 32, 64 or 128), one wave per 32 rows, contraction tiles of 64.
 // NQ = 32-column groups of the widest Out_p.
+// RAG: some rank is no multiple of 8 (k-major operand; B_k's rows are whole chunks for any rank).
 // ------------------------------------------------------------------------------------------
-template <bool SMALL_KMAJOR, int NQ, int NS, int TM, int NP>
+template <bool SMALL_KMAJOR, int NQ, int NS, int TM, int NP, bool RAG>
 __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) {
   constexpr int NWV = TM / 32;                     // waves per block
   constexpr int SPW = (4 * NQ + NWV - 1) / NWV;    // 1 KiB pieces of one small operand per wave
@@ -139,14 +157,14 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
   for (int p = 0; p < NP; ++p) {
     r[p] = ra.rank[p][k];
     const bf16* Mk = static_cast<const bf16*>(ra.M[p].p[k]);
-    const int pieces = r[p] / 8;  // 1 KiB pieces of the small operand's tile
+    const int pieces = (r[p] + 7) / 8;  // 1 KiB pieces of the small operand's tile
 #pragma unroll
     for (int it = 0; it < SPW; ++it) {
       // pieces beyond the operand's rank re-fetch piece 0 into their own (never read) slot, so
       // that every wave issues the same number of loads per tile
       const int piece = (wave + NWV * it) < pieces ? (wave + NWV * it) : 0;
       if (SMALL_KMAJOR) {
-        sptr[p][it] = Mk + swizzled_source(piece * 64 + lane, r[p]);
+        sptr[p][it] = Mk + (RAG ? ragged_source(piece * 64 + lane, r[p]) : swizzled_source(piece * 64 + lane, r[p]));
       } else {
         int q = 8 * piece + (lane >> 3);
         const int c = (lane & 7) ^ ((q >> 1) & 7);
@@ -197,7 +215,9 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
         for (int j = 0; j < NQ; ++j) {
           if (32 * j < r[p]) {
             bf16x8 sf;
-            if (SMALL_KMAJOR) {
+            if (SMALL_KMAJOR && RAG && r[p] % 4 != 0) {
+              sf = ragged_column(ss, ks, j, r[p], lane, SBYTES);
+            } else if (SMALL_KMAJOR) {
               const int n = 32 * j + tr_n;
               const int kk = 16 * ks + tr_k;
               const int ns = n ^ (seg_swizzle(kk, r[p]) << 5);
@@ -271,7 +291,7 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
 // its own loads wrote), then waves 1..3 hand their partial sums to wave 0 through LDS, which adds
 // them in that order (deterministic) and writes the rows.  Ranks up to 64.
 // ------------------------------------------------------------------------------------------
-template <bool SMALL_KMAJOR, int NQ, int NS>
+template <bool SMALL_KMAJOR, int NQ, int NS, bool RAG>
 __global__ __launch_bounds__(256) void k_lowrank_mfma_splitk(const RowsArgs<1> ra) {
   constexpr int TM = 32, NSPLIT = 4;
   constexpr int SBYTES = NQ * 32 * 128;
@@ -314,13 +334,13 @@ __global__ __launch_bounds__(256) void k_lowrank_mfma_splitk(const RowsArgs<1> r
     row = row < hi ? row : hi - 1;
     xptr[it] = In + (size_t)row * inner + c * 8;
   }
-  const int pieces = r / 8;
+  const int pieces = (r + 7) / 8;
   const bf16* sptr[4 * NQ];
 #pragma unroll
   for (int it = 0; it < 4 * NQ; ++it) {
     const int piece = it < pieces ? it : 0;
     if (SMALL_KMAJOR) {
-      sptr[it] = Mk + swizzled_source(piece * 64 + lane, r);
+      sptr[it] = Mk + (RAG ? ragged_source(piece * 64 + lane, r) : swizzled_source(piece * 64 + lane, r));
     } else {
       int q = 8 * piece + (lane >> 3);
       const int c = (lane & 7) ^ ((q >> 1) & 7);
@@ -363,7 +383,9 @@ __global__ __launch_bounds__(256) void k_lowrank_mfma_splitk(const RowsArgs<1> r
       for (int j = 0; j < NQ; ++j) {
         if (32 * j < r) {
           bf16x8 sf;
-          if (SMALL_KMAJOR) {
+          if (SMALL_KMAJOR && RAG && r % 4 != 0) {
+            sf = ragged_column(ss, ks, j, r, lane, SBYTES);
+          } else if (SMALL_KMAJOR) {
             const int n = 32 * j + tr_n;
             const int kk = 16 * ks + tr_k;
             const int ns = n ^ (seg_swizzle(kk, r) << 5);
@@ -737,11 +759,25 @@ double grad_bytes(const GradArgs<NP>& a) {
   return b;
 }
 
+// whether a k-major small operand needs the ragged form
+template <int NP>
+bool ragged_ranks(const RowsArgs<NP>& a) {
+  for (int p = 0; p < NP; ++p)
+    for (int k = 0; k < a.K; ++k)
+      if (a.rank[p][k] % 8 != 0) return true;
+  return false;
+}
+
 template <bool KMAJOR, int NQ, int TM, int NP>
 hipError_t launch_rows_one(const RowsArgs<NP>& a, int blocks, hipStream_t s) {
   if constexpr (NP * NQ <= 8) {
     const int slot = profile_begin(kProfileRows, rows_bytes(a), s);
-    hipLaunchKernelGGL((k_lowrank_mfma<KMAJOR, NQ, kRing, TM, NP>), dim3(blocks), dim3(TM * 2), 0, s, a);
+    bool rag = false;
+    if constexpr (KMAJOR) {
+      rag = ragged_ranks(a);
+      if (rag) hipLaunchKernelGGL((k_lowrank_mfma<true, NQ, kRing, TM, NP, true>), dim3(blocks), dim3(TM * 2), 0, s, a);
+    }
+    if (!rag) hipLaunchKernelGGL((k_lowrank_mfma<KMAJOR, NQ, kRing, TM, NP, false>), dim3(blocks), dim3(TM * 2), 0, s, a);
     const hipError_t e = hipGetLastError();
     profile_end(slot, s);
     return e;
@@ -760,7 +796,12 @@ hipError_t launch_rows_tm(const RowsArgs<NP>& a, int tm, int blocks, hipStream_t
 template <bool KMAJOR, int NQ>
 hipError_t launch_rows_splitk(const RowsArgs<1>& a, int blocks, hipStream_t s) {
   const int slot = profile_begin(kProfileRows, rows_bytes(a), s);
-  hipLaunchKernelGGL((k_lowrank_mfma_splitk<KMAJOR, NQ, kRing>), dim3(blocks), dim3(256), 0, s, a);
+  bool rag = false;
+  if constexpr (KMAJOR) {
+    rag = ragged_ranks(a);
+    if (rag) hipLaunchKernelGGL((k_lowrank_mfma_splitk<true, NQ, kRing, true>), dim3(blocks), dim3(256), 0, s, a);
+  }
+  if (!rag) hipLaunchKernelGGL((k_lowrank_mfma_splitk<KMAJOR, NQ, kRing, false>), dim3(blocks), dim3(256), 0, s, a);
   const hipError_t e = hipGetLastError();
   profile_end(slot, s);
   return e;
@@ -870,8 +911,9 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
 
 // dA_k = x_k^T G (wide_first = true; Big = X [T,h], Small = G) or dB_k = Z^T dy_k (Big = dY [T,d], Small = Z).
 // Token ranges per task for the gradient kernels: 1 when tasks x column blocks fill the chip,
-// otherwise enough ranges for about two blocks per CU (at most 16, at least 256 tokens each).
-int grad_splits(const SegTable& st, int wide) {
+// otherwise enough ranges for about two blocks per CU (at most 16, at least 256 tokens each), as far
+// as their partial sums stay within `limit` bytes.
+int grad_splits(const SegTable& st, int wide, size_t limit) {
   const int blocks = st.K * ((wide + 127) / 128);
   if (st.K == 0 || blocks >= 384) return 1;
   int longest = 0;
@@ -879,12 +921,15 @@ int grad_splits(const SegTable& st, int wide) {
   int s = (512 + blocks - 1) / blocks;
   s = s < 16 ? s : 16;
   s = s < longest / 256 ? s : longest / 256;
+  size_t rtotal = 0;
+  for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
+  while (s > 1 && (size_t)s * rtotal * wide * sizeof(float) > limit) --s;
   return s > 1 ? s : 1;
 }
 
 // Bytes of partial sums grad_mfma needs for an output of `wide` columns (0 when it does not split).
-size_t grad_partial_bytes(const SegTable& st, int wide) {
-  const int s = grad_splits(st, wide);
+size_t grad_partial_bytes(const SegTable& st, int wide, size_t limit) {
+  const int s = grad_splits(st, wide, limit);
   if (s <= 1) return 0;
   size_t rtotal = 0;
   for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
@@ -892,7 +937,7 @@ size_t grad_partial_bytes(const SegTable& st, int wide) {
 }
 
 hipError_t grad_mfma(const CallCtx& c, const bf16* Big, int wide, const bf16* Small, const OutTable& out,
-                     int accumulate, bool wide_first, float* partial) {
+                     int accumulate, bool wide_first, float* partial, size_t limit) {
   if (c.K == 0) return hipSuccess;
   GradArgs<1> a;
   a.Big = Big;
@@ -906,7 +951,7 @@ hipError_t grad_mfma(const CallCtx& c, const bf16* Big, int wide, const bf16* Sm
   a.out[0] = out;
   a.accumulate = accumulate;
   a.chunks = (wide + 127) / 128;
-  a.splits = partial != nullptr ? grad_splits(c.st, wide) : 1;
+  a.splits = partial != nullptr ? grad_splits(c.st, wide, limit) : 1;
   a.rtotal = 0;
   for (int k = 0; k < c.K; ++k) a.rtotal += c.st.rank[k];
   a.part = partial;

@@ -69,3 +69,27 @@ def test_general_group_sum(ds, dtype):
     ranks = [[3, 16 + p] for p in range(len(ds))]
     ins = _group_inputs(150, 52, ds, [80, 61], ranks, dtype, lead=4, seed=73)
     check_group(ins, run_group(ins), TOL[dtype], label=f"general group {ds}")
+
+
+@pytest.mark.parametrize("case", [
+    # T, h, d, tokens, ranks, lead: bf16, h and d multiples of 64, ranks that are no multiple of 8
+    (300, 64, 64, [300], [9], 0),                                  # the LoRA tile right behind one base tile
+    (1000, 192, 320, [100, 0, 333, 500], [7, 24, 127, 66], 7),     # beside whole-chunk ranks; two LoRA tiles
+    (500, 1024, 1088, [77, 200, 223], [3, 20, 30], 0),             # contraction split over a block's waves
+    (500, 1024, 1088, [77, 200, 223], [3, 36, 64], 0),
+    (17000, 64, 128, [9000, 8000], [5, 12], 0),                    # 64-row low-rank blocks
+    (33100, 128, 64, [16500, 16500], [1, 44], 60),                 # 128-row low-rank blocks
+])
+def test_ragged_ranks_on_aligned_shapes(case):
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=74)
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"ragged ranks {case}")
+
+
+@pytest.mark.parametrize("P", [2, 3, 4])
+def test_ragged_ranks_in_a_group(P):
+    ranks = [[5 + p, 12, 8] for p in range(P)]
+    if P == 2:
+        ranks[1] = [100, 33, 64]      # four 32-column groups
+    ins = _group_inputs(420, 128, [64 * (p + 1) for p in range(P)], [90, 201, 100], ranks, torch.bfloat16, lead=6, seed=75)
+    check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"ragged group {P}")
