@@ -432,11 +432,14 @@ __global__ __launch_bounds__(256) void k_gen_reduce(const GenReduceArgs a) {
 // Out[i, 0:ldz] = s_k * In[i, :] * M_k for the rows i of task k; columns >= r_k are zero.
 //   KMAJOR = true : M_k = A_k [inner, r_k]      KMAJOR = false: M_k = B_k^T, B_k [r_k, inner]
 // Block: 16 RM rows of one task; its NW waves split the contraction (each takes every NW-th run of
-// U x 64 bytes per row, no barrier in the loop) and add their sums through LDS in wave order.  Lanes
-// load MFMA operands straight from memory: a row's 64-byte run is shared by four lanes, and enough
-// waves are resident to keep HBM busy without a ring.  Bound by the activation rows' bytes: fp32,
-// T = 2048, 4096 features, rank 16: 14 us (s x A) and 17 us (s dy B^T) for 34 MB, against 553 and
-// 338 us with one thread per output element.
+// U x 64 bytes per row, no barrier in the loop) and add their sums through LDS in a fixed order.
+// Lanes load MFMA operands straight from memory: a row's 64-byte run is shared by four lanes.  Each
+// block runs the body for its own task's rank (VW groups of 16 columns), so that the deepest run a
+// wave keeps in flight does not depend on the largest rank of the call.
+// A_k's columns are contiguous where the MFMA wants contraction indices: lane i of 16 carries
+// columns VW i .. VW i + VW - 1, one for each group, loads them as one piece per contraction index
+// and regroups them in registers; a lane whose columns would cross the rank takes the last VW
+// columns instead (the same sums a second time).
 // ------------------------------------------------------------------------------------------
 struct GenRowsArgs {
   const void* In;
@@ -448,27 +451,18 @@ struct GenRowsArgs {
   PtrTable M;
 };
 
-template <typename T, int NQ, int RM, int NW, bool KMAJOR>
-__global__ __launch_bounds__(NW * 64) void k_gen_rows(const GenRowsArgs a) {
+template <typename T, int VW, int RM, int NW, bool KMAJOR>
+__device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, int hi, float* red) {
   constexpr int V = kV<T>, STEP = 4 * V;             // contraction indices per MFMA group (64 bytes)
-  constexpr int U = NQ <= 1 ? 4 : (NQ <= 2 ? 2 : 1);
-  constexpr int TM = 16 * RM;
-  __shared__ float red[NW * RM * NQ * 256];
-  int b = a.b0 + blockIdx.x, k = 0;
-  for (; k < a.K; ++k) {
-    const int nb = (a.off[k + 1] - a.off[k] + TM - 1) / TM;
-    if (b < nb) break;
-    b -= nb;
-  }
-  if (k >= a.K) return;
-  const int lo = a.off[k] + b * TM;
-  const int hi = a.off[k + 1] < lo + TM ? a.off[k + 1] : lo + TM;
+  constexpr int U = VW <= 2 ? 4 : (VW == 4 ? 2 : 1);
+  typedef T Cols __attribute__((ext_vector_type(VW), aligned(sizeof(T))));
   const int r = a.rank[k], inner = a.inner;
   const T* Mk = static_cast<const T*>(a.M.p[k]);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kg = lane >> 4;
-  const int nq = (r + 15) / 16;
+  auto first_col = [&](int i16) { return VW * i16 < r - VW ? VW * i16 : r - VW; };   // k-major
+  const int q0 = first_col(l16);
 
   const T* x[RM];
 #pragma unroll
@@ -476,32 +470,48 @@ __global__ __launch_bounds__(NW * 64) void k_gen_rows(const GenRowsArgs a) {
     const int row = lo + 16 * i + l16;
     x[i] = static_cast<const T*>(a.In) + (size_t)(row < hi ? row : hi - 1) * inner;
   }
-  f32x4 acc[RM][NQ];
+  f32x4 acc[RM][VW];
 #pragma unroll
   for (int i = 0; i < RM; ++i)
 #pragma unroll
-    for (int j = 0; j < NQ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < VW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  union Op {
-    u32x4 v;
-    T e[V];
-  };
   // operand pieces of contraction indices k0 + kg V ..; `tail`: some lie beyond `inner`
-  auto small = [&](int k0, int j, bool tail) {
+  struct Small {
+    u32x4 v[VW];
+  };
+  auto small = [&](int k0, bool tail) {
     const int kk = k0 + kg * V;
-    int q = 16 * j + l16;
-    q = q < r ? q : r - 1;                           // columns >= r_k are discarded below
-    Op o;
+    Small o;
     if constexpr (KMAJOR) {
-      const T* p = Mk + (size_t)kk * r + q;
+      union {
+        u32x4 v[VW];
+        T e[VW][V];
+      } u;
+      const T* p = Mk + (size_t)kk * r + q0;
 #pragma unroll
-      for (int e = 0; e < V; ++e) o.e[e] = (!tail || kk + e < inner) ? p[(size_t)e * r] : T(0.f);
+      for (int e = 0; e < V; ++e) {
+        Cols c;
+        if (!tail || kk + e < inner) {
+          c = *reinterpret_cast<const Cols*>(p + (size_t)e * r);
+        } else {
+#pragma unroll
+          for (int f = 0; f < VW; ++f) c[f] = T(0.f);
+        }
+#pragma unroll
+        for (int f = 0; f < VW; ++f) u.e[f][e] = c[f];
+      }
+#pragma unroll
+      for (int f = 0; f < VW; ++f) o.v[f] = u.v[f];
     } else {
-      const T* p = Mk + (size_t)q * inner;
-      o.v = load_piece<T>(p, kk, tail ? inner : kk + V);
-      if (tail) o.v = tail_shift<T>(o.v, kk, inner);
+#pragma unroll
+      for (int f = 0; f < VW; ++f) {
+        const int q = 16 * f + l16;
+        o.v[f] = load_piece<T>(Mk + (size_t)(q < r ? q : r - 1) * inner, kk, tail ? inner : kk + V);
+        if (tail) o.v[f] = tail_shift<T>(o.v[f], kk, inner);
+      }
     }
-    return o.v;
+    return o;
   };
   auto big = [&](int k0, int i, bool tail) {
     const int kk = k0 + kg * V;
@@ -513,56 +523,98 @@ __global__ __launch_bounds__(NW * 64) void k_gen_rows(const GenRowsArgs a) {
   const int full = inner / (U * STEP);               // runs that need no masks
   for (int run = wave; run < full; run += NW) {
     const int k0 = run * U * STEP;
-    u32x4 xf[U][RM], sf[U][NQ];
+    u32x4 xf[U][RM];
+    Small sf[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
       for (int i = 0; i < RM; ++i) xf[u][i] = big(k0 + u * STEP, i, false);
-#pragma unroll
-      for (int j = 0; j < NQ; ++j)
-        if (j < nq) sf[u][j] = small(k0 + u * STEP, j, false);
+      sf[u] = small(k0 + u * STEP, false);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int j = 0; j < NQ; ++j)
-        if (j < nq) {
+      for (int j = 0; j < VW; ++j)
 #pragma unroll
-          for (int i = 0; i < RM; ++i) mma16(acc[i][j], xf[u][i], sf[u][j], T{});
-        }
+        for (int i = 0; i < RM; ++i) mma16(acc[i][j], xf[u][i], sf[u].v[j], T{});
   }
   // what is left of the contraction, in single groups
   for (int k0 = full * U * STEP + wave * STEP; k0 < inner; k0 += NW * STEP) {
     u32x4 xf[RM];
 #pragma unroll
     for (int i = 0; i < RM; ++i) xf[i] = big(k0, i, true);
+    const Small sv = small(k0, true);
 #pragma unroll
-    for (int j = 0; j < NQ; ++j)
-      if (j < nq) {
-        const u32x4 sv = small(k0, j, true);
+    for (int j = 0; j < VW; ++j)
 #pragma unroll
-        for (int i = 0; i < RM; ++i) mma16(acc[i][j], xf[i], sv, T{});
-      }
+      for (int i = 0; i < RM; ++i) mma16(acc[i][j], xf[i], sv.v[j], T{});
   }
 
-  // acc[i][j]: lane holds column q = 16 j + l16 and rows 16 i + 4 kg + e
+  // the upper half of the waves hands its sums to the lower half, which adds them and hands on its
+  // own; the block adds those in wave order.  acc[i][j]: lane holds operand column l16 of group j
+  // and rows 16 i + 4 kg + e.
+  constexpr int H = NW / 2, FR = RM * VW * 256;
+  auto slot = [&](int w, int i, int j, int e) -> float& { return red[w * FR + (i * VW + j) * 256 + (4 * kg + e) * 16 + l16]; };
+  if (wave >= H) {
 #pragma unroll
-  for (int i = 0; i < RM; ++i)
+    for (int i = 0; i < RM; ++i)
 #pragma unroll
-    for (int j = 0; j < NQ; ++j)
+      for (int j = 0; j < VW; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) red[((wave * RM + i) * NQ + j) * 256 + (4 * kg + e) * 16 + l16] = acc[i][j][e];
+        for (int e = 0; e < 4; ++e) slot(wave - H, i, j, e) = acc[i][j][e];
+  }
+  __syncthreads();
+  if (wave < H) {
+#pragma unroll
+    for (int i = 0; i < RM; ++i)
+#pragma unroll
+      for (int j = 0; j < VW; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) slot(wave, i, j, e) = acc[i][j][e] + slot(wave, i, j, e);
+  }
   __syncthreads();
   const float s = a.s[k];
   T* Out = static_cast<T*>(a.Out);
-  for (int t = tid; t < RM * NQ * 256; t += NW * 64) {
+  for (int t = tid; t < FR; t += NW * 64) {
     float sum = red[t];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) sum += red[w * RM * NQ * 256 + t];
-    const int ij = t >> 8, i = ij / NQ, j = ij % NQ;
-    const int row = lo + 16 * i + ((t >> 4) & 15), q = 16 * j + (t & 15);
-    if (row < hi && q < a.ldz) Out[(size_t)row * a.ldz + q] = from_f32<T>(q < r ? sum * s : 0.f);
+    for (int w = 1; w < H; ++w) sum += red[w * FR + t];
+    const int ij = t >> 8, i = ij / VW, j = ij % VW, i16 = t & 15;
+    const int row = lo + 16 * i + ((t >> 4) & 15), q = KMAJOR ? first_col(i16) + j : 16 * j + i16;
+    if (row < hi && q < r) Out[(size_t)row * a.ldz + q] = from_f32<T>(sum * s);
   }
+  const int pad = a.ldz - r;
+  if (pad > 0)
+    for (int t = tid; t < (hi - lo) * pad; t += NW * 64) Out[(size_t)(lo + t / pad) * a.ldz + r + t % pad] = T(0.f);
+}
+
+// rows of a block of the low-rank kernels: task and row range of block b when tasks are cut into
+// blocks of TM rows
+template <int TM>
+__device__ __forceinline__ int rows_block(const GenRowsArgs& a, int b, int* lo, int* hi) {
+  for (int k = 0; k < a.K; ++k) {
+    const int nb = (a.off[k + 1] - a.off[k] + TM - 1) / TM;
+    if (b < nb) {
+      *lo = a.off[k] + b * TM;
+      *hi = a.off[k + 1] < *lo + TM ? a.off[k + 1] : *lo + TM;
+      return k;
+    }
+    b -= nb;
+  }
+  return -1;
+}
+
+template <typename T, int RM, int NW, bool KMAJOR>
+__global__ __launch_bounds__(NW * 64, 4) void k_gen_rows(const GenRowsArgs a) {
+  extern __shared__ float red[];         // NW / 2 x RM x (groups of the largest rank) KiB
+  int lo = 0, hi = 0;
+  const int k = rows_block<16 * RM>(a, a.b0 + blockIdx.x, &lo, &hi);
+  if (k < 0) return;
+  const int r = a.rank[k];
+  if (r <= 16) rows_body<T, 1, RM, NW, KMAJOR>(a, k, lo, hi, red);
+  else if (r <= 32) rows_body<T, 2, RM, NW, KMAJOR>(a, k, lo, hi, red);
+  else if (r <= 64) rows_body<T, 4, RM, NW, KMAJOR>(a, k, lo, hi, red);
+  else if constexpr (RM == 1) rows_body<T, 8, RM, NW, KMAJOR>(a, k, lo, hi, red);   // (two row groups: ranks up to 64)
 }
 
 // ------------------------------------------------------------------------------------------
@@ -712,22 +764,6 @@ int row_blocks(const SegTable& st, int tm) {
   return blocks;
 }
 
-template <typename T, int NQ, bool KMAJOR>
-void launch_rows(GenRowsArgs& a, const SegTable& st, hipStream_t s) {
-  // 32 rows per block halve the fetches of the small operand once that still leaves two blocks
-  // for every CU
-  const bool two = row_blocks(st, 32) >= 512;
-  const int blocks = row_blocks(st, two ? 32 : 16);
-  constexpr int most = 1 << 22;          // a launch holds fewer than 2^32 threads
-  for (a.b0 = 0; a.b0 < blocks; a.b0 += most) {
-    const dim3 grid((unsigned)(blocks - a.b0 < most ? blocks - a.b0 : most));
-    if (two)
-      hipLaunchKernelGGL((k_gen_rows<T, NQ, 2, NQ <= 4 ? 8 : 4, KMAJOR>), grid, dim3(NQ <= 4 ? 512 : 256), 0, s, a);
-    else
-      hipLaunchKernelGGL((k_gen_rows<T, NQ, 1, 8, KMAJOR>), grid, dim3(512), 0, s, a);
-  }
-}
-
 template <typename T, bool KMAJOR>
 hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const PtrTable& M) {
   if (c.K == 0 || c.T == 0 || row_blocks(c.st, 16) == 0) return hipSuccess;
@@ -743,10 +779,18 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
     a.s[k] = c.st.s[k];
   }
   a.M = M;
-  if (c.ldz <= 16) launch_rows<T, 1, KMAJOR>(a, c.st, c.stream);
-  else if (c.ldz <= 32) launch_rows<T, 2, KMAJOR>(a, c.st, c.stream);
-  else if (c.ldz <= 64) launch_rows<T, 4, KMAJOR>(a, c.st, c.stream);
-  else launch_rows<T, 8, KMAJOR>(a, c.st, c.stream);
+  // 32 rows per block halve the fetches of the small operand once that still leaves two blocks
+  // for every CU (ranks above 64 leave no registers for it)
+  const bool two = c.ldz <= 64 && row_blocks(c.st, 32) >= 512;
+  const int blocks = row_blocks(c.st, two ? 32 : 16);
+  const int groups = c.ldz <= 16 ? 1 : (c.ldz <= 32 ? 2 : (c.ldz <= 64 ? 4 : 8));
+  const unsigned lds = 4 * (two ? 2 : 1) * groups * 1024;
+  constexpr int most = 1 << 22;          // a launch holds fewer than 2^32 threads
+  for (a.b0 = 0; a.b0 < blocks; a.b0 += most) {
+    const dim3 grid((unsigned)(blocks - a.b0 < most ? blocks - a.b0 : most));
+    if (two) hipLaunchKernelGGL((k_gen_rows<T, 2, 8, KMAJOR>), grid, dim3(512), lds, c.stream, a);
+    else hipLaunchKernelGGL((k_gen_rows<T, 1, 8, KMAJOR>), grid, dim3(512), lds, c.stream, a);
+  }
   return hipGetLastError();
 }
 
