@@ -13,7 +13,7 @@
 namespace mlora {
 namespace {
 
-constexpr int BM = gemmk::BM, BN = gemmk::BN;
+constexpr int BM = 256, BN = gemmk::BN;
 
 }  // namespace
 
@@ -31,20 +31,99 @@ double algorithmic_flops(const gemmk::GemmArgs<NSEG>& a) {
   return f;
 }
 
+template <int NSEG>
+bool ragged_ranks(const gemmk::GemmArgs<NSEG>& a) {
+  for (int g = 0; g < NSEG; ++g)
+    for (int k = 0; k < a.K; ++k)
+      if (a.rank[g][k] % 8 != 0) return true;
+  return false;
+}
+
+// tiles [0, tiles) of 256 x 256
 template <bool NN, int NSEG>
-hipError_t launch(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
-  const dim3 grid(a.tiles_m * a.tiles_n);
-  const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
+void launch_whole(const gemmk::GemmArgs<NSEG>& a, int tiles, hipStream_t stream) {
+  if constexpr (!NN) {
+    if (ragged_ranks(a)) {
+      hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, false, NSEG, true>), dim3(tiles), dim3(512), 0, stream, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, NN, NSEG, false>), dim3(tiles), dim3(512), 0, stream, a);
+}
+
+// tiles [a.t0, total) as halves of 128 x 256, their contraction in a.parts ranges
+template <bool NN>
+void launch_halves(const gemmk::GemmArgs<1>& a, hipStream_t stream) {
+  const int units = 2 * (a.tiles_m * a.tiles_n - a.t0);
+  const dim3 grid(units * a.parts);
   bool rag = false;
   if constexpr (!NN) {
-    for (int g = 0; g < NSEG; ++g)
-      for (int k = 0; k < a.K; ++k) rag = rag || a.rank[g][k] % 8 != 0;
-    if (rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, false, NSEG, true>), grid, dim3(512), 0, stream, a);
+    rag = ragged_ranks(a);
+    if (rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, false, 1, true>), grid, dim3(256), 0, stream, a);
   }
-  if (!rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, NN, NSEG, false>), grid, dim3(512), 0, stream, a);
-  const hipError_t err = hipGetLastError();
-  profile_end(slot, stream);
-  return err;
+  if (!rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, 1, false>), grid, dim3(256), 0, stream, a);
+  if (a.parts == 1) return;
+  gemmk::ReduceArgs r;
+  r.C = a.C;
+  r.part = a.part;
+  r.M = a.M;
+  r.N = a.N;
+  r.tiles_m = a.tiles_m;
+  r.tiles_n = a.tiles_n;
+  r.t0 = a.t0;
+  r.parts = a.parts;
+  r.K = a.K;
+  for (int k = 0; k <= kMaxK; ++k) r.off[k] = a.off[k];
+  hipLaunchKernelGGL(gemmk::k_gemm_reduce, dim3(units * 8), dim3(256), 0, stream, r);
+}
+
+// rows of the virtual axis the grid tiles: every row range of the call (before the first task, each
+// task, after the last task) rounded up to whole 32-row MFMA fragments
+long long virtual_rows(const SegTable& st, int M) {
+  long long mv = 0;
+  int prev = 0;
+  for (int r = 0; r < st.K + 2; ++r) {
+    const int b1 = r <= st.K ? st.off[r] : M;
+    mv += (b1 - prev + 31) / 32 * 32;
+    prev = b1;
+  }
+  return mv;
+}
+
+// How a product is cut into launches: tiles [0, whole) as 256 x 256 tiles, a multiple of 256 so that
+// every round fills the chip, the others as halves of them with the contraction in `parts` ranges.
+// A launch takes a round of blocks per 256 blocks; the plan with the smallest estimate wins.  The
+// estimates are measured per block and contraction tile of 64 (us): whole tile 10 + 1.3 KT, half tile
+// 12 + 0.78 KT, reduction 4 + 1 per 7 MB of partial tiles.  Before (whole tiles only) and after:
+//   T = 100,   4096 x 4096   (16 tiles)        87 ->  28 us with 7 ranges
+//   T = 771,   2048 -> 5632  (88 tiles)        50 ->  38 us as halves
+//              its input gradient (32 tiles)  103 ->  42 us as halves, 3 ranges
+//   T = 2048,  11008-deep input gradient (128 tiles) 207 -> 165 us as halves
+//   T = 2048,  4096 -> 11008 (344 tiles)      191 -> 171 us, one whole round and halves
+//   T = 16448, 11008-deep input gradient (1040 tiles) 1227 -> 1090 us, four whole rounds and halves
+//   T = 3072,  4096 x 4096   (192 tiles): halves would take 125 us instead of 93.
+struct Plan {
+  int whole, parts;
+  size_t part_bytes;
+};
+Plan plan_gemm(const SegTable& st, int M, int N, int Kd, size_t scratch_limit) {
+  const int tiles_m = (int)((virtual_rows(st, M) + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
+  const int total = tiles_m * tiles_n, q = total / 256 * 256, halves = 2 * (total - q);
+  const int KT = Kd / 64;
+  auto whole_us = [&](int tiles) { return (double)((tiles + 255) / 256) * (10.0 + 1.3 * KT); };
+  Plan best{total, 1, 0};
+  double best_us = whole_us(total);
+  for (int parts = 1; halves > 0 && parts <= 16 && parts <= KT; ++parts) {
+    const size_t bytes = parts > 1 ? (size_t)halves * parts * (BM / 2) * BN * sizeof(float) : 0;
+    if (bytes > scratch_limit) break;
+    const double us = whole_us(q) + (double)((halves * parts + 255) / 256) * (12.0 + 0.78 * ((KT + parts - 1) / parts)) +
+                      (parts > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
+    if (us < best_us) {
+      best_us = us;
+      best = Plan{q, parts, bytes};
+    }
+  }
+  return best;
 }
 
 template <int NSEG>
@@ -55,16 +134,10 @@ void fill_common(gemmk::GemmArgs<NSEG>* a, bf16* C, int M, int N, const SegTable
   a->tiles_n = (N + BN - 1) / BN;
   a->K = st.K;
   for (int k = 0; k <= kMaxK; ++k) a->off[k] = st.off[k];
-  // rows of the virtual axis the grid tiles: every row range of the call (before the first
-  // task, each task, after the last task) rounded up to whole 32-row MFMA fragments
-  long long mv = 0;
-  int prev = 0;
-  for (int r = 0; r < st.K + 2; ++r) {
-    const int b1 = r <= st.K ? st.off[r] : M;
-    mv += (b1 - prev + 31) / 32 * 32;
-    prev = b1;
-  }
-  a->tiles_m = (int)((mv + BM - 1) / BM);
+  a->tiles_m = (int)((virtual_rows(st, M) + BM - 1) / BM);
+  a->t0 = 0;
+  a->parts = 1;
+  a->part = nullptr;
 }
 
 template <int NSEG>
@@ -80,14 +153,18 @@ hipError_t launch_sum(const GemmOperands* ops, bf16* C, int M, int N, const SegT
     for (int k = 0; k < kMaxK; ++k) a.rank[g][k] = (unsigned char)(k < st.K ? ops[g].rank[k] : 0);
     a.R[g] = *ops[g].R;
   }
-  return launch<false, NSEG>(a, stream);
+  const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
+  launch_whole<false, NSEG>(a, a.tiles_m * a.tiles_n, stream);
+  const hipError_t err = hipGetLastError();
+  profile_end(slot, stream);
+  return err;
 }
 
 }  // namespace
 
 // C[M,N] = A[M,Kd] * (nn ? Bm[Kd,N] : Bm[N,Kd]^T) + rows_k( L[rows_k, :r_k] * (nn ? R_k[r_k,N] : R_k[N,r_k]^T) )
 hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, bool nn, const bf16* L, int ldz,
-                     const SegTable& st, const PtrTable& R, hipStream_t stream) {
+                     const SegTable& st, const PtrTable& R, float* scratch, size_t scratch_bytes, hipStream_t stream) {
   gemmk::GemmArgs<1> a;
   fill_common(&a, C, M, N, st);
   a.A[0] = A;
@@ -97,7 +174,20 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
   a.ldz[0] = ldz;
   for (int k = 0; k < kMaxK; ++k) a.rank[0][k] = (unsigned char)(k < st.K ? st.rank[k] : 0);
   a.R[0] = R;
-  return nn ? launch<true, 1>(a, stream) : launch<false, 1>(a, stream);
+  const Plan pl = plan_gemm(st, M, N, Kd, scratch != nullptr ? scratch_bytes : 0);
+  a.t0 = pl.whole;
+  a.parts = pl.parts;
+  a.part = scratch;
+  const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
+  if (pl.whole > 0) nn ? launch_whole<true, 1>(a, pl.whole, stream) : launch_whole<false, 1>(a, pl.whole, stream);
+  if (pl.whole < a.tiles_m * a.tiles_n) nn ? launch_halves<true>(a, stream) : launch_halves<false>(a, stream);
+  const hipError_t err = hipGetLastError();
+  profile_end(slot, stream);
+  return err;
+}
+
+size_t gemm_partial_bytes(const SegTable& st, int M, int N, int Kd, size_t scratch_limit) {
+  return plan_gemm(st, M, N, Kd, scratch_limit).part_bytes;
 }
 
 // C[M,N] = sum_g ( A_g[M,Kd_g] * Bm_g[N,Kd_g]^T + rows_k( L_g[rows_k, :r_gk] * R_gk[N,r_gk]^T ) ), 1 <= n <= 4

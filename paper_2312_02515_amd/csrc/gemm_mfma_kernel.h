@@ -62,7 +62,7 @@ namespace gemmk {
 
 using namespace stage;
 
-constexpr int BM = 256, BN = 256;
+constexpr int BN = 256;   // columns of a tile; its rows: 128 x WAVES_M
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // Kernel arguments (passed by value, read with scalar loads).  The contraction may run over
@@ -73,7 +73,9 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 template <int NSEG>
 struct GemmArgs {
   bf16* C;
-  int M, N, tiles_m, tiles_n;            // tiles_m counts tiles of the virtual row axis
+  int M, N, tiles_m, tiles_n;            // tiles_m counts 256-row tiles of the virtual row axis
+  int t0, parts;                         // HALF: first tile of the launch, contraction ranges per tile
+  float* part;                           // HALF: partial tiles in fp32 when parts > 1
   int K;                                 // tasks
   int off[kMaxK + 1];                    // split positions (rows of C)
   const bf16* A[NSEG];                   // [M, Kd_g]
@@ -100,6 +102,12 @@ __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const b
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
+// WAVES_M = 1 (HALF): 128 x 256 tiles of 4 waves for grids that leave the chip idle: the halves of the
+// tiles that do not fill a round of 256 blocks, their contraction cut into ranges where even those
+// are too few (fp32 partial tiles, added in order by k_gemm_reduce).  Such blocks are short, and what
+// they spend outside the contraction loop counts: the loop is not unrolled (47 KB of code, fetched
+// once, cost 10 us of a block's time) and the LoRA term is added from registers instead of by LoRA
+// tiles in the pipeline (T = 100, 4096 x 4096, 8 ranges: 33 us -> 22 us).
 // RAG (backward layout): some rank is no multiple of 8, so A_k's rows [N, r] are no whole 16-byte
 // chunks; such a task's LoRA tile is put together in registers, element by element (at most two of
 // a block's contraction tiles per task).  B_k [r, N] has whole chunks for any rank.  12 tasks of 256
@@ -108,6 +116,9 @@ __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const b
 template <int WAVES_M, int WAVES_N, bool NN, int NSEG, bool RAG>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmArgs<NSEG> ga) {
   constexpr int BK = 64;
+  constexpr int BM = 128 * WAVES_M;
+  constexpr bool HALF = WAVES_M == 1;
+  static_assert(!HALF || NSEG == 1, "the summed contraction runs whole tiles");
   bf16* __restrict__ C = ga.C;
   const int M = ga.M, N = ga.N, tiles_m = ga.tiles_m, tiles_n = ga.tiles_n;
   constexpr int NW = WAVES_M * WAVES_N;
@@ -116,9 +127,10 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   constexpr int HM = FM / 2;                   // row fragments per sub-step
   constexpr int NMF = HM * FN;                 // MFMAs per sub-step
   constexpr int ROWB = BK * 2, CPR = BK / 8, RW = 256 / ROWB, RPI = 1024 / ROWB;
-  constexpr int TILE_BYTES = BM * ROWB;        // the NN weight tile (BK x 512 B) has the same size
-  constexpr int LPW = TILE_BYTES / 1024 / NW;  // wave-wide loads per wave per operand tile
-  constexpr int PER_TILE = 2 * LPW;
+  constexpr int ABYTES = BM * ROWB, BBYTES = BN * ROWB;   // the NN weight tile (BK x 512 B) has BBYTES too
+  constexpr int LPA = ABYTES / 1024 / NW;      // wave-wide loads per wave and tile: A side,
+  constexpr int LPB = BBYTES / 1024 / NW;      // Bm side
+  constexpr int PER_TILE = LPA + LPB;
   static_assert(WM == 128, "the sub-steps halve a 128-row wave tile");
 
   // Three stages for the A side, two for the Bm side: all 160 KiB of the CU's LDS.  The rows of
@@ -126,11 +138,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // cold line takes longer than the one contraction tile a two-stage ring gives it, and every
   // block that shares the strip waits for it together.  With the third stage the A loads run two
   // tiles ahead of their use, the Bm loads one.
-  __shared__ __attribute__((aligned(1024))) char sA0[TILE_BYTES];
-  __shared__ __attribute__((aligned(1024))) char sA1[TILE_BYTES];
-  __shared__ __attribute__((aligned(1024))) char sA2[TILE_BYTES];
-  __shared__ __attribute__((aligned(1024))) char sB0[TILE_BYTES];
-  __shared__ __attribute__((aligned(1024))) char sB1[TILE_BYTES];
+  __shared__ __attribute__((aligned(1024))) char sA0[ABYTES];
+  __shared__ __attribute__((aligned(1024))) char sA1[ABYTES];
+  __shared__ __attribute__((aligned(1024))) char sA2[ABYTES];
+  __shared__ __attribute__((aligned(1024))) char sB0[BBYTES];
+  __shared__ __attribute__((aligned(1024))) char sB1[BBYTES];
   char* const sA[3] = {sA0, sA1, sA2};
   char* const sB[2] = {sB0, sB1};
 
@@ -147,8 +159,16 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // The tiles beyond the last full round of 256 are taken in block order.
   const int total = tiles_m * tiles_n;
   const int bid = blockIdx.x;
-  int t = bid;
-  if (bid < (total / 256) * 256) {
+  int t = bid, part = 0, half = 0;
+  if constexpr (HALF) {
+    // the upper and the lower half of the tiles from t0 on, range by range of the contraction; an
+    // XCD takes a contiguous eighth of that order
+    const int units = 2 * (total - ga.t0), per = units * ga.parts / 8;
+    const int u = bid < 8 * per ? (bid % 8) * per + bid / 8 : bid;
+    part = u / units;
+    t = ga.t0 + (u % units) / 2;
+    half = u % 2;
+  } else if (bid < (total / 256) * 256) {
     const int xcd = bid % 8, local = bid / 8;
     t = 256 * (local / 32) + 32 * xcd + (local % 32);
   }
@@ -158,7 +178,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   const int first_m = group * GM;
   const int gm = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
   const int in_g = t - group * gsize;
-  const int tm = first_m + in_g % gm, tn = in_g / gm;
+  const int tm256 = first_m + in_g % gm, tn = in_g / gm;
+  const int tm = HALF ? 2 * tm256 + half : tm256;
   const int col0 = tn * BN;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -197,6 +218,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   auto frag_n = [&](int f) { return tab(1, f); };
   auto frag_task = [&](int f) { return tab(2, f); };
   const int row0 = frag_row(0);  // the block's lowest real row
+  if constexpr (HALF) {
+    if (frag_n(0) == 0) return;  // the last row tile's lower half may be empty
+  }
   // real row behind row rl (0..255) of the block's tile; the 8 rows of one wave-wide load lie in
   // one piece, so f is wave-uniform there
   auto real_row = [&](int rl) {
@@ -210,21 +234,22 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // operand pair by set_operands()
   const char* abase = nullptr;
   const char* bbase = nullptr;
-  unsigned aoff[LPW], boff[LPW];
+  unsigned aoff[LPA], boff[LPB];
   size_t bstep = 0;  // bytes per contraction tile of Bm
   auto nn_swz = [](int kr) { return ((kr & 3) << 2) | (((kr >> 3) & 1) << 1); };
   auto set_operands = [&](const bf16* A, const bf16* Bm, int Kd) {
     abase = reinterpret_cast<const char*>(A + (size_t)row0 * Kd);
     bbase = NN ? reinterpret_cast<const char*>(Bm + col0) : reinterpret_cast<const char*>(Bm + (size_t)col0 * Kd);
 #pragma unroll
-    for (int it = 0; it < LPW; ++it) {
+    for (int it = 0; it < LPA; ++it) {
+      const int rl = RPI * (wave + NW * it) + lane / CPR;
+      const int c = (lane % CPR) ^ ((rl / RW) % CPR);
+      const int gr = real_row(rl);
+      aoff[it] = (unsigned)(((size_t)(gr - row0) * Kd + c * 8) * 2);
+    }
+#pragma unroll
+    for (int it = 0; it < LPB; ++it) {
       const int w = wave + NW * it;
-      {
-        const int rl = RPI * w + lane / CPR;
-        const int c = (lane % CPR) ^ ((rl / RW) % CPR);
-        const int gr = real_row(rl);
-        aoff[it] = (unsigned)(((size_t)(gr - row0) * Kd + c * 8) * 2);
-      }
       if (NN) {
         const int kr = 2 * w + (lane >> 5);
         const int c = (lane & 31) ^ nn_swz(kr);
@@ -290,11 +315,12 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     int sg, k, q0;
   };
   int n_lora = 0;
-  for (int sg = 0; sg < NSEG; ++sg)
-    for (int f = 0; f < NFR; ++f) {
-      const int k = frag_task(f);
-      if (k >= 0 && (f == 0 || frag_task(f - 1) != k)) n_lora += (ga.rank[sg][k] + BK - 1) / BK;
-    }
+  if constexpr (!HALF)
+    for (int sg = 0; sg < NSEG; ++sg)
+      for (int f = 0; f < NFR; ++f) {
+        const int k = frag_task(f);
+        if (k >= 0 && (f == 0 || frag_task(f - 1) != k)) n_lora += (ga.rank[sg][k] + BK - 1) / BK;
+      }
   auto find_lora = [&](int e) {
     LoraTile t{0, -1, 0};
     for (int sg = 0; sg < NSEG; ++sg)
@@ -318,17 +344,17 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     return LoadCtx{false, abase + (size_t)kt * (BK * 2), bbase + (size_t)kt * bstep, LoraTile{0, -1, 0}};
   };
   const char* const zeros = reinterpret_cast<const char*>(&g_zero_chunk);
-  // wave-wide load number idx (0..LPW-1: A side, LPW..PER_TILE-1: Bm side) of the tile `lc` describes
+  // wave-wide load number idx (0..LPA-1: A side, LPA..PER_TILE-1: Bm side) of the tile `lc` describes
   auto issue_one = [&](const LoadCtx& lc, int idx, char* sa, char* sb) {
-    if (!lc.lora) {
-      if (idx < LPW)
+    if (HALF || !lc.lora) {
+      if (idx < LPA)
         load_lds_16B_sbase(lc.atile, aoff[idx], sa + (wave + NW * idx) * 1024);
       else
-        load_lds_16B_sbase(lc.btile, boff[idx - LPW], sb + (wave + NW * (idx - LPW)) * 1024);
+        load_lds_16B_sbase(lc.btile, boff[idx - LPA], sb + (wave + NW * (idx - LPA)) * 1024);
       return;
     }
     const LoraTile& t = lc.lt;
-    if (idx < LPW) {
+    if (idx < LPA) {
       const bf16* L = ga.L[t.sg];
       const int ldz = ga.ldz[t.sg];
       const int w = wave + NW * idx;
@@ -341,7 +367,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     } else {
       const int r = ga.rank[t.sg][t.k];
       const bf16* Rk = static_cast<const bf16*>(ga.R[t.sg].p[t.k]);
-      const int w = wave + NW * (idx - LPW);
+      const int w = wave + NW * (idx - LPA);
       const char* p = zeros;
       if (NN) {
         const int kr = 2 * w + (lane >> 5);
@@ -402,7 +428,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     constexpr int q = S / 2, h = S % 2;
     constexpr int NS_ = (S + 1) % 4;                 // the sub-step whose row fragments are read now
     constexpr int nq = NS_ / 2, nh = NS_ % 2;
-    static_assert((FN - 1) * (HM - 1) >= PER_TILE, "load slots");
+    // slots of the PER_TILE loads: behind the MFMAs of weight fragments 1 .. FN - 1 that carry no
+    // fragment read, or behind all of them where those are too few
+    constexpr bool SHARED = (FN - 1) * (HM - 1) < PER_TILE;
+    constexpr int SPF = SHARED ? HM : HM - 1;        // slots per weight fragment
+    static_assert((FN - 1) * SPF >= PER_TILE, "load slots");
 #pragma unroll
     for (int m = 0; m < NMF; ++m) {
       const int j = m / HM, i = m % HM;
@@ -411,11 +441,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       if (on) mfma_16x16x32(acc[h * HM + i][j], bfr[j], af[h][i]);
       if (rd && m < HM) read_a(rsa, nq, nh, m, af[nh]);
       if (rd && h == 1 && i == HM - 1) read_b(rsb, nq, j);
-      if (S == 3 && m >= HM && i != HM - 1) {
+      if (S == 3 && m >= HM && i < SPF) {
         // the Bm side first: the next barrier waits for it and lets the A loads behind it fly on
-        const int idx = (j - 1) * (HM - 1) + i;
-        if (ldb && idx < LPW) issue_one(lcb, LPW + idx, nullptr, lsb);
-        if (lda && idx >= LPW && idx < PER_TILE) issue_one(lca, idx - LPW, lsa, nullptr);
+        const int idx = (j - 1) * SPF + i;
+        if (ldb && idx < LPB) issue_one(lcb, LPA + idx, nullptr, lsb);
+        if (lda && idx >= LPB && idx < PER_TILE) issue_one(lca, idx - LPB, lsa, nullptr);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -432,7 +462,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // the next tile's first fragments from (na, nb) (if rd), the Bm loads of the tile after that,
   // `lcb`, into cb (if ldb) and the A loads of the tile after that one, `lca`, into ca (if lda).
   // `abehind`: whether A loads were issued behind the Bm loads the barrier waits for (the
-  // previous tile's lda) -- vector loads return in order, so the wait leaves exactly those LPW
+  // previous tile's lda) -- vector loads return in order, so the wait leaves exactly those LPA
   // loads in flight.
   auto tile = [&](char* ca, char* cb, const char* na, const char* nb, auto rd, auto ldb, const LoadCtx& lcb, auto lda,
                   const LoadCtx& lca, auto abehind, const auto& fo) {
@@ -442,7 +472,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     // the next tile has landed (this wave's part), every fragment of this tile is in registers
     // (the weight fragments of this half tile stay in use until sub-step 3 re-reads them)
     if (abehind)
-      wait_vmcnt<LPW>();
+      wait_vmcnt<LPA>();
     else
       wait_vmcnt<0>();
     wait_lds();
@@ -456,19 +486,27 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // fragments in registers, so all stages are free for the next pair's first tiles.
   for (int sg = 0; sg < NSEG; ++sg) {
     set_operands(ga.A[sg], ga.Bm[sg], ga.Kd[sg]);
-    const int KT = ga.Kd[sg] / BK;
-    const int VT = KT + (sg == NSEG - 1 ? n_lora : 0);  // tiles of this pass: base tiles, then LoRA tiles
+    int KT = ga.Kd[sg] / BK;
+    const int lora_tiles = !HALF && sg == NSEG - 1 ? n_lora : 0;
+    if constexpr (HALF) {
+      // this block's range of the base tiles (at least one)
+      const int k0 = (int)((long long)KT * part / ga.parts), k1 = (int)((long long)KT * (part + 1) / ga.parts);
+      abase += (size_t)k0 * (BK * 2);
+      bbase += (size_t)k0 * bstep;
+      KT = k1 - k0;
+    }
+    const int VT = KT + lora_tiles;  // tiles of this pass: base tiles, then LoRA tiles
     auto ctx_of = [&](int v) {
-      if (v < KT) return base_ctx(v);
+      if (HALF || v < KT) return base_ctx(v);
       return LoadCtx{true, nullptr, nullptr, find_lora(v - KT)};
     };
     auto issue_a = [&](const LoadCtx& lc, char* sa) {
 #pragma unroll
-      for (int idx = 0; idx < LPW; ++idx) issue_one(lc, idx, sa, nullptr);
+      for (int idx = 0; idx < LPA; ++idx) issue_one(lc, idx, sa, nullptr);
     };
     auto issue_b = [&](const LoadCtx& lc, char* sb) {
 #pragma unroll
-      for (int idx = 0; idx < LPW; ++idx) issue_one(lc, LPW + idx, nullptr, sb);
+      for (int idx = 0; idx < LPB; ++idx) issue_one(lc, LPA + idx, nullptr, sb);
     };
     // tiles 0 and 1 whole and the A side of tile 2; the first reads need tile 0
     issue_a(base_ctx(0), sA[0]);
@@ -477,11 +515,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       issue_a(ctx_of(1), sA[1]);
       issue_b(ctx_of(1), sB[1]);
       issue_a(ctx_of(2), sA[2]);
-      wait_vmcnt<3 * LPW>();
+      wait_vmcnt<2 * LPA + LPB>();
     } else if (VT > 1) {
       issue_a(ctx_of(1), sA[1]);
       issue_b(ctx_of(1), sB[1]);
-      wait_vmcnt<2 * LPW>();
+      wait_vmcnt<LPA + LPB>();
     } else {
       wait_vmcnt<0>();
     }
@@ -494,7 +532,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     // steady state, six base tiles per trip: each has a successor to read, a base tile two ahead
     // for its Bm loads and one three ahead for its A loads
     int v = 0;
-    for (; v + 8 < KT; v += 6) {
+    // (A half tile's short contraction is not worth fetching six copies of the loop's code.)
+    for (; !HALF && v + 8 < KT; v += 6) {
       tile(sA[0], sB[0], sA[1], sB[1], yes, yes, base_ctx(v + 2), yes, base_ctx(v + 3), yes, yes);
       tile(sA[1], sB[1], sA[2], sB[0], yes, yes, base_ctx(v + 3), yes, base_ctx(v + 4), yes, yes);
       tile(sA[2], sB[0], sA[0], sB[1], yes, yes, base_ctx(v + 4), yes, base_ctx(v + 5), yes, yes);
@@ -508,6 +547,12 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     auto stage_b = [&](int u) { return u % 2 == 0 ? sB0 : sB1; };
     for (; v + 3 < KT; ++v)
       tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), yes, yes, base_ctx(v + 2), yes, base_ctx(v + 3), yes, yes);
+    if constexpr (HALF) {
+      for (; v < VT; ++v)
+        tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, base_ctx(v + 2), v + 3 < VT,
+             base_ctx(v + 3), v + 2 < VT, yes);
+      break;
+    }
     // the last base tiles and the LoRA tiles
     auto frags_at = [&](int u) { return u < KT ? frags_of(LoraTile{0, -1, 0}, true) : frags_of(find_lora(u - KT), false); };
     for (; v < VT; ++v) {
@@ -516,6 +561,66 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     }
   }  // operand pairs
 
+  // the accumulators were last written by MFMAs in inline assembly: wait states before other
+  // instructions read them
+  asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+  // ---- HALF: the LoRA term, from registers, with the last range.  Fragments straight from memory (a few
+  // KB per block that the caches hold): lane 16 kg + r16 loads 8 ranks of row r16 of L, and of output
+  // column r16 of R_k, which is kept while the pieces belong to the same task.
+  if constexpr (HALF) {
+    if (part == ga.parts - 1) {
+      const bf16* L = ga.L[0];
+      const int ldz = ga.ldz[0];
+      for (int q0 = 0; q0 < ldz; q0 += 32) {
+        int held = -1;
+#pragma unroll
+        for (int f = 0; f < NFR; ++f) {
+          const int k = frag_task(f);
+          if (k < 0) continue;
+          const int r = ga.rank[0][k];
+          if (q0 >= r) continue;
+          const int q = q0 + 8 * kg;
+          if (k != held) {
+            held = k;
+            const bf16* Rk = static_cast<const bf16*>(ga.R[0].p[k]);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+              int n = col0 + wn * WN + 16 * j + r16;
+              n = n < N ? n : N - 1;
+#pragma unroll
+              for (int e = 0; e < 8; ++e)
+                bfr[j][e] = q + e < r ? Rk[NN ? (size_t)(q + e) * N + n : (size_t)n * r + q + e] : (bf16)0.f;
+            }
+          }
+          const int n = frag_n(f);
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            const int o = 16 * i + r16;
+            bf16x8 lf;
+            if (q < ldz) {
+              lf = *(const bf16x8*)(L + (size_t)(frag_row(f) + (o < n ? o : n - 1)) * ldz + q);
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) lf[e] = (bf16)0.f;
+            }
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[2 * f + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], lf, acc[2 * f + i][j], 0, 0, 0);
+          }
+        }
+      }
+    }
+  }
+  if constexpr (HALF) {
+    if (ga.parts > 1) {
+      // fp32 partial tile, one KiB per fragment in lane order (k_gemm_reduce reads it back the same way)
+      float* dst = ga.part + ((size_t)part * 2 * (total - ga.t0) + 2 * (t - ga.t0) + half) * (BM * BN) + lane * 4;
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) *(f32x4*)(dst + ((i * WAVES_N + wave) * FN + j) * 256) = acc[i][j];
+      return;
+    }
+  }
   // ---- output: through LDS, so that the tile leaves as 16 B per lane in full row segments of
   // the wave's sub-tile.  Each wave owns WM x WN x 2 bytes of the stage arrays (row stride WN x 2
   // bytes, chunk c of row m at c ^ swizzle(m)); nothing is shared between waves after the barrier.
@@ -523,15 +628,16 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   constexpr int OROWB = WN * 2;               // bytes per such row
   constexpr int ORPI = 64 / OCH;              // rows per wave-wide store
   constexpr int WBYTES = WM * OROWB;          // bytes per wave
-  static_assert(NW * WBYTES == 4 * TILE_BYTES && (TILE_BYTES % WBYTES) == 0, "sub-tiles must tile the stage arrays");
-  constexpr int WPA = TILE_BYTES / WBYTES;    // waves per stage array
+  constexpr int WPA = ABYTES / WBYTES;        // waves per A stage
+  static_assert(ABYTES % WBYTES == 0 && (HALF ? NW == 3 * WPA + 1 : NW == 4 * WPA && ABYTES == BBYTES),
+                "sub-tiles must fit the stage arrays");
   typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
   auto oswz = [](int m) { return OCH == 8 ? ((m >> 1) & 7) : (m & (OCH - 1)); };
   __syncthreads();
   char* ep = sA0;
   if (wave / WPA == 1) ep = sA1;
-  if (wave / WPA == 2) ep = sB0;
-  if (wave / WPA == 3) ep = sB1;
+  if (wave / WPA == 2) ep = HALF ? sA2 : sB0;
+  if (wave / WPA == 3) ep = HALF ? sB0 : sB1;
   ep += (wave % WPA) * WBYTES;
   // lane 16 kg + r16 holds row 16 i + r16, columns 16 j + 4 kg + 0..3 of the wave's sub-tile
 #pragma unroll
@@ -556,6 +662,60 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     // operand strips in the L2 / Infinity Cache (measured +0.7 % on the whole forward + backward)
     if (o < frag_n(f) && gcol < N)
       __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4*)(C + (size_t)grow * N + gcol));
+  }
+}
+
+// Adds the contraction ranges of k_gemm_mfma<1, 4, ..> in order and writes the rows: block = 16 rows
+// (fragment row i) of one half tile, a wave its 64 columns.
+struct ReduceArgs {
+  bf16* C;
+  const float* part;
+  int M, N, tiles_m, tiles_n, t0, parts, K;
+  int off[kMaxK + 1];
+};
+__global__ __launch_bounds__(256) void k_gemm_reduce(const ReduceArgs a) {
+  constexpr int GM = 8, FM = 8, FN = 4;
+  const int i = blockIdx.x % FM, u = blockIdx.x / FM;
+  const int t = a.t0 + u / 2;
+  const int gsize = GM * a.tiles_n, group = t / gsize, first_m = group * GM;
+  const int gm = (a.tiles_m - first_m) < GM ? (a.tiles_m - first_m) : GM;
+  const int in_g = t - group * gsize;
+  const int tm = 2 * (first_m + in_g % gm) + u % 2, tn = in_g / gm;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r16 = lane & 15, kg = lane >> 4;
+  const int v0 = tm * 128 + 16 * i;      // the fragment's first virtual row
+  int vstart = 0, prev = 0, row = 0, n = 0;
+  for (int r = 0; r < a.K + 2; ++r) {
+    const int b1 = r <= a.K ? a.off[r] : a.M;
+    const int len = b1 - prev, vlen = (len + 31) & ~31;
+    if (v0 >= vstart && v0 < vstart + vlen) {
+      row = prev + v0 - vstart;
+      n = len - (v0 - vstart);
+    }
+    vstart += vlen;
+    prev = b1;
+  }
+  const int units = 2 * (a.tiles_m * a.tiles_n - a.t0);
+  const float* src = a.part + (size_t)u * (128 * BN) + ((i * 4 + wave) * FN) * 256 + lane * 4;
+  const size_t step = (size_t)units * (128 * BN);
+  if (n <= 0) return;
+  f32x4 acc[FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+  for (int s_ = 0; s_ < a.parts; ++s_)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[j] += *(const f32x4*)(src + s_ * step + j * 256);
+  if (r16 >= n) return;
+#pragma unroll
+  for (int j = 0; j < FN; ++j) {
+    const int col = tn * BN + wave * 64 + 16 * j + 4 * kg;
+    if (col < a.N) {
+      bf16x4 o;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[e] = static_cast<bf16>(acc[j][e]);
+      *(bf16x4*)(a.C + (size_t)(row + r16) * a.N + col) = o;
+    }
   }
 }
 

@@ -152,8 +152,12 @@ Scratch plan_scratch(const mlora_problem* p, const CallCtx& c) {
   s.limit = z + s.bytes <= fixed ? fixed - z : 2 * fixed;
   s.grad_limit = unbounded ? SIZE_MAX : s.limit;
   if (aligned && !unbounded) s.bytes = grad_bytes(s.limit);
-  const size_t g = general_scratch_bytes(c.st, c.T, c.h, c.d, c.dtype, s.limit);
-  s.bytes = g > s.bytes ? g : s.bytes;
+  auto most = [&](size_t b) { s.bytes = b > s.bytes ? b : s.bytes; };
+  most(general_scratch_bytes(c.st, c.T, c.h, c.d, c.dtype, s.limit));
+  if (mfma_sizes_ok(p)) {
+    most(gemm_partial_bytes(c.st, c.T, c.d, c.h, s.limit));
+    most(gemm_partial_bytes(c.st, c.T, c.h, c.d, s.limit));
+  }
   return s;
 }
 size_t scratch_bytes(const mlora_problem* p) {
@@ -177,13 +181,13 @@ hipError_t compute_Z(const mlora_problem* p, const CallCtx& c, const void* X, vo
 
 // Y = X W + Z B_k, given Z
 hipError_t forward_gemm(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, const void* Z, void* scratch) {
+  const Scratch s = plan_scratch(p, c);
+  float* partial = s.bytes ? static_cast<float*>(scratch) : nullptr;
   if (mfma_gemm_applies(p) && aligned16(X) && aligned16(Y) && aligned16(Z))
     return gemm_mfma((const bf16*)X, (const bf16*)p->W, (bf16*)Y, c.T, c.d, c.h, true, (const bf16*)Z, c.ldz, c.st, c.B,
-                     c.stream);
+                     partial, s.limit, c.stream);
   const GenOperands o{X, p->W, Z, c.h, c.ldz, c.st.rank, &c.B};
-  const Scratch s = plan_scratch(p, c);
-  return general_gemm(1, &o, c.dtype, Y, c.T, c.d, true, c.st, s.bytes ? static_cast<float*>(scratch) : nullptr, s.limit,
-                      c.stream);
+  return general_gemm(1, &o, c.dtype, Y, c.T, c.d, true, c.st, partial, s.limit, c.stream);
 }
 
 hipError_t forward_impl(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, void* Z, void* scratch) {
@@ -233,13 +237,13 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
                          void* dX, float* const* dA, float* const* dB, int accumulate, void* scratch) {
   hipError_t e = adapter_grads_impl(p, c, X, dY, Z, G, dA, dB, accumulate, scratch);
   if (e == hipSuccess && dX != nullptr && p->T > 0) {
+    const Scratch s = plan_scratch(p, c);
+    float* partial = s.bytes ? static_cast<float*>(scratch) : nullptr;
     if (mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G))
       return gemm_mfma((const bf16*)dY, (const bf16*)p->W, (bf16*)dX, c.T, c.h, c.d, false, (const bf16*)G, c.ldz, c.st,
-                       c.A, c.stream);
+                       c.A, partial, s.limit, c.stream);
     const GenOperands o{dY, p->W, G, c.d, c.ldz, c.st.rank, &c.A};
-    const Scratch s = plan_scratch(p, c);
-    e = general_gemm(1, &o, c.dtype, dX, c.T, c.h, false, c.st, s.bytes ? static_cast<float*>(scratch) : nullptr, s.limit,
-                     c.stream);
+    e = general_gemm(1, &o, c.dtype, dX, c.T, c.h, false, c.st, partial, s.limit, c.stream);
   }
   return e;
 }

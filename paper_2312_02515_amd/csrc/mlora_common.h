@@ -88,7 +88,9 @@ hipError_t general_dA(const CallCtx& c, const void* X, const void* G, const OutT
 // gemm_mfma.hip : bf16 MFMA GEMM with the LoRA term as extra contraction steps
 bool gemm_mfma_ok(int M, int N, int Kd);
 hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, bool nn, const bf16* L, int ldz,
-                     const SegTable& st, const PtrTable& R, hipStream_t stream);
+                     const SegTable& st, const PtrTable& R, float* scratch, size_t scratch_bytes, hipStream_t stream);
+// scratch gemm_mfma asks for when it may use up to `scratch_limit` bytes (what is passed as scratch_bytes)
+size_t gemm_partial_bytes(const SegTable& st, int M, int N, int Kd, size_t scratch_limit);
 
 // One operand pair of a summed contraction (the input gradient of projections that share X):
 // A [M, Kd], Bm [N, Kd], L [M, ldz] with R_k [N, rank[k]].

@@ -93,3 +93,18 @@ def test_ragged_ranks_in_a_group(P):
         ranks[1] = [100, 33, 64]      # four 32-column groups
     ins = _group_inputs(420, 128, [64 * (p + 1) for p in range(P)], [90, 201, 100], ranks, torch.bfloat16, lead=6, seed=75)
     check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"ragged group {P}")
+
+
+@pytest.mark.parametrize("case", [
+    # T, h, d, tokens, ranks, lead: bf16 base products cut into half tiles and contraction ranges
+    (100, 4096, 512, [37, 20, 40], [16, 7, 128], 3),        # one row tile whose lower half is empty; many ranges
+    (300, 512, 2048, [140, 0, 131], [64, 33, 8], 20),       # a task across half tiles; ranks 33..64
+    (520, 1088, 448, [33, 31, 450], [1, 100, 32], 6),       # contraction ranges of unequal length
+    (4200, 1024, 4096, [2100, 2050], [16, 24], 50),         # a whole round of tiles and halves behind it
+])
+def test_half_tiles_and_contraction_ranges(case):
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=76)
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"half tiles {case}")
+    inp.W.zero_()      # the LoRA terms alone
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"half tiles, W = 0 {case}")
