@@ -78,6 +78,26 @@ __device__ __forceinline__ void mma32(f32x16& acc, u32x4 a, u32x4 b, float) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[e], y[e], acc, 0, 0, 0);
 }
+// ... for FM x FN such accumulators; fp32: one contraction pair after the other, so that an accumulator
+// comes up again only FM x FN MFMAs later
+template <int FM, int FN>
+__device__ __forceinline__ void mma_tile(f32x16 (&acc)[FM][FN], const u32x4 (&a)[FM], const u32x4 (&b)[FN], bf16) {
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) mma32(acc[i][j], a[i], b[j], bf16{});
+}
+template <int FM, int FN>
+__device__ __forceinline__ void mma_tile(f32x16 (&acc)[FM][FN], const u32x4 (&a)[FM], const u32x4 (&b)[FN], float) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(f32x4, a[i])[e], __builtin_bit_cast(f32x4, b[j])[e],
+                                                         acc[i][j], 0, 0, 0);
+}
 // the same on 16 rows x 16 columns
 __device__ __forceinline__ void mma16(f32x4& acc, u32x4 a, u32x4 b, bf16) {
   acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
@@ -179,10 +199,13 @@ __device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const
 // from memory (r_k <= 128 contraction indices against thousands).
 // With parts > 1 a tile's contraction is cut into `parts` ranges, one block each; the partial tiles
 // go to memory in fp32 and k_gen_reduce adds them in order.
+// A tile's LDS writes and the next loads are issued between its MFMA groups, whose fragments are read
+// one group ahead; tiles that need no masks load without bounds arithmetic.
 // Bound by the fp32 matrix rate in fp32 (153 TFLOP/s for a large product on this card): T = 2048,
-// 4096 x 4096: 720 us forward, 605 us backward layout (95 and 114 TFLOP/s), against 1714 and 1686 us
-// of a vector-ALU kernel with 64 x 64 tiles; bf16, T = 3072, 4096 x 4096, 240 us (430 TFLOP/s,
-// bound by LDS traffic and the wait for each tile's loads) against 2800 and 3084 us.
+// 4096 x 4096: 600 us forward, 546 us backward layout (115 and 126 TFLOP/s; 693 and 550 us with loads
+// and LDS writes behind the MFMAs, 1714 and 1686 us on the vector ALUs); T = 3000: 812 and 800 us
+// (1003 and 1042).  bf16, T = 2048, 4100 x 4100: 160 and 144 us (206 and 151), bound by LDS traffic
+// and the wait for each tile's loads.
 template <typename T, int BM, int BN, bool NN, int NSEG>
 __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   constexpr int V = kV<T>, BK = 8 * V;
@@ -236,25 +259,51 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
     if (t0 >= t1) continue;
     const T* A = static_cast<const T*>(a.A[g]);
     const T* W = static_cast<const T*>(a.W[g]);
-    const T* arow[NA];
+    // rows of this thread's pieces, as byte offsets from the block's first row (a block spans at most
+    // BM rows of up to 16 MiB: below 2^32)
+    const int row0 = pc[0].row;
+    const char* abase = reinterpret_cast<const char*>(A + (size_t)row0 * Kd);
+    unsigned aoff[NA], boff[NB];
 #pragma unroll
     for (int it = 0; it < NA; ++it) {
       const int last = pc[it].n > 0 ? pc[it].n - 1 : 0;
-      arow[it] = A + (size_t)(pc[it].row + (ar < last ? ar : last)) * Kd;
+      aoff[it] = (unsigned)(((size_t)(pc[it].row - row0 + (ar < last ? ar : last)) * Kd + ac * V) * sizeof(T));
     }
-    const T* brow[NB];
-    if constexpr (!NN) {
+    const char* bbase;
+    if constexpr (NN) {
+      bbase = reinterpret_cast<const char*>(W + col0);
+#pragma unroll
+      for (int it = 0; it < NB; ++it) {
+        const int idx = tid + 256 * it;
+        boff[it] = (unsigned)(((size_t)(idx / CPR) * N + (idx % CPR) * V) * sizeof(T));
+      }
+    } else {
+      bbase = reinterpret_cast<const char*>(W + (size_t)col0 * Kd);
 #pragma unroll
       for (int it = 0; it < NB; ++it) {
         const int n = col0 + ar + 32 * it;
-        brow[it] = W + (size_t)(n < N ? n : N - 1) * Kd;
+        boff[it] = (unsigned)(((size_t)((n < N ? n : N - 1) - col0) * Kd + ac * V) * sizeof(T));
       }
     }
+    const size_t bstep = (NN ? (size_t)BK * N : (size_t)BK) * sizeof(T);
+    // tiles before `whole` need no masks (none does in a block at the ragged right edge)
+    const int whole = n_edge ? 0 : Kd / BK;
+    typedef typename Piece16<T>::type Piece;
     u32x4 ra[NA], rb[NB];
     auto load = [&](int kt) {
       const int k0 = kt * BK;
+      const char* at = abase + (size_t)k0 * sizeof(T);
+      const char* bt = bbase + (size_t)kt * bstep;
+      if (kt < whole) {
 #pragma unroll
-      for (int it = 0; it < NA; ++it) ra[it] = load_piece<T>(arow[it], k0 + ac * V, Kd);
+        for (int it = 0; it < NA; ++it) ra[it] = *reinterpret_cast<const Piece*>(at + aoff[it]);
+#pragma unroll
+        for (int it = 0; it < NB; ++it) rb[it] = *reinterpret_cast<const Piece*>(bt + boff[it]);
+        return;
+      }
+#pragma unroll
+      for (int it = 0; it < NA; ++it)
+        ra[it] = load_piece<T>(reinterpret_cast<const T*>(abase + aoff[it]) - ac * V, k0 + ac * V, Kd);
 #pragma unroll
       for (int it = 0; it < NB; ++it) {
         if constexpr (NN) {
@@ -263,66 +312,67 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
           k = k < Kd ? k : Kd - 1;
           rb[it] = load_piece<T>(W + (size_t)k * N, col0 + (idx % CPR) * V, N);
         } else {
-          rb[it] = load_piece<T>(brow[it], k0 + ac * V, Kd);
+          rb[it] = load_piece<T>(reinterpret_cast<const T*>(bbase + boff[it]) - ac * V, k0 + ac * V, Kd);
         }
       }
     };
     auto put = [&](int kt, char* st) {
-      const int k0 = kt * BK;
-      const bool tail = k0 + BK > Kd;
+      if (kt >= whole) {
+        const int k0 = kt * BK;
+#pragma unroll
+        for (int it = 0; it < NA; ++it) ra[it] = tail_shift<T>(ra[it], k0 + ac * V, Kd);
+#pragma unroll
+        for (int it = 0; it < NB; ++it) {
+          if constexpr (NN) {
+            const int idx = tid + 256 * it;
+            rb[it] = tail_shift<T>(rb[it], col0 + (idx % CPR) * V, N);
+            if (k0 + idx / CPR >= Kd) rb[it] = u32x4{0, 0, 0, 0};
+          } else {
+            rb[it] = tail_shift<T>(rb[it], k0 + ac * V, Kd);
+          }
+        }
+      }
       const int sw = (ac ^ ((ar >> 1) & 7)) << 4;
 #pragma unroll
-      for (int it = 0; it < NA; ++it) {
-        if (tail) ra[it] = tail_shift<T>(ra[it], k0 + ac * V, Kd);
-        *reinterpret_cast<u32x4*>(st + (ar + 32 * it) * 128 + sw) = ra[it];
-      }
+      for (int it = 0; it < NA; ++it) *reinterpret_cast<u32x4*>(st + (ar + 32 * it) * 128 + sw) = ra[it];
       char* sb = st + ABYTES;
 #pragma unroll
       for (int it = 0; it < NB; ++it) {
         if constexpr (NN) {
           const int idx = tid + 256 * it;
           const int k = idx / CPR, c = idx % CPR;
-          if (n_edge) rb[it] = tail_shift<T>(rb[it], col0 + c * V, N);
-          if (tail && k0 + k >= Kd) rb[it] = u32x4{0, 0, 0, 0};
           const int cs = !B16 ? c : (CPR == 16 ? c ^ ((k & 3) << 2) : c ^ (((k >> 1) & 1) << 2));
           *reinterpret_cast<u32x4*>(sb + (k * CPR + cs) * 16) = rb[it];
         } else {
-          if (tail) rb[it] = tail_shift<T>(rb[it], k0 + ac * V, Kd);
           *reinterpret_cast<u32x4*>(sb + (ar + 32 * it) * 128 + sw) = rb[it];
         }
       }
     };
-    auto compute = [&](const char* st) {
+    // fragments of group ks (a quarter) of the tile in st
+    auto read = [&](const char* st, int ks, u32x4 (&af)[FM], u32x4 (&bfr)[FN]) {
       const char* sb = st + ABYTES;
+      const int coff = ((2 * ks + lhi) ^ fsw) << 4;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const int coff = ((2 * ks + lhi) ^ fsw) << 4;
-        u32x4 af[FM], bfr[FN];
+      for (int i = 0; i < FM; ++i) af[i] = *reinterpret_cast<const u32x4*>(st + a_off + i * 4096 + coff);
 #pragma unroll
-        for (int i = 0; i < FM; ++i) af[i] = *reinterpret_cast<const u32x4*>(st + a_off + i * 4096 + coff);
+      for (int j = 0; j < FN; ++j) {
+        if constexpr (!NN) {
+          bfr[j] = *reinterpret_cast<const u32x4*>(sb + b_off + j * 4096 + coff);
+        } else if constexpr (B16) {
+          const int n = wn * WN + 32 * j + tr_n, kk = 16 * ks + tr_k;
+          const int c = CPR == 16 ? (n >> 3) ^ (kq << 2) : (n >> 3) ^ (((kk >> 1) & 1) << 2);
+          const char* q = sb + (kk * CPR + c) * 16 + (n & 7) * 2;
+          bfr[j] = __builtin_bit_cast(u32x4, lds_read_tr_pair(q, q + 4 * CPR * 16));
+        } else {
+          const float* q = reinterpret_cast<const float*>(sb) + (2 * ks + lhi) * 4 * BN + wn * WN + 32 * j + l32;
+          f32x4 v;
 #pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          if constexpr (!NN) {
-            bfr[j] = *reinterpret_cast<const u32x4*>(sb + b_off + j * 4096 + coff);
-          } else if constexpr (B16) {
-            const int n = wn * WN + 32 * j + tr_n, kk = 16 * ks + tr_k;
-            const int c = CPR == 16 ? (n >> 3) ^ (kq << 2) : (n >> 3) ^ (((kk >> 1) & 1) << 2);
-            const char* q = sb + (kk * CPR + c) * 16 + (n & 7) * 2;
-            bfr[j] = __builtin_bit_cast(u32x4, lds_read_tr_pair(q, q + 4 * CPR * 16));
-          } else {
-            const float* q = reinterpret_cast<const float*>(sb) + (2 * ks + lhi) * 4 * BN + wn * WN + 32 * j + l32;
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = q[e * BN];
-            bfr[j] = __builtin_bit_cast(u32x4, v);
-          }
+          for (int e = 0; e < 4; ++e) v[e] = q[e * BN];
+          bfr[j] = __builtin_bit_cast(u32x4, v);
         }
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j) mma32(acc[i][j], af[i], bfr[j], T{});
       }
     };
+    auto multiply = [&](const u32x4 (&af)[FM], const u32x4 (&bfr)[FN]) { mma_tile<FM, FN>(acc, af, bfr, T{}); };
     __syncthreads();   // the previous operand pair's last tile has been read
     load(t0);
     put(t0, sm);
@@ -330,9 +380,18 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
     __syncthreads();
     for (int kt = t0; kt < t1; ++kt) {
       const int s = (kt - t0) & 1;
-      compute(sm + s * (ABYTES + BBYTES));
+      const char* st = sm + s * (ABYTES + BBYTES);
+      u32x4 af[2][FM], bfr[2][FN];
+      read(st, 0, af[0], bfr[0]);
+      read(st, 1, af[1], bfr[1]);
+      multiply(af[0], bfr[0]);
       if (kt + 1 < t1) put(kt + 1, sm + (s ^ 1) * (ABYTES + BBYTES));
+      read(st, 2, af[0], bfr[0]);
+      multiply(af[1], bfr[1]);
       if (kt + 2 < t1) load(kt + 2);
+      read(st, 3, af[1], bfr[1]);
+      multiply(af[0], bfr[0]);
+      multiply(af[1], bfr[1]);
       __syncthreads();
     }
   }
