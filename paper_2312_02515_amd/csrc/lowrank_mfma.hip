@@ -20,6 +20,7 @@ namespace mlora {
 namespace {
 
 using namespace stage;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // Bank-conflict swizzle of a small tile stored with the contraction index as its rows
 // ([64 k][w] bf16) and read with transposing LDS reads, which touch 4 consecutive rows x 64 B per
@@ -72,6 +73,11 @@ struct RowsArgs {
   unsigned char rank[NP][kMaxK];
   float s[NP][kMaxK];
   PtrTable M[NP];
+  // splits > 1 (NP == 1 only): the contraction is cut into `splits` ranges, one block each; range s
+  // writes its fp32 sums of row i at part + (s * rows + i - off[0]) * ldz, rows = off[K] - off[0], and
+  // k_rows_reduce adds the ranges in order
+  int splits;
+  float* part;
 };
 
 template <int NP>
@@ -122,7 +128,8 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
 
   const bf16* __restrict__ In = ra.In;
   const int inner = ra.inner;
-  int b = blockIdx.x, k = 0;
+  const int sp = NP == 1 ? blockIdx.x % ra.splits : 0;
+  int b = NP == 1 ? blockIdx.x / ra.splits : blockIdx.x, k = 0;
   for (; k < ra.K; ++k) {
     const int nb = (ra.off[k + 1] - ra.off[k] + TM - 1) / TM;
     if (b < nb) break;
@@ -238,7 +245,15 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
   // have landed (the loads of the NS-2 younger tiles may stay in flight); the barrier then makes
   // every wave's part of tile kt visible and tells that all waves are done with tile kt-1,
   // whose stage is refilled next.
-  const int KT = inner / 64;
+  int KT = inner / 64;
+  if (NP == 1 && ra.splits > 1) {
+    const int k0 = (int)((long long)KT * sp / ra.splits), k1 = (int)((long long)KT * (sp + 1) / ra.splits);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) xptr[it] += (size_t)k0 * 64;
+#pragma unroll
+    for (int it = 0; it < SPW; ++it) sptr[0][it] += (size_t)k0 * sstep[0];
+    KT = k1 - k0;
+  }
   __syncthreads();  // the zero pads
 #pragma unroll
   for (int s_ = 0; s_ < NS - 1; ++s_)
@@ -261,6 +276,21 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
 
   // lane holds row m = 32*wave + l32 and columns q = 32j + 8g + 4*lhi + 0..3
   const int row = lo + 32 * wave + l32;
+  if (NP == 1 && ra.splits > 1) {
+    if (row < hi) {
+      const int ldz = ra.ldz[0];
+      float* part = ra.part + ((size_t)sp * (ra.off[ra.K] - ra.off[0]) + row - ra.off[0]) * ldz;
+#pragma unroll
+      for (int j = 0; j < NQ; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int q = 32 * j + 8 * g + 4 * lhi;
+          if (q < r[0])
+            *(f32x4*)(part + q) = f32x4{acc[0][j][4 * g], acc[0][j][4 * g + 1], acc[0][j][4 * g + 2], acc[0][j][4 * g + 3]};
+        }
+    }
+    return;
+  }
   if (row < hi) {
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
@@ -282,6 +312,30 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
       }
     }
   }
+}
+
+// Adds the contraction ranges of k_lowrank_mfma in order, scales and rounds.  One thread per four
+// columns of a row.
+__global__ __launch_bounds__(256) void k_rows_reduce(const RowsArgs<1> ra) {
+  const int ldz = ra.ldz[0], rows = ra.off[ra.K] - ra.off[0], per = ldz / 4;
+  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (t >= (long long)rows * per) return;
+  const int i = (int)(t / per), q = (int)(t % per) * 4;
+  int k = 0;
+  while (ra.off[0] + i >= ra.off[k + 1]) ++k;
+  const int r = ra.rank[0][k];
+  const float s = ra.s[0][k];
+  f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (q < r) {
+    const float* p = ra.part + (size_t)i * ldz + q;
+    const size_t step = (size_t)rows * ldz;
+#pragma unroll 4
+    for (int s_ = 0; s_ < ra.splits; ++s_) sum += *(const f32x4*)(p + s_ * step);
+  }
+  bf16x4 o;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) o[e] = static_cast<bf16>(q + e < r ? sum[e] * s : 0.f);
+  *(bf16x4*)(ra.Out[0] + (size_t)(ra.off[0] + i) * ldz + q) = o;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -735,6 +789,38 @@ int pick_row_tile(const SegTable& st) {
   return tm;
 }
 
+// Row tile and contraction ranges of one launch.  Ranges (fp32 sums in scratch, one more launch to add
+// them) where the rows alone leave the chip short of loads in flight; powers of two, so that an XCD
+// sees the same ranges of the small operand in every row block.  Measured, us, all launches of the
+// product, one range -> as chosen here:
+//   ranks above 64 (four column groups: the four-wave form of few rows does not fit the LDS):
+//     3072 x 4096 (12 tasks)  s x A 85 -> 25, s dy B^T 56 -> 22;  8192 x 4096  62 -> 33, 56 -> 33
+//   ranks up to 64:
+//     16448 x 11008  119 -> 90,  16448 x 4096  44 -> 38-40,  12288 x 4096  31 -> 26
+//     2048 x 11008, operands from HBM  30 -> 22 (from the Infinity Cache 21 -> 19)
+//   left alone: 32768 rows (64 against 70 with two ranges), up to 8192 rows of 4096 (the four-wave
+//   form: 8192 rows 21.5 against 21-22).
+struct RowsPlan {
+  int tm, splits;
+};
+RowsPlan plan_rows(const SegTable& st, int inner, int ldz, size_t limit) {
+  const RowsPlan plain{pick_row_tile(st), 1};
+  const int KT = inner / 64, b128 = row_blocks(st, 128), b32 = row_blocks(st, 32);
+  if (b128 == 0 || b128 >= 256) return plain;
+  RowsPlan pl = plain;
+  if (nq_of(ldz) == 4) {
+    pl.tm = 128;
+    while (2 * pl.splits * b128 <= 256 && 8 * pl.splits <= KT && pl.splits < 16) pl.splits *= 2;
+  } else if (b32 > 256) {
+    pl = RowsPlan{128, KT >= 128 ? 8 : 4};
+  } else if (b32 >= 32 && KT >= 128) {
+    pl = RowsPlan{64, 8};
+  }
+  const size_t one = (size_t)(st.off[st.K] - st.off[0]) * ldz * sizeof(float);
+  while (pl.splits > 1 && (one * pl.splits > limit || 4 * pl.splits > KT)) pl.splits /= 2;
+  return pl.splits > 1 ? pl : plain;
+}
+
 // Algorithmic bytes of one launch: the tasks' rows of the big operand read once, the outputs
 // written once, the small operands read once.
 template <int NP>
@@ -810,6 +896,17 @@ hipError_t launch_rows_splitk(const RowsArgs<1>& a, int blocks, hipStream_t s) {
 template <bool KMAJOR, int NP>
 hipError_t launch_rows(const RowsArgs<NP>& a, int nq, int tm, int blocks, hipStream_t s) {
   if constexpr (NP == 1) {
+    if (a.splits > 1) {
+      hipError_t e = nq == 1 ? launch_rows_tm<KMAJOR, 1, 1>(a, tm, blocks, s)
+                             : (nq == 2 ? launch_rows_tm<KMAJOR, 2, 1>(a, tm, blocks, s) : launch_rows_tm<KMAJOR, 4, 1>(a, tm, blocks, s));
+      if (e != hipSuccess) return e;
+      const long long n = (long long)(a.off[a.K] - a.off[0]) * (a.ldz[0] / 4);
+      const int slot = profile_begin(kProfileRows, 0.0, s);   // its time counts, it adds no algorithmic bytes
+      hipLaunchKernelGGL(k_rows_reduce, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, a);
+      e = hipGetLastError();
+      profile_end(slot, s);
+      return e;
+    }
     // few rows: four waves per 32-row block, each on a quarter of the contraction
     if (tm == 32 && nq <= 2 && a.inner >= 1024 && blocks <= 1024) {
       return nq == 1 ? launch_rows_splitk<KMAJOR, 1>(a, blocks, s) : launch_rows_splitk<KMAJOR, 2>(a, blocks, s);
@@ -856,6 +953,8 @@ hipError_t rows_group(const LowrankGroupItem* it, const SegTable& st, const bf16
     }
     a.M[p] = *it[p].M;
   }
+  a.splits = 1;
+  a.part = nullptr;
   const int tm = pick_row_tile(st);
   const int blocks = row_blocks(st, tm);
   if (blocks == 0) return hipSuccess;
@@ -887,13 +986,20 @@ hipError_t grad_group(const LowrankGroupItem* it, const SegTable& st, const bf16
 
 }  // namespace
 
+size_t rows_partial_bytes(const SegTable& st, int inner, int ldz, size_t limit) {
+  const RowsPlan pl = plan_rows(st, inner, ldz, limit);
+  return pl.splits > 1 ? align_up((size_t)pl.splits * (st.off[st.K] - st.off[0]) * ldz * sizeof(float), 256) : 0;
+}
+
 // Z = s x A (a_major = true, M = A_k) or G = s dy B^T (a_major = false, M = B_k).
 hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M,
-                             bool a_major) {
-  const int tm = pick_row_tile(c.st);
-  const int blocks = row_blocks(c.st, tm);
+                             bool a_major, float* partial, size_t limit) {
+  const RowsPlan pl = plan_rows(c.st, inner, c.ldz, partial != nullptr ? limit : 0);
+  const int tm = pl.tm, blocks = row_blocks(c.st, tm) * pl.splits;
   if (blocks == 0) return hipSuccess;
   RowsArgs<1> a;
+  a.splits = pl.splits;
+  a.part = partial;
   a.In = In;
   a.inner = inner;
   a.K = c.st.K;

@@ -157,6 +157,10 @@ Scratch plan_scratch(const mlora_problem* p, const CallCtx& c) {
   if (mfma_sizes_ok(p)) {
     most(gemm_partial_bytes(c.st, c.T, c.d, c.h, s.limit));
     most(gemm_partial_bytes(c.st, c.T, c.h, c.d, s.limit));
+    if (p->K > 0) {
+      most(rows_partial_bytes(c.st, c.h, c.ldz, s.limit));
+      most(rows_partial_bytes(c.st, c.d, c.ldz, s.limit));
+    }
   }
   return s;
 }
@@ -173,9 +177,12 @@ mlora_status hip_status(hipError_t e) {
 }
 
 // Z = s_k x_k A_k into `Z` ([T, ldz], layout of the `saved` buffer)
-hipError_t compute_Z(const mlora_problem* p, const CallCtx& c, const void* X, void* Z) {
-  if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(Z))
-    return lowrank_rows_mfma(c, (const bf16*)X, c.h, (bf16*)Z, c.A, true);
+hipError_t compute_Z(const mlora_problem* p, const CallCtx& c, const void* X, void* Z, void* scratch) {
+  if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(Z)) {
+    const Scratch s = plan_scratch(p, c);
+    return lowrank_rows_mfma(c, (const bf16*)X, c.h, (bf16*)Z, c.A, true, s.bytes ? static_cast<float*>(scratch) : nullptr,
+                             s.limit);
+  }
   return general_Z(c, X, Z);
 }
 
@@ -191,7 +198,7 @@ hipError_t forward_gemm(const mlora_problem* p, const CallCtx& c, const void* X,
 }
 
 hipError_t forward_impl(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, void* Z, void* scratch) {
-  hipError_t e = compute_Z(p, c, X, Z);
+  hipError_t e = compute_Z(p, c, X, Z, scratch);
   if (e != hipSuccess) return e;
   return forward_gemm(p, c, X, Y, Z, scratch);
 }
@@ -220,7 +227,7 @@ hipError_t adapter_grads_impl(const mlora_problem* p, const CallCtx& c, const vo
   accumulate = accumulate ? 1 : 0;
   hipError_t e;
   if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(dY) && aligned16(Z) && aligned16(G)) {
-    e = lowrank_rows_mfma(c, (const bf16*)dY, c.d, (bf16*)G, c.B, false);
+    e = lowrank_rows_mfma(c, (const bf16*)dY, c.d, (bf16*)G, c.B, false, partial, s.limit);
     if (e == hipSuccess) e = grad_mfma(c, (const bf16*)dY, c.d, (const bf16*)Z, tb, accumulate, false, partial, s.grad_limit);
     if (e == hipSuccess && !skip_dA)
       e = grad_mfma(c, (const bf16*)X, c.h, (const bf16*)G, ta, accumulate, true, partial, s.grad_limit);
@@ -375,10 +382,10 @@ mlora_status mlora_lora_bwd_recompute(const mlora_problem* p, const void* X, con
   CallCtx c;
   fill_ctx(p, hip_stream, &c);
   void* Z = static_cast<char*>(workspace) + lowrank_bytes(p);
-  hipError_t e = p->T > 0 ? compute_Z(p, c, X, Z) : hipSuccess;
+  void* scratch = static_cast<char*>(workspace) + 2 * lowrank_bytes(p);
+  hipError_t e = p->T > 0 ? compute_Z(p, c, X, Z, scratch) : hipSuccess;
   if (e != hipSuccess) return hip_status(e);
-  return hip_status(backward_impl(p, c, X, dY, Z, workspace, dX, dA, dB, accumulate,
-                                  static_cast<char*>(workspace) + 2 * lowrank_bytes(p)));
+  return hip_status(backward_impl(p, c, X, dY, Z, workspace, dX, dA, dB, accumulate, scratch));
 }
 
 // ---- 8-bit frozen base weight: decode into the head of the workspace, then the plain path ----

@@ -117,7 +117,11 @@ hipError_t w8_quantize(const void* W, int dtype, int h, int d, int8_t* Wq, float
 hipError_t w8_dequantize(const int8_t* Wq, const float* c, int dtype, int h, int d, void* Wh, hipStream_t stream);
 
 // lowrank_mfma.hip : bf16 MFMA kernels for Z, G (row-local) and dA_k, dB_k (reduce over a task's tokens)
-hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M, bool a_major);
+// `partial`, `limit`: scratch of contraction-split launches and how much of it may be used; the launch
+// needs rows_partial_bytes(.., limit) bytes.
+size_t rows_partial_bytes(const SegTable& st, int inner, int ldz, size_t limit);
+hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M, bool a_major,
+                             float* partial, size_t limit);
 // `partial`: grad_partial_bytes(c.st, wide, limit) bytes of scratch for calls whose tasks x column
 // blocks do not fill the chip (the tokens of a task are then split over blocks); NULL = never split.
 int grad_splits(const SegTable& st, int wide, size_t limit);

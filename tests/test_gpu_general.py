@@ -108,3 +108,18 @@ def test_half_tiles_and_contraction_ranges(case):
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"half tiles {case}")
     inp.W.zero_()      # the LoRA terms alone
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"half tiles, W = 0 {case}")
+
+
+@pytest.mark.parametrize("case", [
+    # T, h, d, tokens, ranks, lead: low-rank rows whose contraction is cut into ranges over blocks
+    (700, 512, 2048, [300, 0, 390], [128, 8, 70], 4),       # four column groups, rows before and after the tasks
+    (8500, 256, 320, [4000, 4400], [16, 33], 60),           # more than 256 blocks of 32 rows
+    (1100, 8192, 64, [500, 560], [24, 9], 10),              # deep contraction of few rows (forward)
+    (1100, 64, 8256, [500, 560], [24, 8], 10),              # ... and of s dy B^T; ranges of unequal length
+])
+def test_contraction_split_low_rank_rows(case):
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=77)
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"split rows {case}")
+    inp.W.zero_()
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"split rows, W = 0 {case}")
