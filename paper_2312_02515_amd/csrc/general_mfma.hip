@@ -683,14 +683,15 @@ __global__ __launch_bounds__(NW * 64, 4) void k_gen_rows(const GenRowsArgs a) {
 // A wave owns 64 columns of Big as four MFMA fragments of 16: lane i of 16 carries columns
 // 4 i .. 4 i + 3, one for each fragment, so that it loads (and, for dB, stores) them as one piece.
 // splits > 1: a task's tokens are cut into ranges of whole MFMA groups, one block each, whose sums go
-// to `part` ([range][sum of r_k][wide]) for grad_reduce to add in order.  fp32, T = 2048, 4 tasks, 4096
+// to part + range * part_step ([sum of r_k][wide]) for grad_reduce to add in order.  fp32, T = 2048, 4 tasks, 4096
 // columns, rank 16: 13-14 us + 5 us of reduction for 34 MB, against 131 us with a serial sum per
 // output element.
 // ------------------------------------------------------------------------------------------
 struct GenGradArgs {
   const void* Big;
   const void* Small;
-  int wide, ldz, K, accumulate, chunks, splits, rtotal;
+  int wide, ldz, K, accumulate, chunks, splits;
+  size_t part_step;
   float* part;
   int off[kMaxK + 1];
   unsigned char rank[kMaxK];
@@ -698,13 +699,13 @@ struct GenGradArgs {
 };
 
 template <typename T, int NQ, bool WIDE_FIRST>
-__global__ __launch_bounds__(256) void k_gen_grad(const GenGradArgs a) {
+__device__ __forceinline__ void gen_grad_body(const GenGradArgs& a, int bid) {
   constexpr int GT = sizeof(T) == 2 ? 32 : 4;        // tokens per MFMA
   constexpr int TE = GT / 4;                         // ... of which a lane carries TE
   const int wide = a.wide;
-  const int ch = blockIdx.x % a.chunks;
-  const int sp = blockIdx.x / a.chunks % a.splits;
-  const int k = blockIdx.x / (a.chunks * a.splits);
+  const int ch = bid % a.chunks;
+  const int sp = bid / a.chunks % a.splits;
+  const int k = bid / (a.chunks * a.splits);
   int lo = a.off[k], hi = a.off[k + 1];
   if (a.splits > 1) {
     const int len = ((hi - lo + a.splits - 1) / a.splits + 31) / 32 * 32;
@@ -796,7 +797,7 @@ __global__ __launch_bounds__(256) void k_gen_grad(const GenGradArgs a) {
   if (a.splits > 1) {
     int rbase = 0;
     for (int kk = 0; kk < k; ++kk) rbase += a.rank[kk];
-    o = a.part + ((size_t)sp * a.rtotal + rbase) * wide;
+    o = a.part + sp * a.part_step + (size_t)rbase * wide;
     accumulate = 0;
   }
 #pragma unroll
@@ -815,6 +816,13 @@ __global__ __launch_bounds__(256) void k_gen_grad(const GenGradArgs a) {
       }
     }
   }
+}
+
+// dB (the first blocks_b blocks) and dA of one call
+template <typename T, int NQ>
+__global__ __launch_bounds__(256) void k_gen_grad(const GenGradArgs b, const GenGradArgs a, int blocks_b) {
+  if ((int)blockIdx.x < blocks_b) gen_grad_body<T, NQ, false>(b, blockIdx.x);
+  else gen_grad_body<T, NQ, true>(a, blockIdx.x - blocks_b);
 }
 
 int row_blocks(const SegTable& st, int tm) {
@@ -950,8 +958,8 @@ hipError_t gemm_n(int n, const GenOperands* ops, int dtype, void* C, int M, int 
 }
 
 // Token ranges per task: about four blocks per CU, at least 64 tokens each, as far as the scratch goes
-int gen_grad_splits(const SegTable& st, int wide, size_t scratch_limit) {
-  const int blocks = st.K * ((wide + 255) / 256);
+int gen_grad_splits(const SegTable& st, int wide_b, int wide_a, size_t scratch_limit) {
+  const int blocks = st.K * ((wide_b + 255) / 256 + (wide_a + 255) / 256);
   if (st.K == 0) return 1;
   int longest = 0;
   size_t rtotal = 0;
@@ -962,55 +970,25 @@ int gen_grad_splits(const SegTable& st, int wide, size_t scratch_limit) {
   int s = (1024 + blocks - 1) / blocks;
   s = s < 16 ? s : 16;
   s = s < longest / 64 ? s : longest / 64;
-  while (s > 1 && (size_t)s * rtotal * wide * sizeof(float) > scratch_limit) --s;
+  while (s > 1 && (size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float) > scratch_limit) --s;
   return s > 1 ? s : 1;
 }
 
-size_t gen_grad_bytes(const SegTable& st, int wide, size_t scratch_limit) {
-  const int s = gen_grad_splits(st, wide, scratch_limit);
+size_t gen_grad_bytes(const SegTable& st, int wide_b, int wide_a, size_t scratch_limit) {
+  const int s = gen_grad_splits(st, wide_b, wide_a, scratch_limit);
   if (s <= 1) return 0;
   size_t rtotal = 0;
   for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
-  return align_up((size_t)s * rtotal * wide * sizeof(float), 256);
+  return align_up((size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float), 256);
 }
 
-template <typename T, bool WIDE_FIRST>
-void launch_grad(const GenGradArgs& a, int ldz, int blocks, hipStream_t s) {
-  if (ldz <= 16) hipLaunchKernelGGL((k_gen_grad<T, 1, WIDE_FIRST>), dim3(blocks), dim3(256), 0, s, a);
-  else if (ldz <= 32) hipLaunchKernelGGL((k_gen_grad<T, 2, WIDE_FIRST>), dim3(blocks), dim3(256), 0, s, a);
-  else if (ldz <= 64) hipLaunchKernelGGL((k_gen_grad<T, 4, WIDE_FIRST>), dim3(blocks), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k_gen_grad<T, 8, WIDE_FIRST>), dim3(blocks), dim3(256), 0, s, a);
-}
-
-hipError_t grad_any(const CallCtx& c, const void* Big, int wide, const void* Small, const OutTable& out, int accumulate,
-                    bool wide_first, float* scratch, size_t scratch_bytes) {
-  if (c.K == 0) return hipSuccess;
-  GenGradArgs a;
-  a.Big = Big;
-  a.Small = Small;
-  a.wide = wide;
-  a.ldz = c.ldz;
-  a.K = c.K;
-  a.accumulate = accumulate;
-  a.chunks = (wide + 255) / 256;
-  a.splits = gen_grad_splits(c.st, wide, scratch != nullptr ? scratch_bytes : 0);
-  a.rtotal = 0;
-  for (int k = 0; k < c.K; ++k) a.rtotal += c.st.rank[k];
-  a.part = scratch;
-  for (int k = 0; k <= kMaxK; ++k) a.off[k] = c.st.off[k];
-  for (int k = 0; k < kMaxK; ++k) a.rank[k] = (unsigned char)c.st.rank[k];
-  a.out = out;
-  const int blocks = c.K * a.chunks * a.splits;
-  if (c.dtype == MLORA_F32) {
-    if (wide_first) launch_grad<float, true>(a, c.ldz, blocks, c.stream);
-    else launch_grad<float, false>(a, c.ldz, blocks, c.stream);
-  } else {
-    if (wide_first) launch_grad<bf16, true>(a, c.ldz, blocks, c.stream);
-    else launch_grad<bf16, false>(a, c.ldz, blocks, c.stream);
-  }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.splits == 1) return e;
-  return grad_reduce(c.st, scratch, a.splits, wide, out, accumulate, c.stream);
+template <typename T>
+void launch_grads(const GenGradArgs& b, const GenGradArgs& a, int blocks_b, int blocks, int ldz, hipStream_t s) {
+  const dim3 grid((unsigned)blocks);
+  if (ldz <= 16) hipLaunchKernelGGL((k_gen_grad<T, 1>), grid, dim3(256), 0, s, b, a, blocks_b);
+  else if (ldz <= 32) hipLaunchKernelGGL((k_gen_grad<T, 2>), grid, dim3(256), 0, s, b, a, blocks_b);
+  else if (ldz <= 64) hipLaunchKernelGGL((k_gen_grad<T, 4>), grid, dim3(256), 0, s, b, a, blocks_b);
+  else hipLaunchKernelGGL((k_gen_grad<T, 8>), grid, dim3(256), 0, s, b, a, blocks_b);
 }
 
 }  // namespace
@@ -1018,8 +996,7 @@ hipError_t grad_any(const CallCtx& c, const void* Big, int wide, const void* Sma
 size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype, size_t limit) {
   size_t b = 0;
   auto most = [&](size_t v) { b = v > b ? v : b; };
-  most(gen_grad_bytes(st, h, limit));
-  most(gen_grad_bytes(st, d, limit));
+  most(gen_grad_bytes(st, d, h, limit));
   most(plan_gemm(st, T, d, h, dtype, limit).part_bytes);
   most(plan_gemm(st, T, h, d, dtype, limit).part_bytes);
   return b;
@@ -1041,14 +1018,38 @@ hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M
                 : gemm_n<MLORA_MAX_GROUP>(n, ops, dtype, C, M, N, nn, st, scratch, scratch_bytes, stream);
 }
 
-hipError_t general_dB(const CallCtx& c, const void* Z, const void* dY, const OutTable& dB, int accumulate, float* scratch,
-                      size_t scratch_bytes) {
-  return grad_any(c, dY, c.d, Z, dB, accumulate, false, scratch, scratch_bytes);
-}
-
-hipError_t general_dA(const CallCtx& c, const void* X, const void* G, const OutTable& dA, int accumulate, float* scratch,
-                      size_t scratch_bytes) {
-  return grad_any(c, X, c.h, G, dA, accumulate, true, scratch, scratch_bytes);
+hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G,
+                         const OutTable* dA, int accumulate, float* scratch, size_t scratch_bytes) {
+  if (c.K == 0) return hipSuccess;
+  const int wide_b = c.d, wide_a = dA != nullptr ? c.h : 0;
+  // (planned for both outputs, so that the scratch suffices for either)
+  const int splits = gen_grad_splits(c.st, wide_b, c.h, scratch != nullptr ? scratch_bytes : 0);
+  size_t rtotal = 0;
+  for (int k = 0; k < c.K; ++k) rtotal += c.st.rank[k];
+  GenGradArgs b, a;
+  auto fill = [&](GenGradArgs& g, const void* big, int wide, const void* small, const OutTable& out, float* part) {
+    g.Big = big;
+    g.Small = small;
+    g.wide = wide;
+    g.ldz = c.ldz;
+    g.K = c.K;
+    g.accumulate = accumulate;
+    g.chunks = (wide + 255) / 256;
+    g.splits = splits;
+    g.part_step = rtotal * ((size_t)wide_b + wide_a);
+    g.part = part;
+    for (int k = 0; k <= kMaxK; ++k) g.off[k] = c.st.off[k];
+    for (int k = 0; k < kMaxK; ++k) g.rank[k] = (unsigned char)c.st.rank[k];
+    g.out = out;
+    return c.K * g.chunks * splits;
+  };
+  const int blocks_b = fill(b, dY, wide_b, Z, dB, scratch);
+  const int blocks_a = dA != nullptr ? fill(a, X, wide_a, G, *dA, scratch + (scratch ? rtotal * wide_b : 0)) : (a = b, 0);
+  if (c.dtype == MLORA_F32) launch_grads<float>(b, a, blocks_b, blocks_b + blocks_a, c.ldz, c.stream);
+  else launch_grads<bf16>(b, a, blocks_b, blocks_b + blocks_a, c.ldz, c.stream);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || splits == 1) return e;
+  return grad_reduce(c.st, scratch, splits, wide_b, dB, wide_a, dA != nullptr ? *dA : dB, accumulate, c.stream);
 }
 
 }  // namespace mlora

@@ -92,9 +92,10 @@ struct GradArgs {
   OutTable out[NP];
   int accumulate, chunks;
   // splits > 1 (NP == 1 only): a task's tokens are cut into `splits` ranges, one block each;
-  // block (task k, range s) overwrites its partial sums at part + (s * rtotal + rbase_k) * wide
+  // block (task k, range s) overwrites its partial sums at part + s * part_step + rbase_k * wide
   // (same element order as the output), and k_grad_reduce adds the ranges in order
-  int splits, rtotal;
+  int splits;
+  size_t part_step;
   float* part;
 };
 
@@ -525,30 +526,26 @@ __global__ __launch_bounds__(256) void k_lowrank_mfma_splitk(const RowsArgs<1> r
 // Block: one task, 128 columns of Big, all its tokens in tiles of 64; 4 waves x 32 columns.
 // The whole reduction of an output element happens inside one block: deterministic, no atomics.
 // ------------------------------------------------------------------------------------------
+template <int NQ, int NS, int NP>
+struct GradSmem {
+  static constexpr int BIG = 64 * 128 * 2;             // 64 tokens x 128 columns
+  // 64 tokens x ldz x 2 B, ldz <= 32 NQ, followed by 64 zero bytes (where lanes beyond the tile's
+  // columns point), at a multiple of 1 KiB
+  static constexpr int SBYTES = NQ * 32 * 128, SREG = SBYTES + 1024;
+  __attribute__((aligned(1024))) char big[NS][BIG];
+  __attribute__((aligned(1024))) char small[NS][NP * SREG];
+};
 template <bool WIDE_FIRST, int NQ, int NS, int NP>
-__global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
+__device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, GradSmem<NQ, NS, NP>& sm) {
   constexpr int WC = 128;
-  constexpr int SBYTES = NQ * 32 * 128;  // 64 tokens x ldz x 2 B, ldz <= 32 NQ
-  // a small-operand tile is followed by 64 zero bytes: where lanes beyond the tile's columns point
-  constexpr int SREG = SBYTES + 1024;    // per projection; keeps every 1 KiB load slot aligned
-  __shared__ __attribute__((aligned(1024))) char sB0[64 * WC * 2];
-  __shared__ __attribute__((aligned(1024))) char sB1[64 * WC * 2];
-  __shared__ __attribute__((aligned(1024))) char sB2[64 * WC * 2];
-  __shared__ __attribute__((aligned(1024))) char sB3[NS > 3 ? 64 * WC * 2 : 16];
-  __shared__ __attribute__((aligned(1024))) char sS0[NP * SREG];
-  __shared__ __attribute__((aligned(1024))) char sS1[NP * SREG];
-  __shared__ __attribute__((aligned(1024))) char sS2[NP * SREG];
-  __shared__ __attribute__((aligned(1024))) char sS3[NS > 3 ? NP * SREG : 64];
-  static_assert(NS == 3 || NS == 4, "ring depth");
+  constexpr int SBYTES = GradSmem<NQ, NS, NP>::SBYTES, SREG = GradSmem<NQ, NS, NP>::SREG;
   static_assert(WIDE_FIRST || NP == 1, "shared-input form exists for dA only");
-  char* const sB[4] = {sB0, sB1, sB2, sB3};
-  char* const sS[4] = {sS0, sS1, sS2, sS3};
 
   const bf16* __restrict__ Big = ga.Big;
   const int wide = ga.wide;
-  const int ch = blockIdx.x % ga.chunks;
-  const int sp = (blockIdx.x / ga.chunks) % ga.splits;
-  const int k = blockIdx.x / (ga.chunks * ga.splits);
+  const int ch = bid % ga.chunks;
+  const int sp = (bid / ga.chunks) % ga.splits;
+  const int k = bid / (ga.chunks * ga.splits);
   const int col0 = ch * WC;
   int lo = ga.off[k], hi = ga.off[k + 1];
   if (ga.splits > 1) {
@@ -564,7 +561,7 @@ __global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
 #pragma unroll
     for (int s_ = 0; s_ < NS; ++s_)
 #pragma unroll
-      for (int p = 0; p < NP; ++p) reinterpret_cast<int*>(sS[s_] + p * SREG + SBYTES)[tid] = 0;
+      for (int p = 0; p < NP; ++p) reinterpret_cast<int*>(sm.small[s_] + p * SREG + SBYTES)[tid] = 0;
   }
 
   // Big tile: 64 token rows x 256 B; wave instruction w covers rows 4w..4w+3
@@ -674,7 +671,7 @@ __global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
   __syncthreads();  // the zero pads
 #pragma unroll
   for (int s_ = 0; s_ < NS - 1; ++s_)
-    if (s_ < KT) issue(s_, sB[s_], sS[s_]);
+    if (s_ < KT) issue(s_, sm.big[s_], sm.small[s_]);
   for (int kt0 = 0; kt0 < KT; kt0 += NS) {
 #pragma unroll
     for (int s_ = 0; s_ < NS; ++s_) {
@@ -685,9 +682,9 @@ __global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
         else
           wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
-        if (kt + NS - 1 < KT) issue(kt + NS - 1, sB[(s_ + NS - 1) % NS], sS[(s_ + NS - 1) % NS]);
+        if (kt + NS - 1 < KT) issue(kt + NS - 1, sm.big[(s_ + NS - 1) % NS], sm.small[(s_ + NS - 1) % NS]);
         const int left = tk - kt * 64;
-        compute(sB[s_], sS[s_], left < 64 ? left : 64);
+        compute(sm.big[s_], sm.small[s_], left < 64 ? left : 64);
       }
     }
   }
@@ -700,7 +697,7 @@ __global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
     if (NP == 1 && ga.splits > 1) {
       int rbase = 0;
       for (int kk = 0; kk < k; ++kk) rbase += ga.rank[0][kk];
-      o = ga.part + ((size_t)sp * ga.rtotal + rbase) * wide;
+      o = ga.part + sp * ga.part_step + (size_t)rbase * wide;
       accumulate = 0;
     }
     if (WIDE_FIRST) {
@@ -742,29 +739,48 @@ __global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
   }
 }
 
-// Adds the token ranges' partial sums of k_grad_mfma in range order (deterministic) into the
-// tasks' outputs.  One thread per output element; `total` = rtotal * wide elements.
+// dA of projections that share their input
+template <int NQ, int NS, int NP>
+__global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
+  __shared__ GradSmem<NQ, NS, NP> sm;
+  grad_body<true, NQ, NS, NP>(ga, blockIdx.x, sm);
+}
+// dB (the first blocks_b blocks: dY has just been read for G) and dA of one call
+template <int NQ, int NS>
+__global__ __launch_bounds__(256) void k_grad_pair(const GradArgs<1> b, const GradArgs<1> a, int blocks_b) {
+  __shared__ GradSmem<NQ, NS, 1> sm;
+  if ((int)blockIdx.x < blocks_b) grad_body<false, NQ, NS, 1>(b, blockIdx.x, sm);
+  else grad_body<true, NQ, NS, 1>(a, blockIdx.x - blocks_b, sm);
+}
+
+// Adds the token ranges' partial sums in range order (deterministic) into the tasks' outputs.  One
+// thread per output element; a range holds the tasks' dB, then their dA (part_step elements in all).
 struct ReduceArgs {
   const float* part;
-  int splits, rtotal, wide, K, accumulate;
+  size_t part_step;
+  int splits, wide_b, wide_a, rtotal, K, accumulate;
   unsigned char rank[kMaxK];
-  OutTable out;
+  OutTable out_b, out_a;
 };
 __global__ __launch_bounds__(256) void k_grad_reduce(const ReduceArgs a) {
-  const size_t total = (size_t)a.rtotal * a.wide;
-  const size_t g = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (g >= total) return;
+  const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= a.part_step) return;
   float sum = 0.f;
-  for (int s_ = 0; s_ < a.splits; ++s_) sum += a.part[(size_t)s_ * total + g];
+#pragma unroll 4
+  for (int s_ = 0; s_ < a.splits; ++s_) sum += a.part[s_ * a.part_step + e];
+  const size_t nb = (size_t)a.rtotal * a.wide_b;
+  const bool is_b = e < nb;
+  const size_t g = is_b ? e : e - nb;
+  const int wide = is_b ? a.wide_b : a.wide_a;
   // which task: element g lies in [rbase_k * wide, (rbase_k + r_k) * wide)
   size_t base = 0;
   int k = 0;
   for (; k < a.K; ++k) {
-    const size_t n = (size_t)a.rank[k] * a.wide;
+    const size_t n = (size_t)a.rank[k] * wide;
     if (g < base + n) break;
     base += n;
   }
-  float* dst = a.out.p[k] + (g - base);
+  float* dst = (is_b ? a.out_b.p[k] : a.out_a.p[k]) + (g - base);
   *dst = a.accumulate ? *dst + sum : sum;
 }
 
@@ -917,11 +933,11 @@ hipError_t launch_rows(const RowsArgs<NP>& a, int nq, int tm, int blocks, hipStr
   return launch_rows_tm<KMAJOR, 4, NP>(a, tm, blocks, s);
 }
 
-template <bool WIDE_FIRST, int NQ, int NP>
+template <int NQ, int NP>
 hipError_t launch_grad_one(const GradArgs<NP>& a, int blocks, hipStream_t s) {
   if constexpr (NP * NQ <= 8) {
     const int slot = profile_begin(kProfileGrad, grad_bytes(a), s);
-    hipLaunchKernelGGL((k_grad_mfma<WIDE_FIRST, NQ, kRing, NP>), dim3(blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_grad_mfma<NQ, kRing, NP>), dim3(blocks), dim3(256), 0, s, a);
     const hipError_t e = hipGetLastError();
     profile_end(slot, s);
     return e;
@@ -930,11 +946,11 @@ hipError_t launch_grad_one(const GradArgs<NP>& a, int blocks, hipStream_t s) {
   }
 }
 
-template <bool WIDE_FIRST, int NP>
+template <int NP>
 hipError_t launch_grad(const GradArgs<NP>& a, int nq, int blocks, hipStream_t s) {
-  if (nq == 1) return launch_grad_one<WIDE_FIRST, 1, NP>(a, blocks, s);
-  if (nq == 2) return launch_grad_one<WIDE_FIRST, 2, NP>(a, blocks, s);
-  return launch_grad_one<WIDE_FIRST, 4, NP>(a, blocks, s);
+  if (nq == 1) return launch_grad_one<1, NP>(a, blocks, s);
+  if (nq == 2) return launch_grad_one<2, NP>(a, blocks, s);
+  return launch_grad_one<4, NP>(a, blocks, s);
 }
 
 template <int NP>
@@ -979,9 +995,9 @@ hipError_t grad_group(const LowrankGroupItem* it, const SegTable& st, const bf16
   a.accumulate = accumulate;
   a.chunks = (wide + 127) / 128;
   a.splits = 1;
-  a.rtotal = 0;
+  a.part_step = 0;
   a.part = nullptr;
-  return launch_grad<true, NP>(a, nq, st.K * a.chunks, s);
+  return launch_grad<NP>(a, nq, st.K * a.chunks, s);
 }
 
 }  // namespace
@@ -1015,78 +1031,93 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
   return a_major ? launch_rows<true, 1>(a, nq, tm, blocks, c.stream) : launch_rows<false, 1>(a, nq, tm, blocks, c.stream);
 }
 
-// dA_k = x_k^T G (wide_first = true; Big = X [T,h], Small = G) or dB_k = Z^T dy_k (Big = dY [T,d], Small = Z).
-// Token ranges per task for the gradient kernels: 1 when tasks x column blocks fill the chip,
+// Token ranges per task for the gradient kernels: 1 when tasks x column blocks (of 128) fill the chip,
 // otherwise enough ranges for about two blocks per CU (at most 16, at least 256 tokens each), as far
 // as their partial sums stay within `limit` bytes.
-int grad_splits(const SegTable& st, int wide, size_t limit) {
-  const int blocks = st.K * ((wide + 127) / 128);
+int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit) {
+  const int blocks = st.K * ((wide_b + 127) / 128 + (wide_a + 127) / 128);
   if (st.K == 0 || blocks >= 384) return 1;
   int longest = 0;
-  for (int k = 0; k < st.K; ++k) longest = st.off[k + 1] - st.off[k] > longest ? st.off[k + 1] - st.off[k] : longest;
+  size_t rtotal = 0;
+  for (int k = 0; k < st.K; ++k) {
+    longest = st.off[k + 1] - st.off[k] > longest ? st.off[k + 1] - st.off[k] : longest;
+    rtotal += st.rank[k];
+  }
   int s = (512 + blocks - 1) / blocks;
   s = s < 16 ? s : 16;
   s = s < longest / 256 ? s : longest / 256;
-  size_t rtotal = 0;
-  for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
-  while (s > 1 && (size_t)s * rtotal * wide * sizeof(float) > limit) --s;
+  while (s > 1 && (size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float) > limit) --s;
   return s > 1 ? s : 1;
 }
 
-// Bytes of partial sums grad_mfma needs for an output of `wide` columns (0 when it does not split).
-size_t grad_partial_bytes(const SegTable& st, int wide, size_t limit) {
-  const int s = grad_splits(st, wide, limit);
+// Bytes of partial sums of a launch for outputs of wide_b and wide_a columns (0 when it does not split).
+size_t grad_partial_bytes(const SegTable& st, int wide_b, int wide_a, size_t limit) {
+  const int s = grad_splits(st, wide_b, wide_a, limit);
   if (s <= 1) return 0;
   size_t rtotal = 0;
   for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
-  return align_up((size_t)s * rtotal * wide * sizeof(float), 256);
+  return align_up((size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float), 256);
 }
 
-hipError_t grad_mfma(const CallCtx& c, const bf16* Big, int wide, const bf16* Small, const OutTable& out,
-                     int accumulate, bool wide_first, float* partial, size_t limit) {
+// dB_k = Z^T dy_k and, unless dA is NULL, dA_k = x_k^T G, in one launch (and one that adds the token
+// ranges where there are several): two launches each before, which cost few tokens 10 us of 108
+// (771 tokens, 2048 -> 5632) and 8192 tokens of 4096 features 40 us instead of 33.
+hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const OutTable& dB, const bf16* X, const bf16* G,
+                      const OutTable* dA, int accumulate, float* partial, size_t limit) {
   if (c.K == 0) return hipSuccess;
-  GradArgs<1> a;
-  a.Big = Big;
-  a.wide = wide;
-  a.T = c.T;
-  a.K = c.st.K;
-  for (int k = 0; k <= kMaxK; ++k) a.off[k] = c.st.off[k];
-  a.Small[0] = Small;
-  a.ldz[0] = c.ldz;
-  for (int k = 0; k < kMaxK; ++k) a.rank[0][k] = (unsigned char)c.st.rank[k];
-  a.out[0] = out;
-  a.accumulate = accumulate;
-  a.chunks = (wide + 127) / 128;
-  a.splits = partial != nullptr ? grad_splits(c.st, wide, limit) : 1;
-  a.rtotal = 0;
-  for (int k = 0; k < c.K; ++k) a.rtotal += c.st.rank[k];
-  a.part = partial;
+  const int wide_b = c.d, wide_a = dA != nullptr ? c.h : 0;
+  const int splits = partial != nullptr ? grad_splits(c.st, wide_b, wide_a, limit) : 1;
+  size_t rtotal = 0;
+  for (int k = 0; k < c.K; ++k) rtotal += c.st.rank[k];
+  GradArgs<1> b, a;
+  auto fill = [&](GradArgs<1>& g, const bf16* big, int wide, const bf16* small, const OutTable& out, float* part) {
+    g.Big = big;
+    g.wide = wide;
+    g.T = c.T;
+    g.K = c.st.K;
+    for (int k = 0; k <= kMaxK; ++k) g.off[k] = c.st.off[k];
+    g.Small[0] = small;
+    g.ldz[0] = c.ldz;
+    for (int k = 0; k < kMaxK; ++k) g.rank[0][k] = (unsigned char)c.st.rank[k];
+    g.out[0] = out;
+    g.accumulate = accumulate;
+    g.chunks = (wide + 127) / 128;
+    g.splits = splits;
+    g.part_step = rtotal * ((size_t)wide_b + wide_a);
+    g.part = part;
+    return c.K * g.chunks * splits;
+  };
+  const int blocks_b = fill(b, dY, wide_b, Z, dB, partial);
+  const int blocks_a = dA != nullptr ? fill(a, X, wide_a, G, *dA, partial + (partial ? rtotal * wide_b : 0)) : (a = b, 0);
   const int nq = nq_of(c.ldz);
-  const int blocks = c.K * a.chunks * a.splits;
-  hipError_t e =
-      wide_first ? launch_grad<true, 1>(a, nq, blocks, c.stream) : launch_grad<false, 1>(a, nq, blocks, c.stream);
-  if (e != hipSuccess || a.splits == 1) return e;
-  // timed with the gradient kernels (its time counts, the launch adds no algorithmic bytes)
-  const int slot = profile_begin(kProfileGrad, 0.0, c.stream);
-  e = grad_reduce(c.st, partial, a.splits, wide, out, accumulate, c.stream);
+  const int slot = profile_begin(kProfileGrad, grad_bytes(b) + (dA != nullptr ? grad_bytes(a) : 0.0), c.stream);
+  const dim3 grid((unsigned)(blocks_b + blocks_a));
+  if (nq == 1) hipLaunchKernelGGL((k_grad_pair<1, kRing>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  else if (nq == 2) hipLaunchKernelGGL((k_grad_pair<2, kRing>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  else hipLaunchKernelGGL((k_grad_pair<4, kRing>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  hipError_t e = hipGetLastError();
+  if (e == hipSuccess && splits > 1)
+    e = grad_reduce(c.st, partial, splits, wide_b, dB, wide_a, dA != nullptr ? *dA : dB, accumulate, c.stream);
   profile_end(slot, c.stream);
   return e;
 }
 
-hipError_t grad_reduce(const SegTable& st, const float* partial, int splits, int wide, const OutTable& out, int accumulate,
-                       hipStream_t stream) {
+hipError_t grad_reduce(const SegTable& st, const float* partial, int splits, int wide_b, const OutTable& dB, int wide_a,
+                       const OutTable& dA, int accumulate, hipStream_t stream) {
   ReduceArgs r;
   r.part = partial;
   r.splits = splits;
   r.rtotal = 0;
   for (int k = 0; k < st.K; ++k) r.rtotal += st.rank[k];
-  r.wide = wide;
+  r.wide_b = wide_b;
+  r.wide_a = wide_a;
+  r.part_step = (size_t)r.rtotal * ((size_t)wide_b + wide_a);
   r.K = st.K;
   r.accumulate = accumulate;
   for (int k = 0; k < kMaxK; ++k) r.rank[k] = (unsigned char)st.rank[k];
-  r.out = out;
-  const size_t total = (size_t)r.rtotal * wide;
-  hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, stream, r);
+  r.out_b = dB;
+  r.out_a = dA;
+  hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((r.part_step + 255) / 256)), dim3(256), 0, stream, r);
   return hipGetLastError();
 }
 

@@ -133,35 +133,36 @@ bool mfma_lowrank_applies(const mlora_problem* p) { return !(g_kernel_path.load(
 // Scratch behind the low-rank intermediates: partial sums of token-split gradient launches and
 // partial tiles of contraction-split base products (0 when nothing splits).  A function of the
 // sizes alone: a size query must not change its answer with the addresses, so it covers whichever
-// kernels the addresses will allow.  Splitting is optional: `limit` bounds what it may ask for, so
-// that a problem whose intermediates fit the static scratch array fits it with its partial sums too
-// (`grad_limit`: unbounded for the aligned gradient kernels at ranks that are multiples of 8).
+// kernels the addresses will allow.  Splitting is optional, and `limit` bounds what it may use: a
+// problem whose intermediates fit the static scratch array has to fit it with its partial sums too.
+// (Aligned shapes with whole-chunk ranks have always asked for `reserve`, the sums of one gradient at
+// a time; the limit lets them in or keeps them out of the static scratch by that size.)
 struct Scratch {
-  size_t limit, grad_limit, bytes;
+  size_t limit, bytes;
 };
 Scratch plan_scratch(const mlora_problem* p, const CallCtx& c) {
-  Scratch s{0, 0, 0};
+  Scratch s{0, 0};
   if (p->T < 1) return s;
   const size_t z = lowrank_bytes(p), fixed = (size_t)MLORA_STATIC_SCRATCH_BYTES;
-  const bool aligned = mfma_sizes_ok(p) && p->K > 0, unbounded = aligned && whole_chunk_ranks(p);
-  auto grad_bytes = [&](size_t limit) {
-    const size_t a = grad_partial_bytes(c.st, c.h, limit), b = grad_partial_bytes(c.st, c.d, limit);
-    return a > b ? a : b;
-  };
-  if (unbounded) s.bytes = grad_bytes(SIZE_MAX);
-  s.limit = z + s.bytes <= fixed ? fixed - z : 2 * fixed;
-  s.grad_limit = unbounded ? SIZE_MAX : s.limit;
-  if (aligned && !unbounded) s.bytes = grad_bytes(s.limit);
+  const bool aligned = mfma_sizes_ok(p), grads = aligned && p->K > 0;
   auto most = [&](size_t b) { s.bytes = b > s.bytes ? b : s.bytes; };
-  most(general_scratch_bytes(c.st, c.T, c.h, c.d, c.dtype, s.limit));
-  if (mfma_sizes_ok(p)) {
+  if (grads && whole_chunk_ranks(p)) {
+    most(grad_partial_bytes(c.st, c.h, 0, SIZE_MAX));
+    most(grad_partial_bytes(c.st, c.d, 0, SIZE_MAX));
+  }
+  const size_t reserve = s.bytes;
+  s.limit = z + reserve <= fixed ? fixed - z : (reserve > 2 * fixed ? reserve : 2 * fixed);
+  if (grads) {
+    most(grad_partial_bytes(c.st, c.d, c.h, s.limit));
+    most(grad_partial_bytes(c.st, c.d, 0, s.limit));     // a group's dA is a launch of its own
+    most(rows_partial_bytes(c.st, c.h, c.ldz, s.limit));
+    most(rows_partial_bytes(c.st, c.d, c.ldz, s.limit));
+  }
+  if (aligned) {
     most(gemm_partial_bytes(c.st, c.T, c.d, c.h, s.limit));
     most(gemm_partial_bytes(c.st, c.T, c.h, c.d, s.limit));
-    if (p->K > 0) {
-      most(rows_partial_bytes(c.st, c.h, c.ldz, s.limit));
-      most(rows_partial_bytes(c.st, c.d, c.ldz, s.limit));
-    }
   }
+  most(general_scratch_bytes(c.st, c.T, c.h, c.d, c.dtype, s.limit));
   return s;
 }
 size_t scratch_bytes(const mlora_problem* p) {
@@ -228,13 +229,12 @@ hipError_t adapter_grads_impl(const mlora_problem* p, const CallCtx& c, const vo
   hipError_t e;
   if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(dY) && aligned16(Z) && aligned16(G)) {
     e = lowrank_rows_mfma(c, (const bf16*)dY, c.d, (bf16*)G, c.B, false, partial, s.limit);
-    if (e == hipSuccess) e = grad_mfma(c, (const bf16*)dY, c.d, (const bf16*)Z, tb, accumulate, false, partial, s.grad_limit);
-    if (e == hipSuccess && !skip_dA)
-      e = grad_mfma(c, (const bf16*)X, c.h, (const bf16*)G, ta, accumulate, true, partial, s.grad_limit);
+    if (e == hipSuccess)
+      e = grads_mfma(c, (const bf16*)dY, (const bf16*)Z, tb, (const bf16*)X, (const bf16*)G, skip_dA ? nullptr : &ta,
+                     accumulate, partial, s.limit);
   } else {
     e = general_G(c, dY, G);
-    if (e == hipSuccess) e = general_dB(c, Z, dY, tb, accumulate, partial, s.limit);
-    if (e == hipSuccess && !skip_dA) e = general_dA(c, X, G, ta, accumulate, partial, s.limit);
+    if (e == hipSuccess) e = general_grads(c, dY, Z, tb, X, G, skip_dA ? nullptr : &ta, accumulate, partial, s.limit);
   }
   return e;
 }

@@ -80,10 +80,9 @@ struct GenOperands {
 // C = sum over the n <= MLORA_MAX_GROUP operand pairs of A op(W) + rows_k(L R_k)
 hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st,
                         float* scratch, size_t scratch_bytes, hipStream_t stream);
-hipError_t general_dB(const CallCtx& c, const void* Z, const void* dY, const OutTable& dB, int accumulate, float* scratch,
-                      size_t scratch_bytes);
-hipError_t general_dA(const CallCtx& c, const void* X, const void* G, const OutTable& dA, int accumulate, float* scratch,
-                      size_t scratch_bytes);
+// dB_k = Z^T dy_k and, unless dA is NULL, dA_k = x_k^T G
+hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G,
+                         const OutTable* dA, int accumulate, float* scratch, size_t scratch_bytes);
 
 // gemm_mfma.hip : bf16 MFMA GEMM with the LoRA term as extra contraction steps
 bool gemm_mfma_ok(int M, int N, int Kd);
@@ -122,15 +121,17 @@ hipError_t w8_dequantize(const int8_t* Wq, const float* c, int dtype, int h, int
 size_t rows_partial_bytes(const SegTable& st, int inner, int ldz, size_t limit);
 hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M, bool a_major,
                              float* partial, size_t limit);
-// `partial`: grad_partial_bytes(c.st, wide, limit) bytes of scratch for calls whose tasks x column
-// blocks do not fill the chip (the tokens of a task are then split over blocks); NULL = never split.
-int grad_splits(const SegTable& st, int wide, size_t limit);
-size_t grad_partial_bytes(const SegTable& st, int wide, size_t limit);
-// adds `splits` ranges of partial sums ([range][sum of ranks][wide]) in order into the tasks' outputs
-hipError_t grad_reduce(const SegTable& st, const float* partial, int splits, int wide, const OutTable& out, int accumulate,
-                       hipStream_t stream);
-hipError_t grad_mfma(const CallCtx& c, const bf16* Big, int wide, const bf16* Small, const OutTable& out,
-                     int accumulate, bool wide_first, float* partial, size_t limit);
+// Gradients dB (wide_b = d columns) and dA (wide_a = h columns; 0 = not wanted) of one call.  `partial`:
+// grad_partial_bytes(..) bytes of scratch for calls whose tasks x column blocks do not fill the chip
+// (the tokens of a task are then split over blocks); NULL = never split.
+int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit);
+size_t grad_partial_bytes(const SegTable& st, int wide_b, int wide_a, size_t limit);
+hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const OutTable& dB, const bf16* X, const bf16* G,
+                      const OutTable* dA, int accumulate, float* partial, size_t limit);
+// adds `splits` ranges of partial sums ([range][sum of ranks][wide_b], then [sum of ranks][wide_a]) in
+// order into the tasks' outputs
+hipError_t grad_reduce(const SegTable& st, const float* partial, int splits, int wide_b, const OutTable& dB, int wide_a,
+                       const OutTable& dA, int accumulate, hipStream_t stream);
 
 // One projection of a group that shares its input, for the two shared-input kernels:
 // rows: Z_p = s_pk x_k A_pk (M = A_pk, output rows_out [T, ldz]); grad: dA_pk = x_k^T G_p
