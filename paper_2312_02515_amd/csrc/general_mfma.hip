@@ -510,30 +510,23 @@ struct GenRowsArgs {
   PtrTable M;
 };
 
+// Adds a stretch of contraction to a wave's accumulators (16 RM rows x 16 VW columns): rows x[i] of
+// `inner` elements times the columns col0 .. of the small operand,
+//   KMAJOR = true : M [inner, stride], `ncols` columns in all      KMAJOR = false: M [ncols, stride]
+// Each of the NW waves takes every NW-th run of U groups.
+template <int VW>
+__device__ __forceinline__ int first_column(int i16, int col0, int ncols) {   // k-major: first column of lane i16
+  const int q = col0 + VW * i16;
+  return q < ncols - VW ? q : ncols - VW;
+}
 template <typename T, int VW, int RM, int NW, bool KMAJOR>
-__device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, int hi, float* red) {
+__device__ __forceinline__ void accumulate_rows(f32x4 (&acc)[RM][VW], const T* const (&x)[RM], int inner, const T* M, size_t stride,
+                                                int col0, int ncols, int wave, int lane) {
   constexpr int V = kV<T>, STEP = 4 * V;             // contraction indices per MFMA group (64 bytes)
   constexpr int U = VW <= 2 ? 4 : (VW == 4 ? 2 : 1);
   typedef T Cols __attribute__((ext_vector_type(VW), aligned(sizeof(T))));
-  const int r = a.rank[k], inner = a.inner;
-  const T* Mk = static_cast<const T*>(a.M.p[k]);
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kg = lane >> 4;
-  auto first_col = [&](int i16) { return VW * i16 < r - VW ? VW * i16 : r - VW; };   // k-major
-  const int q0 = first_col(l16);
-
-  const T* x[RM];
-#pragma unroll
-  for (int i = 0; i < RM; ++i) {
-    const int row = lo + 16 * i + l16;
-    x[i] = static_cast<const T*>(a.In) + (size_t)(row < hi ? row : hi - 1) * inner;
-  }
-  f32x4 acc[RM][VW];
-#pragma unroll
-  for (int i = 0; i < RM; ++i)
-#pragma unroll
-    for (int j = 0; j < VW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int q0 = first_column<VW>(l16, col0, ncols);
 
   // operand pieces of contraction indices k0 + kg V ..; `tail`: some lie beyond `inner`
   struct Small {
@@ -547,12 +540,12 @@ __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, i
         u32x4 v[VW];
         T e[VW][V];
       } u;
-      const T* p = Mk + (size_t)kk * r + q0;
+      const T* p = M + (size_t)kk * stride + q0;
 #pragma unroll
       for (int e = 0; e < V; ++e) {
         Cols c;
         if (!tail || kk + e < inner) {
-          c = *reinterpret_cast<const Cols*>(p + (size_t)e * r);
+          c = *reinterpret_cast<const Cols*>(p + (size_t)e * stride);
         } else {
 #pragma unroll
           for (int f = 0; f < VW; ++f) c[f] = T(0.f);
@@ -565,8 +558,8 @@ __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, i
     } else {
 #pragma unroll
       for (int f = 0; f < VW; ++f) {
-        const int q = 16 * f + l16;
-        o.v[f] = load_piece<T>(Mk + (size_t)(q < r ? q : r - 1) * inner, kk, tail ? inner : kk + V);
+        const int q = col0 + 16 * f + l16;
+        o.v[f] = load_piece<T>(M + (size_t)(q < ncols ? q : ncols - 1) * stride, kk, tail ? inner : kk + V);
         if (tail) o.v[f] = tail_shift<T>(o.v[f], kk, inner);
       }
     }
@@ -608,11 +601,16 @@ __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, i
 #pragma unroll
       for (int i = 0; i < RM; ++i) mma16(acc[i][j], xf[i], sv.v[j], T{});
   }
+}
 
-  // the upper half of the waves hands its sums to the lower half, which adds them and hands on its
-  // own; the block adds those in wave order.  acc[i][j]: lane holds operand column l16 of group j
-  // and rows 16 i + 4 kg + e.
+// The waves' sums through LDS: the upper half of the waves hands its sums to the lower half, which adds
+// them and hands on its own; element t of the block's sum is then the NW / 2 slots red[w * FR + t] in
+// wave order.  acc[i][j]: lane holds operand column l16 of group j and rows 16 i + 4 kg + e; t holds
+// group (i, j) in its upper bits, then the row of 16 and the operand column.
+template <int VW, int RM, int NW>
+__device__ __forceinline__ void share_sums(const f32x4 (&acc)[RM][VW], float* red, int wave, int lane) {
   constexpr int H = NW / 2, FR = RM * VW * 256;
+  const int l16 = lane & 15, kg = lane >> 4;
   auto slot = [&](int w, int i, int j, int e) -> float& { return red[w * FR + (i * VW + j) * 256 + (4 * kg + e) * 16 + l16]; };
   if (wave >= H) {
 #pragma unroll
@@ -632,14 +630,40 @@ __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, i
         for (int e = 0; e < 4; ++e) slot(wave, i, j, e) = acc[i][j][e] + slot(wave, i, j, e);
   }
   __syncthreads();
+}
+template <int FR, int H>
+__device__ __forceinline__ float shared_sum(const float* red, int t) {
+  float sum = red[t];
+#pragma unroll
+  for (int w = 1; w < H; ++w) sum += red[w * FR + t];
+  return sum;
+}
+
+template <typename T, int VW, int RM, int NW, bool KMAJOR>
+__device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, int hi, float* red) {
+  const int r = a.rank[k], inner = a.inner;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const T* x[RM];
+#pragma unroll
+  for (int i = 0; i < RM; ++i) {
+    const int row = lo + 16 * i + (lane & 15);
+    x[i] = static_cast<const T*>(a.In) + (size_t)(row < hi ? row : hi - 1) * inner;
+  }
+  f32x4 acc[RM][VW];
+#pragma unroll
+  for (int i = 0; i < RM; ++i)
+#pragma unroll
+    for (int j = 0; j < VW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  accumulate_rows<T, VW, RM, NW, KMAJOR>(acc, x, inner, static_cast<const T*>(a.M.p[k]), KMAJOR ? r : inner, 0, r, wave, lane);
+  share_sums<VW, RM, NW>(acc, red, wave, lane);
+  constexpr int FR = RM * VW * 256;
   const float s = a.s[k];
   T* Out = static_cast<T*>(a.Out);
   for (int t = tid; t < FR; t += NW * 64) {
-    float sum = red[t];
-#pragma unroll
-    for (int w = 1; w < H; ++w) sum += red[w * FR + t];
+    const float sum = shared_sum<FR, NW / 2>(red, t);
     const int ij = t >> 8, i = ij / VW, j = ij % VW, i16 = t & 15;
-    const int row = lo + 16 * i + ((t >> 4) & 15), q = KMAJOR ? first_col(i16) + j : 16 * j + i16;
+    const int row = lo + 16 * i + ((t >> 4) & 15), q = KMAJOR ? first_column<VW>(i16, 0, r) + j : 16 * j + i16;
     if (row < hi && q < r) Out[(size_t)row * a.ldz + q] = from_f32<T>(sum * s);
   }
   const int pad = a.ldz - r;
@@ -674,6 +698,48 @@ __global__ __launch_bounds__(NW * 64, 4) void k_gen_rows(const GenRowsArgs a) {
   else if (r <= 32) rows_body<T, 2, RM, NW, KMAJOR>(a, k, lo, hi, red);
   else if (r <= 64) rows_body<T, 4, RM, NW, KMAJOR>(a, k, lo, hi, red);
   else if constexpr (RM == 1) rows_body<T, 8, RM, NW, KMAJOR>(a, k, lo, hi, red);   // (two row groups: ranks up to 64)
+}
+
+// ------------------------------------------------------------------------------------------
+// The base product of k_gen_gemm for small problems: block = 16 rows x 64 columns, its 8 waves split the
+// contraction as in k_gen_rows (LoRA term: a second stretch of it), operands straight from memory.
+// ------------------------------------------------------------------------------------------
+template <typename T, bool NN, int NSEG>
+__global__ __launch_bounds__(512, 4) void k_gen_skinny(const GenGemmArgs<NSEG> a) {
+  constexpr int NW = 8, VW = 4;
+  __shared__ float red[NW / 2 * VW * 256];
+  const int tm = blockIdx.x % a.tiles_m, tn = blockIdx.x / a.tiles_m;
+  const int N = a.N, col0 = tn * 16 * VW;
+  RowPiece p = find_piece(a, 16LL * tm);
+  if (p.n <= 0) return;
+  p.n = p.n < 16 ? p.n : 16;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15;
+  const size_t row = p.row + (l16 < p.n ? l16 : p.n - 1);
+  const int task = __builtin_amdgcn_readfirstlane(p.task);
+  f32x4 acc[1][VW];
+#pragma unroll
+  for (int j = 0; j < VW; ++j) acc[0][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int g = 0; g < NSEG; ++g) {
+    const int Kd = a.Kd[g];
+    if (Kd == 0) continue;
+    const T* const x[1] = {static_cast<const T*>(a.A[g]) + row * Kd};
+    accumulate_rows<T, VW, 1, NW, NN>(acc, x, Kd, static_cast<const T*>(a.W[g]), NN ? N : Kd, col0, N, wave, lane);
+    if (task >= 0) {
+      const int r = a.rank[g][task];
+      const T* const l[1] = {static_cast<const T*>(a.L[g]) + row * a.ldz[g]};
+      accumulate_rows<T, VW, 1, NW, NN>(acc, l, r, static_cast<const T*>(a.R[g].p[task]), NN ? N : r, col0, N, wave, lane);
+    }
+  }
+  share_sums<VW, 1, NW>(acc, red, wave, lane);
+  T* C = static_cast<T*>(a.C);
+  for (int t = tid; t < VW * 256; t += NW * 64) {
+    const float sum = shared_sum<VW * 256, NW / 2>(red, t);
+    const int j = t >> 8, i16 = t & 15, o = (t >> 4) & 15;
+    const int col = NN ? first_column<VW>(i16, col0, N) + j : col0 + 16 * j + i16;
+    if (o < p.n && col < N) C[(size_t)(p.row + o) * N + col] = from_f32<T>(sum);
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -873,17 +939,25 @@ long long virtual_rows(const SegTable& st, int M) {
   return mv;
 }
 
-// Tile size and contraction parts of one base product.  128 x 128 tiles once they give every CU a
+// Tile size and contraction parts of one base product.  Small problems (rows of up to 4 KB, up to 640 KB
+// of them over all blocks of 16 rows) run k_gen_skinny: with 64 x 64 tiles the few blocks walk the
+// contraction one tile after the other.  us, 64 x 64 tiles -> skinny: fp32 128 rows 256 x 256 10 -> 5,
+// 1024 x 1024 20 -> 15, 500 rows 512 x 512 16 -> 9; beyond the line: 128 rows, 4096 deep 31 -> 60,
+// 1000 rows 1024 x 1024 33 -> 43.  128 x 128 tiles once they give every CU a
 // block; below that 64 x 64, and the contraction cut into parts of at least 16 tiles until the
 // blocks fill two thirds of the chip's 512 block slots or the scratch is used up.
 struct GemmPlan {
-  bool small;
+  bool skinny, small;
   int tiles_m, tiles_n, parts;
   size_t part_bytes;
 };
 GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dtype, size_t scratch_limit) {
   const long long mv = virtual_rows(st, M);
   GemmPlan p;
+  p.skinny = false;
+  const long long units = (mv + 15) / 16 * ((N + 63) / 64), row_bytes = Kd_total * (dtype == MLORA_F32 ? 4 : 2);
+  if (N >= 4 && row_bytes <= 4096 && units * row_bytes <= 640 << 10)
+    return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1, 0};
   const long long t128 = ((mv + 127) / 128) * ((N + 127) / 128);
   p.small = t128 < 256;
   const int b = p.small ? 64 : 128;
@@ -908,7 +982,9 @@ hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch,
   a.parts = pl.parts;
   a.part = scratch;
   const dim3 grid((unsigned)(pl.tiles_m * pl.tiles_n * pl.parts));
-  if (pl.small)
+  if (pl.skinny)
+    hipLaunchKernelGGL((k_gen_skinny<T, NN, NSEG>), grid, dim3(512), 0, s, a);
+  else if (pl.small)
     hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG>), grid, dim3(256), 0, s, a);
   else
     hipLaunchKernelGGL((k_gen_gemm<T, 128, 128, NN, NSEG>), grid, dim3(256), 0, s, a);

@@ -35,6 +35,8 @@ def _inputs(T, h, d, tokens, ranks, dtype, lead=0, seed=0):
     (2200, 136, 2101, [1000, 0, 1150], [7, 64, 32], 25),  # 128 x 128 tiles, odd stride
     (16500, 41, 24, [9000, 7000], [4, 40], 300),          # 32 rows per low-rank block
     (700, 70, 514, [640], [9], 13),                       # token ranges; column groups of 64 that end early
+    (150, 515, 67, [20, 101], [100, 17], 12),             # 16-row blocks: runs, single groups and a tail
+    (49, 1021, 4, [16, 17], [1, 128], 3),                 # ... exactly one piece of columns
 ])
 def test_general_kernel_edges(case, dtype):
     T, h, d, tokens, ranks, lead = case
