@@ -143,8 +143,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   __shared__ __attribute__((aligned(1024))) char sA2[ABYTES];
   __shared__ __attribute__((aligned(1024))) char sB0[BBYTES];
   __shared__ __attribute__((aligned(1024))) char sB1[BBYTES];
+  // A half tile takes half as long, so its weight loads need two tiles of lead as well; 3 + 3 stages of
+  // 16 and 32 KiB fit.
+  __shared__ __attribute__((aligned(1024))) char sB2[HALF ? BBYTES : 16];
   char* const sA[3] = {sA0, sA1, sA2};
-  char* const sB[2] = {sB0, sB1};
+  char* const sB[3] = {sB0, sB1, sB2};
 
   // block -> tile.  Tiles are taken in a grouped order (8 row tiles x all column tiles per group,
   // column by column), cut into chunks of 32: a chunk is an 8 x 4 patch of output tiles sharing
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     // the next tile has landed (this wave's part), every fragment of this tile is in registers
     // (the weight fragments of this half tile stay in use until sub-step 3 re-reads them)
     if (abehind)
-      wait_vmcnt<LPA>();
+      wait_vmcnt<HALF ? PER_TILE : LPA>();
     else
       wait_vmcnt<0>();
     wait_lds();
@@ -508,14 +511,15 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
 #pragma unroll
       for (int idx = 0; idx < LPB; ++idx) issue_one(lc, LPA + idx, nullptr, sb);
     };
-    // tiles 0 and 1 whole and the A side of tile 2; the first reads need tile 0
+    // tiles 0 and 1 whole and the A side of tile 2 (HALF: all of it); the first reads need tile 0
     issue_a(base_ctx(0), sA[0]);
     issue_b(base_ctx(0), sB[0]);
     if (VT > 2) {
       issue_a(ctx_of(1), sA[1]);
       issue_b(ctx_of(1), sB[1]);
       issue_a(ctx_of(2), sA[2]);
-      wait_vmcnt<2 * LPA + LPB>();
+      if constexpr (HALF) issue_b(ctx_of(2), sB[2]);
+      wait_vmcnt<HALF ? 2 * PER_TILE : 2 * LPA + LPB>();
     } else if (VT > 1) {
       issue_a(ctx_of(1), sA[1]);
       issue_b(ctx_of(1), sB[1]);
@@ -544,13 +548,18 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     // (v is a multiple of 6 here.)  The up to seven base tiles left that still have all of the
     // above: the same straight-line code, with the stage addresses in registers
     auto stage_a = [&](int u) { return u % 3 == 0 ? sA0 : (u % 3 == 1 ? sA1 : sA2); };
-    auto stage_b = [&](int u) { return u % 2 == 0 ? sB0 : sB1; };
+    auto stage_b = [&](int u) {
+      if constexpr (HALF) return u % 3 == 0 ? sB0 : (u % 3 == 1 ? sB1 : sB2);
+      else return u % 2 == 0 ? sB0 : sB1;
+    };
+    constexpr int LEAD_B = HALF ? 3 : 2;
     for (; v + 3 < KT; ++v)
-      tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), yes, yes, base_ctx(v + 2), yes, base_ctx(v + 3), yes, yes);
+      tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), yes, yes, base_ctx(v + LEAD_B), yes, base_ctx(v + 3), yes,
+           yes);
     if constexpr (HALF) {
+      // (the last three: nothing left to load)
       for (; v < VT; ++v)
-        tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, base_ctx(v + 2), v + 3 < VT,
-             base_ctx(v + 3), v + 2 < VT, yes);
+        tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, no, none, no, none, v + 2 < VT, yes);
       break;
     }
     // the last base tiles and the LoRA tiles
@@ -615,9 +624,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       // fp32 partial tile, one KiB per fragment in lane order (k_gemm_reduce reads it back the same way)
       float* dst = ga.part + ((size_t)part * 2 * (total - ga.t0) + 2 * (t - ga.t0) + half) * (BM * BN) + lane * 4;
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
+      for (int i = 0; i < FM; ++i) {
+        if (frag_n(i / 2) == 0) break;   // pieces beyond the last row come last
 #pragma unroll
         for (int j = 0; j < FN; ++j) *(f32x4*)(dst + ((i * WAVES_N + wave) * FN + j) * 256) = acc[i][j];
+      }
       return;
     }
   }
