@@ -813,9 +813,10 @@ int pick_row_tile(const SegTable& st) {
 //     3072 x 4096 (12 tasks)  s x A 85 -> 25, s dy B^T 56 -> 22;  8192 x 4096  62 -> 33, 56 -> 33
 //   ranks up to 64:
 //     16448 x 11008  119 -> 90,  16448 x 4096  44 -> 38-40,  12288 x 4096  31 -> 26
+//     8192 x 4096, a forward and backward pass 474 -> 466 with two such products
 //     2048 x 11008, operands from HBM  30 -> 22 (from the Infinity Cache 21 -> 19)
-//   left alone: 32768 rows (64 against 70 with two ranges), up to 8192 rows of 4096 (the four-wave
-//   form: 8192 rows 21.5 against 21-22).
+//   left alone: 32768 rows (64 against 70 with two ranges), fewer than 4096 rows of 4096 features (the
+//   four-wave form takes less than two launches: 771 x 2048  9 against 12).
 struct RowsPlan {
   int tm, splits;
 };
@@ -827,7 +828,7 @@ RowsPlan plan_rows(const SegTable& st, int inner, int ldz, size_t limit) {
   if (nq_of(ldz) == 4) {
     pl.tm = 128;
     while (2 * pl.splits * b128 <= 256 && 8 * pl.splits <= KT && pl.splits < 16) pl.splits *= 2;
-  } else if (b32 > 256) {
+  } else if (b32 >= 128) {
     pl = RowsPlan{128, KT >= 128 ? 8 : 4};
   } else if (b32 >= 32 && KT >= 128) {
     pl = RowsPlan{64, 8};
@@ -1031,19 +1032,20 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
   return a_major ? launch_rows<true, 1>(a, nq, tm, blocks, c.stream) : launch_rows<false, 1>(a, nq, tm, blocks, c.stream);
 }
 
-// Token ranges per task for the gradient kernels: 1 when tasks x column blocks (of 128) fill the chip,
-// otherwise enough ranges for about two blocks per CU (at most 16, at least 256 tokens each), as far
-// as their partial sums stay within `limit` bytes.
+// Token ranges per task for the gradient kernels: as many as give every CU a block (at most 16, at least
+// 256 tokens each, as far as their partial sums stay within `limit` bytes).  More cost their reduction
+// more than they bring: 6000 tokens of 4 tasks, 4096 x 4096, rank 64, forward + backward 423 us with two
+// blocks per CU, 411 us with one.
 int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit) {
   const int blocks = st.K * ((wide_b + 127) / 128 + (wide_a + 127) / 128);
-  if (st.K == 0 || blocks >= 384) return 1;
+  if (st.K == 0 || blocks >= 256) return 1;
   int longest = 0;
   size_t rtotal = 0;
   for (int k = 0; k < st.K; ++k) {
     longest = st.off[k + 1] - st.off[k] > longest ? st.off[k + 1] - st.off[k] : longest;
     rtotal += st.rank[k];
   }
-  int s = (512 + blocks - 1) / blocks;
+  int s = (256 + blocks - 1) / blocks;
   s = s < 16 ? s : 16;
   s = s < longest / 256 ? s : longest / 256;
   while (s > 1 && (size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float) > limit) --s;
@@ -1057,6 +1059,23 @@ size_t grad_partial_bytes(const SegTable& st, int wide_b, int wide_a, size_t lim
   size_t rtotal = 0;
   for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
   return align_up((size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float), 256);
+}
+
+// What the size queries reserve for one gradient of `wide` columns whatever the launch plan: sums of the
+// ranges that would give every CU two blocks.
+size_t grad_reserve_bytes(const SegTable& st, int wide) {
+  const int blocks = st.K * ((wide + 127) / 128);
+  if (st.K == 0 || blocks >= 384) return 0;
+  int longest = 0;
+  size_t rtotal = 0;
+  for (int k = 0; k < st.K; ++k) {
+    longest = st.off[k + 1] - st.off[k] > longest ? st.off[k + 1] - st.off[k] : longest;
+    rtotal += st.rank[k];
+  }
+  int s = (512 + blocks - 1) / blocks;
+  s = s < 16 ? s : 16;
+  s = s < longest / 256 ? s : longest / 256;
+  return s > 1 ? align_up((size_t)s * rtotal * wide * sizeof(float), 256) : 0;
 }
 
 // dB_k = Z^T dy_k and, unless dA is NULL, dA_k = x_k^T G, in one launch (and one that adds the token

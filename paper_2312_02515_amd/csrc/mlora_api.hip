@@ -147,8 +147,8 @@ Scratch plan_scratch(const mlora_problem* p, const CallCtx& c) {
   const bool aligned = mfma_sizes_ok(p), grads = aligned && p->K > 0;
   auto most = [&](size_t b) { s.bytes = b > s.bytes ? b : s.bytes; };
   if (grads && whole_chunk_ranks(p)) {
-    most(grad_partial_bytes(c.st, c.h, 0, SIZE_MAX));
-    most(grad_partial_bytes(c.st, c.d, 0, SIZE_MAX));
+    most(grad_reserve_bytes(c.st, c.h));
+    most(grad_reserve_bytes(c.st, c.d));
   }
   const size_t reserve = s.bytes;
   s.limit = z + reserve <= fixed ? fixed - z : (reserve > 2 * fixed ? reserve : 2 * fixed);

@@ -126,6 +126,7 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
 // (the tokens of a task are then split over blocks); NULL = never split.
 int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit);
 size_t grad_partial_bytes(const SegTable& st, int wide_b, int wide_a, size_t limit);
+size_t grad_reserve_bytes(const SegTable& st, int wide);
 hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const OutTable& dB, const bf16* X, const bf16* G,
                       const OutTable* dA, int accumulate, float* partial, size_t limit);
 // adds `splits` ranges of partial sums ([range][sum of ranks][wide_b], then [sum of ranks][wide_a]) in
