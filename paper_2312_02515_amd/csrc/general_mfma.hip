@@ -202,9 +202,8 @@ __device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const
 // A tile's LDS writes and the next loads are issued between its MFMA groups, whose fragments are read
 // one group ahead; tiles that need no masks load without bounds arithmetic.
 // Bound by the fp32 matrix rate in fp32 (153 TFLOP/s for a large product on this card): T = 2048,
-// 4096 x 4096: 600 us forward, 546 us backward layout (115 and 126 TFLOP/s; 693 and 550 us with loads
-// and LDS writes behind the MFMAs, 1714 and 1686 us on the vector ALUs); T = 3000: 812 and 800 us
-// (1003 and 1042).  bf16, T = 2048, 4100 x 4100: 160 and 144 us (206 and 151), bound by LDS traffic
+// 4096 x 4096: 570 us forward, 510 us backward layout (121 and 135 TFLOP/s; 693 and 550 us with loads
+// and LDS writes behind the MFMAs, 1714 and 1686 us on the vector ALUs); T = 1024: 279 and 270 us.  bf16, T = 2048, 4100 x 4100: 160 and 144 us (206 and 151), bound by LDS traffic
 // and the wait for each tile's loads.
 template <typename T, int BM, int BN, bool NN, int NSEG>
 __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
@@ -316,6 +315,23 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
         }
       }
     };
+    auto write = [&](char* st) {
+      const int sw = (ac ^ ((ar >> 1) & 7)) << 4;
+#pragma unroll
+      for (int it = 0; it < NA; ++it) *reinterpret_cast<u32x4*>(st + (ar + 32 * it) * 128 + sw) = ra[it];
+      char* sb = st + ABYTES;
+#pragma unroll
+      for (int it = 0; it < NB; ++it) {
+        if constexpr (NN) {
+          const int idx = tid + 256 * it;
+          const int k = idx / CPR, c = idx % CPR;
+          const int cs = !B16 ? c : (CPR == 16 ? c ^ ((k & 3) << 2) : c ^ (((k >> 1) & 1) << 2));
+          *reinterpret_cast<u32x4*>(sb + (k * CPR + cs) * 16) = rb[it];
+        } else {
+          *reinterpret_cast<u32x4*>(sb + (ar + 32 * it) * 128 + sw) = rb[it];
+        }
+      }
+    };
     auto put = [&](int kt, char* st) {
       if (kt >= whole) {
         const int k0 = kt * BK;
@@ -332,21 +348,7 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
           }
         }
       }
-      const int sw = (ac ^ ((ar >> 1) & 7)) << 4;
-#pragma unroll
-      for (int it = 0; it < NA; ++it) *reinterpret_cast<u32x4*>(st + (ar + 32 * it) * 128 + sw) = ra[it];
-      char* sb = st + ABYTES;
-#pragma unroll
-      for (int it = 0; it < NB; ++it) {
-        if constexpr (NN) {
-          const int idx = tid + 256 * it;
-          const int k = idx / CPR, c = idx % CPR;
-          const int cs = !B16 ? c : (CPR == 16 ? c ^ ((k & 3) << 2) : c ^ (((k >> 1) & 1) << 2));
-          *reinterpret_cast<u32x4*>(sb + (k * CPR + cs) * 16) = rb[it];
-        } else {
-          *reinterpret_cast<u32x4*>(sb + (ar + 32 * it) * 128 + sw) = rb[it];
-        }
-      }
+      write(st);
     };
     // fragments of group ks (a quarter) of the tile in st
     auto read = [&](const char* st, int ks, u32x4 (&af)[FM], u32x4 (&bfr)[FN]) {
@@ -378,7 +380,41 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
     put(t0, sm);
     if (t0 + 1 < t1) load(t0 + 1);
     __syncthreads();
-    for (int kt = t0; kt < t1; ++kt) {
+    int kt = t0;
+    // fp32, tiles whose successors need no masks: straight-line code, one memory instruction and two
+    // others behind each MFMA (64 cycles).  bf16 MFMAs are too short for that: 4 % slower there.
+    auto load_whole = [&](int kt) {
+      const char* at = abase + (size_t)kt * (BK * sizeof(T));
+      const char* bt = bbase + (size_t)kt * bstep;
+#pragma unroll
+      for (int it = 0; it < NA; ++it) ra[it] = *reinterpret_cast<const Piece*>(at + aoff[it]);
+#pragma unroll
+      for (int it = 0; it < NB; ++it) rb[it] = *reinterpret_cast<const Piece*>(bt + boff[it]);
+    };
+    const int steady = B16 ? 0 : (whole < t1 ? whole : t1);
+    for (; kt + 2 < steady; ++kt) {
+      const int s = (kt - t0) & 1;
+      const char* st = sm + s * (ABYTES + BBYTES);
+      u32x4 af[2][FM], bfr[2][FN];
+      read(st, 0, af[0], bfr[0]);
+      read(st, 1, af[1], bfr[1]);
+      multiply(af[0], bfr[0]);
+      write(sm + (s ^ 1) * (ABYTES + BBYTES));
+      read(st, 2, af[0], bfr[0]);
+      multiply(af[1], bfr[1]);
+      load_whole(kt + 2);
+      read(st, 3, af[1], bfr[1]);
+      multiply(af[0], bfr[0]);
+      multiply(af[1], bfr[1]);
+#pragma unroll
+      for (int m = 0; m < 16 * FM * FN; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA
+        __builtin_amdgcn_sched_group_barrier(0x320, 1, 0);   // a load, an LDS read or write
+        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);   // vector arithmetic
+      }
+      __syncthreads();
+    }
+    for (; kt < t1; ++kt) {
       const int s = (kt - t0) & 1;
       const char* st = sm + s * (ABYTES + BBYTES);
       u32x4 af[2][FM], bfr[2][FN];
