@@ -108,6 +108,18 @@ __device__ __forceinline__ void mma16(f32x4& acc, u32x4 a, u32x4 b, float) {
   for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], y[e], acc, 0, 0, 0);
 }
 
+// Scheduling of straight-line code of n MFMAs: behind each a memory instruction and two of vector
+// arithmetic, as long as there are any
+template <int n>
+__device__ __forceinline__ void interleave() {
+#pragma unroll
+  for (int m = 0; m < n; ++m) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA
+    __builtin_amdgcn_sched_group_barrier(0x320, 1, 0);   // a load, an LDS read or write
+    __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);   // vector arithmetic
+  }
+}
+
 // 32 consecutive rows of the virtual row axis, on which every row range of the call (before the
 // first task, each task, after the last) is padded to a multiple of 32: a piece never holds rows of
 // two tasks, so no row ever meets another task's adapter, not even multiplied by zero.
@@ -392,32 +404,32 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
       for (int it = 0; it < NB; ++it) rb[it] = *reinterpret_cast<const Piece*>(bt + boff[it]);
     };
     const int steady = B16 ? 0 : (whole < t1 ? whole : t1);
+    u32x4 af[2][FM], bfr[2][FN];
+    if (kt + 2 < steady) read(sm, 0, af[0], bfr[0]);
     for (; kt + 2 < steady; ++kt) {
       const int s = (kt - t0) & 1;
       const char* st = sm + s * (ABYTES + BBYTES);
-      u32x4 af[2][FM], bfr[2][FN];
-      read(st, 0, af[0], bfr[0]);
+      char* const next = sm + (s ^ 1) * (ABYTES + BBYTES);
       read(st, 1, af[1], bfr[1]);
       multiply(af[0], bfr[0]);
-      write(sm + (s ^ 1) * (ABYTES + BBYTES));
+      write(next);
       read(st, 2, af[0], bfr[0]);
       multiply(af[1], bfr[1]);
       load_whole(kt + 2);
       read(st, 3, af[1], bfr[1]);
       multiply(af[0], bfr[0]);
-      multiply(af[1], bfr[1]);
-#pragma unroll
-      for (int m = 0; m < 16 * FM * FN; ++m) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // an MFMA
-        __builtin_amdgcn_sched_group_barrier(0x320, 1, 0);   // a load, an LDS read or write
-        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);   // vector arithmetic
-      }
+      interleave<12 * FM * FN>();
+      // the tile's last fragments are in registers and the next tile is written: the barrier stands in
+      // front of the last group, whose MFMAs cover the first fragment reads of the next tile
       __syncthreads();
+      read(next, 0, af[0], bfr[0]);
+      multiply(af[1], bfr[1]);
+      interleave<4 * FM * FN>();
     }
+    __syncthreads();
     for (; kt < t1; ++kt) {
       const int s = (kt - t0) & 1;
       const char* st = sm + s * (ABYTES + BBYTES);
-      u32x4 af[2][FM], bfr[2][FN];
       read(st, 0, af[0], bfr[0]);
       read(st, 1, af[1], bfr[1]);
       multiply(af[0], bfr[0]);
