@@ -212,6 +212,17 @@ def _stream_handle(stream: Optional[torch.cuda.Stream]) -> int:
     return int(stream.cuda_stream)
 
 
+# Array types by length, made once; a call passes its array as it is (ctypes hands an array of
+# c_void_p over where POINTER(c_void_p) is declared): type lookup and casts were most of what a
+# backward call spent in Python.
+_VOID_PTRS = [ctypes.c_void_p * max(n, 1) for n in range(MLORA_MAX_ADAPTERS + 1)]
+
+
+def _grad_ptrs(tensors: Sequence[torch.Tensor], K: int):
+    """Host array of K (at least one) device pointers."""
+    return (_VOID_PTRS[K] if K <= MLORA_MAX_ADAPTERS else ctypes.c_void_p * K)(*[t.data_ptr() for t in tensors])
+
+
 def mlora_lora_fwd(prob: Problem, X: torch.Tensor, Y: torch.Tensor, saved: torch.Tensor, workspace: torch.Tensor,
                    stream: Optional[torch.cuda.Stream] = None) -> None:
     """Y = X W + rows_k(s_k x_k A_k B_k); fills `saved` for the backward call."""
@@ -226,12 +237,10 @@ def mlora_lora_bwd(prob: Problem, X: torch.Tensor, dY: torch.Tensor, saved: torc
                    workspace: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
     """dX = dY W^T + rows_k(s_k dy_k B_k^T A_k^T); dA_k, dB_k as in Eq. grad_lora."""
     K = prob.K
-    pa = (ctypes.c_void_p * max(K, 1))(*[t.data_ptr() for t in dA])
-    pb = (ctypes.c_void_p * max(K, 1))(*[t.data_ptr() for t in dB])
+    pa, pb = _grad_ptrs(dA, K), _grad_ptrs(dB, K)
     st = lib.mlora_lora_bwd(ctypes.byref(prob.c), X.data_ptr(), dY.data_ptr(), saved.data_ptr(),
                             dX.data_ptr() if dX is not None else None,
-                            ctypes.cast(pa, ctypes.POINTER(ctypes.c_void_p)),
-                            ctypes.cast(pb, ctypes.POINTER(ctypes.c_void_p)), 1 if accumulate else 0,
+                            pa, pb, 1 if accumulate else 0,
                             workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                             _stream_handle(stream))
     if st != 0:
@@ -243,12 +252,10 @@ def mlora_lora_bwd_static(prob: Problem, X: torch.Tensor, dY: torch.Tensor, save
                           stream: Optional[torch.cuda.Stream] = None) -> None:
     """mlora_lora_bwd with the library's own fixed scratch array instead of a workspace."""
     K = prob.K
-    pa = (ctypes.c_void_p * max(K, 1))(*[t.data_ptr() for t in dA])
-    pb = (ctypes.c_void_p * max(K, 1))(*[t.data_ptr() for t in dB])
+    pa, pb = _grad_ptrs(dA, K), _grad_ptrs(dB, K)
     st = lib.mlora_lora_bwd_static(ctypes.byref(prob.c), X.data_ptr(), dY.data_ptr(), saved.data_ptr(),
                                    dX.data_ptr() if dX is not None else None,
-                                   ctypes.cast(pa, ctypes.POINTER(ctypes.c_void_p)),
-                                   ctypes.cast(pb, ctypes.POINTER(ctypes.c_void_p)), 1 if accumulate else 0,
+                                   pa, pb, 1 if accumulate else 0,
                                    _stream_handle(stream))
     if st != 0:
         raise MloraError(st, "mlora_lora_bwd_static")
@@ -294,12 +301,10 @@ def mlora_lora_bwd_w8(prob: Problem, Wq: torch.Tensor, c: torch.Tensor, X: torch
                       accumulate: bool, workspace: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
     """mlora_lora_bwd with the frozen weight given as its 8-bit code (Wq, c)."""
     K = prob.K
-    pa = (ctypes.c_void_p * max(K, 1))(*[t.data_ptr() for t in dA])
-    pb = (ctypes.c_void_p * max(K, 1))(*[t.data_ptr() for t in dB])
+    pa, pb = _grad_ptrs(dA, K), _grad_ptrs(dB, K)
     st = lib.mlora_lora_bwd_w8(ctypes.byref(prob.c), Wq.data_ptr(), c.data_ptr(), X.data_ptr(), dY.data_ptr(),
                                saved.data_ptr(), dX.data_ptr() if dX is not None else None,
-                               ctypes.cast(pa, ctypes.POINTER(ctypes.c_void_p)),
-                               ctypes.cast(pb, ctypes.POINTER(ctypes.c_void_p)), 1 if accumulate else 0,
+                               pa, pb, 1 if accumulate else 0,
                                workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                _stream_handle(stream))
     if st != 0:
@@ -320,12 +325,10 @@ def mlora_lora_bwd_recompute(prob: Problem, X: torch.Tensor, dY: torch.Tensor, d
                              workspace: torch.Tensor, stream: Optional[torch.cuda.Stream] = None) -> None:
     """Backward of the activation-recompute variant: recomputes s_k x_k A_k from X."""
     K = prob.K
-    pa = (ctypes.c_void_p * max(K, 1))(*[t.data_ptr() for t in dA])
-    pb = (ctypes.c_void_p * max(K, 1))(*[t.data_ptr() for t in dB])
+    pa, pb = _grad_ptrs(dA, K), _grad_ptrs(dB, K)
     st = lib.mlora_lora_bwd_recompute(ctypes.byref(prob.c), X.data_ptr(), dY.data_ptr(),
                                       dX.data_ptr() if dX is not None else None,
-                                      ctypes.cast(pa, ctypes.POINTER(ctypes.c_void_p)),
-                                      ctypes.cast(pb, ctypes.POINTER(ctypes.c_void_p)), 1 if accumulate else 0,
+                                      pa, pb, 1 if accumulate else 0,
                                       workspace.data_ptr(), workspace.numel() * workspace.element_size(),
                                       _stream_handle(stream))
     if st != 0:
