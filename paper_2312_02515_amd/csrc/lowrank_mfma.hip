@@ -526,19 +526,23 @@ __global__ __launch_bounds__(256) void k_lowrank_mfma_splitk(const RowsArgs<1> r
 // Block: one task, 128 columns of Big, all its tokens in tiles of 64; 4 waves x 32 columns.
 // The whole reduction of an output element happens inside one block: deterministic, no atomics.
 // ------------------------------------------------------------------------------------------
-template <int NQ, int NS, int NP>
-struct GradSmem {
-  static constexpr int BIG = 64 * 128 * 2;             // 64 tokens x 128 columns
-  // 64 tokens x ldz x 2 B, ldz <= 32 NQ, followed by 64 zero bytes (where lanes beyond the tile's
-  // columns point), at a multiple of 1 KiB
-  static constexpr int SBYTES = NQ * 32 * 128, SREG = SBYTES + 1024;
-  __attribute__((aligned(1024))) char big[NS][BIG];
-  __attribute__((aligned(1024))) char small[NS][NP * SREG];
-};
-template <bool WIDE_FIRST, int NQ, int NS, int NP>
-__device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, GradSmem<NQ, NS, NP>& sm) {
-  constexpr int WC = 128;
-  constexpr int SBYTES = GradSmem<NQ, NS, NP>::SBYTES, SREG = GradSmem<NQ, NS, NP>::SREG;
+// LDS of one ring stage: 64 tokens x 128 columns of Big; 64 tokens x ldz of every Small_p, ldz <= 32 NQ, each
+// followed by 64 zero bytes (where lanes beyond the tile's columns point), at a multiple of 1 KiB.  The
+// stages are separate arrays of the kernels (as members of one struct they cost the shared-input
+// launch 10 us of 178).
+constexpr int kBigStage = 64 * 128 * 2;
+template <int NQ> constexpr int kSmallStage = NQ * 32 * 128 + 1024;
+#define MLORA_GRAD_STAGES(NQ, NP)                                                                                  \
+  __shared__ __attribute__((aligned(1024))) char sB0[kBigStage], sB1[kBigStage], sB2[kBigStage];                    \
+  __shared__ __attribute__((aligned(1024))) char sS0[NP * kSmallStage<NQ>], sS1[NP * kSmallStage<NQ>],              \
+      sS2[NP * kSmallStage<NQ>];                                                                                    \
+  char* const sB[3] = {sB0, sB1, sB2};                                                                              \
+  char* const sS[3] = {sS0, sS1, sS2}
+
+template <bool WIDE_FIRST, int NQ, int NP>
+__device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char* const (&sB)[3], char* const (&sS)[3]) {
+  constexpr int WC = 128, NS = 3;
+  constexpr int SREG = kSmallStage<NQ>, SBYTES = SREG - 1024;
   static_assert(WIDE_FIRST || NP == 1, "shared-input form exists for dA only");
 
   const bf16* __restrict__ Big = ga.Big;
@@ -561,7 +565,7 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, GradS
 #pragma unroll
     for (int s_ = 0; s_ < NS; ++s_)
 #pragma unroll
-      for (int p = 0; p < NP; ++p) reinterpret_cast<int*>(sm.small[s_] + p * SREG + SBYTES)[tid] = 0;
+      for (int p = 0; p < NP; ++p) reinterpret_cast<int*>(sS[s_] + p * SREG + SBYTES)[tid] = 0;
   }
 
   // Big tile: 64 token rows x 256 B; wave instruction w covers rows 4w..4w+3
@@ -671,7 +675,7 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, GradS
   __syncthreads();  // the zero pads
 #pragma unroll
   for (int s_ = 0; s_ < NS - 1; ++s_)
-    if (s_ < KT) issue(s_, sm.big[s_], sm.small[s_]);
+    if (s_ < KT) issue(s_, sB[s_], sS[s_]);
   for (int kt0 = 0; kt0 < KT; kt0 += NS) {
 #pragma unroll
     for (int s_ = 0; s_ < NS; ++s_) {
@@ -682,9 +686,9 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, GradS
         else
           wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
-        if (kt + NS - 1 < KT) issue(kt + NS - 1, sm.big[(s_ + NS - 1) % NS], sm.small[(s_ + NS - 1) % NS]);
+        if (kt + NS - 1 < KT) issue(kt + NS - 1, sB[(s_ + NS - 1) % NS], sS[(s_ + NS - 1) % NS]);
         const int left = tk - kt * 64;
-        compute(sm.big[s_], sm.small[s_], left < 64 ? left : 64);
+        compute(sB[s_], sS[s_], left < 64 ? left : 64);
       }
     }
   }
@@ -740,17 +744,17 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, GradS
 }
 
 // dA of projections that share their input
-template <int NQ, int NS, int NP>
+template <int NQ, int NP>
 __global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
-  __shared__ GradSmem<NQ, NS, NP> sm;
-  grad_body<true, NQ, NS, NP>(ga, blockIdx.x, sm);
+  MLORA_GRAD_STAGES(NQ, NP);
+  grad_body<true, NQ, NP>(ga, blockIdx.x, sB, sS);
 }
 // dB (the first blocks_b blocks: dY has just been read for G) and dA of one call
-template <int NQ, int NS>
+template <int NQ>
 __global__ __launch_bounds__(256) void k_grad_pair(const GradArgs<1> b, const GradArgs<1> a, int blocks_b) {
-  __shared__ GradSmem<NQ, NS, 1> sm;
-  if ((int)blockIdx.x < blocks_b) grad_body<false, NQ, NS, 1>(b, blockIdx.x, sm);
-  else grad_body<true, NQ, NS, 1>(a, blockIdx.x - blocks_b, sm);
+  MLORA_GRAD_STAGES(NQ, 1);
+  if ((int)blockIdx.x < blocks_b) grad_body<false, NQ, 1>(b, blockIdx.x, sB, sS);
+  else grad_body<true, NQ, 1>(a, blockIdx.x - blocks_b, sB, sS);
 }
 
 // Adds the token ranges' partial sums in range order (deterministic) into the tasks' outputs.  One
@@ -938,7 +942,7 @@ template <int NQ, int NP>
 hipError_t launch_grad_one(const GradArgs<NP>& a, int blocks, hipStream_t s) {
   if constexpr (NP * NQ <= 8) {
     const int slot = profile_begin(kProfileGrad, grad_bytes(a), s);
-    hipLaunchKernelGGL((k_grad_mfma<NQ, kRing, NP>), dim3(blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_grad_mfma<NQ, NP>), dim3(blocks), dim3(256), 0, s, a);
     const hipError_t e = hipGetLastError();
     profile_end(slot, s);
     return e;
@@ -1111,9 +1115,9 @@ hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const Out
   const int nq = nq_of(c.ldz);
   const int slot = profile_begin(kProfileGrad, grad_bytes(b) + (dA != nullptr ? grad_bytes(a) : 0.0), c.stream);
   const dim3 grid((unsigned)(blocks_b + blocks_a));
-  if (nq == 1) hipLaunchKernelGGL((k_grad_pair<1, kRing>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
-  else if (nq == 2) hipLaunchKernelGGL((k_grad_pair<2, kRing>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
-  else hipLaunchKernelGGL((k_grad_pair<4, kRing>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  if (nq == 1) hipLaunchKernelGGL((k_grad_pair<1>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  else if (nq == 2) hipLaunchKernelGGL((k_grad_pair<2>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  else hipLaunchKernelGGL((k_grad_pair<4>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && splits > 1)
     e = grad_reduce(c.st, partial, splits, wide_b, dB, wide_a, dA != nullptr ? *dA : dB, accumulate, c.stream);
