@@ -52,16 +52,16 @@ void launch_whole(const gemmk::GemmArgs<NSEG>& a, int tiles, hipStream_t stream)
 }
 
 // tiles [a.t0, total) as halves of 128 x 256, their contraction in a.parts ranges
-template <bool NN>
-void launch_halves(const gemmk::GemmArgs<1>& a, hipStream_t stream) {
+template <bool NN, int NSEG>
+void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
   const int units = 2 * (a.tiles_m * a.tiles_n - a.t0);
   const dim3 grid(units * a.parts);
   bool rag = false;
   if constexpr (!NN) {
     rag = ragged_ranks(a);
-    if (rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, false, 1, true>), grid, dim3(256), 0, stream, a);
+    if (rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, false, NSEG, true>), grid, dim3(256), 0, stream, a);
   }
-  if (!rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, 1, false>), grid, dim3(256), 0, stream, a);
+  if (!rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, false>), grid, dim3(256), 0, stream, a);
   if (a.parts == 1) return;
   gemmk::ReduceArgs r;
   r.C = a.C;
@@ -101,6 +101,8 @@ long long virtual_rows(const SegTable& st, int M) {
 //   T = 2048,  11008-deep input gradient (128 tiles) 207 -> 165 us as halves
 //   T = 2048,  4096 -> 11008 (344 tiles)      191 -> 171 us, one whole round and halves
 //   T = 16448, 11008-deep input gradient (1040 tiles) 1227 -> 1090 us, four whole rounds and halves
+//   summed input gradient of q, k, v (4096 each): T = 128  250 -> 48 us, T = 512  233 -> 79 us,
+//   T = 2048  237 -> 182 us; T = 16448  1447 -> 1354 us
 //   T = 3072,  4096 x 4096   (192 tiles): halves would take 125 us instead of 93.
 struct Plan {
   int whole, parts;
@@ -140,24 +142,38 @@ void fill_common(gemmk::GemmArgs<NSEG>* a, bf16* C, int M, int N, const SegTable
   a->part = nullptr;
 }
 
+template <bool NN, int NSEG>
+hipError_t launch(gemmk::GemmArgs<NSEG>& a, int Kd_total, float* scratch, size_t scratch_bytes, const SegTable& st,
+                  hipStream_t stream) {
+  const Plan pl = plan_gemm(st, a.M, a.N, Kd_total, scratch != nullptr ? scratch_bytes : 0);
+  a.t0 = pl.whole;
+  a.parts = pl.parts;
+  a.part = scratch;
+  const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
+  if (pl.whole > 0) launch_whole<NN, NSEG>(a, pl.whole, stream);
+  if (pl.whole < a.tiles_m * a.tiles_n) launch_halves<NN, NSEG>(a, stream);
+  const hipError_t err = hipGetLastError();
+  profile_end(slot, stream);
+  return err;
+}
+
 template <int NSEG>
-hipError_t launch_sum(const GemmOperands* ops, bf16* C, int M, int N, const SegTable& st, hipStream_t stream) {
+hipError_t launch_sum(const GemmOperands* ops, bf16* C, int M, int N, const SegTable& st, float* scratch, size_t scratch_bytes,
+                      hipStream_t stream) {
   gemmk::GemmArgs<NSEG> a;
   fill_common(&a, C, M, N, st);
+  int kd = 0;
   for (int g = 0; g < NSEG; ++g) {
     a.A[g] = ops[g].A;
     a.Bm[g] = ops[g].Bm;
     a.L[g] = ops[g].L;
     a.Kd[g] = ops[g].Kd;
+    kd += ops[g].Kd;
     a.ldz[g] = ops[g].ldz;
     for (int k = 0; k < kMaxK; ++k) a.rank[g][k] = (unsigned char)(k < st.K ? ops[g].rank[k] : 0);
     a.R[g] = *ops[g].R;
   }
-  const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
-  launch_whole<false, NSEG>(a, a.tiles_m * a.tiles_n, stream);
-  const hipError_t err = hipGetLastError();
-  profile_end(slot, stream);
-  return err;
+  return launch<false, NSEG>(a, kd, scratch, scratch_bytes, st, stream);
 }
 
 }  // namespace
@@ -174,16 +190,8 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
   a.ldz[0] = ldz;
   for (int k = 0; k < kMaxK; ++k) a.rank[0][k] = (unsigned char)(k < st.K ? st.rank[k] : 0);
   a.R[0] = R;
-  const Plan pl = plan_gemm(st, M, N, Kd, scratch != nullptr ? scratch_bytes : 0);
-  a.t0 = pl.whole;
-  a.parts = pl.parts;
-  a.part = scratch;
-  const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
-  if (pl.whole > 0) nn ? launch_whole<true, 1>(a, pl.whole, stream) : launch_whole<false, 1>(a, pl.whole, stream);
-  if (pl.whole < a.tiles_m * a.tiles_n) nn ? launch_halves<true>(a, stream) : launch_halves<false>(a, stream);
-  const hipError_t err = hipGetLastError();
-  profile_end(slot, stream);
-  return err;
+  return nn ? launch<true, 1>(a, Kd, scratch, scratch_bytes, st, stream)
+            : launch<false, 1>(a, Kd, scratch, scratch_bytes, st, stream);
 }
 
 size_t gemm_partial_bytes(const SegTable& st, int M, int N, int Kd, size_t scratch_limit) {
@@ -191,13 +199,13 @@ size_t gemm_partial_bytes(const SegTable& st, int M, int N, int Kd, size_t scrat
 }
 
 // C[M,N] = sum_g ( A_g[M,Kd_g] * Bm_g[N,Kd_g]^T + rows_k( L_g[rows_k, :r_gk] * R_gk[N,r_gk]^T ) ), 1 <= n <= 4
-hipError_t gemm_mfma_sum_nt(int n, const GemmOperands* ops, bf16* C, int M, int N, const SegTable& st,
-                            hipStream_t stream) {
+hipError_t gemm_mfma_sum_nt(int n, const GemmOperands* ops, bf16* C, int M, int N, const SegTable& st, float* scratch,
+                            size_t scratch_bytes, hipStream_t stream) {
   switch (n) {
-    case 1: return launch_sum<1>(ops, C, M, N, st, stream);
-    case 2: return launch_sum<2>(ops, C, M, N, st, stream);
-    case 3: return launch_sum<3>(ops, C, M, N, st, stream);
-    case 4: return launch_sum<4>(ops, C, M, N, st, stream);
+    case 1: return launch_sum<1>(ops, C, M, N, st, scratch, scratch_bytes, stream);
+    case 2: return launch_sum<2>(ops, C, M, N, st, scratch, scratch_bytes, stream);
+    case 3: return launch_sum<3>(ops, C, M, N, st, scratch, scratch_bytes, stream);
+    case 4: return launch_sum<4>(ops, C, M, N, st, scratch, scratch_bytes, stream);
   }
   return hipErrorInvalidValue;
 }

@@ -118,7 +118,6 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   constexpr int BK = 64;
   constexpr int BM = 128 * WAVES_M;
   constexpr bool HALF = WAVES_M == 1;
-  static_assert(!HALF || NSEG == 1, "the summed contraction runs whole tiles");
   bf16* __restrict__ C = ga.C;
   const int M = ga.M, N = ga.N, tiles_m = ga.tiles_m, tiles_n = ga.tiles_n;
   constexpr int NW = WAVES_M * WAVES_N;
@@ -487,17 +486,27 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // state is unrolled by six so that stage addresses are constants.  Operand pairs run one after
   // the other.  When a pair's last tile has passed its barrier every wave holds that tile's last
   // fragments in registers, so all stages are free for the next pair's first tiles.
+  int h0 = 0, h1 = 0;   // HALF: this block's range of the base tiles of all operand pairs
+  if constexpr (HALF) {
+    int total_kt = 0;
+    for (int sg = 0; sg < NSEG; ++sg) total_kt += ga.Kd[sg] / BK;
+    h0 = (int)((long long)total_kt * part / ga.parts);
+    h1 = (int)((long long)total_kt * (part + 1) / ga.parts);
+  }
   for (int sg = 0; sg < NSEG; ++sg) {
-    set_operands(ga.A[sg], ga.Bm[sg], ga.Kd[sg]);
-    int KT = ga.Kd[sg] / BK;
-    const int lora_tiles = !HALF && sg == NSEG - 1 ? n_lora : 0;
+    int KT = ga.Kd[sg] / BK, k0 = 0;
     if constexpr (HALF) {
-      // this block's range of the base tiles (at least one)
-      const int k0 = (int)((long long)KT * part / ga.parts), k1 = (int)((long long)KT * (part + 1) / ga.parts);
-      abase += (size_t)k0 * (BK * 2);
-      bbase += (size_t)k0 * bstep;
-      KT = k1 - k0;
+      const int lo = h0 > 0 ? h0 : 0, hi = h1 < KT ? h1 : KT;
+      h0 -= KT;
+      h1 -= KT;
+      if (lo >= hi) continue;
+      k0 = lo;
+      KT = hi - lo;
     }
+    set_operands(ga.A[sg], ga.Bm[sg], ga.Kd[sg]);
+    abase += (size_t)k0 * (BK * 2);
+    bbase += (size_t)k0 * bstep;
+    const int lora_tiles = !HALF && sg == NSEG - 1 ? n_lora : 0;
     const int VT = KT + lora_tiles;  // tiles of this pass: base tiles, then LoRA tiles
     auto ctx_of = [&](int v) {
       if (HALF || v < KT) return base_ctx(v);
@@ -560,7 +569,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       // (the last three: nothing left to load)
       for (; v < VT; ++v)
         tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, no, none, no, none, v + 2 < VT, yes);
-      break;
+      continue;
     }
     // the last base tiles and the LoRA tiles
     auto frags_at = [&](int u) { return u < KT ? frags_of(LoraTile{0, -1, 0}, true) : frags_of(find_lora(u - KT), false); };
@@ -577,21 +586,21 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // KB per block that the caches hold): lane 16 kg + r16 loads 8 ranks of row r16 of L, and of output
   // column r16 of R_k, which is kept while the pieces belong to the same task.
   if constexpr (HALF) {
-    if (part == ga.parts - 1) {
-      const bf16* L = ga.L[0];
-      const int ldz = ga.ldz[0];
+    for (int sg = 0; part == ga.parts - 1 && sg < NSEG; ++sg) {
+      const bf16* L = ga.L[sg];
+      const int ldz = ga.ldz[sg];
       for (int q0 = 0; q0 < ldz; q0 += 32) {
         int held = -1;
 #pragma unroll
         for (int f = 0; f < NFR; ++f) {
           const int k = frag_task(f);
           if (k < 0) continue;
-          const int r = ga.rank[0][k];
+          const int r = ga.rank[sg][k];
           if (q0 >= r) continue;
           const int q = q0 + 8 * kg;
           if (k != held) {
             held = k;
-            const bf16* Rk = static_cast<const bf16*>(ga.R[0].p[k]);
+            const bf16* Rk = static_cast<const bf16*>(ga.R[sg].p[k]);
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
               int n = col0 + wn * WN + 16 * j + r16;

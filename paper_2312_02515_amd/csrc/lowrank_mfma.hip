@@ -1148,6 +1148,14 @@ hipError_t grad_reduce(const SegTable& st, const float* partial, int splits, int
 // (accumulators: np x ceil(max_ldz / 32) MFMA column groups, at most 8).
 bool lowrank_group_ok(int np, int max_ldz) { return np >= 2 && np <= 4 && np * nq_of(max_ldz) <= 8; }
 
+// Below these sizes the shared pass leaves the chip idle, while a launch per projection can cut the
+// contraction or the tokens into ranges.  q, k, v at 4096 features, one pass -> a launch each, us:
+// forward 512 tokens 157 -> 137, 2048 tokens 237 -> 219, 16448 tokens 1482 -> 1452 (32768 tokens of 5120:
+// the pass 120, a launch 64 each); gradients 2048 tokens, 4 tasks 68 -> 52, 8192 tokens, 4 tasks 131 -> 117,
+// 12288 tokens, 6 tasks 248 -> 224, but 4096 tokens, 8 tasks 76 -> 79, 16448 tokens, 8 tasks 268 -> 290.
+bool group_rows_pay(const SegTable& st) { return row_blocks(st, 128) >= 256; }
+bool group_grads_pay(const SegTable& st, int h) { return st.K * ((h + 127) / 128) >= 256; }
+
 // Z_p = s_pk x_k A_pk for np projections in one pass over X.
 hipError_t lowrank_rows_mfma_group(int np, const LowrankGroupItem* items, const SegTable& st, const bf16* X, int h,
                                    hipStream_t stream) {

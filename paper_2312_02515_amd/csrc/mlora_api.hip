@@ -503,6 +503,7 @@ mlora_status mlora_lora_group_fwd(const mlora_problem* const* ps, int P, const v
     fill_ctx(ps[p], hip_stream, &c[p]);
     fused = fused && aligned16(saved[p]);
   }
+  fused = fused && group_rows_pay(c[0].st);
   if (fused) {
     // every Z_p in one pass over X
     LowrankGroupItem it[MLORA_MAX_GROUP];
@@ -554,7 +555,7 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
     w += lowrank_bytes(ps[p]);
     sum_kernel = sum_kernel && mfma_gemm_applies(ps[p]) && aligned16(dY[p]) && aligned16(G[p]);
   }
-  bool fused = ps[0]->K > 0 && group_lowrank_applies(ps, P, X);
+  bool fused = ps[0]->K > 0 && group_lowrank_applies(ps, P, X) && group_grads_pay(c[0].st, c[0].h);
   for (int p = 0; p < P; ++p) fused = fused && aligned16(dY[p]) && aligned16(saved[p]) && aligned16(G[p]);
   for (int p = 0; p < P; ++p) {
     hipError_t e = adapter_grads_impl(ps[p], c[p], X, dY[p], saved[p], G[p], ps[0]->K > 0 ? dA[p] : nullptr,
@@ -574,6 +575,12 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
   }
   if (dX == nullptr || ps[0]->T == 0) return MLORA_OK;
   hipError_t e = hipSuccess;
+  size_t scratch = 0;   // what the size query reserved behind the last G_p
+  for (int p = 0; p < P; ++p) {
+    const size_t b = scratch_bytes(ps[p]);
+    scratch = b > scratch ? b : scratch;
+  }
+  float* partial = scratch ? reinterpret_cast<float*>(w) : nullptr;
   if (sum_kernel) {
     // one kernel: the P products accumulate in fp32 in the same output tile, dX is written once
     GemmOperands ops[MLORA_MAX_GROUP];
@@ -586,17 +593,11 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
       ops[p].rank = c[p].st.rank;
       ops[p].R = &c[p].A;
     }
-    e = gemm_mfma_sum_nt(P, ops, (bf16*)dX, c[0].T, c[0].h, c[0].st, c[0].stream);
+    e = gemm_mfma_sum_nt(P, ops, (bf16*)dX, c[0].T, c[0].h, c[0].st, partial, scratch, c[0].stream);
   } else {
     GenOperands ops[MLORA_MAX_GROUP];
-    size_t scratch = 0;
-    for (int p = 0; p < P; ++p) {
-      ops[p] = GenOperands{dY[p], ps[p]->W, G[p], c[p].d, c[p].ldz, c[p].st.rank, &c[p].A};
-      const size_t b = scratch_bytes(ps[p]);
-      scratch = b > scratch ? b : scratch;
-    }
-    e = general_gemm(P, ops, c[0].dtype, dX, c[0].T, c[0].h, false, c[0].st, scratch ? reinterpret_cast<float*>(w) : nullptr,
-                     scratch, c[0].stream);
+    for (int p = 0; p < P; ++p) ops[p] = GenOperands{dY[p], ps[p]->W, G[p], c[p].d, c[p].ldz, c[p].st.rank, &c[p].A};
+    e = general_gemm(P, ops, c[0].dtype, dX, c[0].T, c[0].h, false, c[0].st, partial, scratch, c[0].stream);
   }
   return hip_status(e);
 }

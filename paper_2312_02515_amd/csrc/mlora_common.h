@@ -101,8 +101,8 @@ struct GemmOperands {
   const int* rank;     // K entries
   const PtrTable* R;
 };
-hipError_t gemm_mfma_sum_nt(int n, const GemmOperands* ops, bf16* C, int M, int N, const SegTable& st,
-                            hipStream_t stream);
+hipError_t gemm_mfma_sum_nt(int n, const GemmOperands* ops, bf16* C, int M, int N, const SegTable& st, float* scratch,
+                            size_t scratch_bytes, hipStream_t stream);
 
 // profile.hip : optional HIP-event timing of the MFMA kernels' launches, by kind
 enum { kProfileGemm = 0, kProfileRows = 1, kProfileGrad = 2, kProfileKinds = 3 };
@@ -147,6 +147,9 @@ struct LowrankGroupItem {
   const OutTable* grad_out;
 };
 bool lowrank_group_ok(int np, int max_ldz);
+// whether one pass over X for all projections beats a launch per projection at these sizes
+bool group_rows_pay(const SegTable& st);
+bool group_grads_pay(const SegTable& st, int h);
 hipError_t lowrank_rows_mfma_group(int np, const LowrankGroupItem* items, const SegTable& st, const bf16* X, int h,
                                    hipStream_t stream);
 hipError_t grad_mfma_group(int np, const LowrankGroupItem* items, const SegTable& st, const bf16* X, int h, int T,

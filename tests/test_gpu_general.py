@@ -125,3 +125,19 @@ def test_contraction_split_low_rank_rows(case):
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"split rows {case}")
     inp.W.zero_()
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"split rows, W = 0 {case}")
+
+
+@pytest.mark.parametrize("case", [
+    # T, h, d per projection, tokens, lead: a group's summed input gradient in half tiles
+    (100, 512, [4096, 64, 1088], [37, 40], 5),       # contraction ranges that cross and skip operand pairs
+    (300, 640, [512, 2048], [130, 0, 160], 3),
+    (700, 1088, [1024, 1024, 256, 64], [300, 333], 60),
+])
+def test_group_sum_in_half_tiles(case):
+    T, h, ds, tokens, lead = case
+    ranks = [[(8, 64, 24)[(p + k) % 3] + (p == 1) for k in range(len(tokens))] for p in range(len(ds))]
+    ins = _group_inputs(T, h, ds, tokens, ranks, torch.bfloat16, lead=lead, seed=78)
+    check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"group halves {case}")
+    for i in ins:
+        i.W.zero_()
+    check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"group halves, W = 0 {case}")
