@@ -234,7 +234,9 @@ hipError_t quantize_t(const T* W, int h, int d, int8_t* Wq, float* c, hipStream_
   // rows: enough blocks for the chip from about 16 columns' worth of column blocks on.
   const int ranges = h / 32 < 64 ? h / 32 : 64;
   constexpr int VEC = 16 / (int)sizeof(T);
-  if (ranges < 2) {
+  // (Small weights: one launch at about 0.07 us a row takes less than three, 16 us; 192 x 128 16.0 against
+  // 16.5 us, 4096 x 11008 691 against 49 us.)
+  if (ranges < 2 || (h < 256 && (size_t)h * d <= (size_t)1 << 18)) {
     hipLaunchKernelGGL(k_w8_quantize<T>, dim3((unsigned)((d + 63) / 64)), dim3(256), 0, stream, W, h, d, Wq, c);
     return hipGetLastError();
   }

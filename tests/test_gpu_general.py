@@ -141,3 +141,18 @@ def test_group_sum_in_half_tiles(case):
     for i in ins:
         i.W.zero_()
     check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"group halves, W = 0 {case}")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("h,d", [(256, 72), (257, 131), (64, 4104), (2085, 40), (3000, 7)])
+def test_weight_coder_over_row_ranges(h, d, dtype):
+    """Row ranges of unequal length, 16-byte pieces and single columns, a zero column: codes and scales
+    bit for bit against the oracle."""
+    from oracle import w8_oracle as w8
+    from paper_2312_02515_amd import binding as mb
+    W = torch.randn((h, d), generator=torch.Generator().manual_seed(h + d)) * torch.logspace(-6, 3, d)
+    W[:, d // 2] = 0
+    W = W.to(dtype)
+    Wq, c = mb.mlora_w8_quantize(W.to(DEV))
+    ref_q, ref_c = w8.quantize_w8(W.to(torch.float32).numpy())
+    assert np.array_equal(c.cpu().numpy(), ref_c) and np.array_equal(Wq.cpu().numpy(), ref_q)
