@@ -247,7 +247,7 @@ def main():
         kind: {"bound": "hbm", "kernel": kname, "achieved": (by / (ms * 1e-3) / 1e9 if ms > 0 else 0.0),
                "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": (by / (ms * 1e-3) / 1e9 / PEAK_HBM_GBS if ms > 0 else 0.0),
                "launches": n, "avg_launch_ms": ms / max(n, 1), "share_of_step_time": ms / prof_steps / ms_per_step}
-        for kind, kname, (ms, by, n) in (("rows", "k_lowrank_mfma", prof["rows"]), ("grad", "k_grad_mfma", prof["grad"]))}
+        for kind, kname, (ms, by, n) in (("rows", "k_lowrank_mfma", prof["rows"]), ("grad", "k_grad_pair", prof["grad"]))}
     if not args.no_power:
         out["power"] = sample_power(step)
     if args.cpu_tokens > 0:
