@@ -1036,7 +1036,7 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
   return a_major ? launch_rows<true, 1>(a, nq, tm, blocks, c.stream) : launch_rows<false, 1>(a, nq, tm, blocks, c.stream);
 }
 
-// Token ranges per task for the gradient kernels: as many as give every CU a block (at most 16, at least
+// Token ranges per task for the gradient kernels, one number for dB and dA: as many as give every CU a block (at most 16, at least
 // 256 tokens each, as far as their partial sums stay within `limit` bytes).  More cost their reduction
 // more than they bring: 6000 tokens of 4 tasks, 4096 x 4096, rank 64, forward + backward 423 us with two
 // blocks per CU, 411 us with one.
@@ -1089,7 +1089,8 @@ hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const Out
                       const OutTable* dA, int accumulate, float* partial, size_t limit) {
   if (c.K == 0) return hipSuccess;
   const int wide_b = c.d, wide_a = dA != nullptr ? c.h : 0;
-  const int splits = partial != nullptr ? grad_splits(c.st, wide_b, wide_a, limit) : 1;
+  // (planned for both outputs: dB's bits are the same whether or not a group computes dA elsewhere)
+  const int splits = partial != nullptr ? grad_splits(c.st, wide_b, c.h, limit) : 1;
   size_t rtotal = 0;
   for (int k = 0; k < c.K; ++k) rtotal += c.st.rank[k];
   GradArgs<1> b, a;

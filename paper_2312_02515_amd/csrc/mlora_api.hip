@@ -154,7 +154,6 @@ Scratch plan_scratch(const mlora_problem* p, const CallCtx& c) {
   s.limit = z + reserve <= fixed ? fixed - z : (reserve > 2 * fixed ? reserve : 2 * fixed);
   if (grads) {
     most(grad_partial_bytes(c.st, c.d, c.h, s.limit));
-    most(grad_partial_bytes(c.st, c.d, 0, s.limit));     // a group's dA is a launch of its own
     most(rows_partial_bytes(c.st, c.h, c.ldz, s.limit));
     most(rows_partial_bytes(c.st, c.d, c.ldz, s.limit));
   }

@@ -121,7 +121,7 @@ hipError_t w8_dequantize(const int8_t* Wq, const float* c, int dtype, int h, int
 size_t rows_partial_bytes(const SegTable& st, int inner, int ldz, size_t limit);
 hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M, bool a_major,
                              float* partial, size_t limit);
-// Gradients dB (wide_b = d columns) and dA (wide_a = h columns; 0 = not wanted) of one call.  `partial`:
+// Gradients dB (wide_b = d columns) and dA (wide_a = h columns) of one call.  `partial`:
 // grad_partial_bytes(..) bytes of scratch for calls whose tasks x column blocks do not fill the chip
 // (the tokens of a task are then split over blocks); NULL = never split.
 int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit);

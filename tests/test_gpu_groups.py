@@ -140,6 +140,26 @@ def test_group_matches_single_calls():
     assert relerr(np64(out["dX"]), total) <= 1e-2
 
 
+@pytest.mark.parametrize("K,h,ds,tokens", [
+    (16, 2048, [64, 128], 512),       # one task's tokens would be cut into two ranges for dB alone
+    (8, 4096, [1024, 512], 1024),     # k and v of a grouped-query layer: into four
+])
+def test_group_with_shared_dA_pass_matches_single_calls(K, h, ds, tokens):
+    """Enough tasks x features that all dA_pk come from one pass over X (K x h / 128 >= 256 blocks):
+    Y and dB_pk are still bit-identical to the single calls, which compute dB and dA together."""
+    from tests.parity_util import run_hip
+    assert K * (h // 128) >= 256
+    ranks = [[8 * (1 + (k + p) % 4) for k in range(K)] for p in range(len(ds))]
+    ins = _group_inputs(K * tokens, h, ds, [tokens] * K, ranks, torch.bfloat16, seed=33)
+    out = run_group(ins)
+    for p, i in enumerate(ins):
+        one = run_hip(i)
+        assert torch.equal(one["Y"], out["Y"][p])
+        for k in range(K):
+            assert torch.equal(one["dB"][k], out["dB"][p][k]), (p, k)
+            assert relerr(np64(one["dA"][k]), np64(out["dA"][p][k])) <= 1e-5, (p, k)
+
+
 def test_group_accumulate_and_skip_dx():
     ins = _group_inputs(384, 128, [192, 64], [128, 0, 200], [[8, 16, 16], [8, 8, 8]], torch.bfloat16, lead=16, seed=3)
     base = run_group(ins)
