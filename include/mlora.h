@@ -95,7 +95,12 @@ size_t mlora_lora_saved_bytes(const mlora_problem* p);
 
 /* Size in bytes of the scratch `workspace` either call needs (the larger of the two).
  * Depends on the sizes in `p` only (T, h, d, dtype, split positions, ranks), never on the
- * addresses it holds.  The workspace carries nothing from one call to the next.
+ * addresses it holds: the intermediate s_k dy_k B_k^T ([T, largest rank rounded up to 16]) and
+ * up to 64 MiB of partial sums of launches that cut a contraction into ranges.  With the other
+ * sizes as they are it never falls as T and the longest task grow, so a workspace for the
+ * largest batch serves the smaller ones (the same holds for the recompute, group and 8-bit
+ * queries below).  The workspace carries nothing from one call to the next, but every call may
+ * write it, the forward ones too: calls that may overlap in time need separate workspaces.
  * Returns 0 if invalid. */
 size_t mlora_lora_workspace_bytes(const mlora_problem* p);
 

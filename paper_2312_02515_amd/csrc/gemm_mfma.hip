@@ -77,19 +77,6 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
   hipLaunchKernelGGL(gemmk::k_gemm_reduce, dim3(units * 8), dim3(256), 0, stream, r);
 }
 
-// rows of the virtual axis the grid tiles: every row range of the call (before the first task, each
-// task, after the last task) rounded up to whole 32-row MFMA fragments
-long long virtual_rows(const SegTable& st, int M) {
-  long long mv = 0;
-  int prev = 0;
-  for (int r = 0; r < st.K + 2; ++r) {
-    const int b1 = r <= st.K ? st.off[r] : M;
-    mv += (b1 - prev + 31) / 32 * 32;
-    prev = b1;
-  }
-  return mv;
-}
-
 // How a product is cut into launches: tiles [0, whole) as 256 x 256 tiles, a multiple of 256 so that
 // every round fills the chip, the others as halves of them with the contraction in `parts` ranges.
 // A launch takes a round of blocks per 256 blocks; the plan with the smallest estimate wins.  The
@@ -106,23 +93,23 @@ long long virtual_rows(const SegTable& st, int M) {
 //   T = 3072,  4096 x 4096   (192 tiles): halves would take 125 us instead of 93.
 struct Plan {
   int whole, parts;
-  size_t part_bytes;
 };
+constexpr int kMaxParts = 16;
 Plan plan_gemm(const SegTable& st, int M, int N, int Kd, size_t scratch_limit) {
   const int tiles_m = (int)((virtual_rows(st, M) + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
   const int total = tiles_m * tiles_n, q = total / 256 * 256, halves = 2 * (total - q);
   const int KT = Kd / 64;
   auto whole_us = [&](int tiles) { return (double)((tiles + 255) / 256) * (10.0 + 1.3 * KT); };
-  Plan best{total, 1, 0};
+  Plan best{total, 1};
   double best_us = whole_us(total);
-  for (int parts = 1; halves > 0 && parts <= 16 && parts <= KT; ++parts) {
+  for (int parts = 1; halves > 0 && parts <= kMaxParts && parts <= KT; ++parts) {
     const size_t bytes = parts > 1 ? (size_t)halves * parts * (BM / 2) * BN * sizeof(float) : 0;
     if (bytes > scratch_limit) break;
     const double us = whole_us(q) + (double)((halves * parts + 255) / 256) * (12.0 + 0.78 * ((KT + parts - 1) / parts)) +
                       (parts > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
     if (us < best_us) {
       best_us = us;
-      best = Plan{q, parts, bytes};
+      best = Plan{q, parts};
     }
   }
   return best;
@@ -145,7 +132,7 @@ void fill_common(gemmk::GemmArgs<NSEG>* a, bf16* C, int M, int N, const SegTable
 template <bool NN, int NSEG>
 hipError_t launch(gemmk::GemmArgs<NSEG>& a, int Kd_total, float* scratch, size_t scratch_bytes, const SegTable& st,
                   hipStream_t stream) {
-  const Plan pl = plan_gemm(st, a.M, a.N, Kd_total, scratch != nullptr ? scratch_bytes : 0);
+  const Plan pl = plan_gemm(st, a.M, a.N, Kd_total, scratch_bytes);
   a.t0 = pl.whole;
   a.parts = pl.parts;
   a.part = scratch;
@@ -194,8 +181,10 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
             : launch<false, 1>(a, Kd, scratch, scratch_bytes, st, stream);
 }
 
-size_t gemm_partial_bytes(const SegTable& st, int M, int N, int Kd, size_t scratch_limit) {
-  return plan_gemm(st, M, N, Kd, scratch_limit).part_bytes;
+size_t gemm_partial_bytes(int K, int T, int N, int Kd) {
+  const long long mv = most_virtual_rows(K, T), tiles = (mv + BM - 1) / BM * ((N + BN - 1) / BN);
+  const int parts = Kd / 64 < kMaxParts ? Kd / 64 : kMaxParts;
+  return parts > 1 ? (size_t)(2 * (tiles < 255 ? tiles : 255)) * parts * (BM / 2) * BN * sizeof(float) : 0;
 }
 
 // C[M,N] = sum_g ( A_g[M,Kd_g] * Bm_g[N,Kd_g]^T + rows_k( L_g[rows_k, :r_gk] * R_gk[N,r_gk]^T ) ), 1 <= n <= 4

@@ -975,18 +975,6 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
   return hipGetLastError();
 }
 
-// rows of the virtual row axis
-long long virtual_rows(const SegTable& st, int M) {
-  long long mv = 0;
-  int prev = 0;
-  for (int r = 0; r < st.K + 2; ++r) {
-    const int b1 = r <= st.K ? st.off[r] : M;
-    mv += (b1 - prev + 31) / 32 * 32;
-    prev = b1;
-  }
-  return mv;
-}
-
 // Tile size and contraction parts of one base product.  Small problems (rows of up to 4 KB, up to 640 KB
 // of them over all blocks of 16 rows) run k_gen_skinny: with 64 x 64 tiles the few blocks walk the
 // contraction one tile after the other.  us, 64 x 64 tiles -> skinny: fp32 128 rows 256 x 256 10 -> 5,
@@ -997,15 +985,16 @@ long long virtual_rows(const SegTable& st, int M) {
 struct GemmPlan {
   bool skinny, small;
   int tiles_m, tiles_n, parts;
-  size_t part_bytes;
 };
+constexpr int kMaxParts = 16, kFullTiles = 340, kTilesPerPart = 16;   // (contraction tiles of 128 bytes per row)
+long long contraction_tiles(long long Kd, int dtype) { return Kd / (dtype == MLORA_F32 ? 32 : 64); }
 GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dtype, size_t scratch_limit) {
   const long long mv = virtual_rows(st, M);
   GemmPlan p;
   p.skinny = false;
   const long long units = (mv + 15) / 16 * ((N + 63) / 64), row_bytes = Kd_total * (dtype == MLORA_F32 ? 4 : 2);
   if (N >= 4 && row_bytes <= 4096 && units * row_bytes <= 640 << 10)
-    return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1, 0};
+    return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1};
   const long long t128 = ((mv + 127) / 128) * ((N + 127) / 128);
   p.small = t128 < 256;
   const int b = p.small ? 64 : 128;
@@ -1014,12 +1003,11 @@ GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dty
   p.parts = 1;
   const size_t tile_bytes = (size_t)p.tiles_m * p.tiles_n * b * b * 4;
   if (p.small) {
-    const long long kt = Kd_total / (dtype == MLORA_F32 ? 32 : 64);
-    while (p.parts < 16 && (long long)p.tiles_m * p.tiles_n * p.parts < 340 && kt / (p.parts + 1) >= 16 &&
-           tile_bytes * (p.parts + 1) <= scratch_limit)
+    const long long kt = contraction_tiles(Kd_total, dtype);
+    while (p.parts < kMaxParts && (long long)p.tiles_m * p.tiles_n * p.parts < kFullTiles &&
+           kt / (p.parts + 1) >= kTilesPerPart && tile_bytes * (p.parts + 1) <= scratch_limit)
       ++p.parts;
   }
-  p.part_bytes = p.parts > 1 ? align_up(tile_bytes * p.parts, 256) : 0;
   return p;
 }
 
@@ -1073,7 +1061,7 @@ hipError_t gemm_n(int n, const GenOperands* ops, int dtype, void* C, int M, int 
     a.R[g] = *o.R;
     kd += a.Kd[g];
   }
-  const GemmPlan pl = plan_gemm(st, M, N, kd, dtype, scratch != nullptr ? scratch_bytes : 0);
+  const GemmPlan pl = plan_gemm(st, M, N, kd, dtype, scratch_bytes);
   const bool f32 = dtype == MLORA_F32;
   if (!nn) return f32 ? launch_gemm<float, false, NSEG>(a, pl, scratch, s) : launch_gemm<bf16, false, NSEG>(a, pl, scratch, s);
   if constexpr (NSEG == 1)
@@ -1081,29 +1069,28 @@ hipError_t gemm_n(int n, const GenOperands* ops, int dtype, void* C, int M, int 
   return hipErrorInvalidValue;   // only input gradients are summed over projections
 }
 
-// Token ranges per task: about four blocks per CU, at least 64 tokens each, as far as the scratch goes
-int gen_grad_splits(const SegTable& st, int wide_b, int wide_a, size_t scratch_limit) {
+// Token ranges per task of up to `longest` tokens: about four blocks per CU, at least 64 tokens each
+int gen_grad_ranges(const SegTable& st, int wide_b, int wide_a, int longest) {
   const int blocks = st.K * ((wide_b + 255) / 256 + (wide_a + 255) / 256);
-  if (st.K == 0) return 1;
-  int longest = 0;
-  size_t rtotal = 0;
-  for (int k = 0; k < st.K; ++k) {
-    longest = st.off[k + 1] - st.off[k] > longest ? st.off[k + 1] - st.off[k] : longest;
-    rtotal += st.rank[k];
-  }
   int s = (1024 + blocks - 1) / blocks;
   s = s < 16 ? s : 16;
   s = s < longest / 64 ? s : longest / 64;
-  while (s > 1 && (size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float) > scratch_limit) --s;
   return s > 1 ? s : 1;
 }
+// ... as far as the scratch goes
+int gen_grad_splits(const SegTable& st, int wide_b, int wide_a, size_t scratch_limit) {
+  int s = gen_grad_ranges(st, wide_b, wide_a, longest_task(st));
+  while (s > 1 && grad_sum_bytes(st, s, wide_b, wide_a) > scratch_limit) --s;
+  return s;
+}
 
-size_t gen_grad_bytes(const SegTable& st, int wide_b, int wide_a, size_t scratch_limit) {
-  const int s = gen_grad_splits(st, wide_b, wide_a, scratch_limit);
-  if (s <= 1) return 0;
-  size_t rtotal = 0;
-  for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
-  return align_up((size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float), 256);
+// the most plan_gemm cuts off for up to T rows (a part is added while there are fewer than kFullTiles blocks)
+size_t gemm_part_bytes(int K, int T, int N, int Kd, int dtype) {
+  const long long tiles = (most_virtual_rows(K, T) + 63) / 64 * ((N + 63) / 64);
+  long long parts = contraction_tiles(Kd, dtype) / kTilesPerPart;
+  parts = parts < kMaxParts ? parts : kMaxParts;
+  const long long blocks = tiles * parts < 2 * kFullTiles ? tiles * parts : 2 * kFullTiles;
+  return parts > 1 ? (size_t)blocks * 64 * 64 * sizeof(float) : 0;
 }
 
 template <typename T>
@@ -1117,12 +1104,15 @@ void launch_grads(const GenGradArgs& b, const GenGradArgs& a, int blocks_b, int 
 
 }  // namespace
 
-size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype, size_t limit) {
+size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype) {
   size_t b = 0;
   auto most = [&](size_t v) { b = v > b ? v : b; };
-  most(gen_grad_bytes(st, d, h, limit));
-  most(plan_gemm(st, T, d, h, dtype, limit).part_bytes);
-  most(plan_gemm(st, T, h, d, dtype, limit).part_bytes);
+  if (st.K > 0) {
+    const int s = gen_grad_ranges(st, d, h, T);
+    if (s > 1) most(grad_sum_bytes(st, s, d, h));
+  }
+  most(gemm_part_bytes(st.K, T, d, h, dtype));
+  most(gemm_part_bytes(st.K, T, h, d, dtype));
   return b;
 }
 
@@ -1147,7 +1137,7 @@ hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const 
   if (c.K == 0) return hipSuccess;
   const int wide_b = c.d, wide_a = dA != nullptr ? c.h : 0;
   // (planned for both outputs, so that the scratch suffices for either)
-  const int splits = gen_grad_splits(c.st, wide_b, c.h, scratch != nullptr ? scratch_bytes : 0);
+  const int splits = gen_grad_splits(c.st, wide_b, c.h, scratch_bytes);
   size_t rtotal = 0;
   for (int k = 0; k < c.K; ++k) rtotal += c.st.rank[k];
   GenGradArgs b, a;
@@ -1168,7 +1158,7 @@ hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const 
     return c.K * g.chunks * splits;
   };
   const int blocks_b = fill(b, dY, wide_b, Z, dB, scratch);
-  const int blocks_a = dA != nullptr ? fill(a, X, wide_a, G, *dA, scratch + (scratch ? rtotal * wide_b : 0)) : (a = b, 0);
+  const int blocks_a = dA != nullptr ? fill(a, X, wide_a, G, *dA, scratch + rtotal * wide_b) : (a = b, 0);
   if (c.dtype == MLORA_F32) launch_grads<float>(b, a, blocks_b, blocks_b + blocks_a, c.ldz, c.stream);
   else launch_grads<bf16>(b, a, blocks_b, blocks_b + blocks_a, c.ldz, c.stream);
   const hipError_t e = hipGetLastError();

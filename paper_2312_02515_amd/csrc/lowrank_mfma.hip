@@ -1007,15 +1007,22 @@ hipError_t grad_group(const LowrankGroupItem* it, const SegTable& st, const bf16
 
 }  // namespace
 
-size_t rows_partial_bytes(const SegTable& st, int inner, int ldz, size_t limit) {
-  const RowsPlan pl = plan_rows(st, inner, ldz, limit);
-  return pl.splits > 1 ? align_up((size_t)pl.splits * (st.off[st.K] - st.off[0]) * ldz * sizeof(float), 256) : 0;
+// plan_rows cuts fewer than 256 blocks of 128 rows into at most KT / 4 ranges: up to 8, or (ranks above 64)
+// up to 16 as long as there are no more than 256 blocks
+size_t rows_partial_bytes(int T, int inner, int ldz) {
+  const bool four = nq_of(ldz) == 4;
+  const int KT = inner / 64, most = four ? 16 : 8, splits = KT / 4 < most ? KT / 4 : most;
+  if (splits <= 1) return 0;
+  constexpr long long block_rows = 256 * 128;
+  const long long rows = T < block_rows ? T : block_rows;
+  const long long sums = four && rows * splits > block_rows ? block_rows : rows * splits;
+  return align_up((size_t)sums * ldz * sizeof(float), 256);
 }
 
 // Z = s x A (a_major = true, M = A_k) or G = s dy B^T (a_major = false, M = B_k).
 hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M,
                              bool a_major, float* partial, size_t limit) {
-  const RowsPlan pl = plan_rows(c.st, inner, c.ldz, partial != nullptr ? limit : 0);
+  const RowsPlan pl = plan_rows(c.st, inner, c.ldz, limit);
   const int tm = pl.tm, blocks = row_blocks(c.st, tm) * pl.splits;
   if (blocks == 0) return hipSuccess;
   RowsArgs<1> a;
@@ -1036,33 +1043,27 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
   return a_major ? launch_rows<true, 1>(a, nq, tm, blocks, c.stream) : launch_rows<false, 1>(a, nq, tm, blocks, c.stream);
 }
 
-// Token ranges per task for the gradient kernels, one number for dB and dA: as many as give every CU a block (at most 16, at least
-// 256 tokens each, as far as their partial sums stay within `limit` bytes).  More cost their reduction
-// more than they bring: 6000 tokens of 4 tasks, 4096 x 4096, rank 64, forward + backward 423 us with two
-// blocks per CU, 411 us with one.
-int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit) {
+// Token ranges per task of up to `longest` tokens for the gradient kernels, one number for dB and dA: as many
+// as give every CU a block (at most 16, at least 256 tokens each).  More cost their reduction more than they
+// bring: 6000 tokens of 4 tasks, 4096 x 4096, rank 64, forward + backward 423 us with two blocks per CU, 411
+// us with one.
+int grad_ranges(const SegTable& st, int wide_b, int wide_a, int longest) {
   const int blocks = st.K * ((wide_b + 127) / 128 + (wide_a + 127) / 128);
-  if (st.K == 0 || blocks >= 256) return 1;
-  int longest = 0;
-  size_t rtotal = 0;
-  for (int k = 0; k < st.K; ++k) {
-    longest = st.off[k + 1] - st.off[k] > longest ? st.off[k + 1] - st.off[k] : longest;
-    rtotal += st.rank[k];
-  }
   int s = (256 + blocks - 1) / blocks;
   s = s < 16 ? s : 16;
   s = s < longest / 256 ? s : longest / 256;
-  while (s > 1 && (size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float) > limit) --s;
   return s > 1 ? s : 1;
 }
+// ... as far as their partial sums stay within `limit` bytes
+int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit) {
+  int s = grad_ranges(st, wide_b, wide_a, longest_task(st));
+  while (s > 1 && grad_sum_bytes(st, s, wide_b, wide_a) > limit) --s;
+  return s;
+}
 
-// Bytes of partial sums of a launch for outputs of wide_b and wide_a columns (0 when it does not split).
-size_t grad_partial_bytes(const SegTable& st, int wide_b, int wide_a, size_t limit) {
-  const int s = grad_splits(st, wide_b, wide_a, limit);
-  if (s <= 1) return 0;
-  size_t rtotal = 0;
-  for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
-  return align_up((size_t)s * rtotal * ((size_t)wide_b + wide_a) * sizeof(float), 256);
+size_t grad_partial_bytes(const SegTable& st, int T, int wide_b, int wide_a) {
+  const int s = grad_ranges(st, wide_b, wide_a, T);
+  return s > 1 ? grad_sum_bytes(st, s, wide_b, wide_a) : 0;
 }
 
 // What the size queries reserve for one gradient of `wide` columns whatever the launch plan: sums of the
@@ -1070,16 +1071,11 @@ size_t grad_partial_bytes(const SegTable& st, int wide_b, int wide_a, size_t lim
 size_t grad_reserve_bytes(const SegTable& st, int wide) {
   const int blocks = st.K * ((wide + 127) / 128);
   if (st.K == 0 || blocks >= 384) return 0;
-  int longest = 0;
-  size_t rtotal = 0;
-  for (int k = 0; k < st.K; ++k) {
-    longest = st.off[k + 1] - st.off[k] > longest ? st.off[k + 1] - st.off[k] : longest;
-    rtotal += st.rank[k];
-  }
+  const int longest = longest_task(st);
   int s = (512 + blocks - 1) / blocks;
   s = s < 16 ? s : 16;
   s = s < longest / 256 ? s : longest / 256;
-  return s > 1 ? align_up((size_t)s * rtotal * wide * sizeof(float), 256) : 0;
+  return s > 1 ? grad_sum_bytes(st, s, wide, 0) : 0;
 }
 
 // dB_k = Z^T dy_k and, unless dA is NULL, dA_k = x_k^T G, in one launch (and one that adds the token
@@ -1090,7 +1086,7 @@ hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const Out
   if (c.K == 0) return hipSuccess;
   const int wide_b = c.d, wide_a = dA != nullptr ? c.h : 0;
   // (planned for both outputs: dB's bits are the same whether or not a group computes dA elsewhere)
-  const int splits = partial != nullptr ? grad_splits(c.st, wide_b, c.h, limit) : 1;
+  const int splits = grad_splits(c.st, wide_b, c.h, limit);
   size_t rtotal = 0;
   for (int k = 0; k < c.K; ++k) rtotal += c.st.rank[k];
   GradArgs<1> b, a;
@@ -1112,7 +1108,7 @@ hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const Out
     return c.K * g.chunks * splits;
   };
   const int blocks_b = fill(b, dY, wide_b, Z, dB, partial);
-  const int blocks_a = dA != nullptr ? fill(a, X, wide_a, G, *dA, partial + (partial ? rtotal * wide_b : 0)) : (a = b, 0);
+  const int blocks_a = dA != nullptr ? fill(a, X, wide_a, G, *dA, partial + rtotal * wide_b) : (a = b, 0);
   const int nq = nq_of(c.ldz);
   const int slot = profile_begin(kProfileGrad, grad_bytes(b) + (dA != nullptr ? grad_bytes(a) : 0.0), c.stream);
   const dim3 grid((unsigned)(blocks_b + blocks_a));

@@ -79,30 +79,6 @@ size_t lowrank_bytes(const mlora_problem* p) {
   return align_up((size_t)p->T * (size_t)lowrank_ld(p) * elem_size(p), 256);
 }
 
-void fill_ctx(const mlora_problem* p, void* stream, CallCtx* c) {
-  c->T = (int)p->T;
-  c->h = (int)p->h;
-  c->d = (int)p->d;
-  c->K = p->K;
-  c->ldz = lowrank_ld(p);
-  c->dtype = p->dtype;
-  c->W = p->W;
-  c->stream = static_cast<hipStream_t>(stream);
-  c->st.K = p->K;
-  for (int k = 0; k < kMaxK; ++k) {
-    bool live = k < p->K;
-    c->st.off[k] = live ? (int)p->seg_offsets[k] : 0;
-    c->st.rank[k] = live ? p->ranks[k] : 0;
-    c->st.s[k] = live ? p->scalings[k] : 0.f;
-    c->A.p[k] = live ? p->A[k] : nullptr;
-    c->B.p[k] = live ? p->B[k] : nullptr;
-  }
-  c->st.off[kMaxK] = 0;
-  if (p->K > 0) {
-    for (int k = p->K; k <= kMaxK; ++k) c->st.off[k] = (int)p->seg_offsets[p->K];
-  }
-}
-
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 // The aligned kernels take bf16 problems whose feature sizes are multiples of 64 and whose buffers
@@ -130,44 +106,68 @@ bool mfma_shapes_ok(const mlora_problem* p) {
 bool mfma_gemm_applies(const mlora_problem* p) { return !(g_kernel_path.load() & 1) && mfma_shapes_ok(p); }
 bool mfma_lowrank_applies(const mlora_problem* p) { return !(g_kernel_path.load() & 2) && mfma_shapes_ok(p); }
 
-// Scratch behind the low-rank intermediates: partial sums of token-split gradient launches and
-// partial tiles of contraction-split base products (0 when nothing splits).  A function of the
-// sizes alone: a size query must not change its answer with the addresses, so it covers whichever
-// kernels the addresses will allow.  Splitting is optional, and `limit` bounds what it may use: a
-// problem whose intermediates fit the static scratch array has to fit it with its partial sums too.
-// (Aligned shapes with whole-chunk ranks have always asked for `reserve`, the sums of one gradient at
-// a time; the limit lets them in or keeps them out of the static scratch by that size.)
-struct Scratch {
-  size_t limit, bytes;
-};
-Scratch plan_scratch(const mlora_problem* p, const CallCtx& c) {
-  Scratch s{0, 0};
-  if (p->T < 1) return s;
+// Scratch behind the low-rank intermediates, in bytes: fp32 partial sums of launches that cut a
+// contraction into ranges (0 when none ever does).  Splitting is optional: every launch is planned
+// within this amount.  It depends on the sizes alone -- a size query must not change its answer with
+// the addresses, so it covers whichever kernels the addresses will allow -- and together with the
+// intermediates it never falls as T or the longest task grows: it is what T rows or fewer may use
+// (few rows are cut into more ranges than many), so that a workspace for the largest batch serves the
+// smaller ones.  A problem whose intermediates and `reserve` fit the static scratch array fits it with
+// its partial sums too; others may use up to twice that array.  (`reserve`, the sums of one gradient at
+// a time, is what aligned shapes with whole-chunk ranks have always asked for; it decides which of them
+// the static scratch takes.)
+size_t scratch_bytes(const mlora_problem* p, const CallCtx& c) {
+  if (p->T < 1) return 0;
   const size_t z = lowrank_bytes(p), fixed = (size_t)MLORA_STATIC_SCRATCH_BYTES;
   const bool aligned = mfma_sizes_ok(p), grads = aligned && p->K > 0;
-  auto most = [&](size_t b) { s.bytes = b > s.bytes ? b : s.bytes; };
+  size_t reserve = 0, use = general_scratch_bytes(c.st, c.T, c.h, c.d, c.dtype);
+  auto most = [](size_t& m, size_t b) { m = b > m ? b : m; };
   if (grads && whole_chunk_ranks(p)) {
-    most(grad_reserve_bytes(c.st, c.h));
-    most(grad_reserve_bytes(c.st, c.d));
+    most(reserve, grad_reserve_bytes(c.st, c.h));
+    most(reserve, grad_reserve_bytes(c.st, c.d));
   }
-  const size_t reserve = s.bytes;
-  s.limit = z + reserve <= fixed ? fixed - z : (reserve > 2 * fixed ? reserve : 2 * fixed);
   if (grads) {
-    most(grad_partial_bytes(c.st, c.d, c.h, s.limit));
-    most(rows_partial_bytes(c.st, c.h, c.ldz, s.limit));
-    most(rows_partial_bytes(c.st, c.d, c.ldz, s.limit));
+    most(use, grad_partial_bytes(c.st, c.T, c.d, c.h));
+    most(use, rows_partial_bytes(c.T, c.h, c.ldz));
+    most(use, rows_partial_bytes(c.T, c.d, c.ldz));
   }
   if (aligned) {
-    most(gemm_partial_bytes(c.st, c.T, c.d, c.h, s.limit));
-    most(gemm_partial_bytes(c.st, c.T, c.h, c.d, s.limit));
+    most(use, gemm_partial_bytes(c.K, c.T, c.d, c.h));
+    most(use, gemm_partial_bytes(c.K, c.T, c.h, c.d));
   }
-  most(general_scratch_bytes(c.st, c.T, c.h, c.d, c.dtype, s.limit));
-  return s;
+  const size_t room = z + reserve <= fixed ? fixed - z : 2 * fixed;
+  use = use < room ? use : room;
+  return use > reserve ? use : reserve;
 }
+void fill_ctx(const mlora_problem* p, void* stream, CallCtx* c) {
+  c->T = (int)p->T;
+  c->h = (int)p->h;
+  c->d = (int)p->d;
+  c->K = p->K;
+  c->ldz = lowrank_ld(p);
+  c->dtype = p->dtype;
+  c->W = p->W;
+  c->stream = static_cast<hipStream_t>(stream);
+  c->st.K = p->K;
+  for (int k = 0; k < kMaxK; ++k) {
+    bool live = k < p->K;
+    c->st.off[k] = live ? (int)p->seg_offsets[k] : 0;
+    c->st.rank[k] = live ? p->ranks[k] : 0;
+    c->st.s[k] = live ? p->scalings[k] : 0.f;
+    c->A.p[k] = live ? p->A[k] : nullptr;
+    c->B.p[k] = live ? p->B[k] : nullptr;
+  }
+  c->st.off[kMaxK] = 0;
+  if (p->K > 0) {
+    for (int k = p->K; k <= kMaxK; ++k) c->st.off[k] = (int)p->seg_offsets[p->K];
+  }
+  c->scratch_bytes = scratch_bytes(p, *c);
+}
+
 size_t scratch_bytes(const mlora_problem* p) {
   CallCtx c;
   fill_ctx(p, nullptr, &c);
-  return plan_scratch(p, c).bytes;
+  return c.scratch_bytes;
 }
 
 mlora_status hip_status(hipError_t e) {
@@ -179,22 +179,19 @@ mlora_status hip_status(hipError_t e) {
 // Z = s_k x_k A_k into `Z` ([T, ldz], layout of the `saved` buffer)
 hipError_t compute_Z(const mlora_problem* p, const CallCtx& c, const void* X, void* Z, void* scratch) {
   if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(Z)) {
-    const Scratch s = plan_scratch(p, c);
-    return lowrank_rows_mfma(c, (const bf16*)X, c.h, (bf16*)Z, c.A, true, s.bytes ? static_cast<float*>(scratch) : nullptr,
-                             s.limit);
+    return lowrank_rows_mfma(c, (const bf16*)X, c.h, (bf16*)Z, c.A, true, static_cast<float*>(scratch), c.scratch_bytes);
   }
   return general_Z(c, X, Z);
 }
 
 // Y = X W + Z B_k, given Z
 hipError_t forward_gemm(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, const void* Z, void* scratch) {
-  const Scratch s = plan_scratch(p, c);
-  float* partial = s.bytes ? static_cast<float*>(scratch) : nullptr;
+  float* partial = static_cast<float*>(scratch);
   if (mfma_gemm_applies(p) && aligned16(X) && aligned16(Y) && aligned16(Z))
     return gemm_mfma((const bf16*)X, (const bf16*)p->W, (bf16*)Y, c.T, c.d, c.h, true, (const bf16*)Z, c.ldz, c.st, c.B,
-                     partial, s.limit, c.stream);
+                     partial, c.scratch_bytes, c.stream);
   const GenOperands o{X, p->W, Z, c.h, c.ldz, c.st.rank, &c.B};
-  return general_gemm(1, &o, c.dtype, Y, c.T, c.d, true, c.st, partial, s.limit, c.stream);
+  return general_gemm(1, &o, c.dtype, Y, c.T, c.d, true, c.st, partial, c.scratch_bytes, c.stream);
 }
 
 hipError_t forward_impl(const mlora_problem* p, const CallCtx& c, const void* X, void* Y, void* Z, void* scratch) {
@@ -222,18 +219,17 @@ hipError_t adapter_grads_impl(const mlora_problem* p, const CallCtx& c, const vo
     ta.p[k] = k < p->K ? dA[k] : nullptr;
     tb.p[k] = k < p->K ? dB[k] : nullptr;
   }
-  const Scratch s = plan_scratch(p, c);
-  float* partial = s.bytes ? static_cast<float*>(scratch) : nullptr;
+  float* partial = static_cast<float*>(scratch);
   accumulate = accumulate ? 1 : 0;
   hipError_t e;
   if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(dY) && aligned16(Z) && aligned16(G)) {
-    e = lowrank_rows_mfma(c, (const bf16*)dY, c.d, (bf16*)G, c.B, false, partial, s.limit);
+    e = lowrank_rows_mfma(c, (const bf16*)dY, c.d, (bf16*)G, c.B, false, partial, c.scratch_bytes);
     if (e == hipSuccess)
       e = grads_mfma(c, (const bf16*)dY, (const bf16*)Z, tb, (const bf16*)X, (const bf16*)G, skip_dA ? nullptr : &ta,
-                     accumulate, partial, s.limit);
+                     accumulate, partial, c.scratch_bytes);
   } else {
     e = general_G(c, dY, G);
-    if (e == hipSuccess) e = general_grads(c, dY, Z, tb, X, G, skip_dA ? nullptr : &ta, accumulate, partial, s.limit);
+    if (e == hipSuccess) e = general_grads(c, dY, Z, tb, X, G, skip_dA ? nullptr : &ta, accumulate, partial, c.scratch_bytes);
   }
   return e;
 }
@@ -243,13 +239,12 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
                          void* dX, float* const* dA, float* const* dB, int accumulate, void* scratch) {
   hipError_t e = adapter_grads_impl(p, c, X, dY, Z, G, dA, dB, accumulate, scratch);
   if (e == hipSuccess && dX != nullptr && p->T > 0) {
-    const Scratch s = plan_scratch(p, c);
-    float* partial = s.bytes ? static_cast<float*>(scratch) : nullptr;
-    if (mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G))
+    float* partial = static_cast<float*>(scratch);
+      if (mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G))
       return gemm_mfma((const bf16*)dY, (const bf16*)p->W, (bf16*)dX, c.T, c.h, c.d, false, (const bf16*)G, c.ldz, c.st,
-                       c.A, partial, s.limit, c.stream);
+                       c.A, partial, c.scratch_bytes, c.stream);
     const GenOperands o{dY, p->W, G, c.d, c.ldz, c.st.rank, &c.A};
-    e = general_gemm(1, &o, c.dtype, dX, c.T, c.h, false, c.st, partial, s.limit, c.stream);
+    e = general_gemm(1, &o, c.dtype, dX, c.T, c.h, false, c.st, partial, c.scratch_bytes, c.stream);
   }
   return e;
 }
@@ -575,11 +570,8 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
   if (dX == nullptr || ps[0]->T == 0) return MLORA_OK;
   hipError_t e = hipSuccess;
   size_t scratch = 0;   // what the size query reserved behind the last G_p
-  for (int p = 0; p < P; ++p) {
-    const size_t b = scratch_bytes(ps[p]);
-    scratch = b > scratch ? b : scratch;
-  }
-  float* partial = scratch ? reinterpret_cast<float*>(w) : nullptr;
+  for (int p = 0; p < P; ++p) scratch = c[p].scratch_bytes > scratch ? c[p].scratch_bytes : scratch;
+  float* partial = reinterpret_cast<float*>(w);
   if (sum_kernel) {
     // one kernel: the P products accumulate in fp32 in the same output tile, dX is written once
     GemmOperands ops[MLORA_MAX_GROUP];

@@ -50,6 +50,36 @@ inline int lowrank_ld(const mlora_problem* p) {
 
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
+// Rows of the virtual axis that the base products tile: every row range of the call (before the first
+// task, each task, after the last) rounded up to whole 32-row pieces; and the most of T rows in K + 2 ranges.
+inline long long virtual_rows(const SegTable& st, int M) {
+  long long mv = 0;
+  int prev = 0;
+  for (int r = 0; r < st.K + 2; ++r) {
+    const int b1 = r <= st.K ? st.off[r] : M;
+    mv += (b1 - prev + 31) / 32 * 32;
+    prev = b1;
+  }
+  return mv;
+}
+inline long long most_virtual_rows(int K, int T) {
+  const long long padded = (long long)T + 31LL * (K + 2), apart = 32LL * T;
+  return padded < apart ? padded : apart;
+}
+
+// tokens of the longest task
+inline int longest_task(const SegTable& st) {
+  int n = 0;
+  for (int k = 0; k < st.K; ++k) n = st.off[k + 1] - st.off[k] > n ? st.off[k + 1] - st.off[k] : n;
+  return n;
+}
+// partial sums of the gradients over `ranges` token ranges
+inline size_t grad_sum_bytes(const SegTable& st, int ranges, int wide_b, int wide_a) {
+  size_t rtotal = 0;
+  for (int k = 0; k < st.K; ++k) rtotal += st.rank[k];
+  return align_up((size_t)ranges * rtotal * ((size_t)wide_b + wide_a) * sizeof(float), 256);
+}
+
 // Everything the launchers need, filled once per call from the validated problem.
 struct CallCtx {
   int T, h, d, K, ldz;
@@ -57,14 +87,16 @@ struct CallCtx {
   SegTable st;
   PtrTable A, B;
   const void* W;
+  size_t scratch_bytes;   // behind the low-rank intermediates in the workspace
   hipStream_t stream;
 };
 
 // ---- launchers (each returns a hipError_t; all work goes to c.stream) ----
 // general_mfma.hip : any shape, rank and alignment, fp32 or bf16 storage
-// Scratch: `scratch` holds at least general_scratch_bytes(.., limit) bytes and `limit` is what is
-// passed as scratch_bytes; NULL = no split launches.
-size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype, size_t limit);
+// Launches that cut a contraction into ranges are planned within the `scratch_bytes` (`limit`) bytes at
+// `scratch` (`partial`) that they are given; 0 = none does.  The size functions give the most that T
+// rows or fewer use, whatever their split positions.
+size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype);
 hipError_t general_Z(const CallCtx& c, const void* X, void* Z);      // Z = s x A
 hipError_t general_G(const CallCtx& c, const void* dY, void* G);     // G = s dy B^T
 // One operand pair of a base product: A [M, Kd], W [Kd, N] (nn) or [N, Kd], L [M, ldz] with
@@ -88,8 +120,7 @@ hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const 
 bool gemm_mfma_ok(int M, int N, int Kd);
 hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, bool nn, const bf16* L, int ldz,
                      const SegTable& st, const PtrTable& R, float* scratch, size_t scratch_bytes, hipStream_t stream);
-// scratch gemm_mfma asks for when it may use up to `scratch_limit` bytes (what is passed as scratch_bytes)
-size_t gemm_partial_bytes(const SegTable& st, int M, int N, int Kd, size_t scratch_limit);
+size_t gemm_partial_bytes(int K, int T, int N, int Kd);
 
 // One operand pair of a summed contraction (the input gradient of projections that share X):
 // A [M, Kd], Bm [N, Kd], L [M, ldz] with R_k [N, rank[k]].
@@ -116,16 +147,11 @@ hipError_t w8_quantize(const void* W, int dtype, int h, int d, int8_t* Wq, float
 hipError_t w8_dequantize(const int8_t* Wq, const float* c, int dtype, int h, int d, void* Wh, hipStream_t stream);
 
 // lowrank_mfma.hip : bf16 MFMA kernels for Z, G (row-local) and dA_k, dB_k (reduce over a task's tokens)
-// `partial`, `limit`: scratch of contraction-split launches and how much of it may be used; the launch
-// needs rows_partial_bytes(.., limit) bytes.
-size_t rows_partial_bytes(const SegTable& st, int inner, int ldz, size_t limit);
+size_t rows_partial_bytes(int T, int inner, int ldz);
 hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M, bool a_major,
                              float* partial, size_t limit);
-// Gradients dB (wide_b = d columns) and dA (wide_a = h columns) of one call.  `partial`:
-// grad_partial_bytes(..) bytes of scratch for calls whose tasks x column blocks do not fill the chip
-// (the tokens of a task are then split over blocks); NULL = never split.
-int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit);
-size_t grad_partial_bytes(const SegTable& st, int wide_b, int wide_a, size_t limit);
+// Gradients dB (wide_b = d columns) and dA (wide_a = h columns) of one call.
+size_t grad_partial_bytes(const SegTable& st, int T, int wide_b, int wide_a);
 size_t grad_reserve_bytes(const SegTable& st, int wide);
 hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const OutTable& dB, const bf16* X, const bf16* G,
                       const OutTable* dA, int accumulate, float* partial, size_t limit);

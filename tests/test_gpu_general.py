@@ -156,3 +156,27 @@ def test_weight_coder_over_row_ranges(h, d, dtype):
     Wq, c = mb.mlora_w8_quantize(W.to(DEV))
     ref_q, ref_c = w8.quantize_w8(W.to(torch.float32).numpy())
     assert np.array_equal(c.cpu().numpy(), ref_c) and np.array_equal(Wq.cpu().numpy(), ref_q)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_one_workspace_for_every_batch(dtype):
+    """A workspace of the largest batch's size serves the smaller ones, whose launches are cut into more
+    ranges: the same bits as with a workspace of their own, and the oracle's values."""
+    from paper_2312_02515_amd import binding as mb
+    h, d, ranks = 1024, 1088, [16, 64]
+    batches = [_inputs(T, h, d, [T // 2, T - T // 2], ranks, dtype, seed=79) for T in (8192, 600, 64)]
+    probs = [mb.Problem(i.X.shape[0], h, d, i.W, i.seg_offsets, i.ranks, i.scalings, i.A, i.B) for i in batches]
+    ws = probs[0].alloc_workspace()
+    for inp, prob in zip(batches[1:], probs[1:]):
+        T = inp.X.shape[0]
+        ref = run_hip(inp)
+        check_full(inp, ref, TOL[dtype], label=f"T = {T}")
+        ws.fill_(0xFF)
+        Y, dX = torch.empty((T, d), dtype=dtype, device=DEV), torch.empty((T, h), dtype=dtype, device=DEV)
+        (dA, dB), saved = prob.alloc_grads(), prob.alloc_saved()
+        mb.mlora_lora_fwd(prob, inp.X, Y, saved, ws)
+        mb.mlora_lora_bwd(prob, inp.X, inp.dY, saved, dX, dA, dB, False, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(Y, ref["Y"]) and torch.equal(dX, ref["dX"])
+        for k in range(len(ranks)):
+            assert torch.equal(dA[k], ref["dA"][k]) and torch.equal(dB[k], ref["dB"][k])
