@@ -56,12 +56,7 @@ template <bool NN, int NSEG>
 void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
   const int units = 2 * (a.tiles_m * a.tiles_n - a.t0);
   const dim3 grid(units * a.parts);
-  bool rag = false;
-  if constexpr (!NN) {
-    rag = ragged_ranks(a);
-    if (rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, false, NSEG, true>), grid, dim3(256), 0, stream, a);
-  }
-  if (!rag) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, false>), grid, dim3(256), 0, stream, a);
+  hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, false>), grid, dim3(256), 0, stream, a);
   if (a.parts == 1) return;
   gemmk::ReduceArgs r;
   r.C = a.C;

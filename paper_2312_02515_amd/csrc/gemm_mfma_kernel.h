@@ -108,11 +108,11 @@ __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const b
 // they spend outside the contraction loop counts: the loop is not unrolled (47 KB of code, fetched
 // once, cost 10 us of a block's time) and the LoRA term is added from registers instead of by LoRA
 // tiles in the pipeline (T = 100, 4096 x 4096, 8 ranges: 33 us -> 22 us).
-// RAG (backward layout): some rank is no multiple of 8, so A_k's rows [N, r] are no whole 16-byte
-// chunks; such a task's LoRA tile is put together in registers, element by element (at most two of
-// a block's contraction tiles per task).  B_k [r, N] has whole chunks for any rank.  12 tasks of 256
-// tokens, 4096 x 4096, ranks 1 to 128: 99 us, as long as the forward product, against 244 us in the
-// general kernel.
+// RAG (backward layout, whole tiles; the registers of a half tile take any rank): some rank is no
+// multiple of 8, so A_k's rows [N, r] are no whole 16-byte chunks; such a task's LoRA tile is put
+// together in registers, element by element (at most two of a block's contraction tiles per task).
+// B_k [r, N] has whole chunks for any rank.  12 tasks of 256 tokens, 4096 x 4096, ranks 1 to 128: 99 us,
+// as long as the forward product, against 244 us in the general kernel.
 template <int WAVES_M, int WAVES_N, bool NN, int NSEG, bool RAG>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmArgs<NSEG> ga) {
   constexpr int BK = 64;
@@ -131,6 +131,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   constexpr int LPB = BBYTES / 1024 / NW;      // Bm side
   constexpr int PER_TILE = LPA + LPB;
   static_assert(WM == 128, "the sub-steps halve a 128-row wave tile");
+  static_assert(!RAG || (!NN && !HALF), "half tiles and B_k take any rank");
 
   // Three stages for the A side, two for the Bm side: all 160 KiB of the CU's LDS.  The rows of
   // A come from HBM (every element once per launch, cold), the weight from the Infinity Cache; a

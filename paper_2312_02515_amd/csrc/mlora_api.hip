@@ -146,7 +146,6 @@ void fill_ctx(const mlora_problem* p, void* stream, CallCtx* c) {
   c->K = p->K;
   c->ldz = lowrank_ld(p);
   c->dtype = p->dtype;
-  c->W = p->W;
   c->stream = static_cast<hipStream_t>(stream);
   c->st.K = p->K;
   for (int k = 0; k < kMaxK; ++k) {

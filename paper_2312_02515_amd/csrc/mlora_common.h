@@ -86,7 +86,6 @@ struct CallCtx {
   int dtype;
   SegTable st;
   PtrTable A, B;
-  const void* W;
   size_t scratch_bytes;   // behind the low-rank intermediates in the workspace
   hipStream_t stream;
 };
