@@ -25,6 +25,28 @@ extern "C" {
  * Returns the previous value.  Process-wide. */
 int mlora_set_kernel_path(int path);
 
+/* How the launches of a forward and a backward call of `p` are cut up (plain calls on 16-byte aligned
+ * buffers; honours mlora_set_kernel_path), so that a test can hold the sizes it uses to the forms it
+ * means to run.  Looks at sizes and addresses only and launches nothing.  `plan` (HOST,
+ * MLORA_PLAN_FIELDS entries) is written when `p` is valid; returns the status of mlora_lora_validate. */
+#define MLORA_PLAN_Y        0  /* form of the base product of Y: an MLORA_FORM_*                   */
+#define MLORA_PLAN_Y_PARTS  1  /* ... contraction ranges per tile                                  */
+#define MLORA_PLAN_DX       2  /* the same for dX                                                  */
+#define MLORA_PLAN_DX_PARTS 3
+#define MLORA_PLAN_Z_ROWS   4  /* s x A: rows per block                                            */
+#define MLORA_PLAN_Z_PARTS  5  /* ... contraction ranges                                           */
+#define MLORA_PLAN_G_ROWS   6  /* the same for s dy B^T                                            */
+#define MLORA_PLAN_G_PARTS  7
+#define MLORA_PLAN_GRADS    8  /* dA, dB: token ranges per task                                    */
+#define MLORA_PLAN_FIELDS   9
+#define MLORA_FORM_WHOLE    0  /* aligned: 256 x 256 tiles                                         */
+#define MLORA_FORM_HALVES   1  /* aligned: 128 x 256 tiles                                         */
+#define MLORA_FORM_MIXED    2  /* aligned: whole rounds of the first, the rest as the second       */
+#define MLORA_FORM_SKINNY   3  /* general: 16 x 64                                                 */
+#define MLORA_FORM_64       4  /* general: 64 x 64                                                 */
+#define MLORA_FORM_128      5  /* general: 128 x 128                                               */
+mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan);
+
 /* Measurement aid.  While enabled, every launch of the MFMA kernels by this process is bracketed
  * by a pair of HIP events recorded on the launch stream (at most 16384 launches are kept; the
  * events are created on first use and live until the process ends).  Returns the previous

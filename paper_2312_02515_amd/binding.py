@@ -32,7 +32,11 @@ EXPORTS = ["mlora_lora_saved_bytes", "mlora_lora_workspace_bytes", "mlora_lora_v
            "mlora_lora_w8_workspace_bytes", "mlora_lora_fwd_w8", "mlora_lora_bwd_w8"]
 MLORA_STATIC_SCRATCH_BYTES = 32 << 20
 # include/mlora_testing.h: test and measurement switches
-TESTING_EXPORTS = ["mlora_set_kernel_path", "mlora_profile_kernels", "mlora_profile_kernels_read"]
+TESTING_EXPORTS = ["mlora_set_kernel_path", "mlora_kernel_plan", "mlora_profile_kernels", "mlora_profile_kernels_read"]
+
+# entries of mlora_kernel_plan, names of its MLORA_FORM_* values
+PLAN_FIELDS = ["Y", "Y_parts", "dX", "dX_parts", "Z_rows", "Z_parts", "G_rows", "G_parts", "grads"]
+PLAN_FORMS = ["whole", "halves", "mixed", "skinny", "64", "128"]
 
 
 class MloraError(RuntimeError):
@@ -121,6 +125,8 @@ def _load() -> ctypes.CDLL:
     l.mlora_last_hip_error.argtypes = []
     l.mlora_lora_kernel_path.restype = ctypes.c_int
     l.mlora_lora_kernel_path.argtypes = [pp]
+    l.mlora_kernel_plan.restype = ctypes.c_int
+    l.mlora_kernel_plan.argtypes = [pp, ctypes.POINTER(ctypes.c_int32)]
     l.mlora_set_kernel_path.restype = ctypes.c_int
     l.mlora_set_kernel_path.argtypes = [ctypes.c_int]
     l.mlora_profile_kernels.restype = ctypes.c_int
@@ -187,6 +193,16 @@ class Problem:
     def kernel_path(self) -> int:
         """0 = aligned bf16 kernels; bit 0 / bit 1 = general kernels for the base / low-rank products."""
         return int(lib.mlora_lora_kernel_path(ctypes.byref(self.c)))
+
+    def kernel_plan(self) -> dict:
+        """How the launches of a forward and a backward call are cut up (mlora_testing.h)."""
+        plan = (ctypes.c_int32 * len(PLAN_FIELDS))()
+        st = lib.mlora_kernel_plan(ctypes.byref(self.c), plan)
+        if st != 0:
+            raise MloraError(st, "mlora_kernel_plan")
+        out = dict(zip(PLAN_FIELDS, plan))
+        out["Y"], out["dX"] = PLAN_FORMS[out["Y"]], PLAN_FORMS[out["dX"]]
+        return out
 
     def alloc_saved(self) -> torch.Tensor:
         return torch.empty(self.saved_bytes(), dtype=torch.uint8, device=self.device)

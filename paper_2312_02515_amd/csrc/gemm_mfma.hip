@@ -8,6 +8,7 @@
 // base product is launched once over all tasks' rows; the output tile is written once with the
 // LoRA term already in it (no full-size intermediate for the LoRA part of dX exists).
 #include "gemm_mfma_kernel.h"
+#include "../../include/mlora_testing.h"
 #include "mlora_common.h"
 
 namespace mlora {
@@ -174,6 +175,12 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
   a.R[0] = R;
   return nn ? launch<true, 1>(a, Kd, scratch, scratch_bytes, st, stream)
             : launch<false, 1>(a, Kd, scratch, scratch_bytes, st, stream);
+}
+
+GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_bytes) {
+  const Plan pl = plan_gemm(st, M, N, Kd, scratch_bytes);
+  const long long total = (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN);
+  return GemmForm{pl.whole == total ? MLORA_FORM_WHOLE : (pl.whole == 0 ? MLORA_FORM_HALVES : MLORA_FORM_MIXED), pl.parts};
 }
 
 size_t gemm_partial_bytes(int K, int T, int N, int Kd) {

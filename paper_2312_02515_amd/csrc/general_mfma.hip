@@ -17,6 +17,7 @@
 #include <type_traits>
 
 #include "mfma_staging.h"
+#include "../../include/mlora_testing.h"
 #include "mlora_common.h"
 
 namespace mlora {
@@ -945,6 +946,10 @@ int row_blocks(const SegTable& st, int tm) {
   return blocks;
 }
 
+// 32 rows per block halve the fetches of the small operand once that still leaves two blocks
+// for every CU (ranks above 64 leave no registers for it)
+bool two_row_groups(const CallCtx& c) { return c.ldz <= 64 && row_blocks(c.st, 32) >= 512; }
+
 template <typename T, bool KMAJOR>
 hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const PtrTable& M) {
   if (c.K == 0 || c.T == 0 || row_blocks(c.st, 16) == 0) return hipSuccess;
@@ -960,9 +965,7 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
     a.s[k] = c.st.s[k];
   }
   a.M = M;
-  // 32 rows per block halve the fetches of the small operand once that still leaves two blocks
-  // for every CU (ranks above 64 leave no registers for it)
-  const bool two = c.ldz <= 64 && row_blocks(c.st, 32) >= 512;
+  const bool two = two_row_groups(c);
   const int blocks = row_blocks(c.st, two ? 32 : 16);
   const int groups = c.ldz <= 16 ? 1 : (c.ldz <= 32 ? 2 : (c.ldz <= 64 ? 4 : 8));
   const unsigned lds = 4 * (two ? 2 : 1) * groups * 1024;
@@ -1114,6 +1117,15 @@ size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype)
   most(gemm_part_bytes(st.K, T, d, h, dtype));
   most(gemm_part_bytes(st.K, T, h, d, dtype));
   return b;
+}
+
+GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, int dtype, size_t scratch_bytes) {
+  const GemmPlan pl = plan_gemm(st, M, N, Kd, dtype, scratch_bytes);
+  return GemmForm{pl.skinny ? MLORA_FORM_SKINNY : (pl.small ? MLORA_FORM_64 : MLORA_FORM_128), pl.parts};
+}
+RowsForm general_rows_form(const CallCtx& c) { return RowsForm{two_row_groups(c) ? 32 : 16, 1}; }
+int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes) {
+  return st.K > 0 ? gen_grad_splits(st, wide_b, wide_a, scratch_bytes) : 1;
 }
 
 hipError_t general_Z(const CallCtx& c, const void* X, void* Z) {

@@ -1019,6 +1019,11 @@ size_t rows_partial_bytes(int T, int inner, int ldz) {
   return align_up((size_t)sums * ldz * sizeof(float), 256);
 }
 
+RowsForm rows_form(const SegTable& st, int inner, int ldz, size_t limit) {
+  const RowsPlan pl = plan_rows(st, inner, ldz, limit);
+  return RowsForm{pl.tm, pl.splits};
+}
+
 // Z = s x A (a_major = true, M = A_k) or G = s dy B^T (a_major = false, M = B_k).
 hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M,
                              bool a_major, float* partial, size_t limit) {

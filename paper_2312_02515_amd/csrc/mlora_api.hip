@@ -614,6 +614,30 @@ int mlora_lora_kernel_path(const mlora_problem* p) {
   return (mfma_gemm_applies(p) ? 0 : 1) | (mfma_lowrank_applies(p) ? 0 : 2);
 }
 
+mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
+  const mlora_status st = validate(p);
+  if (st != MLORA_OK) return st;
+  if (plan == nullptr) return MLORA_ERR_NULL;
+  CallCtx c;
+  fill_ctx(p, nullptr, &c);
+  const size_t room = c.scratch_bytes;
+  const bool ag = mfma_gemm_applies(p), al = mfma_lowrank_applies(p);
+  const GemmForm y = ag ? gemm_form(c.st, c.T, c.d, c.h, room) : general_gemm_form(c.st, c.T, c.d, c.h, c.dtype, room);
+  const GemmForm dx = ag ? gemm_form(c.st, c.T, c.h, c.d, room) : general_gemm_form(c.st, c.T, c.h, c.d, c.dtype, room);
+  const RowsForm z = al ? rows_form(c.st, c.h, c.ldz, room) : general_rows_form(c);
+  const RowsForm g = al ? rows_form(c.st, c.d, c.ldz, room) : general_rows_form(c);
+  plan[MLORA_PLAN_Y] = y.form;
+  plan[MLORA_PLAN_Y_PARTS] = y.parts;
+  plan[MLORA_PLAN_DX] = dx.form;
+  plan[MLORA_PLAN_DX_PARTS] = dx.parts;
+  plan[MLORA_PLAN_Z_ROWS] = z.rows;
+  plan[MLORA_PLAN_Z_PARTS] = z.parts;
+  plan[MLORA_PLAN_G_ROWS] = g.rows;
+  plan[MLORA_PLAN_G_PARTS] = g.parts;
+  plan[MLORA_PLAN_GRADS] = c.K == 0 ? 1 : (al ? grad_splits(c.st, c.d, c.h, room) : general_grad_ranges(c.st, c.d, c.h, room));
+  return MLORA_OK;
+}
+
 int mlora_set_kernel_path(int path) { return g_kernel_path.exchange(path); }
 
 int mlora_profile_kernels(int enable) { return profile_enable(enable); }

@@ -80,6 +80,15 @@ inline size_t grad_sum_bytes(const SegTable& st, int ranges, int wide_b, int wid
   return align_up((size_t)ranges * rtotal * ((size_t)wide_b + wide_a) * sizeof(float), 256);
 }
 
+// How a base product is cut up: MLORA_FORM_* (mlora_testing.h) and contraction ranges per tile
+struct GemmForm {
+  int form, parts;
+};
+// ... and a low-rank product: rows per block, contraction ranges
+struct RowsForm {
+  int rows, parts;
+};
+
 // Everything the launchers need, filled once per call from the validated problem.
 struct CallCtx {
   int T, h, d, K, ldz;
@@ -108,6 +117,9 @@ struct GenOperands {
   const int* rank;     // K entries
   const PtrTable* R;
 };
+GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, int dtype, size_t scratch_bytes);
+RowsForm general_rows_form(const CallCtx& c);
+int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes);
 // C = sum over the n <= MLORA_MAX_GROUP operand pairs of A op(W) + rows_k(L R_k)
 hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st,
                         float* scratch, size_t scratch_bytes, hipStream_t stream);
@@ -120,6 +132,7 @@ bool gemm_mfma_ok(int M, int N, int Kd);
 hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, bool nn, const bf16* L, int ldz,
                      const SegTable& st, const PtrTable& R, float* scratch, size_t scratch_bytes, hipStream_t stream);
 size_t gemm_partial_bytes(int K, int T, int N, int Kd);
+GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_bytes);
 
 // One operand pair of a summed contraction (the input gradient of projections that share X):
 // A [M, Kd], Bm [N, Kd], L [M, ldz] with R_k [N, rank[k]].
@@ -147,6 +160,8 @@ hipError_t w8_dequantize(const int8_t* Wq, const float* c, int dtype, int h, int
 
 // lowrank_mfma.hip : bf16 MFMA kernels for Z, G (row-local) and dA_k, dB_k (reduce over a task's tokens)
 size_t rows_partial_bytes(int T, int inner, int ldz);
+RowsForm rows_form(const SegTable& st, int inner, int ldz, size_t limit);
+int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit);
 hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M, bool a_major,
                              float* partial, size_t limit);
 // Gradients dB (wide_b = d columns) and dA (wide_a = h columns) of one call.
