@@ -820,7 +820,11 @@ int pick_row_tile(const SegTable& st) {
 //     8192 x 4096, a forward and backward pass 474 -> 466 with two such products
 //     2048 x 11008, operands from HBM  30 -> 22 (from the Infinity Cache 21 -> 19)
 //   left alone: 32768 rows (64 against 70 with two ranges), fewer than 4096 rows of 4096 features (the
-//   four-wave form takes less than two launches: 771 x 2048  9 against 12).
+//   four-wave form takes less than two launches: 771 x 2048  9 against 12), and shallow contractions, whose
+//   sums and their reduction weigh more than what the ranges bring.  Time of a forward call with 64 outputs
+//   with one range over its time with ranges, rank 64, 16384 rows: 512 deep 0.84, 1024 0.86, 3072 0.98-1.0,
+//   4096 1.02, 8192 0.96 (12288 rows: 0.88, 0.96, 1.01, 1.17, 1.10); rank 128: 512 deep 0.85-0.95, 1024
+//   1.01-1.17 up to 12288 rows and 0.95 with 16384, 2048 1.05-1.4.
 struct RowsPlan {
   int tm, splits;
 };
@@ -830,9 +834,10 @@ RowsPlan plan_rows(const SegTable& st, int inner, int ldz, size_t limit) {
   if (b128 == 0 || b128 >= 256) return plain;
   RowsPlan pl = plain;
   if (nq_of(ldz) == 4) {
+    if (KT < 16 || (KT < 32 && b128 >= 128)) return plain;
     pl.tm = 128;
     while (2 * pl.splits * b128 <= 256 && 8 * pl.splits <= KT && pl.splits < 16) pl.splits *= 2;
-  } else if (b32 >= 128) {
+  } else if (b32 >= 128 && KT >= 64) {
     pl = RowsPlan{128, KT >= 128 ? 8 : 4};
   } else if (b32 >= 32 && KT >= 128) {
     pl = RowsPlan{64, 8};
