@@ -606,6 +606,12 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
             for (int j = 0; j < FN; ++j) {
               int n = col0 + wn * WN + 16 * j + r16;
               n = n < N ? n : N - 1;
+              // A_k's whole 16-byte chunks in one piece (128 rows of 4 tasks, 256 x 256, rank 128: the input
+              // gradient 26 us, element by element 75)
+              if (!NN && r % 8 == 0) {
+                bfr[j] = *(const bf16x8*)(q < r ? Rk + (size_t)n * r + q : reinterpret_cast<const bf16*>(zeros));
+                continue;
+              }
 #pragma unroll
               for (int e = 0; e < 8; ++e)
                 bfr[j][e] = q + e < r ? Rk[NN ? (size_t)(q + e) * N + n : (size_t)n * r + q + e] : (bf16)0.f;
