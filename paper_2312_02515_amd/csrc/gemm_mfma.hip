@@ -87,21 +87,35 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
 //   summed input gradient of q, k, v (4096 each): T = 128  250 -> 48 us, T = 512  233 -> 79 us,
 //   T = 2048  237 -> 182 us; T = 16448  1447 -> 1354 us
 //   T = 3072,  4096 x 4096   (192 tiles): halves would take 125 us instead of 93.
+// Where several tasks share a tile, each beyond the first adds 4.7 us per 64 ranks to a whole tile (a LoRA
+// tile of the pipeline) and 1.5 us per 32 ranks to a half one (which holds half as many).
 struct Plan {
   int whole, parts;
 };
 constexpr int kMaxParts = 16;
-Plan plan_gemm(const SegTable& st, int M, int N, int Kd, size_t scratch_limit) {
+// (`pairs` operand pairs of Kd contraction indices in all)
+Plan plan_gemm(const SegTable& st, int M, int N, int Kd, int pairs, size_t scratch_limit) {
   const int tiles_m = (int)((virtual_rows(st, M) + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
   const int total = tiles_m * tiles_n, q = total / 256 * 256, halves = 2 * (total - q);
   const int KT = Kd / 64;
-  auto whole_us = [&](int tiles) { return (double)((tiles + 255) / 256) * (10.0 + 1.3 * KT); };
+  int live = 0, rmax = 0;
+  for (int k = 0; k < st.K; ++k) {
+    live += st.off[k + 1] > st.off[k];
+    rmax = st.rank[k] > rmax ? st.rank[k] : rmax;
+  }
+  auto others = [&](int tiles, int most) {   // tasks of a tile beyond the first
+    const int n = (live + tiles - 1) / tiles;
+    return pairs * ((n < most ? n : most) - (n > 0 ? 1 : 0));
+  };
+  const double whole_fixed = 10.0 + 4.7 * others(tiles_m, 8) * ((rmax + 63) / 64);
+  const double half_fixed = 12.0 + 1.5 * others(2 * tiles_m, 4) * ((rmax + 31) / 32);
+  auto whole_us = [&](int tiles) { return (double)((tiles + 255) / 256) * (whole_fixed + 1.3 * KT); };
   Plan best{total, 1};
   double best_us = whole_us(total);
   for (int parts = 1; halves > 0 && parts <= kMaxParts && parts <= KT; ++parts) {
     const size_t bytes = parts > 1 ? (size_t)halves * parts * (BM / 2) * BN * sizeof(float) : 0;
     if (bytes > scratch_limit) break;
-    const double us = whole_us(q) + (double)((halves * parts + 255) / 256) * (12.0 + 0.78 * ((KT + parts - 1) / parts)) +
+    const double us = whole_us(q) + (double)((halves * parts + 255) / 256) * (half_fixed + 0.78 * ((KT + parts - 1) / parts)) +
                       (parts > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
     if (us < best_us) {
       best_us = us;
@@ -128,7 +142,7 @@ void fill_common(gemmk::GemmArgs<NSEG>* a, bf16* C, int M, int N, const SegTable
 template <bool NN, int NSEG>
 hipError_t launch(gemmk::GemmArgs<NSEG>& a, int Kd_total, float* scratch, size_t scratch_bytes, const SegTable& st,
                   hipStream_t stream) {
-  const Plan pl = plan_gemm(st, a.M, a.N, Kd_total, scratch_bytes);
+  const Plan pl = plan_gemm(st, a.M, a.N, Kd_total, NSEG, scratch_bytes);
   a.t0 = pl.whole;
   a.parts = pl.parts;
   a.part = scratch;
@@ -178,7 +192,7 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
 }
 
 GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_bytes) {
-  const Plan pl = plan_gemm(st, M, N, Kd, scratch_bytes);
+  const Plan pl = plan_gemm(st, M, N, Kd, 1, scratch_bytes);
   const long long total = (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN);
   return GemmForm{pl.whole == total ? MLORA_FORM_WHOLE : (pl.whole == 0 ? MLORA_FORM_HALVES : MLORA_FORM_MIXED), pl.parts};
 }
