@@ -823,8 +823,9 @@ int pick_row_tile(const SegTable& st) {
 //   four-wave form takes less than two launches: 771 x 2048  9 against 12), and shallow contractions, whose
 //   sums and their reduction weigh more than what the ranges bring.  Time of a forward call with 64 outputs
 //   with one range over its time with ranges, rank 64, 16384 rows: 512 deep 0.84, 1024 0.86, 3072 0.98-1.0,
-//   4096 1.02, 8192 0.96 (12288 rows: 0.88, 0.96, 1.01, 1.17, 1.10); rank 128: 512 deep 0.85-0.95, 1024
-//   1.01-1.17 up to 12288 rows and 0.95 with 16384, 2048 1.05-1.4.
+//   4096 1.02, 8192 0.96 (12288 rows: 0.88, 0.96, 1.01, 1.17, 1.10); rank 8, 16384 rows: 4096 and 5120 deep
+//   0.92-0.96, 8192 1.02; rank 128: 512 deep 0.85-0.95, 1024 1.01-1.17 up to 12288 rows and 0.95 with 16384,
+//   2048 1.05-1.4.
 struct RowsPlan {
   int tm, splits;
 };
@@ -837,7 +838,7 @@ RowsPlan plan_rows(const SegTable& st, int inner, int ldz, size_t limit) {
     if (KT < 16 || (KT < 32 && b128 >= 128)) return plain;
     pl.tm = 128;
     while (2 * pl.splits * b128 <= 256 && 8 * pl.splits <= KT && pl.splits < 16) pl.splits *= 2;
-  } else if (b32 >= 128 && KT >= 64) {
+  } else if (b32 >= 128 && KT >= 64 && !(nq_of(ldz) == 1 && KT < 128 && b128 >= 128)) {
     pl = RowsPlan{128, KT >= 128 ? 8 : 4};
   } else if (b32 >= 32 && KT >= 128) {
     pl = RowsPlan{64, 8};
@@ -846,6 +847,9 @@ RowsPlan plan_rows(const SegTable& st, int inner, int ldz, size_t limit) {
   while (pl.splits > 1 && (one * pl.splits > limit || 4 * pl.splits > KT)) pl.splits /= 2;
   return pl.splits > 1 ? pl : plain;
 }
+
+// few rows: four waves per 32-row block, each on a quarter of the contraction
+bool four_wave_form(int tm, int nq, int inner, int blocks) { return tm == 32 && nq <= 2 && inner >= 1024 && blocks <= 1024; }
 
 // Algorithmic bytes of one launch: the tasks' rows of the big operand read once, the outputs
 // written once, the small operands read once.
@@ -933,8 +937,7 @@ hipError_t launch_rows(const RowsArgs<NP>& a, int nq, int tm, int blocks, hipStr
       profile_end(slot, s);
       return e;
     }
-    // few rows: four waves per 32-row block, each on a quarter of the contraction
-    if (tm == 32 && nq <= 2 && a.inner >= 1024 && blocks <= 1024) {
+    if (four_wave_form(tm, nq, a.inner, blocks)) {
       return nq == 1 ? launch_rows_splitk<KMAJOR, 1>(a, blocks, s) : launch_rows_splitk<KMAJOR, 2>(a, blocks, s);
     }
   }
@@ -1155,12 +1158,22 @@ hipError_t grad_reduce(const SegTable& st, const float* partial, int splits, int
 // (accumulators: np x ceil(max_ldz / 32) MFMA column groups, at most 8).
 bool lowrank_group_ok(int np, int max_ldz) { return np >= 2 && np <= 4 && np * nq_of(max_ldz) <= 8; }
 
-// Below these sizes the shared pass leaves the chip idle, while a launch per projection can cut the
-// contraction or the tokens into ranges.  q, k, v at 4096 features, one pass -> a launch each, us:
-// forward 512 tokens 157 -> 137, 2048 tokens 237 -> 219, 16448 tokens 1482 -> 1452 (32768 tokens of 5120:
-// the pass 120, a launch 64 each); gradients 2048 tokens, 4 tasks 68 -> 52, 8192 tokens, 4 tasks 131 -> 117,
-// 12288 tokens, 6 tasks 248 -> 224, but 4096 tokens, 8 tasks 76 -> 79, 16448 tokens, 8 tasks 268 -> 290.
-bool group_rows_pay(const SegTable& st) { return row_blocks(st, 128) >= 256; }
+// Below these sizes the shared pass leaves the chip idle, while a launch per projection has as many blocks
+// as projections, and deep contractions in ranges.  Whole group calls, time with a launch each over time
+// with one pass:
+//   rows, P = 3, 1024 | 4096 features, tokens   2048         8192         12288        16384
+//     ranks up to 32                           0.97 | 0.91  1.00 | 0.99  1.10 | 1.02  1.08 | 1.03
+//     ranks up to 64                           0.93 | 0.83  0.95 | 0.95  0.90 | 0.92  1.06 | 1.01
+//   (32768 tokens of 5120: the pass 120 us, a launch 64 each); P = 4, 512 features 1.04-1.13 from 2048 to
+//   16384 tokens, but 0.88-0.92 at 12288 tokens of rank 64
+//   gradients, 4096 features: 4 tasks 0.94-1.0 up to 24576 tokens, 1 task 0.83-0.91, 16 tasks 1.0
+// The pass is taken only where a launch of the projection's own would add in the same order, so that a
+// group's Z and Y have the bits of the single calls.
+bool group_rows_pay(const SegTable& st, int h, int ldz, size_t limit) {
+  const RowsPlan pl = plan_rows(st, h, ldz, limit);
+  if (pl.splits > 1 || four_wave_form(pl.tm, nq_of(ldz), h, row_blocks(st, pl.tm))) return false;
+  return h <= 512 || row_blocks(st, 128) >= 128;
+}
 bool group_grads_pay(const SegTable& st, int h) { return st.K * ((h + 127) / 128) >= 256; }
 
 // Z_p = s_pk x_k A_pk for np projections in one pass over X.

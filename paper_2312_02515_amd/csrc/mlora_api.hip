@@ -494,9 +494,8 @@ mlora_status mlora_lora_group_fwd(const mlora_problem* const* ps, int P, const v
   bool fused = group_lowrank_applies(ps, P, X);
   for (int p = 0; p < P; ++p) {
     fill_ctx(ps[p], hip_stream, &c[p]);
-    fused = fused && aligned16(saved[p]);
+    fused = fused && aligned16(saved[p]) && group_rows_pay(c[p].st, c[p].h, c[p].ldz, c[p].scratch_bytes);
   }
-  fused = fused && group_rows_pay(c[0].st);
   if (fused) {
     // every Z_p in one pass over X
     LowrankGroupItem it[MLORA_MAX_GROUP];

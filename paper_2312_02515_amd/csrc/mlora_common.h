@@ -188,7 +188,7 @@ struct LowrankGroupItem {
 };
 bool lowrank_group_ok(int np, int max_ldz);
 // whether one pass over X for all projections beats a launch per projection at these sizes
-bool group_rows_pay(const SegTable& st);
+bool group_rows_pay(const SegTable& st, int h, int ldz, size_t limit);   // (asked for every projection)
 bool group_grads_pay(const SegTable& st, int h);
 hipError_t lowrank_rows_mfma_group(int np, const LowrankGroupItem* items, const SegTable& st, const bf16* X, int h,
                                    hipStream_t stream);

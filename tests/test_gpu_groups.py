@@ -143,12 +143,15 @@ def test_group_matches_single_calls():
 @pytest.mark.parametrize("K,h,ds,tokens", [
     (16, 2048, [64, 128], 512),       # one task's tokens would be cut into two ranges for dB alone
     (8, 4096, [1024, 512], 1024),     # k and v of a grouped-query layer: into four
+    (2, 512, [128, 64, 192], 700),    # shallow: every Z_p from one pass over X
+    (2, 1024, [64, 128], 8200),       # ... and from 16384 tokens on
+    (3, 4096, [64, 64], 5500),
+    (2, 2048, [64, 128], 900),        # no shared pass for few tokens
 ])
-def test_group_with_shared_dA_pass_matches_single_calls(K, h, ds, tokens):
-    """Enough tasks x features that all dA_pk come from one pass over X (K x h / 128 >= 256 blocks):
-    Y and dB_pk are still bit-identical to the single calls, which compute dB and dA together."""
+def test_group_with_shared_passes_matches_single_calls(K, h, ds, tokens):
+    """Enough tasks x features that all dA_pk come from one pass over X (K x h / 128 >= 256 blocks), or few
+    features or enough tokens that all Z_p do: Y and dB_pk are still bit-identical to the single calls."""
     from tests.parity_util import run_hip
-    assert K * (h // 128) >= 256
     ranks = [[8 * (1 + (k + p) % 4) for k in range(K)] for p in range(len(ds))]
     ins = _group_inputs(K * tokens, h, ds, [tokens] * K, ranks, torch.bfloat16, seed=33)
     out = run_group(ins)

@@ -47,6 +47,7 @@ def test_plans_of_known_calls(mb, T, h, d, tokens, ranks, want):  # noqa: F811
 
 @pytest.mark.parametrize("T,inner,rank,parts", [
     (16384, 512, 64, 1), (12288, 1024, 8, 1), (8192, 3072, 64, 1),     # shallow: the ranges' sums outweigh them
+    (16384, 4096, 8, 1),
     (8192, 4096, 16, 4), (16448, 11008, 64, 4), (2048, 11008, 32, 8),  # deep
     (2048, 512, 128, 1), (16384, 1024, 128, 1),                        # ranks above 64, shallow
     (2048, 1024, 128, 4), (3072, 4096, 128, 8), (8192, 2048, 128, 4),
