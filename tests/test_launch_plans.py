@@ -55,3 +55,8 @@ def test_plans_of_known_calls(mb, T, h, d, tokens, ranks, want):  # noqa: F811
 def test_contraction_ranges_of_low_rank_rows(mb, T, inner, rank, parts):  # noqa: F811
     assert plan(mb, T, inner, 64, [T], [rank])["Z_parts"] == parts
     assert plan(mb, T, 64, inner, [T], [rank])["G_parts"] == parts
+
+
+def test_short_tasks_keep_one_range(mb):  # noqa: F811
+    assert plan(mb, 4096, 4096, 4096, [64] * 64, [8] * 64)["Z_parts"] == 1
+    assert plan(mb, 4096, 4096, 4096, [128] * 32, [8] * 32)["Z_parts"] == 4
