@@ -234,9 +234,11 @@ hipError_t quantize_t(const T* W, int h, int d, int8_t* Wq, float* c, hipStream_
   // rows: enough blocks for the chip from about 16 columns' worth of column blocks on.
   const int ranges = h / 32 < 64 ? h / 32 : 64;
   constexpr int VEC = 16 / (int)sizeof(T);
-  // (Small weights: one launch at about 0.07 us a row takes less than three, 16 us; 192 x 128 16.0 against
-  // 16.5 us, 4096 x 11008 691 against 49 us.)
-  if (ranges < 2 || (h < 256 && (size_t)h * d <= (size_t)1 << 18)) {
+  // (Few rows: one launch at about 0.075 us a row takes less than three, 15 us whatever the weight up to
+  // 256 x 32768: 64 x 11008 10.7 against 15.4 us, 160 x 4096 14.0 against 15.1, 192 x 4096 16.5 against 15.1,
+  // 4096 x 11008 691 against 49; where the columns alone are more than a round of blocks earlier: 131072
+  // columns, 64 rows 12.1 against 15.1, 96 rows 20.0 against 15.5.)
+  if (ranges < 2 || h < 80 || (h <= 160 && d <= 1 << 16)) {
     hipLaunchKernelGGL(k_w8_quantize<T>, dim3((unsigned)((d + 63) / 64)), dim3(256), 0, stream, W, h, d, Wq, c);
     return hipGetLastError();
   }

@@ -144,7 +144,8 @@ def test_group_sum_in_half_tiles(case):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("h,d", [(256, 72), (257, 131), (64, 4104), (2085, 40), (3000, 7)])
+@pytest.mark.parametrize("h,d", [(256, 72), (257, 131), (64, 4104), (2085, 40), (3000, 7),
+                                 (161, 4104), (81, 65544), (160, 72)])
 def test_weight_coder_over_row_ranges(h, d, dtype):
     """Row ranges of unequal length, 16-byte pieces and single columns, a zero column: codes and scales
     bit for bit against the oracle."""
