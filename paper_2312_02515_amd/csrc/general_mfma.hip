@@ -148,24 +148,76 @@ struct GenGemmArgs {
   PtrTable R[NSEG];
 };
 
-template <typename Args>
-__device__ __forceinline__ RowPiece find_piece(const Args& a, long long v0) {
-  RowPiece p{a.M - 1, 0, -1};
-  long long vstart = 0;
-  int prev = 0;
-  for (int r = 0; r < a.K + 2; ++r) {
-    const int b1 = r <= a.K ? a.off[r] : a.M;
-    const int len = b1 - prev, vlen = (len + 31) & ~31;
-    if (v0 >= vstart && v0 < vstart + vlen) {
-      const int o = (int)(v0 - vstart);
-      p.row = prev + o;
-      p.n = (len - o) < 32 ? (len - o) : 32;
-      p.task = (r >= 1 && r <= a.K) ? r - 1 : -1;
-    }
-    vstart += vlen;
-    prev = b1;
+// inclusive sums over the first n lanes of a wave
+__device__ __forceinline__ int scan_lanes(int v, int n) {
+  const int lane = threadIdx.x & 63;
+  for (int s = 1; s < n; s <<= 1) {
+    const int u = __shfl_up(v, s);
+    if (lane >= s) v += u;
   }
-  return p;
+  return v;
+}
+
+// Up to this many tasks are searched one after the other, by scalar loads; more by all lanes at once: 66
+// dependent loads for 64 tasks took 7 us of every block, while the vector loads and the scan cost 1.7 us
+// whatever the number of tasks.
+constexpr int kFewTasks = 8;
+
+// The virtual row axis, spread over a wave: lane k knows where task k stands (all of a wave's lanes call
+// this)
+struct RowAxis {
+  int off, len;                          // task `lane`: first row, rows
+  unsigned vlen, vstart;                 // ... rows on the axis, where they start there
+  int lead, rows_end, M;                 // rows before the first task, end of the last task's rows
+  unsigned vlead, tasks_end;             // ... on the axis
+};
+template <typename Args>
+__device__ __forceinline__ RowAxis row_axis(const Args& a) {
+  RowAxis x{};
+  if (a.K <= kFewTasks) return x;
+  const int lane = threadIdx.x & 63;
+  x.off = a.off[lane];                   // (entries from K on repeat the last split position)
+  x.len = lane < a.K ? a.off[lane + 1] - x.off : 0;
+  x.vlen = ((unsigned)x.len + 31) & ~31u;
+  const int sum = scan_lanes((int)x.vlen, a.K);
+  x.lead = a.off[0];
+  x.rows_end = a.off[kMaxK];
+  x.M = a.M;
+  x.vlead = ((unsigned)x.lead + 31) & ~31u;
+  x.vstart = x.vlead + (unsigned)sum - x.vlen;
+  x.tasks_end = x.vlead + (unsigned)__builtin_amdgcn_readlane(sum, a.K - 1);
+  return x;
+}
+template <typename Args>
+__device__ __forceinline__ RowPiece find_piece(const Args& a, const RowAxis& x, unsigned v0) {
+  if (a.K <= kFewTasks) {
+    RowPiece p{a.M - 1, 0, -1};
+    unsigned vstart = 0;
+    int prev = 0;
+    for (int r = 0; r < a.K + 2; ++r) {
+      const int b1 = r <= a.K ? a.off[r] : a.M;
+      const int len = b1 - prev;
+      const unsigned o = v0 - vstart;
+      if (v0 >= vstart && o < (unsigned)len) p = RowPiece{prev + (int)o, len - (int)o < 32 ? len - (int)o : 32, r >= 1 && r <= a.K ? r - 1 : -1};
+      vstart += ((unsigned)len + 31) & ~31u;
+      prev = b1;
+    }
+    return p;
+  }
+  int first = 0, len = x.lead, task = -1;
+  unsigned o = v0;
+  if (v0 >= x.tasks_end) {
+    first = x.rows_end;
+    len = x.M - x.rows_end;
+    o = v0 - x.tasks_end;
+  } else if (v0 >= x.vlead) {
+    task = __builtin_ctzll(__ballot(v0 >= x.vstart && v0 - x.vstart < x.vlen));
+    first = __builtin_amdgcn_readlane(x.off, task);
+    len = __builtin_amdgcn_readlane(x.len, task);
+    o = v0 - (unsigned)__builtin_amdgcn_readlane((int)x.vstart, task);
+  }
+  if (o >= (unsigned)len) return RowPiece{x.M - 1, 0, -1};
+  return RowPiece{first + (int)o, len - (int)o < 32 ? len - (int)o : 32, task};
 }
 
 // Block id -> (tile, part).  Consecutive ids go round-robin over the 8 XCDs; each XCD takes a
@@ -237,8 +289,9 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   const int col0 = tn * BN, M = a.M, N = a.N;
 
   RowPiece pc[NA];
+  const RowAxis axis = row_axis(a);
 #pragma unroll
-  for (int f = 0; f < NA; ++f) pc[f] = find_piece(a, (long long)tm * BM + 32 * f);
+  for (int f = 0; f < NA; ++f) pc[f] = find_piece(a, axis, (unsigned)tm * BM + 32 * f);
 
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -518,7 +571,7 @@ __global__ __launch_bounds__(256) void k_gen_reduce(const GenReduceArgs a) {
   const int wm = wave >> 1, wn = wave & 1;
   const int j = blockIdx.x % FN, i = blockIdx.x / FN % FM, tile = blockIdx.x / (FM * FN);
   const int tm = tile / a.tiles_n, tn = tile % a.tiles_n;
-  const RowPiece p = find_piece(a, (long long)tm * BM + wm * WM + 32 * i);
+  const RowPiece p = find_piece(a, row_axis(a), (unsigned)tm * BM + wm * WM + 32 * i);
   if (p.n <= 0) return;
   const float* src = a.part + (size_t)tile * (BM * BN) + ((wave * FM + i) * FN + j) * 1024 + lane * 4;
   const size_t step = (size_t)a.tiles_m * a.tiles_n * (BM * BN);
@@ -724,16 +777,28 @@ __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, i
 // blocks of TM rows
 template <int TM>
 __device__ __forceinline__ int rows_block(const GenRowsArgs& a, int b, int* lo, int* hi) {
-  for (int k = 0; k < a.K; ++k) {
-    const int nb = (a.off[k + 1] - a.off[k] + TM - 1) / TM;
-    if (b < nb) {
-      *lo = a.off[k] + b * TM;
-      *hi = a.off[k + 1] < *lo + TM ? a.off[k + 1] : *lo + TM;
-      return k;
+  if (a.K <= kFewTasks) {
+    for (int k = 0; k < a.K; ++k) {
+      const int nb = (a.off[k + 1] - a.off[k] + TM - 1) / TM;
+      if (b < nb) {
+        *lo = a.off[k] + b * TM;
+        *hi = a.off[k + 1] < *lo + TM ? a.off[k + 1] : *lo + TM;
+        return k;
+      }
+      b -= nb;
     }
-    b -= nb;
+    return -1;
   }
-  return -1;
+  const int lane = threadIdx.x & 63;
+  const int off = a.off[lane], len = lane < a.K ? a.off[lane + 1] - off : 0;
+  const int nb = (len + TM - 1) / TM, first = scan_lanes(nb, a.K) - nb;
+  const unsigned long long mine = __ballot(b >= first && b < first + nb);
+  if (mine == 0) return -1;
+  const int k = __builtin_ctzll(mine);
+  const int o = (b - __builtin_amdgcn_readlane(first, k)) * TM, left = __builtin_amdgcn_readlane(len, k) - o;
+  *lo = __builtin_amdgcn_readlane(off, k) + o;
+  *hi = *lo + (left < TM ? left : TM);
+  return k;
 }
 
 template <typename T, int RM, int NW, bool KMAJOR>
@@ -759,7 +824,7 @@ __global__ __launch_bounds__(512, 4) void k_gen_skinny(const GenGemmArgs<NSEG> a
   __shared__ float red[NW / 2 * VW * 256];
   const int tm = blockIdx.x % a.tiles_m, tn = blockIdx.x / a.tiles_m;
   const int N = a.N, col0 = tn * 16 * VW;
-  RowPiece p = find_piece(a, 16LL * tm);
+  RowPiece p = find_piece(a, row_axis(a), 16u * tm);
   if (p.n <= 0) return;
   p.n = p.n < 16 ? p.n : 16;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -982,7 +1047,11 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
 // of them over all blocks of 16 rows) run k_gen_skinny: with 64 x 64 tiles the few blocks walk the
 // contraction one tile after the other.  us, 64 x 64 tiles -> skinny: fp32 128 rows 256 x 256 10 -> 5,
 // 1024 x 1024 20 -> 15, 500 rows 512 x 512 16 -> 9; beyond the line: 128 rows, 4096 deep 31 -> 60,
-// 1000 rows 1024 x 1024 33 -> 43.  128 x 128 tiles once they give every CU a
+// 1000 rows 1024 x 1024 33 -> 43.  Beyond a round of blocks (1024; 1536 with ranks above 32, whose LoRA term
+// the tiles add last: 700 x 2000 fp32, 4 deep, rank 128 21.5 us against 18.4) only outputs of one column
+// block do: whole calls, tiles against skinny, 4000 x 2000 outputs 4 deep 11.4 against 22.8 us, 1500 x 2000, 32 deep 7.4
+// against 10.3, 16000 x 100, 100 deep 12.4 against 16.6, but 40000 x 50, 50 deep, rank 64 55 against 41.
+// 128 x 128 tiles once they give every CU a
 // block; below that 64 x 64, and the contraction cut into parts of at least 16 tiles until the
 // blocks fill two thirds of the chip's 512 block slots or the scratch is used up.
 struct GemmPlan {
@@ -995,8 +1064,11 @@ GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dty
   const long long mv = virtual_rows(st, M);
   GemmPlan p;
   p.skinny = false;
+  int rmax = 0;
+  for (int k = 0; k < st.K; ++k) rmax = st.rank[k] > rmax ? st.rank[k] : rmax;
+  const long long most_units = rmax > 32 ? 1536 : 1024;
   const long long units = (mv + 15) / 16 * ((N + 63) / 64), row_bytes = Kd_total * (dtype == MLORA_F32 ? 4 : 2);
-  if (N >= 4 && row_bytes <= 4096 && units * row_bytes <= 640 << 10)
+  if (N >= 4 && row_bytes <= 4096 && units * row_bytes <= 640 << 10 && (units <= most_units || N <= 64))
     return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1};
   const long long t128 = ((mv + 127) / 128) * ((N + 127) / 128);
   p.small = t128 < 256;

@@ -57,6 +57,16 @@ def test_contraction_ranges_of_low_rank_rows(mb, T, inner, rank, parts):  # noqa
     assert plan(mb, T, 64, inner, [T], [rank])["G_parts"] == parts
 
 
+@pytest.mark.parametrize("T,h,d,K,form", [
+    (4000, 4, 2000, 4, "128"), (700, 4, 2000, 1, "64"),     # more blocks than a round: tiles
+    (300, 4, 2000, 4, "skinny"), (128, 256, 256, 2, "skinny"),
+    (40000, 50, 50, 1, "skinny"),                           # ... but one column block
+])
+def test_forms_of_shallow_base_products(mb, T, h, d, K, form):  # noqa: F811
+    assert plan(mb, T, h, d, [T // K] * K, [4] * K, f32=True)["Y"] == form
+    assert plan(mb, T, d, h, [T // K] * K, [4] * K, f32=True)["dX"] == form
+
+
 def test_short_tasks_keep_one_range(mb):  # noqa: F811
     assert plan(mb, 4096, 4096, 4096, [64] * 64, [8] * 64)["Z_parts"] == 1
     assert plan(mb, 4096, 4096, 4096, [128] * 32, [8] * 32)["Z_parts"] == 4
