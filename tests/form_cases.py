@@ -1,0 +1,54 @@
+"""Sizes at which the launches of a call take a certain form: (T, h, d, tokens, ranks, lead) and the form,
+as mlora_kernel_plan names it ({"f32": .., "bf16": ..} where the two differ).  The GPU tests run them, the
+CPU test holds them to their forms, so that a changed threshold cannot move them elsewhere unnoticed."""
+
+# General kernels, fp32 and bf16
+GENERAL = [
+    # one element around the contraction tiles (32 fp32, 64 bf16) of the 64 x 64 form
+    ((2000, 31, 1000, [900, 1050], [16, 5], 30), {"Y": "64", "Y_parts": 1}),
+    ((2000, 33, 1000, [1990], [17], 3), {"Y": "64"}),
+    ((2000, 63, 1000, [900, 1050], [3, 40], 30), {"Y": "64"}),
+    ((2000, 65, 1000, [900, 1050], [33, 8], 0), {"Y": "64"}),
+    ((2000, 1000, 33, [900, 1050], [33, 8], 7), {"dX": "64"}),
+    ((2000, 1000, 63, [900, 1050], [16, 20], 7), {"dX": "64"}),
+    # one column around its column tiles
+    ((1500, 2300, 127, [700, 0, 755], [9, 4, 32], 5), {"Y": "64", "dX": "64"}),
+    ((1500, 2300, 129, [700, 755], [9, 32], 5), {"Y": "64", "dX": "64"}),
+    # 128 x 128 tiles: ragged contraction, odd strides, several contraction tiles
+    ((2200, 139, 2101, [1000, 0, 1150], [7, 64, 32], 25), {"Y": "128"}),
+    ((2200, 2101, 139, [1000, 0, 1150], [7, 64, 32], 25), {"dX": "128", "dX_parts": 1}),
+    ((2200, 2101, 320, [1000, 1150], [128, 3], 25), {"dX": "128"}),
+    # 32 rows per block of the low-rank rows
+    ((17000, 41, 24, [9000, 7500], [4, 40], 300), {"Z_rows": 32, "G_rows": 32}),
+    # 64 tasks: the tasks of a block are searched by all lanes
+    ((1500, 40, 600, [k % 40 for k in range(64)], [1 + k % 20 for k in range(64)], 11), {"Y": "64"}),
+    ((700, 60, 70, [k % 15 for k in range(64)], [1 + k % 20 for k in range(64)], 40), {"Y": "skinny", "dX": "skinny"}),
+]
+
+# bf16, h and d multiples of 64: contraction ranges of the low-rank rows
+SPLIT_ROWS = [
+    ((4300, 4160, 64, [2000, 2140], [16, 33], 60), {"Z_rows": 128, "Z_parts": 4, "G_parts": 1}),
+    ((4300, 64, 4160, [2000, 2140], [12, 40], 60), {"G_rows": 128, "G_parts": 4, "Z_parts": 1}),
+    ((4300, 8256, 64, [2000, 2140], [16, 5], 0), {"Z_rows": 128, "Z_parts": 8}),   # ranges of unequal length
+    ((4300, 64, 8256, [2000, 2140], [16, 33], 0), {"G_rows": 128, "G_parts": 8}),
+]
+
+# Isolation of a diverged task (the last entry of a case) from its neighbours
+ISOLATION = [
+    # dtype, (T, h, d, tokens, ranks, lead), form, task
+    # ragged ranks, whole tiles: A_k's tile put together in registers, 64-row blocks of the low-rank rows
+    ("bf16", (17000, 64, 128, [9000, 7900], [5, 12], 3), {"Y": "whole", "dX": "whole", "Z_rows": 64}, 0),
+    ("bf16", (1100, 64, 64, [300, 90, 700], [9, 127, 33], 7), {"Y": "whole", "dX": "whole", "Z_rows": 32}, 1),
+    ("bf16", (300, 64, 64, [60, 90, 33, 100], [9, 127, 33, 2], 7), {"Y": "halves", "dX": "halves"}, 1),
+    ("bf16", (700, 1088, 64, [300, 33, 360], [3, 20, 30], 2), {"Z_rows": 32, "Z_parts": 1}, 1),
+    ("bf16", (4300, 4160, 64, [2000, 2140], [16, 33], 60), {"Z_rows": 128, "Z_parts": 4}, 0),
+    ("bf16", (33100, 64, 64, [16500, 16500], [1, 44], 60), {"Z_rows": 128, "Z_parts": 1}, 1),
+    # a round of whole tiles with halves behind it; contraction ranges
+    ("bf16", (4300, 512, 4096, [2100, 100, 2050], [16, 24, 64], 50), {"Y": "mixed", "dX": "halves"}, 1),
+    # general tiles
+    ("bf16", (2200, 139, 2101, [1000, 33, 1100], [7, 64, 32], 25), {"Y": "128"}, 1),
+    ("f32", (2200, 139, 2101, [1000, 33, 1100], [7, 64, 32], 25), {"Y": "128"}, 1),
+    ("bf16", (2200, 2101, 139, [1000, 33, 1100], [7, 64, 32], 25), {"dX": "128"}, 1),
+    ("f32", (2200, 2101, 139, [1000, 33, 1100], [7, 64, 32], 25), {"dX": "128"}, 1),
+    ("f32", (1500, 40, 600, [k % 40 for k in range(64)], [1 + k % 20 for k in range(64)], 11), {"Y": "64"}, 38),
+]

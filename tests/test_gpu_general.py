@@ -5,8 +5,10 @@ import pytest
 import torch
 
 from paper_2312_02515_amd import workloads as wl
+from tests import form_cases
 from tests.parity_util import TOL, check_full, run_hip
 from tests.test_gpu_groups import _group_inputs, check_group, run_group
+from tests.test_gpu_parity import _others_identical
 
 pytestmark = pytest.mark.gpu
 
@@ -28,12 +30,12 @@ def _inputs(T, h, d, tokens, ranks, dtype, lead=0, seed=0):
     (40, 1, 1, [17, 20], [1, 3], 2),                      # rows of one element
     (70, 3, 5, [33, 30], [2, 8], 1),                      # rows shorter than one 16-byte piece
     (33, 8, 4, [33], [128], 0),                           # exactly one piece; 8 column groups of 16
-    (65, 31, 33, [31, 34], [16, 17], 0),                  # one element around the fp32 contraction tile
-    (90, 127, 129, [90], [33], 0),                        # one element around a column tile
+    (65, 31, 33, [31, 34], [16, 17], 0),                  # 16 x 64 blocks: tails of one element
+    (90, 127, 129, [90], [33], 0),                        # ... a column block of one column
     (100, 2050, 70, [60, 37], [5, 20], 2),                # few tiles, deep: forward split over the contraction
     (100, 70, 3001, [60, 37], [5, 20], 2),                # the same for the input gradient
-    (2200, 136, 2101, [1000, 0, 1150], [7, 64, 32], 25),  # 128 x 128 tiles, odd stride
-    (16500, 41, 24, [9000, 7000], [4, 40], 300),          # 32 rows per low-rank block
+    (2200, 136, 2101, [1000, 0, 1150], [7, 64, 32], 25),  # 128 x 128 tiles forward, odd stride
+    (16500, 41, 24, [9000, 7000], [4, 40], 300),          # many 16-row blocks (501 blocks of 32 rows are too few)
     (700, 70, 514, [640], [9], 13),                       # token ranges; column groups of 64 that end early
     (150, 515, 67, [20, 101], [100, 17], 12),             # 16-row blocks: runs, single groups and a tail
     (49, 1021, 4, [16, 17], [1, 128], 3),                 # ... exactly one piece of columns
@@ -50,9 +52,25 @@ def test_general_kernel_edges(case, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-def test_general_kernels_take_misaligned_buffers(dtype):
+@pytest.mark.parametrize("case", [c for c, _ in form_cases.GENERAL])
+def test_general_kernel_forms(case, dtype):
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, dtype, lead=lead, seed=80)
+    check_full(inp, run_hip(inp), TOL[dtype], label=f"general {case}")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_general_group_sum_in_large_tiles(dtype):
+    """The summed input gradient in 128 x 128 tiles (2200 x 2101 outputs)."""
+    ins = _group_inputs(2200, 2101, [139, 320], [1000, 1150], [[7, 64], [32, 5]], dtype, lead=25, seed=81)
+    check_group(ins, run_group(ins), TOL[dtype], label="general group, large tiles")
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,h,d", [(300, 128, 192), (1500, 520, 1032), (2200, 256, 2112)])   # 16 x 64, 64 x 64, 128 x 128
+def test_general_kernels_take_misaligned_buffers(dtype, T, h, d):
     """Activations and weight one element off a 16-byte boundary: same results as aligned copies."""
-    inp = _inputs(300, 128, 192, [100, 150], [8, 16], dtype, lead=5, seed=72)
+    inp = _inputs(T, h, d, [100, 150], [8, 16], dtype, lead=5, seed=72)
 
     def off_by_one(t):
         buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)
@@ -115,7 +133,7 @@ def test_half_tiles_and_contraction_ranges(case):
 @pytest.mark.parametrize("case", [
     # T, h, d, tokens, ranks, lead: low-rank rows whose contraction is cut into ranges over blocks
     (700, 512, 2048, [300, 0, 390], [128, 8, 70], 4),       # four column groups, rows before and after the tasks
-    (8500, 256, 320, [4000, 4400], [16, 33], 60),           # more than 256 blocks of 32 rows
+    (8500, 256, 320, [4000, 4400], [16, 33], 60),           # more than 256 blocks of 32 rows: not split
     (1100, 8192, 64, [500, 560], [24, 9], 10),              # deep contraction of few rows (forward)
     (1100, 64, 8256, [500, 560], [24, 8], 10),              # ... and of s dy B^T; ranges of unequal length
 ])
@@ -125,6 +143,34 @@ def test_contraction_split_low_rank_rows(case):
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"split rows {case}")
     inp.W.zero_()
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"split rows, W = 0 {case}")
+
+
+@pytest.mark.parametrize("case", [c for c, _ in form_cases.SPLIT_ROWS])
+def test_contraction_ranges_of_low_rank_rows(case):
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=82)
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"ranges {case}")
+    inp.W.zero_()
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"ranges, W = 0 {case}")
+
+
+@pytest.mark.parametrize("what", ["A", "B", "X", "dY"])
+@pytest.mark.parametrize("dtype,case,j", [(t, c, j) for t, c, _, j in form_cases.ISOLATION])
+def test_isolation_from_non_finite_values_in_every_form(dtype, case, j, what):
+    """A diverged task (NaN or Inf in its adapter or its rows) leaves its neighbours' results finite and
+    bit-identical, also in ragged ranks, split launches and the general tiles."""
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, {"f32": torch.float32, "bf16": torch.bfloat16}[dtype], lead=lead, seed=83)
+    a = run_hip(inp)
+    lo, hi = inp.seg_offsets[j], inp.seg_offsets[j + 1]
+    flat = {"A": inp.A[j], "B": inp.B[j], "X": inp.X[lo:hi], "dY": inp.dY[lo:hi]}[what].view(-1)
+    flat[0::3] = float("nan")
+    flat[1::3] = float("inf")
+    flat[2::3] = -float("inf")
+    b = run_hip(inp)
+    _others_identical(a, b, inp, j)
+    for name in ("Y", "dX"):
+        assert torch.isfinite(b[name][:lo]).all() and torch.isfinite(b[name][hi:]).all()
 
 
 @pytest.mark.parametrize("case", [

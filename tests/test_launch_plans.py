@@ -3,6 +3,7 @@ import ctypes
 
 import pytest
 
+from tests import form_cases
 from tests.test_host_abi import _problem, mb  # noqa: F401  (mb is a fixture)
 
 
@@ -70,3 +71,12 @@ def test_forms_of_shallow_base_products(mb, T, h, d, K, form):  # noqa: F811
 def test_short_tasks_keep_one_range(mb):  # noqa: F811
     assert plan(mb, 4096, 4096, 4096, [64] * 64, [8] * 64)["Z_parts"] == 1
     assert plan(mb, 4096, 4096, 4096, [128] * 32, [8] * 32)["Z_parts"] == 4
+
+
+@pytest.mark.parametrize("dtype,case,want", [(t, c, w) for c, w in form_cases.GENERAL for t in ("f32", "bf16")] +
+                         [("bf16", c, w) for c, w in form_cases.SPLIT_ROWS] +
+                         [(t, c, w) for t, c, w, _ in form_cases.ISOLATION])
+def test_sizes_of_the_gpu_tests_take_their_forms(mb, dtype, case, want):  # noqa: F811
+    T, h, d, tokens, ranks, lead = case
+    got = plan(mb, T, h, d, tokens, ranks, lead, f32=dtype == "f32")
+    assert {k: got[k] for k in want} == want
