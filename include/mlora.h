@@ -235,19 +235,19 @@ const char* mlora_status_string(mlora_status s);
 /* hipError_t (as int) of the last HIP failure seen by this thread's calls; 0 if none. */
 int mlora_last_hip_error(void);
 
-/* Which kernels the calls will run for `p` (bit mask), so that a caller can tell the fast path
- * from the general one before it launches anything:
- *   0      aligned bf16 kernels (direct-to-LDS loads) everywhere,
- *   bit 0  the two base products run the general kernels (any size, alignment and dtype; matrix
- *          pipes as well, operands through registers: 2 to 3 times the time in bf16, and the fp32
- *          MFMA rate in fp32),
- *   bit 1  the low-rank products run the general kernels (3 = general everywhere).
- * The aligned kernels take bf16 problems whose h and d are multiples of 64, whose ranks are
- * multiples of 8 and whose W, A_k, B_k are 16-byte aligned (with other ranks such a problem runs
- * forms of its own of the aligned kernels, a little slower, and reports 3); the answer assumes that the buffers
- * passed to the calls (X, Y, dY, dX, saved, workspace) are 16-byte aligned too, as device
- * allocations are -- a call handed a misaligned buffer falls back for that call.  Returns -1 if
- * the problem is invalid.  Honours mlora_set_kernel_path (mlora_testing.h). */
+/* Whether the calls run the fastest kernels for `p`, the aligned bf16 ones (direct-to-LDS loads) in
+ * their whole-chunk form (bit mask), so that a caller can tell before it launches anything:
+ *   0      they do everywhere,
+ *   bit 0  the two base products run other kernels,
+ *   bit 1  the low-rank products do.
+ * That form takes bf16 problems whose h and d are multiples of 64, whose ranks are multiples of 8 and
+ * whose W, A_k, B_k are 16-byte aligned.  Where only a rank stands in the way, both bits are set and
+ * the aligned kernels run in forms for ragged ranks, a little slower; otherwise the general kernels
+ * run (any size, alignment and dtype; matrix pipes as well, operands through registers: 2 to 3 times
+ * the time in bf16, and the fp32 MFMA rate in fp32).  The answer assumes that the buffers passed to
+ * the calls (X, Y, dY, dX, saved, workspace) are 16-byte aligned too, as device allocations are -- a
+ * call handed a misaligned buffer runs the general kernels for that call.  Returns -1 if the problem
+ * is invalid.  Honours mlora_set_kernel_path (mlora_testing.h). */
 int mlora_lora_kernel_path(const mlora_problem* p);
 
 #ifdef __cplusplus

@@ -17,9 +17,9 @@ extern "C" {
 #endif
 
 /* Selects which kernels the entry points use (bit mask):
- *   0 (default) fastest applicable path: aligned bf16 kernels when the problem is bf16, h and d
- *               are multiples of 64, every rank is a multiple of 8 and all buffers are 16-byte
- *               aligned; the general kernels otherwise,
+ *   0 (default) fastest applicable path: aligned bf16 kernels (with forms of their own for ranks
+ *               that are no multiple of 8) when the problem is bf16, h and d are multiples of 64
+ *               and all buffers are 16-byte aligned; the general kernels otherwise,
  *   bit 0       general kernels for the two base products,
  *   bit 1       general kernels for the low-rank products (3 = general everywhere).
  * Returns the previous value.  Process-wide. */

@@ -191,7 +191,8 @@ class Problem:
         return int(lib.mlora_lora_validate(ctypes.byref(self.c)))
 
     def kernel_path(self) -> int:
-        """0 = aligned bf16 kernels; bit 0 / bit 1 = general kernels for the base / low-rank products."""
+        """0 = aligned bf16 kernels in whole-chunk form; bit 0 / bit 1 = other kernels for the base / low-rank
+        products (ragged-rank forms where only a rank stands in the way, else the general kernels)."""
         return int(lib.mlora_lora_kernel_path(ctypes.byref(self.c)))
 
     def kernel_plan(self) -> dict:

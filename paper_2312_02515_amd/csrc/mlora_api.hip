@@ -609,7 +609,7 @@ int mlora_last_hip_error(void) { return g_last_hip_error; }
 
 int mlora_lora_kernel_path(const mlora_problem* p) {
   if (validate(p) != MLORA_OK) return -1;
-  if (!whole_chunk_ranks(p)) return 3;  // forms of their own, reported with the general kernels
+  if (!whole_chunk_ranks(p)) return 3;  // ragged-rank forms, or general kernels
   return (mfma_gemm_applies(p) ? 0 : 1) | (mfma_lowrank_applies(p) ? 0 : 2);
 }
 

@@ -241,8 +241,8 @@ def test_kernel_path_switch(mb):
 
 
 def test_kernel_path_query(mb):
-    """A caller can learn, before launching, whether the MFMA kernels or the ~100x slower generic
-    kernels will run: bf16, h and d multiples of 64, ranks multiples of 8, 16-byte aligned W, A_k, B_k."""
+    """A caller can learn, before launching, whether the aligned kernels run in their whole-chunk form:
+    bf16, h and d multiples of 64, ranks multiples of 8, 16-byte aligned W, A_k, B_k."""
     fast = _problem(mb, T=64, h=128, d=192, ranks=(8, 16))
     assert fast.kernel_path() == 0
     assert _problem(mb, T=64, h=32, d=48).kernel_path() == 3           # h, d not multiples of 64
