@@ -87,8 +87,12 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
 //   summed input gradient of q, k, v (4096 each): T = 128  250 -> 48 us, T = 512  233 -> 79 us,
 //   T = 2048  237 -> 182 us; T = 16448  1447 -> 1354 us
 //   T = 3072,  4096 x 4096   (192 tiles): halves would take 125 us instead of 93.
-// Where several tasks share a tile, each beyond the first adds 4.7 us per 64 ranks to a whole tile (a LoRA
-// tile of the pipeline) and 1.5 us per 32 ranks to a half one (which holds half as many).
+// LoRA: every 64 ranks of a task beyond the first 64 of the tile's first task add 4.7 us to a whole tile (a
+// LoRA tile of the pipeline); in a half tile, which holds half as many tasks, each further task adds 1.5 us
+// per 32 ranks, and ranks above 64 add 5 us.  Behind full rounds the caches are cold for it: 4 us per 32
+// ranks beyond the first 32; and a last round of at most 128 whole tiles takes 0.85 of a full one there.
+// Forward, rank 128: 20000 x 2048 x 2048 195 us in whole tiles (201 as two rounds and halves), 12288 x 512
+// -> 2048 57 (63), 128 x 256 x 256 22.4 (23.8), but 16 x 1024 x 1024 41 us in whole tiles, 25 as halves.
 struct Plan {
   int whole, parts;
 };
@@ -98,18 +102,42 @@ Plan plan_gemm(const SegTable& st, int M, int N, int Kd, int pairs, size_t scrat
   const int tiles_m = (int)((virtual_rows(st, M) + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
   const int total = tiles_m * tiles_n, q = total / 256 * 256, halves = 2 * (total - q);
   const int KT = Kd / 64;
-  int live = 0, rmax = 0;
-  for (int k = 0; k < st.K; ++k) {
-    live += st.off[k + 1] > st.off[k];
-    rmax = st.rank[k] > rmax ? st.rank[k] : rmax;
+  // tasks of a tile beyond the first: the most of any tile where a tile's time shows, on average in several
+  // rounds
+  int live = 0, rmax = 0, most_whole = 0, most_half = 0;
+  {
+    int tile_w = -1, tile_h = -1, in_w = 0, in_h = 0;
+    long long v = (st.off[0] + 31) / 32 * 32;
+    for (int k = 0; k < st.K; ++k) {
+      rmax = st.rank[k] > rmax ? st.rank[k] : rmax;
+      const int len = st.off[k + 1] - st.off[k];
+      if (len == 0) continue;
+      ++live;
+      auto enter = [&](int rows, int& tile, int& in, int& most) {
+        const int first = (int)(v / rows), last = (int)((v + len - 1) / rows);
+        in = first == tile ? in + 1 : 1;
+        most = in > most ? in : most;
+        if (last > first) in = 1;
+        tile = last;
+      };
+      enter(BM, tile_w, in_w, most_whole);
+      enter(BM / 2, tile_h, in_h, most_half);
+      v += (len + 31) / 32 * 32;
+    }
   }
-  auto others = [&](int tiles, int most) {   // tasks of a tile beyond the first
-    const int n = (live + tiles - 1) / tiles;
-    return pairs * ((n < most ? n : most) - (n > 0 ? 1 : 0));
+  auto others = [&](int tiles, int most) {
+    const int n = total > 256 ? (live + tiles - 1) / tiles : most;
+    return pairs * (n > 0 ? (n < most ? n : most) - 1 : 0);
   };
-  const double whole_fixed = 10.0 + 4.7 * others(tiles_m, 8) * ((rmax + 63) / 64);
-  const double half_fixed = 12.0 + 1.5 * others(2 * tiles_m, 4) * ((rmax + 31) / 32);
-  auto whole_us = [&](int tiles) { return (double)((tiles + 255) / 256) * (whole_fixed + 1.3 * KT); };
+  const int r64 = rmax > 0 ? (rmax + 63) / 64 : 1, r32 = rmax > 0 ? (rmax + 31) / 32 : 1;
+  const double whole_fixed = 10.0 + 4.7 * (pairs * (r64 - 1) + others(tiles_m, most_whole) * r64);
+  const double half_fixed =
+      12.0 + pairs * (q > 0 ? 4.0 * (r32 - 1) : (r32 > 2 ? 5.0 : 0.0)) + 1.5 * others(2 * tiles_m, most_half) * r32;
+  auto whole_us = [&](int tiles) {
+    const int last = tiles % 256;
+    const double part = last == 0 ? 0.0 : (tiles > 256 && last <= 128 ? 0.85 : 1.0);
+    return (tiles / 256 + part) * (whole_fixed + 1.3 * KT);
+  };
   Plan best{total, 1};
   double best_us = whole_us(total);
   for (int parts = 1; halves > 0 && parts <= kMaxParts && parts <= KT; ++parts) {

@@ -33,18 +33,29 @@ SPLIT_ROWS = [
     ((4300, 64, 8256, [2000, 2140], [16, 33], 0), {"G_rows": 128, "G_parts": 8}),
 ]
 
+# bf16, h and d multiples of 64: whole tiles that hold several tasks of mixed ranks (forward, backward)
+_SHARED = [1, 255, 257, 31, 33, 95, 97, 160, 161, 500, 12, 700] * 4
+WHOLE_TILES = [
+    ((9268, 128, 1024, _SHARED, [8, 64, 128, 16] * 12, 20), {"Y": "whole"}),
+    ((9268, 1024, 128, _SHARED, [8, 64, 128, 16] * 12, 20), {"dX": "whole"}),
+    ((9268, 128, 1024, _SHARED, [5, 33, 127, 12] * 12, 20), {"Y": "whole"}),
+    ((9268, 1024, 128, _SHARED, [5, 33, 127, 12] * 12, 20), {"dX": "whole"}),
+]
+
 # Isolation of a diverged task (the last entry of a case) from its neighbours
 ISOLATION = [
     # dtype, (T, h, d, tokens, ranks, lead), form, task
     # ragged ranks, whole tiles: A_k's tile put together in registers, 64-row blocks of the low-rank rows
-    ("bf16", (17000, 64, 128, [9000, 7900], [5, 12], 3), {"Y": "whole", "dX": "whole", "Z_rows": 64}, 0),
-    ("bf16", (1100, 64, 64, [300, 90, 700], [9, 127, 33], 7), {"Y": "whole", "dX": "whole", "Z_rows": 32}, 1),
+    ("bf16", (17000, 1024, 64, [9000, 7900], [5, 12], 3), {"dX": "whole", "Z_rows": 64}, 0),
+    ("bf16", (9268, 1024, 128, _SHARED, [5, 33, 127, 12] * 12, 20), {"dX": "whole"}, 14),
+    ("bf16", (9268, 128, 1024, _SHARED, [8, 64, 128, 16] * 12, 20), {"Y": "whole"}, 14),
+    ("bf16", (1100, 64, 64, [300, 90, 700], [9, 127, 33], 7), {"Y": "halves", "dX": "halves", "Z_rows": 32}, 1),
     ("bf16", (300, 64, 64, [60, 90, 33, 100], [9, 127, 33, 2], 7), {"Y": "halves", "dX": "halves"}, 1),
     ("bf16", (700, 1088, 64, [300, 33, 360], [3, 20, 30], 2), {"Z_rows": 32, "Z_parts": 1}, 1),
     ("bf16", (4300, 4160, 64, [2000, 2140], [16, 33], 60), {"Z_rows": 128, "Z_parts": 4}, 0),
     ("bf16", (33100, 64, 64, [16500, 16500], [1, 44], 60), {"Z_rows": 128, "Z_parts": 1}, 1),
     # a round of whole tiles with halves behind it; contraction ranges
-    ("bf16", (4300, 512, 4096, [2100, 100, 2050], [16, 24, 64], 50), {"Y": "mixed", "dX": "halves"}, 1),
+    ("bf16", (4300, 1024, 4096, [2100, 100, 2050], [16, 24, 30], 50), {"Y": "mixed", "dX": "halves"}, 1),
     # general tiles
     ("bf16", (2200, 139, 2101, [1000, 33, 1100], [7, 64, 32], 25), {"Y": "128"}, 1),
     ("f32", (2200, 139, 2101, [1000, 33, 1100], [7, 64, 32], 25), {"Y": "128"}, 1),

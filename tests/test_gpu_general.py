@@ -154,6 +154,15 @@ def test_contraction_ranges_of_low_rank_rows(case):
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"ranges, W = 0 {case}")
 
 
+@pytest.mark.parametrize("case", [c for c, _ in form_cases.WHOLE_TILES])
+def test_whole_tiles_of_several_tasks(case):
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=84)
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"whole tiles {case[:3]}")
+    inp.W.zero_()
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"whole tiles, W = 0 {case[:3]}")
+
+
 @pytest.mark.parametrize("what", ["A", "B", "X", "dY"])
 @pytest.mark.parametrize("dtype,case,j", [(t, c, j) for t, c, _, j in form_cases.ISOLATION])
 def test_isolation_from_non_finite_values_in_every_form(dtype, case, j, what):
