@@ -1061,10 +1061,13 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
 // Token ranges per task of up to `longest` tokens for the gradient kernels, one number for dB and dA: as many
 // as give every CU a block (at most 16, at least 256 tokens each).  More cost their reduction more than they
 // bring: 6000 tokens of 4 tasks, 4096 x 4096, rank 64, forward + backward 423 us with two blocks per CU, 411
-// us with one.
+// us with one.  Ranks above 64 leave a CU one block (99 KB of LDS): there no more than 256 in all (65536
+// tokens of one task, 1024 -> 4096, rank 128, backward 843 us with 280 blocks, 753 with 240).
 int grad_ranges(const SegTable& st, int wide_b, int wide_a, int longest) {
   const int blocks = st.K * ((wide_b + 127) / 128 + (wide_a + 127) / 128);
-  int s = (256 + blocks - 1) / blocks;
+  int rmax = 0;
+  for (int k = 0; k < st.K; ++k) rmax = st.rank[k] > rmax ? st.rank[k] : rmax;
+  int s = (256 + (rmax > 64 ? 0 : blocks - 1)) / blocks;
   s = s < 16 ? s : 16;
   s = s < longest / 256 ? s : longest / 256;
   return s > 1 ? s : 1;
