@@ -266,10 +266,11 @@ __device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const
 // go to memory in fp32 and k_gen_reduce adds them in order.
 // A tile's LDS writes and the next loads are issued between its MFMA groups, whose fragments are read
 // one group ahead; tiles that need no masks load without bounds arithmetic.
-// Bound by the fp32 matrix rate in fp32 (153 TFLOP/s for a large product on this card): T = 2048,
-// 4096 x 4096: 570 us forward, 510 us backward layout (121 and 135 TFLOP/s; 693 and 550 us with loads
-// and LDS writes behind the MFMAs, 1714 and 1686 us on the vector ALUs); T = 1024: 279 and 270 us.  bf16, T = 2048, 4100 x 4100: 160 and 144 us (206 and 151), bound by LDS traffic
-// and the wait for each tile's loads.
+// Bound by the fp32 matrix rate in fp32 (153 TFLOP/s for a large product on this card).  Median and least of
+// 20 traced passes: T = 2048, 4096 x 4096 561 and 513 us forward, 551 and 503 us backward layout (1714 and
+// 1686 us on the vector ALUs; an untraced forward and backward pass takes 1060 us, of which the low-rank
+// launches are 57); T = 1024 300 and 287, 293 and 280 us.  bf16, T = 2048, 4100 x 4100: 171 and 150 us,
+// bound by LDS traffic and the wait for each tile's loads.
 template <typename T, int BM, int BN, bool NN, int NSEG>
 __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   constexpr int V = kV<T>, BK = 8 * V;
@@ -864,8 +865,8 @@ __global__ __launch_bounds__(512, 4) void k_gen_skinny(const GenGemmArgs<NSEG> a
 // 4 i .. 4 i + 3, one for each fragment, so that it loads (and, for dB, stores) them as one piece.
 // splits > 1: a task's tokens are cut into ranges of whole MFMA groups, one block each, whose sums go
 // to part + range * part_step ([sum of r_k][wide]) for grad_reduce to add in order.  fp32, T = 2048, 4 tasks, 4096
-// columns, rank 16: 13-14 us + 5 us of reduction for 34 MB, against 131 us with a serial sum per
-// output element.
+// columns, rank 16: dB and dA in one launch 19 us + 5 us of reduction for 67 MB, against 131 us each with
+// a serial sum per output element.
 // ------------------------------------------------------------------------------------------
 struct GenGradArgs {
   const void* Big;
