@@ -33,13 +33,19 @@ SPLIT_ROWS = [
     ((4300, 64, 8256, [2000, 2140], [16, 33], 0), {"G_rows": 128, "G_parts": 8}),
 ]
 
-# bf16, h and d multiples of 64: whole tiles that hold several tasks of mixed ranks (forward, backward)
+# bf16, h and d multiples of 64: whole tiles that hold several tasks of mixed ranks (forward, backward).
+# (Fewer than 256 tiles of several tasks run as halves.)
 _SHARED = [1, 255, 257, 31, 33, 95, 97, 160, 161, 500, 12, 700] * 4
 WHOLE_TILES = [
     ((9268, 128, 1024, _SHARED, [8, 64, 128, 16] * 12, 20), {"Y": "whole"}),
     ((9268, 1024, 128, _SHARED, [8, 64, 128, 16] * 12, 20), {"dX": "whole"}),
     ((9268, 128, 1024, _SHARED, [5, 33, 127, 12] * 12, 20), {"Y": "whole"}),
     ((9268, 1024, 128, _SHARED, [5, 33, 127, 12] * 12, 20), {"dX": "whole"}),
+] + [
+    # one, three and five base tiles in front of the LoRA tiles: the short forms of prologue and tail
+    c for k in (64, 192, 320) for c in (
+        ((9268, k, 1024, _SHARED, [128, 8, 33, 64] * 12, 20), {"Y": "whole"}),
+        ((9268, 1024, k, _SHARED, [128, 8, 33, 64] * 12, 20), {"dX": "whole"}))
 ]
 
 # Isolation of a diverged task (the last entry of a case) from its neighbours

@@ -59,7 +59,8 @@ def test_small_shapes(dtype, case):
 def test_short_contractions(case):
     """The base-product kernel keeps three tiles of A and two of the weight in flight; with
     fewer tiles than that in all (small h or d, with and without LoRA tiles behind them) its
-    prologue and its last tiles take their short forms."""
+    prologue and its last tiles take their short forms.  (Where a tile holds several tasks these
+    sizes run half tiles; whole ones of that kind are in tests/form_cases.py, WHOLE_TILES.)"""
     T, h, d, tokens, ranks, lead = case
     inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=23, scal=[1.0 + 0.5 * i for i in range(len(ranks))])
     out = run_hip(inp)
