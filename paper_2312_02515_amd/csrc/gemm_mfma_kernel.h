@@ -32,14 +32,19 @@
 // sub-step ahead of their use (two register sets); a weight fragment serves both sub-steps of
 // its half tile and is re-read in place right behind its last MFMA, a sub-step before its next
 // use.  At most one memory instruction rides behind each MFMA:
-//   sub-steps 0..2 of tile kt: MFMAs | LDS reads of the next sub-step's fragments
+//   sub-steps 0..2 of tile kt: MFMAs | LDS reads of the next sub-step's fragments | the direct loads
+//               of A's tile kt+2
 //   s_waitcnt vmcnt(4), lgkmcnt(0); barrier  (tile kt+1 visible -- the 4 loads still in flight are
 //                                             A's of tile kt+2; every wave holds its last fragments
 //                                             of tile kt in registers: kt's stages are free)
-//   sub-step 3: MFMAs | LDS reads of tile kt+1's first fragments | the direct loads of Bm's tile
-//               kt+2, then of A's tile kt+3
-// A is loaded two tiles ahead because its rows come from HBM, once per launch: with one tile of
-// lead the blocks that share a row strip stalled together on every cold line (the time lost grew
+//   sub-step 3: MFMAs | LDS reads of tile kt+1's first fragments | the direct loads of Bm's tile kt+2
+// Where the loads ride matters: a wave-wide load of 16 B per lane occupies the CU's address path for 16
+// cycles (measured: 62 B per clock and CU), so the 64 loads of a tile need 1024 of the 2048 cycles that its
+// MFMAs take.  All of them behind the barrier, in sub-step 3 (512 cycles of MFMAs), made every wave stand in
+// that queue; spread over the tile, 16384 x 5120 x 5120 takes 562 / 551 us forward / backward instead of
+// 579 / 574, 32768 rows 1131 / 1125 instead of 1180 / 1177, and half tiles 2048 x 11008 -> 4096 137 instead of 150.
+// A keeps more than one tile of lead because its rows come from HBM, once per launch: with two stages
+// and one tile of lead the blocks that share a row strip stalled together on every cold line (the time lost grew
 // linearly with the rate at which A is read from HBM, at every shape measured).  Bm, the weight,
 // is read from the Infinity Cache and keeps one tile of lead; 3 + 2 stages of 32 KiB are all of
 // the CU's 160 KiB of LDS, which is why the block's piece table lives in a register.
@@ -420,22 +425,17 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // not: they serve both sub-steps of a half tile, and in the second of them (h = 1) fragment j
   // is re-read for the next half tile right behind its last MFMA (slot HM j + HM - 1), a whole
   // sub-step before its next use -- 16 registers instead of 32.  The reads come from (rsa, rsb)
-  // (if rd); in sub-step 3, after the barrier, the remaining slots carry the PER_TILE loads of
-  // the tile `lc` into (lsa, lsb) (if ld).  rd and ld are std::true_type / std::false_type in
-  // the steady-state loop, so that it compiles to straight-line code, and plain bools in the few
+  // (if rd); `load(n)` is called in the n-th slot behind the first HM that carries no read, and issues the
+  // direct load that rides there, if any.  rd is std::true_type / std::false_type in
+  // the steady-state loop, so that it compiles to straight-line code, and a plain bool in the few
   // tiles around it; `fo` is std::true_type there (base tiles: every piece) and a FragOn in
   // the tiles that may be LoRA tiles.
-  auto substep = [&](auto S_, auto rd, const char* rsa, const char* rsb, auto ldb, const LoadCtx& lcb, char* lsb, auto lda,
-                     const LoadCtx& lca, char* lsa, const auto& fo) {
+  auto substep = [&](auto S_, auto rd, const char* rsa, const char* rsb, auto load, const auto& fo) {
     constexpr int S = decltype(S_)::value;
     constexpr int q = S / 2, h = S % 2;
     constexpr int NS_ = (S + 1) % 4;                 // the sub-step whose row fragments are read now
     constexpr int nq = NS_ / 2, nh = NS_ % 2;
-    // slots of the PER_TILE loads: behind the MFMAs of weight fragments 1 .. FN - 1 that carry no
-    // fragment read, or behind all of them where those are too few
-    constexpr bool SHARED = (FN - 1) * (HM - 1) < PER_TILE;
-    constexpr int SPF = SHARED ? HM : HM - 1;        // slots per weight fragment
-    static_assert((FN - 1) * SPF >= PER_TILE, "load slots");
+    int slot = 0;
 #pragma unroll
     for (int m = 0; m < NMF; ++m) {
       const int j = m / HM, i = m % HM;
@@ -444,12 +444,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       if (on) mfma_16x16x32(acc[h * HM + i][j], bfr[j], af[h][i]);
       if (rd && m < HM) read_a(rsa, nq, nh, m, af[nh]);
       if (rd && h == 1 && i == HM - 1) read_b(rsb, nq, j);
-      if (S == 3 && m >= HM && i < SPF) {
-        // the Bm side first: the next barrier waits for it and lets the A loads behind it fly on
-        const int idx = (j - 1) * SPF + i;
-        if (ldb && idx < LPB) issue_one(lcb, LPA + idx, nullptr, lsb);
-        if (lda && idx >= LPB && idx < PER_TILE) issue_one(lca, idx - LPB, lsa, nullptr);
-      }
+      if (m >= HM && !(h == 1 && i == HM - 1)) load(slot++);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
@@ -461,26 +456,47 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   constexpr std::integral_constant<int, 3> S3{};
   const LoadCtx none{false, nullptr, nullptr, LoraTile{0, -1, 0}};
 
-  // A tile whose operands sit in (ca, cb): sub-steps 0..2, barrier, sub-step 3 with the reads of
-  // the next tile's first fragments from (na, nb) (if rd), the Bm loads of the tile after that,
-  // `lcb`, into cb (if ldb) and the A loads of the tile after that one, `lca`, into ca (if lda).
-  // `abehind`: whether A loads were issued behind the Bm loads the barrier waits for (the
-  // previous tile's lda) -- vector loads return in order, so the wait leaves exactly those LPA
-  // loads in flight.
-  auto tile = [&](char* ca, char* cb, const char* na, const char* nb, auto rd, auto ldb, const LoadCtx& lcb, auto lda,
-                  const LoadCtx& lca, auto abehind, const auto& fo) {
-    substep(S0, yes, ca, cb, no, none, nullptr, no, none, nullptr, fo);
-    substep(S1, yes, ca, cb, no, none, nullptr, no, none, nullptr, fo);
-    substep(S2, yes, ca, cb, no, none, nullptr, no, none, nullptr, fo);
+  // A tile whose operands sit in (ca, cb): sub-steps 0..2 with the late loads of `lcl` into lsl (if ldl; whole
+  // tiles: the A side of tile v + 2, half tiles: its Bm side), barrier, sub-step 3 with the reads of the next
+  // tile's first fragments from (na, nb) (if rd) and the early loads of `lce` (if lde; whole tiles: the Bm side
+  // of tile v + 2 into cb, half tiles: the A side of tile v + 3 into ca).
+  // `behind`: whether loads of tile v + 2 follow those of tile v + 1 that the barrier waits for -- vector
+  // loads return in order, so the wait leaves exactly the younger ones in flight.
+  // Loads per sub-step: a wave-wide load keeps the CU's one address path busy for 16 cycles.
+  constexpr int EARLY = HALF ? LPA : LPB, LATE = HALF ? LPB : LPA;
+  constexpr int E_GAP = 2, L0 = LATE < 3 ? LATE : 3, L0_GAP = 4, L1 = LATE - L0 < 3 ? LATE - L0 : 3, L1_GAP = 3, L2 = LATE - L0 - L1;
+  static_assert((EARLY - 1) * E_GAP < (FN - 1) * (HM - 1) && (L0 - 1) * L0_GAP < (FN - 1) * HM &&
+                    (L1 == 0 || (L1 - 1) * L1_GAP < (FN - 1) * (HM - 1)) && (L2 == 0 || (L2 - 1) * L1_GAP < (FN - 1) * HM),
+                "load slots");
+  auto tile = [&](char* ca, char* cb, const char* na, const char* nb, auto rd, auto ldl, const LoadCtx& lcl, char* lsl,
+                  auto lde, const LoadCtx& lce, auto behind, const auto& fo) {
+    // load `first` + n / gap of the side in every gap-th slot
+    auto late = [&](int slot, int first, int count, int gap) {
+      if (!ldl || slot % gap != 0 || slot / gap >= count) return;
+      if constexpr (HALF)
+        issue_one(lcl, LPA + first + slot / gap, nullptr, lsl);
+      else
+        issue_one(lcl, first + slot / gap, lsl, nullptr);
+    };
+    auto early = [&](int slot) {
+      if (!lde || slot % E_GAP != 0 || slot / E_GAP >= EARLY) return;
+      if constexpr (HALF)
+        issue_one(lce, slot / E_GAP, ca, nullptr);
+      else
+        issue_one(lce, LPA + slot / E_GAP, nullptr, cb);
+    };
+    substep(S0, yes, ca, cb, [&](int slot) { late(slot, 0, L0, L0_GAP); }, fo);
+    substep(S1, yes, ca, cb, [&](int slot) { late(slot, L0, L1, L1_GAP); }, fo);
+    substep(S2, yes, ca, cb, [&](int slot) { late(slot, L0 + L1, L2, L1_GAP); }, fo);
     // the next tile has landed (this wave's part), every fragment of this tile is in registers
     // (the weight fragments of this half tile stay in use until sub-step 3 re-reads them)
-    if (abehind)
+    if (behind)
       wait_vmcnt<HALF ? PER_TILE : LPA>();
     else
       wait_vmcnt<0>();
     wait_lds();
     __builtin_amdgcn_s_barrier();
-    substep(S3, rd, na, nb, ldb, lcb, cb, lda, lca, ca, fo);
+    substep(S3, rd, na, nb, early, fo);
   };
 
   // ---- main contraction loop.  Tile v of a pass uses A stage v % 3 and Bm stage v % 2; the steady
@@ -521,19 +537,18 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
 #pragma unroll
       for (int idx = 0; idx < LPB; ++idx) issue_one(lc, LPA + idx, nullptr, sb);
     };
-    // tiles 0 and 1 whole and the A side of tile 2 (HALF: all of it); the first reads need tile 0
+    // whole tiles: tiles 0 and 1.  HALF: also the A side of tile 2.  The first reads need tile 0
     issue_a(base_ctx(0), sA[0]);
     issue_b(base_ctx(0), sB[0]);
-    if (VT > 2) {
+    if (VT > 1) {
       issue_a(ctx_of(1), sA[1]);
       issue_b(ctx_of(1), sB[1]);
-      issue_a(ctx_of(2), sA[2]);
-      if constexpr (HALF) issue_b(ctx_of(2), sB[2]);
-      wait_vmcnt<HALF ? 2 * PER_TILE : 2 * LPA + LPB>();
-    } else if (VT > 1) {
-      issue_a(ctx_of(1), sA[1]);
-      issue_b(ctx_of(1), sB[1]);
-      wait_vmcnt<LPA + LPB>();
+      if (HALF && VT > 2) {
+        issue_a(ctx_of(2), sA[2]);
+        wait_vmcnt<PER_TILE + LPA>();
+      } else {
+        wait_vmcnt<PER_TILE>();
+      }
     } else {
       wait_vmcnt<0>();
     }
@@ -543,40 +558,37 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
 #pragma unroll
     for (int i = 0; i < HM; ++i) read_a(sA[0], 0, 0, i, af[0]);
     __builtin_amdgcn_sched_barrier(0);
-    // steady state, six base tiles per trip: each has a successor to read, a base tile two ahead
-    // for its Bm loads and one three ahead for its A loads
     int v = 0;
     // (A half tile's short contraction is not worth fetching six copies of the loop's code.)
-    for (; !HALF && v + 8 < KT; v += 6) {
-      tile(sA[0], sB[0], sA[1], sB[1], yes, yes, base_ctx(v + 2), yes, base_ctx(v + 3), yes, yes);
-      tile(sA[1], sB[1], sA[2], sB[0], yes, yes, base_ctx(v + 3), yes, base_ctx(v + 4), yes, yes);
-      tile(sA[2], sB[0], sA[0], sB[1], yes, yes, base_ctx(v + 4), yes, base_ctx(v + 5), yes, yes);
-      tile(sA[0], sB[1], sA[1], sB[0], yes, yes, base_ctx(v + 5), yes, base_ctx(v + 6), yes, yes);
-      tile(sA[1], sB[0], sA[2], sB[1], yes, yes, base_ctx(v + 6), yes, base_ctx(v + 7), yes, yes);
-      tile(sA[2], sB[1], sA[0], sB[0], yes, yes, base_ctx(v + 7), yes, base_ctx(v + 8), yes, yes);
+    for (; !HALF && v + 7 < KT; v += 6) {
+      tile(sA[0], sB[0], sA[1], sB[1], yes, yes, base_ctx(v + 2), sA[2], yes, base_ctx(v + 2), yes, yes);
+      tile(sA[1], sB[1], sA[2], sB[0], yes, yes, base_ctx(v + 3), sA[0], yes, base_ctx(v + 3), yes, yes);
+      tile(sA[2], sB[0], sA[0], sB[1], yes, yes, base_ctx(v + 4), sA[1], yes, base_ctx(v + 4), yes, yes);
+      tile(sA[0], sB[1], sA[1], sB[0], yes, yes, base_ctx(v + 5), sA[2], yes, base_ctx(v + 5), yes, yes);
+      tile(sA[1], sB[0], sA[2], sB[1], yes, yes, base_ctx(v + 6), sA[0], yes, base_ctx(v + 6), yes, yes);
+      tile(sA[2], sB[1], sA[0], sB[0], yes, yes, base_ctx(v + 7), sA[1], yes, base_ctx(v + 7), yes, yes);
     }
-    // (v is a multiple of 6 here.)  The up to seven base tiles left that still have all of the
-    // above: the same straight-line code, with the stage addresses in registers
     auto stage_a = [&](int u) { return u % 3 == 0 ? sA0 : (u % 3 == 1 ? sA1 : sA2); };
     auto stage_b = [&](int u) {
       if constexpr (HALF) return u % 3 == 0 ? sB0 : (u % 3 == 1 ? sB1 : sB2);
       else return u % 2 == 0 ? sB0 : sB1;
     };
-    constexpr int LEAD_B = HALF ? 3 : 2;
     for (; v + 3 < KT; ++v)
-      tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), yes, yes, base_ctx(v + LEAD_B), yes, base_ctx(v + 3), yes,
-           yes);
+      tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), yes, yes, base_ctx(v + 2), HALF ? stage_b(v + 2) : stage_a(v + 2), yes,
+           base_ctx(HALF ? v + 3 : v + 2), yes, yes);
     if constexpr (HALF) {
-      // (the last three: nothing left to load)
+      // (the last three: tile VT - 1's weight is the last load)
       for (; v < VT; ++v)
-        tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, no, none, no, none, v + 2 < VT, yes);
+        tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, base_ctx(v + 2), stage_b(v + 2), no,
+             none, v + 2 < VT, yes);
       continue;
     }
     // the last base tiles and the LoRA tiles
     auto frags_at = [&](int u) { return u < KT ? frags_of(LoraTile{0, -1, 0}, true) : frags_of(find_lora(u - KT), false); };
     for (; v < VT; ++v) {
-      tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, v + 2 < VT ? ctx_of(v + 2) : none,
-           v + 3 < VT, v + 3 < VT ? ctx_of(v + 3) : none, v + 2 < VT, frags_at(v));
+      const LoadCtx lc = v + 2 < VT ? ctx_of(v + 2) : none;
+      tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, lc, stage_a(v + 2), v + 2 < VT, lc,
+           v + 2 < VT, frags_at(v));
     }
   }  // operand pairs
 
