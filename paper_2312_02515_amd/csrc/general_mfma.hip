@@ -239,10 +239,24 @@ __device__ __forceinline__ void block_tile(const Args& a, int bid, int* tm, int*
   *tn = in_g / gm;
 }
 
-// C element store of one 32 x 32 accumulator: lane holds column l32 and rows 8 g + 4 lhi + e
+// Output column behind column n of the grid's tiles (-1: none).  NN: the weight's rows are loaded in pieces of V
+// columns; the piece that crosses the right edge is loaded so that it ends there and is not shifted into
+// place, so its V columns are the output's last V, some of them computed twice, with the same bits.  (Shifted
+// into place tile by tile, the blocks at the right edge took up to twice as long and every launch waited for
+// them: forward, fp32 3000 x 4001 -> 4001 956 us against 728, 913 x 1000 -> 1500 67 against 44, bf16 156
+// against 127 for 2048 x 4100 -> 4100.)
+template <typename T, bool NN>
+__device__ __forceinline__ int real_column(int n, int N) {
+  constexpr int V = kV<T>;
+  const int piece = n / V * V;
+  if (NN && N >= V && piece < N && piece + V > N) return N - V + n % V;
+  return n < N ? n : -1;
+}
+
+// C element store of one 32 x 32 accumulator: lane holds column `col` (-1: none) and rows 8 g + 4 lhi + e
 template <typename T>
 __device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const RowPiece& p, int col, int lhi) {
-  if (col < N) {
+  if (col >= 0) {
 #pragma unroll
     for (int g = 0; g < 4; ++g)
 #pragma unroll
@@ -309,7 +323,7 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   int p0 = (int)((long long)total_kt * part / a.parts), p1 = (int)((long long)total_kt * (part + 1) / a.parts);
 
   const int ar = tid >> 3, ac = tid & 7;             // K-contiguous: row (of 32) and piece of this thread
-  const bool n_edge = NN && col0 + BN > N;
+  const bool narrow = NN && N < V;                   // no whole piece in a row of W
   // fragment addresses
   const int fsw = (l32 >> 1) & 7;
   const int a_off = (wm * WM + l32) * 128, b_off = (wn * WN + l32) * 128;
@@ -337,11 +351,13 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
     }
     const char* bbase;
     if constexpr (NN) {
-      bbase = reinterpret_cast<const char*>(W + col0);
+      bbase = reinterpret_cast<const char*>(W);
 #pragma unroll
       for (int it = 0; it < NB; ++it) {
         const int idx = tid + 256 * it;
-        boff[it] = (unsigned)(((size_t)(idx / CPR) * N + (idx % CPR) * V) * sizeof(T));
+        int n = col0 + (idx % CPR) * V;
+        n = n <= N - V || narrow ? n : N - V;        // (see real_column)
+        boff[it] = (unsigned)(((size_t)(idx / CPR) * N + n) * sizeof(T));
       }
     } else {
       bbase = reinterpret_cast<const char*>(W + (size_t)col0 * Kd);
@@ -352,8 +368,8 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
       }
     }
     const size_t bstep = (NN ? (size_t)BK * N : (size_t)BK) * sizeof(T);
-    // tiles before `whole` need no masks (none does in a block at the ragged right edge)
-    const int whole = n_edge ? 0 : Kd / BK;
+    // tiles before `whole` need no masks
+    const int whole = narrow ? 0 : Kd / BK;
     typedef typename Piece16<T>::type Piece;
     u32x4 ra[NA], rb[NB];
     auto load = [&](int kt) {
@@ -376,7 +392,8 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
           const int idx = tid + 256 * it;
           int k = k0 + idx / CPR;
           k = k < Kd ? k : Kd - 1;
-          rb[it] = load_piece<T>(W + (size_t)k * N, col0 + (idx % CPR) * V, N);
+          if (narrow) rb[it] = load_piece<T>(W + (size_t)k * N, col0 + (idx % CPR) * V, N);
+          else rb[it] = *reinterpret_cast<const Piece*>(bbase + (ptrdiff_t)(k - idx / CPR) * N * (ptrdiff_t)sizeof(T) + boff[it]);
         } else {
           rb[it] = load_piece<T>(reinterpret_cast<const T*>(bbase + boff[it]) - ac * V, k0 + ac * V, Kd);
         }
@@ -408,7 +425,6 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
         for (int it = 0; it < NB; ++it) {
           if constexpr (NN) {
             const int idx = tid + 256 * it;
-            rb[it] = tail_shift<T>(rb[it], col0 + (idx % CPR) * V, N);
             if (k0 + idx / CPR >= Kd) rb[it] = u32x4{0, 0, 0, 0};
           } else {
             rb[it] = tail_shift<T>(rb[it], k0 + ac * V, Kd);
@@ -518,8 +534,8 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
           const u32x4 lf = *reinterpret_cast<const typename Piece16<T>::type*>(lrow + q);
 #pragma unroll
           for (int j = 0; j < FN; ++j) {
-            int n = col0 + wn * WN + 32 * j + l32;
-            n = n < N ? n : N - 1;
+            int n = real_column<T, NN>(col0 + wn * WN + 32 * j + l32, N);
+            n = n >= 0 ? n : N - 1;
             union {
               u32x4 v;
               T e[V];
@@ -552,7 +568,7 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
     RowPiece p = pc[i];
     if (wm == 1) p = pc[NA / 2 + i];
 #pragma unroll
-    for (int j = 0; j < FN; ++j) store_frag<T>(acc[i][j], C, N, p, col0 + wn * WN + 32 * j + l32, lhi);
+    for (int j = 0; j < FN; ++j) store_frag<T>(acc[i][j], C, N, p, real_column<T, NN>(col0 + wn * WN + 32 * j + l32, N), lhi);
   }
 }
 
@@ -564,7 +580,7 @@ struct GenReduceArgs {
   int K;
   int off[kMaxK + 1];
 };
-template <typename T, int BM, int BN>
+template <typename T, int BM, int BN, bool NN>
 __global__ __launch_bounds__(256) void k_gen_reduce(const GenReduceArgs a) {
   constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
   const int lane = threadIdx.x & 63;
@@ -587,7 +603,7 @@ __global__ __launch_bounds__(256) void k_gen_reduce(const GenReduceArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[4 * g + e] += v[e];
     }
-  store_frag<T>(acc, static_cast<T*>(a.C), a.N, p, tn * BN + wn * WN + 32 * j + (lane & 31), lane >> 5);
+  store_frag<T>(acc, static_cast<T*>(a.C), a.N, p, real_column<T, NN>(tn * BN + wn * WN + 32 * j + (lane & 31), a.N), lane >> 5);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1112,7 +1128,7 @@ hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch,
   r.parts = a.parts;
   r.K = a.K;
   for (int k = 0; k <= kMaxK; ++k) r.off[k] = a.off[k];
-  hipLaunchKernelGGL((k_gen_reduce<T, 64, 64>), dim3((unsigned)(pl.tiles_m * pl.tiles_n)), dim3(256), 0, s, r);
+  hipLaunchKernelGGL((k_gen_reduce<T, 64, 64, NN>), dim3((unsigned)(pl.tiles_m * pl.tiles_n)), dim3(256), 0, s, r);
   return hipGetLastError();
 }
 

@@ -60,6 +60,21 @@ def test_general_kernel_forms(case, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("T,h,d", [(1500, 520, 1024 + r) for r in range(1, 9)] + [   # 64 x 64 tiles, every remainder of a piece
+    (2200, 139, 2113), (2200, 139, 2175), (2200, 139, 2167),                         # 128 x 128
+    (100, 2050, 67), (100, 4200, 1)])                                                # ranges; rows shorter than a piece
+def test_last_columns_of_general_tiles(dtype, T, h, d):
+    """The piece of columns that crosses the right edge, with ranks and rows of no task beside it; an Inf in
+    the last column of W stays there."""
+    inp = _inputs(T, h, d, [T // 2, T // 3], [9, 24], dtype, lead=5, seed=83)
+    check_full(inp, run_hip(inp), TOL[dtype], label=f"last columns {T, h, d}")
+    inp.W[0, -1] = float("inf")
+    inp.X[:, 0] = 1.0
+    Y = run_hip(inp)["Y"]
+    assert torch.isinf(Y[:, -1]).all() and torch.isfinite(Y[:, :-1]).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_general_group_sum_in_large_tiles(dtype):
     """The summed input gradient in 128 x 128 tiles (2200 x 2101 outputs)."""
     ins = _group_inputs(2200, 2101, [139, 320], [1000, 1150], [[7, 64], [32, 5]], dtype, lead=25, seed=81)
