@@ -137,6 +137,8 @@ struct GenGemmArgs {
   void* C;
   float* part;                           // fp32 partial tiles when parts > 1
   int M, N, tiles_m, tiles_n, parts;
+  int units;                             // tiles of the launch (times parts: its blocks)
+  int t0;                                // quarters: the first 128 x 128 tile (of tiles_m x tiles_n) cut into them
   int K;
   int off[kMaxK + 1];
   const void* A[NSEG];
@@ -222,21 +224,28 @@ __device__ __forceinline__ RowPiece find_piece(const Args& a, const RowAxis& x, 
 
 // Block id -> (tile, part).  Consecutive ids go round-robin over the 8 XCDs; each XCD takes a
 // contiguous eighth of the order (8 row tiles x all column tiles at a time, column by column), so
-// that the blocks it runs together share operand strips in its L2.
-template <typename Args>
-__device__ __forceinline__ void block_tile(const Args& a, int bid, int* tm, int* tn, int* part) {
-  const int total = a.tiles_m * a.tiles_n * a.parts;
-  const int per = total / 8;
-  int t = bid < per * 8 ? (bid % 8) * per + bid / 8 : bid;
-  *part = t % a.parts;
-  t /= a.parts;
+// that the blocks it runs together share operand strips in its L2.  `unit` numbers the partial tiles.
+struct BlockTile {
+  int tm, tn, part, unit;
+};
+template <bool QUARTERS, typename Args>
+__device__ __forceinline__ BlockTile tile_of_unit(const Args& a, int u) {
+  const int t = QUARTERS ? a.t0 + u / 4 : u;
   constexpr int GM = 8;
   const int gsize = GM * a.tiles_n;
   const int group = t / gsize, first = group * GM;
   const int gm = (a.tiles_m - first) < GM ? (a.tiles_m - first) : GM;
   const int in_g = t - group * gsize;
-  *tm = first + in_g % gm;
-  *tn = in_g / gm;
+  const int tm = first + in_g % gm, tn = in_g / gm;
+  return QUARTERS ? BlockTile{2 * tm + u % 4 / 2, 2 * tn + u % 2, 0, u} : BlockTile{tm, tn, 0, u};
+}
+template <bool QUARTERS, typename Args>
+__device__ __forceinline__ BlockTile block_tile(const Args& a, int bid) {
+  const int per = a.units * a.parts / 8;
+  const int t = bid < per * 8 ? (bid % 8) * per + bid / 8 : bid;
+  BlockTile b = tile_of_unit<QUARTERS>(a, t / a.parts);
+  b.part = t % a.parts;
+  return b;
 }
 
 // Output column behind column n of the grid's tiles (-1: none).  NN: the weight's rows are loaded in pieces of V
@@ -285,7 +294,8 @@ __device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const
 // 1686 us on the vector ALUs; an untraced forward and backward pass takes 1060 us, of which the low-rank
 // launches are 57); T = 1024 300 and 287, 293 and 280 us.  bf16, T = 2048, 4100 x 4100: 171 and 150 us,
 // bound by LDS traffic and the wait for each tile's loads.
-template <typename T, int BM, int BN, bool NN, int NSEG>
+// QUARTERS: tiles of 64 x 64 that are quarters of 128 x 128 tiles.
+template <typename T, int BM, int BN, bool NN, int NSEG, bool QUARTERS>
 __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   constexpr int V = kV<T>, BK = 8 * V;
   constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
@@ -299,14 +309,16 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int l32 = lane & 31, lhi = lane >> 5;
-  int tm, tn, part;
-  block_tile(a, blockIdx.x, &tm, &tn, &part);
-  const int col0 = tn * BN, M = a.M, N = a.N;
+  const BlockTile bt = block_tile<QUARTERS>(a, blockIdx.x);
+  const int part = bt.part, col0 = bt.tn * BN, N = a.N;
+  if (QUARTERS && col0 >= N) return;                 // a quarter beyond the right edge
 
   RowPiece pc[NA];
   const RowAxis axis = row_axis(a);
 #pragma unroll
-  for (int f = 0; f < NA; ++f) pc[f] = find_piece(a, axis, (unsigned)tm * BM + 32 * f);
+  for (int f = 0; f < NA; ++f) pc[f] = find_piece(a, axis, (unsigned)bt.tm * BM + 32 * f);
+
+  if (QUARTERS && pc[0].n == 0) return;              // ... or below the last row
 
   f32x16 acc[FM][FN];
 #pragma unroll
@@ -551,7 +563,7 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   }
 
   if (a.parts > 1) {
-    float* dst = a.part + ((size_t)part * a.tiles_m * a.tiles_n + (size_t)tm * a.tiles_n + tn) * (BM * BN);
+    float* dst = a.part + ((size_t)part * a.units + bt.unit) * (BM * BN);
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -576,22 +588,23 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
 struct GenReduceArgs {
   void* C;
   const float* part;
-  int M, N, tiles_m, tiles_n, parts;
+  int M, N, tiles_m, tiles_n, parts, units, t0;
   int K;
   int off[kMaxK + 1];
 };
-template <typename T, int BM, int BN, bool NN>
+template <typename T, int BM, int BN, bool NN, bool QUARTERS>
 __global__ __launch_bounds__(256) void k_gen_reduce(const GenReduceArgs a) {
   constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int j = blockIdx.x % FN, i = blockIdx.x / FN % FM, tile = blockIdx.x / (FM * FN);
-  const int tm = tile / a.tiles_n, tn = tile % a.tiles_n;
-  const RowPiece p = find_piece(a, row_axis(a), (unsigned)tm * BM + wm * WM + 32 * i);
+  const BlockTile bt = tile_of_unit<QUARTERS>(a, tile);
+  if (QUARTERS && bt.tn * BN >= a.N) return;
+  const RowPiece p = find_piece(a, row_axis(a), (unsigned)bt.tm * BM + wm * WM + 32 * i);
   if (p.n <= 0) return;
   const float* src = a.part + (size_t)tile * (BM * BN) + ((wave * FM + i) * FN + j) * 1024 + lane * 4;
-  const size_t step = (size_t)a.tiles_m * a.tiles_n * (BM * BN);
+  const size_t step = (size_t)a.units * (BM * BN);
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; ++e) acc[e] = 0.f;
@@ -603,7 +616,7 @@ __global__ __launch_bounds__(256) void k_gen_reduce(const GenReduceArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[4 * g + e] += v[e];
     }
-  store_frag<T>(acc, static_cast<T*>(a.C), a.N, p, real_column<T, NN>(tn * BN + wn * WN + 32 * j + (lane & 31), a.N), lane >> 5);
+  store_frag<T>(acc, static_cast<T*>(a.C), a.N, p, real_column<T, NN>(bt.tn * BN + wn * WN + 32 * j + (lane & 31), a.N), lane >> 5);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1068,15 +1081,44 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
 // the tiles add last: 700 x 2000 fp32, 4 deep, rank 128 21.5 us against 18.4) only outputs of one column
 // block do: whole calls, tiles against skinny, 4000 x 2000 outputs 4 deep 11.4 against 22.8 us, 1500 x 2000, 32 deep 7.4
 // against 10.3, 16000 x 100, 100 deep 12.4 against 16.6, but 40000 x 50, 50 deep, rank 64 55 against 41.
-// 128 x 128 tiles once they give every CU a
-// block; below that 64 x 64, and the contraction cut into parts of at least 16 tiles until the
-// blocks fill two thirds of the chip's 512 block slots or the scratch is used up.
+// 128 x 128 tiles once they give every CU a block; below that 64 x 64, the contraction cut into `parts`
+// ranges where that is faster.  A launch costs a CU the tiles of its fullest share, so of the 128 x 128 tiles
+// only whole rounds of 256 need be run as such: the others may run as quarters of 64 x 64, in ranges.  Both
+// choices go by an estimate from measured times per contraction tile (constants below).  Forward, us:
+//   fp32  2048 x 2048 -> 2176 (272 tiles)  248 in whole tiles, 151 as one round and quarters in 8 ranges
+//         2048 x 4100 -> 4100 (528)        740 and 533 (4 ranges);   8000 x 1501 -> 701 (378)  188 and 161
+//         2048 x 2048 -> 4096 (512: two rounds) 253; quarters alone take 283
+//         1280 x 2048 -> 2048 (160: all 64 x 64) 110 in one range, 100 in two; 1024 x 2048 -> 2048 79 and 82
+//   bf16  2048 x 4100 -> 4100              128 and 104;   2048 x 2048 -> 2176  40 and 42
 struct GemmPlan {
   bool skinny, small;
-  int tiles_m, tiles_n, parts;
+  int tiles_m, tiles_n, parts;           // of 16 x 64, 64 x 64 (small) or 128 x 128
+  int whole;                             // 128 x 128: tiles [0, whole) as such, the others in quarters (small: 0)
 };
-constexpr int kMaxParts = 16, kFullTiles = 340, kTilesPerPart = 16;   // (contraction tiles of 128 bytes per row)
-long long contraction_tiles(long long Kd, int dtype) { return Kd / (dtype == MLORA_F32 ? 32 : 64); }
+constexpr int kMaxParts = 16, kMostUnits = 1024, kTilesPerPart = 4;   // (contraction tiles of 128 bytes per row)
+// us per contraction tile: a block alone on its CU, and the share of one among several
+struct StepTimes {
+  double large_alone, large, small_alone, small;
+};
+constexpr StepTimes kSteps[2] = {{1.97, 1.97, 0.70, 0.58}, {0.80, 0.60, 0.36, 0.27}};   // fp32, bf16
+// launches of n blocks of a form: 256 of them are a round
+double rounds_us(long long n, double alone, double among) { return n <= 256 ? alone : (double)((n + 255) / 256) * among; }
+// `units` 64 x 64 tiles of kt contraction tiles: fewest us, the ranges for it, at least kTilesPerPart deep
+double small_tiles_us(long long units, long long kt, const StepTimes& t, size_t scratch_limit, int* parts) {
+  double best = 0;
+  *parts = 0;
+  for (int p = 1; p <= kMaxParts && (p == 1 || (kt / p >= kTilesPerPart && units * p <= kMostUnits)); ++p) {
+    const size_t bytes = p > 1 ? (size_t)units * p * 64 * 64 * sizeof(float) : 0;
+    if (bytes > scratch_limit) break;
+    const double us = 6 + (double)((kt + p - 1) / p) * rounds_us(units * p, t.small_alone, t.small) + (p > 1 ? 4 + (double)bytes / 7e6 : 0);
+    if (*parts == 0 || us < best) {
+      best = us;
+      *parts = p;
+    }
+  }
+  return best;
+}
+long long contraction_tiles(long long Kd, int dtype) { return (Kd + (dtype == MLORA_F32 ? 31 : 63)) / (dtype == MLORA_F32 ? 32 : 64); }
 GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dtype, size_t scratch_limit) {
   const long long mv = virtual_rows(st, M);
   GemmPlan p;
@@ -1086,19 +1128,26 @@ GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dty
   const long long most_units = rmax > 32 ? 1536 : 1024;
   const long long units = (mv + 15) / 16 * ((N + 63) / 64), row_bytes = Kd_total * (dtype == MLORA_F32 ? 4 : 2);
   if (N >= 4 && row_bytes <= 4096 && units * row_bytes <= 640 << 10 && (units <= most_units || N <= 64))
-    return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1};
+    return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1, 0};
   const long long t128 = ((mv + 127) / 128) * ((N + 127) / 128);
   p.small = t128 < 256;
   const int b = p.small ? 64 : 128;
   p.tiles_m = (int)((mv + b - 1) / b);
   p.tiles_n = (N + b - 1) / b;
+  const long long tiles = (long long)p.tiles_m * p.tiles_n, kt = contraction_tiles(Kd_total, dtype);
+  const StepTimes& t = kSteps[dtype == MLORA_F32 ? 0 : 1];
   p.parts = 1;
-  const size_t tile_bytes = (size_t)p.tiles_m * p.tiles_n * b * b * 4;
+  p.whole = p.small ? 0 : (int)tiles;
   if (p.small) {
-    const long long kt = contraction_tiles(Kd_total, dtype);
-    while (p.parts < kMaxParts && (long long)p.tiles_m * p.tiles_n * p.parts < kFullTiles &&
-           kt / (p.parts + 1) >= kTilesPerPart && tile_bytes * (p.parts + 1) <= scratch_limit)
-      ++p.parts;
+    small_tiles_us(tiles, kt, t, scratch_limit, &p.parts);
+  } else if (tiles % 256 != 0) {
+    const long long q = tiles / 256 * 256;
+    int parts;
+    const double rest = small_tiles_us(4 * (tiles - q), kt, t, scratch_limit, &parts);
+    if ((double)kt * rounds_us(q, t.large_alone, t.large) + rest < (double)kt * rounds_us(tiles, t.large_alone, t.large)) {
+      p.whole = (int)q;
+      p.parts = parts;
+    }
   }
   return p;
 }
@@ -1107,15 +1156,21 @@ template <typename T, bool NN, int NSEG>
 hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch, hipStream_t s) {
   a.tiles_m = pl.tiles_m;
   a.tiles_n = pl.tiles_n;
-  a.parts = pl.parts;
   a.part = scratch;
-  const dim3 grid((unsigned)(pl.tiles_m * pl.tiles_n * pl.parts));
-  if (pl.skinny)
-    hipLaunchKernelGGL((k_gen_skinny<T, NN, NSEG>), grid, dim3(512), 0, s, a);
-  else if (pl.small)
-    hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG>), grid, dim3(256), 0, s, a);
-  else
-    hipLaunchKernelGGL((k_gen_gemm<T, 128, 128, NN, NSEG>), grid, dim3(256), 0, s, a);
+  a.parts = 1;
+  a.t0 = a.units = pl.whole;
+  const int tiles = pl.tiles_m * pl.tiles_n;
+  if (pl.skinny) {
+    hipLaunchKernelGGL((k_gen_skinny<T, NN, NSEG>), dim3((unsigned)tiles), dim3(512), 0, s, a);
+    return hipGetLastError();
+  }
+  if (pl.whole > 0) hipLaunchKernelGGL((k_gen_gemm<T, 128, 128, NN, NSEG, false>), dim3((unsigned)pl.whole), dim3(256), 0, s, a);
+  if (pl.whole == tiles) return hipGetLastError();
+  a.parts = pl.parts;
+  a.units = pl.small ? tiles : 4 * (tiles - pl.whole);
+  const dim3 grid((unsigned)(a.units * pl.parts));
+  if (pl.small) hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG, false>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG, true>), grid, dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || pl.parts == 1) return e;
   GenReduceArgs r;
@@ -1126,9 +1181,12 @@ hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch,
   r.tiles_m = a.tiles_m;
   r.tiles_n = a.tiles_n;
   r.parts = a.parts;
+  r.units = a.units;
+  r.t0 = a.t0;
   r.K = a.K;
   for (int k = 0; k <= kMaxK; ++k) r.off[k] = a.off[k];
-  hipLaunchKernelGGL((k_gen_reduce<T, 64, 64, NN>), dim3((unsigned)(pl.tiles_m * pl.tiles_n)), dim3(256), 0, s, r);
+  if (pl.small) hipLaunchKernelGGL((k_gen_reduce<T, 64, 64, NN, false>), dim3((unsigned)a.units), dim3(256), 0, s, r);
+  else hipLaunchKernelGGL((k_gen_reduce<T, 64, 64, NN, true>), dim3((unsigned)a.units), dim3(256), 0, s, r);
   return hipGetLastError();
 }
 
@@ -1176,12 +1234,11 @@ int gen_grad_splits(const SegTable& st, int wide_b, int wide_a, size_t scratch_l
   return s;
 }
 
-// the most plan_gemm cuts off for up to T rows (a part is added while there are fewer than kFullTiles blocks)
+// the most plan_gemm cuts off for up to T rows
 size_t gemm_part_bytes(int K, int T, int N, int Kd, int dtype) {
-  const long long tiles = (most_virtual_rows(K, T) + 63) / 64 * ((N + 63) / 64);
-  long long parts = contraction_tiles(Kd, dtype) / kTilesPerPart;
-  parts = parts < kMaxParts ? parts : kMaxParts;
-  const long long blocks = tiles * parts < 2 * kFullTiles ? tiles * parts : 2 * kFullTiles;
+  const long long rows = most_virtual_rows(K, T), units = 4 * ((rows + 127) / 128) * ((N + 127) / 128);
+  const long long deep = contraction_tiles(Kd, dtype) / kTilesPerPart, parts = deep < kMaxParts ? deep : kMaxParts;
+  const long long blocks = units * parts < kMostUnits ? units * parts : kMostUnits;
   return parts > 1 ? (size_t)blocks * 64 * 64 * sizeof(float) : 0;
 }
 

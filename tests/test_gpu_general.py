@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2312_02515_amd import binding as mb
 from paper_2312_02515_amd import workloads as wl
 from tests import form_cases
 from tests.parity_util import TOL, check_full, run_hip
@@ -72,6 +73,22 @@ def test_last_columns_of_general_tiles(dtype, T, h, d):
     inp.X[:, 0] = 1.0
     Y = run_hip(inp)["Y"]
     assert torch.isinf(Y[:, -1]).all() and torch.isfinite(Y[:, :-1]).all()
+
+
+@pytest.mark.parametrize("case,dtype", [
+    # T, h, d, tokens, ranks, lead: a round of 128 x 128 tiles (two in bf16), the rest as quarters in ranges; quarters beyond the last row and column
+    ((2150, 1700, 2101, [1000, 0, 1100], [7, 64, 32], 25), torch.float32),
+    ((2150, 2101, 1700, [1000, 0, 1100], [7, 64, 32], 25), torch.float32),
+    ((8330, 1500, 1000, [4100, 4150], [9, 100], 70), torch.bfloat16),
+    ((8330, 1000, 1500, [4100, 4150], [9, 100], 70), torch.bfloat16),
+])
+def test_general_quarters(case, dtype):
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, dtype, lead=lead, seed=84)
+    plan = mb.Problem(T, h, d, inp.W, inp.seg_offsets, inp.ranks, inp.scalings, inp.A, inp.B).kernel_plan()
+    which = "Y" if d in (2101, 1000) else "dX"
+    assert plan[which] == "128" and plan[which + "_parts"] > 1, plan
+    check_full(inp, run_hip(inp), TOL[dtype], label=f"quarters {case}")
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
