@@ -894,8 +894,10 @@ __global__ __launch_bounds__(512, 4) void k_gen_skinny(const GenGemmArgs<NSEG> a
 // 4 i .. 4 i + 3, one for each fragment, so that it loads (and, for dB, stores) them as one piece.
 // splits > 1: a task's tokens are cut into ranges of whole MFMA groups, one block each, whose sums go
 // to part + range * part_step ([sum of r_k][wide]) for grad_reduce to add in order.  fp32, T = 2048, 4 tasks, 4096
-// columns, rank 16: dB and dA in one launch 19 us + 5 us of reduction for 67 MB, against 131 us each with
-// a serial sum per output element.
+// columns, rank 16: dB and dA in one launch 18 us + 5 us of reduction for 67 MB, against 131 us each with
+// a serial sum per output element.  Small calls are bound by latency: a run of groups is requested at once, the
+// last one with masks (one launch, 64 tokens x 256 columns x 2 tasks 4.9 us instead of 10.4 with a wait per group,
+// 125 x 1000 x 8 7.6 instead of 19.3; bf16 300 x (1000 + 1500) x 3 6.4 instead of 16.6, 1333 tokens 9.5 instead of 19.9).
 // ------------------------------------------------------------------------------------------
 struct GenGradArgs {
   const void* Big;
@@ -909,13 +911,10 @@ struct GenGradArgs {
 };
 
 template <typename T, int NQ, bool WIDE_FIRST>
-__device__ __forceinline__ void gen_grad_body(const GenGradArgs& a, int bid) {
+__device__ __forceinline__ void grad_body(const GenGradArgs& a, int ch, int sp, int k) {
   constexpr int GT = sizeof(T) == 2 ? 32 : 4;        // tokens per MFMA
   constexpr int TE = GT / 4;                         // ... of which a lane carries TE
   const int wide = a.wide;
-  const int ch = bid % a.chunks;
-  const int sp = bid / a.chunks % a.splits;
-  const int k = bid / (a.chunks * a.splits);
   int lo = a.off[k], hi = a.off[k + 1];
   if (a.splits > 1) {
     const int len = ((hi - lo + a.splits - 1) / a.splits + 31) / 32 * 32;
@@ -927,12 +926,14 @@ __device__ __forceinline__ void gen_grad_body(const GenGradArgs& a, int bid) {
   const int l16 = lane & 15, kg = lane >> 4;
   const int c0 = (ch * 4 + wave) * 64;
   if (c0 >= wide) return;
-  const int r = a.rank[k], nq = (r + 15) / 16;
-  const int col = c0 + 4 * l16;
-  // a piece of four columns that crosses the end is loaded so that it ends there (wide >= 4) and
-  // read with `cs` positions of shift
-  const int cb = wide >= 4 ? (col < wide - 4 ? col : wide - 4) : 0;
-  const int cs = col - cb;
+  const int r = a.rank[k];
+  // lane i's four columns start here: a piece that crosses the end is loaded so that it ends there and is not
+  // shifted; its columns below c0 + 4 i belong to other lanes and are not stored
+  auto first_col = [&](int i) {
+    const int c = c0 + 4 * i;
+    return wide < 4 || c < wide - 4 ? c : wide - 4;
+  };
+  const int cb = first_col(l16);
   const T* Big = static_cast<const T*>(a.Big);
   const T* Small = static_cast<const T*>(a.Small);
 
@@ -944,63 +945,86 @@ __device__ __forceinline__ void gen_grad_body(const GenGradArgs& a, int bid) {
 
   typedef T Vec4 __attribute__((ext_vector_type(4), aligned(sizeof(T))));
   const T zero = T(0.f);
-  auto group = [&](int t0, bool tail) {
-    T bv[4][TE], sv[NQ][TE];
+  // A group of GT tokens: what a lane carries of it.  Loading knows no branches, so that the loads of all of
+  // a run's groups are in flight together (with one per piece at the right edge, each group waited for its own:
+  // fp32, 64 tokens of 256 columns 10.4 us).
+  struct Group {
+    Vec4 b[TE];
+    T s[NQ][TE];
+  };
+  auto load = [&](Group& g, int t0) {
 #pragma unroll
     for (int e = 0; e < TE; ++e) {
-      const int t = t0 + kg * TE + e;
-      const bool in = !tail || t < hi;
-      const T* row = Big + (size_t)(in ? t : hi - 1) * wide;
-      if (wide >= 4) {
-        const Vec4 v = *reinterpret_cast<const Vec4*>(row + cb);
+      int t = t0 + kg * TE + e;
+      t = t < hi ? t : hi - 1;
+      g.b[e] = *reinterpret_cast<const Vec4*>(Big + (size_t)t * wide + cb);
+      const T* srow = Small + (size_t)t * a.ldz;
 #pragma unroll
-        for (int f = 0; f < 4; ++f) bv[f][e] = in ? v[f] : zero;
-        if (cs > 0) {                                // columns beyond `wide` are discarded: no fill needed
-          const T w1 = bv[1][e], w2 = bv[2][e], w3 = bv[3][e];
-          bv[0][e] = cs == 1 ? w1 : (cs == 2 ? w2 : w3);
-          bv[1][e] = cs == 1 ? w2 : w3;
-          bv[2][e] = w3;
-        }
-      } else {
+      for (int j = 0; j < NQ; ++j) g.s[j][e] = srow[(16 * j < a.ldz ? 16 * j : 0) + l16];
+    }
+  };
+  auto load_narrow = [&](Group& g, int t0) {         // rows of fewer than four columns
 #pragma unroll
-        for (int f = 0; f < 4; ++f) bv[f][e] = (in && col + f < wide) ? row[col + f] : zero;
+    for (int e = 0; e < TE; ++e) {
+      int t = t0 + kg * TE + e;
+      t = t < hi ? t : hi - 1;
+#pragma unroll
+      for (int f = 0; f < 4; ++f) g.b[e][f] = cb + f < wide ? Big[(size_t)t * wide + cb + f] : zero;
+      const T* srow = Small + (size_t)t * a.ldz;
+#pragma unroll
+      for (int j = 0; j < NQ; ++j) g.s[j][e] = srow[(16 * j < a.ldz ? 16 * j : 0) + l16];
+    }
+  };
+  auto multiply = [&](Group& g, int t0, bool tail) {
+    if (tail) {
+#pragma unroll
+      for (int e = 0; e < TE; ++e) {
+        if (t0 + kg * TE + e < hi) continue;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) g.b[e][f] = zero;
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) g.s[j][e] = zero;
       }
-      const T* srow = Small + (size_t)(in ? t : hi - 1) * a.ldz;
-#pragma unroll
-      for (int j = 0; j < NQ; ++j)
-        if (j < nq) sv[j][e] = in ? srow[16 * j + l16] : zero;
     }
 #pragma unroll
     for (int j = 0; j < NQ; ++j)
-      if (j < nq) {
 #pragma unroll
-        for (int f = 0; f < 4; ++f) {
-          if constexpr (sizeof(T) == 2) {
-            bf16x8 b8, s8;
+      for (int f = 0; f < 4; ++f) {
+        if constexpr (sizeof(T) == 2) {
+          bf16x8 b8, s8;
 #pragma unroll
-            for (int e = 0; e < TE; ++e) {
-              b8[e] = bv[f][e];
-              s8[e] = sv[j][e];
-            }
-            acc[f][j] = WIDE_FIRST ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b8, s8, acc[f][j], 0, 0, 0)
-                                   : __builtin_amdgcn_mfma_f32_16x16x32_bf16(s8, b8, acc[f][j], 0, 0, 0);
-          } else {
-            acc[f][j] = WIDE_FIRST ? __builtin_amdgcn_mfma_f32_16x16x4f32(bv[f][0], sv[j][0], acc[f][j], 0, 0, 0)
-                                   : __builtin_amdgcn_mfma_f32_16x16x4f32(sv[j][0], bv[f][0], acc[f][j], 0, 0, 0);
+          for (int e = 0; e < TE; ++e) {
+            b8[e] = g.b[e][f];
+            s8[e] = g.s[j][e];
           }
+          acc[f][j] = WIDE_FIRST ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(b8, s8, acc[f][j], 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_f32_16x16x32_bf16(s8, b8, acc[f][j], 0, 0, 0);
+        } else {
+          acc[f][j] = WIDE_FIRST ? __builtin_amdgcn_mfma_f32_16x16x4f32(g.b[0][f], g.s[j][0], acc[f][j], 0, 0, 0)
+                                 : __builtin_amdgcn_mfma_f32_16x16x4f32(g.s[j][0], g.b[0][f], acc[f][j], 0, 0, 0);
         }
       }
   };
-  int t = lo;
-  if constexpr (sizeof(T) == 4) {
-    // eight groups' loads in flight at a time
-    for (; t + 8 * GT <= hi; t += 8 * GT) {
+  constexpr int U = sizeof(T) == 4 ? (NQ <= 2 ? 8 : 4) : (NQ <= 2 ? 2 : 1);   // groups of a run
+  auto run = [&](int t, bool tail) {
+    Group g[U];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) group(t + u * GT, false);
+    for (int u = 0; u < U; ++u) load(g[u], t + u * GT);
+    __builtin_amdgcn_sched_barrier(0);               // (the loads stay in front)
+#pragma unroll
+    for (int u = 0; u < U; ++u) multiply(g[u], t + u * GT, tail);
+  };
+  int t = lo;
+  if (wide >= 4) {
+    for (; t + U * GT <= hi; t += U * GT) run(t, false);
+    if (t < hi) run(t, true);
+  } else {
+    for (; t < hi; t += GT) {
+      Group g;
+      load_narrow(g, t);
+      multiply(g, t, true);
     }
   }
-  for (; t + GT <= hi; t += GT) group(t, false);
-  if (t < hi) group(t, true);
 
   float* o = a.out.p[k];
   int accumulate = a.accumulate;
@@ -1010,22 +1034,32 @@ __device__ __forceinline__ void gen_grad_body(const GenGradArgs& a, int bid) {
     o = a.part + sp * a.part_step + (size_t)rbase * wide;
     accumulate = 0;
   }
+  // columns cb + f of a lane, f from `skip` on
+  auto put = [&](float* dst, float v) { *dst = accumulate ? *dst + v : v; };
 #pragma unroll
   for (int j = 0; j < NQ; ++j) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
+      // WIDE_FIRST: lane holds q = 16 j + l16 and the columns carried by lane i = 4 kg + e
+      const int i = WIDE_FIRST ? 4 * kg + e : l16;
+      const int c = first_col(i), skip = c0 + 4 * i - c, q = WIDE_FIRST ? 16 * j + l16 : 16 * j + 4 * kg + e;
+      if (q >= r) continue;
 #pragma unroll
-      for (int f = 0; f < 4; ++f) {
-        // WIDE_FIRST: lane holds q = 16 j + l16 and the columns carried by lane i = 4 kg + e
-        const int c = WIDE_FIRST ? c0 + 4 * (4 * kg + e) + f : col + f;
-        const int q = WIDE_FIRST ? 16 * j + l16 : 16 * j + 4 * kg + e;
-        if (q < r && c < wide) {
-          float* dst = WIDE_FIRST ? o + (size_t)c * r + q : o + (size_t)q * wide + c;
-          *dst = accumulate ? *dst + acc[f][j][e] : acc[f][j][e];
-        }
-      }
+      for (int f = 0; f < 4; ++f)
+        if (f >= skip && c + f < wide) put(WIDE_FIRST ? o + (size_t)(c + f) * r + q : o + (size_t)q * wide + c + f, acc[f][j][e]);
     }
   }
+}
+
+// the body for the task's own rank, of NQ groups of 16 columns at most
+template <typename T, int NQ, bool WIDE_FIRST>
+__device__ __forceinline__ void gen_grad_body(const GenGradArgs& a, int bid) {
+  const int ch = bid % a.chunks, sp = bid / a.chunks % a.splits, k = bid / (a.chunks * a.splits);
+  const int r = a.rank[k];
+  if (NQ == 1 || r <= 16) grad_body<T, 1, WIDE_FIRST>(a, ch, sp, k);
+  else if (NQ == 2 || r <= 32) grad_body<T, 2, WIDE_FIRST>(a, ch, sp, k);
+  else if (NQ == 4 || r <= 64) grad_body<T, 4, WIDE_FIRST>(a, ch, sp, k);
+  else grad_body<T, 8, WIDE_FIRST>(a, ch, sp, k);
 }
 
 // dB (the first blocks_b blocks) and dA of one call

@@ -92,6 +92,24 @@ def test_general_quarters(case, dtype):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("h,d,tokens,ranks", [
+    (61, 66, [31, 32, 33, 1], [16, 17, 8, 33]),           # around a run's tokens; edges inside and between lanes' pieces
+    (259, 7, [63, 64, 65, 0], [65, 4, 64, 128]),          # ranks on either side of each group count
+    (3, 513, [97, 130], [5, 40], ),                       # rows shorter than a piece; one column in the last block
+])
+def test_general_gradients_add_to_what_is_there(dtype, h, d, tokens, ranks):
+    """A column that two lanes load is stored, and in accumulate mode added, once."""
+    inp = _inputs(sum(tokens) + 9, h, d, tokens, ranks, dtype, lead=4, seed=85)
+    got = run_hip(inp)
+    check_full(inp, got, TOL[dtype], label=f"gradients {h, d}")
+    pre = [[torch.full_like(g, 0.5 + k) for k, g in enumerate(got[n])] for n in ("dA", "dB")]
+    acc = run_hip(inp, accumulate=True, preset_grads=pre)
+    for n, p in zip(("dA", "dB"), pre):
+        for g, was, now in zip(got[n], p, acc[n]):
+            assert torch.equal(now, was + g)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_general_group_sum_in_large_tiles(dtype):
     """The summed input gradient in 128 x 128 tiles (2200 x 2101 outputs)."""
     ins = _group_inputs(2200, 2101, [139, 320], [1000, 1150], [[7, 64], [32, 5]], dtype, lead=25, seed=81)
