@@ -526,23 +526,32 @@ __global__ __launch_bounds__(256) void k_lowrank_mfma_splitk(const RowsArgs<1> r
 // Block: one task, 128 columns of Big, all its tokens in tiles of 64; 4 waves x 32 columns.
 // The whole reduction of an output element happens inside one block: deterministic, no atomics.
 // ------------------------------------------------------------------------------------------
-// LDS of one ring stage: 64 tokens x 128 columns of Big; 64 tokens x ldz of every Small_p, ldz <= 32 NQ, each
-// followed by 64 zero bytes (where lanes beyond the tile's columns point), at a multiple of 1 KiB.  The
+// LDS of one ring stage: 64 tokens x 128 columns of Big; 64 tokens x ldz of every Small_p, ldz <= 32 NQ, in
+// NQ x 4 KiB each.  (Lanes whose column lies beyond the tile read another one: what they sum is not stored.)  The
 // stages are separate arrays of the kernels (as members of one struct they cost the shared-input
 // launch 10 us of 178).
 constexpr int kBigStage = 64 * 128 * 2;
-template <int NQ> constexpr int kSmallStage = NQ * 32 * 128 + 1024;
-#define MLORA_GRAD_STAGES(NQ, NP)                                                                                  \
-  __shared__ __attribute__((aligned(1024))) char sB0[kBigStage], sB1[kBigStage], sB2[kBigStage];                    \
-  __shared__ __attribute__((aligned(1024))) char sS0[NP * kSmallStage<NQ>], sS1[NP * kSmallStage<NQ>],              \
-      sS2[NP * kSmallStage<NQ>];                                                                                    \
-  char* const sB[3] = {sB0, sB1, sB2};                                                                              \
+template <int NQ> constexpr int kSmallStage = NQ * 32 * 128;
+// Three stages where two blocks of them share a CU, two where that is what makes room for the second
+// block (160 KiB of LDS).  us with three and with two stages: ranks above 64, 16384 x 4096 98 and 76, 12 tasks of 256
+// tokens 33 and 24, 64 tasks of 32 tokens 59 and 37; dA of three projections that share X, ranks up to 64, 32768 x
+// 5120 168 and 133.  Where two blocks of three stages fit, two stages lose: 16384 x 4096, ranks up to 64, 53 and 59.
+template <int NQ, int NP>
+constexpr int grad_stages() {
+  constexpr int stage = kBigStage + NP * kSmallStage<NQ>, half = 80 * 1024;
+  return 3 * stage > half && 2 * stage <= half ? 2 : 3;
+}
+#define MLORA_GRAD_STAGES(NQ, NP)                                                                              \
+  constexpr int kThird = grad_stages<NQ, NP>() == 3 ? 1 : 0;                                                    \
+  __shared__ __attribute__((aligned(1024))) char sB0[kBigStage], sB1[kBigStage], sS0[NP * kSmallStage<NQ>],     \
+      sS1[NP * kSmallStage<NQ>], sB2[kThird ? kBigStage : 1], sS2[kThird ? NP * kSmallStage<NQ> : 1];            \
+  char* const sB[3] = {sB0, sB1, sB2};                                                                          \
   char* const sS[3] = {sS0, sS1, sS2}
 
 template <bool WIDE_FIRST, int NQ, int NP>
 __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char* const (&sB)[3], char* const (&sS)[3]) {
-  constexpr int WC = 128, NS = 3;
-  constexpr int SREG = kSmallStage<NQ>, SBYTES = SREG - 1024;
+  constexpr int WC = 128, NS = grad_stages<NQ, NP>();
+  constexpr int SREG = kSmallStage<NQ>;
   static_assert(WIDE_FIRST || NP == 1, "shared-input form exists for dA only");
 
   const bf16* __restrict__ Big = ga.Big;
@@ -561,12 +570,6 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char*
   const int tk = hi - lo;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  if (tid < 16) {
-#pragma unroll
-    for (int s_ = 0; s_ < NS; ++s_)
-#pragma unroll
-      for (int p = 0; p < NP; ++p) reinterpret_cast<int*>(sS[s_] + p * SREG + SBYTES)[tid] = 0;
-  }
 
   // Big tile: 64 token rows x 256 B; wave instruction w covers rows 4w..4w+3
   int brow[4], bcol[4];
@@ -580,11 +583,12 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char*
     bcol[it] = col;
   }
   // Small tiles: 64 tokens x ldz_p, contiguous in memory; piece = 1 KiB = 64 chunks of 16 B
-  int ldz[NP];
+  int ldz[NP], rank[NP];
   int srow[NP][NQ], scol[NP][NQ];
 #pragma unroll
   for (int p = 0; p < NP; ++p) {
     ldz[p] = ga.ldz[p];
+    rank[p] = ga.rank[p][k];
     const int cpr = ldz[p] / 8;  // chunks per token row = 1 KiB pieces per tile
 #pragma unroll
     for (int it = 0; it < NQ; ++it) {
@@ -645,11 +649,11 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char*
         const char* ss = ssall + p * SREG;
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
-          if (32 * j < ldz[p]) {
-            const int n = 32 * j + tr_n;
+          if (32 * j < rank[p]) {
+            const int n = 32 * j + tr_n < ldz[p] ? 32 * j + tr_n : 0;
             const int ns = n ^ (seg_swizzle(kk, ldz[p]) << 5);
-            const char* p0 = ss + ((n < ldz[p]) ? (kk * ldz[p] + ns) * 2 : SBYTES);
-            const char* p1 = ss + ((n < ldz[p]) ? ((kk + 4) * ldz[p] + ns) * 2 : SBYTES);
+            const char* p0 = ss + (kk * ldz[p] + ns) * 2;
+            const char* p1 = ss + ((kk + 4) * ldz[p] + ns) * 2;
             short4v s0 = lds_read_tr(p0), s1 = lds_read_tr(p1);
             if (valid < 64) {
               // the lane's 8 contraction indices are tokens 16ks + 8*lhi + 0..7 of the tile
@@ -672,7 +676,6 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char*
   };
 
   const int KT = (tk + 63) / 64;
-  __syncthreads();  // the zero pads
 #pragma unroll
   for (int s_ = 0; s_ < NS - 1; ++s_)
     if (s_ < KT) issue(s_, sB[s_], sS[s_]);
