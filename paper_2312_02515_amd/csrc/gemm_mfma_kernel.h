@@ -61,11 +61,13 @@
 
 #include "mfma_staging.h"
 #include "mlora_common.h"
+#include "row_axis.h"
 
 namespace mlora {
 namespace gemmk {
 
 using namespace stage;
+using namespace rowaxis;
 
 constexpr int BN = 256;   // columns of a tile; its rows: 128 x WAVES_M
 typedef __attribute__((ext_vector_type(4))) float f32x4;
@@ -202,8 +204,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // out for itself, lane 8 c + f holding column c (0: first row, 1: rows, 2: task) of piece f.
   // Every use looks up a wave-uniform piece, so an entry is read with v_readlane.
   constexpr int NFR = BM / 32;
-  int v_tab;
-  {
+  int v_tab = 0;
+  if (__builtin_expect(ga.K <= kFewTasks, 1)) {
     const int v0 = tm * BM + 32 * (lane & (NFR - 1));
     int vstart = 0, prev = 0, frow = M - 1, fn = 0, ftask = -1;
     for (int r = 0; r < ga.K + 2; ++r) {
@@ -220,6 +222,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     }
     const int col = lane / NFR;
     v_tab = col == 0 ? frow : (col == 1 ? fn : ftask);
+  } else {
+    const RowAxis axis = row_axis(ga);
+    const int col = lane / NFR;
+    for (int f = 0; f < NFR; ++f) {
+      const RowPiece p = find_piece(ga, axis, (unsigned)(tm * BM + 32 * f));
+      if ((lane & (NFR - 1)) == f) v_tab = col == 0 ? p.row : (col == 1 ? p.n : p.task);
+    }
   }
   auto tab = [&](int c, int f) { return __builtin_amdgcn_readlane(v_tab, __builtin_amdgcn_readfirstlane(NFR * c + f)); };
   auto frag_row = [&](int f) { return tab(0, f); };
@@ -507,8 +516,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   if constexpr (HALF) {
     int total_kt = 0;
     for (int sg = 0; sg < NSEG; ++sg) total_kt += ga.Kd[sg] / BK;
-    h0 = (int)((long long)total_kt * part / ga.parts);
-    h1 = (int)((long long)total_kt * (part + 1) / ga.parts);
+    // (below 2^32: at most 16 ranges of 4 x 2^25 tiles)
+    h0 = (int)((unsigned)total_kt * (unsigned)part / (unsigned)ga.parts);
+    h1 = (int)((unsigned)total_kt * (unsigned)(part + 1) / (unsigned)ga.parts);
   }
   for (int sg = 0; sg < NSEG; ++sg) {
     int KT = ga.Kd[sg] / BK, k0 = 0;
@@ -723,17 +733,9 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(const ReduceArgs a) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int r16 = lane & 15, kg = lane >> 4;
   const int v0 = tm * 128 + 16 * i;      // the fragment's first virtual row
-  int vstart = 0, prev = 0, row = 0, n = 0;
-  for (int r = 0; r < a.K + 2; ++r) {
-    const int b1 = r <= a.K ? a.off[r] : a.M;
-    const int len = b1 - prev, vlen = (len + 31) & ~31;
-    if (v0 >= vstart && v0 < vstart + vlen) {
-      row = prev + v0 - vstart;
-      n = len - (v0 - vstart);
-    }
-    vstart += vlen;
-    prev = b1;
-  }
+  // (16 rows: the upper or lower half of a piece)
+  const RowPiece p = find_piece(a, row_axis(a), (unsigned)v0);
+  const int row = p.row, n = p.n;
   const int units = 2 * (a.tiles_m * a.tiles_n - a.t0);
   const float* src = a.part + (size_t)u * (128 * BN) + ((i * 4 + wave) * FN) * 256 + lane * 4;
   const size_t step = (size_t)units * (128 * BN);

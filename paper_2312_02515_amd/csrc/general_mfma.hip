@@ -19,11 +19,13 @@
 #include "mfma_staging.h"
 #include "../../include/mlora_testing.h"
 #include "mlora_common.h"
+#include "row_axis.h"
 
 namespace mlora {
 namespace {
 
 using namespace stage;
+using namespace rowaxis;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
@@ -121,13 +123,6 @@ __device__ __forceinline__ void interleave() {
   }
 }
 
-// 32 consecutive rows of the virtual row axis, on which every row range of the call (before the
-// first task, each task, after the last) is padded to a multiple of 32: a piece never holds rows of
-// two tasks, so no row ever meets another task's adapter, not even multiplied by zero.
-struct RowPiece {
-  int row, n, task;   // first real row, real rows (0 = beyond the last row), task (-1 = none)
-};
-
 // ------------------------------------------------------------------------------------------
 // C[M,N] = sum_g ( A_g[M,Kd_g] * op(W_g) + rows_k( L_g[rows_k, :r_gk] * R_gk ) )
 //   NN = true : W_g [Kd_g, N], R_gk [r_gk, N]      NN = false: W_g [N, Kd_g], R_gk [N, r_gk]
@@ -149,78 +144,6 @@ struct GenGemmArgs {
   unsigned char rank[NSEG][kMaxK];
   PtrTable R[NSEG];
 };
-
-// inclusive sums over the first n lanes of a wave
-__device__ __forceinline__ int scan_lanes(int v, int n) {
-  const int lane = threadIdx.x & 63;
-  for (int s = 1; s < n; s <<= 1) {
-    const int u = __shfl_up(v, s);
-    if (lane >= s) v += u;
-  }
-  return v;
-}
-
-// Up to this many tasks are searched one after the other, by scalar loads; more by all lanes at once: 66
-// dependent loads for 64 tasks took 7 us of every block, while the vector loads and the scan cost 1.7 us
-// whatever the number of tasks.
-constexpr int kFewTasks = 8;
-
-// The virtual row axis, spread over a wave: lane k knows where task k stands (all of a wave's lanes call
-// this)
-struct RowAxis {
-  int off, len;                          // task `lane`: first row, rows
-  unsigned vlen, vstart;                 // ... rows on the axis, where they start there
-  int lead, rows_end, M;                 // rows before the first task, end of the last task's rows
-  unsigned vlead, tasks_end;             // ... on the axis
-};
-template <typename Args>
-__device__ __forceinline__ RowAxis row_axis(const Args& a) {
-  RowAxis x{};
-  if (a.K <= kFewTasks) return x;
-  const int lane = threadIdx.x & 63;
-  x.off = a.off[lane];                   // (entries from K on repeat the last split position)
-  x.len = lane < a.K ? a.off[lane + 1] - x.off : 0;
-  x.vlen = ((unsigned)x.len + 31) & ~31u;
-  const int sum = scan_lanes((int)x.vlen, a.K);
-  x.lead = a.off[0];
-  x.rows_end = a.off[kMaxK];
-  x.M = a.M;
-  x.vlead = ((unsigned)x.lead + 31) & ~31u;
-  x.vstart = x.vlead + (unsigned)sum - x.vlen;
-  x.tasks_end = x.vlead + (unsigned)__builtin_amdgcn_readlane(sum, a.K - 1);
-  return x;
-}
-template <typename Args>
-__device__ __forceinline__ RowPiece find_piece(const Args& a, const RowAxis& x, unsigned v0) {
-  if (a.K <= kFewTasks) {
-    RowPiece p{a.M - 1, 0, -1};
-    unsigned vstart = 0;
-    int prev = 0;
-    for (int r = 0; r < a.K + 2; ++r) {
-      const int b1 = r <= a.K ? a.off[r] : a.M;
-      const int len = b1 - prev;
-      const unsigned o = v0 - vstart;
-      if (v0 >= vstart && o < (unsigned)len) p = RowPiece{prev + (int)o, len - (int)o < 32 ? len - (int)o : 32, r >= 1 && r <= a.K ? r - 1 : -1};
-      vstart += ((unsigned)len + 31) & ~31u;
-      prev = b1;
-    }
-    return p;
-  }
-  int first = 0, len = x.lead, task = -1;
-  unsigned o = v0;
-  if (v0 >= x.tasks_end) {
-    first = x.rows_end;
-    len = x.M - x.rows_end;
-    o = v0 - x.tasks_end;
-  } else if (v0 >= x.vlead) {
-    task = __builtin_ctzll(__ballot(v0 >= x.vstart && v0 - x.vstart < x.vlen));
-    first = __builtin_amdgcn_readlane(x.off, task);
-    len = __builtin_amdgcn_readlane(x.len, task);
-    o = v0 - (unsigned)__builtin_amdgcn_readlane((int)x.vstart, task);
-  }
-  if (o >= (unsigned)len) return RowPiece{x.M - 1, 0, -1};
-  return RowPiece{first + (int)o, len - (int)o < 32 ? len - (int)o : 32, task};
-}
 
 // Block id -> (tile, part).  Consecutive ids go round-robin over the 8 XCDs; each XCD takes a
 // contiguous eighth of the order (8 row tiles x all column tiles at a time, column by column), so
@@ -332,7 +255,9 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   int total_kt = 0;
 #pragma unroll
   for (int g = 0; g < NSEG; ++g) total_kt += (a.Kd[g] + BK - 1) / BK;
-  int p0 = (int)((long long)total_kt * part / a.parts), p1 = (int)((long long)total_kt * (part + 1) / a.parts);
+  // (the products stay below 2^32: at most 16 parts of 4 x 2^26 tiles)
+  int p0 = (int)((unsigned)total_kt * (unsigned)part / (unsigned)a.parts);
+  int p1 = (int)((unsigned)total_kt * (unsigned)(part + 1) / (unsigned)a.parts);
 
   const int ar = tid >> 3, ac = tid & 7;             // K-contiguous: row (of 32) and piece of this thread
   const bool narrow = NN && N < V;                   // no whole piece in a row of W
@@ -801,34 +726,6 @@ __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, i
   const int pad = a.ldz - r;
   if (pad > 0)
     for (int t = tid; t < (hi - lo) * pad; t += NW * 64) Out[(size_t)(lo + t / pad) * a.ldz + r + t % pad] = T(0.f);
-}
-
-// rows of a block of the low-rank kernels: task and row range of block b when tasks are cut into
-// blocks of TM rows
-template <int TM>
-__device__ __forceinline__ int rows_block(const GenRowsArgs& a, int b, int* lo, int* hi) {
-  if (a.K <= kFewTasks) {
-    for (int k = 0; k < a.K; ++k) {
-      const int nb = (a.off[k + 1] - a.off[k] + TM - 1) / TM;
-      if (b < nb) {
-        *lo = a.off[k] + b * TM;
-        *hi = a.off[k + 1] < *lo + TM ? a.off[k + 1] : *lo + TM;
-        return k;
-      }
-      b -= nb;
-    }
-    return -1;
-  }
-  const int lane = threadIdx.x & 63;
-  const int off = a.off[lane], len = lane < a.K ? a.off[lane + 1] - off : 0;
-  const int nb = (len + TM - 1) / TM, first = scan_lanes(nb, a.K) - nb;
-  const unsigned long long mine = __ballot(b >= first && b < first + nb);
-  if (mine == 0) return -1;
-  const int k = __builtin_ctzll(mine);
-  const int o = (b - __builtin_amdgcn_readlane(first, k)) * TM, left = __builtin_amdgcn_readlane(len, k) - o;
-  *lo = __builtin_amdgcn_readlane(off, k) + o;
-  *hi = *lo + (left < TM ? left : TM);
-  return k;
 }
 
 template <typename T, int RM, int NW, bool KMAJOR>

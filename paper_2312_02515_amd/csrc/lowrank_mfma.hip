@@ -15,11 +15,13 @@
 // tokens) are read from LDS with the transposing ds_read_b64_tr_b16.
 #include "mfma_staging.h"
 #include "mlora_common.h"
+#include "row_axis.h"
 
 namespace mlora {
 namespace {
 
 using namespace stage;
+using namespace rowaxis;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // Bank-conflict swizzle of a small tile stored with the contraction index as its rows
@@ -130,15 +132,9 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
   const bf16* __restrict__ In = ra.In;
   const int inner = ra.inner;
   const int sp = NP == 1 ? blockIdx.x % ra.splits : 0;
-  int b = NP == 1 ? blockIdx.x / ra.splits : blockIdx.x, k = 0;
-  for (; k < ra.K; ++k) {
-    const int nb = (ra.off[k + 1] - ra.off[k] + TM - 1) / TM;
-    if (b < nb) break;
-    b -= nb;
-  }
-  if (k >= ra.K) return;
-  const int lo = ra.off[k] + b * TM;
-  const int hi = (ra.off[k + 1] < lo + TM) ? ra.off[k + 1] : lo + TM;
+  int lo = 0, hi = 0;
+  const int k = rows_block<TM>(ra, NP == 1 ? blockIdx.x / ra.splits : blockIdx.x, &lo, &hi);
+  if (k < 0) return;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -248,7 +244,8 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
   // whose stage is refilled next.
   int KT = inner / 64;
   if (NP == 1 && ra.splits > 1) {
-    const int k0 = (int)((long long)KT * sp / ra.splits), k1 = (int)((long long)KT * (sp + 1) / ra.splits);
+    // (below 2^32: at most 16 ranges of 2^25 tiles)
+    const int k0 = (int)((unsigned)KT * (unsigned)sp / (unsigned)ra.splits), k1 = (int)((unsigned)KT * (unsigned)(sp + 1) / (unsigned)ra.splits);
 #pragma unroll
     for (int it = 0; it < 4; ++it) xptr[it] += (size_t)k0 * 64;
 #pragma unroll
@@ -322,8 +319,7 @@ __global__ __launch_bounds__(256) void k_rows_reduce(const RowsArgs<1> ra) {
   const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
   if (t >= (long long)rows * per) return;
   const int i = (int)(t / per), q = (int)(t % per) * 4;
-  int k = 0;
-  while (ra.off[0] + i >= ra.off[k + 1]) ++k;
+  const int k = task_of_row(ra, ra.off[0] + i);
   const int r = ra.rank[0][k];
   const float s = ra.s[0][k];
   f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -359,15 +355,9 @@ __global__ __launch_bounds__(256) void k_lowrank_mfma_splitk(const RowsArgs<1> r
 
   const bf16* __restrict__ In = ra.In;
   const int inner = ra.inner;
-  int b = blockIdx.x, k = 0;
-  for (; k < ra.K; ++k) {
-    const int nb = (ra.off[k + 1] - ra.off[k] + TM - 1) / TM;
-    if (b < nb) break;
-    b -= nb;
-  }
-  if (k >= ra.K) return;
-  const int lo = ra.off[k] + b * TM;
-  const int hi = (ra.off[k + 1] < lo + TM) ? ra.off[k + 1] : lo + TM;
+  int lo = 0, hi = 0;
+  const int k = rows_block<TM>(ra, blockIdx.x, &lo, &hi);
+  if (k < 0) return;
   const int r = ra.rank[0][k];
   const bf16* Mk = static_cast<const bf16*>(ra.M[0].p[k]);
 
