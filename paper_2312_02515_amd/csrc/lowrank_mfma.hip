@@ -808,6 +808,9 @@ int pick_row_tile(const SegTable& st) {
 // product, one range -> as chosen here:
 //   ranks above 64 (four column groups: the four-wave form of few rows does not fit the LDS):
 //     3072 x 4096 (12 tasks)  s x A 85 -> 25, s dy B^T 56 -> 22;  8192 x 4096  62 -> 33, 56 -> 33
+//     short tasks, both products, blocks of 128 rows -> of 32: 2048 x 2048 (64 tasks) 53 -> 41, 3000 x 3072 (60) 67 ->
+//     48, 1000 x 4096 (40) 54 -> 41; with 1024 blocks at most 47, 54, 48; where the number of ranges stays the same
+//     (200 x 2048, 10 tasks) 32.5 and 33.3
 //   ranks up to 64:
 //     16448 x 11008  119 -> 90,  16448 x 4096  44 -> 38-40,  12288 x 4096  31 -> 26
 //     8192 x 4096, a forward and backward pass 474 -> 466 with two such products
@@ -831,8 +834,15 @@ RowsPlan plan_rows(const SegTable& st, int inner, int ldz, size_t limit) {
   RowsPlan pl = plain;
   if (nq_of(ldz) == 4) {
     if (KT < 16 || (KT < 32 && b128 >= 128)) return plain;
-    pl.tm = 128;
-    while (2 * pl.splits * b128 <= 256 && 8 * pl.splits <= KT && pl.splits < 16) pl.splits *= 2;
+    auto ranges = [&](int blocks, int most) {
+      int n = 1;
+      while (2 * n * blocks <= most && 8 * n <= KT && n < 16) n *= 2;
+      return n;
+    };
+    pl = RowsPlan{128, ranges(b128, 256)};
+    // short tasks, whose 128-row blocks are mostly empty, in blocks of one wave where that makes room for
+    // more ranges
+    if (2 * rows <= 128LL * b128 && b32 <= 256 && ranges(b32, 512) > pl.splits) pl = RowsPlan{32, ranges(b32, 512)};
   } else if (b32 >= 128 && KT >= 64 && !(nq_of(ldz) == 1 && KT < 128 && b128 >= 128) && 4 * rows >= 3 * 128LL * b128) {
     pl = RowsPlan{128, KT >= 128 ? 8 : 4};
   } else if (b32 >= 32 && KT >= 128) {

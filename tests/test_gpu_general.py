@@ -174,6 +174,18 @@ def test_tasks_searched_by_all_lanes(T, h, d, rank, K):
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"tasks {T, h, d, K}")
 
 
+@pytest.mark.parametrize("h,d,rank", [(2048, 192, 128), (192, 2112, 77), (4160, 64, 65)])
+def test_short_tasks_of_high_rank_in_ranges(h, d, rank):
+    """64 tasks of up to 32 rows, ranks above 64 among them: low-rank rows in blocks of 32 rows and ranges."""
+    tokens = [(13 * k) % 33 for k in range(64)]
+    inp = _inputs(sum(tokens) + 21, h, d, tokens, [rank if k % 3 == 0 else 1 + k for k in range(64)], torch.bfloat16, lead=9,
+                  seed=87)
+    plan = mb.Problem(sum(tokens) + 21, h, d, inp.W, inp.seg_offsets, inp.ranks, inp.scalings, inp.A, inp.B).kernel_plan()
+    side = "Z" if h > d else "G"
+    assert plan[side + "_rows"] == 32 and plan[side + "_parts"] > 1, plan
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"short tasks {h, d, rank}")
+
+
 @pytest.mark.parametrize("P", [2, 3, 4])
 def test_ragged_ranks_in_a_group(P):
     ranks = [[5 + p, 12, 8] for p in range(P)]
