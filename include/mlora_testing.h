@@ -44,7 +44,8 @@ int mlora_set_kernel_path(int path);
 #define MLORA_FORM_MIXED    2  /* aligned: whole rounds of the first, the rest as the second       */
 #define MLORA_FORM_SKINNY   3  /* general: 16 x 64                                                 */
 #define MLORA_FORM_64       4  /* general: 64 x 64                                                 */
-#define MLORA_FORM_128      5  /* general: 128 x 128                                               */
+#define MLORA_FORM_128      5  /* general: 128 x 128; the tiles beyond whole rounds of 256 may run as
+                                  quarters of 64 x 64, in the ranges that *_PARTS gives            */
 mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan);
 
 /* Measurement aid.  While enabled, every launch of the MFMA kernels by this process is bracketed

@@ -8,8 +8,8 @@
 //                  dB_k = Z^T dy_k          (Eq. "grad_lora", right)
 //
 // One launch covers all tasks: a block finds its task from the split positions.
-// Tiles are staged with direct global->LDS loads (16 B per lane) into a 3-stage
-// ring, two tiles in flight per block and two blocks per CU (an HBM-bound stream needs tens of KiB in
+// Tiles are staged with direct global->LDS loads (16 B per lane) into a ring of three stages (gradients: or
+// two), two tiles in flight per block and two blocks per CU (an HBM-bound stream needs tens of KiB in
 // flight per CU); operands whose contraction index is not contiguous in memory (A_k, and
 // everything in the two gradient products, where the contraction runs over
 // tokens) are read from LDS with the transposing ds_read_b64_tr_b16.
@@ -1064,8 +1064,8 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
 // Token ranges per task of up to `longest` tokens for the gradient kernels, one number for dB and dA: as many
 // as give every CU a block (at most 16, at least 256 tokens each).  More cost their reduction more than they
 // bring: 6000 tokens of 4 tasks, 4096 x 4096, rank 64, forward + backward 423 us with two blocks per CU, 411
-// us with one.  Ranks above 64 leave a CU one block (99 KB of LDS): there no more than 256 in all (65536
-// tokens of one task, 1024 -> 4096, rank 128, backward 843 us with 280 blocks, 753 with 240).
+// us with one.  Ranks above 64: no more than 256 in all (65536 tokens of one task, 1024 -> 4096, rank 128,
+// backward 843 us with 280 blocks, 753 with 240, measured when such a block had its CU to itself).
 int grad_ranges(const SegTable& st, int wide_b, int wide_a, int longest) {
   const int blocks = st.K * ((wide_b + 127) / 128 + (wide_a + 127) / 128);
   int rmax = 0;

@@ -3,7 +3,7 @@
 //     c_j = max_i |W[i, j]| / 127,   Wq[i, j] = rint(W[i, j] / c_j),   W^[i, j] = Wq[i, j] c_j.
 // Streaming kernels: the coder (run once when a model is loaded) and the decoder that the
 // w8 entry points run in front of the base products (1 byte read and one element written per
-// weight: 1 % of the product it feeds at 32768 tokens, a sixth at 2048).  Decoding inside the product was
+// weight: 1 % of the product it feeds at 32768 tokens, a seventh at 2048).  Decoding inside the product was
 // not tried: every row tile would decode the weight again, in the inner loop and without the direct
 // global-to-LDS loads.
 #include "mlora_common.h"
