@@ -48,6 +48,16 @@ int mlora_set_kernel_path(int path);
                                   quarters of 64 x 64, in the ranges that *_PARTS gives            */
 mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan);
 
+/* The tiles of the two base products in the size that their form names (256 x 256 for the aligned
+ * ones): how many run as such, and how many there are -- the others run as halves (HALVES, MIXED) or
+ * quarters (128).  `tiles` (HOST, MLORA_PLAN_TILES entries) and the status as for mlora_kernel_plan. */
+#define MLORA_PLAN_Y_WHOLE  0
+#define MLORA_PLAN_Y_TILES  1
+#define MLORA_PLAN_DX_WHOLE 2
+#define MLORA_PLAN_DX_TILES 3
+#define MLORA_PLAN_TILES    4
+mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles);
+
 /* Measurement aid.  While enabled, every launch of the MFMA kernels by this process is bracketed
  * by a pair of HIP events recorded on the launch stream (at most 16384 launches are kept; the
  * events are created on first use and live until the process ends).  Returns the previous

@@ -32,10 +32,12 @@ EXPORTS = ["mlora_lora_saved_bytes", "mlora_lora_workspace_bytes", "mlora_lora_v
            "mlora_lora_w8_workspace_bytes", "mlora_lora_fwd_w8", "mlora_lora_bwd_w8"]
 MLORA_STATIC_SCRATCH_BYTES = 32 << 20
 # include/mlora_testing.h: test and measurement switches
-TESTING_EXPORTS = ["mlora_set_kernel_path", "mlora_kernel_plan", "mlora_profile_kernels", "mlora_profile_kernels_read"]
+TESTING_EXPORTS = ["mlora_set_kernel_path", "mlora_kernel_plan", "mlora_kernel_plan_tiles", "mlora_profile_kernels",
+                   "mlora_profile_kernels_read"]
 
-# entries of mlora_kernel_plan, names of its MLORA_FORM_* values
+# entries of mlora_kernel_plan and of mlora_kernel_plan_tiles, names of the MLORA_FORM_* values
 PLAN_FIELDS = ["Y", "Y_parts", "dX", "dX_parts", "Z_rows", "Z_parts", "G_rows", "G_parts", "grads"]
+PLAN_TILES = ["Y_whole", "Y_tiles", "dX_whole", "dX_tiles"]
 PLAN_FORMS = ["whole", "halves", "mixed", "skinny", "64", "128"]
 
 
@@ -127,6 +129,8 @@ def _load() -> ctypes.CDLL:
     l.mlora_lora_kernel_path.argtypes = [pp]
     l.mlora_kernel_plan.restype = ctypes.c_int
     l.mlora_kernel_plan.argtypes = [pp, ctypes.POINTER(ctypes.c_int32)]
+    l.mlora_kernel_plan_tiles.restype = ctypes.c_int
+    l.mlora_kernel_plan_tiles.argtypes = [pp, ctypes.POINTER(ctypes.c_int32)]
     l.mlora_set_kernel_path.restype = ctypes.c_int
     l.mlora_set_kernel_path.argtypes = [ctypes.c_int]
     l.mlora_profile_kernels.restype = ctypes.c_int
@@ -203,6 +207,11 @@ class Problem:
             raise MloraError(st, "mlora_kernel_plan")
         out = dict(zip(PLAN_FIELDS, plan))
         out["Y"], out["dX"] = PLAN_FORMS[out["Y"]], PLAN_FORMS[out["dX"]]
+        tiles = (ctypes.c_int32 * len(PLAN_TILES))()
+        st = lib.mlora_kernel_plan_tiles(ctypes.byref(self.c), tiles)
+        if st != 0:
+            raise MloraError(st, "mlora_kernel_plan_tiles")
+        out.update(zip(PLAN_TILES, tiles))
         return out
 
     def alloc_saved(self) -> torch.Tensor:

@@ -223,7 +223,8 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
 GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_bytes) {
   const Plan pl = plan_gemm(st, M, N, Kd, 1, scratch_bytes);
   const long long total = (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN);
-  return GemmForm{pl.whole == total ? MLORA_FORM_WHOLE : (pl.whole == 0 ? MLORA_FORM_HALVES : MLORA_FORM_MIXED), pl.parts};
+  const int form = pl.whole == total ? MLORA_FORM_WHOLE : (pl.whole == 0 ? MLORA_FORM_HALVES : MLORA_FORM_MIXED);
+  return GemmForm{form, pl.parts, pl.whole, (int)total};
 }
 
 size_t gemm_partial_bytes(int K, int T, int N, int Kd) {

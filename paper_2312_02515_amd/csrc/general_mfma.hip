@@ -1219,7 +1219,8 @@ size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype)
 
 GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, int dtype, size_t scratch_bytes) {
   const GemmPlan pl = plan_gemm(st, M, N, Kd, dtype, scratch_bytes);
-  return GemmForm{pl.skinny ? MLORA_FORM_SKINNY : (pl.small ? MLORA_FORM_64 : MLORA_FORM_128), pl.parts};
+  const int form = pl.skinny ? MLORA_FORM_SKINNY : (pl.small ? MLORA_FORM_64 : MLORA_FORM_128), tiles = pl.tiles_m * pl.tiles_n;
+  return GemmForm{form, pl.parts, form == MLORA_FORM_128 ? pl.whole : tiles, tiles};
 }
 RowsForm general_rows_form(const CallCtx& c) { return RowsForm{two_row_groups(c) ? 32 : 16, 1}; }
 int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes) {

@@ -248,6 +248,12 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
   return e;
 }
 
+// how a base product of N outputs and Kd contraction indices is cut up
+GemmForm product_form(const mlora_problem* p, const CallCtx& c, int N, int Kd) {
+  return mfma_gemm_applies(p) ? gemm_form(c.st, c.T, N, Kd, c.scratch_bytes)
+                              : general_gemm_form(c.st, c.T, N, Kd, c.dtype, c.scratch_bytes);
+}
+
 // Whether the shared-input low-rank kernels (one pass over X for all projections) apply
 bool group_lowrank_applies(const mlora_problem* const* ps, int P, const void* X) {
   if (P < 2 || !aligned16(X)) return false;
@@ -620,9 +626,8 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
   CallCtx c;
   fill_ctx(p, nullptr, &c);
   const size_t room = c.scratch_bytes;
-  const bool ag = mfma_gemm_applies(p), al = mfma_lowrank_applies(p);
-  const GemmForm y = ag ? gemm_form(c.st, c.T, c.d, c.h, room) : general_gemm_form(c.st, c.T, c.d, c.h, c.dtype, room);
-  const GemmForm dx = ag ? gemm_form(c.st, c.T, c.h, c.d, room) : general_gemm_form(c.st, c.T, c.h, c.d, c.dtype, room);
+  const bool al = mfma_lowrank_applies(p);
+  const GemmForm y = product_form(p, c, c.d, c.h), dx = product_form(p, c, c.h, c.d);
   const RowsForm z = al ? rows_form(c.st, c.h, c.ldz, room) : general_rows_form(c);
   const RowsForm g = al ? rows_form(c.st, c.d, c.ldz, room) : general_rows_form(c);
   plan[MLORA_PLAN_Y] = y.form;
@@ -634,6 +639,20 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
   plan[MLORA_PLAN_G_ROWS] = g.rows;
   plan[MLORA_PLAN_G_PARTS] = g.parts;
   plan[MLORA_PLAN_GRADS] = c.K == 0 ? 1 : (al ? grad_splits(c.st, c.d, c.h, room) : general_grad_ranges(c.st, c.d, c.h, room));
+  return MLORA_OK;
+}
+
+mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles) {
+  const mlora_status st = validate(p);
+  if (st != MLORA_OK) return st;
+  if (tiles == nullptr) return MLORA_ERR_NULL;
+  CallCtx c;
+  fill_ctx(p, nullptr, &c);
+  const GemmForm y = product_form(p, c, c.d, c.h), dx = product_form(p, c, c.h, c.d);
+  tiles[MLORA_PLAN_Y_WHOLE] = y.whole;
+  tiles[MLORA_PLAN_Y_TILES] = y.tiles;
+  tiles[MLORA_PLAN_DX_WHOLE] = dx.whole;
+  tiles[MLORA_PLAN_DX_TILES] = dx.tiles;
   return MLORA_OK;
 }
 

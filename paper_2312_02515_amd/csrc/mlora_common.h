@@ -80,9 +80,11 @@ inline size_t grad_sum_bytes(const SegTable& st, int ranges, int wide_b, int wid
   return align_up((size_t)ranges * rtotal * ((size_t)wide_b + wide_a) * sizeof(float), 256);
 }
 
-// How a base product is cut up: MLORA_FORM_* (mlora_testing.h) and contraction ranges per tile
+// How a base product is cut up: MLORA_FORM_* (mlora_testing.h), contraction ranges per tile, and of the tiles of
+// that form how many run as such
 struct GemmForm {
   int form, parts;
+  int whole, tiles;
 };
 // ... and a low-rank product: rows per block, contraction ranges
 struct RowsForm {

@@ -14,7 +14,8 @@ GENERAL = [
     # one column around its column tiles
     ((1500, 2300, 127, [700, 0, 755], [9, 4, 32], 5), {"Y": "64", "dX": "64"}),
     ((1500, 2300, 129, [700, 755], [9, 32], 5), {"Y": "64", "dX": "64"}),
-    # 128 x 128 tiles: ragged contraction, odd strides, several contraction tiles
+    # 128 x 128 tiles (fp32: a round of them, the rest as quarters, see QUARTERS): ragged contraction, odd strides,
+    # several contraction tiles
     ((2200, 139, 2101, [1000, 0, 1150], [7, 64, 32], 25), {"Y": "128"}),
     ((2200, 2101, 139, [1000, 0, 1150], [7, 64, 32], 25), {"dX": "128", "dX_parts": 1}),
     ((2200, 2101, 320, [1000, 1150], [128, 3], 25), {"dX": "128"}),
@@ -23,6 +24,22 @@ GENERAL = [
     # 64 tasks: the tasks of a block are searched by all lanes
     ((1500, 40, 600, [k % 40 for k in range(64)], [1 + k % 20 for k in range(64)], 11), {"Y": "64"}),
     ((700, 60, 70, [k % 15 for k in range(64)], [1 + k % 20 for k in range(64)], 40), {"Y": "skinny", "dX": "skinny"}),
+]
+
+# General kernels, 128 x 128 tiles: all of them, or whole rounds and the rest as quarters of 64 x 64, in one
+# contraction range or several; quarters beyond the last row and column
+QUARTERS = [
+    # dtype, (T, h, d, tokens, ranks, lead), form
+    ("f32", (2150, 1700, 2101, [1000, 0, 1100], [7, 64, 32], 25), {"Y": "128", "Y_parts": 5, "Y_whole": 256, "Y_tiles": 306}),
+    ("f32", (2150, 2101, 1700, [1000, 0, 1100], [7, 64, 32], 25), {"dX": "128", "dX_parts": 5, "dX_whole": 256, "dX_tiles": 306}),
+    ("f32", (2200, 139, 2101, [1000, 0, 1150], [7, 64, 32], 25), {"Y": "128", "Y_parts": 1, "Y_whole": 256, "Y_tiles": 306}),
+    ("f32", (2200, 2101, 139, [1000, 0, 1150], [7, 64, 32], 25), {"dX": "128", "dX_parts": 1, "dX_whole": 256, "dX_tiles": 306}),
+    ("bf16", (8330, 1500, 1000, [4100, 4150], [9, 100], 70), {"Y": "128", "Y_parts": 4, "Y_whole": 512, "Y_tiles": 528}),
+    ("bf16", (8330, 1000, 1500, [4100, 4150], [9, 100], 70), {"dX": "128", "dX_parts": 4, "dX_whole": 512, "dX_tiles": 528}),
+    ("bf16", (1308, 2050, 6500, [1248, 40], [9, 24], 7), {"Y": "128", "Y_parts": 1, "Y_whole": 512, "Y_tiles": 561}),
+    ("bf16", (1308, 6500, 2050, [1248, 40], [9, 24], 7), {"dX": "128", "dX_parts": 1, "dX_whole": 512, "dX_tiles": 561}),
+    ("bf16", (2200, 139, 2101, [1000, 0, 1150], [7, 64, 32], 25), {"Y": "128", "Y_parts": 1, "Y_whole": 306, "Y_tiles": 306}),
+    ("bf16", (2200, 2101, 139, [1000, 0, 1150], [7, 64, 32], 25), {"dX": "128", "dX_parts": 1, "dX_whole": 306, "dX_tiles": 306}),
 ]
 
 # bf16, h and d multiples of 64: contraction ranges of the low-rank rows

@@ -23,8 +23,13 @@ def test_plan_query(mb):  # noqa: F811
     assert mb.lib.mlora_kernel_plan(ctypes.byref(p.c), out) == 0
     assert mb.lib.mlora_kernel_plan(ctypes.byref(p.c), None) == 1
     assert mb.lib.mlora_kernel_plan(None, out) == 1
+    tiles = (ctypes.c_int32 * len(mb.PLAN_TILES))()
+    assert mb.lib.mlora_kernel_plan_tiles(ctypes.byref(p.c), tiles) == 0
+    assert mb.lib.mlora_kernel_plan_tiles(ctypes.byref(p.c), None) == 1
+    assert mb.lib.mlora_kernel_plan_tiles(None, tiles) == 1
     bad = _problem(mb, off=(0, 40, 30))
     assert mb.lib.mlora_kernel_plan(ctypes.byref(bad.c), out) == 3
+    assert mb.lib.mlora_kernel_plan_tiles(ctypes.byref(bad.c), tiles) == 3
     old = mb.set_kernel_path(1)      # general base products, aligned low-rank kernels
     try:
         q = p.kernel_plan()
@@ -44,6 +49,15 @@ def test_plan_query(mb):  # noqa: F811
 def test_plans_of_known_calls(mb, T, h, d, tokens, ranks, want):  # noqa: F811
     got = plan(mb, T, h, d, tokens, ranks)
     assert {k: got[k] for k in want} == want
+
+
+def test_tiles_of_the_aligned_products(mb):  # noqa: F811
+    def tiles(*a):
+        p = plan(mb, *a)
+        return p["Y"], p["Y_whole"], p["Y_tiles"]
+    assert tiles(16384, 4096, 4096, [16384], [16]) == ("whole", 1024, 1024)
+    assert tiles(100, 4096, 4096, [100], [16]) == ("halves", 0, 16)
+    assert tiles(4300, 1024, 4096, [2100, 2050], [16, 24], 50) == ("mixed", 256, 288)
 
 
 @pytest.mark.parametrize("T,inner,rank,parts", [
@@ -68,12 +82,27 @@ def test_forms_of_shallow_base_products(mb, T, h, d, K, form):  # noqa: F811
     assert plan(mb, T, d, h, [T // K] * K, [4] * K, f32=True)["dX"] == form
 
 
+@pytest.mark.parametrize("dtype,T,inner,outer,parts", [
+    # 64 x 64 tiles: contraction ranges on both sides of the estimate
+    ("f32", 500, 2048, 2048, 2), ("f32", 600, 2048, 2048, 3), ("f32", 800, 2048, 2048, 1),
+    ("f32", 300, 1024, 1024, 6), ("f32", 600, 1024, 1024, 3), ("f32", 800, 1024, 1024, 1),
+    ("bf16", 700, 2050, 1500, 3), ("bf16", 900, 2050, 1500, 1), ("bf16", 512, 1500, 2050, 1),
+])
+def test_contraction_ranges_of_general_products(mb, dtype, T, inner, outer, parts):  # noqa: F811
+    want = ("64", parts)
+    got = plan(mb, T, inner, outer, [T], [8], f32=dtype == "f32")
+    assert (got["Y"], got["Y_parts"]) == want and got["Y_whole"] == got["Y_tiles"]
+    got = plan(mb, T, outer, inner, [T], [8], f32=dtype == "f32")
+    assert (got["dX"], got["dX_parts"]) == want and got["dX_whole"] == got["dX_tiles"]
+
+
 def test_short_tasks_keep_one_range(mb):  # noqa: F811
     assert plan(mb, 4096, 4096, 4096, [64] * 64, [8] * 64)["Z_parts"] == 1
     assert plan(mb, 4096, 4096, 4096, [128] * 32, [8] * 32)["Z_parts"] == 4
 
 
 @pytest.mark.parametrize("dtype,case,want", [(t, c, w) for c, w in form_cases.GENERAL for t in ("f32", "bf16")] +
+                         form_cases.QUARTERS +
                          [("bf16", c, w) for c, w in form_cases.SPLIT_ROWS + form_cases.WHOLE_TILES] +
                          [(t, c, w) for t, c, w, _ in form_cases.ISOLATION])
 def test_sizes_of_the_gpu_tests_take_their_forms(mb, dtype, case, want):  # noqa: F811
