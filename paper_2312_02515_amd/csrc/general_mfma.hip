@@ -173,7 +173,8 @@ __device__ __forceinline__ BlockTile block_tile(const Args& a, int bid) {
 
 // Output column behind column n of the grid's tiles (-1: none).  NN: the weight's rows are loaded in pieces of V
 // columns; the piece that crosses the right edge is loaded so that it ends there and is not shifted into
-// place, so its V columns are the output's last V, some of them computed twice, with the same bits.  (Shifted
+// place, so its V columns are the output's last V.  Those that belong to the piece before it are not stored: that
+// piece may lie in a tile whose contraction is cut into other ranges.  (Shifted
 // into place tile by tile, the blocks at the right edge took up to twice as long and every launch waited for
 // them: forward, fp32 3000 x 4001 -> 4001 956 us against 728, 913 x 1000 -> 1500 67 against 44, bf16 156
 // against 127 for 2048 x 4100 -> 4100.)
@@ -181,7 +182,7 @@ template <typename T, bool NN>
 __device__ __forceinline__ int real_column(int n, int N) {
   constexpr int V = kV<T>;
   const int piece = n / V * V;
-  if (NN && N >= V && piece < N && piece + V > N) return N - V + n % V;
+  if (NN && N >= V && piece < N && piece + V > N) return N - V + n % V >= piece ? N - V + n % V : -1;
   return n < N ? n : -1;
 }
 

@@ -42,6 +42,15 @@ QUARTERS = [
     ("bf16", (2200, 2101, 139, [1000, 0, 1150], [7, 64, 32], 25), {"dX": "128", "dX_parts": 1, "dX_whole": 306, "dX_tiles": 306}),
 ]
 
+# ... forward, the last column tile alone in quarters and ranges, 1 .. V - 1 columns wide (V = columns of a
+# 16-byte piece): the piece of columns at the right edge begins in the tile before it
+EDGE_QUARTERS = [
+    ("f32", (1436, 600, 5377, [1376, 40], [9, 24], 7), {"Y": "128", "Y_parts": 4, "Y_whole": 512, "Y_tiles": 516}),
+    ("f32", (1436, 600, 5379, [1376, 40], [9, 24], 7), {"Y": "128", "Y_parts": 4, "Y_whole": 512, "Y_tiles": 516}),
+    ("bf16", (2460, 2050, 1537, [2400, 40], [9, 24], 7), {"Y": "128", "Y_parts": 7, "Y_whole": 256, "Y_tiles": 260}),
+    ("bf16", (2460, 2050, 1543, [2400, 40], [9, 24], 7), {"Y": "128", "Y_parts": 7, "Y_whole": 256, "Y_tiles": 260}),
+]
+
 # bf16, h and d multiples of 64: contraction ranges of the low-rank rows
 SPLIT_ROWS = [
     ((4300, 4160, 64, [2000, 2140], [16, 33], 60), {"Z_rows": 128, "Z_parts": 4, "G_parts": 1}),

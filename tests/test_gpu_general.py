@@ -83,6 +83,23 @@ def test_general_quarters(dtype, case):
     check_full(inp, run_hip(inp), TOL[dtype], label=f"quarters {case}")
 
 
+@pytest.mark.parametrize("dtype,case", [(t, c) for t, c, _ in form_cases.EDGE_QUARTERS])
+def test_columns_of_a_tile_are_summed_alike(dtype, case):
+    """Columns of one 128 x 128 tile that hold the same values come out with the same bits, also those that the
+    piece of columns at the right edge (of the next tile, which is summed in ranges) covers again."""
+    T, h, d, tokens, ranks, lead = case
+    dtype = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    inp = _inputs(T, h, d, tokens, ranks, dtype, lead=lead, seed=88)
+    V = 16 // inp.X.element_size()
+    p = d // 128 * 128                     # first column of the last tile
+    again, other = slice(d - V, p), slice(d - V - 2 * V, p - 2 * V)
+    for M in [inp.W] + inp.B:
+        M[:, again] = M[:, other]
+    out = run_hip(inp)
+    assert torch.equal(out["Y"][:, again], out["Y"][:, other])
+    check_full(inp, out, TOL[dtype], label=f"right edge {case}")
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("h,d,tokens,ranks", [
     (61, 66, [31, 32, 33, 1], [16, 17, 8, 33]),           # around a run's tokens; edges inside and between lanes' pieces
