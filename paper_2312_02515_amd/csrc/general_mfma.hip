@@ -815,8 +815,11 @@ __global__ __launch_bounds__(512, 4) void k_gen_skinny(const GenGemmArgs<NSEG> a
 // to part + range * part_step ([sum of r_k][wide]) for grad_reduce to add in order.  fp32, T = 2048, 4 tasks, 4096
 // columns, rank 16: dB and dA in one launch 18 us + 5 us of reduction for 67 MB, against 131 us each with
 // a serial sum per output element.  Small calls are bound by latency: a run of groups is requested at once, the
-// last one with masks (one launch, 64 tokens x 256 columns x 2 tasks 4.9 us instead of 10.4 with a wait per group,
-// 125 x 1000 x 8 7.6 instead of 19.3; bf16 300 x (1000 + 1500) x 3 6.4 instead of 16.6, 1333 tokens 9.5 instead of 19.9).
+// last one with masks and without the groups behind the last token (one launch, 64 tokens x 256 columns x 2 tasks 4.9 us
+// instead of 10.4 with a wait per group, 125 x 1000 x 8 7.6 instead of 19.3; bf16 300 x (1000 + 1500) x 3 6.4 instead of
+// 16.6, 1333 tokens 9.5 instead of 19.9).  Where a task has no more tokens than a group there is nothing to overlap:
+// fp32, 64 tasks of one token, 16 + 16 columns, rank 128 9.9 us, a wait per group 9.2, all groups of the run 12.7;
+// rank 64 6.6, 6.3, 8.0.
 // ------------------------------------------------------------------------------------------
 struct GenGradArgs {
   const void* Big;
@@ -928,10 +931,12 @@ __device__ __forceinline__ void grad_body(const GenGradArgs& a, int ch, int sp, 
   auto run = [&](int t, bool tail) {
     Group g[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) load(g[u], t + u * GT);
+    for (int u = 0; u < U; ++u)
+      if (!tail || u == 0 || t + u * GT < hi) load(g[u], t + u * GT);
     __builtin_amdgcn_sched_barrier(0);               // (the loads stay in front)
 #pragma unroll
-    for (int u = 0; u < U; ++u) multiply(g[u], t + u * GT, tail);
+    for (int u = 0; u < U; ++u)
+      if (!tail || u == 0 || t + u * GT < hi) multiply(g[u], t + u * GT, tail);
   };
   int t = lo;
   if (wide >= 4) {
@@ -963,9 +968,10 @@ __device__ __forceinline__ void grad_body(const GenGradArgs& a, int ch, int sp, 
       const int i = WIDE_FIRST ? 4 * kg + e : l16;
       const int c = first_col(i), skip = c0 + 4 * i - c, q = WIDE_FIRST ? 16 * j + l16 : 16 * j + 4 * kg + e;
       if (q >= r) continue;
+      const unsigned n = wide >= 4 ? 4 : (wide > c ? wide - c : 0);   // (from four columns on c + 3 < wide)
 #pragma unroll
       for (int f = 0; f < 4; ++f)
-        if (f >= skip && c + f < wide) put(WIDE_FIRST ? o + (size_t)(c + f) * r + q : o + (size_t)q * wide + c + f, acc[f][j][e]);
+        if ((unsigned)(f - skip) < n) put(WIDE_FIRST ? o + (size_t)(c + f) * r + q : o + (size_t)q * wide + c + f, acc[f][j][e]);
     }
   }
 }

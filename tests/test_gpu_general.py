@@ -105,6 +105,8 @@ def test_columns_of_a_tile_are_summed_alike(dtype, case):
     (61, 66, [31, 32, 33, 1], [16, 17, 8, 33]),           # around a run's tokens; edges inside and between lanes' pieces
     (259, 7, [63, 64, 65, 0], [65, 4, 64, 128]),          # ranks on either side of each group count
     (3, 513, [97, 130], [5, 40], ),                       # rows shorter than a piece; one column in the last block
+    (70, 1027, [1, 2, 3, 4, 5, 8, 9, 12, 13, 16, 17, 28], [128, 17, 64, 1, 33, 65, 16, 128, 40, 66, 32, 8]),   # tokens around
+                                                          # the groups of one run, in the body for each rank
 ])
 def test_general_gradients_add_to_what_is_there(dtype, h, d, tokens, ranks):
     """A column that two lanes load is stored, and in accumulate mode added, once."""
