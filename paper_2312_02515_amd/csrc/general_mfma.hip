@@ -1047,7 +1047,8 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
 //   fp32  2048 x 2048 -> 2176 (272 tiles)  248 in whole tiles, 151 as one round and quarters in 8 ranges
 //         2048 x 4100 -> 4100 (528)        740 and 533 (4 ranges);   8000 x 1501 -> 701 (378)  188 and 161
 //         2048 x 2048 -> 4096 (512: two rounds) 253; quarters alone take 283
-//         1280 x 2048 -> 2048 (160: all 64 x 64) 110 in one range, 100 in two; 1024 x 2048 -> 2048 79 and 82
+//         1280 x 2048 -> 2048 (160: all 64 x 64) 110 in one range (two, 100 us, would be more than kMostUnits partial
+//         tiles); 1024 x 2048 -> 2048 79 in one, 82 in two
 //   bf16  2048 x 4100 -> 4100              128 and 104;   2048 x 2048 -> 2176  40 and 42
 struct GemmPlan {
   bool skinny, small;
@@ -1055,21 +1056,28 @@ struct GemmPlan {
   int whole;                             // 128 x 128: tiles [0, whole) as such, the others in quarters (small: 0)
 };
 constexpr int kMaxParts = 16, kMostUnits = 1024, kTilesPerPart = 4;   // (contraction tiles of 128 bytes per row)
-// us per contraction tile: a block alone on its CU, and the share of one among several
+// us per contraction tile: a block alone on its CU, and the share of one among several; and per 16 ranks of the
+// LoRA term of a 64 x 64 tile, forward and backward layout
 struct StepTimes {
-  double large_alone, large, small_alone, small;
+  double large_alone, large, small_alone, small, lora_nn, lora_nt;
 };
-constexpr StepTimes kSteps[2] = {{1.97, 1.97, 0.70, 0.58}, {0.80, 0.60, 0.36, 0.27}};   // fp32, bf16
+constexpr StepTimes kSteps[2] = {{1.97, 1.97, 0.70, 0.58, 0.45, 0.9}, {0.80, 0.60, 0.36, 0.27, 0.3, 0.7}};   // fp32, bf16
 // launches of n blocks of a form: 256 of them are a round
 double rounds_us(long long n, double alone, double among) { return n <= 256 ? alone : (double)((n + 255) / 256) * among; }
-// `units` 64 x 64 tiles of kt contraction tiles: fewest us, the ranges for it, at least kTilesPerPart deep
-double small_tiles_us(long long units, long long kt, const StepTimes& t, size_t scratch_limit, int* parts) {
+// `units` 64 x 64 tiles of kt contraction tiles with `lora` us of LoRA term in the last range and `per_7mb` us of
+// reduction for 7 MB of partial tiles: fewest us, the ranges for it, at least kTilesPerPart deep.  An XCD deals its
+// blocks to its 32 CUs in turn, so with 2, 4, 8 or 16 ranges the tiles' last ranges, which hold the LoRA terms, share a
+// half .. a sixteenth of the CUs: each further one on a CU adds 0.8 of the term.
+double small_tiles_us(long long units, long long kt, const StepTimes& t, double lora, double per_7mb, size_t scratch_limit,
+                      int* parts) {
   double best = 0;
   *parts = 0;
   for (int p = 1; p <= kMaxParts && (p == 1 || (kt / p >= kTilesPerPart && units * p <= kMostUnits)); ++p) {
     const size_t bytes = p > 1 ? (size_t)units * p * 64 * 64 * sizeof(float) : 0;
     if (bytes > scratch_limit) break;
-    const double us = 6 + (double)((kt + p - 1) / p) * rounds_us(units * p, t.small_alone, t.small) + (p > 1 ? 4 + (double)bytes / 7e6 : 0);
+    const long long on_one_cu = (units * (p & -p) + 255) / 256;   // (p & -p: the power of two in p)
+    const double us = 6 + (double)((kt + p - 1) / p) * rounds_us(units * p, t.small_alone, t.small) +
+                      lora * (1 + 0.8 * (double)(on_one_cu - 1)) + (p > 1 ? 4 + per_7mb * (double)bytes / 7e6 : 0);
     if (*parts == 0 || us < best) {
       best = us;
       *parts = p;
@@ -1077,8 +1085,15 @@ double small_tiles_us(long long units, long long kt, const StepTimes& t, size_t 
   }
   return best;
 }
+// steps of 16 of the largest rank
+int rank_steps(const int* rank, int K) {
+  int rmax = 0;
+  for (int k = 0; k < K; ++k) rmax = rank[k] > rmax ? rank[k] : rmax;
+  return (rmax + 15) / 16;
+}
 long long contraction_tiles(long long Kd, int dtype) { return (Kd + (dtype == MLORA_F32 ? 31 : 63)) / (dtype == MLORA_F32 ? 32 : 64); }
-GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dtype, size_t scratch_limit) {
+// (`steps16` steps of 16 ranks over all operand pairs)
+GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int steps16, bool nn, int dtype, size_t scratch_limit) {
   const long long mv = virtual_rows(st, M);
   GemmPlan p;
   p.skinny = false;
@@ -1098,11 +1113,19 @@ GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int dty
   p.parts = 1;
   p.whole = p.small ? 0 : (int)tiles;
   if (p.small) {
-    small_tiles_us(tiles, kt, t, scratch_limit, &p.parts);
+    // The LoRA term and 1.25 us: without the one and with 1, high ranks were cut into too many ranges.  Backward, product
+    // and reduction, us with ranges of 4 contraction tiles and more whatever the rank, of 16 and more, and as chosen here:
+    //   fp32  500 rows, 2000 deep, 700 columns, rank 128  48, 40, 34;   500 x 1000 x 1000, rank 128  37, 30, 30
+    //   bf16  300 x 1500 x 1500, rank 128  30.6, 20.2, 20.4;   150 rows, 3000 deep, 300 columns, rank 2  12.6, 17.0, 12.9
+    // (1292 products of 60 to 1500 rows: 1 % less in sum than with the first rule, none more than 6 % behind it).
+    small_tiles_us(tiles, kt, t, steps16 * (nn ? t.lora_nn : t.lora_nt), 1.25, scratch_limit, &p.parts);
   } else if (tiles % 256 != 0) {
     const long long q = tiles / 256 * 256;
     int parts;
-    const double rest = small_tiles_us(4 * (tiles - q), kt, t, scratch_limit, &parts);
+    // (The round of 128 x 128 tiles that the quarters replace has a LoRA term too; with it and 1.5 us the choice
+    // takes 6-10 % longer: forward, fp32 2540 x 300 -> 2037, rank 128 46.8 and 59.9, bf16 3436 x 1500 -> 2549, rank 8
+    // 55 and 61.)
+    const double rest = small_tiles_us(4 * (tiles - q), kt, t, 0, 1, scratch_limit, &parts);
     if ((double)kt * rounds_us(q, t.large_alone, t.large) + rest < (double)kt * rounds_us(tiles, t.large_alone, t.large)) {
       p.whole = (int)q;
       p.parts = parts;
@@ -1159,6 +1182,7 @@ hipError_t gemm_n(int n, const GenOperands* ops, int dtype, void* C, int M, int 
   a.K = st.K;
   for (int k = 0; k <= kMaxK; ++k) a.off[k] = st.off[k];
   long long kd = 0;
+  int steps16 = 0;
   for (int g = 0; g < NSEG; ++g) {
     const GenOperands& o = ops[g < n ? g : 0];
     a.A[g] = o.A;
@@ -1169,8 +1193,9 @@ hipError_t gemm_n(int n, const GenOperands* ops, int dtype, void* C, int M, int 
     for (int k = 0; k < kMaxK; ++k) a.rank[g][k] = (unsigned char)(g < n && k < st.K ? o.rank[k] : 0);
     a.R[g] = *o.R;
     kd += a.Kd[g];
+    if (g < n) steps16 += rank_steps(o.rank, st.K);
   }
-  const GemmPlan pl = plan_gemm(st, M, N, kd, dtype, scratch_bytes);
+  const GemmPlan pl = plan_gemm(st, M, N, kd, steps16, nn, dtype, scratch_bytes);
   const bool f32 = dtype == MLORA_F32;
   if (!nn) return f32 ? launch_gemm<float, false, NSEG>(a, pl, scratch, s) : launch_gemm<bf16, false, NSEG>(a, pl, scratch, s);
   if constexpr (NSEG == 1)
@@ -1224,8 +1249,8 @@ size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype)
   return b;
 }
 
-GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, int dtype, size_t scratch_bytes) {
-  const GemmPlan pl = plan_gemm(st, M, N, Kd, dtype, scratch_bytes);
+GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, int dtype, size_t scratch_bytes) {
+  const GemmPlan pl = plan_gemm(st, M, N, Kd, rank_steps(st.rank, st.K), nn, dtype, scratch_bytes);
   const int form = pl.skinny ? MLORA_FORM_SKINNY : (pl.small ? MLORA_FORM_64 : MLORA_FORM_128), tiles = pl.tiles_m * pl.tiles_n;
   return GemmForm{form, pl.parts, form == MLORA_FORM_128 ? pl.whole : tiles, tiles};
 }

@@ -248,10 +248,11 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
   return e;
 }
 
-// how a base product of N outputs and Kd contraction indices is cut up
-GemmForm product_form(const mlora_problem* p, const CallCtx& c, int N, int Kd) {
+// how the base product of Y (nn) or dX is cut up
+GemmForm product_form(const mlora_problem* p, const CallCtx& c, bool nn) {
+  const int N = nn ? c.d : c.h, Kd = nn ? c.h : c.d;
   return mfma_gemm_applies(p) ? gemm_form(c.st, c.T, N, Kd, c.scratch_bytes)
-                              : general_gemm_form(c.st, c.T, N, Kd, c.dtype, c.scratch_bytes);
+                              : general_gemm_form(c.st, c.T, N, Kd, nn, c.dtype, c.scratch_bytes);
 }
 
 // Whether the shared-input low-rank kernels (one pass over X for all projections) apply
@@ -627,7 +628,7 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
   fill_ctx(p, nullptr, &c);
   const size_t room = c.scratch_bytes;
   const bool al = mfma_lowrank_applies(p);
-  const GemmForm y = product_form(p, c, c.d, c.h), dx = product_form(p, c, c.h, c.d);
+  const GemmForm y = product_form(p, c, true), dx = product_form(p, c, false);
   const RowsForm z = al ? rows_form(c.st, c.h, c.ldz, room) : general_rows_form(c);
   const RowsForm g = al ? rows_form(c.st, c.d, c.ldz, room) : general_rows_form(c);
   plan[MLORA_PLAN_Y] = y.form;
@@ -648,7 +649,7 @@ mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles) {
   if (tiles == nullptr) return MLORA_ERR_NULL;
   CallCtx c;
   fill_ctx(p, nullptr, &c);
-  const GemmForm y = product_form(p, c, c.d, c.h), dx = product_form(p, c, c.h, c.d);
+  const GemmForm y = product_form(p, c, true), dx = product_form(p, c, false);
   tiles[MLORA_PLAN_Y_WHOLE] = y.whole;
   tiles[MLORA_PLAN_Y_TILES] = y.tiles;
   tiles[MLORA_PLAN_DX_WHOLE] = dx.whole;

@@ -119,7 +119,7 @@ struct GenOperands {
   const int* rank;     // K entries
   const PtrTable* R;
 };
-GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, int dtype, size_t scratch_bytes);
+GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, int dtype, size_t scratch_bytes);
 RowsForm general_rows_form(const CallCtx& c);
 int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes);
 // C = sum over the n <= MLORA_MAX_GROUP operand pairs of A op(W) + rows_k(L R_k)

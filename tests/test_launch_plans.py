@@ -82,17 +82,20 @@ def test_forms_of_shallow_base_products(mb, T, h, d, K, form):  # noqa: F811
     assert plan(mb, T, d, h, [T // K] * K, [4] * K, f32=True)["dX"] == form
 
 
-@pytest.mark.parametrize("dtype,T,inner,outer,parts", [
+@pytest.mark.parametrize("dtype,T,inner,outer,rank,parts", [
     # 64 x 64 tiles: contraction ranges on both sides of the estimate
-    ("f32", 500, 2048, 2048, 2), ("f32", 600, 2048, 2048, 3), ("f32", 800, 2048, 2048, 1),
-    ("f32", 300, 1024, 1024, 6), ("f32", 600, 1024, 1024, 3), ("f32", 800, 1024, 1024, 1),
-    ("bf16", 700, 2050, 1500, 3), ("bf16", 900, 2050, 1500, 1), ("bf16", 512, 1500, 2050, 1),
+    ("f32", 500, 2048, 2048, 8, 2), ("f32", 600, 2048, 2048, 8, 3), ("f32", 800, 2048, 2048, 8, 1),
+    ("f32", 300, 1024, 1024, 8, 6), ("f32", 600, 1024, 1024, 8, 3), ("f32", 800, 1024, 1024, 8, 1),
+    ("bf16", 150, 3000, 300, 2, 10), ("bf16", 900, 2050, 1500, 8, 1), ("bf16", 512, 1500, 2050, 8, 1),
+    # high ranks, whose LoRA terms share the CUs of the last ranges
+    ("f32", 500, 1000, 1000, 16, 4), ("f32", 500, 1000, 1000, 128, 2), ("f32", 500, 2000, 700, 128, 5),
+    ("bf16", 300, 1500, 1500, 128, 1),
 ])
-def test_contraction_ranges_of_general_products(mb, dtype, T, inner, outer, parts):  # noqa: F811
+def test_contraction_ranges_of_general_products(mb, dtype, T, inner, outer, rank, parts):  # noqa: F811
     want = ("64", parts)
-    got = plan(mb, T, inner, outer, [T], [8], f32=dtype == "f32")
+    got = plan(mb, T, inner, outer, [T], [rank], f32=dtype == "f32")
     assert (got["Y"], got["Y_parts"]) == want and got["Y_whole"] == got["Y_tiles"]
-    got = plan(mb, T, outer, inner, [T], [8], f32=dtype == "f32")
+    got = plan(mb, T, outer, inner, [T], [rank], f32=dtype == "f32")
     assert (got["dX"], got["dX_parts"]) == want and got["dX_whole"] == got["dX_tiles"]
 
 
