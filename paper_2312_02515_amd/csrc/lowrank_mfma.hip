@@ -8,9 +8,9 @@
 //                  dB_k = Z^T dy_k          (Eq. "grad_lora", right)
 //
 // One launch covers all tasks: a block finds its task from the split positions.
-// Tiles are staged with direct global->LDS loads (16 B per lane) into a ring of three stages (gradients: or
-// two), two tiles in flight per block and two blocks per CU (an HBM-bound stream needs tens of KiB in
-// flight per CU); operands whose contraction index is not contiguous in memory (A_k, and
+// Tiles are staged with direct global->LDS loads (16 B per lane) into a ring of three stages, two tiles in
+// flight per block (some gradients: two stages and one tile), and two blocks per CU where they fit (an HBM-bound
+// stream needs tens of KiB in flight per CU); operands whose contraction index is not contiguous in memory (A_k, and
 // everything in the two gradient products, where the contraction runs over
 // tokens) are read from LDS with the transposing ds_read_b64_tr_b16.
 #include "mfma_staging.h"
@@ -517,31 +517,38 @@ __global__ __launch_bounds__(256) void k_lowrank_mfma_splitk(const RowsArgs<1> r
 // The whole reduction of an output element happens inside one block: deterministic, no atomics.
 // ------------------------------------------------------------------------------------------
 // LDS of one ring stage: 64 tokens x 128 columns of Big; 64 tokens x ldz of every Small_p, ldz <= 32 NQ, in
-// NQ x 4 KiB each.  (Lanes whose column lies beyond the tile read another one: what they sum is not stored.)  The
+// NQ x 4 KiB each.  Lanes whose column lies beyond the tile sum what is not stored: they read another column or, with
+// `pads`, the 64 zero bytes behind the tile.  The pads take a barrier before the first load, but the long tasks of one
+// block per CU are faster with them (dB and dA, rank 128, 32768 x 4096, one task 142 us against 153, 16384 x 1024 -> 4096, 4
+// tasks 63 against 68); short tasks and the smaller ranks are not (4 us launches 0.2 us longer).  The
 // stages are separate arrays of the kernels (as members of one struct they cost the shared-input
 // launch 10 us of 178).
 constexpr int kBigStage = 64 * 128 * 2;
-template <int NQ> constexpr int kSmallStage = NQ * 32 * 128;
-// Three stages where two blocks of them share a CU, two where that is what makes room for the second
-// block (160 KiB of LDS).  us with three and with two stages: ranks above 64, 16384 x 4096 98 and 76, 12 tasks of 256
-// tokens 33 and 24, 64 tasks of 32 tokens 59 and 37; dA of three projections that share X, ranks up to 64, 32768 x
-// 5120 168 and 133.  Where two blocks of three stages fit, two stages lose: 16384 x 4096, ranks up to 64, 53 and 59.
+constexpr bool grad_pads(int nq, int np, int stages) { return nq == 4 && np == 1 && stages == 3; }
+template <int NQ, int NP, int NS> constexpr int kSmallStage = NQ * 32 * 128 + (grad_pads(NQ, NP, NS) ? 1024 : 0);
+// Three stages (two tiles in flight) where two blocks of them share a CU, and where a CU has no second block to
+// run; two where that is what makes room for the second block (160 KiB of LDS).  us with three and with two stages: ranks above
+// 64, dB and dA, 16384 x 4096 (16 tasks) 89 and 64, 12 tasks of 256 tokens 25 and 19, 64 tasks of 32 tokens 59 and 37, but at
+// most 256 blocks: 1024 x 64 (4 tasks) 10.4 and 11.9, 2048 x 1024 (16) 12.1 and 13.2, 16384 x 4096 (4) 73.8 and 75.1;
+// dA of three projections that share X, ranks up to 64, 32768 x 5120 168 and 133.  Where two blocks of three
+// stages fit, two stages lose: 16384 x 4096, ranks up to 64, 53 and 59.
 template <int NQ, int NP>
 constexpr int grad_stages() {
-  constexpr int stage = kBigStage + NP * kSmallStage<NQ>, half = 80 * 1024;
+  constexpr int stage = kBigStage + NP * kSmallStage<NQ, NP, 2>, half = 80 * 1024;
   return 3 * stage > half && 2 * stage <= half ? 2 : 3;
 }
-#define MLORA_GRAD_STAGES(NQ, NP)                                                                              \
-  constexpr int kThird = grad_stages<NQ, NP>() == 3 ? 1 : 0;                                                    \
-  __shared__ __attribute__((aligned(1024))) char sB0[kBigStage], sB1[kBigStage], sS0[NP * kSmallStage<NQ>],     \
-      sS1[NP * kSmallStage<NQ>], sB2[kThird ? kBigStage : 1], sS2[kThird ? NP * kSmallStage<NQ> : 1];            \
+#define MLORA_GRAD_STAGES(NQ, NP, NS)                                                                          \
+  constexpr int kSmall = NP * kSmallStage<NQ, NP, NS>;                                                          \
+  __shared__ __attribute__((aligned(1024))) char sB0[kBigStage], sB1[kBigStage], sS0[kSmall], sS1[kSmall],       \
+      sB2[NS == 3 ? kBigStage : 1], sS2[NS == 3 ? kSmall : 1];                                                   \
   char* const sB[3] = {sB0, sB1, sB2};                                                                          \
   char* const sS[3] = {sS0, sS1, sS2}
 
-template <bool WIDE_FIRST, int NQ, int NP>
+template <bool WIDE_FIRST, int NQ, int NP, int NS>
 __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char* const (&sB)[3], char* const (&sS)[3]) {
-  constexpr int WC = 128, NS = grad_stages<NQ, NP>();
-  constexpr int SREG = kSmallStage<NQ>;
+  constexpr int WC = 128;
+  constexpr int SREG = kSmallStage<NQ, NP, NS>, SBYTES = NQ * 32 * 128;
+  constexpr bool PADS = grad_pads(NQ, NP, NS);
   static_assert(WIDE_FIRST || NP == 1, "shared-input form exists for dA only");
 
   const bf16* __restrict__ Big = ga.Big;
@@ -560,6 +567,11 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char*
   const int tk = hi - lo;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  if (PADS && tid < 16) {
+#pragma unroll
+    for (int s_ = 0; s_ < NS; ++s_) reinterpret_cast<int*>(sS[s_] + SBYTES)[tid] = 0;
+  }
 
   // Big tile: 64 token rows x 256 B; wave instruction w covers rows 4w..4w+3
   int brow[4], bcol[4];
@@ -640,10 +652,11 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char*
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
           if (32 * j < rank[p]) {
-            const int n = 32 * j + tr_n < ldz[p] ? 32 * j + tr_n : 0;
+            const bool in = 32 * j + tr_n < ldz[p];
+            const int n = in || PADS ? 32 * j + tr_n : 0;
             const int ns = n ^ (seg_swizzle(kk, ldz[p]) << 5);
-            const char* p0 = ss + (kk * ldz[p] + ns) * 2;
-            const char* p1 = ss + ((kk + 4) * ldz[p] + ns) * 2;
+            const char* p0 = ss + (in || !PADS ? (kk * ldz[p] + ns) * 2 : SBYTES);
+            const char* p1 = ss + (in || !PADS ? ((kk + 4) * ldz[p] + ns) * 2 : SBYTES);
             short4v s0 = lds_read_tr(p0), s1 = lds_read_tr(p1);
             if (valid < 64) {
               // the lane's 8 contraction indices are tokens 16ks + 8*lhi + 0..7 of the tile
@@ -666,6 +679,7 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char*
   };
 
   const int KT = (tk + 63) / 64;
+  if (PADS) __syncthreads();
 #pragma unroll
   for (int s_ = 0; s_ < NS - 1; ++s_)
     if (s_ < KT) issue(s_, sB[s_], sS[s_]);
@@ -739,15 +753,16 @@ __device__ __forceinline__ void grad_body(const GradArgs<NP>& ga, int bid, char*
 // dA of projections that share their input
 template <int NQ, int NP>
 __global__ __launch_bounds__(256) void k_grad_mfma(const GradArgs<NP> ga) {
-  MLORA_GRAD_STAGES(NQ, NP);
-  grad_body<true, NQ, NP>(ga, blockIdx.x, sB, sS);
+  constexpr int NS = grad_stages<NQ, NP>();
+  MLORA_GRAD_STAGES(NQ, NP, NS);
+  grad_body<true, NQ, NP, NS>(ga, blockIdx.x, sB, sS);
 }
 // dB (the first blocks_b blocks: dY has just been read for G) and dA of one call
-template <int NQ>
+template <int NQ, int NS>
 __global__ __launch_bounds__(256) void k_grad_pair(const GradArgs<1> b, const GradArgs<1> a, int blocks_b) {
-  MLORA_GRAD_STAGES(NQ, 1);
-  if ((int)blockIdx.x < blocks_b) grad_body<false, NQ, 1>(b, blockIdx.x, sB, sS);
-  else grad_body<true, NQ, 1>(a, blockIdx.x - blocks_b, sB, sS);
+  MLORA_GRAD_STAGES(NQ, 1, NS);
+  if ((int)blockIdx.x < blocks_b) grad_body<false, NQ, 1, NS>(b, blockIdx.x, sB, sS);
+  else grad_body<true, NQ, 1, NS>(a, blockIdx.x - blocks_b, sB, sS);
 }
 
 // Adds the token ranges' partial sums in range order (deterministic) into the tasks' outputs.  One
@@ -1064,8 +1079,11 @@ hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* 
 // Token ranges per task of up to `longest` tokens for the gradient kernels, one number for dB and dA: as many
 // as give every CU a block (at most 16, at least 256 tokens each).  More cost their reduction more than they
 // bring: 6000 tokens of 4 tasks, 4096 x 4096, rank 64, forward + backward 423 us with two blocks per CU, 411
-// us with one.  Ranks above 64: no more than 256 in all (65536 tokens of one task, 1024 -> 4096, rank 128,
-// backward 843 us with 280 blocks, 753 with 240, measured when such a block had its CU to itself).
+// us with one.  Ranks above 64: no more than 256 in all, each with a CU to itself (65536 tokens of one task, 1024 ->
+// 4096, rank 128, backward 843 us with 280 blocks of three stages, 753 with 240).  Up to 512 blocks, two on a CU with two
+// stages, would suit few long tasks and hurt others, sums included, rank 128 unless stated: 16384 x 5120 (2 tasks) 129 -> 88 us,
+// 32768 x 1024 -> 4096 (4) 129 -> 95, 8192 x 5120 (2, rank 72) 62 -> 43, but 8192 x 1024 (12) 21 -> 40, 4096 x 1024 -> 4096 (4) 24
+// -> 33, 8192 x 4096 (4, rank 72) 36 -> 42: that takes a rule of its own.
 int grad_ranges(const SegTable& st, int wide_b, int wide_a, int longest) {
   const int blocks = st.K * ((wide_b + 127) / 128 + (wide_a + 127) / 128);
   int rmax = 0;
@@ -1133,9 +1151,10 @@ hipError_t grads_mfma(const CallCtx& c, const bf16* dY, const bf16* Z, const Out
   const int nq = nq_of(c.ldz);
   const int slot = profile_begin(kProfileGrad, grad_bytes(b) + (dA != nullptr ? grad_bytes(a) : 0.0), c.stream);
   const dim3 grid((unsigned)(blocks_b + blocks_a));
-  if (nq == 1) hipLaunchKernelGGL((k_grad_pair<1>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
-  else if (nq == 2) hipLaunchKernelGGL((k_grad_pair<2>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
-  else hipLaunchKernelGGL((k_grad_pair<4>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  if (nq == 1) hipLaunchKernelGGL((k_grad_pair<1, grad_stages<1, 1>()>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  else if (nq == 2) hipLaunchKernelGGL((k_grad_pair<2, grad_stages<2, 1>()>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  else if (grid.x > 256) hipLaunchKernelGGL((k_grad_pair<4, grad_stages<4, 1>()>), grid, dim3(256), 0, c.stream, b, a, blocks_b);
+  else hipLaunchKernelGGL((k_grad_pair<4, 3>), grid, dim3(256), 0, c.stream, b, a, blocks_b);   // (see grad_stages)
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && splits > 1)
     e = grad_reduce(c.st, partial, splits, wide_b, dB, wide_a, dA != nullptr ? *dA : dB, accumulate, c.stream);

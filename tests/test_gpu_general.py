@@ -197,6 +197,22 @@ def test_short_tasks_of_high_rank_in_ranges(h, d, rank):
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"short tasks {h, d, rank}")
 
 
+@pytest.mark.parametrize("h,d", [(256, 320), (5120, 1088)])
+def test_gradients_of_high_ranks(h, d):
+    """Ranks above 64 with at most 256 gradient blocks (three ring stages) and with more (two): tasks around whole
+    64-token tiles, long enough to go round the ring, overwriting and adding."""
+    tokens, ranks = [0, 1, 64, 65, 700, 449], [128, 65, 72, 100, 127, 128]
+    assert (len(tokens) * ((h + 127) // 128 + (d + 127) // 128) > 256) == (h == 5120)
+    inp = _inputs(sum(tokens) + 7, h, d, tokens, ranks, torch.bfloat16, lead=3, seed=89)
+    got = run_hip(inp)
+    check_full(inp, got, TOL[torch.bfloat16], label=f"high ranks {h, d}")
+    pre = [[torch.full_like(g, 0.5 + k) for k, g in enumerate(got[n])] for n in ("dA", "dB")]
+    acc = run_hip(inp, accumulate=True, preset_grads=pre)
+    for n, p in zip(("dA", "dB"), pre):
+        for g, was, now in zip(got[n], p, acc[n]):
+            assert torch.equal(now, was + g)
+
+
 @pytest.mark.parametrize("P", [2, 3, 4])
 def test_ragged_ranks_in_a_group(P):
     ranks = [[5 + p, 12, 8] for p in range(P)]
