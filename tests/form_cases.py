@@ -74,6 +74,28 @@ WHOLE_TILES = [
         ((9268, 1024, k, _SHARED, [128, 8, 33, 64] * 12, 20), {"dX": "whole"}))
 ]
 
+# bf16, h and d multiples of 64: around the number of tasks from which a wave's lanes search for a row's task
+# (eight), in blocks of 32 rows with four waves each, 128 with ranges, 64 and 128
+
+
+def _lanes_case(T, h, d, rank, K):
+    """Empty tasks at either end and in between, tasks of one row; the second task takes what is left."""
+    left, tokens = T - 60, []
+    for k in range(K):
+        t = 0 if k in (0, 4, K - 1) else 1 if k % 7 == 5 else min(left, 2 * (T - 60) // K * (1 + k % 3) // 4)
+        tokens.append(t)
+        left -= t
+    tokens[1] += left
+    return T, h, d, tokens, [max(1, rank - 5 * (k % 4)) for k in range(K)], 31
+
+
+LANES = [(_lanes_case(*size, K), dict(want, **({"Z_parts": 2 if K == 64 else 4} if size[0] == 4300 else {})))
+         for K in (8, 9, 33, 64) for size, want in [
+             ((1700, 4096, 128, 24), {"Y": "halves", "Z_rows": 32, "G_rows": 32, "Z_parts": 1}),
+             ((4300, 2048, 192, 128), {"Y": "halves", "dX": "whole", "Z_rows": 128}),
+             ((17000, 128, 1088, 16), {"Y": "whole", "dX": "halves", "Z_rows": 64, "G_rows": 64}),
+             ((33600, 128, 64, 16), {"Y": "whole", "dX": "whole", "Z_rows": 128, "G_rows": 128, "Z_parts": 1, "G_parts": 1})]]
+
 # Isolation of a diverged task (the last entry of a case) from its neighbours
 ISOLATION = [
     # dtype, (T, h, d, tokens, ranks, lead), form, task

@@ -167,22 +167,13 @@ def test_ragged_ranks_on_aligned_shapes(case):
     check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"ragged ranks {case}")
 
 
-@pytest.mark.parametrize("K", [8, 9, 33, 64])
-@pytest.mark.parametrize("T,h,d,rank", [
-    (1700, 4096, 128, 24),       # few rows per task: four-wave rows, half tiles in ranges
-    (4300, 2048, 192, 128),      # ranges of the low-rank rows, added task by task
-    (17000, 128, 1088, 16),      # whole tiles, 64- and 128-row blocks
-])
-def test_tasks_searched_by_all_lanes(T, h, d, rank, K):
+@pytest.mark.parametrize("case", [c for c, _ in form_cases.LANES])
+def test_tasks_searched_by_all_lanes(case):
     """Around the number of tasks from which a wave's lanes search for a row's task: empty tasks at either
     end and in between, tasks of one row, rows of no task before and after."""
-    left, tokens = T - 60, []
-    for k in range(K):
-        t = 0 if k in (0, 4, K - 1) else 1 if k % 7 == 5 else min(left, 2 * (T - 60) // K * (1 + k % 3) // 4)
-        tokens.append(t)
-        left -= t
-    inp = _inputs(T, h, d, tokens, [max(1, rank - 5 * (k % 4)) for k in range(K)], torch.bfloat16, lead=31, seed=86)
-    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"tasks {T, h, d, K}")
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=86)
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"tasks {T, h, d, len(tokens)}")
 
 
 @pytest.mark.parametrize("h,d,rank", [(2048, 192, 128), (192, 2112, 77), (4160, 64, 65)])

@@ -163,6 +163,21 @@ def test_group_with_shared_passes_matches_single_calls(K, h, ds, tokens):
             assert relerr(np64(one["dA"][k]), np64(out["dA"][p][k])) <= 1e-5, (p, k)
 
 
+@pytest.mark.parametrize("P,top", [(2, 32), (2, 64), (2, 128), (3, 32), (3, 64), (4, 32), (4, 64)])
+def test_gradients_of_shared_input_in_every_form(P, top):
+    """All dA_pk from one pass over X (K x h / 128 = 256 blocks): every number of projections with every group of
+    ranks, tasks around whole 64-token tiles and long enough to go round the ring, overwriting and adding."""
+    tokens = [0, 1, 63, 64, 65, 129, 321, 200]
+    ranks = [[top if k == p else 1 + (7 * k + 5 * p) % top for k in range(len(tokens))] for p in range(P)]
+    ins = _group_inputs(sum(tokens) + 9, 4096, [64 + 64 * (p % 2) for p in range(P)], tokens, ranks, torch.bfloat16, lead=5, seed=35)
+    out = run_group(ins)
+    check_group(ins, out, TOL[torch.bfloat16], label=f"group of {P}, ranks up to {top}")
+    acc = run_group(ins, accumulate=True, preset=(0.5, -1.5))
+    for p in range(P):
+        for k in range(len(tokens)):
+            assert torch.equal(acc["dA"][p][k], out["dA"][p][k] + 0.5)
+
+
 def test_group_accumulate_and_skip_dx():
     ins = _group_inputs(384, 128, [192, 64], [128, 0, 200], [[8, 16, 16], [8, 8, 8]], torch.bfloat16, lead=16, seed=3)
     base = run_group(ins)

@@ -106,7 +106,7 @@ def test_short_tasks_keep_one_range(mb):  # noqa: F811
 
 @pytest.mark.parametrize("dtype,case,want", [(t, c, w) for c, w in form_cases.GENERAL for t in ("f32", "bf16")] +
                          form_cases.QUARTERS + form_cases.EDGE_QUARTERS +
-                         [("bf16", c, w) for c, w in form_cases.SPLIT_ROWS + form_cases.WHOLE_TILES] +
+                         [("bf16", c, w) for c, w in form_cases.SPLIT_ROWS + form_cases.WHOLE_TILES + form_cases.LANES] +
                          [(t, c, w) for t, c, w, _ in form_cases.ISOLATION])
 def test_sizes_of_the_gpu_tests_take_their_forms(mb, dtype, case, want):  # noqa: F811
     T, h, d, tokens, ranks, lead = case
