@@ -77,8 +77,10 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
 // every round fills the chip, the others as halves of them with the contraction in `parts` ranges.
 // A launch takes a round of blocks per 256 blocks; the plan with the smallest estimate wins.  The
 // estimates are measured per block and contraction tile of 64 (us): whole tile 10 + 1.3 KT, half tile
-// 12 + 0.78 KT, reduction 4 + 1 per 7 MB of partial tiles (taken before the loads were spread over the tile,
-// which brought both forms down alike: 1.2 and 0.74).  Before (whole tiles only) and after:
+// 12 + 0.78 KT, reduction 4 + 1 per 7 MB of partial tiles, taken before the loads were spread over the tile.  Launches of
+// the present kernels, forward, N(0,1) data, 32 to 256 tiles deep: whole tiles 15 + 1.37 KT for one round, 1.40 KT a round for two
+// and four; half tiles 6 + 0.83 KT for 256 blocks, 4 + 0.70 KT for 176 -- the ratio of the slopes is the same, 1.65.
+// Before (whole tiles only) and after:
 //   T = 100,   4096 x 4096   (16 tiles)        87 ->  28 us with 7 ranges
 //   T = 771,   2048 -> 5632  (88 tiles)        50 ->  38 us as halves
 //              its input gradient (32 tiles)  103 ->  42 us as halves, 3 ranges

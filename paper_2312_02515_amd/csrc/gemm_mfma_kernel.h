@@ -33,7 +33,7 @@
 // its half tile and is re-read in place right behind its last MFMA, a sub-step before its next
 // use.  At most one memory instruction rides behind each MFMA:
 //   sub-steps 0..2 of tile kt: MFMAs | LDS reads of the next sub-step's fragments | the direct loads
-//               of A's tile kt+2
+//               of A's tile kt+2 (three in sub-step 0, one in sub-step 1)
 //   s_waitcnt vmcnt(4), lgkmcnt(0); barrier  (tile kt+1 visible -- the 4 loads still in flight are
 //                                             A's of tile kt+2; every wave holds its last fragments
 //                                             of tile kt in registers: kt's stages are free)
@@ -43,6 +43,11 @@
 // MFMAs take.  All of them behind the barrier, in sub-step 3 (512 cycles of MFMAs), made every wave stand in
 // that queue; spread over the tile, 16384 x 5120 x 5120 takes 562 / 551 us forward / backward instead of
 // 579 / 574, 32768 rows 1131 / 1125 instead of 1180 / 1177, and half tiles 2048 x 11008 -> 4096 137 instead of 150.
+// One shape loses, and on zeros only, where no power cap holds the loop: a contraction 13824 deep into 5120 columns, us
+// per launch of 32768 rows, loads behind the barrier -> spread: zeros 2596 -> 2764 forward, 2600 -> 2810 backward; N(0,1) data 3214
+// -> 3090 and 3170 -> 3100 (every other shape measured, 4096 to 16384 deep, gains 5-25 % on zeros and 1-13 % on data).  It
+// is not A's lead: all four of A's loads in sub-step 0 leave it where it is, and so does one of them behind the
+// barrier (2790-2820 both ways); two behind it bring zeros to 2670 and 2490 and cost most shapes 2-8 % on data.
 // A keeps more than one tile of lead because its rows come from HBM, once per launch: with two stages
 // and one tile of lead the blocks that share a row strip stalled together on every cold line (the time lost grew
 // linearly with the rate at which A is read from HBM, at every shape measured).  Bm, the weight,
@@ -516,7 +521,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   if constexpr (HALF) {
     int total_kt = 0;
     for (int sg = 0; sg < NSEG; ++sg) total_kt += ga.Kd[sg] / BK;
-    // (below 2^32: at most 16 ranges of 4 x 2^25 tiles)
+    // (below 2^32: a contraction has up to 2^22 indices, so 16 ranges of 4 operand pairs of 2^16 tiles make 2^22)
     h0 = (int)((unsigned)total_kt * (unsigned)part / (unsigned)ga.parts);
     h1 = (int)((unsigned)total_kt * (unsigned)(part + 1) / (unsigned)ga.parts);
   }

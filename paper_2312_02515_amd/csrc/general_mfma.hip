@@ -216,8 +216,8 @@ __device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const
 // Bound by the fp32 matrix rate in fp32 (153 TFLOP/s for a large product on this card).  Median and least of
 // 20 traced passes: T = 2048, 4096 x 4096 561 and 513 us forward, 551 and 503 us backward layout (1714 and
 // 1686 us on the vector ALUs; an untraced forward and backward pass takes 1060 us, of which the low-rank
-// launches are 57); T = 1024 300 and 287, 293 and 280 us.  bf16, T = 2048, 4100 x 4100: 171 and 150 us,
-// bound by LDS traffic and the wait for each tile's loads.
+// launches are 57); T = 1024 300 and 287, 293 and 280 us.  bf16, T = 2048, 4100 x 4100, whole tiles and quarters: 113 and
+// 119 us, bound by LDS traffic and the wait for each tile's loads.
 // QUARTERS: tiles of 64 x 64 that are quarters of 128 x 128 tiles.
 template <typename T, int BM, int BN, bool NN, int NSEG, bool QUARTERS>
 __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   int total_kt = 0;
 #pragma unroll
   for (int g = 0; g < NSEG; ++g) total_kt += (a.Kd[g] + BK - 1) / BK;
-  // (the products stay below 2^32: at most 16 parts of 4 x 2^26 tiles)
+  // (below 2^32: a contraction has up to 2^22 indices, so 16 parts of 4 operand pairs of 2^17 tiles make 2^23)
   int p0 = (int)((unsigned)total_kt * (unsigned)part / (unsigned)a.parts);
   int p1 = (int)((unsigned)total_kt * (unsigned)(part + 1) / (unsigned)a.parts);
 
@@ -439,7 +439,7 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
     }
     __syncthreads();
     // bf16 in 64 x 64 tiles: the loop below without its masks and their branches (913 x 1500 x 1000, backward layout
-    // 14.2 -> 13.1 us; 128 x 128 tiles 2-4 % slower with a loop more)
+    // 14.2 -> 13.6 us; 128 x 128 tiles 2-4 % slower with a loop more)
     if constexpr (B16 && BM == 64) {
       for (; kt + 2 < steady; ++kt) {
         const int s = (kt - t0) & 1;
@@ -1041,7 +1041,9 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
 // block do: whole calls, tiles against skinny, 4000 x 2000 outputs 4 deep 11.4 against 22.8 us, 1500 x 2000, 32 deep 7.4
 // against 10.3, 16000 x 100, 100 deep 12.4 against 16.6, but 40000 x 50, 50 deep, rank 64 55 against 41.
 // 128 x 128 tiles once they give every CU a block; below that 64 x 64, the contraction cut into `parts`
-// ranges where that is faster.  A launch costs a CU the tiles of its fullest share, so of the 128 x 128 tiles
+// ranges where that is faster.  (From 193 to 255 tiles of 128 x 128 that line is too high for deep contractions: 64 x 64
+// against 128 x 128, 2050 deep, fp32 216-316 against 212-301 us, bf16 64-90 against 58-76; 1100 deep fp32 level, bf16 up to 9 %; 500
+// deep level to 3 % for 64 x 64.)  A launch costs a CU the tiles of its fullest share, so of the 128 x 128 tiles
 // only whole rounds of 256 need be run as such: the others may run as quarters of 64 x 64, in ranges.  Both
 // choices go by an estimate from measured times per contraction tile (constants below).  Forward, us:
 //   fp32  2048 x 2048 -> 2176 (272 tiles)  248 in whole tiles, 151 as one round and quarters in 8 ranges

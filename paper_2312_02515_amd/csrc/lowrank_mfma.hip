@@ -244,7 +244,7 @@ __global__ __launch_bounds__(TM * 2) void k_lowrank_mfma(const RowsArgs<NP> ra) 
   // whose stage is refilled next.
   int KT = inner / 64;
   if (NP == 1 && ra.splits > 1) {
-    // (below 2^32: at most 16 ranges of 2^25 tiles)
+    // (below 2^32: 16 ranges of a contraction of up to 2^22 indices, 2^16 tiles)
     const int k0 = (int)((unsigned)KT * (unsigned)sp / (unsigned)ra.splits), k1 = (int)((unsigned)KT * (unsigned)(sp + 1) / (unsigned)ra.splits);
 #pragma unroll
     for (int it = 0; it < 4; ++it) xptr[it] += (size_t)k0 * 64;
@@ -1036,7 +1036,7 @@ hipError_t grad_group(const LowrankGroupItem* it, const SegTable& st, const bf16
 }  // namespace
 
 // plan_rows cuts fewer than 256 blocks of 128 rows into at most KT / 4 ranges: up to 8, or (ranks above 64)
-// up to 16 as long as there are no more than 256 blocks
+// up to 16 as long as there are no more than 256 blocks of 128 rows or 512 of 32, which is half as many rows
 size_t rows_partial_bytes(int T, int inner, int ldz) {
   const bool four = nq_of(ldz) == 4;
   const int KT = inner / 64, most = four ? 16 : 8, splits = KT / 4 < most ? KT / 4 : most;

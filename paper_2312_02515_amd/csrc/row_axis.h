@@ -117,7 +117,8 @@ __device__ __forceinline__ int rows_block(const Args& a, int b, int* lo, int* hi
   return k;
 }
 
-// task of row i (off[0] <= i < off[K]); all of a wave's lanes call this with rows in ascending order
+// task of row i (off[0] <= i < off[K]); the first lanes of a wave, or all, call this with rows in ascending order (tasks
+// whose lane has left are not counted by the vote, and the walk behind it goes on from the count)
 template <typename Args>
 __device__ __forceinline__ int task_of_row(const Args& a, int i) {
   int k = 0;
