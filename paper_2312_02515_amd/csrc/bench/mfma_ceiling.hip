@@ -1,10 +1,10 @@
 // Hardware characterisation for the base-product kernel (not a product kernel, not linked into
 // libmlora): what one MI355X sustains on the inner loop of a 256 x 256 x 64 bf16 GEMM tile when
 // the loop's ingredients are added one at a time.  256 blocks of 8 waves (one per CU), wave tile
-// 128 x 64, fp32 accumulators in AccVGPRs updated in place, the same sub-step schedule as
-// k_gemm_mfma (row fragments double-buffered and read one sub-step ahead, weight fragments
-// re-read in place behind their last use, loads behind the MFMAs of the last sub-step, one
-// barrier per tile) -- so every register that an MFMA reads was loaded at least 12 MFMAs earlier
+// 128 x 64, fp32 accumulators in AccVGPRs updated in place, the sub-step schedule that k_gemm_mfma
+// had before it spread A's loads over the first two sub-steps (row fragments double-buffered and read one
+// sub-step ahead, weight fragments re-read in place behind their last use, all loads behind the MFMAs of the
+// last sub-step, one barrier per tile; the present kernel outruns levels 2 to 5 on zeros) -- so every register that an MFMA reads was loaded at least 12 MFMAs earlier
 // and no level stalls on a dependency the real kernel does not have.
 //
 //   level 0  MFMAs on fragments held in registers
@@ -18,7 +18,7 @@
 //            Every XCD walks row strips of its own here, so A leaves HBM at five times the rate of
 //            the GEMM, where the XCDs that work on one row group share its strips through the
 //            Infinity Cache: the level bounds the effect from above
-//   level 5  level 4 with k_gemm_mfma's load order and wait: the weight's loads first, then A's,
+//   level 5  level 4 with that schedule's load order and wait for three A stages: the weight's loads first, then A's,
 //            and the wait in front of the barrier leaves A's four loads in flight -- A has two
 //            tiles of lead over its use (the kernel's three A stages), the weight one
 //

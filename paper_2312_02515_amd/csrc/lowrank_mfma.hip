@@ -528,7 +528,7 @@ constexpr bool grad_pads(int nq, int np, int stages) { return nq == 4 && np == 1
 template <int NQ, int NP, int NS> constexpr int kSmallStage = NQ * 32 * 128 + (grad_pads(NQ, NP, NS) ? 1024 : 0);
 // Three stages (two tiles in flight) where two blocks of them share a CU, and where a CU has no second block to
 // run; two where that is what makes room for the second block (160 KiB of LDS).  us with three and with two stages: ranks above
-// 64, dB and dA, 16384 x 4096 (16 tasks) 89 and 64, 12 tasks of 256 tokens 25 and 19, 64 tasks of 32 tokens 59 and 37, but at
+// 64, dB and dA, 16384 x 4096 (32 tasks) 123 and 90, 8192 x 4096 (16) 63 and 45, 512 x 4096 (12) 25 and 20, but at
 // most 256 blocks: 1024 x 64 (4 tasks) 10.4 and 11.9, 2048 x 1024 (16) 12.1 and 13.2, 16384 x 4096 (4) 73.8 and 75.1;
 // dA of three projections that share X, ranks up to 64, 32768 x 5120 168 and 133.  Where two blocks of three
 // stages fit, two stages lose: 16384 x 4096, ranks up to 64, 53 and 59.
