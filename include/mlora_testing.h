@@ -18,8 +18,8 @@ extern "C" {
 
 /* Selects which kernels the entry points use (bit mask):
  *   0 (default) fastest applicable path: aligned bf16 kernels (with forms of their own for ranks
- *               that are no multiple of 8) when the problem is bf16, h and d are multiples of 64
- *               and all buffers are 16-byte aligned; the general kernels otherwise,
+ *               that are no multiple of 8) when the problem is bf16, h and d are multiples of 64 (the base
+ *               products: of 8) and all buffers are 16-byte aligned; the general kernels otherwise,
  *   bit 0       general kernels for the two base products,
  *   bit 1       general kernels for the low-rank products (3 = general everywhere).
  * Returns the previous value.  Process-wide. */
@@ -40,22 +40,25 @@ int mlora_set_kernel_path(int path);
 #define MLORA_PLAN_GRADS    8  /* dA, dB: token ranges per task                                    */
 #define MLORA_PLAN_FIELDS   9
 #define MLORA_FORM_WHOLE    0  /* aligned: 256 x 256 tiles                                         */
-#define MLORA_FORM_HALVES   1  /* aligned: 128 x 256 tiles                                         */
+#define MLORA_FORM_HALVES   1  /* aligned: smaller tiles, 128 x 256 or (MLORA_PLAN_*_ROWS)
+                                  64 x 64 or 16 x 64                                               */
 #define MLORA_FORM_MIXED    2  /* aligned: whole rounds of the first, the rest as the second       */
-#define MLORA_FORM_SKINNY   3  /* general: 16 x 64                                                 */
-#define MLORA_FORM_64       4  /* general: 64 x 64                                                 */
+#define MLORA_FORM_SKINNY   3  /* features no multiples of 64: 16 x 64                             */
+#define MLORA_FORM_64       4  /* ... or fp32: 64 x 64                                             */
 #define MLORA_FORM_128      5  /* general: 128 x 128; the tiles beyond whole rounds of 256 may run as
                                   quarters of 64 x 64, in the ranges that *_PARTS gives            */
 mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan);
 
 /* The tiles of the two base products in the size that their form names (256 x 256 for the aligned
  * ones): how many run as such, and how many there are -- the others run as halves (HALVES, MIXED) or
- * quarters (128).  `tiles` (HOST, MLORA_PLAN_TILES entries) and the status as for mlora_kernel_plan. */
+ * quarters (128); and the rows of the smallest tiles that run: 256, 128, 64 or 16.  `tiles` (HOST, MLORA_PLAN_TILES entries) and the status as for mlora_kernel_plan. */
 #define MLORA_PLAN_Y_WHOLE  0
 #define MLORA_PLAN_Y_TILES  1
 #define MLORA_PLAN_DX_WHOLE 2
 #define MLORA_PLAN_DX_TILES 3
-#define MLORA_PLAN_TILES    4
+#define MLORA_PLAN_Y_ROWS   4
+#define MLORA_PLAN_DX_ROWS  5
+#define MLORA_PLAN_TILES    6
 mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles);
 
 /* Measurement aid.  While enabled, every launch of the MFMA kernels by this process is bracketed

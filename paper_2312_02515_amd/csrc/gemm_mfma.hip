@@ -8,6 +8,7 @@
 // base product is launched once over all tasks' rows; the output tile is written once with the
 // LoRA term already in it (no full-size intermediate for the LoRA part of dX exists).
 #include "gemm_mfma_kernel.h"
+#include "gemm_ring.h"
 #include "../../include/mlora_testing.h"
 #include "mlora_common.h"
 
@@ -18,7 +19,8 @@ constexpr int BM = 256, BN = gemmk::BN;
 
 }  // namespace
 
-bool gemm_mfma_ok(int M, int N, int Kd) { return M >= 1 && (N % 64) == 0 && (Kd % 64) == 0 && N >= 64 && Kd >= 64; }
+// whole 16-byte chunks in every row
+bool gemm_mfma_ok(int M, int N, int Kd) { return M >= 1 && (N % 8) == 0 && (Kd % 8) == 0 && N >= 8 && Kd >= 8; }
 
 namespace {
 
@@ -96,15 +98,60 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
 // ranks beyond the first 32; and a last round of at most 128 whole tiles takes 0.85 of a full one there.
 // Forward, rank 128: 20000 x 2048 x 2048 195 us in whole tiles (201 as two rounds and halves), 12288 x 512
 // -> 2048 57 (63), 128 x 256 x 256 22.4 (23.8), but 16 x 1024 x 1024 41 us in whole tiles, 25 as halves.
+//
+// Small tiles (gemm_ring_kernel.h), 64 x 64 and of one or two groups of four waves, for up to 64 tiles of 256 x 256.
+// Estimates (us, measured; n tiles of `steps` contraction and LoRA tiles): one group 5 + m (0.9 + 0.19 steps), m tiles on
+// the fullest CU, but 0.25 a step where it has one; two groups, for up to 256 tiles, 6.3 + 0.4 per two steps; the
+// reduction of ranges as above.  Half or whole tiles -> small tiles, forward and backward product, us:
+//   128 rows, 256 -> 256, rank 64   15.5, 14.1 ->  6.7,  6.9     1024 x 1024 -> 1024, rank 64   23.7, 22.0 -> 10.2, 10.4
+//   220 rows, 1920 -> 2688 (10 tasks)  30.2, 26.6 -> 13.0, 14.9     2048 x 1024 -> 1024   24.8, 23.3 -> 12.9, 12.7
+//   1024 x 4096 -> 1024   27.2, 21.7 -> 20.1, 22.6     2048 x 2048 -> 2048   36.0, 33.5 -> 33.3, 32.5
+//   beyond: 3000 x 512 -> 2944  22.7 and 31.8 forward; 771 x 2048 -> 5632  34 and 36.  Where the estimates are level the larger
+//   tiles stay (771 x 5632 -> 2048: level in a loop, 38 us, and 2 % slower behind other launches).
+// Weights of 32 MiB and more, which the L2 caches of the chip do not hold together, keep the larger tiles in ranges, whose plans
+// a test holds (100 x 4096 -> 4096: 25 us, and 19 in small tiles).
+constexpr int kSmallTiles = 64;
 struct Plan {
   int whole, parts;
+  int small;          // groups of four waves per 64 x 64 tile; 0: 256 x 256 tiles and halves
 };
 constexpr int kMaxParts = 16;
-// (`pairs` operand pairs of Kd contraction indices in all)
-Plan plan_gemm(const SegTable& st, int M, int N, int Kd, int pairs, size_t scratch_limit) {
+constexpr size_t kSmallWeight = (size_t)32 << 20;
+// the fewest us of a product in small tiles, and its plan
+double plan_small(const SegTable& st, int M, int N, int KT, int pairs, size_t scratch_limit, Plan* out) {
+  const long long n = (virtual_rows(st, M) + 63) / 64 * ((N + 63) / 64);
+  // LoRA tiles of a block: two slots of 32 ranks each, for one or two tasks
+  int slots = 0, live = 0;
+  for (int k = 0; k < st.K; ++k) {
+    if (st.off[k + 1] == st.off[k]) continue;
+    ++live;
+    const int r = (st.rank[k] + 31) / 32;
+    slots = r > slots ? r : slots;
+  }
+  const bool shared = live > 1 && (long long)(st.off[st.K] - st.off[0]) < 64LL * live;   // most tiles hold two tasks
+  const int lora = pairs * (shared ? slots : (slots + 1) / 2);
+  double best = 0;
+  for (int p = 1; p <= kMaxParts && 2 * p <= KT + 1; ++p) {
+    const size_t bytes = p > 1 ? (size_t)n * p * 64 * 64 * sizeof(float) : 0;
+    if (bytes > scratch_limit) break;
+    const int steps = (KT + p - 1) / p + lora;
+    const double m = n * p <= 768 ? (double)((n * p + 255) / 256) : (double)(n * p) / 256.0;
+    const double us = 5.0 + m * (0.9 + (m > 1 ? 0.19 : 0.25) * steps) + (p > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
+    if (p == 1 || us < best) {
+      best = us;
+      *out = Plan{0, p, 1};
+    }
+    if (p == 1 && n <= 256 && pairs == 1 && 6.3 + 0.4 * ((steps + 1) / 2) < best) {
+      best = 6.3 + 0.4 * ((steps + 1) / 2);
+      *out = Plan{0, 1, 2};
+    }
+  }
+  return best;
+}
+// (`pairs` operand pairs of Kd contraction indices in all; KT contraction tiles)
+Plan plan_gemm(const SegTable& st, int M, int N, int KT, int pairs, size_t scratch_limit) {
   const int tiles_m = (int)((virtual_rows(st, M) + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
   const int total = tiles_m * tiles_n, q = total / 256 * 256, halves = 2 * (total - q);
-  const int KT = Kd / 64;
   // tasks of a tile beyond the first: the most of any tile where a tile's time shows, on average in several
   // rounds
   int live = 0, rmax = 0, most_whole = 0, most_half = 0;
@@ -141,7 +188,7 @@ Plan plan_gemm(const SegTable& st, int M, int N, int Kd, int pairs, size_t scrat
     const double part = last == 0 ? 0.0 : (tiles > 256 && last <= 128 ? 0.85 : 1.0);
     return (tiles / 256 + part) * (whole_fixed + 1.3 * KT);
   };
-  Plan best{total, 1};
+  Plan best{total, 1, 0};
   double best_us = whole_us(total);
   for (int parts = 1; halves > 0 && parts <= kMaxParts && parts <= KT; ++parts) {
     const size_t bytes = parts > 1 ? (size_t)halves * parts * (BM / 2) * BN * sizeof(float) : 0;
@@ -150,10 +197,20 @@ Plan plan_gemm(const SegTable& st, int M, int N, int Kd, int pairs, size_t scrat
                       (parts > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
     if (us < best_us) {
       best_us = us;
-      best = Plan{q, parts};
+      best = Plan{q, parts, 0};
     }
   }
+  Plan small;
+  if (total <= kSmallTiles && (size_t)N * KT * 64 * sizeof(bf16) < kSmallWeight &&
+      plan_small(st, M, N, KT, pairs, scratch_limit, &small) < 0.93 * best_us)
+    return small;
   return best;
+}
+
+// The smallest problems run k_gen_skinny (16 x 64 tiles, operands straight from memory): 128 rows 256 -> 256, rank 64 4.9
+// and 5.1 us, in 64 x 64 tiles 6.7 and 6.9; 128 x 1024 -> 256 6.7 and 5.2, 9.4 and 6.6; 1024 x 64 -> 1024 6.4 and 8.6, 6.3 and 9.0.
+bool skinny(const SegTable& st, int M, int N, long long Kd) {
+  return (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN) <= kSmallTiles && general_skinny(st, M, N, Kd, MLORA_BF16);
 }
 
 template <int NSEG>
@@ -171,13 +228,21 @@ void fill_common(gemmk::GemmArgs<NSEG>* a, bf16* C, int M, int N, const SegTable
 }
 
 template <bool NN, int NSEG>
-hipError_t launch(gemmk::GemmArgs<NSEG>& a, int Kd_total, float* scratch, size_t scratch_bytes, const SegTable& st,
+hipError_t launch(gemmk::GemmArgs<NSEG>& a, float* scratch, size_t scratch_bytes, const SegTable& st,
                   hipStream_t stream) {
-  const Plan pl = plan_gemm(st, a.M, a.N, Kd_total, NSEG, scratch_bytes);
+  int kt = 0;
+  for (int g = 0; g < NSEG; ++g) kt += (a.Kd[g] + 63) / 64;
+  const Plan pl = plan_gemm(st, a.M, a.N, kt, NSEG, scratch_bytes);
   a.t0 = pl.whole;
   a.parts = pl.parts;
   a.part = scratch;
   const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
+  if (pl.small > 0) {
+    launch_ring<NSEG>(a, st, NN, pl.small, pl.parts, scratch, stream);
+    const hipError_t e = hipGetLastError();
+    profile_end(slot, stream);
+    return e;
+  }
   if (pl.whole > 0) launch_whole<NN, NSEG>(a, pl.whole, stream);
   if (pl.whole < a.tiles_m * a.tiles_n) launch_halves<NN, NSEG>(a, stream);
   const hipError_t err = hipGetLastError();
@@ -190,18 +255,16 @@ hipError_t launch_sum(const GemmOperands* ops, bf16* C, int M, int N, const SegT
                       hipStream_t stream) {
   gemmk::GemmArgs<NSEG> a;
   fill_common(&a, C, M, N, st);
-  int kd = 0;
   for (int g = 0; g < NSEG; ++g) {
     a.A[g] = ops[g].A;
     a.Bm[g] = ops[g].Bm;
     a.L[g] = ops[g].L;
     a.Kd[g] = ops[g].Kd;
-    kd += ops[g].Kd;
     a.ldz[g] = ops[g].ldz;
     for (int k = 0; k < kMaxK; ++k) a.rank[g][k] = (unsigned char)(k < st.K ? ops[g].rank[k] : 0);
     a.R[g] = *ops[g].R;
   }
-  return launch<false, NSEG>(a, kd, scratch, scratch_bytes, st, stream);
+  return launch<false, NSEG>(a, scratch, scratch_bytes, st, stream);
 }
 
 }  // namespace
@@ -209,6 +272,10 @@ hipError_t launch_sum(const GemmOperands* ops, bf16* C, int M, int N, const SegT
 // C[M,N] = A[M,Kd] * (nn ? Bm[Kd,N] : Bm[N,Kd]^T) + rows_k( L[rows_k, :r_k] * (nn ? R_k[r_k,N] : R_k[N,r_k]^T) )
 hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, bool nn, const bf16* L, int ldz,
                      const SegTable& st, const PtrTable& R, float* scratch, size_t scratch_bytes, hipStream_t stream) {
+  if (skinny(st, M, N, Kd)) {
+    const GenOperands o{A, Bm, L, Kd, ldz, st.rank, &R};
+    return general_gemm(1, &o, MLORA_BF16, C, M, N, nn, st, scratch, scratch_bytes, stream);
+  }
   gemmk::GemmArgs<1> a;
   fill_common(&a, C, M, N, st);
   a.A[0] = A;
@@ -218,15 +285,16 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
   a.ldz[0] = ldz;
   for (int k = 0; k < kMaxK; ++k) a.rank[0][k] = (unsigned char)(k < st.K ? st.rank[k] : 0);
   a.R[0] = R;
-  return nn ? launch<true, 1>(a, Kd, scratch, scratch_bytes, st, stream)
-            : launch<false, 1>(a, Kd, scratch, scratch_bytes, st, stream);
+  return nn ? launch<true, 1>(a, scratch, scratch_bytes, st, stream)
+            : launch<false, 1>(a, scratch, scratch_bytes, st, stream);
 }
 
 GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_bytes) {
-  const Plan pl = plan_gemm(st, M, N, Kd, 1, scratch_bytes);
   const long long total = (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN);
+  if (skinny(st, M, N, Kd)) return GemmForm{MLORA_FORM_HALVES, 1, 0, (int)total, 16};
+  const Plan pl = plan_gemm(st, M, N, (Kd + 63) / 64, 1, scratch_bytes);
   const int form = pl.whole == total ? MLORA_FORM_WHOLE : (pl.whole == 0 ? MLORA_FORM_HALVES : MLORA_FORM_MIXED);
-  return GemmForm{form, pl.parts, pl.whole, (int)total};
+  return GemmForm{form, pl.parts, pl.whole, (int)total, form == MLORA_FORM_WHOLE ? BM : (pl.small > 0 ? 64 : BM / 2)};
 }
 
 size_t gemm_partial_bytes(int K, int T, int N, int Kd) {
@@ -238,6 +306,15 @@ size_t gemm_partial_bytes(int K, int T, int N, int Kd) {
 // C[M,N] = sum_g ( A_g[M,Kd_g] * Bm_g[N,Kd_g]^T + rows_k( L_g[rows_k, :r_gk] * R_gk[N,r_gk]^T ) ), 1 <= n <= 4
 hipError_t gemm_mfma_sum_nt(int n, const GemmOperands* ops, bf16* C, int M, int N, const SegTable& st, float* scratch,
                             size_t scratch_bytes, hipStream_t stream) {
+  long long kd = 0;
+  GenOperands o[MLORA_MAX_GROUP];
+  if (n < 1 || n > MLORA_MAX_GROUP) return hipErrorInvalidValue;
+  for (int g = 0; g < n; ++g) {
+    kd += ops[g].Kd;
+    o[g] = GenOperands{ops[g].A, ops[g].Bm, ops[g].L, ops[g].Kd, ops[g].ldz, ops[g].rank, ops[g].R};
+  }
+  if (skinny(st, M, N, kd))
+    return general_gemm(n, o, MLORA_BF16, C, M, N, false, st, scratch, scratch_bytes, stream);
   switch (n) {
     case 1: return launch_sum<1>(ops, C, M, N, st, scratch, scratch_bytes, stream);
     case 2: return launch_sum<2>(ops, C, M, N, st, scratch, scratch_bytes, stream);

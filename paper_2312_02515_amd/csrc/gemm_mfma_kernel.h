@@ -101,8 +101,51 @@ struct GemmArgs {
 
 // 16 zero bytes in device memory: where the lanes of a LoRA tile point whose row, column or rank
 // index lies outside the task (a direct-to-LDS load cannot be masked)
-__device__ uint4 g_zero_chunk;
+static __device__ uint4 g_zero_chunk;
 
+
+// r_gk: a dword read (a byte at a run-time index would be a vector load)
+template <int NSEG>
+__device__ __forceinline__ int rank_of(const GemmArgs<NSEG>& a, int sg, int k) {
+  static_assert(offsetof(GemmArgs<NSEG>, rank) % 4 == 0, "read as dwords");
+  return (int)(reinterpret_cast<const unsigned*>(a.rank[sg])[k >> 2] >> (8 * (k & 3))) & 255;
+}
+
+// The LoRA term's contraction tiles.  A slot is 32 ranks of one (operand pair, task of the block); a LoRA tile holds two
+// slots, one in each half of its 64 contraction indices, and a piece of rows takes part in the halves of its own task
+// only.  Lane t of the table keeps tile t's two slots (the most is 4 pairs x 8 pieces x 4 slots = 64 tiles): 16 bits
+// each, task in 7 (127: none), pair in 2, first rank / 32 in 2.
+struct LoraTiles {
+  unsigned tab;
+  int n;
+};
+struct LoraSlot {
+  int sg, k, q0;
+};
+constexpr unsigned kNoSlot = 127;
+__device__ __forceinline__ LoraSlot lora_slot(const LoraTiles& t, int tile, int half) {
+  const unsigned v = (unsigned)__builtin_amdgcn_readlane((int)t.tab, __builtin_amdgcn_readfirstlane(tile)) >> (16 * half);
+  return LoraSlot{(int)(v >> 7 & 3), (int)(v & 127), (int)(v >> 9 & 3) * 32};
+}
+// `task(f)`: task of the block's piece f (-1: none); the pieces of a task are consecutive
+template <int NFR, int NSEG, typename F>
+__device__ __forceinline__ LoraTiles lora_tiles(const GemmArgs<NSEG>& a, F task) {
+  const int lane = threadIdx.x & 63;
+  LoraTiles t{kNoSlot | kNoSlot << 16, 0};
+  int e = 0;
+  for (int sg = 0; sg < NSEG; ++sg)
+    for (int f = 0; f < NFR; ++f) {
+      const int k = task(f);
+      if (k < 0 || (f > 0 && task(f - 1) == k)) continue;
+      const int r = rank_of(a, sg, k);
+      for (int q = 0; 32 * q < r; ++q, ++e) {
+        const unsigned v = (unsigned)k | (unsigned)sg << 7 | (unsigned)q << 9;
+        if (lane == e >> 1) t.tab = e & 1 ? (t.tab & 0xffffu) | v << 16 : (t.tab & 0xffff0000u) | v;
+      }
+    }
+  t.n = (e + 1) / 2;
+  return t;
+}
 
 // c += a x b on a 16 x 16 x 32 bf16 MFMA, accumulating in place in AccVGPRs.  Written as inline
 // assembly with the accumulator as a tied operand: with the builtin the register allocator is
@@ -326,109 +369,117 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     af[i] = *(const bf16x8*)(sa + a_row_off + (h * HM + i) * 16 * ROWB + (((4 * q + kg) ^ fsw) << 4));
   };
 
-  // ---- LoRA contraction tiles.  After the last operand pair's base tiles the same pipeline
-  // runs one more tile per (task k that owns rows of this block, 64 ranks of it): its A side is
-  // the task's slice of L (Z or G; zeros for the other pieces), its B side the same ranks of R_k
-  // (B_k or A_k), fetched into the same LDS layouts by the same direct loads two tiles ahead --
-  // so the LoRA term costs ceil(r_k / 64) more tiles on the same accumulators and no exposed
-  // load latency.  The pieces of one task are consecutive, so the block's tasks are the runs of
-  // the task column of the piece table.
-  struct LoraTile {
-    int sg, k, q0;
-  };
-  int n_lora = 0;
-  if constexpr (!HALF)
-    for (int sg = 0; sg < NSEG; ++sg)
-      for (int f = 0; f < NFR; ++f) {
-        const int k = frag_task(f);
-        if (k >= 0 && (f == 0 || frag_task(f - 1) != k)) n_lora += (ga.rank[sg][k] + BK - 1) / BK;
-      }
-  auto find_lora = [&](int e) {
-    LoraTile t{0, -1, 0};
-    for (int sg = 0; sg < NSEG; ++sg)
-      for (int f = 0; f < NFR; ++f) {
-        const int k = frag_task(f);
-        if (k < 0 || (f > 0 && frag_task(f - 1) == k)) continue;
-        const int nch = (ga.rank[sg][k] + BK - 1) / BK;
-        if (e >= 0 && e < nch) t = LoraTile{sg, k, e * BK};
-        e -= nch;
-      }
-    return t;
-  };
-  // what the load slots of a tile fetch: base tile kt of the current operand pair, or a LoRA tile
+  // ---- LoRA contraction tiles.  After the last operand pair's base tiles the same pipeline runs the tiles of `lora`: the
+  // A side is the tasks' slices of L (Z or G; zeros for the other pieces), the B side the same ranks of R_k (B_k
+  // or A_k), fetched into the same LDS layouts by the same direct loads two tiles ahead, so the LoRA term
+  // costs ceil(r_k / 32) more half tiles on the same accumulators and no exposed load latency.
+  LoraTiles lora{0, 0};
+  if constexpr (!HALF) lora = lora_tiles<NFR>(ga, [&](int f) { return frag_task(f); });
+  // what the load slots of a tile fetch: base tile kt of the current operand pair, or a LoRA tile.
+  // `left`: contraction indices of the tile, fewer than 64 in the last one of features that are no multiple of 64
   struct LoadCtx {
     bool lora;
     const char* atile;
     const char* btile;
-    LoraTile lt;
+    int lt;              // which LoRA tile
+    int left, Kd;
   };
   auto base_ctx = [&](int kt) {
-    return LoadCtx{false, abase + (size_t)kt * (BK * 2), bbase + (size_t)kt * bstep, LoraTile{0, -1, 0}};
+    return LoadCtx{false, abase + (size_t)kt * (BK * 2), bbase + (size_t)kt * bstep, 0, BK, 0};
   };
   const char* const zeros = reinterpret_cast<const char*>(&g_zero_chunk);
-  // wave-wide load number idx (0..LPA-1: A side, LPA..PER_TILE-1: Bm side) of the tile `lc` describes
+  // wave-wide load number idx (0..LPA-1: A side, LPA..PER_TILE-1: Bm side) of a base tile that needs no masks
   auto issue_one = [&](const LoadCtx& lc, int idx, char* sa, char* sb) {
-    if (HALF || !lc.lora) {
-      if (idx < LPA)
-        load_lds_16B_sbase(lc.atile, aoff[idx], sa + (wave + NW * idx) * 1024);
-      else
-        load_lds_16B_sbase(lc.btile, boff[idx - LPA], sb + (wave + NW * (idx - LPA)) * 1024);
-      return;
+    if (idx < LPA)
+      load_lds_16B_sbase(lc.atile, aoff[idx], sa + (wave + NW * idx) * 1024);
+    else
+      load_lds_16B_sbase(lc.btile, boff[idx - LPA], sb + (wave + NW * (idx - LPA)) * 1024);
+  };
+  // One side of a partial or LoRA tile.  The loops are rolled: this code stands in every launch's path, where it is
+  // fetched cold, and runs a few times at most.
+  auto masked = [](const LoadCtx& lc) { return lc.lora || lc.left < BK; };
+  // (the chunk a lane fetches: the same in every load of a wave, the rows of two loads are a multiple of 16 apart)
+  const int kchunk = (lane % CPR) ^ ((RPI * wave + lane / CPR) / RW % CPR);
+  static_assert(RPI * NW % (RW * CPR) == 0, "chunk of a lane");
+  auto issue_masked_a = [&](const LoadCtx& lc, char* sa) {
+    const int h = kchunk >> 2;                     // (LoRA: the half of the tile, i.e. the slot)
+    const char* base = lc.atile;
+    int ld = lc.Kd, q = kchunk * 8, end = lc.left, task = -1;
+    if (!HALF && lc.lora) {
+      const LoraSlot s0 = lora_slot(lora, lc.lt, 0), s1 = lora_slot(lora, lc.lt, 1);
+      const int l0 = ga.ldz[s0.sg], l1 = ga.ldz[s1.sg];
+      const bf16 *p0 = ga.L[s0.sg], *p1 = ga.L[s1.sg];
+      base = reinterpret_cast<const char*>(h ? p1 : p0);
+      ld = end = h ? l1 : l0;
+      q = (h ? s1.q0 : s0.q0) + (kchunk & 3) * 8;
+      task = h ? s1.k : s0.k;
     }
-    const LoraTile& t = lc.lt;
-    if (idx < LPA) {
-      const bf16* L = ga.L[t.sg];
-      const int ldz = ga.ldz[t.sg];
-      const int w = wave + NW * idx;
+#pragma clang loop unroll(disable)
+    for (int it = 0; it < LPA; ++it) {
+      const int w = wave + NW * it;
       const int rl = RPI * w + lane / CPR;
-      const int c = (lane % CPR) ^ ((rl / RW) % CPR);
-      const int q = t.q0 + c * 8;
-      const bool mine = frag_task(rl >> 5) == t.k;  // wave-uniform: the 8 rows of this load share a piece
-      const char* p = (mine && q < ldz) ? reinterpret_cast<const char*>(L + (size_t)real_row(rl) * ldz + q) : zeros;
-      load_lds_16B(p, sa + w * 1024);
-    } else {
-      const int r = ga.rank[t.sg][t.k];
-      const bf16* Rk = static_cast<const bf16*>(ga.R[t.sg].p[t.k]);
-      const int w = wave + NW * (idx - LPA);
+      // (a LoRA tile: the rows of its tasks)
+      const bool in = q < end && (HALF || !lc.lora || frag_task(rl >> 5) == task);
+      const int row = !HALF && lc.lora ? real_row(rl) : real_row(rl) - row0;
+      load_lds_16B(in ? base + ((size_t)row * ld + q) * 2 : zeros, sa + w * 1024);
+    }
+  };
+  auto issue_masked_b = [&](const LoadCtx& lc, char* sb) {
+    const char *p0 = lc.btile, *p1 = lc.btile;
+    int r0 = lc.left, r1 = lc.left, q0 = 0, q1 = 32;   // contraction indices that exist, first of each half
+    if (!HALF && lc.lora) {
+      const LoraSlot s0 = lora_slot(lora, lc.lt, 0), s1 = lora_slot(lora, lc.lt, 1);
+      r0 = rank_of(ga, s0.sg, s0.k & 63);
+      p0 = static_cast<const char*>(ga.R[s0.sg].p[s0.k & 63]) + (size_t)col0 * 2 * (NN ? 1 : r0);
+      q0 = s0.q0;
+      r1 = rank_of(ga, s1.sg, s1.k & 63);
+      p1 = static_cast<const char*>(ga.R[s1.sg].p[s1.k & 63]) + (size_t)col0 * 2 * (NN ? 1 : r1);
+      q1 = s1.q0;
+      if (s1.k == (int)kNoSlot) r1 = 0;
+    }
+    // (NT: a lane's half is that of its chunk; NN: a load's rows lie in one half)
+    const int ch = kchunk >> 2, cr = ch ? r1 : r0, cq = (ch ? q1 : q0) + (kchunk & 3) * 8;
+    const char* const cp = ch ? p1 : p0;
+#pragma clang loop unroll(disable)
+    for (int it = 0; it < LPB; ++it) {
+      const int w = wave + NW * it;
       const char* p = zeros;
       if (NN) {
-        const int kr = 2 * w + (lane >> 5);
-        const int c = (lane & 31) ^ nn_swz(kr);
-        const int q = t.q0 + kr, n = col0 + c * 8;
-        if (q < r && n < N) p = reinterpret_cast<const char*>(Rk + (size_t)q * N + n);
+        const int kr = 2 * w + (lane >> 5), n = ((lane & 31) ^ nn_swz(kr)) * 8;
+        const bool hi = w >= 16;
+        const int q = (hi ? q1 - 32 : q0) + kr;
+        if (q < (hi ? r1 : r0) && col0 + n < N) p = (hi ? p1 : p0) + ((size_t)q * N + n) * 2;
       } else {
         const int rl = RPI * w + lane / CPR;
-        const int c = (lane % CPR) ^ ((rl / RW) % CPR);
-        const int n = col0 + rl, q = t.q0 + c * 8;
         if constexpr (RAG) {
-          if (r % 8 != 0) {
+          if (lc.lora && ((r0 | r1) & 7) != 0) {
+            const bf16* row = reinterpret_cast<const bf16*>(cp) + (size_t)rl * cr;
             bf16x8 v;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = (n < N && q + e < r) ? Rk[(size_t)n * r + q + e] : (bf16)0.f;
+            for (int e = 0; e < 8; ++e) v[e] = (col0 + rl < N && cq + e < cr) ? row[cq + e] : (bf16)0.f;
             *(bf16x8*)(sb + w * 1024 + lane * 16) = v;
-            return;
+            continue;
           }
         }
-        if (n < N && q < r) p = reinterpret_cast<const char*>(Rk + (size_t)n * r + q);
+        if (col0 + rl < N && cq < cr) p = cp + ((size_t)rl * (!HALF && lc.lora ? cr : lc.Kd) + cq) * 2;
       }
       load_lds_16B(p, sb + w * 1024);
     }
   };
 
-  // Which of the wave's WM / 32 pieces take part in a tile: all of them in a base tile, the
-  // pieces of task k in a LoRA tile of task k (the others' MFMAs are skipped).
-  // `q1`: whether the second half of the tile's 64 contraction indices holds anything -- a LoRA
-  // tile whose remaining ranks are at most 32 (rank 8, 16, 32: most adapters) runs the MFMAs of
-  // its first half only (the other half of the staged operands is zeros).
+  // Which of the wave's WM / 32 pieces take part in each half of a tile: all of them in a base tile, the pieces of
+  // the half's task in a LoRA tile (the others' MFMAs are skipped, and those of an empty slot).
   struct FragOn {
-    bool on[WM / 32];
-    bool q1;
+    bool on[2][WM / 32];
   };
-  auto frags_of = [&](const LoraTile& t, bool base) {
+  auto frags_of = [&](int lt, bool base) {
     FragOn f;
 #pragma unroll
-    for (int i = 0; i < WM / 32; ++i) f.on[i] = base || frag_task(wm * (WM / 32) + i) == t.k;
-    f.q1 = base || (int)ga.rank[t.sg][t.k < 0 ? 0 : t.k] - t.q0 > 32;
+    for (int q = 0; q < 2; ++q) {
+      const int k = base ? 0 : lora_slot(lora, lt, q).k;
+#pragma unroll
+      for (int i = 0; i < WM / 32; ++i) f.on[q][i] = base || frag_task(wm * (WM / 32) + i) == k;
+    }
     return f;
   };
 
@@ -454,7 +505,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     for (int m = 0; m < NMF; ++m) {
       const int j = m / HM, i = m % HM;
       bool on = true;
-      if constexpr (!std::is_same_v<std::decay_t<decltype(fo)>, std::true_type>) on = fo.on[(h * HM + i) / 2] && (q == 0 || fo.q1);
+      if constexpr (!std::is_same_v<std::decay_t<decltype(fo)>, std::true_type>) on = fo.on[q][(h * HM + i) / 2];
       if (on) mfma_16x16x32(acc[h * HM + i][j], bfr[j], af[h][i]);
       if (rd && m < HM) read_a(rsa, nq, nh, m, af[nh]);
       if (rd && h == 1 && i == HM - 1) read_b(rsb, nq, j);
@@ -468,7 +519,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   constexpr std::integral_constant<int, 1> S1{};
   constexpr std::integral_constant<int, 2> S2{};
   constexpr std::integral_constant<int, 3> S3{};
-  const LoadCtx none{false, nullptr, nullptr, LoraTile{0, -1, 0}};
+  const LoadCtx none{false, nullptr, nullptr, 0, BK, 0};
 
   // A tile whose operands sit in (ca, cb): sub-steps 0..2 with the late loads of `lcl` into lsl (if ldl; whole
   // tiles: the A side of tile v + 2, half tiles: its Bm side), barrier, sub-step 3 with the reads of the next
@@ -483,22 +534,26 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
                     (L1 == 0 || (L1 - 1) * L1_GAP < (FN - 1) * (HM - 1)) && (L2 == 0 || (L2 - 1) * L1_GAP < (FN - 1) * HM),
                 "load slots");
   auto tile = [&](char* ca, char* cb, const char* na, const char* nb, auto rd, auto ldl, const LoadCtx& lcl, char* lsl,
-                  auto lde, const LoadCtx& lce, auto behind, const auto& fo) {
+                  auto lde, const LoadCtx& lce, auto behind, const auto& fo, char* lsa = nullptr) {
     // load `first` + n / gap of the side in every gap-th slot
     auto late = [&](int slot, int first, int count, int gap) {
-      if (!ldl || slot % gap != 0 || slot / gap >= count) return;
+      if (!ldl || slot % gap != 0 || slot / gap >= count || masked(lcl)) return;
       if constexpr (HALF)
         issue_one(lcl, LPA + first + slot / gap, nullptr, lsl);
       else
         issue_one(lcl, first + slot / gap, lsl, nullptr);
     };
     auto early = [&](int slot) {
-      if (!lde || slot % E_GAP != 0 || slot / E_GAP >= EARLY) return;
+      if (!lde || slot % E_GAP != 0 || slot / E_GAP >= EARLY || masked(lce)) return;
       if constexpr (HALF)
         issue_one(lce, slot / E_GAP, ca, nullptr);
       else
         issue_one(lce, LPA + slot / E_GAP, nullptr, cb);
     };
+    if (ldl && masked(lcl)) {
+      issue_masked_a(lcl, HALF ? lsa : lsl);
+      if constexpr (HALF) issue_masked_b(lcl, lsl);
+    }
     substep(S0, yes, ca, cb, [&](int slot) { late(slot, 0, L0, L0_GAP); }, fo);
     substep(S1, yes, ca, cb, [&](int slot) { late(slot, L0, L1, L1_GAP); }, fo);
     substep(S2, yes, ca, cb, [&](int slot) { late(slot, L0 + L1, L2, L1_GAP); }, fo);
@@ -510,6 +565,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       wait_vmcnt<0>();
     wait_lds();
     __builtin_amdgcn_s_barrier();
+    if constexpr (!HALF) {
+      if (lde && masked(lce)) issue_masked_b(lce, cb);
+    }
     substep(S3, rd, na, nb, early, fo);
   };
 
@@ -520,53 +578,61 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   int h0 = 0, h1 = 0;   // HALF: this block's range of the base tiles of all operand pairs
   if constexpr (HALF) {
     int total_kt = 0;
-    for (int sg = 0; sg < NSEG; ++sg) total_kt += ga.Kd[sg] / BK;
+    for (int sg = 0; sg < NSEG; ++sg) total_kt += (ga.Kd[sg] + BK - 1) / BK;
     // (below 2^32: a contraction has up to 2^22 indices, so 16 ranges of 4 operand pairs of 2^16 tiles make 2^22)
     h0 = (int)((unsigned)total_kt * (unsigned)part / (unsigned)ga.parts);
     h1 = (int)((unsigned)total_kt * (unsigned)(part + 1) / (unsigned)ga.parts);
   }
   for (int sg = 0; sg < NSEG; ++sg) {
-    int KT = ga.Kd[sg] / BK, k0 = 0;
+    const int last = ga.Kd[sg] % BK;         // contraction indices of a last, partial tile (0: none)
+    int KT = ga.Kd[sg] / BK, k0 = 0;         // whole base tiles of this pass
+    int base_tiles = KT + (last != 0);
     if constexpr (HALF) {
-      const int lo = h0 > 0 ? h0 : 0, hi = h1 < KT ? h1 : KT;
-      h0 -= KT;
-      h1 -= KT;
+      const int all = base_tiles, lo = h0 > 0 ? h0 : 0, hi = h1 < all ? h1 : all;
+      h0 -= all;
+      h1 -= all;
       if (lo >= hi) continue;
       k0 = lo;
-      KT = hi - lo;
+      KT = (hi < KT ? hi : KT) - lo;
+      base_tiles = hi - lo;
     }
     set_operands(ga.A[sg], ga.Bm[sg], ga.Kd[sg]);
     abase += (size_t)k0 * (BK * 2);
     bbase += (size_t)k0 * bstep;
-    const int lora_tiles = !HALF && sg == NSEG - 1 ? n_lora : 0;
-    const int VT = KT + lora_tiles;  // tiles of this pass: base tiles, then LoRA tiles
+    const int VT = base_tiles + (!HALF && sg == NSEG - 1 ? lora.n : 0);  // tiles of this pass: base tiles, then LoRA tiles
     auto ctx_of = [&](int v) {
-      if (HALF || v < KT) return base_ctx(v);
-      return LoadCtx{true, nullptr, nullptr, find_lora(v - KT)};
+      LoadCtx lc = base_ctx(v);
+      lc.Kd = ga.Kd[sg];
+      if (!HALF && v >= base_tiles) lc = LoadCtx{true, nullptr, nullptr, v - base_tiles, BK, 0};
+      else if (v >= KT) lc.left = last;
+      return lc;
     };
     auto issue_a = [&](const LoadCtx& lc, char* sa) {
+      if (masked(lc)) return issue_masked_a(lc, sa);
 #pragma unroll
       for (int idx = 0; idx < LPA; ++idx) issue_one(lc, idx, sa, nullptr);
     };
     auto issue_b = [&](const LoadCtx& lc, char* sb) {
+      if (masked(lc)) return issue_masked_b(lc, sb);
 #pragma unroll
       for (int idx = 0; idx < LPB; ++idx) issue_one(lc, LPA + idx, nullptr, sb);
     };
+    auto stage_a = [&](int u) { return u % 3 == 0 ? sA0 : (u % 3 == 1 ? sA1 : sA2); };
+    auto stage_b = [&](int u) {
+      if constexpr (HALF) return u % 3 == 0 ? sB0 : (u % 3 == 1 ? sB1 : sB2);
+      else return u % 2 == 0 ? sB0 : sB1;
+    };
     // whole tiles: tiles 0 and 1.  HALF: also the A side of tile 2.  The first reads need tile 0
-    issue_a(base_ctx(0), sA[0]);
-    issue_b(base_ctx(0), sB[0]);
-    if (VT > 1) {
-      issue_a(ctx_of(1), sA[1]);
-      issue_b(ctx_of(1), sB[1]);
-      if (HALF && VT > 2) {
-        issue_a(ctx_of(2), sA[2]);
-        wait_vmcnt<PER_TILE + LPA>();
-      } else {
-        wait_vmcnt<PER_TILE>();
-      }
-    } else {
-      wait_vmcnt<0>();
+#pragma unroll(HALF ? 3 : 1)
+    for (int t = 0; t < (HALF ? 3 : 2); ++t) {
+      if (t >= VT) break;
+      const LoadCtx lc = ctx_of(t);
+      issue_a(lc, stage_a(t));
+      if (t < 2) issue_b(lc, stage_b(t));
     }
+    if (VT > 2 && HALF) wait_vmcnt<PER_TILE + LPA>();
+    else if (VT > 1) wait_vmcnt<PER_TILE>();
+    else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int j = 0; j < FN; ++j) read_b(sB[0], 0, j);
@@ -583,27 +649,22 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       tile(sA[1], sB[0], sA[2], sB[1], yes, yes, base_ctx(v + 6), sA[0], yes, base_ctx(v + 6), yes, yes);
       tile(sA[2], sB[1], sA[0], sB[0], yes, yes, base_ctx(v + 7), sA[1], yes, base_ctx(v + 7), yes, yes);
     }
-    auto stage_a = [&](int u) { return u % 3 == 0 ? sA0 : (u % 3 == 1 ? sA1 : sA2); };
-    auto stage_b = [&](int u) {
-      if constexpr (HALF) return u % 3 == 0 ? sB0 : (u % 3 == 1 ? sB1 : sB2);
-      else return u % 2 == 0 ? sB0 : sB1;
-    };
     for (; v + 3 < KT; ++v)
       tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), yes, yes, base_ctx(v + 2), HALF ? stage_b(v + 2) : stage_a(v + 2), yes,
            base_ctx(HALF ? v + 3 : v + 2), yes, yes);
-    if constexpr (HALF) {
-      // (the last three: tile VT - 1's weight is the last load)
-      for (; v < VT; ++v)
-        tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, base_ctx(v + 2), stage_b(v + 2), no,
-             none, v + 2 < VT, yes);
-      continue;
-    }
     // the last base tiles and the LoRA tiles
-    auto frags_at = [&](int u) { return u < KT ? frags_of(LoraTile{0, -1, 0}, true) : frags_of(find_lora(u - KT), false); };
+    auto frags_at = [&](int u) {
+      return u < base_tiles ? frags_of(0, true) : frags_of(u - base_tiles, false);
+    };
     for (; v < VT; ++v) {
       const LoadCtx lc = v + 2 < VT ? ctx_of(v + 2) : none;
-      tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, lc, stage_a(v + 2), v + 2 < VT, lc,
-           v + 2 < VT, frags_at(v));
+      if constexpr (HALF)
+        // (a partial tile's A side comes late, with its weight)
+        tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, lc, stage_b(v + 2), no, none, v + 2 < VT, yes,
+             stage_a(v + 2));
+      else
+        tile(stage_a(v), stage_b(v), stage_a(v + 1), stage_b(v + 1), v + 1 < VT, v + 2 < VT, lc, stage_a(v + 2), v + 2 < VT, lc,
+             v + 2 < VT, frags_at(v));
     }
   }  // operand pairs
 
@@ -727,7 +788,7 @@ struct ReduceArgs {
   int M, N, tiles_m, tiles_n, t0, parts, K;
   int off[kMaxK + 1];
 };
-__global__ __launch_bounds__(256) void k_gemm_reduce(const ReduceArgs a) {
+static __global__ __launch_bounds__(256) void k_gemm_reduce(const ReduceArgs a) {
   constexpr int GM = 8, FM = 8, FN = 4;
   const int i = blockIdx.x % FM, u = blockIdx.x / FM;
   const int t = a.t0 + u / 2;

@@ -1094,17 +1094,21 @@ int rank_steps(const int* rank, int K) {
   return (rmax + 15) / 16;
 }
 long long contraction_tiles(long long Kd, int dtype) { return (Kd + (dtype == MLORA_F32 ? 31 : 63)) / (dtype == MLORA_F32 ? 32 : 64); }
-// (`steps16` steps of 16 ranks over all operand pairs)
-GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int steps16, bool nn, int dtype, size_t scratch_limit) {
-  const long long mv = virtual_rows(st, M);
-  GemmPlan p;
-  p.skinny = false;
+}  // namespace
+bool general_skinny(const SegTable& st, int M, int N, long long Kd, int dtype) {
   int rmax = 0;
   for (int k = 0; k < st.K; ++k) rmax = st.rank[k] > rmax ? st.rank[k] : rmax;
   const long long most_units = rmax > 32 ? 1536 : 1024;
-  const long long units = (mv + 15) / 16 * ((N + 63) / 64), row_bytes = Kd_total * (dtype == MLORA_F32 ? 4 : 2);
-  if (N >= 4 && row_bytes <= 4096 && units * row_bytes <= 640 << 10 && (units <= most_units || N <= 64))
-    return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1, 0};
+  const long long units = (virtual_rows(st, M) + 15) / 16 * ((N + 63) / 64), row_bytes = Kd * (dtype == MLORA_F32 ? 4 : 2);
+  return N >= 4 && row_bytes <= 4096 && units * row_bytes <= 640 << 10 && (units <= most_units || N <= 64);
+}
+namespace {
+// (`steps16` steps of 16 ranks over all operand pairs)
+GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int steps16, bool nn, int dtype, size_t scratch_limit) {
+  const long long mv = virtual_rows(st, M);
+  if (general_skinny(st, M, N, Kd_total, dtype)) return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1, 0};
+  GemmPlan p;
+  p.skinny = false;
   const long long t128 = ((mv + 127) / 128) * ((N + 127) / 128);
   p.small = t128 < 256;
   const int b = p.small ? 64 : 128;
@@ -1254,7 +1258,8 @@ size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype)
 GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, int dtype, size_t scratch_bytes) {
   const GemmPlan pl = plan_gemm(st, M, N, Kd, rank_steps(st.rank, st.K), nn, dtype, scratch_bytes);
   const int form = pl.skinny ? MLORA_FORM_SKINNY : (pl.small ? MLORA_FORM_64 : MLORA_FORM_128), tiles = pl.tiles_m * pl.tiles_n;
-  return GemmForm{form, pl.parts, form == MLORA_FORM_128 ? pl.whole : tiles, tiles};
+  const bool quarters = form == MLORA_FORM_128 && pl.whole < tiles;
+  return GemmForm{form, pl.parts, form == MLORA_FORM_128 ? pl.whole : tiles, tiles, pl.skinny ? 16 : (pl.small || quarters ? 64 : 128)};
 }
 RowsForm general_rows_form(const CallCtx& c) { return RowsForm{two_row_groups(c) ? 32 : 16, 1}; }
 int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes) {

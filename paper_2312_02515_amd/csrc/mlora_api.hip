@@ -81,14 +81,16 @@ size_t lowrank_bytes(const mlora_problem* p) {
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// The aligned kernels take bf16 problems whose feature sizes are multiples of 64 and whose buffers
-// are 16-byte aligned, with any ranks (ranks that are no multiple of 8 have forms of their own: 12
-// tasks of 256 tokens, 4096 x 4096, ranks 1 to 128, forward + backward 364 us against 650 us in the
-// general kernels); everything else runs the general kernels.
-bool mfma_sizes_ok(const mlora_problem* p) {
+// The aligned kernels take bf16 problems whose buffers are 16-byte aligned, with any ranks (ranks that are
+// no multiple of 8 have forms of their own: 12 tasks of 256 tokens, 4096 x 4096, ranks 1 to 128, forward + backward 364 us
+// against 650 us in the general kernels): the base products with features that are multiples of 8 (their
+// rows are whole 16-byte chunks; 64 is a contraction tile, of which the last may be partial), the
+// low-rank products with multiples of 64; everything else runs the general kernels.
+bool mfma_chunks_ok(const mlora_problem* p) {
   if (p->dtype != MLORA_BF16 || p->T < 1) return false;
   return gemm_mfma_ok((int)p->T, (int)p->d, (int)p->h) && gemm_mfma_ok((int)p->T, (int)p->h, (int)p->d);
 }
+bool mfma_sizes_ok(const mlora_problem* p) { return mfma_chunks_ok(p) && p->h % 64 == 0 && p->d % 64 == 0; }
 
 bool whole_chunk_ranks(const mlora_problem* p) {
   for (int k = 0; k < p->K; ++k)
@@ -96,15 +98,15 @@ bool whole_chunk_ranks(const mlora_problem* p) {
   return true;
 }
 
-bool mfma_shapes_ok(const mlora_problem* p) {
-  if (!mfma_sizes_ok(p) || !aligned16(p->W)) return false;
+bool mfma_buffers_ok(const mlora_problem* p) {
+  if (!aligned16(p->W)) return false;
   for (int k = 0; k < p->K; ++k)
     if (!aligned16(p->A[k]) || !aligned16(p->B[k])) return false;
   return true;
 }
 
-bool mfma_gemm_applies(const mlora_problem* p) { return !(g_kernel_path.load() & 1) && mfma_shapes_ok(p); }
-bool mfma_lowrank_applies(const mlora_problem* p) { return !(g_kernel_path.load() & 2) && mfma_shapes_ok(p); }
+bool mfma_gemm_applies(const mlora_problem* p) { return !(g_kernel_path.load() & 1) && mfma_chunks_ok(p) && mfma_buffers_ok(p); }
+bool mfma_lowrank_applies(const mlora_problem* p) { return !(g_kernel_path.load() & 2) && mfma_sizes_ok(p) && mfma_buffers_ok(p); }
 
 // Scratch behind the low-rank intermediates, in bytes: fp32 partial sums of launches that cut a
 // contraction into ranges (0 when none ever does).  Splitting is optional: every launch is planned
@@ -251,8 +253,10 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
 // how the base product of Y (nn) or dX is cut up
 GemmForm product_form(const mlora_problem* p, const CallCtx& c, bool nn) {
   const int N = nn ? c.d : c.h, Kd = nn ? c.h : c.d;
-  return mfma_gemm_applies(p) ? gemm_form(c.st, c.T, N, Kd, c.scratch_bytes)
-                              : general_gemm_form(c.st, c.T, N, Kd, nn, c.dtype, c.scratch_bytes);
+  if (!mfma_gemm_applies(p)) return general_gemm_form(c.st, c.T, N, Kd, nn, c.dtype, c.scratch_bytes);
+  GemmForm f = gemm_form(c.st, c.T, N, Kd, c.scratch_bytes);
+  if (!mfma_sizes_ok(p) && f.rows <= 64) f.form = f.rows == 16 ? MLORA_FORM_SKINNY : MLORA_FORM_64;
+  return f;
 }
 
 // Whether the shared-input low-rank kernels (one pass over X for all projections) apply
@@ -617,7 +621,7 @@ int mlora_last_hip_error(void) { return g_last_hip_error; }
 int mlora_lora_kernel_path(const mlora_problem* p) {
   if (validate(p) != MLORA_OK) return -1;
   if (!whole_chunk_ranks(p)) return 3;  // ragged-rank forms, or general kernels
-  return (mfma_gemm_applies(p) ? 0 : 1) | (mfma_lowrank_applies(p) ? 0 : 2);
+  return (mfma_gemm_applies(p) && mfma_sizes_ok(p) ? 0 : 1) | (mfma_lowrank_applies(p) ? 0 : 2);
 }
 
 mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
@@ -654,6 +658,8 @@ mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles) {
   tiles[MLORA_PLAN_Y_TILES] = y.tiles;
   tiles[MLORA_PLAN_DX_WHOLE] = dx.whole;
   tiles[MLORA_PLAN_DX_TILES] = dx.tiles;
+  tiles[MLORA_PLAN_Y_ROWS] = y.rows;
+  tiles[MLORA_PLAN_DX_ROWS] = dx.rows;
   return MLORA_OK;
 }
 

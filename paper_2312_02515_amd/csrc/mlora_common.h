@@ -85,6 +85,7 @@ inline size_t grad_sum_bytes(const SegTable& st, int ranges, int wide_b, int wid
 struct GemmForm {
   int form, parts;
   int whole, tiles;
+  int rows;           // rows of the smallest tiles
 };
 // ... and a low-rank product: rows per block, contraction ranges
 struct RowsForm {
@@ -119,6 +120,8 @@ struct GenOperands {
   const int* rank;     // K entries
   const PtrTable* R;
 };
+// whether the product runs in 16 x 64 tiles there (`Kd` over all operand pairs)
+bool general_skinny(const SegTable& st, int M, int N, long long Kd, int dtype);
 GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, int dtype, size_t scratch_bytes);
 RowsForm general_rows_form(const CallCtx& c);
 int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes);

@@ -1,0 +1,38 @@
+"""Sizes at which the bf16 base products run in small tiles, or in any tile with a last, partial contraction tile
+(features that are multiples of 8 but not of 64): (T, h, d, tokens, ranks, lead) and parts of mlora_kernel_plan's
+answer.  The GPU tests run them, the CPU test holds them to their forms."""
+
+CASES = [
+    # 64 x 64 tiles, one group of waves: rows and columns around the tile, two tasks in a tile, ranks around a slot of 32
+    ((2900, 192, 704, [63, 65, 1, 2700], [8, 32, 33, 64], 3), {"Y_rows": 64}),
+    ((2900, 704, 192, [31, 33, 95, 97, 160, 2461], [8, 16, 33, 127, 5, 128], 17), {"dX_rows": 64}),
+    ((1100, 1024, 1024, [1000], [16], 20), {"Y_rows": 64, "dX_rows": 64, "Y_parts": 1}),
+    # ... two groups: an odd and an even number of contraction tiles behind their LoRA tiles
+    ((220, 1920, 2688, [22] * 9 + [21], [64] * 10, 0), {"Y_rows": 64, "dX_rows": 64}),
+    ((300, 1984, 1216, [100, 190], [5, 100], 10), {"Y_rows": 64, "dX_rows": 64}),
+    # ... contraction ranges
+    ((60, 4096, 576, [37, 20], [16, 64], 1), {"Y_rows": 64, "Y_parts": 8}),
+    ((60, 576, 4096, [37, 20], [12, 40], 1), {"dX_rows": 64, "dX_parts": 8}),
+    # 16 x 64 tiles
+    ((128, 256, 256, [60, 60], [8, 64], 4), {"Y_rows": 16, "dX_rows": 16}),
+    # partial contraction tiles, one chunk more or less than a whole one; 64 x 64 tiles
+    ((2900, 200, 712, [63, 65, 1, 2700], [8, 32, 33, 64], 3), {"Y_rows": 64}),
+    ((600, 1016, 520, [63, 65, 1, 300], [8, 32, 33, 64], 3), {"Y_rows": 64, "dX_rows": 64}),
+    ((600, 520, 1032, [63, 500], [9, 127], 3), {"Y_rows": 64, "dX_rows": 64}),
+    ((60, 4040, 584, [37, 20], [16, 64], 1), {"Y_rows": 64}),
+    ((60, 584, 4040, [37, 20], [12, 40], 1), {"dX_rows": 64}),
+    ((3000, 8, 712, [2000, 900], [3, 17], 1), {"Y_rows": 64}),                 # a single, partial tile
+    ((3000, 712, 8, [2000, 900], [3, 24], 1), {"dX_rows": 64}),
+    # ... halves, in ranges and not, and whole tiles
+    ((900, 2056, 5640, [256, 515], [8, 17], 30), {"Y": "halves", "Y_rows": 128}),
+    ((900, 5640, 2056, [256, 515], [8, 16], 30), {"dX": "halves", "dX_rows": 128}),
+    ((200, 5128, 4104, [80, 90], [16, 30], 3), {"Y": "halves", "dX": "halves", "Y_rows": 128, "dX_rows": 128}),
+    ((9268, 136, 1032, [4000, 33, 5000], [128, 8, 33], 20), {"Y": "whole"}),
+    ((9268, 1032, 136, [4000, 33, 5000], [128, 8, 33], 20), {"dX": "whole"}),
+    ((9268, 56, 1032, [4000, 33, 5000], [64, 8, 16], 20), {"Y": "whole"}),      # ... of one partial tile
+    ((9268, 1032, 56, [4000, 33, 5000], [64, 8, 16], 20), {"dX": "whole"}),
+    ((9268, 120, 1032, [4000, 33, 5000], [64, 8, 16], 20), {"Y": "whole"}),
+    ((9268, 1032, 184, [4000, 33, 5000], [64, 8, 16], 20), {"dX": "whole"}),
+    ((9268, 632, 1032, [4000, 33, 5000], [64, 8, 16], 20), {"Y": "whole"}),
+    ((9268, 1032, 632, [4000, 33, 5000], [64, 8, 20], 20), {"dX": "whole"}),
+]

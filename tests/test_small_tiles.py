@@ -1,0 +1,65 @@
+"""bf16 base products in small tiles, and with a last, partial contraction tile (features that are multiples of 8
+but not of 64), at the sizes of small_tile_cases.py."""
+import pytest
+import torch
+
+from tests.small_tile_cases import CASES
+from tests.test_host_abi import mb  # noqa: F401  (a fixture)
+from tests.test_launch_plans import plan
+
+
+@pytest.mark.parametrize("case,want", CASES)
+def test_sizes_take_their_forms(mb, case, want):  # noqa: F811
+    T, h, d, tokens, ranks, lead = case
+    got = plan(mb, T, h, d, tokens, ranks, lead)
+    assert {k: got[k] for k in want} == want
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [c for c, _ in CASES])
+def test_small_tile_forms(case):
+    from tests.parity_util import TOL, check_full, run_hip
+    from tests.test_gpu_general import _inputs
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=90)
+    check_full(inp, run_hip(inp), TOL[torch.bfloat16], label=f"small tiles {case}")
+
+
+# one task's adapter and rows are not finite: every other task's results keep their bits (the task whose rows
+# share tiles with two neighbours)
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [
+    (2900, 704, 192, [31, 33, 95, 97, 160, 2461], [8, 16, 33, 127, 5, 128], 17),
+    (220, 1920, 2688, [22] * 9 + [21], [64] * 10, 0),
+    (600, 1016, 520, [63, 65, 1, 300], [8, 32, 33, 64], 3),
+    (128, 256, 256, [20, 20, 20, 60], [8, 64, 16, 9], 4),
+    (9268, 1032, 136, [4000, 33, 5000], [128, 8, 33], 20),
+])
+def test_small_tile_isolation(case):
+    from tests.parity_util import run_hip
+    from tests.test_gpu_general import _inputs
+    T, h, d, tokens, ranks, lead = case
+    k = 1
+    inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=91)
+    ref = run_hip(inp)
+    lo, hi = inp.seg_offsets[k], inp.seg_offsets[k + 1]
+    inp.A[k].fill_(float("nan"))
+    inp.B[k].fill_(float("inf"))
+    out = run_hip(inp)
+    for name in ("Y", "dX"):
+        a, b = ref[name].view(torch.int16), out[name].view(torch.int16)
+        assert torch.equal(a[:lo], b[:lo]) and torch.equal(a[hi:], b[hi:]), name
+    for name in ("dA", "dB"):
+        for i in range(len(ranks)):
+            assert i == k or torch.equal(ref[name][i], out[name][i]), (name, i)
+
+
+# projections that share their input: the summed dX in small tiles of two and four operand pairs, with partial
+# contraction tiles
+@pytest.mark.gpu
+@pytest.mark.parametrize("h,ds", [(512, [512, 256]), (520, [712, 264, 1000, 72]), (1024, [512, 512, 1032])])
+def test_small_tile_groups(h, ds):
+    from tests.test_gpu_groups import _group_inputs, check_group, run_group
+    from tests.parity_util import TOL
+    ins = _group_inputs(500, h, ds, [100, 197, 170], [[16, 8, 64]] * len(ds), torch.bfloat16, lead=3, seed=92)
+    check_group(ins, run_group(ins), TOL[torch.bfloat16])
