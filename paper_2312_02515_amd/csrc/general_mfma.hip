@@ -583,6 +583,10 @@ struct GenRowsArgs {
   const void* In;
   void* Out;
   int inner, ldz, K, b0;                 // b0: first block of this launch
+  // parts > 1: the contraction is cut into ranges, one block each; range s writes its fp32 sums of row i at part +
+  // (s * rows + i - off[0]) * ldz, rows = off[K] - off[0], and k_gen_rows_reduce adds them in order
+  int parts;
+  float* part;
   int off[kMaxK + 1];
   unsigned char rank[kMaxK];
   float s[kMaxK];
@@ -719,24 +723,43 @@ __device__ __forceinline__ float shared_sum(const float* red, int t) {
 }
 
 template <typename T, int VW, int RM, int NW, bool KMAJOR>
-__device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, int hi, float* red) {
-  const int r = a.rank[k], inner = a.inner;
+__device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, int hi, int sp, float* red) {
+  const int r = a.rank[k];
+  // this block's range, in whole runs of 64 contraction indices
+  int c0 = 0, inner = a.inner;
+  if (a.parts > 1) {
+    const unsigned runs = (unsigned)(a.inner + 63) / 64;
+    c0 = (int)(runs * (unsigned)sp / (unsigned)a.parts) * 64;
+    const int c1 = (int)(runs * (unsigned)(sp + 1) / (unsigned)a.parts) * 64;
+    inner = (c1 < a.inner ? c1 : a.inner) - c0;
+  }
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const T* x[RM];
 #pragma unroll
   for (int i = 0; i < RM; ++i) {
     const int row = lo + 16 * i + (lane & 15);
-    x[i] = static_cast<const T*>(a.In) + (size_t)(row < hi ? row : hi - 1) * inner;
+    x[i] = static_cast<const T*>(a.In) + (size_t)(row < hi ? row : hi - 1) * a.inner + c0;
   }
   f32x4 acc[RM][VW];
 #pragma unroll
   for (int i = 0; i < RM; ++i)
 #pragma unroll
     for (int j = 0; j < VW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  accumulate_rows<T, VW, RM, NW, KMAJOR>(acc, x, inner, static_cast<const T*>(a.M.p[k]), KMAJOR ? r : inner, 0, r, wave, lane);
+  accumulate_rows<T, VW, RM, NW, KMAJOR>(acc, x, inner, static_cast<const T*>(a.M.p[k]) + (KMAJOR ? (size_t)c0 * r : (size_t)c0),
+                                         KMAJOR ? r : a.inner, 0, r, wave, lane);
   share_sums<VW, RM, NW>(acc, red, wave, lane);
   constexpr int FR = RM * VW * 256;
+  if (a.parts > 1) {
+    float* part = a.part + ((size_t)sp * (a.off[a.K] - a.off[0]) + lo - a.off[0]) * a.ldz;
+    for (int t = tid; t < FR; t += NW * 64) {
+      const float sum = shared_sum<FR, NW / 2>(red, t);
+      const int ij = t >> 8, i = ij / VW, j = ij % VW, i16 = t & 15;
+      const int o = 16 * i + ((t >> 4) & 15), q = KMAJOR ? first_column<VW>(i16, 0, r) + j : 16 * j + i16;
+      if (lo + o < hi && q < r) part[(size_t)o * a.ldz + q] = sum;
+    }
+    return;
+  }
   const float s = a.s[k];
   T* Out = static_cast<T*>(a.Out);
   for (int t = tid; t < FR; t += NW * 64) {
@@ -754,13 +777,40 @@ template <typename T, int RM, int NW, bool KMAJOR>
 __global__ __launch_bounds__(NW * 64, 4) void k_gen_rows(const GenRowsArgs a) {
   extern __shared__ float red[];         // NW / 2 x RM x (groups of the largest rank) KiB
   int lo = 0, hi = 0;
-  const int k = rows_block<16 * RM>(a, a.b0 + blockIdx.x, &lo, &hi);
+  int block = blockIdx.x, sp = 0;
+  if (a.parts > 1) {
+    sp = block % a.parts;
+    block /= a.parts;
+  }
+  const int k = rows_block<16 * RM>(a, a.b0 + block, &lo, &hi);
   if (k < 0) return;
   const int r = a.rank[k];
-  if (r <= 16) rows_body<T, 1, RM, NW, KMAJOR>(a, k, lo, hi, red);
-  else if (r <= 32) rows_body<T, 2, RM, NW, KMAJOR>(a, k, lo, hi, red);
-  else if (r <= 64) rows_body<T, 4, RM, NW, KMAJOR>(a, k, lo, hi, red);
-  else if constexpr (RM == 1) rows_body<T, 8, RM, NW, KMAJOR>(a, k, lo, hi, red);   // (two row groups: ranks up to 64)
+  if (r <= 16) rows_body<T, 1, RM, NW, KMAJOR>(a, k, lo, hi, sp, red);
+  else if (r <= 32) rows_body<T, 2, RM, NW, KMAJOR>(a, k, lo, hi, sp, red);
+  else if (r <= 64) rows_body<T, 4, RM, NW, KMAJOR>(a, k, lo, hi, sp, red);
+  else if constexpr (RM == 1) rows_body<T, 8, RM, NW, KMAJOR>(a, k, lo, hi, sp, red);   // (two row groups: ranks up to 64)
+}
+
+// Adds the contraction ranges of k_gen_rows in order, scales and rounds.  One thread per four columns of a row.
+template <typename T>
+__global__ __launch_bounds__(256) void k_gen_rows_reduce(const GenRowsArgs a) {
+  const int rows = a.off[a.K] - a.off[0], per = a.ldz / 4;
+  const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+  if (t >= (long long)rows * per) return;
+  const int i = (int)(t / per), q = (int)(t % per) * 4;
+  const int k = task_of_row(a, a.off[0] + i);
+  const int r = a.rank[k];
+  const float s = a.s[k];
+  f32x4 sum = f32x4{0.f, 0.f, 0.f, 0.f};
+  if (q < r) {
+    const float* p = a.part + (size_t)i * a.ldz + q;
+    const size_t step = (size_t)rows * a.ldz;
+#pragma unroll 4
+    for (int u = 0; u < a.parts; ++u) sum += *reinterpret_cast<const f32x4*>(p + u * step);
+  }
+  T* out = static_cast<T*>(a.Out) + (size_t)(a.off[0] + i) * a.ldz + q;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) out[e] = from_f32<T>(q + e < r ? sum[e] * s : 0.f);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1004,8 +1054,30 @@ int row_blocks(const SegTable& st, int tm) {
 // for every CU (ranks above 64 leave no registers for it)
 bool two_row_groups(const CallCtx& c) { return c.ldz <= 64 && row_blocks(c.st, 32) >= 512; }
 
+// Contraction ranges of one low-rank product: a block reads 16 rows and its task's whole operand, and a CU draws
+// about 30 GB/s that way, so few blocks of long contractions take long while the other CUs idle.  From 320 KB a block on, as
+// many ranges as give every CU a block, of at least 64 KB each.  One launch -> ranges and their reduction, us:
+//   fp32  91 x 3840 (25 tasks), rank 64  45.7 -> 14.3;  687 x 2480, rank 58  33.0 -> 15.4, its s dy B^T, 1320 deep 14.4 -> 12.1
+//         2048 x 4096, rank 16 (128 blocks)  14.7, 17.1 -> 14.7, 15.4
+//   bf16  112 x 4960 (15 tasks), rank 87  30.1 -> 11.1;  212 x 10674, rank 64  24.5 -> 11.4
+//         61 x 13770, rank 72, s dy B^T  64.8 -> 15.9;  106 x 3120 (4 tasks), rank 39  11.3 -> 9.0
+int gen_rows_parts(const CallCtx& c, int inner, size_t limit) {
+  if (c.K == 0 || two_row_groups(c)) return 1;
+  const int blocks = row_blocks(c.st, 16);
+  int rmax = 0;
+  for (int k = 0; k < c.K; ++k) rmax = c.st.rank[k] > rmax ? c.st.rank[k] : rmax;
+  const long long bytes = (long long)(16 + (rmax + 15) / 16 * 16) * inner * (c.dtype == MLORA_F32 ? 4 : 2);
+  if (blocks == 0 || bytes < 320 << 10) return 1;
+  const size_t one = (size_t)(c.st.off[c.K] - c.st.off[0]) * c.ldz * sizeof(float);
+  int p = 256 / blocks;
+  p = p < 16 ? p : 16;
+  p = p < bytes >> 16 ? p : (int)(bytes >> 16);
+  while (p > 1 && p * one > limit) --p;
+  return p > 1 ? p : 1;
+}
+
 template <typename T, bool KMAJOR>
-hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const PtrTable& M) {
+hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const PtrTable& M, float* scratch) {
   if (c.K == 0 || c.T == 0 || row_blocks(c.st, 16) == 0) return hipSuccess;
   GenRowsArgs a;
   a.In = In;
@@ -1019,15 +1091,21 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
     a.s[k] = c.st.s[k];
   }
   a.M = M;
+  a.parts = gen_rows_parts(c, inner, c.scratch_bytes);
+  a.part = scratch;
   const bool two = two_row_groups(c);
   const int blocks = row_blocks(c.st, two ? 32 : 16);
   const int groups = c.ldz <= 16 ? 1 : (c.ldz <= 32 ? 2 : (c.ldz <= 64 ? 4 : 8));
   const unsigned lds = 4 * (two ? 2 : 1) * groups * 1024;
   constexpr int most = 1 << 22;          // a launch holds fewer than 2^32 threads
   for (a.b0 = 0; a.b0 < blocks; a.b0 += most) {
-    const dim3 grid((unsigned)(blocks - a.b0 < most ? blocks - a.b0 : most));
+    const dim3 grid((unsigned)(blocks - a.b0 < most ? blocks - a.b0 : most) * (unsigned)a.parts);
     if (two) hipLaunchKernelGGL((k_gen_rows<T, 2, 8, KMAJOR>), grid, dim3(512), lds, c.stream, a);
     else hipLaunchKernelGGL((k_gen_rows<T, 1, 8, KMAJOR>), grid, dim3(512), lds, c.stream, a);
+  }
+  if (a.parts > 1) {
+    const long long n = (long long)(c.st.off[c.K] - c.st.off[0]) * (c.ldz / 4);
+    hipLaunchKernelGGL((k_gen_rows_reduce<T>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c.stream, a);
   }
   return hipGetLastError();
 }
@@ -1261,17 +1339,29 @@ GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, in
   const bool quarters = form == MLORA_FORM_128 && pl.whole < tiles;
   return GemmForm{form, pl.parts, form == MLORA_FORM_128 ? pl.whole : tiles, tiles, pl.skinny ? 16 : (pl.small || quarters ? 64 : 128)};
 }
-RowsForm general_rows_form(const CallCtx& c) { return RowsForm{two_row_groups(c) ? 32 : 16, 1}; }
+// Estimate for s x A (us): blocks of 16 rows, the share of the fullest CU, at what a CU draws; `block_bytes`: what a block reads
+double general_rows_us(const CallCtx& c, int inner, double* block_bytes) {
+  const int parts = gen_rows_parts(c, inner, c.scratch_bytes);
+  const double blocks = (double)row_blocks(c.st, 16) * parts;
+  int rmax = 0;
+  for (int k = 0; k < c.K; ++k) rmax = c.st.rank[k] > rmax ? c.st.rank[k] : rmax;
+  const double bytes = (16.0 + (rmax + 15) / 16 * 16) * inner * (c.dtype == MLORA_F32 ? 4 : 2) / parts;
+  *block_bytes = bytes;
+  return 4.0 + (blocks <= 256 ? 1.0 : blocks / 256) * bytes / 30e3 + (parts > 1 ? 4.5 : 0.0);
+}
+RowsForm general_rows_form(const CallCtx& c, int inner) {
+  return RowsForm{two_row_groups(c) ? 32 : 16, gen_rows_parts(c, inner, c.scratch_bytes)};
+}
 int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes) {
   return st.K > 0 ? gen_grad_splits(st, wide_b, wide_a, scratch_bytes) : 1;
 }
 
-hipError_t general_Z(const CallCtx& c, const void* X, void* Z) {
-  return c.dtype == MLORA_F32 ? rows_t<float, true>(c, X, c.h, Z, c.A) : rows_t<bf16, true>(c, X, c.h, Z, c.A);
+hipError_t general_Z(const CallCtx& c, const void* X, void* Z, float* scratch) {
+  return c.dtype == MLORA_F32 ? rows_t<float, true>(c, X, c.h, Z, c.A, scratch) : rows_t<bf16, true>(c, X, c.h, Z, c.A, scratch);
 }
 
-hipError_t general_G(const CallCtx& c, const void* dY, void* G) {
-  return c.dtype == MLORA_F32 ? rows_t<float, false>(c, dY, c.d, G, c.B) : rows_t<bf16, false>(c, dY, c.d, G, c.B);
+hipError_t general_G(const CallCtx& c, const void* dY, void* G, float* scratch) {
+  return c.dtype == MLORA_F32 ? rows_t<float, false>(c, dY, c.d, G, c.B, scratch) : rows_t<bf16, false>(c, dY, c.d, G, c.B, scratch);
 }
 
 hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st,

@@ -862,6 +862,8 @@ RowsPlan plan_rows(const SegTable& st, int inner, int ldz, size_t limit) {
     pl = RowsPlan{128, KT >= 128 ? 8 : 4};
   } else if (b32 >= 32 && KT >= 128) {
     pl = RowsPlan{64, 8};
+  } else if (b32 < 32 && KT > 64) {
+    pl = RowsPlan{32, KT >= 128 ? 16 : 8};
   }
   const size_t one = (size_t)rows * ldz * sizeof(float);
   while (pl.splits > 1 && (one * pl.splits > limit || 4 * pl.splits > KT)) pl.splits /= 2;
@@ -1050,6 +1052,23 @@ size_t rows_partial_bytes(int T, int inner, int ldz) {
 RowsForm rows_form(const SegTable& st, int inner, int ldz, size_t limit) {
   const RowsPlan pl = plan_rows(st, inner, ldz, limit);
   return RowsForm{pl.tm, pl.splits};
+}
+
+// A_k's tile of a rank above 64 that is no multiple of 4 is read element by element (2.7 us a contraction tile): where
+// the rows fill few blocks, the general kernel, which puts such columns together in registers, is faster: 219 x 1920 (10
+// tasks, ranks up to 114) 27.3 -> 9.2 us, 4458 x 640 (43 tasks, up to 123) 27.4 -> 9.8, 6251 x 448 (2 tasks, up to 96) 13.7 ->
+// 5.8.  Blocks that read more than 512 KB, and a single or few contraction tiles, stay (3072 x 4096, 12 tasks, up to 128: 21.8).
+bool general_rows_pay(const CallCtx& c) {
+  if (nq_of(c.ldz) != 4 || c.h < 256) return false;
+  bool odd = false;
+  for (int k = 0; k < c.K; ++k) odd = odd || c.st.rank[k] % 4 != 0;
+  if (!odd) return false;
+  const RowsPlan pl = plan_rows(c.st, c.h, c.ldz, c.scratch_bytes);
+  if (pl.tm == 32 && pl.splits > 1) return false;   // (short tasks in blocks of one wave and ranges)
+  const double blocks = (double)row_blocks(c.st, pl.tm) * pl.splits, rounds = blocks <= 256 ? 1.0 : blocks / 256;
+  const double us = 4.0 + rounds * 2.7 * (c.h / 64) / pl.splits + (pl.splits > 1 ? 4.5 : 0.0);
+  double bytes;
+  return general_rows_us(c, c.h, &bytes) < 0.7 * us && bytes <= 512 << 10;
 }
 
 // Z = s x A (a_major = true, M = A_k) or G = s dy B^T (a_major = false, M = B_k).

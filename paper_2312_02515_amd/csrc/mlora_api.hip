@@ -179,10 +179,10 @@ mlora_status hip_status(hipError_t e) {
 
 // Z = s_k x_k A_k into `Z` ([T, ldz], layout of the `saved` buffer)
 hipError_t compute_Z(const mlora_problem* p, const CallCtx& c, const void* X, void* Z, void* scratch) {
-  if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(Z)) {
+  if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(Z) && !general_rows_pay(c)) {
     return lowrank_rows_mfma(c, (const bf16*)X, c.h, (bf16*)Z, c.A, true, static_cast<float*>(scratch), c.scratch_bytes);
   }
-  return general_Z(c, X, Z);
+  return general_Z(c, X, Z, static_cast<float*>(scratch));
 }
 
 // Y = X W + Z B_k, given Z
@@ -229,7 +229,7 @@ hipError_t adapter_grads_impl(const mlora_problem* p, const CallCtx& c, const vo
       e = grads_mfma(c, (const bf16*)dY, (const bf16*)Z, tb, (const bf16*)X, (const bf16*)G, skip_dA ? nullptr : &ta,
                      accumulate, partial, c.scratch_bytes);
   } else {
-    e = general_G(c, dY, G);
+    e = general_G(c, dY, G, partial);
     if (e == hipSuccess) e = general_grads(c, dY, Z, tb, X, G, skip_dA ? nullptr : &ta, accumulate, partial, c.scratch_bytes);
   }
   return e;
@@ -505,7 +505,7 @@ mlora_status mlora_lora_group_fwd(const mlora_problem* const* ps, int P, const v
   bool fused = group_lowrank_applies(ps, P, X);
   for (int p = 0; p < P; ++p) {
     fill_ctx(ps[p], hip_stream, &c[p]);
-    fused = fused && aligned16(saved[p]) && group_rows_pay(c[p].st, c[p].h, c[p].ldz, c[p].scratch_bytes);
+    fused = fused && aligned16(saved[p]) && !general_rows_pay(c[p]) && group_rows_pay(c[p].st, c[p].h, c[p].ldz, c[p].scratch_bytes);
   }
   if (fused) {
     // every Z_p in one pass over X
@@ -633,8 +633,8 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
   const size_t room = c.scratch_bytes;
   const bool al = mfma_lowrank_applies(p);
   const GemmForm y = product_form(p, c, true), dx = product_form(p, c, false);
-  const RowsForm z = al ? rows_form(c.st, c.h, c.ldz, room) : general_rows_form(c);
-  const RowsForm g = al ? rows_form(c.st, c.d, c.ldz, room) : general_rows_form(c);
+  const RowsForm z = al && !general_rows_pay(c) ? rows_form(c.st, c.h, c.ldz, room) : general_rows_form(c, c.h);
+  const RowsForm g = al ? rows_form(c.st, c.d, c.ldz, room) : general_rows_form(c, c.d);
   plan[MLORA_PLAN_Y] = y.form;
   plan[MLORA_PLAN_Y_PARTS] = y.parts;
   plan[MLORA_PLAN_DX] = dx.form;

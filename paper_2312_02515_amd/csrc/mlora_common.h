@@ -108,8 +108,8 @@ struct CallCtx {
 // `scratch` (`partial`) that they are given; 0 = none does.  The size functions give the most that T
 // rows or fewer use, whatever their split positions.
 size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype);
-hipError_t general_Z(const CallCtx& c, const void* X, void* Z);      // Z = s x A
-hipError_t general_G(const CallCtx& c, const void* dY, void* G);     // G = s dy B^T
+hipError_t general_Z(const CallCtx& c, const void* X, void* Z, float* scratch);      // Z = s x A
+hipError_t general_G(const CallCtx& c, const void* dY, void* G, float* scratch);     // G = s dy B^T
 // One operand pair of a base product: A [M, Kd], W [Kd, N] (nn) or [N, Kd], L [M, ldz] with
 // R_k [rank[k], N] (nn) or [N, rank[k]].
 struct GenOperands {
@@ -123,7 +123,8 @@ struct GenOperands {
 // whether the product runs in 16 x 64 tiles there (`Kd` over all operand pairs)
 bool general_skinny(const SegTable& st, int M, int N, long long Kd, int dtype);
 GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, int dtype, size_t scratch_bytes);
-RowsForm general_rows_form(const CallCtx& c);
+double general_rows_us(const CallCtx& c, int inner, double* block_bytes);
+RowsForm general_rows_form(const CallCtx& c, int inner);
 int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes);
 // C = sum over the n <= MLORA_MAX_GROUP operand pairs of A op(W) + rows_k(L R_k)
 hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st,
@@ -166,6 +167,8 @@ hipError_t w8_dequantize(const int8_t* Wq, const float* c, int dtype, int h, int
 // lowrank_mfma.hip : bf16 MFMA kernels for Z, G (row-local) and dA_k, dB_k (reduce over a task's tokens)
 size_t rows_partial_bytes(int T, int inner, int ldz);
 RowsForm rows_form(const SegTable& st, int inner, int ldz, size_t limit);
+// whether Z = s x A is faster in the general kernel
+bool general_rows_pay(const CallCtx& c);
 int grad_splits(const SegTable& st, int wide_b, int wide_a, size_t limit);
 hipError_t lowrank_rows_mfma(const CallCtx& c, const bf16* In, int inner, bf16* Out, const PtrTable& M, bool a_major,
                              float* partial, size_t limit);

@@ -36,3 +36,17 @@ CASES = [
     ((9268, 632, 1032, [4000, 33, 5000], [64, 8, 16], 20), {"Y": "whole"}),
     ((9268, 1032, 632, [4000, 33, 5000], [64, 8, 20], 20), {"dX": "whole"}),
 ]
+
+# Low-rank products: few rows of deep contractions in ranges, in the general kernel (fp32, and features that are no
+# multiple of 64) and in blocks of one wave; ranks above 64 that are no multiple of 4 in the general kernel
+ROWS = [
+    ("f32", (91, 3840, 388, [10, 0, 44, 30], [64, 3, 17, 40], 2), {"Z_rows": 16, "Z_parts": 16, "G_parts": 1}),
+    ("f32", (90, 130, 4999, [50, 33], [64, 33], 2), {"G_rows": 16, "G_parts": 16}),
+    ("f32", (700, 2480, 132, [600, 33], [9, 58], 2), {"Z_rows": 16, "Z_parts": 6}),
+    ("bf16", (112, 4967, 132, [50, 33], [87, 16], 2), {"Z_rows": 16, "Z_parts": 16}),
+    ("bf16", (112, 132, 4960, [50, 33], [128, 16], 2), {"G_rows": 16, "G_parts": 16}),
+    ("bf16", (68, 9536, 64, [20, 1, 40], [15, 8, 3], 2), {"Z_rows": 32, "Z_parts": 16}),
+    ("bf16", (68, 64, 4160, [20, 1, 40], [15, 64, 3], 2), {"G_rows": 32, "G_parts": 8}),
+    ("bf16", (219, 1920, 128, [22] * 9, [114, 5, 70, 128, 1, 99, 66, 8, 33], 2), {"Z_rows": 16, "Z_parts": 8}),
+    ("bf16", (4458, 640, 128, [100] * 43, [123, 64, 7] * 14 + [97], 2), {"Z_rows": 16, "Z_parts": 1}),
+]

@@ -1,9 +1,9 @@
 """bf16 base products in small tiles, and with a last, partial contraction tile (features that are multiples of 8
-but not of 64), at the sizes of small_tile_cases.py."""
+but not of 64), and low-rank products of few rows in contraction ranges, at the sizes of small_tile_cases.py."""
 import pytest
 import torch
 
-from tests.small_tile_cases import CASES
+from tests.small_tile_cases import CASES, ROWS
 from tests.test_host_abi import mb  # noqa: F401  (a fixture)
 from tests.test_launch_plans import plan
 
@@ -13,6 +13,24 @@ def test_sizes_take_their_forms(mb, case, want):  # noqa: F811
     T, h, d, tokens, ranks, lead = case
     got = plan(mb, T, h, d, tokens, ranks, lead)
     assert {k: got[k] for k in want} == want
+
+
+@pytest.mark.parametrize("dtype,case,want", ROWS)
+def test_low_rank_sizes_take_their_forms(mb, dtype, case, want):  # noqa: F811
+    T, h, d, tokens, ranks, lead = case
+    got = plan(mb, T, h, d, tokens, ranks, lead, f32=dtype == "f32")
+    assert {k: got[k] for k in want} == want
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,case", [(t, c) for t, c, _ in ROWS])
+def test_low_rank_forms(dtype, case):
+    from tests.parity_util import TOL, check_full, run_hip
+    from tests.test_gpu_general import _inputs
+    T, h, d, tokens, ranks, lead = case
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    inp = _inputs(T, h, d, tokens, ranks, dt, lead=lead, seed=93)
+    check_full(inp, run_hip(inp), TOL[dt], label=f"low-rank {dtype} {case}")
 
 
 @pytest.mark.gpu
