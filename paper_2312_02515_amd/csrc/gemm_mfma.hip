@@ -56,10 +56,11 @@ void launch_whole(const gemmk::GemmArgs<NSEG>& a, int tiles, hipStream_t stream)
 
 // tiles [a.t0, total) as halves of 128 x 256, their contraction in a.parts ranges
 template <bool NN, int NSEG>
-void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
+void launch_halves(const gemmk::GemmArgs<NSEG>& a, bool packed, hipStream_t stream) {
   const int units = 2 * (a.tiles_m * a.tiles_n - a.t0);
   const dim3 grid(units * a.parts);
-  hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, false>), grid, dim3(256), 0, stream, a);
+  if (packed) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, true>), grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, false>), grid, dim3(256), 0, stream, a);
   if (a.parts == 1) return;
   gemmk::ReduceArgs r;
   r.C = a.C;
@@ -70,6 +71,7 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, hipStream_t stream) {
   r.tiles_n = a.tiles_n;
   r.t0 = a.t0;
   r.parts = a.parts;
+  r.packed = packed;
   r.K = a.K;
   for (int k = 0; k <= kMaxK; ++k) r.off[k] = a.off[k];
   hipLaunchKernelGGL(gemmk::k_gemm_reduce, dim3(units * 8), dim3(256), 0, stream, r);
@@ -114,6 +116,7 @@ constexpr int kSmallTiles = 64;
 struct Plan {
   int whole, parts;
   int small;          // groups of four waves per 64 x 64 tile; 0: 256 x 256 tiles and halves
+  bool packed;        // halves: rows of several tasks in a piece of 32
 };
 constexpr int kMaxParts = 16;
 constexpr size_t kSmallWeight = (size_t)32 << 20;
@@ -139,11 +142,11 @@ double plan_small(const SegTable& st, int M, int N, int KT, int pairs, size_t sc
     const double us = 5.0 + m * (0.9 + (m > 1 ? 0.19 : 0.25) * steps) + (p > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
     if (p == 1 || us < best) {
       best = us;
-      *out = Plan{0, p, 1};
+      *out = Plan{0, p, 1, false};
     }
     if (p == 1 && n <= 256 && pairs == 1 && 6.3 + 0.4 * ((steps + 1) / 2) < best) {
       best = 6.3 + 0.4 * ((steps + 1) / 2);
-      *out = Plan{0, 1, 2};
+      *out = Plan{0, 1, 2, false};
     }
   }
   return best;
@@ -188,7 +191,7 @@ Plan plan_gemm(const SegTable& st, int M, int N, int KT, int pairs, size_t scrat
     const double part = last == 0 ? 0.0 : (tiles > 256 && last <= 128 ? 0.85 : 1.0);
     return (tiles / 256 + part) * (whole_fixed + 1.3 * KT);
   };
-  Plan best{total, 1, 0};
+  Plan best{total, 1, 0, false};
   double best_us = whole_us(total);
   for (int parts = 1; halves > 0 && parts <= kMaxParts && parts <= KT; ++parts) {
     const size_t bytes = parts > 1 ? (size_t)halves * parts * (BM / 2) * BN * sizeof(float) : 0;
@@ -197,7 +200,22 @@ Plan plan_gemm(const SegTable& st, int M, int N, int KT, int pairs, size_t scrat
                       (parts > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
     if (us < best_us) {
       best_us = us;
-      best = Plan{q, parts, 0};
+      best = Plan{q, parts, 0, false};
+    }
+  }
+  if (packed_rows(st, M)) {
+    // half tiles of packed rows: the tasks' LoRA terms one after the other
+    const int halves_p = 2 * (int)((M + 255LL) / 256 * tiles_n), in_tile = (int)((long long)live * 128 / M) + 2;
+    const double fixed = 12.0 + pairs * 1.5 * ((in_tile < live ? in_tile : live) * r32 - 1);
+    for (int parts = 1; parts <= kMaxParts && parts <= KT; ++parts) {
+      const size_t bytes = parts > 1 ? (size_t)halves_p * parts * (BM / 2) * BN * sizeof(float) : 0;
+      if (bytes > scratch_limit) break;
+      const double us = (double)((halves_p * parts + 255) / 256) * (fixed + 0.78 * ((KT + parts - 1) / parts)) +
+                        (parts > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
+      if (us < 0.93 * best_us) {
+        best_us = us / 0.93;
+        best = Plan{0, parts, 0, true};
+      }
     }
   }
   Plan small;
@@ -244,7 +262,8 @@ hipError_t launch(gemmk::GemmArgs<NSEG>& a, float* scratch, size_t scratch_bytes
     return e;
   }
   if (pl.whole > 0) launch_whole<NN, NSEG>(a, pl.whole, stream);
-  if (pl.whole < a.tiles_m * a.tiles_n) launch_halves<NN, NSEG>(a, stream);
+  if (pl.packed) a.tiles_m = (a.M + BM - 1) / BM;
+  if (pl.whole < a.tiles_m * a.tiles_n) launch_halves<NN, NSEG>(a, pl.packed, stream);
   const hipError_t err = hipGetLastError();
   profile_end(slot, stream);
   return err;
@@ -293,6 +312,7 @@ GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_byte
   const long long total = (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN);
   if (skinny(st, M, N, Kd)) return GemmForm{MLORA_FORM_HALVES, 1, 0, (int)total, 16};
   const Plan pl = plan_gemm(st, M, N, (Kd + 63) / 64, 1, scratch_bytes);
+  if (pl.packed) return GemmForm{MLORA_FORM_HALVES, pl.parts, 0, (M + BM - 1) / BM * ((N + BN - 1) / BN), BM / 2};
   const int form = pl.whole == total ? MLORA_FORM_WHOLE : (pl.whole == 0 ? MLORA_FORM_HALVES : MLORA_FORM_MIXED);
   return GemmForm{form, pl.parts, pl.whole, (int)total, form == MLORA_FORM_WHOLE ? BM : (pl.small > 0 ? 64 : BM / 2)};
 }

@@ -168,6 +168,9 @@ __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const b
 // together in registers, element by element (at most two of a block's contraction tiles per task).
 // B_k [r, N] has whole chunks for any rank.  12 tasks of 256 tokens, 4096 x 4096, ranks 1 to 128: 99 us,
 // as long as the forward product, against 244 us in the general kernel.
+// RAG of half tiles stands for PACKED: many tasks of few rows, whose pieces of 32 rows would hold few rows each.  Pieces
+// then hold rows of several tasks, and the LoRA term is added task by task, to the task's own rows only (a select, no
+// product with zeros).  855 rows of 42 tasks, 10880 -> 1728, rank 64 83 -> 70 us.
 template <int WAVES_M, int WAVES_N, bool NN, int NSEG, bool RAG>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmArgs<NSEG> ga) {
   constexpr int BK = 64;
@@ -186,7 +189,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   constexpr int LPB = BBYTES / 1024 / NW;      // Bm side
   constexpr int PER_TILE = LPA + LPB;
   static_assert(WM == 128, "the sub-steps halve a 128-row wave tile");
-  static_assert(!RAG || (!NN && !HALF), "half tiles and B_k take any rank");
+  constexpr bool PACKED = HALF && RAG;
+  static_assert(!RAG || HALF || !NN, "B_k takes any rank");
 
   // Three stages for the A side, two for the Bm side: all 160 KiB of the CU's LDS.  The rows of
   // A come from HBM (every element once per launch, cold), the weight from the Infinity Cache; a
@@ -253,7 +257,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // Every use looks up a wave-uniform piece, so an entry is read with v_readlane.
   constexpr int NFR = BM / 32;
   int v_tab = 0;
-  if (__builtin_expect(ga.K <= kFewTasks, 1)) {
+  if constexpr (PACKED) {
+    const RowPiece p = packed_piece(M, (unsigned)(tm * BM + 32 * (lane & (NFR - 1))));
+    const int col = lane / NFR;
+    v_tab = col == 0 ? p.row : (col == 1 ? p.n : p.task);
+  } else if (__builtin_expect(ga.K <= kFewTasks, 1)) {
     const int v0 = tm * BM + 32 * (lane & (NFR - 1));
     int vstart = 0, prev = 0, frow = M - 1, fn = 0, ftask = -1;
     for (int r = 0; r < ga.K + 2; ++r) {
@@ -451,7 +459,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
         if (q < (hi ? r1 : r0) && col0 + n < N) p = (hi ? p1 : p0) + ((size_t)q * N + n) * 2;
       } else {
         const int rl = RPI * w + lane / CPR;
-        if constexpr (RAG) {
+        if constexpr (RAG && !HALF) {
           if (lc.lora && ((r0 | r1) & 7) != 0) {
             const bf16* row = reinterpret_cast<const bf16*>(cp) + (size_t)rl * cr;
             bf16x8 v;
@@ -674,7 +682,47 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // ---- HALF: the LoRA term, from registers, with the last range.  Fragments straight from memory (a few
   // KB per block that the caches hold): lane 16 kg + r16 loads 8 ranks of row r16 of L, and of output
   // column r16 of R_k, which is kept while the pieces belong to the same task.
-  if constexpr (HALF) {
+  if constexpr (PACKED) {
+    const TaskWalk walk = task_walk(ga);
+    const int end = row0 + BM < M ? row0 + BM : M, first = part == ga.parts - 1 ? first_task(ga, row0) : ga.K;
+    for (int sg = 0; sg < NSEG; ++sg) {
+      const bf16* L = ga.L[sg];
+      const int ldz = ga.ldz[sg];
+      for (int k = first; k < ga.K; ++k) {
+        const int lo = task_begin(walk, k, ga.off[kMaxK]), hi = task_begin(walk, k + 1, ga.off[kMaxK]);
+        if (lo >= end) break;
+        if (hi <= lo) continue;
+        const int r = rank_of(ga, sg, k);
+        const bf16* Rk = static_cast<const bf16*>(ga.R[sg].p[k]);
+        for (int q0 = 0; q0 < r; q0 += 32) {
+          const int q = q0 + 8 * kg;
+#pragma unroll
+          for (int j = 0; j < FN; ++j) {
+            int n = col0 + wn * WN + 16 * j + r16;
+            n = n < N ? n : N - 1;
+            if (!NN && r % 8 == 0) {
+              bfr[j] = *(const bf16x8*)(q < r ? Rk + (size_t)n * r + q : reinterpret_cast<const bf16*>(zeros));
+              continue;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) bfr[j][e] = q + e < r ? Rk[NN ? (size_t)(q + e) * N + n : (size_t)n * r + q + e] : (bf16)0.f;
+          }
+#pragma unroll
+          for (int i = 0; i < FM; ++i) {
+            const int first_row = row0 + 16 * i, row = first_row + r16;
+            if (hi <= first_row || lo >= first_row + 16 || first_row >= M) continue;
+            const bf16x8 lf = *(const bf16x8*)(q < ldz ? L + (size_t)(row < M ? row : M - 1) * ldz + q : reinterpret_cast<const bf16*>(zeros));
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+              const f32x4 t = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[j], lf, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[i][j][e] += row >= lo && row < hi ? t[e] : 0.f;
+            }
+          }
+        }
+      }
+    }
+  } else if constexpr (HALF) {
     for (int sg = 0; part == ga.parts - 1 && sg < NSEG; ++sg) {
       const bf16* L = ga.L[sg];
       const int ldz = ga.ldz[sg];
@@ -785,7 +833,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
 struct ReduceArgs {
   bf16* C;
   const float* part;
-  int M, N, tiles_m, tiles_n, t0, parts, K;
+  int M, N, tiles_m, tiles_n, t0, parts, packed, K;
   int off[kMaxK + 1];
 };
 static __global__ __launch_bounds__(256) void k_gemm_reduce(const ReduceArgs a) {
@@ -800,7 +848,12 @@ static __global__ __launch_bounds__(256) void k_gemm_reduce(const ReduceArgs a) 
   const int r16 = lane & 15, kg = lane >> 4;
   const int v0 = tm * 128 + 16 * i;      // the fragment's first virtual row
   // (16 rows: the upper or lower half of a piece)
-  const RowPiece p = find_piece(a, row_axis(a), (unsigned)v0);
+  RowPiece p;
+  if (a.packed) {
+    p = packed_piece(a.M, (unsigned)v0);
+  } else {
+    p = find_piece(a, row_axis(a), (unsigned)v0);
+  }
   const int row = p.row, n = p.n;
   const int units = 2 * (a.tiles_m * a.tiles_n - a.t0);
   const float* src = a.part + (size_t)u * (128 * BN) + ((i * 4 + wave) * FN) * 256 + lane * 4;

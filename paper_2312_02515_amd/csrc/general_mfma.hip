@@ -219,7 +219,9 @@ __device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const
 // launches are 57); T = 1024 300 and 287, 293 and 280 us.  bf16, T = 2048, 4100 x 4100, whole tiles and quarters: 113 and
 // 119 us, bound by LDS traffic and the wait for each tile's loads.
 // QUARTERS: tiles of 64 x 64 that are quarters of 128 x 128 tiles.
-template <typename T, int BM, int BN, bool NN, int NSEG, bool QUARTERS>
+// PACKED (64 x 64): many tasks of few rows, whose pieces of 32 rows would hold few rows each: pieces hold rows of several
+// tasks, and the LoRA term is added task by task, to the task's own rows only (a select, no product with zeros).
+template <typename T, int BM, int BN, bool NN, int NSEG, bool QUARTERS, bool PACKED>
 __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   constexpr int V = kV<T>, BK = 8 * V;
   constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
@@ -238,9 +240,14 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   if (QUARTERS && col0 >= N) return;                 // a quarter beyond the right edge
 
   RowPiece pc[NA];
-  const RowAxis axis = row_axis(a);
+  if constexpr (PACKED) {
 #pragma unroll
-  for (int f = 0; f < NA; ++f) pc[f] = find_piece(a, axis, (unsigned)bt.tm * BM + 32 * f);
+    for (int f = 0; f < NA; ++f) pc[f] = packed_piece(a.M, (unsigned)bt.tm * BM + 32 * f);
+  } else {
+    const RowAxis axis = row_axis(a);
+#pragma unroll
+    for (int f = 0; f < NA; ++f) pc[f] = find_piece(a, axis, (unsigned)bt.tm * BM + 32 * f);
+  }
 
   if (QUARTERS && pc[0].n == 0) return;              // ... or below the last row
 
@@ -484,10 +491,54 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
         RowPiece p = pc[i];
         if (wm == 1) p = pc[NA / 2 + i];
         const int task = __builtin_amdgcn_readfirstlane(p.task);
+        const T* lrow = L + (size_t)(p.row + (l32 < p.n ? l32 : p.n - 1)) * ldz;
+        if constexpr (PACKED) {
+          // task by task: the others' rows are computed from whatever L holds there and left out
+          const TaskWalk walk = task_walk(a);
+          const int row = __builtin_amdgcn_readfirstlane(p.row), end = row + __builtin_amdgcn_readfirstlane(p.n);
+          for (int k = first_task(a, row); k < a.K && row < end; ++k) {
+            const int b = task_begin(walk, k, a.off[kMaxK]);
+            if (b >= end) break;
+            const int lo = b - row, hi = task_begin(walk, k + 1, a.off[kMaxK]) - row;
+            if (hi <= lo) continue;
+            const int r = a.rank[g][k];
+            const T* R = static_cast<const T*>(a.R[g].p[k]);
+            f32x16 sum[FN];
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) sum[j][e] = 0.f;
+#pragma unroll 2
+            for (int q0 = 0; q0 < r; q0 += 2 * V) {
+              const int q = q0 + lhi * V;
+              const u32x4 lf = *reinterpret_cast<const typename Piece16<T>::type*>(lrow + q);
+#pragma unroll
+              for (int j = 0; j < FN; ++j) {
+                int n = real_column<T, NN>(col0 + wn * WN + 32 * j + l32, N);
+                n = n >= 0 ? n : N - 1;
+                union {
+                  u32x4 v;
+                  T e[V];
+                } rf;
+#pragma unroll
+                for (int e = 0; e < V; ++e)
+                  rf.e[e] = q + e < r ? (NN ? R[(size_t)(q + e) * N + n] : R[(size_t)n * r + q + e]) : T(0.f);
+                mma32(sum[j], lf, rf.v, T{});
+              }
+            }
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+              for (int e = 0; e < 16; ++e) {
+                const int o = 8 * (e / 4) + 4 * lhi + e % 4;
+                acc[i][j][e] += o >= lo && o < hi ? sum[j][e] : 0.f;
+              }
+          }
+          continue;
+        }
         if (task < 0) continue;
         const int r = a.rank[g][task];
         const T* R = static_cast<const T*>(a.R[g].p[task]);
-        const T* lrow = L + (size_t)(p.row + (l32 < p.n ? l32 : p.n - 1)) * ldz;
         for (int q0 = 0; q0 < r; q0 += 2 * V) {
           const int q = q0 + lhi * V;                // q + V <= ldz: ldz is a multiple of 16
           const u32x4 lf = *reinterpret_cast<const typename Piece16<T>::type*>(lrow + q);
@@ -536,6 +587,7 @@ struct GenReduceArgs {
   void* C;
   const float* part;
   int M, N, tiles_m, tiles_n, parts, units, t0;
+  int packed;                            // as the product's PACKED
   int K;
   int off[kMaxK + 1];
 };
@@ -548,7 +600,8 @@ __global__ __launch_bounds__(256) void k_gen_reduce(const GenReduceArgs a) {
   const int j = blockIdx.x % FN, i = blockIdx.x / FN % FM, tile = blockIdx.x / (FM * FN);
   const BlockTile bt = tile_of_unit<QUARTERS>(a, tile);
   if (QUARTERS && bt.tn * BN >= a.N) return;
-  const RowPiece p = find_piece(a, row_axis(a), (unsigned)bt.tm * BM + wm * WM + 32 * i);
+  const unsigned v0 = (unsigned)bt.tm * BM + wm * WM + 32 * i;
+  const RowPiece p = a.packed ? packed_piece(a.M, v0) : find_piece(a, row_axis(a), v0);
   if (p.n <= 0) return;
   const float* src = a.part + (size_t)tile * (BM * BN) + ((wave * FM + i) * FN + j) * 1024 + lane * 4;
   const size_t step = (size_t)a.units * (BM * BN);
@@ -1134,6 +1187,7 @@ struct GemmPlan {
   bool skinny, small;
   int tiles_m, tiles_n, parts;           // of 16 x 64, 64 x 64 (small) or 128 x 128
   int whole;                             // 128 x 128: tiles [0, whole) as such, the others in quarters (small: 0)
+  bool packed;                           // rows of several tasks in a piece
 };
 constexpr int kMaxParts = 16, kMostUnits = 1024, kTilesPerPart = 4;   // (contraction tiles of 128 bytes per row)
 // us per contraction tile: a block alone on its CU, and the share of one among several; and per 16 ranks of the
@@ -1183,10 +1237,11 @@ bool general_skinny(const SegTable& st, int M, int N, long long Kd, int dtype) {
 namespace {
 // (`steps16` steps of 16 ranks over all operand pairs)
 GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int steps16, bool nn, int dtype, size_t scratch_limit) {
-  const long long mv = virtual_rows(st, M);
-  if (general_skinny(st, M, N, Kd_total, dtype)) return GemmPlan{true, true, (int)((mv + 15) / 16), (N + 63) / 64, 1, 0};
+  if (general_skinny(st, M, N, Kd_total, dtype)) return GemmPlan{true, true, (int)((virtual_rows(st, M) + 15) / 16), (N + 63) / 64, 1, 0, false};
   GemmPlan p;
   p.skinny = false;
+  p.packed = false;
+  const long long mv = virtual_rows(st, M);
   const long long t128 = ((mv + 127) / 128) * ((N + 127) / 128);
   p.small = t128 < 256;
   const int b = p.small ? 64 : 128;
@@ -1196,13 +1251,14 @@ GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int ste
   const StepTimes& t = kSteps[dtype == MLORA_F32 ? 0 : 1];
   p.parts = 1;
   p.whole = p.small ? 0 : (int)tiles;
+  double us = 6 + (double)kt * rounds_us(tiles, t.large_alone, t.large);
   if (p.small) {
     // The LoRA term and 1.25 us: without the one and with 1, high ranks were cut into too many ranges.  Backward, product
     // and reduction, us with ranges of 4 contraction tiles and more whatever the rank, of 16 and more, and as chosen here:
     //   fp32  500 rows, 2000 deep, 700 columns, rank 128  48, 40, 34;   500 x 1000 x 1000, rank 128  37, 30, 30
     //   bf16  300 x 1500 x 1500, rank 128  30.6, 20.2, 20.4;   150 rows, 3000 deep, 300 columns, rank 2  12.6, 17.0, 12.9
     // (1292 products of 60 to 1500 rows: 1 % less in sum than with the first rule, none more than 6 % behind it).
-    small_tiles_us(tiles, kt, t, steps16 * (nn ? t.lora_nn : t.lora_nt), 1.25, scratch_limit, &p.parts);
+    us = small_tiles_us(tiles, kt, t, steps16 * (nn ? t.lora_nn : t.lora_nt), 1.25, scratch_limit, &p.parts);
   } else if (tiles % 256 != 0) {
     const long long q = tiles / 256 * 256;
     int parts;
@@ -1213,7 +1269,21 @@ GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int ste
     if ((double)kt * rounds_us(q, t.large_alone, t.large) + rest < (double)kt * rounds_us(tiles, t.large_alone, t.large)) {
       p.whole = (int)q;
       p.parts = parts;
+      us = 6 + (double)kt * rounds_us(q, t.large_alone, t.large) + rest;
     }
+  }
+  if (packed_rows(st, M) && ((M + 127LL) / 128) * ((N + 127) / 128) < 256) {
+    // 64 x 64 tiles of packed rows: the LoRA terms of a piece's tasks one after the other.  Padded -> packed, us:
+    // fp32 364 rows of 47 tasks, 2896 -> 384 49 -> 40, 2896 -> 3968 334 -> 122, the summed input gradient of both
+    // 364 -> 167; but 41 rows of 33 tasks, 2816 -> 384 32 -> 51, which the estimate leaves padded.
+    long long live = 0;
+    for (int k = 0; k < st.K; ++k) live += st.off[k + 1] > st.off[k];
+    const double in_piece = (double)live * 32 / M + 1;
+    const int tm = (M + 63) / 64, tn = (N + 63) / 64;
+    int parts;
+    const double packed_us = small_tiles_us((long long)tm * tn, kt, t, steps16 * (nn ? t.lora_nn : t.lora_nt) * (in_piece < live ? in_piece : (double)live),
+                                            1.25, scratch_limit, &parts);
+    if (packed_us < 0.93 * us) return GemmPlan{false, true, tm, tn, parts, 0, true};
   }
   return p;
 }
@@ -1230,13 +1300,14 @@ hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch,
     hipLaunchKernelGGL((k_gen_skinny<T, NN, NSEG>), dim3((unsigned)tiles), dim3(512), 0, s, a);
     return hipGetLastError();
   }
-  if (pl.whole > 0) hipLaunchKernelGGL((k_gen_gemm<T, 128, 128, NN, NSEG, false>), dim3((unsigned)pl.whole), dim3(256), 0, s, a);
+  if (pl.whole > 0) hipLaunchKernelGGL((k_gen_gemm<T, 128, 128, NN, NSEG, false, false>), dim3((unsigned)pl.whole), dim3(256), 0, s, a);
   if (pl.whole == tiles) return hipGetLastError();
   a.parts = pl.parts;
   a.units = pl.small ? tiles : 4 * (tiles - pl.whole);
   const dim3 grid((unsigned)(a.units * pl.parts));
-  if (pl.small) hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG, false>), grid, dim3(256), 0, s, a);
-  else hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG, true>), grid, dim3(256), 0, s, a);
+  if (pl.packed) hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG, false, true>), grid, dim3(256), 0, s, a);
+  else if (pl.small) hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG, false, false>), grid, dim3(256), 0, s, a);
+  else hipLaunchKernelGGL((k_gen_gemm<T, 64, 64, NN, NSEG, true, false>), grid, dim3(256), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || pl.parts == 1) return e;
   GenReduceArgs r;
@@ -1249,6 +1320,7 @@ hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch,
   r.parts = a.parts;
   r.units = a.units;
   r.t0 = a.t0;
+  r.packed = pl.packed;
   r.K = a.K;
   for (int k = 0; k <= kMaxK; ++k) r.off[k] = a.off[k];
   if (pl.small) hipLaunchKernelGGL((k_gen_reduce<T, 64, 64, NN, false>), dim3((unsigned)a.units), dim3(256), 0, s, r);

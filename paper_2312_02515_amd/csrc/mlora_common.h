@@ -62,6 +62,9 @@ inline long long virtual_rows(const SegTable& st, int M) {
   }
   return mv;
 }
+// Whether the pieces of 32 rows are packed instead: rows of several tasks in one piece, whose LoRA terms are added
+// task by task and row by row.  Taken where the padding makes a quarter more rows (tasks of few rows).
+inline bool packed_rows(const SegTable& st, int M) { return 4 * virtual_rows(st, M) > 5LL * M && M > 32; }
 inline long long most_virtual_rows(int K, int T) {
   const long long padded = (long long)T + 31LL * (K + 2), apart = 32LL * T;
   return padded < apart ? padded : apart;

@@ -87,6 +87,30 @@ __device__ __forceinline__ RowPiece find_piece(const Args& a, const RowAxis& x, 
   return RowPiece{first + (int)o, len - (int)o < 32 ? len - (int)o : 32, task};
 }
 
+// The packed axis (many short tasks, see packed_rows): the rows themselves, 32 at a time, whatever their tasks
+__device__ __forceinline__ RowPiece packed_piece(int M, unsigned v0) {
+  const int left = M - (int)v0;
+  return left > 0 ? RowPiece{(int)v0, left < 32 ? left : 32, -1} : RowPiece{M - 1, 0, -1};
+}
+// ... the tasks of rows [row, row + n): k from first() on, as long as their rows begin inside
+struct TaskWalk {
+  int off;                 // lane k: first row of task k (entries from K on: the end of the last one's rows)
+  int K;
+};
+template <typename Args>
+__device__ __forceinline__ TaskWalk task_walk(const Args& a) {
+  return TaskWalk{a.off[threadIdx.x & 63], a.K};
+}
+__device__ __forceinline__ int task_begin(const TaskWalk& w, int k, int rows_end) {
+  return k < 64 ? __builtin_amdgcn_readlane(w.off, k) : rows_end;
+}
+// the first task whose rows end behind `row`
+template <typename Args>
+__device__ __forceinline__ int first_task(const Args& a, int row) {
+  const int lane = threadIdx.x & 63;
+  return __builtin_popcountll(__ballot(lane < a.K && a.off[lane + 1] <= row));
+}
+
 // rows of a block of the low-rank kernels: task and row range of block b when tasks are cut into
 // blocks of TM rows
 template <int TM, typename Args>

@@ -37,6 +37,19 @@ CASES = [
     ((9268, 1032, 632, [4000, 33, 5000], [64, 8, 20], 20), {"dX": "whole"}),
 ]
 
+# Many tasks of few rows, whose rows are packed in pieces of 32 (half tiles, and 64 x 64 tiles of the general kernel): the
+# tiles are those of the rows alone.  Empty tasks, tasks of one row, rows of no task before, between and after.
+_MANY = [(5 * k) % 17 for k in range(60)]
+_FEW = [(3 * k) % 16 for k in range(47)]
+PACKED = [
+    ("bf16", (494, 4096, 4096, _MANY, [1 + k % 30 for k in range(60)], 9), {"Y": "halves", "Y_tiles": 32, "dX_tiles": 32}),
+    ("bf16", (494, 4104, 4104, _MANY, [8 * (1 + k % 4) for k in range(60)], 9), {"Y": "halves", "Y_tiles": 34, "dX_tiles": 34}),
+    ("f32", (367, 2896, 388, _FEW, [1 + 3 * k % 20 for k in range(47)], 9), {"Y": "64", "Y_tiles": 42}),
+    ("f32", (367, 388, 2896, _FEW, [1 + 3 * k % 20 for k in range(47)], 9), {"dX": "64", "dX_tiles": 42}),
+    ("bf16", (367, 2501, 1003, _FEW, [1 + 3 * k % 20 for k in range(47)], 9), {"Y": "64", "Y_tiles": 96}),
+    ("bf16", (367, 1003, 2501, _FEW, [1 + 3 * k % 20 for k in range(47)], 9), {"dX": "64", "dX_tiles": 96}),
+]
+
 # Low-rank products: few rows of deep contractions in ranges, in the general kernel (fp32, and features that are no
 # multiple of 64) and in blocks of one wave; ranks above 64 that are no multiple of 4 in the general kernel
 ROWS = [

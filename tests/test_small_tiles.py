@@ -3,7 +3,7 @@ but not of 64), and low-rank products of few rows in contraction ranges, at the 
 import pytest
 import torch
 
-from tests.small_tile_cases import CASES, ROWS
+from tests.small_tile_cases import CASES, PACKED, ROWS
 from tests.test_host_abi import mb  # noqa: F401  (a fixture)
 from tests.test_launch_plans import plan
 
@@ -15,22 +15,22 @@ def test_sizes_take_their_forms(mb, case, want):  # noqa: F811
     assert {k: got[k] for k in want} == want
 
 
-@pytest.mark.parametrize("dtype,case,want", ROWS)
-def test_low_rank_sizes_take_their_forms(mb, dtype, case, want):  # noqa: F811
+@pytest.mark.parametrize("dtype,case,want", ROWS + PACKED)
+def test_few_rows_sizes_take_their_forms(mb, dtype, case, want):  # noqa: F811
     T, h, d, tokens, ranks, lead = case
     got = plan(mb, T, h, d, tokens, ranks, lead, f32=dtype == "f32")
     assert {k: got[k] for k in want} == want
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,case", [(t, c) for t, c, _ in ROWS])
-def test_low_rank_forms(dtype, case):
+@pytest.mark.parametrize("dtype,case", [(t, c) for t, c, _ in ROWS + PACKED])
+def test_few_rows_forms(dtype, case):
     from tests.parity_util import TOL, check_full, run_hip
     from tests.test_gpu_general import _inputs
     T, h, d, tokens, ranks, lead = case
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
     inp = _inputs(T, h, d, tokens, ranks, dt, lead=lead, seed=93)
-    check_full(inp, run_hip(inp), TOL[dt], label=f"low-rank {dtype} {case}")
+    check_full(inp, run_hip(inp), TOL[dt], label=f"few rows {dtype} {case[:3]}")
 
 
 @pytest.mark.gpu
@@ -52,6 +52,7 @@ def test_small_tile_forms(case):
     (600, 1016, 520, [63, 65, 1, 300], [8, 32, 33, 64], 3),
     (128, 256, 256, [20, 20, 20, 60], [8, 64, 16, 9], 4),
     (9268, 1032, 136, [4000, 33, 5000], [128, 8, 33], 20),
+    PACKED[0][1], PACKED[5][1],
 ])
 def test_small_tile_isolation(case):
     from tests.parity_util import run_hip
@@ -81,3 +82,14 @@ def test_small_tile_groups(h, ds):
     from tests.parity_util import TOL
     ins = _group_inputs(500, h, ds, [100, 197, 170], [[16, 8, 64]] * len(ds), torch.bfloat16, lead=3, seed=92)
     check_group(ins, run_group(ins), TOL[torch.bfloat16])
+
+
+# ... of packed rows in the general kernel
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_packed_group(dtype):
+    from tests.test_gpu_groups import _group_inputs, check_group, run_group
+    from tests.parity_util import TOL
+    T, _, _, tokens, _, lead = PACKED[2][1]
+    ins = _group_inputs(T, 1001, [385, 1500], tokens, [[1 + k % 9 for k in range(len(tokens))]] * 2, dtype, lead=lead, seed=94)
+    check_group(ins, run_group(ins), TOL[dtype])
