@@ -308,6 +308,24 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
             : launch<false, 1>(a, scratch, scratch_bytes, st, stream);
 }
 
+SmallForm gemm_small_nt(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, const bf16* L, int ldz, const SegTable& st,
+                        const PtrTable& R, size_t limit, gemmk::GemmArgs<1>* a, int* groups, int* parts) {
+  if (skinny(st, M, N, Kd)) return kSkinny;
+  const Plan pl = plan_gemm(st, M, N, (Kd + 63) / 64, 1, limit);
+  if (pl.small == 0) return kNotSmall;
+  fill_common(a, C, M, N, st);
+  a->A[0] = A;
+  a->Bm[0] = Bm;
+  a->L[0] = L;
+  a->Kd[0] = Kd;
+  a->ldz[0] = ldz;
+  for (int k = 0; k < kMaxK; ++k) a->rank[0][k] = (unsigned char)(k < st.K ? st.rank[k] : 0);
+  a->R[0] = R;
+  *groups = pl.small;
+  *parts = pl.parts;
+  return kRing;
+}
+
 GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_bytes) {
   const long long total = (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN);
   if (skinny(st, M, N, Kd)) return GemmForm{MLORA_FORM_HALVES, 1, 0, (int)total, 16};

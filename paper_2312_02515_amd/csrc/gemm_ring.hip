@@ -9,6 +9,14 @@ template <int G, int NS, bool NN, int NSEG>
 void launch_tile(const gemmk::GemmArgs<NSEG>& a, hipStream_t s) {
   const int units = a.tiles_m * a.tiles_n;
   hipLaunchKernelGGL((ringk::k_gemm_ring<G, NS, NN, NSEG>), dim3((unsigned)(units * a.parts)), dim3(256 * G), 0, s, a);
+  launch_ring_reduce(a, s);
+}
+
+}  // namespace
+
+template <int NSEG>
+void launch_ring_reduce(const gemmk::GemmArgs<NSEG>& a, hipStream_t s) {
+  const int units = a.tiles_m * a.tiles_n;
   if (a.parts == 1) return;
   ringk::RingReduceArgs r;
   r.C = a.C;
@@ -22,8 +30,15 @@ void launch_tile(const gemmk::GemmArgs<NSEG>& a, hipStream_t s) {
   for (int k = 0; k <= kMaxK; ++k) r.off[k] = a.off[k];
   hipLaunchKernelGGL(ringk::k_ring_reduce, dim3((unsigned)(4 * units)), dim3(256), 0, s, r);
 }
+template void launch_ring_reduce<1>(const gemmk::GemmArgs<1>&, hipStream_t);
 
-}  // namespace
+void ring_tiles(gemmk::GemmArgs<1>* a, const SegTable& st, int parts, float* scratch) {
+  a->tiles_m = (int)((virtual_rows(st, a->M) + 63) / 64);
+  a->tiles_n = (a->N + 63) / 64;
+  a->t0 = 0;
+  a->parts = parts;
+  a->part = scratch;
+}
 
 template <int NSEG>
 void launch_ring(gemmk::GemmArgs<NSEG> a, const SegTable& st, bool nn, int groups, int parts, float* scratch, hipStream_t s) {

@@ -40,22 +40,22 @@ __device__ __forceinline__ Tile tile_of(int t, int tiles_m, int tiles_n) {
   return Tile{first + in_g % gm, in_g / gm};
 }
 
+template <int G, int NS> constexpr int kRingLds = G * NS * 2 * 64 * 128;
 template <int G, int NS, bool NN, int NSEG>
-__global__ __launch_bounds__(256 * G, G == 1 ? 3 : 2) void k_gemm_ring(const GemmArgs<NSEG> ga) {
+__device__ __forceinline__ void ring_body(const GemmArgs<NSEG>& ga, int bid, char* sm) {
   constexpr int BK = 64, BM = 64, BN = 64, NFR = 2;
   constexpr int ABYTES = BM * 128, SBYTES = 2 * ABYTES;
   constexpr int LP = 2, PER_TILE = 2 * LP;             // wave-wide loads of 1 KiB per wave and tile: A, Bm
   static_assert((NS - 2) * PER_TILE < 64 && NS >= 3, "vmcnt range");
   static_assert(G == 1 || G == 2, "groups of four waves");
   static_assert(G * NS * SBYTES >= (G == 1 ? 48 : 64) * 1024, "the waves' sums fit the rings");
-  __shared__ __attribute__((aligned(1024))) char sm[G * NS * SBYTES];
 
   const int N = ga.N;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3), grp = G == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
   char* const ring = sm + grp * (NS * SBYTES);
   const int units = ga.tiles_m * ga.tiles_n, per = units * ga.parts / 8;
-  const int bid = blockIdx.x, u = bid < 8 * per ? (bid % 8) * per + bid / 8 : bid;
+  const int u = bid < 8 * per ? (bid % 8) * per + bid / 8 : bid;
   const int unit = u / ga.parts, part = u % ga.parts;
   const Tile bt = tile_of(unit, ga.tiles_m, ga.tiles_n);
   const int col0 = bt.tn * BN;
@@ -350,6 +350,12 @@ __global__ __launch_bounds__(256 * G, G == 1 ? 3 : 2) void k_gemm_ring(const Gem
     const uint4 v = *(const uint4*)(sm + m * 128 + ((c ^ (m & 7)) << 4));
     if (o < pc[it].n && col < N) *(uint4*)(ga.C + (size_t)(pc[it].row + o) * N + col) = v;
   }
+}
+
+template <int G, int NS, bool NN, int NSEG>
+__global__ __launch_bounds__(256 * G, G == 1 ? 3 : 2) void k_gemm_ring(const GemmArgs<NSEG> ga) {
+  __shared__ __attribute__((aligned(1024))) char sm[kRingLds<G, NS>];
+  ring_body<G, NS, NN, NSEG>(ga, blockIdx.x, sm);
 }
 
 // Adds the contraction ranges in order and writes the rows: block = a quarter of each quadrant of a tile, a wave one of

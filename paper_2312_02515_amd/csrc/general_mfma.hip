@@ -16,6 +16,8 @@
 // operands use the same one, which is what lets a lane feed its four MFMAs from one 16-byte piece.
 #include <type_traits>
 
+#include "gemm_ring.h"
+#include "gemm_ring_kernel.h"
 #include "mfma_staging.h"
 #include "../../include/mlora_testing.h"
 #include "mlora_common.h"
@@ -221,21 +223,20 @@ __device__ __forceinline__ void store_frag(const f32x16& acc, T* C, int N, const
 // QUARTERS: tiles of 64 x 64 that are quarters of 128 x 128 tiles.
 // PACKED (64 x 64): many tasks of few rows, whose pieces of 32 rows would hold few rows each: pieces hold rows of several
 // tasks, and the LoRA term is added task by task, to the task's own rows only (a select, no product with zeros).
+template <int BM, int BN> constexpr int kGemmLds = 2 * (BM + BN) * 128;
 template <typename T, int BM, int BN, bool NN, int NSEG, bool QUARTERS, bool PACKED>
-__global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
+__device__ __forceinline__ void gemm_body(const GenGemmArgs<NSEG>& a, int bid, char* sm) {
   constexpr int V = kV<T>, BK = 8 * V;
   constexpr int WM = BM / 2, WN = BN / 2, FM = WM / 32, FN = WN / 32;
   constexpr int NA = BM / 32, NB = BN / 32;          // pieces per thread and tile of each operand
   constexpr int ABYTES = BM * 128, BBYTES = BN * 128;
   constexpr int CPR = BN / V;                        // pieces per row of the NN weight tile
   constexpr bool B16 = sizeof(T) == 2;
-  __shared__ __attribute__((aligned(1024))) char sm[2 * (ABYTES + BBYTES)];
-
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int l32 = lane & 31, lhi = lane >> 5;
-  const BlockTile bt = block_tile<QUARTERS>(a, blockIdx.x);
+  const BlockTile bt = block_tile<QUARTERS>(a, bid);
   const int part = bt.part, col0 = bt.tn * BN, N = a.N;
   if (QUARTERS && col0 >= N) return;                 // a quarter beyond the right edge
 
@@ -582,6 +583,12 @@ __global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
   }
 }
 
+template <typename T, int BM, int BN, bool NN, int NSEG, bool QUARTERS, bool PACKED>
+__global__ __launch_bounds__(256) void k_gen_gemm(const GenGemmArgs<NSEG> a) {
+  __shared__ __attribute__((aligned(1024))) char sm[kGemmLds<BM, BN>];
+  gemm_body<T, BM, BN, NN, NSEG, QUARTERS, PACKED>(a, blockIdx.x, sm);
+}
+
 // Adds the parts of k_gen_gemm in order; block = fragment (i, j) of each of a tile's four waves.
 struct GenReduceArgs {
   void* C;
@@ -870,11 +877,11 @@ __global__ __launch_bounds__(256) void k_gen_rows_reduce(const GenRowsArgs a) {
 // The base product of k_gen_gemm for small problems: block = 16 rows x 64 columns, its 8 waves split the
 // contraction as in k_gen_rows (LoRA term: a second stretch of it), operands straight from memory.
 // ------------------------------------------------------------------------------------------
+constexpr int kSkinnySums = 4 * 4 * 256;
 template <typename T, bool NN, int NSEG>
-__global__ __launch_bounds__(512, 4) void k_gen_skinny(const GenGemmArgs<NSEG> a) {
+__device__ __forceinline__ void skinny_body(const GenGemmArgs<NSEG>& a, int bid, float* red) {
   constexpr int NW = 8, VW = 4;
-  __shared__ float red[NW / 2 * VW * 256];
-  const int tm = blockIdx.x % a.tiles_m, tn = blockIdx.x / a.tiles_m;
+  const int tm = bid % a.tiles_m, tn = bid / a.tiles_m;
   const int N = a.N, col0 = tn * 16 * VW;
   RowPiece p = find_piece(a, row_axis(a), 16u * tm);
   if (p.n <= 0) return;
@@ -907,6 +914,11 @@ __global__ __launch_bounds__(512, 4) void k_gen_skinny(const GenGemmArgs<NSEG> a
     if (o < p.n && col < N) C[(size_t)(p.row + o) * N + col] = from_f32<T>(sum);
   }
 }
+template <typename T, bool NN, int NSEG>
+__global__ __launch_bounds__(512, 4) void k_gen_skinny(const GenGemmArgs<NSEG> a) {
+  __shared__ float red[kSkinnySums];
+  skinny_body<T, NN, NSEG>(a, blockIdx.x, red);
+}
 
 // ------------------------------------------------------------------------------------------
 // Gradients, contraction over a task's tokens:
@@ -936,7 +948,7 @@ struct GenGradArgs {
 };
 
 template <typename T, int NQ, bool WIDE_FIRST>
-__device__ __forceinline__ void grad_body(const GenGradArgs& a, int ch, int sp, int k) {
+__device__ __forceinline__ void grad_body(const GenGradArgs& a, int c0, int sp, int k) {
   constexpr int GT = sizeof(T) == 2 ? 32 : 4;        // tokens per MFMA
   constexpr int TE = GT / 4;                         // ... of which a lane carries TE
   const int wide = a.wide;
@@ -947,9 +959,7 @@ __device__ __forceinline__ void grad_body(const GenGradArgs& a, int ch, int sp, 
     hi = lo + len < hi ? lo + len : hi;
   }
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kg = lane >> 4;
-  const int c0 = (ch * 4 + wave) * 64;
   if (c0 >= wide) return;
   const int r = a.rank[k];
   // lane i's four columns start here: a piece that crosses the end is loaded so that it ends there and is not
@@ -1079,22 +1089,58 @@ __device__ __forceinline__ void grad_body(const GenGradArgs& a, int ch, int sp, 
   }
 }
 
-// the body for the task's own rank, of NQ groups of 16 columns at most
+// the body for the task's own rank, of NQ groups of 16 columns at most; a chunk is the four columns of 64 of four waves
 template <typename T, int NQ, bool WIDE_FIRST>
 __device__ __forceinline__ void gen_grad_body(const GenGradArgs& a, int bid) {
   const int ch = bid % a.chunks, sp = bid / a.chunks % a.splits, k = bid / (a.chunks * a.splits);
-  const int r = a.rank[k];
-  if (NQ == 1 || r <= 16) grad_body<T, 1, WIDE_FIRST>(a, ch, sp, k);
-  else if (NQ == 2 || r <= 32) grad_body<T, 2, WIDE_FIRST>(a, ch, sp, k);
-  else if (NQ == 4 || r <= 64) grad_body<T, 4, WIDE_FIRST>(a, ch, sp, k);
-  else grad_body<T, 8, WIDE_FIRST>(a, ch, sp, k);
+  const int r = a.rank[k], c0 = (ch * 4 + (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 3)) * 64;
+  if (NQ == 1 || r <= 16) grad_body<T, 1, WIDE_FIRST>(a, c0, sp, k);
+  else if (NQ == 2 || r <= 32) grad_body<T, 2, WIDE_FIRST>(a, c0, sp, k);
+  else if (NQ == 4 || r <= 64) grad_body<T, 4, WIDE_FIRST>(a, c0, sp, k);
+  else grad_body<T, 8, WIDE_FIRST>(a, c0, sp, k);
+}
+// block `bid` of four waves: dB (the first blocks_b blocks) or dA
+template <typename T, int NQ>
+__device__ __forceinline__ void gen_grads_body(const GenGradArgs& b, const GenGradArgs& a, int blocks_b, int blocks, int bid) {
+  if (bid < blocks_b) gen_grad_body<T, NQ, false>(b, bid);
+  else if (bid < blocks) gen_grad_body<T, NQ, true>(a, bid - blocks_b);
 }
 
 // dB (the first blocks_b blocks) and dA of one call
 template <typename T, int NQ>
 __global__ __launch_bounds__(256) void k_gen_grad(const GenGradArgs b, const GenGradArgs a, int blocks_b) {
-  if ((int)blockIdx.x < blocks_b) gen_grad_body<T, NQ, false>(b, blockIdx.x);
-  else gen_grad_body<T, NQ, true>(a, blockIdx.x - blocks_b);
+  gen_grads_body<T, NQ>(b, a, blocks_b, gridDim.x, blockIdx.x);
+}
+
+// Both gradients (the first blocks, which take longest) and the input gradient's product in one launch: neither reads what the other
+// writes, each leaves most of the chip idle in a small call, and a launch costs 4 us.  Backward calls, two launches and the ranges'
+// reduction -> one, us: bf16 913 x 1000 -> 1500 (3 tasks) 28.9 -> 22.9, 1024 -> 1536 21.9 -> 16.4, 1000 x 3000 -> 1000 33.0 -> 26.0,
+// 400 x 64 -> 64 13.6 -> 11.1; fp32 128 x 256 -> 256 14.4 -> 11.2, 500 x 700 -> 1000 34.2 -> 27.1, 1000 x 300 -> 1500 44.1 -> 37.3.
+struct BackArgs {
+  GenGradArgs b, a;
+  int blocks_b, blocks;
+  int lead;              // blocks of the launch that hold gradients
+};
+template <typename T, int NQ>
+__global__ __launch_bounds__(512, NQ == 4 ? 2 : 4) void k_gen_back_skinny(const GenGemmArgs<1> g, const BackArgs p) {
+  __shared__ float red[kSkinnySums];
+  const int bid = blockIdx.x;
+  if (bid >= p.lead) skinny_body<T, false, 1>(g, bid - p.lead, red);
+  else gen_grads_body<T, NQ>(p.b, p.a, p.blocks_b, p.blocks, 2 * bid + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 8));
+}
+template <typename T, int NQ>
+__global__ __launch_bounds__(256) void k_gen_back_64(const GenGemmArgs<1> g, const BackArgs p) {
+  __shared__ __attribute__((aligned(1024))) char sm[kGemmLds<64, 64>];
+  const int bid = blockIdx.x;
+  if (bid >= p.lead) gemm_body<T, 64, 64, false, 1, false, false>(g, bid - p.lead, sm);
+  else gen_grads_body<T, NQ>(p.b, p.a, p.blocks_b, p.blocks, bid);
+}
+template <int G, int NQ>
+__global__ __launch_bounds__(256 * G, G == 1 ? 3 : 2) void k_gen_back_ring(const gemmk::GemmArgs<1> g, const BackArgs p) {
+  __shared__ __attribute__((aligned(1024))) char sm[ringk::kRingLds<G, 3>];
+  const int bid = blockIdx.x;
+  if (bid >= p.lead) ringk::ring_body<G, 3, false, 1>(g, bid - p.lead, sm);
+  else gen_grads_body<bf16, NQ>(p.b, p.a, p.blocks_b, p.blocks, G * bid + (G == 1 ? 0 : (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 8)));
 }
 
 int row_blocks(const SegTable& st, int tm) {
@@ -1328,6 +1374,25 @@ hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch,
   return hipGetLastError();
 }
 
+// adds the ranges of a product in 64 x 64 tiles, backward layout
+void launch_reduce64(const GenGemmArgs<1>& a, bool f32, hipStream_t s) {
+  GenReduceArgs r;
+  r.C = a.C;
+  r.part = a.part;
+  r.M = a.M;
+  r.N = a.N;
+  r.tiles_m = a.tiles_m;
+  r.tiles_n = a.tiles_n;
+  r.parts = a.parts;
+  r.units = a.units;
+  r.t0 = 0;
+  r.packed = 0;
+  r.K = a.K;
+  for (int k = 0; k <= kMaxK; ++k) r.off[k] = a.off[k];
+  if (f32) hipLaunchKernelGGL((k_gen_reduce<float, 64, 64, false, false>), dim3((unsigned)a.units), dim3(256), 0, s, r);
+  else hipLaunchKernelGGL((k_gen_reduce<bf16, 64, 64, false, false>), dim3((unsigned)a.units), dim3(256), 0, s, r);
+}
+
 template <int NSEG>
 hipError_t gemm_n(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st, float* scratch,
                   size_t scratch_bytes, hipStream_t s) {
@@ -1359,17 +1424,23 @@ hipError_t gemm_n(int n, const GenOperands* ops, int dtype, void* C, int M, int 
   return hipErrorInvalidValue;   // only input gradients are summed over projections
 }
 
-// Token ranges per task of up to `longest` tokens: about four blocks per CU, at least 64 tokens each
-int gen_grad_ranges(const SegTable& st, int wide_b, int wide_a, int longest) {
+// Token ranges per task of up to `longest` tokens: about four blocks per CU, at least `least` tokens each
+int gen_grad_ranges(const SegTable& st, int wide_b, int wide_a, int longest, int least) {
   const int blocks = st.K * ((wide_b + 255) / 256 + (wide_a + 255) / 256);
   int s = (1024 + blocks - 1) / blocks;
   s = s < 16 ? s : 16;
-  s = s < longest / 64 ? s : longest / 64;
+  s = s < longest / least ? s : longest / least;
   return s > 1 ? s : 1;
 }
+// 64 tokens; where the gradients share a launch with dX, which takes as long as several hundred, the ranges' reduction would
+// come on top
+constexpr int kLeastTokens = 64;
+int least_tokens(bool small, int dtype, int ldz) {
+  return !small || (dtype == MLORA_F32 && ldz > 32) ? kLeastTokens : (dtype == MLORA_F32 ? 192 : 384);
+}
 // ... as far as the scratch goes
-int gen_grad_splits(const SegTable& st, int wide_b, int wide_a, size_t scratch_limit) {
-  int s = gen_grad_ranges(st, wide_b, wide_a, longest_task(st));
+int gen_grad_splits(const SegTable& st, int wide_b, int wide_a, size_t scratch_limit, int least = kLeastTokens) {
+  int s = gen_grad_ranges(st, wide_b, wide_a, longest_task(st), least);
   while (s > 1 && grad_sum_bytes(st, s, wide_b, wide_a) > scratch_limit) --s;
   return s;
 }
@@ -1397,7 +1468,7 @@ size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype)
   size_t b = 0;
   auto most = [&](size_t v) { b = v > b ? v : b; };
   if (st.K > 0) {
-    const int s = gen_grad_ranges(st, d, h, T);
+    const int s = gen_grad_ranges(st, d, h, T, kLeastTokens);
     if (s > 1) most(grad_sum_bytes(st, s, d, h));
   }
   most(gemm_part_bytes(st.K, T, d, h, dtype));
@@ -1424,8 +1495,8 @@ double general_rows_us(const CallCtx& c, int inner, double* block_bytes) {
 RowsForm general_rows_form(const CallCtx& c, int inner) {
   return RowsForm{two_row_groups(c) ? 32 : 16, gen_rows_parts(c, inner, c.scratch_bytes)};
 }
-int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes) {
-  return st.K > 0 ? gen_grad_splits(st, wide_b, wide_a, scratch_bytes) : 1;
+int general_grad_ranges(const CallCtx& c, bool small, size_t scratch_bytes) {
+  return c.K > 0 ? gen_grad_splits(c.st, c.d, c.h, scratch_bytes, least_tokens(small, c.dtype, c.ldz)) : 1;
 }
 
 hipError_t general_Z(const CallCtx& c, const void* X, void* Z, float* scratch) {
@@ -1444,15 +1515,19 @@ hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M
                 : gemm_n<MLORA_MAX_GROUP>(n, ops, dtype, C, M, N, nn, st, scratch, scratch_bytes, stream);
 }
 
-hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G,
-                         const OutTable* dA, int accumulate, float* scratch, size_t scratch_bytes) {
-  if (c.K == 0) return hipSuccess;
+namespace {
+// both gradients' arguments; returns the blocks of dB and of both
+struct GradPlan {
+  GenGradArgs b, a;
+  int blocks_b, blocks, splits;
+};
+void plan_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G, const OutTable* dA,
+                int accumulate, bool small, float* scratch, size_t scratch_bytes, GradPlan* p) {
   const int wide_b = c.d, wide_a = dA != nullptr ? c.h : 0;
   // (planned for both outputs, so that the scratch suffices for either)
-  const int splits = gen_grad_splits(c.st, wide_b, c.h, scratch_bytes);
+  p->splits = gen_grad_splits(c.st, wide_b, c.h, scratch_bytes, least_tokens(small, c.dtype, c.ldz));
   size_t rtotal = 0;
   for (int k = 0; k < c.K; ++k) rtotal += c.st.rank[k];
-  GenGradArgs b, a;
   auto fill = [&](GenGradArgs& g, const void* big, int wide, const void* small, const OutTable& out, float* part) {
     g.Big = big;
     g.Small = small;
@@ -1461,21 +1536,112 @@ hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const 
     g.K = c.K;
     g.accumulate = accumulate;
     g.chunks = (wide + 255) / 256;
-    g.splits = splits;
+    g.splits = p->splits;
     g.part_step = rtotal * ((size_t)wide_b + wide_a);
     g.part = part;
     for (int k = 0; k <= kMaxK; ++k) g.off[k] = c.st.off[k];
     for (int k = 0; k < kMaxK; ++k) g.rank[k] = (unsigned char)c.st.rank[k];
     g.out = out;
-    return c.K * g.chunks * splits;
+    return c.K * g.chunks * p->splits;
   };
-  const int blocks_b = fill(b, dY, wide_b, Z, dB, scratch);
-  const int blocks_a = dA != nullptr ? fill(a, X, wide_a, G, *dA, scratch + rtotal * wide_b) : (a = b, 0);
-  if (c.dtype == MLORA_F32) launch_grads<float>(b, a, blocks_b, blocks_b + blocks_a, c.ldz, c.stream);
-  else launch_grads<bf16>(b, a, blocks_b, blocks_b + blocks_a, c.ldz, c.stream);
+  p->blocks_b = fill(p->b, dY, wide_b, Z, dB, scratch);
+  p->blocks = p->blocks_b + (dA != nullptr ? fill(p->a, X, wide_a, G, *dA, scratch + rtotal * wide_b) : (p->a = p->b, 0));
+}
+
+template <typename T, int NQ>
+void launch_back(const GenGemmArgs<1>& g, bool skinny, BackArgs p, hipStream_t s) {
+  const unsigned products = (unsigned)(g.tiles_m * g.tiles_n * g.parts);
+  p.lead = skinny ? (p.blocks + 1) / 2 : p.blocks;
+  if (skinny) hipLaunchKernelGGL((k_gen_back_skinny<T, NQ>), dim3(products + p.lead), dim3(512), 0, s, g, p);
+  else hipLaunchKernelGGL((k_gen_back_64<T, NQ>), dim3(products + p.lead), dim3(256), 0, s, g, p);
+}
+template <int NQ>
+void launch_back_ring(const gemmk::GemmArgs<1>& g, int groups, BackArgs p, hipStream_t s) {
+  const unsigned products = (unsigned)(g.tiles_m * g.tiles_n * g.parts);
+  p.lead = groups == 2 ? (p.blocks + 1) / 2 : p.blocks;
+  if (groups == 2) hipLaunchKernelGGL((k_gen_back_ring<2, NQ>), dim3(products + p.lead), dim3(512), 0, s, g, p);
+  else hipLaunchKernelGGL((k_gen_back_ring<1, NQ>), dim3(products + p.lead), dim3(256), 0, s, g, p);
+}
+}  // namespace
+
+hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G,
+                         const OutTable* dA, int accumulate, bool small, float* scratch, size_t scratch_bytes) {
+  if (c.K == 0) return hipSuccess;
+  GradPlan p;
+  plan_grads(c, dY, Z, dB, X, G, dA, accumulate, small, scratch, scratch_bytes, &p);
+  if (c.dtype == MLORA_F32) launch_grads<float>(p.b, p.a, p.blocks_b, p.blocks, c.ldz, c.stream);
+  else launch_grads<bf16>(p.b, p.a, p.blocks_b, p.blocks, c.ldz, c.stream);
   const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || splits == 1) return e;
-  return grad_reduce(c.st, scratch, splits, wide_b, dB, wide_a, dA != nullptr ? *dA : dB, accumulate, c.stream);
+  if (e != hipSuccess || p.splits == 1) return e;
+  return grad_reduce(c.st, scratch, p.splits, c.d, dB, dA != nullptr ? c.h : 0, dA != nullptr ? *dA : dB, accumulate, c.stream);
+}
+
+// Calls whose gradients and dX leave most CUs idle each: up to 4 Mi activation elements, ranks up to 64 (higher ones take all
+// registers), and up to 32 where the aligned gradients could run, which are faster above (2000 x 256 -> 256, 16 tasks, rank 64
+// 18 against 24 us).  The sizes alone decide, so that the gradients of a call have the same bits whatever runs beside them.
+bool small_back(const CallCtx& c) {
+  const bool fast = c.dtype == MLORA_BF16 && c.h % 64 == 0 && c.d % 64 == 0;
+  return c.K > 0 && c.T > 0 && (long long)c.T * (c.h + c.d) <= 4 << 20 && c.ldz <= (fast ? 32 : 64);
+}
+
+hipError_t general_back(const CallCtx& c, bool aligned, const void* X, const void* W, const void* dY, const void* Z, const void* G,
+                        void* dX, const OutTable& dA, const OutTable& dB, int accumulate, float* scratch) {
+  GradPlan gp;
+  plan_grads(c, dY, Z, dB, X, G, &dA, accumulate, true, scratch, c.scratch_bytes, &gp);
+  const size_t used = gp.splits > 1 ? grad_sum_bytes(c.st, gp.splits, c.d, c.h) : 0, left = c.scratch_bytes - used;
+  float* const partial = scratch + used / sizeof(float);
+  BackArgs p{gp.b, gp.a, gp.blocks_b, gp.blocks, 0};
+  const int nq = c.ldz <= 16 ? 1 : (c.ldz <= 32 ? 2 : 4);
+  hipError_t e;
+  gemmk::GemmArgs<1> r;
+  int groups = 0, parts = 1;
+  const SmallForm form = aligned ? gemm_small_nt((const bf16*)dY, (const bf16*)W, (bf16*)dX, c.T, c.h, c.d, (const bf16*)G, c.ldz,
+                                                 c.st, c.A, left, &r, &groups, &parts)
+                                 : kNotSmall;
+  if (form == kRing) {
+    ring_tiles(&r, c.st, parts, partial);
+    if (nq == 1) launch_back_ring<1>(r, groups, p, c.stream);
+    else if (nq == 2) launch_back_ring<2>(r, groups, p, c.stream);
+    else launch_back_ring<4>(r, groups, p, c.stream);
+    e = hipGetLastError();
+    if (e == hipSuccess && parts > 1) {
+      launch_ring_reduce(r, c.stream);
+      e = hipGetLastError();
+    }
+  } else {
+    const GemmPlan pl = plan_gemm(c.st, c.T, c.h, c.d, rank_steps(c.st.rank, c.K), false, c.dtype, left);
+    if (aligned ? form != kSkinny || !pl.skinny : !pl.small || pl.packed) return hipErrorNotSupported;
+    GenGemmArgs<1> g;
+    g.C = dX;
+    g.M = c.T;
+    g.N = c.h;
+    g.K = c.K;
+    for (int k = 0; k <= kMaxK; ++k) g.off[k] = c.st.off[k];
+    g.A[0] = dY;
+    g.W[0] = W;
+    g.L[0] = G;
+    g.Kd[0] = c.d;
+    g.ldz[0] = c.ldz;
+    for (int k = 0; k < kMaxK; ++k) g.rank[0][k] = (unsigned char)c.st.rank[k];
+    g.R[0] = c.A;
+    g.tiles_m = pl.tiles_m;
+    g.tiles_n = pl.tiles_n;
+    g.units = pl.tiles_m * pl.tiles_n;
+    g.parts = pl.parts;
+    g.part = partial;
+    g.t0 = 0;
+    const bool f32 = c.dtype == MLORA_F32;
+    if (nq == 1) f32 ? launch_back<float, 1>(g, pl.skinny, p, c.stream) : launch_back<bf16, 1>(g, pl.skinny, p, c.stream);
+    else if (nq == 2) f32 ? launch_back<float, 2>(g, pl.skinny, p, c.stream) : launch_back<bf16, 2>(g, pl.skinny, p, c.stream);
+    else f32 ? launch_back<float, 4>(g, pl.skinny, p, c.stream) : launch_back<bf16, 4>(g, pl.skinny, p, c.stream);
+    e = hipGetLastError();
+    if (e == hipSuccess && g.parts > 1) {
+      launch_reduce64(g, f32, c.stream);
+      e = hipGetLastError();
+    }
+  }
+  if (e != hipSuccess || gp.splits == 1) return e;
+  return grad_reduce(c.st, scratch, gp.splits, c.d, dB, c.h, dA, accumulate, c.stream);
 }
 
 }  // namespace mlora

@@ -210,38 +210,66 @@ mlora_status check_grad_tables(const mlora_problem* p, float* const* dA, float* 
   return MLORA_OK;
 }
 
+bool overlap(const void* a, const void* b, size_t bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + bytes && y < x + bytes;
+}
+
+void grad_tables(const mlora_problem* p, float* const* dA, float* const* dB, OutTable* ta, OutTable* tb) {
+  for (int k = 0; k < kMaxK; ++k) {
+    ta->p[k] = k < p->K ? dA[k] : nullptr;
+    tb->p[k] = k < p->K ? dB[k] : nullptr;
+  }
+}
+
+bool grads_aligned(const mlora_problem* p, const void* X, const void* dY, const void* Z, const void* G) {
+  return mfma_lowrank_applies(p) && aligned16(X) && aligned16(dY) && aligned16(Z) && aligned16(G);
+}
+
+hipError_t compute_G(const mlora_problem* p, const CallCtx& c, const void* X, const void* dY, const void* Z, void* G, void* scratch) {
+  float* partial = static_cast<float*>(scratch);
+  return grads_aligned(p, X, dY, Z, G) ? lowrank_rows_mfma(c, (const bf16*)dY, c.d, (bf16*)G, c.B, false, partial, c.scratch_bytes)
+                                       : general_G(c, dY, G, partial);
+}
+
 // G, dB_k and dA_k, given Z
-// (with `skip_dA` the caller computes dA_k itself from G)
+// (with `skip_dA` the caller computes dA_k itself from G; `have_G`: G has been computed; `small`: the gradients of small calls
+// that want dX, which come from the general kernel whether or not they run with dX)
 hipError_t adapter_grads_impl(const mlora_problem* p, const CallCtx& c, const void* X, const void* dY, const void* Z,
                               void* G, float* const* dA, float* const* dB, int accumulate, void* scratch,
-                              bool skip_dA = false) {
+                              bool small, bool skip_dA = false, bool have_G = false) {
   OutTable ta, tb;
-  for (int k = 0; k < kMaxK; ++k) {
-    ta.p[k] = k < p->K ? dA[k] : nullptr;
-    tb.p[k] = k < p->K ? dB[k] : nullptr;
-  }
+  grad_tables(p, dA, dB, &ta, &tb);
   float* partial = static_cast<float*>(scratch);
   accumulate = accumulate ? 1 : 0;
-  hipError_t e;
-  if (mfma_lowrank_applies(p) && aligned16(X) && aligned16(dY) && aligned16(Z) && aligned16(G)) {
-    e = lowrank_rows_mfma(c, (const bf16*)dY, c.d, (bf16*)G, c.B, false, partial, c.scratch_bytes);
-    if (e == hipSuccess)
-      e = grads_mfma(c, (const bf16*)dY, (const bf16*)Z, tb, (const bf16*)X, (const bf16*)G, skip_dA ? nullptr : &ta,
-                     accumulate, partial, c.scratch_bytes);
-  } else {
-    e = general_G(c, dY, G, partial);
-    if (e == hipSuccess) e = general_grads(c, dY, Z, tb, X, G, skip_dA ? nullptr : &ta, accumulate, partial, c.scratch_bytes);
-  }
-  return e;
+  const hipError_t e = have_G ? hipSuccess : compute_G(p, c, X, dY, Z, G, scratch);
+  if (e != hipSuccess) return e;
+  const OutTable* const a = skip_dA ? nullptr : &ta;
+  if (grads_aligned(p, X, dY, Z, G) && !small)
+    return grads_mfma(c, (const bf16*)dY, (const bf16*)Z, tb, (const bf16*)X, (const bf16*)G, a, accumulate, partial, c.scratch_bytes);
+  return general_grads(c, dY, Z, tb, X, G, a, accumulate, small, partial, c.scratch_bytes);
 }
 
 // G, dB_k, dA_k and (unless dX is NULL) dX, given Z
 hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X, const void* dY, const void* Z, void* G,
                          void* dX, float* const* dA, float* const* dB, int accumulate, void* scratch) {
-  hipError_t e = adapter_grads_impl(p, c, X, dY, Z, G, dA, dB, accumulate, scratch);
+  const bool small = dX != nullptr && small_back(c);
+  bool have_G = false;
+  if (small && !overlap(X, dX, (size_t)c.T * c.h * elem_size(p))) {
+    // the products and the gradients of a small call in one launch (not where dX overwrites the X that dA reads)
+    OutTable ta, tb;
+    grad_tables(p, dA, dB, &ta, &tb);
+    hipError_t e = compute_G(p, c, X, dY, Z, G, scratch);
+    if (e != hipSuccess) return e;
+    have_G = true;
+    e = general_back(c, mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G), X, p->W, dY, Z, G, dX, ta, tb,
+                     accumulate ? 1 : 0, static_cast<float*>(scratch));
+    if (e != hipErrorNotSupported) return e;
+  }
+  hipError_t e = adapter_grads_impl(p, c, X, dY, Z, G, dA, dB, accumulate, scratch, small, false, have_G);
   if (e == hipSuccess && dX != nullptr && p->T > 0) {
     float* partial = static_cast<float*>(scratch);
-      if (mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G))
+    if (mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G))
       return gemm_mfma((const bf16*)dY, (const bf16*)p->W, (bf16*)dX, c.T, c.h, c.d, false, (const bf16*)G, c.ldz, c.st,
                        c.A, partial, c.scratch_bytes, c.stream);
     const GenOperands o{dY, p->W, G, c.d, c.ldz, c.st.rank, &c.A};
@@ -562,7 +590,7 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
   for (int p = 0; p < P; ++p) fused = fused && aligned16(dY[p]) && aligned16(saved[p]) && aligned16(G[p]);
   for (int p = 0; p < P; ++p) {
     hipError_t e = adapter_grads_impl(ps[p], c[p], X, dY[p], saved[p], G[p], ps[0]->K > 0 ? dA[p] : nullptr,
-                                      ps[0]->K > 0 ? dB[p] : nullptr, accumulate, w, fused);  // w: behind the last G_p
+                                      ps[0]->K > 0 ? dB[p] : nullptr, accumulate, w, dX != nullptr && small_back(c[p]), fused);  // w: behind the last G_p
     if (e != hipSuccess) return hip_status(e);
   }
   if (fused) {
@@ -643,7 +671,7 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
   plan[MLORA_PLAN_Z_PARTS] = z.parts;
   plan[MLORA_PLAN_G_ROWS] = g.rows;
   plan[MLORA_PLAN_G_PARTS] = g.parts;
-  plan[MLORA_PLAN_GRADS] = c.K == 0 ? 1 : (al ? grad_splits(c.st, c.d, c.h, room) : general_grad_ranges(c.st, c.d, c.h, room));
+  plan[MLORA_PLAN_GRADS] = c.K == 0 ? 1 : (al && !small_back(c) ? grad_splits(c.st, c.d, c.h, room) : general_grad_ranges(c, small_back(c), room));
   return MLORA_OK;
 }
 

@@ -128,13 +128,19 @@ bool general_skinny(const SegTable& st, int M, int N, long long Kd, int dtype);
 GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, int dtype, size_t scratch_bytes);
 double general_rows_us(const CallCtx& c, int inner, double* block_bytes);
 RowsForm general_rows_form(const CallCtx& c, int inner);
-int general_grad_ranges(const SegTable& st, int wide_b, int wide_a, size_t scratch_bytes);
+int general_grad_ranges(const CallCtx& c, bool small, size_t scratch_bytes);
 // C = sum over the n <= MLORA_MAX_GROUP operand pairs of A op(W) + rows_k(L R_k)
 hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st,
                         float* scratch, size_t scratch_bytes, hipStream_t stream);
-// dB_k = Z^T dy_k and, unless dA is NULL, dA_k = x_k^T G
+// dB_k = Z^T dy_k and, unless dA is NULL, dA_k = x_k^T G (`small`: of a call that is small_back and wants dX)
 hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G,
-                         const OutTable* dA, int accumulate, float* scratch, size_t scratch_bytes);
+                         const OutTable* dA, int accumulate, bool small, float* scratch, size_t scratch_bytes);
+
+// Small backward calls: dX (as in general_gemm, one operand pair; `aligned`: in the forms of gemm_mfma), dA_k and dB_k in
+// one launch, and one each for ranges to add.  hipErrorNotSupported, with nothing launched: not at these sizes.
+bool small_back(const CallCtx& c);
+hipError_t general_back(const CallCtx& c, bool aligned, const void* X, const void* W, const void* dY, const void* Z, const void* G,
+                        void* dX, const OutTable& dA, const OutTable& dB, int accumulate, float* scratch);
 
 // gemm_mfma.hip : bf16 MFMA GEMM with the LoRA term as extra contraction steps
 bool gemm_mfma_ok(int M, int N, int Kd);

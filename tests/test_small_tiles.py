@@ -93,3 +93,51 @@ def test_packed_group(dtype):
     T, _, _, tokens, _, lead = PACKED[2][1]
     ins = _group_inputs(T, 1001, [385, 1500], tokens, [[1 + k % 9 for k in range(len(tokens))]] * 2, dtype, lead=lead, seed=94)
     check_group(ins, run_group(ins), TOL[dtype])
+
+
+# small backward calls, whose dX and gradients share a launch: every form of the product with one and several ranges of
+# either; overwriting, and adding to the gradients
+SMALL_BACK = [
+    (torch.float32, (128, 256, 256, [60, 60], [8, 5], 4)),                  # 16 x 64 tiles
+    (torch.bfloat16, (400, 64, 64, [100, 0, 290], [16, 3, 8], 4)),
+    (torch.bfloat16, (1001, 70, 514, [980], [40], 13)),                     # ... ranges of tokens
+    (torch.float32, (500, 700, 1001, [100, 390], [17, 4], 3)),              # 64 x 64 tiles
+    (torch.float32, (900, 300, 1500, [880], [64], 3)),                      # ... ranges of both
+    (torch.bfloat16, (913, 1000, 1500, [300, 77, 513], [8, 10, 16], 5)),
+    (torch.bfloat16, (1500, 999, 1500, [1400], [50], 5)),
+    (torch.bfloat16, (913, 1024, 1536, [300, 77, 513], [8, 10, 16], 5)),    # small aligned tiles
+    (torch.bfloat16, (300, 1216, 1984, [100, 190], [32, 5], 10)),
+    (torch.bfloat16, (60, 584, 4040, [37, 20], [12, 40], 1)),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,case", SMALL_BACK)
+def test_small_backward(dtype, case):
+    from paper_2312_02515_amd import binding as hip
+    from tests.parity_util import TOL, check_full, run_hip
+    from tests.test_gpu_general import _inputs
+    T, h, d, tokens, ranks, lead = case
+    inp = _inputs(T, h, d, tokens, ranks, dtype, lead=lead, seed=95)
+    out = run_hip(inp)
+    check_full(inp, out, TOL[dtype], label=f"small backward {case}")
+    # added to what is there: one fp32 addition behind the same sums
+    pre = [[torch.randn_like(t) for t in out[n]] for n in ("dA", "dB")]
+    acc = run_hip(inp, accumulate=True, preset_grads=pre)
+    for n, ps in zip(("dA", "dB"), pre):
+        for a, b, p in zip(acc[n], out[n], ps):
+            assert torch.equal(a, p + b), n
+    # dX in the place of X: the gradients still read X
+    prob = hip.Problem(T, h, d, inp.W, inp.seg_offsets, inp.ranks, inp.scalings, inp.A, inp.B)
+    saved, ws, X = prob.alloc_saved(), prob.alloc_workspace(), inp.X.clone()
+    Y = torch.empty_like(out["Y"])
+    hip.mlora_lora_fwd(prob, X, Y, saved, ws)
+    dA, dB = prob.alloc_grads()
+    hip.mlora_lora_bwd(prob, X, inp.dY, saved, X, dA, dB, False, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, out["Y"])
+    for a, b in zip(dA + dB, out["dA"] + out["dB"]):
+        assert torch.equal(a, b)
+    # (dX's ranges are planned with the whole scratch there: the sums may come in another order)
+    err = (X.double() - out["dX"].double()).norm() / out["dX"].double().norm()
+    assert err <= TOL[dtype]
