@@ -42,6 +42,14 @@ bool ragged_ranks(const gemmk::GemmArgs<NSEG>& a) {
   return false;
 }
 
+// whether some contraction ends in a partial tile
+template <int NSEG>
+bool partial_tiles(const gemmk::GemmArgs<NSEG>& a) {
+  for (int g = 0; g < NSEG; ++g)
+    if (a.Kd[g] % 64 != 0) return true;
+  return false;
+}
+
 // tiles [0, tiles) of 256 x 256
 template <bool NN, int NSEG>
 void launch_whole(const gemmk::GemmArgs<NSEG>& a, int tiles, hipStream_t stream) {
@@ -60,7 +68,8 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, bool packed, hipStream_t stre
   const int units = 2 * (a.tiles_m * a.tiles_n - a.t0);
   const dim3 grid(units * a.parts);
   if (packed) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, true>), grid, dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, false>), grid, dim3(256), 0, stream, a);
+  else if (partial_tiles(a)) hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, false, true>), grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL((gemmk::k_gemm_mfma<1, 4, NN, NSEG, false, false>), grid, dim3(256), 0, stream, a);
   if (a.parts == 1) return;
   gemmk::ReduceArgs r;
   r.C = a.C;
