@@ -171,7 +171,8 @@ __device__ __forceinline__ void mfma_16x16x32(f32x4& c, const bf16x8& a, const b
 // RAG of half tiles stands for PACKED: many tasks of few rows, whose pieces of 32 rows would hold few rows each.  Pieces
 // then hold rows of several tasks, and the LoRA term is added task by task, to the task's own rows only (a select, no
 // product with zeros).  855 rows of 42 tasks, 10880 -> 1728, rank 64 83 -> 70 us.
-// TAIL: whether a contraction may end in a partial tile (half tiles: the code for it costs the others 1-2 us of 34).
+// TAIL: whether a contraction may end in a partial tile (the code for it costs the others 1-2 us of 34 in half tiles, up to
+// 1 % in whole ones).
 template <int WAVES_M, int WAVES_N, bool NN, int NSEG, bool RAG, bool TAIL = true>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmArgs<NSEG> ga) {
   constexpr int BK = 64;
@@ -406,7 +407,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   };
   // One side of a partial or LoRA tile.  The loops are rolled: this code stands in every launch's path, where it is
   // fetched cold, and runs a few times at most.
-  auto masked = [](const LoadCtx& lc) { return TAIL && (lc.lora || lc.left < BK); };
+  auto masked = [](const LoadCtx& lc) { return (!HALF && lc.lora) || (TAIL && lc.left < BK); };
   // (the chunk a lane fetches: the same in every load of a wave, the rows of two loads are a multiple of 16 apart)
   const int kchunk = (lane % CPR) ^ ((RPI * wave + lane / CPR) / RW % CPR);
   static_assert(RPI * NW % (RW * CPR) == 0, "chunk of a lane");
