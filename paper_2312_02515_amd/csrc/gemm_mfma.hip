@@ -115,8 +115,10 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, bool packed, hipStream_t stre
 //
 // Small tiles (gemm_ring_kernel.h), 64 x 64 and of one or two groups of four waves, for up to 64 tiles of 256 x 256.
 // Estimates (us, measured; n tiles of `steps` contraction and LoRA tiles): one group 5 + m (0.9 + 0.19 steps), m tiles on
-// the fullest CU, but 0.25 a step where it has one; two groups, for up to 256 tiles, 6.3 + 0.4 per two steps; the
-// reduction of ranges as above.  Half or whole tiles -> small tiles, forward and backward product, us:
+// the fullest CU, but 0.25 a step for one that it runs by itself (three fit a CU, so a first, fourth, .. one: with 918
+// blocks counted as 3.6 a CU, 3230 x 7248 -> 368 took 54 + 6 us, in half tiles 40 + 6); two groups, for up to 256 tiles,
+// 6.3 + 0.4 per two steps; the reduction of ranges as above.  Half or whole tiles -> small tiles, forward and backward
+// product, us:
 //   128 rows, 256 -> 256, rank 64   15.5, 14.1 ->  6.7,  6.9     1024 x 1024 -> 1024, rank 64   23.7, 22.0 -> 10.2, 10.4
 //   220 rows, 1920 -> 2688 (10 tasks)  30.2, 26.6 -> 13.0, 14.9     2048 x 1024 -> 1024   24.8, 23.3 -> 12.9, 12.7
 //   1024 x 4096 -> 1024   27.2, 21.7 -> 20.1, 22.6     2048 x 2048 -> 2048   36.0, 33.5 -> 33.3, 32.5
@@ -150,8 +152,9 @@ double plan_small(const SegTable& st, int M, int N, int KT, int pairs, size_t sc
     const size_t bytes = p > 1 ? (size_t)n * p * 64 * 64 * sizeof(float) : 0;
     if (bytes > scratch_limit) break;
     const int steps = (KT + p - 1) / p + lora;
-    const double m = n * p <= 768 ? (double)((n * p + 255) / 256) : (double)(n * p) / 256.0;
-    const double us = 5.0 + m * (0.9 + (m > 1 ? 0.19 : 0.25) * steps) + (p > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
+    const long long m = (n * p + 255) / 256, alone = m % 3 == 1 ? 1 : 0;   // blocks of a CU, those that run by themselves
+    const double us = 5.0 + (double)(m - alone) * (0.9 + 0.19 * steps) + (double)alone * (0.9 + 0.25 * steps) +
+                      (p > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
     if (p == 1 || us < best) {
       best = us;
       *out = Plan{0, p, 1, false};

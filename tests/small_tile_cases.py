@@ -13,6 +13,10 @@ CASES = [
     # ... contraction ranges
     ((60, 4096, 576, [37, 20], [16, 64], 1), {"Y_rows": 64, "Y_parts": 8}),
     ((60, 576, 4096, [37, 20], [12, 40], 1), {"dX_rows": 64, "dX_parts": 8}),
+    # ... tiles that would leave one block to some CUs: no ranges, or half tiles in ranges
+    ((3230, 4104, 384, [1600, 1600], [64, 33], 3), {"Y_rows": 64, "Y_parts": 1}),
+    ((3230, 7248, 368, [1615, 1600], [64, 33], 3), {"Y": "halves", "Y_rows": 128, "Y_parts": 4}),
+    ((3230, 368, 7248, [1615, 1600], [64, 33], 3), {"dX": "halves", "dX_rows": 128, "dX_parts": 4}),
     # 16 x 64 tiles
     ((128, 256, 256, [60, 60], [8, 64], 4), {"Y_rows": 16, "dX_rows": 16}),
     # partial contraction tiles, one chunk more or less than a whole one; 64 x 64 tiles
