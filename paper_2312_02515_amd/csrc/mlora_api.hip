@@ -210,9 +210,9 @@ mlora_status check_grad_tables(const mlora_problem* p, float* const* dA, float* 
   return MLORA_OK;
 }
 
-bool overlap(const void* a, const void* b, size_t bytes) {
+bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
   const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
-  return x < y + bytes && y < x + bytes;
+  return x < y + b_bytes && y < x + a_bytes;
 }
 
 void grad_tables(const mlora_problem* p, float* const* dA, float* const* dB, OutTable* ta, OutTable* tb) {
@@ -255,8 +255,9 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
                          void* dX, float* const* dA, float* const* dB, int accumulate, void* scratch) {
   const bool small = dX != nullptr && small_back(c);
   bool have_G = false;
-  if (small && !overlap(X, dX, (size_t)c.T * c.h * elem_size(p))) {
-    // the products and the gradients of a small call in one launch (not where dX overwrites the X that dA reads)
+  const size_t bytes = (size_t)c.T * c.h * elem_size(p);
+  if (small && !overlap(X, bytes, dX, bytes) && !overlap(Z, (size_t)c.T * c.ldz * elem_size(p), dX, bytes)) {
+    // the products and the gradients of a small call in one launch (not where dX overwrites the X or Z that the gradients read)
     OutTable ta, tb;
     grad_tables(p, dA, dB, &ta, &tb);
     hipError_t e = compute_G(p, c, X, dY, Z, G, scratch);

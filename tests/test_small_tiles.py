@@ -141,3 +141,15 @@ def test_small_backward(dtype, case):
     # (dX's ranges are planned with the whole scratch there: the sums may come in another order)
     err = (X.double() - out["dX"].double()).norm() / out["dX"].double().norm()
     assert err <= TOL[dtype]
+    # dX in the place of the saved Z, which the gradients still read
+    n = X.numel() * X.element_size()
+    buf = torch.empty(max(n, prob.saved_bytes()), dtype=torch.uint8, device=X.device)
+    saved, dX = buf[:prob.saved_bytes()], buf[:n].view(dtype).view(T, h)
+    hip.mlora_lora_fwd(prob, inp.X, Y, saved, ws)
+    dA, dB = prob.alloc_grads()
+    hip.mlora_lora_bwd(prob, inp.X, inp.dY, saved, dX, dA, dB, False, ws)
+    torch.cuda.synchronize()
+    for a, b in zip(dA + dB, out["dA"] + out["dB"]):
+        assert torch.equal(a, b)
+    err = (dX.double() - out["dX"].double()).norm() / out["dX"].double().norm()
+    assert err <= TOL[dtype]
