@@ -242,7 +242,8 @@ int mlora_last_hip_error(void);
  *   bit 1  the low-rank products do.
  * That form takes bf16 problems whose h and d are multiples of 64, whose ranks are multiples of 8 and
  * whose W, A_k, B_k are 16-byte aligned.  Where only a rank stands in the way, both bits are set and
- * the aligned kernels run in forms for ragged ranks, a little slower; otherwise the general kernels
+ * the aligned kernels run in forms for ragged ranks, a little slower; with features that are multiples of
+ * 8 both bits are set and the base products still run aligned kernels; otherwise the general kernels
  * run (any size, alignment and dtype; matrix pipes as well, operands through registers: 2 to 3 times
  * the time in bf16, and the fp32 MFMA rate in fp32).  The answer assumes that the buffers passed to
  * the calls (X, Y, dY, dX, saved, workspace) are 16-byte aligned too, as device allocations are -- a
