@@ -6,11 +6,11 @@
 // multiples of 8 but not of 64.
 //
 // Such calls are bound by latency, not by a rate: what a block does before, between and behind its MFMAs counts.
-// A block of 4 waves (2 x 2) owns a BM x BN tile (64 x 64 or 128 x 128); contraction tiles of 64 come by direct
-// global->LDS loads into a ring of NS stages, NS - 1 tiles ahead of their use, with one barrier per
-// tile; the loop is rolled (its code is fetched cold by every launch).  The LoRA term is ceil(r_k / 64) more
-// contraction tiles per task of the tile, from the same ring, so that no load of it is waited for at the
-// end.
+// A block of one or two groups of 4 waves owns a 64 x 64 tile; the waves of a group split each contraction tile, and two
+// groups take every other one.  Contraction tiles of 64 come by direct global->LDS loads into a ring of NS stages per
+// group, NS - 1 tiles ahead of their use, with one barrier per tile; the loop is rolled (its code is fetched cold by
+// every launch).  The LoRA term is more contraction tiles from the same ring, of two slots of 32 ranks each, so that no
+// load of it is waited for at the end.
 //
 // Features that are no multiple of 64: the last contraction tile's chunks beyond the features come from 16 zero
 // bytes (a direct load cannot be masked); chunks of 8 are whole, so stores are too.
