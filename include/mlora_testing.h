@@ -40,18 +40,19 @@ int mlora_set_kernel_path(int path);
 #define MLORA_PLAN_GRADS    8  /* dA, dB: token ranges per task                                    */
 #define MLORA_PLAN_FIELDS   9
 #define MLORA_FORM_WHOLE    0  /* aligned: 256 x 256 tiles                                         */
-#define MLORA_FORM_HALVES   1  /* aligned: smaller tiles, 128 x 256 or (MLORA_PLAN_*_ROWS)
-                                  64 x 64 or 16 x 64                                               */
+#define MLORA_FORM_HALVES   1  /* aligned: 128 x 256 tiles                                         */
 #define MLORA_FORM_MIXED    2  /* aligned: whole rounds of the first, the rest as the second       */
-#define MLORA_FORM_SKINNY   3  /* features no multiples of 64: 16 x 64                             */
-#define MLORA_FORM_64       4  /* ... or fp32: 64 x 64                                             */
+#define MLORA_FORM_SKINNY   3  /* general: 16 x 64 (aligned problems of few tiles too)             */
+#define MLORA_FORM_64       4  /* general: 64 x 64                                                 */
 #define MLORA_FORM_128      5  /* general: 128 x 128; the tiles beyond whole rounds of 256 may run as
                                   quarters of 64 x 64, in the ranges that *_PARTS gives            */
+#define MLORA_FORM_RING     6  /* aligned: 64 x 64 tiles from a ring                               */
 mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan);
 
-/* The tiles of the two base products in the size that their form names (256 x 256 for the aligned
- * ones): how many run as such, and how many there are -- the others run as halves (HALVES, MIXED) or
- * quarters (128); and the rows of the smallest tiles that run: 256, 128, 64 or 16.  `tiles` (HOST, MLORA_PLAN_TILES entries) and the status as for mlora_kernel_plan. */
+/* The tiles of the two base products in the size that their form names (256 x 256 for WHOLE, HALVES and
+ * MIXED): how many run as such, and how many there are -- the others run as halves (HALVES, MIXED) or
+ * quarters (128); and the rows of the smallest tiles that run: 256, 128, 64 or 16.  `tiles` (HOST,
+ * MLORA_PLAN_TILES entries) and the status as for mlora_kernel_plan. */
 #define MLORA_PLAN_Y_WHOLE  0
 #define MLORA_PLAN_Y_TILES  1
 #define MLORA_PLAN_DX_WHOLE 2
@@ -60,6 +61,16 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan);
 #define MLORA_PLAN_DX_ROWS  5
 #define MLORA_PLAN_TILES    6
 mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles);
+
+/* The same for the summed input gradient of a group (`plan`: HOST, MLORA_PLAN_GROUP entries); returns the
+ * status of mlora_lora_group_validate. */
+#define MLORA_PLAN_GROUP_DX       0  /* form: an MLORA_FORM_*                                      */
+#define MLORA_PLAN_GROUP_DX_PARTS 1  /* contraction ranges per tile, over all projections          */
+#define MLORA_PLAN_GROUP_DX_WHOLE 2  /* tiles that run as such                                     */
+#define MLORA_PLAN_GROUP_DX_TILES 3  /* tiles                                                      */
+#define MLORA_PLAN_GROUP_DX_ROWS  4  /* rows of the smallest tiles                                 */
+#define MLORA_PLAN_GROUP          5
+mlora_status mlora_kernel_plan_group(const mlora_problem* const* ps, int P, int32_t* plan);
 
 /* Measurement aid.  While enabled, every launch of the MFMA kernels by this process is bracketed
  * by a pair of HIP events recorded on the launch stream (at most 16384 launches are kept; the

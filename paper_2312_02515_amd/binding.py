@@ -32,13 +32,14 @@ EXPORTS = ["mlora_lora_saved_bytes", "mlora_lora_workspace_bytes", "mlora_lora_v
            "mlora_lora_w8_workspace_bytes", "mlora_lora_fwd_w8", "mlora_lora_bwd_w8"]
 MLORA_STATIC_SCRATCH_BYTES = 32 << 20
 # include/mlora_testing.h: test and measurement switches
-TESTING_EXPORTS = ["mlora_set_kernel_path", "mlora_kernel_plan", "mlora_kernel_plan_tiles", "mlora_profile_kernels",
-                   "mlora_profile_kernels_read"]
+TESTING_EXPORTS = ["mlora_set_kernel_path", "mlora_kernel_plan", "mlora_kernel_plan_tiles", "mlora_kernel_plan_group",
+                   "mlora_profile_kernels", "mlora_profile_kernels_read"]
 
-# entries of mlora_kernel_plan and of mlora_kernel_plan_tiles, names of the MLORA_FORM_* values
+# entries of mlora_kernel_plan, mlora_kernel_plan_tiles and mlora_kernel_plan_group, names of the MLORA_FORM_* values
 PLAN_FIELDS = ["Y", "Y_parts", "dX", "dX_parts", "Z_rows", "Z_parts", "G_rows", "G_parts", "grads"]
 PLAN_TILES = ["Y_whole", "Y_tiles", "dX_whole", "dX_tiles", "Y_rows", "dX_rows"]
-PLAN_FORMS = ["whole", "halves", "mixed", "skinny", "64", "128"]
+PLAN_GROUP = ["dX", "dX_parts", "dX_whole", "dX_tiles", "dX_rows"]
+PLAN_FORMS = ["whole", "halves", "mixed", "skinny", "64", "128", "ring"]
 
 
 class MloraError(RuntimeError):
@@ -131,6 +132,8 @@ def _load() -> ctypes.CDLL:
     l.mlora_kernel_plan.argtypes = [pp, ctypes.POINTER(ctypes.c_int32)]
     l.mlora_kernel_plan_tiles.restype = ctypes.c_int
     l.mlora_kernel_plan_tiles.argtypes = [pp, ctypes.POINTER(ctypes.c_int32)]
+    l.mlora_kernel_plan_group.restype = ctypes.c_int
+    l.mlora_kernel_plan_group.argtypes = [ppp, ctypes.c_int, ctypes.POINTER(ctypes.c_int32)]
     l.mlora_set_kernel_path.restype = ctypes.c_int
     l.mlora_set_kernel_path.argtypes = [ctypes.c_int]
     l.mlora_profile_kernels.restype = ctypes.c_int
@@ -378,6 +381,16 @@ class Group:
 
     def alloc_workspace(self) -> torch.Tensor:
         return torch.empty(self.workspace_bytes(), dtype=torch.uint8, device=self.problems[0].device)
+
+    def kernel_plan(self) -> dict:
+        """How the launch of the summed input gradient is cut up (mlora_testing.h)."""
+        plan = (ctypes.c_int32 * len(PLAN_GROUP))()
+        st = lib.mlora_kernel_plan_group(self.c, self.P, plan)
+        if st != 0:
+            raise MloraError(st, "mlora_kernel_plan_group")
+        out = dict(zip(PLAN_GROUP, plan))
+        out["dX"] = PLAN_FORMS[out["dX"]]
+        return out
 
 
 def _ptr_array(tensors):

@@ -341,13 +341,21 @@ SmallForm gemm_small_nt(const bf16* A, const bf16* Bm, bf16* C, int M, int N, in
   return kRing;
 }
 
-GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_bytes) {
-  const long long total = (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN);
-  if (skinny(st, M, N, Kd)) return GemmForm{MLORA_FORM_HALVES, 1, 0, (int)total, 16};
-  const Plan pl = plan_gemm(st, M, N, (Kd + 63) / 64, 1, scratch_bytes);
+GemmForm gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, size_t scratch_bytes) {
+  const long long mv = virtual_rows(st, M), total = (mv + BM - 1) / BM * ((N + BN - 1) / BN);
+  long long kd = 0;
+  int kt = 0;
+  for (int g = 0; g < n; ++g) {
+    kd += Kd[g];
+    kt += (Kd[g] + 63) / 64;
+  }
+  auto tiles = [&](int rows) { return (int)((mv + rows - 1) / rows * ((N + 63) / 64)); };
+  if (skinny(st, M, N, kd)) return GemmForm{MLORA_FORM_SKINNY, 1, tiles(16), tiles(16), 16};
+  const Plan pl = plan_gemm(st, M, N, kt, n, scratch_bytes);
+  if (pl.small > 0) return GemmForm{MLORA_FORM_RING, pl.parts, tiles(64), tiles(64), 64};
   if (pl.packed) return GemmForm{MLORA_FORM_HALVES, pl.parts, 0, (M + BM - 1) / BM * ((N + BN - 1) / BN), BM / 2};
   const int form = pl.whole == total ? MLORA_FORM_WHOLE : (pl.whole == 0 ? MLORA_FORM_HALVES : MLORA_FORM_MIXED);
-  return GemmForm{form, pl.parts, pl.whole, (int)total, form == MLORA_FORM_WHOLE ? BM : (pl.small > 0 ? 64 : BM / 2)};
+  return GemmForm{form, pl.parts, pl.whole, (int)total, form == MLORA_FORM_WHOLE ? BM : BM / 2};
 }
 
 size_t gemm_partial_bytes(int K, int T, int N, int Kd) {

@@ -1476,8 +1476,15 @@ size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype)
   return b;
 }
 
-GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, int dtype, size_t scratch_bytes) {
-  const GemmPlan pl = plan_gemm(st, M, N, Kd, rank_steps(st.rank, st.K), nn, dtype, scratch_bytes);
+GemmForm general_gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, const int* const* rank, bool nn, int dtype,
+                           size_t scratch_bytes) {
+  long long kd = 0;
+  int steps = 0;
+  for (int g = 0; g < n; ++g) {
+    kd += Kd[g];
+    steps += rank_steps(rank[g], st.K);
+  }
+  const GemmPlan pl = plan_gemm(st, M, N, kd, steps, nn, dtype, scratch_bytes);
   const int form = pl.skinny ? MLORA_FORM_SKINNY : (pl.small ? MLORA_FORM_64 : MLORA_FORM_128), tiles = pl.tiles_m * pl.tiles_n;
   const bool quarters = form == MLORA_FORM_128 && pl.whole < tiles;
   return GemmForm{form, pl.parts, form == MLORA_FORM_128 ? pl.whole : tiles, tiles, pl.skinny ? 16 : (pl.small || quarters ? 64 : 128)};

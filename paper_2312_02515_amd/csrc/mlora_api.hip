@@ -282,10 +282,9 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
 // how the base product of Y (nn) or dX is cut up
 GemmForm product_form(const mlora_problem* p, const CallCtx& c, bool nn) {
   const int N = nn ? c.d : c.h, Kd = nn ? c.h : c.d;
-  if (!mfma_gemm_applies(p)) return general_gemm_form(c.st, c.T, N, Kd, nn, c.dtype, c.scratch_bytes);
-  GemmForm f = gemm_form(c.st, c.T, N, Kd, c.scratch_bytes);
-  if (!mfma_sizes_ok(p) && f.rows <= 64) f.form = f.rows == 16 ? MLORA_FORM_SKINNY : MLORA_FORM_64;
-  return f;
+  const int* const rank = c.st.rank;
+  return mfma_gemm_applies(p) ? gemm_form(c.st, c.T, N, 1, &Kd, c.scratch_bytes)
+                              : general_gemm_form(c.st, c.T, N, 1, &Kd, &rank, nn, c.dtype, c.scratch_bytes);
 }
 
 // Whether the shared-input low-rank kernels (one pass over X for all projections) apply
@@ -689,6 +688,32 @@ mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles) {
   tiles[MLORA_PLAN_DX_TILES] = dx.tiles;
   tiles[MLORA_PLAN_Y_ROWS] = y.rows;
   tiles[MLORA_PLAN_DX_ROWS] = dx.rows;
+  return MLORA_OK;
+}
+
+mlora_status mlora_kernel_plan_group(const mlora_problem* const* ps, int P, int32_t* plan) {
+  const mlora_status st = validate_group(ps, P);
+  if (st != MLORA_OK) return st;
+  if (plan == nullptr) return MLORA_ERR_NULL;
+  CallCtx c[MLORA_MAX_GROUP];
+  int Kd[MLORA_MAX_GROUP];
+  const int* rank[MLORA_MAX_GROUP];
+  bool al = true;
+  size_t room = 0;
+  for (int p = 0; p < P; ++p) {
+    fill_ctx(ps[p], nullptr, &c[p]);
+    Kd[p] = c[p].d;
+    rank[p] = c[p].st.rank;
+    al = al && mfma_gemm_applies(ps[p]);
+    room = c[p].scratch_bytes > room ? c[p].scratch_bytes : room;
+  }
+  const GemmForm f = al ? gemm_form(c[0].st, c[0].T, c[0].h, P, Kd, room)
+                        : general_gemm_form(c[0].st, c[0].T, c[0].h, P, Kd, rank, false, c[0].dtype, room);
+  plan[MLORA_PLAN_GROUP_DX] = f.form;
+  plan[MLORA_PLAN_GROUP_DX_PARTS] = f.parts;
+  plan[MLORA_PLAN_GROUP_DX_WHOLE] = f.whole;
+  plan[MLORA_PLAN_GROUP_DX_TILES] = f.tiles;
+  plan[MLORA_PLAN_GROUP_DX_ROWS] = f.rows;
   return MLORA_OK;
 }
 

@@ -125,7 +125,9 @@ struct GenOperands {
 };
 // whether the product runs in 16 x 64 tiles there (`Kd` over all operand pairs)
 bool general_skinny(const SegTable& st, int M, int N, long long Kd, int dtype);
-GemmForm general_gemm_form(const SegTable& st, int M, int N, int Kd, bool nn, int dtype, size_t scratch_bytes);
+// (the form of a sum over n operand pairs of Kd[g] contraction indices and rank[g][k])
+GemmForm general_gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, const int* const* rank, bool nn, int dtype,
+                           size_t scratch_bytes);
 double general_rows_us(const CallCtx& c, int inner, double* block_bytes);
 RowsForm general_rows_form(const CallCtx& c, int inner);
 int general_grad_ranges(const CallCtx& c, bool small, size_t scratch_bytes);
@@ -147,7 +149,7 @@ bool gemm_mfma_ok(int M, int N, int Kd);
 hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, bool nn, const bf16* L, int ldz,
                      const SegTable& st, const PtrTable& R, float* scratch, size_t scratch_bytes, hipStream_t stream);
 size_t gemm_partial_bytes(int K, int T, int N, int Kd);
-GemmForm gemm_form(const SegTable& st, int M, int N, int Kd, size_t scratch_bytes);
+GemmForm gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, size_t scratch_bytes);
 
 // One operand pair of a summed contraction (the input gradient of projections that share X):
 // A [M, Kd], Bm [N, Kd], L [M, ldz] with R_k [N, rank[k]].

@@ -214,12 +214,11 @@ def test_ragged_ranks_in_a_group(P):
 
 
 @pytest.mark.parametrize("case", [
-    # T, h, d, tokens, ranks, lead: bf16 base products cut into half tiles and contraction ranges
+    # T, h, d, tokens, ranks, lead: bf16 base products in small tiles ...
     (100, 4096, 512, [37, 20, 40], [16, 7, 128], 3),        # one row tile whose lower half is empty; many ranges
     (300, 512, 2048, [140, 0, 131], [64, 33, 8], 20),       # a task across half tiles; ranks 33..64
-    (520, 1088, 448, [33, 31, 450], [1, 100, 32], 6),       # contraction ranges of unequal length
-    (4200, 1024, 4096, [2100, 2050], [16, 24], 50),         # a whole round of tiles and halves behind it
-])
+    (520, 1088, 448, [33, 31, 450], [1, 100, 32], 6),
+] + [c for c, _ in form_cases.HALVES])                      # ... and cut into half tiles and contraction ranges
 def test_half_tiles_and_contraction_ranges(case):
     T, h, d, tokens, ranks, lead = case
     inp = _inputs(T, h, d, tokens, ranks, torch.bfloat16, lead=lead, seed=76)
@@ -281,19 +280,20 @@ def test_isolation_from_non_finite_values_in_every_form(dtype, case, j, what):
 
 
 @pytest.mark.parametrize("case", [
-    # T, h, d per projection, tokens, lead: a group's summed input gradient in half tiles
-    (100, 512, [4096, 64, 1088], [37, 40], 5),       # contraction ranges that cross and skip operand pairs
-    (300, 640, [512, 2048], [130, 0, 160], 3),
-    (700, 1088, [1024, 1024, 256, 64], [300, 333], 60),
-])
-def test_group_sum_in_half_tiles(case):
-    T, h, ds, tokens, lead = case
-    ranks = [[(8, 64, 24)[(p + k) % 3] + (p == 1) for k in range(len(tokens))] for p in range(len(ds))]
+    # T, h, d per projection, tokens, ranks, lead: a group's summed input gradient in small tiles ...
+    (T, h, ds, tokens, [[(8, 64, 24)[(p + k) % 3] + (p == 1) for k in range(len(tokens))] for p in range(len(ds))], lead)
+    for T, h, ds, tokens, lead in [
+        (100, 512, [4096, 64, 1088], [37, 40], 5),       # contraction ranges that cross and skip operand pairs
+        (300, 640, [512, 2048], [130, 0, 160], 3),
+        (700, 1088, [1024, 1024, 256, 64], [300, 333], 60)]
+] + [c[:-1] for c in form_cases.GROUPS])                 # ... in half tiles, whole tiles, partial contraction tiles
+def test_group_sum_in_every_form(case):
+    T, h, ds, tokens, ranks, lead = case
     ins = _group_inputs(T, h, ds, tokens, ranks, torch.bfloat16, lead=lead, seed=78)
-    check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"group halves {case}")
+    check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"group {case[:3]}")
     for i in ins:
         i.W.zero_()
-    check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"group halves, W = 0 {case}")
+    check_group(ins, run_group(ins), TOL[torch.bfloat16], label=f"group, W = 0 {case[:3]}")
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])

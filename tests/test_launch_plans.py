@@ -36,7 +36,44 @@ def test_plan_query(mb):  # noqa: F811
         assert q["Y"] in ("skinny", "64", "128") and q["Z_rows"] >= 32
     finally:
         mb.set_kernel_path(old)
-    assert plan(mb, 512, 256, 320, [256, 256], [8, 16])["Y"] in ("whole", "halves", "mixed")
+    assert plan(mb, 1100, 1024, 4096, [500, 600], [8, 16])["Y"] in ("whole", "halves", "mixed")
+
+
+def group_plan(mb, T, h, ds, tokens, ranks, lead):  # noqa: F811
+    off = [lead]
+    for t in tokens:
+        off.append(off[-1] + t)
+    return mb.Group([_problem(mb, T=T, h=h, d=d, off=tuple(off), ranks=tuple(r), s=(1.0,) * len(r))
+                     for d, r in zip(ds, ranks)]).kernel_plan()
+
+
+def test_group_plan_query(mb):  # noqa: F811
+    ps = [_problem(mb, T=512, h=256, d=d, off=(0, 256, 512), ranks=(8, 16)) for d in (320, 64)]
+    g, out = mb.Group(ps), (ctypes.c_int32 * len(mb.PLAN_GROUP))()
+    assert mb.lib.mlora_kernel_plan_group(g.c, 2, out) == 0
+    assert mb.lib.mlora_kernel_plan_group(g.c, 2, None) == 1
+    assert mb.lib.mlora_kernel_plan_group(None, 2, out) == 1
+    assert mb.lib.mlora_kernel_plan_group(g.c, 0, out) == 2
+    # a group of one is the plain call
+    one = mb.Group(ps[:1]).kernel_plan()
+    assert one == {k: ps[0].kernel_plan()[k] for k in one}
+
+
+@pytest.mark.parametrize("case", form_cases.GROUPS)
+def test_groups_of_the_gpu_tests_take_their_forms(mb, case):  # noqa: F811
+    *sizes, want = case
+    got = group_plan(mb, *sizes)
+    assert {k: got[k] for k in want} == want
+
+
+# features that are multiples of 64 or not, aligned or general: a name means one kernel
+@pytest.mark.parametrize("dtype,sizes,form,rows", [
+    ("bf16", (1100, 1024, 1024), "ring", 64), ("bf16", (600, 1016, 520), "ring", 64), ("bf16", (600, 1018, 518), "64", 64),
+    ("f32", (900, 1024, 1024), "64", 64), ("bf16", (128, 256, 256), "skinny", 16), ("f32", (128, 256, 256), "skinny", 16),
+    ("bf16", (1100, 2048, 5632), "halves", 128), ("bf16", (2000, 2056, 5640), "whole", 256)])
+def test_form_names(mb, dtype, sizes, form, rows):  # noqa: F811
+    got = plan(mb, *sizes, [sizes[0]], [8], f32=dtype == "f32")
+    assert (got["Y"], got["Y_rows"]) == (form, rows)
 
 
 @pytest.mark.parametrize("T,h,d,tokens,ranks,want", [
@@ -106,7 +143,8 @@ def test_short_tasks_keep_one_range(mb):  # noqa: F811
 
 @pytest.mark.parametrize("dtype,case,want", [(t, c, w) for c, w in form_cases.GENERAL for t in ("f32", "bf16")] +
                          form_cases.QUARTERS + form_cases.EDGE_QUARTERS +
-                         [("bf16", c, w) for c, w in form_cases.SPLIT_ROWS + form_cases.WHOLE_TILES + form_cases.LANES] +
+                         [("bf16", c, w) for c, w in form_cases.HALVES + form_cases.SPLIT_ROWS + form_cases.WHOLE_TILES +
+                          form_cases.LANES] +
                          [(t, c, w) for t, c, w, _ in form_cases.ISOLATION])
 def test_sizes_of_the_gpu_tests_take_their_forms(mb, dtype, case, want):  # noqa: F811
     T, h, d, tokens, ranks, lead = case
