@@ -113,7 +113,8 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, bool packed, hipStream_t stre
 // Forward, rank 128: 20000 x 2048 x 2048 195 us in whole tiles (201 as two rounds and halves), 12288 x 512
 // -> 2048 57 (63), 128 x 256 x 256 22.4 (23.8), but 16 x 1024 x 1024 41 us in whole tiles, 25 as halves.
 //
-// Small tiles (gemm_ring_kernel.h), 64 x 64 and of one or two groups of four waves, for up to 64 tiles of 256 x 256.
+// Small tiles (gemm_ring_kernel.h), 64 x 64 and of one or two groups of four waves, for up to 64 tiles of 256 x 256, or 128
+// that are no more than five small ones per CU.
 // Estimates (us, measured; n tiles of `steps` contraction and LoRA tiles): one group 5 + m (0.9 + 0.19 steps), m tiles on
 // the fullest CU, but 0.25 a step for one that it runs by itself (three fit a CU, so a first, fourth, .. one: with 918
 // blocks counted as 3.6 a CU, 3230 x 7248 -> 368 took 54 + 6 us, in half tiles 40 + 6); two groups, for up to 256 tiles,
@@ -124,9 +125,14 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, bool packed, hipStream_t stre
 //   1024 x 4096 -> 1024   27.2, 21.7 -> 20.1, 22.6     2048 x 2048 -> 2048   36.0, 33.5 -> 33.3, 32.5
 //   beyond: 3000 x 512 -> 2944  22.7 and 31.8 forward; 771 x 2048 -> 5632  34 and 36.  Where the estimates are level the larger
 //   tiles stay (771 x 5632 -> 2048: level in a loop, 38 us, and 2 % slower behind other launches).
-// Weights of 32 MiB and more, which the L2 caches of the chip do not hold together, keep the larger tiles in ranges, whose plans
-// a test holds (100 x 4096 -> 4096: 25 us, and 19 in small tiles).
-constexpr int kSmallTiles = 64;
+// The estimate has to be 7 % lower; with more than 64 tiles of 256 x 256, or weights of 32 MiB and more, which small tiles read from
+// HBM or the Infinity Cache several times over, 15 %.  Forward calls of 88 sizes from 8 to 700 rows with such weights: none of those
+// that the rule takes lost, and with 7 % one, by 8 % (256 x 11008 -> 4096).  Half tiles -> small tiles, us of the call:
+//   100 x 4096 -> 4096  31 -> 25     32 x 4096 -> 11008  40 -> 28     100 x 8192 -> 8192  51 -> 42     8 x 2048 -> 8192  28 -> 19
+//   30 x 9752 -> 6144 (2 tasks)  72 -> 36     25 x 1824 -> 10296  34 -> 18     50 x 4896 -> 4072 (11 tasks)  50 -> 41
+//   2740 x 368 -> 1600 (84 tiles)  24.4 -> 21.6     3191 x 312 -> 1232 (65)  20.0 -> 18.1
+//   4291 x 64 -> 1536 (1656 small tiles)  stays: a step 70.8 us, 73.0
+constexpr int kSmallTiles = 64, kMostTiles = 128, kMostSmallTiles = 5 * 256;
 struct Plan {
   int whole, parts;
   int small;          // groups of four waves per 64 x 64 tile; 0: 256 x 256 tiles and halves
@@ -234,8 +240,9 @@ Plan plan_gemm(const SegTable& st, int M, int N, int KT, int pairs, size_t scrat
     }
   }
   Plan small;
-  if (total <= kSmallTiles && (size_t)N * KT * 64 * sizeof(bf16) < kSmallWeight &&
-      plan_small(st, M, N, KT, pairs, scratch_limit, &small) < 0.93 * best_us)
+  const double margin = total <= kSmallTiles && (size_t)N * KT * 64 * sizeof(bf16) < kSmallWeight ? 0.93 : 0.85;
+  if ((total <= kSmallTiles || (total <= kMostTiles && (virtual_rows(st, M) + 63) / 64 * ((N + 63) / 64) <= kMostSmallTiles)) &&
+      plan_small(st, M, N, KT, pairs, scratch_limit, &small) < margin * best_us)
     return small;
   return best;
 }

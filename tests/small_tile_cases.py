@@ -17,6 +17,13 @@ CASES = [
     ((3230, 4104, 384, [1600, 1600], [64, 33], 3), {"Y_rows": 64, "Y_parts": 1}),
     ((3230, 7248, 368, [1615, 1600], [64, 33], 3), {"Y": "halves", "Y_rows": 128, "Y_parts": 4}),
     ((3230, 368, 7248, [1615, 1600], [64, 33], 3), {"dX": "halves", "dX_rows": 128, "dX_parts": 4}),
+    # ... weights of more than 32 MiB, features that are multiples of 64 and of 8, several tasks in a tile
+    ((50, 4896, 4072, [7, 11, 20], [14, 33, 8], 2), {"Y_rows": 64, "dX_rows": 64}),
+    ((90, 4096, 4608, [30, 0, 55], [16, 64, 5], 3), {"Y_rows": 64, "dX_rows": 64}),
+    ((25, 1824, 10296, [12, 13], [16, 100], 0), {"Y_rows": 64, "dX_rows": 64}),
+    # ... more than 64 tiles of 256 x 256
+    ((2740, 368, 1600, [230] * 11 + [201], [64, 9, 16] * 4, 4), {"Y_rows": 64}),
+    ((3191, 1232, 312, [1600, 1560], [32, 17], 4), {"dX_rows": 64}),
     # 16 x 64 tiles
     ((128, 256, 256, [60, 60], [8, 64], 4), {"Y_rows": 16, "dX_rows": 16}),
     # partial contraction tiles, one chunk more or less than a whole one; 64 x 64 tiles

@@ -80,8 +80,21 @@ def test_form_names(mb, dtype, sizes, form, rows):  # noqa: F811
     # full rounds of whole tiles, nothing cut
     (32768, 5120, 5120, [2048] * 16, [8, 16, 32, 64] * 4,
      dict(Y="whole", dX="whole", Y_parts=1, dX_parts=1, Z_rows=128, Z_parts=1, G_rows=128, G_parts=1, grads=1)),
-    # a few short prompts: half tiles in contraction ranges
-    (100, 4096, 4096, [37, 20, 43], [16] * 3, dict(Y="halves", dX="halves", Y_parts=7, Z_rows=32, Z_parts=1)),
+    # a few short prompts: small tiles, whatever the size of the weight
+    (100, 4096, 4096, [37, 20, 43], [16] * 3, dict(Y="ring", dX="ring", Z_rows=32, Z_parts=1)),
+    (32, 4096, 11008, [32], [16], dict(Y="ring", dX="ring")),
+    (8, 2048, 8192, [8], [16], dict(Y="ring", dX="ring")),
+    (30, 9752, 6144, [14, 16], [64, 8], dict(Y="ring", dX="ring")),
+    (25, 1824, 10296, [12, 13], [16, 16], dict(Y="ring", dX="ring")),
+    # ... half tiles in ranges for more rows
+    (256, 11008, 4096, [85, 85, 86], [16] * 3, dict(Y="halves")),
+    (300, 13824, 5120, [100] * 3, [32] * 3, dict(Y="halves", dX="halves")),
+    (512, 4096, 4096, [170, 170, 172], [16] * 3, dict(Y="halves", dX="halves")),
+    # small tiles beyond 64 tiles of 256 x 256
+    (2740, 368, 1600, [130, 123, 21, 273, 336, 190, 92, 125, 379, 551, 105, 415], [16, 64, 32] * 4, dict(Y="ring")),
+    (3191, 312, 1232, [1600, 1591], [32, 16], dict(Y="ring")),
+    (3000, 512, 2944, [3000], [16], dict(Y="whole")),
+    (4291, 64, 1536, [656, 69, 1776, 1044, 16, 411, 319], [67, 3, 1, 5, 2, 81, 9], dict(Y="halves")),
 ])
 def test_plans_of_known_calls(mb, T, h, d, tokens, ranks, want):  # noqa: F811
     got = plan(mb, T, h, d, tokens, ranks)
@@ -93,7 +106,7 @@ def test_tiles_of_the_aligned_products(mb):  # noqa: F811
         p = plan(mb, *a)
         return p["Y"], p["Y_whole"], p["Y_tiles"]
     assert tiles(16384, 4096, 4096, [16384], [16]) == ("whole", 1024, 1024)
-    assert tiles(100, 4096, 4096, [100], [16]) == ("halves", 0, 16)
+    assert tiles(1100, 1024, 4096, [1100], [16]) == ("halves", 0, 80)
     assert tiles(4300, 1024, 4096, [2100, 2050], [16, 24], 50) == ("mixed", 256, 288)
 
 
