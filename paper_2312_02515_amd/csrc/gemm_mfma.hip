@@ -367,7 +367,7 @@ GemmForm gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, size_
 
 size_t gemm_partial_bytes(int K, int T, int N, int Kd) {
   const long long mv = most_virtual_rows(K, T), tiles = (mv + BM - 1) / BM * ((N + BN - 1) / BN);
-  const int parts = Kd / 64 < kMaxParts ? Kd / 64 : kMaxParts;
+  const int kt = (Kd + 63) / 64, parts = kt < kMaxParts ? kt : kMaxParts;
   return parts > 1 ? (size_t)(2 * (tiles < 255 ? tiles : 255)) * parts * (BM / 2) * BN * sizeof(float) : 0;
 }
 

@@ -133,7 +133,7 @@ size_t scratch_bytes(const mlora_problem* p, const CallCtx& c) {
     most(use, rows_partial_bytes(c.T, c.h, c.ldz));
     most(use, rows_partial_bytes(c.T, c.d, c.ldz));
   }
-  if (aligned) {
+  if (mfma_chunks_ok(p)) {
     most(use, gemm_partial_bytes(c.K, c.T, c.d, c.h));
     most(use, gemm_partial_bytes(c.K, c.T, c.h, c.d));
   }

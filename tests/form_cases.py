@@ -77,7 +77,7 @@ GROUPS = [(T, h, ds, tokens, _group_ranks(len(ds), len(tokens)), lead, want) for
     # ... that end in partial contraction tiles
     (326, 2816, [1280, 3320], [123, 108], 3, {"dX": "halves", "dX_parts": 5}),
     (172, 3072, [3664, 3592, 768], [46, 57], 3, {"dX": "halves", "dX_parts": 10}),
-    (223, 2224, [3664, 3272, 440, 3304], [71, 74], 3, {"dX": "halves", "dX_parts": 7}),
+    (223, 2224, [3664, 3272, 440, 3304], [71, 74], 3, {"dX": "halves", "dX_parts": 13}),
     # ... one range
     (2000, 2056, [2056, 520], [900, 1055], 3, {"dX": "halves", "dX_parts": 1}),
     # whole tiles that end in partial contraction tiles, one of them alone among them
@@ -85,7 +85,7 @@ GROUPS = [(T, h, ds, tokens, _group_ranks(len(ds), len(tokens)), lead, want) for
     (9268, 1032, [632, 72, 200], [4000, 33, 5000], 3, {"dX": "whole"}),
     (9268, 1032, [136, 64, 72, 8], [4000, 33, 5000], 3, {"dX": "whole"}),
     # half tiles of packed rows (60 tasks of up to 16 rows): the tiles are those of the 494 rows alone
-    (494, 4104, [4104, 2056], _PACKED, 9, {"dX": "halves", "dX_parts": 1, "dX_tiles": 34}),
+    (494, 4104, [4104, 2056], _PACKED, 9, {"dX": "halves", "dX_parts": 3, "dX_tiles": 34}),
     (494, 4480, [2104, 2240, 704], _PACKED, 9, {"dX": "halves", "dX_parts": 3, "dX_tiles": 36}),
     (494, 4224, [384, 336, 3992, 3864], _PACKED, 9, {"dX": "halves", "dX_parts": 3, "dX_tiles": 34}),
     # small tiles

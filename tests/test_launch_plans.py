@@ -90,6 +90,10 @@ def test_form_names(mb, dtype, sizes, form, rows):  # noqa: F811
     (256, 11008, 4096, [85, 85, 86], [16] * 3, dict(Y="halves")),
     (300, 13824, 5120, [100] * 3, [32] * 3, dict(Y="halves", dX="halves")),
     (512, 4096, 4096, [170, 170, 172], [16] * 3, dict(Y="halves", dX="halves")),
+    # ... also with features that are multiples of 8, whose ranges have room in the workspace as well
+    (366, 6496, 11920, [73, 293], [2, 2], dict(dX="halves", dX_parts=2)),
+    (500, 4104, 4104, [200, 300], [16, 16], dict(Y="halves", Y_parts=2, dX="halves", dX_parts=2)),
+    (700, 8200, 2056, [300, 400], [16, 16], dict(Y="halves", Y_parts=4)),
     # small tiles beyond 64 tiles of 256 x 256
     (2740, 368, 1600, [130, 123, 21, 273, 336, 190, 92, 125, 379, 551, 105, 415], [16, 64, 32] * 4, dict(Y="ring")),
     (3191, 312, 1232, [1600, 1591], [32, 16], dict(Y="ring")),
