@@ -1037,16 +1037,20 @@ hipError_t grad_group(const LowrankGroupItem* it, const SegTable& st, const bf16
 
 }  // namespace
 
-// plan_rows cuts fewer than 256 blocks of 128 rows into at most KT / 4 ranges: up to 8, or (ranks above 64)
-// up to 16 as long as there are no more than 256 blocks of 128 rows or 512 of 32, which is half as many rows
+// plan_rows cuts fewer than 256 blocks of 128 rows into at most KT / 4 ranges: up to 8, up to 16 of fewer than 32 blocks of
+// 32 rows, or (ranks above 64) up to 16 as long as there are no more than 256 blocks of 128 rows or 512 of 32, which is half
+// as many rows
 size_t rows_partial_bytes(int T, int inner, int ldz) {
   const bool four = nq_of(ldz) == 4;
-  const int KT = inner / 64, most = four ? 16 : 8, splits = KT / 4 < most ? KT / 4 : most;
-  if (splits <= 1) return 0;
+  const int KT = inner / 64;
+  auto sums = [&](long long rows, int most) {
+    const int splits = KT / 4 < most ? KT / 4 : most;
+    return splits > 1 ? (rows < T ? rows : (long long)T) * splits : 0;
+  };
   constexpr long long block_rows = 256 * 128;
-  const long long rows = T < block_rows ? T : block_rows;
-  const long long sums = four && rows * splits > block_rows ? block_rows : rows * splits;
-  return align_up((size_t)sums * ldz * sizeof(float), 256);
+  const long long many = sums(block_rows, four ? 16 : 8), few = four ? 0 : sums(31 * 32, 16);
+  const long long most = four && many > block_rows ? block_rows : (many > few ? many : few);
+  return align_up((size_t)most * ldz * sizeof(float), 256);
 }
 
 RowsForm rows_form(const SegTable& st, int inner, int ldz, size_t limit) {
