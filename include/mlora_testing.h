@@ -37,7 +37,7 @@ int mlora_set_kernel_path(int path);
 #define MLORA_PLAN_Z_PARTS  5  /* ... contraction ranges                                           */
 #define MLORA_PLAN_G_ROWS   6  /* the same for s dy B^T                                            */
 #define MLORA_PLAN_G_PARTS  7
-#define MLORA_PLAN_GRADS    8  /* dA, dB: token ranges per task                                    */
+#define MLORA_PLAN_GRADS    8  /* dA, dB of a call that wants dX: token ranges per task             */
 #define MLORA_PLAN_FIELDS   9
 #define MLORA_FORM_WHOLE    0  /* aligned: 256 x 256 tiles                                         */
 #define MLORA_FORM_HALVES   1  /* aligned: 128 x 256 tiles                                         */
@@ -51,15 +51,19 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan);
 
 /* The tiles of the two base products in the size that their form names (256 x 256 for WHOLE, HALVES and
  * MIXED): how many run as such, and how many there are -- the others run as halves (HALVES, MIXED) or
- * quarters (128); and the rows of the smallest tiles that run: 256, 128, 64 or 16.  `tiles` (HOST,
- * MLORA_PLAN_TILES entries) and the status as for mlora_kernel_plan. */
+ * quarters (128); and the rows of the smallest tiles that run: 256, 128, 64 or 16.  And whether a call
+ * that wants dX runs it and the gradients in one launch (then the ranges of dX and of the gradients are
+ * those of that launch), and the token ranges of dA, dB without dX.  `tiles` (HOST, MLORA_PLAN_TILES
+ * entries) and the status as for mlora_kernel_plan. */
 #define MLORA_PLAN_Y_WHOLE  0
 #define MLORA_PLAN_Y_TILES  1
 #define MLORA_PLAN_DX_WHOLE 2
 #define MLORA_PLAN_DX_TILES 3
 #define MLORA_PLAN_Y_ROWS   4
 #define MLORA_PLAN_DX_ROWS  5
-#define MLORA_PLAN_TILES    6
+#define MLORA_PLAN_SHARED   6
+#define MLORA_PLAN_GRADS_ALONE 7
+#define MLORA_PLAN_TILES    8
 mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles);
 
 /* The same for the summed input gradient of a group (`plan`: HOST, MLORA_PLAN_GROUP entries); returns the

@@ -37,7 +37,7 @@ TESTING_EXPORTS = ["mlora_set_kernel_path", "mlora_kernel_plan", "mlora_kernel_p
 
 # entries of mlora_kernel_plan, mlora_kernel_plan_tiles and mlora_kernel_plan_group, names of the MLORA_FORM_* values
 PLAN_FIELDS = ["Y", "Y_parts", "dX", "dX_parts", "Z_rows", "Z_parts", "G_rows", "G_parts", "grads"]
-PLAN_TILES = ["Y_whole", "Y_tiles", "dX_whole", "dX_tiles", "Y_rows", "dX_rows"]
+PLAN_TILES = ["Y_whole", "Y_tiles", "dX_whole", "dX_tiles", "Y_rows", "dX_rows", "shared", "grads_alone"]
 PLAN_GROUP = ["dX", "dX_parts", "dX_whole", "dX_tiles", "dX_rows"]
 PLAN_FORMS = ["whole", "halves", "mixed", "skinny", "64", "128", "ring"]
 

@@ -137,6 +137,7 @@ struct Plan {
   int whole, parts;
   int small;          // groups of four waves per 64 x 64 tile; 0: 256 x 256 tiles and halves
   bool packed;        // halves: rows of several tasks in a piece of 32
+  double us;          // small tiles: the estimate
 };
 constexpr int kMaxParts = 16;
 constexpr size_t kSmallWeight = (size_t)32 << 20;
@@ -163,11 +164,11 @@ double plan_small(const SegTable& st, int M, int N, int KT, int pairs, size_t sc
                       (p > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
     if (p == 1 || us < best) {
       best = us;
-      *out = Plan{0, p, 1, false};
+      *out = Plan{0, p, 1, false, us};
     }
     if (p == 1 && n <= 256 && pairs == 1 && 6.3 + 0.4 * ((steps + 1) / 2) < best) {
       best = 6.3 + 0.4 * ((steps + 1) / 2);
-      *out = Plan{0, 1, 2, false};
+      *out = Plan{0, 1, 2, false, best};
     }
   }
   return best;
@@ -212,7 +213,7 @@ Plan plan_gemm(const SegTable& st, int M, int N, int KT, int pairs, size_t scrat
     const double part = last == 0 ? 0.0 : (tiles > 256 && last <= 128 ? 0.85 : 1.0);
     return (tiles / 256 + part) * (whole_fixed + 1.3 * KT);
   };
-  Plan best{total, 1, 0, false};
+  Plan best{total, 1, 0, false, 0};
   double best_us = whole_us(total);
   for (int parts = 1; halves > 0 && parts <= kMaxParts && parts <= KT; ++parts) {
     const size_t bytes = parts > 1 ? (size_t)halves * parts * (BM / 2) * BN * sizeof(float) : 0;
@@ -221,7 +222,7 @@ Plan plan_gemm(const SegTable& st, int M, int N, int KT, int pairs, size_t scrat
                       (parts > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
     if (us < best_us) {
       best_us = us;
-      best = Plan{q, parts, 0, false};
+      best = Plan{q, parts, 0, false, 0};
     }
   }
   if (packed_rows(st, M)) {
@@ -235,7 +236,7 @@ Plan plan_gemm(const SegTable& st, int M, int N, int KT, int pairs, size_t scrat
                         (parts > 1 ? 4.0 + (double)bytes / 7e6 : 0.0);
       if (us < 0.93 * best_us) {
         best_us = us / 0.93;
-        best = Plan{0, parts, 0, true};
+        best = Plan{0, parts, 0, true, 0};
       }
     }
   }
@@ -328,6 +329,16 @@ hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int K
   a.R[0] = R;
   return nn ? launch<true, 1>(a, scratch, scratch_bytes, st, stream)
             : launch<false, 1>(a, scratch, scratch_bytes, st, stream);
+}
+
+bool gemm_small_us(const SegTable& st, int M, int N, int Kd, size_t limit, double* us) {
+  if (skinny(st, M, N, Kd)) {
+    *us = general_skinny_us(st, M, N, Kd, MLORA_BF16);
+    return true;
+  }
+  const Plan pl = plan_gemm(st, M, N, (Kd + 63) / 64, 1, limit);
+  *us = pl.us;
+  return pl.small > 0;
 }
 
 SmallForm gemm_small_nt(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, const bf16* L, int ldz, const SegTable& st,

@@ -15,6 +15,8 @@ void ring_tiles(gemmk::GemmArgs<1>* a, const SegTable& st, int parts, float* scr
 template <int NSEG>
 void launch_ring_reduce(const gemmk::GemmArgs<NSEG>& a, hipStream_t s);
 
+// whether an input gradient runs in small tiles (within `limit` bytes of scratch), and the estimate for it in us
+bool gemm_small_us(const SegTable& st, int M, int N, int Kd, size_t limit, double* us);
 // C = A Bm^T + rows_k(L R_k^T) (an input gradient) where the plan runs it in small tiles: the arguments of the ring kernel
 // in `a`, its groups and ranges (within `limit` bytes of scratch)
 enum SmallForm { kNotSmall = 0, kSkinny = 1, kRing = 2 };

@@ -1121,12 +1121,16 @@ struct BackArgs {
   int blocks_b, blocks;
   int lead;              // blocks of the launch that hold gradients
 };
+// A block of gradients is four waves, the others of a larger block leave: gradients wait for loads and fp32 MFMAs, and two to a
+// CU took up to twice as long while most CUs had nothing to do (fp32 512 x 500 -> 500, one task in 8 ranges, a step 33 us -> 28; 4
+// tasks in one 48 -> 36).  Only where the blocks of the two-group ring, one to a CU, would be more than the CUs that way, a block holds
+// two (908 x 768 -> 2624, 12 tasks, a step 48.2 -> 45.4).
 template <typename T, int NQ>
 __global__ __launch_bounds__(512, NQ == 4 ? 2 : 4) void k_gen_back_skinny(const GenGemmArgs<1> g, const BackArgs p) {
   __shared__ float red[kSkinnySums];
   const int bid = blockIdx.x;
   if (bid >= p.lead) skinny_body<T, false, 1>(g, bid - p.lead, red);
-  else gen_grads_body<T, NQ>(p.b, p.a, p.blocks_b, p.blocks, 2 * bid + (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 8));
+  else if (threadIdx.x < 256) gen_grads_body<T, NQ>(p.b, p.a, p.blocks_b, p.blocks, bid);
 }
 template <typename T, int NQ>
 __global__ __launch_bounds__(256) void k_gen_back_64(const GenGemmArgs<1> g, const BackArgs p) {
@@ -1139,8 +1143,10 @@ template <int G, int NQ>
 __global__ __launch_bounds__(256 * G, G == 1 ? 3 : 2) void k_gen_back_ring(const gemmk::GemmArgs<1> g, const BackArgs p) {
   __shared__ __attribute__((aligned(1024))) char sm[ringk::kRingLds<G, 3>];
   const int bid = blockIdx.x;
-  if (bid >= p.lead) ringk::ring_body<G, 3, false, 1>(g, bid - p.lead, sm);
-  else gen_grads_body<bf16, NQ>(p.b, p.a, p.blocks_b, p.blocks, G * bid + (G == 1 ? 0 : (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 8)));
+  if (bid >= p.lead) return ringk::ring_body<G, 3, false, 1>(g, bid - p.lead, sm);
+  const int half = G == 1 ? 0 : (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
+  const bool two = G == 2 && p.lead < p.blocks;      // neighbours: mostly of one task, which take as long
+  if (two || half == 0) gen_grads_body<bf16, NQ>(p.b, p.a, p.blocks_b, p.blocks, two ? 2 * bid + half : bid);
 }
 
 int row_blocks(const SegTable& st, int tm) {
@@ -1234,6 +1240,7 @@ struct GemmPlan {
   int tiles_m, tiles_n, parts;           // of 16 x 64, 64 x 64 (small) or 128 x 128
   int whole;                             // 128 x 128: tiles [0, whole) as such, the others in quarters (small: 0)
   bool packed;                           // rows of several tasks in a piece
+  double us;                             // the estimate
 };
 constexpr int kMaxParts = 16, kMostUnits = 1024, kTilesPerPart = 4;   // (contraction tiles of 128 bytes per row)
 // us per contraction tile: a block alone on its CU, and the share of one among several; and per 16 ranks of the
@@ -1283,7 +1290,8 @@ bool general_skinny(const SegTable& st, int M, int N, long long Kd, int dtype) {
 namespace {
 // (`steps16` steps of 16 ranks over all operand pairs)
 GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int steps16, bool nn, int dtype, size_t scratch_limit) {
-  if (general_skinny(st, M, N, Kd_total, dtype)) return GemmPlan{true, true, (int)((virtual_rows(st, M) + 15) / 16), (N + 63) / 64, 1, 0, false};
+  if (general_skinny(st, M, N, Kd_total, dtype))
+    return GemmPlan{true, true, (int)((virtual_rows(st, M) + 15) / 16), (N + 63) / 64, 1, 0, false, general_skinny_us(st, M, N, Kd_total, dtype)};
   GemmPlan p;
   p.skinny = false;
   p.packed = false;
@@ -1329,8 +1337,9 @@ GemmPlan plan_gemm(const SegTable& st, int M, int N, long long Kd_total, int ste
     int parts;
     const double packed_us = small_tiles_us((long long)tm * tn, kt, t, steps16 * (nn ? t.lora_nn : t.lora_nt) * (in_piece < live ? in_piece : (double)live),
                                             1.25, scratch_limit, &parts);
-    if (packed_us < 0.93 * us) return GemmPlan{false, true, tm, tn, parts, 0, true};
+    if (packed_us < 0.93 * us) return GemmPlan{false, true, tm, tn, parts, 0, true, packed_us};
   }
+  p.us = us;
   return p;
 }
 
@@ -1432,12 +1441,7 @@ int gen_grad_ranges(const SegTable& st, int wide_b, int wide_a, int longest, int
   s = s < longest / least ? s : longest / least;
   return s > 1 ? s : 1;
 }
-// 64 tokens; where the gradients share a launch with dX, which takes as long as several hundred, the ranges' reduction would
-// come on top
 constexpr int kLeastTokens = 64;
-int least_tokens(bool small, int dtype, int ldz) {
-  return !small || (dtype == MLORA_F32 && ldz > 32) ? kLeastTokens : (dtype == MLORA_F32 ? 192 : 384);
-}
 // ... as far as the scratch goes
 int gen_grad_splits(const SegTable& st, int wide_b, int wide_a, size_t scratch_limit, int least = kLeastTokens) {
   int s = gen_grad_ranges(st, wide_b, wide_a, longest_task(st), least);
@@ -1464,13 +1468,15 @@ void launch_grads(const GenGradArgs& b, const GenGradArgs& a, int blocks_b, int 
 
 }  // namespace
 
+size_t general_grad_bytes(const SegTable& st, int T, int h, int d) {
+  const int s = st.K > 0 ? gen_grad_ranges(st, d, h, T, kLeastTokens) : 1;
+  return s > 1 ? grad_sum_bytes(st, s, d, h) : 0;
+}
+size_t general_dx_bytes(int K, int T, int h, int d, int dtype) { return gemm_part_bytes(K, T, h, d, dtype); }
 size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype) {
   size_t b = 0;
   auto most = [&](size_t v) { b = v > b ? v : b; };
-  if (st.K > 0) {
-    const int s = gen_grad_ranges(st, d, h, T, kLeastTokens);
-    if (s > 1) most(grad_sum_bytes(st, s, d, h));
-  }
+  most(general_grad_bytes(st, T, h, d));
   most(gemm_part_bytes(st.K, T, d, h, dtype));
   most(gemm_part_bytes(st.K, T, h, d, dtype));
   return b;
@@ -1502,8 +1508,50 @@ double general_rows_us(const CallCtx& c, int inner, double* block_bytes) {
 RowsForm general_rows_form(const CallCtx& c, int inner) {
   return RowsForm{two_row_groups(c) ? 32 : 16, gen_rows_parts(c, inner, c.scratch_bytes)};
 }
-int general_grad_ranges(const CallCtx& c, bool small, size_t scratch_bytes) {
-  return c.K > 0 ? gen_grad_splits(c.st, c.d, c.h, scratch_bytes, least_tokens(small, c.dtype, c.ldz)) : 1;
+namespace {
+// Token ranges of a small call's gradients (up to kMostShared activation elements, ranks up to 64), of at least `least` tokens, as an
+// estimate in us has it: the longest range of any task, at so much per token (below: fp32 and bf16, ranks up to 16, 32 and 64);
+// the blocks; the reduction, 3 and 14 per million elements and 0.3 per MB of sums (fp32 2.5 and 0.2 per MB).  Beside a product of `product` us what takes
+// longer, and half of the ranges' time for the CUs that they take from it.  236 calls of 128 to 8000 tokens with dX beside them: the choice
+// takes 0.6 % more than the best number of ranges in the mean, 8 % at most; always one 29 %, always as many as 64 tokens allow
+// 3 %.  Forward, backward and gradients, one range -> several, us: fp32 256 x 256 -> 64 (one task) 19.5 -> 16.9, 1024 39 -> 19.5, but
+// 128 x 1000 -> 1500 43.7 -> 45.3; bf16 1024 x 500 -> 500 29.2 -> 23.4, but 512 x 1000 -> 1500 33.7 -> 36.4, 1801 x 666 -> 87 (16 tasks, rank
+// 64) 43.0 -> 53.5; by themselves 1716 x 2054 -> 115 (13 tasks, rank 32) 60.9 -> 70.1.
+constexpr double kTokenUs[2][3] = {{0.026, 0.041, 0.07}, {0.0125, 0.0185, 0.033}};
+int best_grad_ranges(const CallCtx& c, double product, int least) {
+  const int most = gen_grad_splits(c.st, c.d, c.h, c.scratch_bytes, least);
+  const bool f32 = c.dtype == MLORA_F32;
+  size_t rtotal = 0;
+  for (int k = 0; k < c.K; ++k) rtotal += c.st.rank[k];
+  const double elements = (double)rtotal * (c.h + c.d), blocks = (double)c.K * ((c.h + 255) / 256 + (c.d + 255) / 256);
+  int best = 1;
+  double best_us = 0;
+  for (int s = 1; s <= most; ++s) {
+    double g = 0;
+    for (int k = 0; k < c.K; ++k) {
+      const int len = c.st.off[k + 1] - c.st.off[k], range = ((len + s - 1) / s + 31) / 32 * 32, r = c.st.rank[k];
+      const double us = 3.0 + kTokenUs[f32 ? 0 : 1][r <= 16 ? 0 : (r <= 32 ? 1 : 2)] * (range < len ? range : len);
+      g = us > g ? us : g;
+    }
+    const double us = (product > g ? product : g) + (product > 0 ? 0.5 * g : 0.0) + 0.5 * s * blocks / 64 +
+                      (s == 1 ? 0.0 : (f32 ? 2.5 + 0.8e-6 * s * elements : 3.0 + (14e-6 + 1.2e-6 * s) * elements));
+    if (s == 1 || us < best_us) {
+      best_us = us;
+      best = s;
+    }
+  }
+  return best;
+}
+}  // namespace
+int general_grad_ranges(const CallCtx& c) {
+  if (c.K == 0) return 1;
+  return c.ldz <= 64 && (long long)c.T * (c.h + c.d) <= kMostShared ? best_grad_ranges(c, 0.0, kLeastTokens)
+                                                                    : gen_grad_splits(c.st, c.d, c.h, c.scratch_bytes);
+}
+// 16 x 64 tiles: the waves of a block share out rows of the contraction, a round of 256 blocks takes as long as its bytes
+double general_skinny_us(const SegTable& st, int M, int N, long long Kd, int dtype) {
+  const long long units = (virtual_rows(st, M) + 15) / 16 * ((N + 63) / 64);
+  return 4.0 + 0.00235 * (double)(Kd * (dtype == MLORA_F32 ? 4 : 2)) * (double)((units + 255) / 256);
 }
 
 hipError_t general_Z(const CallCtx& c, const void* X, void* Z, float* scratch) {
@@ -1529,10 +1577,9 @@ struct GradPlan {
   int blocks_b, blocks, splits;
 };
 void plan_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G, const OutTable* dA,
-                int accumulate, bool small, float* scratch, size_t scratch_bytes, GradPlan* p) {
+                int accumulate, int ranges, float* scratch, GradPlan* p) {
   const int wide_b = c.d, wide_a = dA != nullptr ? c.h : 0;
-  // (planned for both outputs, so that the scratch suffices for either)
-  p->splits = gen_grad_splits(c.st, wide_b, c.h, scratch_bytes, least_tokens(small, c.dtype, c.ldz));
+  p->splits = ranges;
   size_t rtotal = 0;
   for (int k = 0; k < c.K; ++k) rtotal += c.st.rank[k];
   auto fill = [&](GenGradArgs& g, const void* big, int wide, const void* small, const OutTable& out, float* part) {
@@ -1556,26 +1603,27 @@ void plan_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable&
 }
 
 template <typename T, int NQ>
-void launch_back(const GenGemmArgs<1>& g, bool skinny, BackArgs p, hipStream_t s) {
-  const unsigned products = (unsigned)(g.tiles_m * g.tiles_n * g.parts);
-  p.lead = skinny ? (p.blocks + 1) / 2 : p.blocks;
-  if (skinny) hipLaunchKernelGGL((k_gen_back_skinny<T, NQ>), dim3(products + p.lead), dim3(512), 0, s, g, p);
-  else hipLaunchKernelGGL((k_gen_back_64<T, NQ>), dim3(products + p.lead), dim3(256), 0, s, g, p);
+void launch_back(const GenGemmArgs<1>& g, bool skinny, const BackArgs& p, hipStream_t s) {
+  const dim3 grid((unsigned)(p.blocks + g.tiles_m * g.tiles_n * g.parts));
+  if (skinny) hipLaunchKernelGGL((k_gen_back_skinny<T, NQ>), grid, dim3(512), 0, s, g, p);
+  else hipLaunchKernelGGL((k_gen_back_64<T, NQ>), grid, dim3(256), 0, s, g, p);
 }
 template <int NQ>
 void launch_back_ring(const gemmk::GemmArgs<1>& g, int groups, BackArgs p, hipStream_t s) {
-  const unsigned products = (unsigned)(g.tiles_m * g.tiles_n * g.parts);
-  p.lead = groups == 2 ? (p.blocks + 1) / 2 : p.blocks;
-  if (groups == 2) hipLaunchKernelGGL((k_gen_back_ring<2, NQ>), dim3(products + p.lead), dim3(512), 0, s, g, p);
-  else hipLaunchKernelGGL((k_gen_back_ring<1, NQ>), dim3(products + p.lead), dim3(256), 0, s, g, p);
+  const int products = g.tiles_m * g.tiles_n * g.parts;
+  if (groups == 2 && p.blocks + products > 256) p.lead = (p.blocks + 1) / 2;
+  const dim3 grid((unsigned)(p.lead + products));
+  if (groups == 2) hipLaunchKernelGGL((k_gen_back_ring<2, NQ>), grid, dim3(512), 0, s, g, p);
+  else hipLaunchKernelGGL((k_gen_back_ring<1, NQ>), grid, dim3(256), 0, s, g, p);
 }
 }  // namespace
 
 hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G,
-                         const OutTable* dA, int accumulate, bool small, float* scratch, size_t scratch_bytes) {
+                         const OutTable* dA, int accumulate, int ranges, float* scratch) {
   if (c.K == 0) return hipSuccess;
   GradPlan p;
-  plan_grads(c, dY, Z, dB, X, G, dA, accumulate, small, scratch, scratch_bytes, &p);
+  // (planned for both outputs, so that the scratch suffices for either)
+  plan_grads(c, dY, Z, dB, X, G, dA, accumulate, ranges > 0 ? ranges : general_grad_ranges(c), scratch, &p);
   if (c.dtype == MLORA_F32) launch_grads<float>(p.b, p.a, p.blocks_b, p.blocks, c.ldz, c.stream);
   else launch_grads<bf16>(p.b, p.a, p.blocks_b, p.blocks, c.ldz, c.stream);
   const hipError_t e = hipGetLastError();
@@ -1583,21 +1631,39 @@ hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const 
   return grad_reduce(c.st, scratch, p.splits, c.d, dB, dA != nullptr ? c.h : 0, dA != nullptr ? *dA : dB, accumulate, c.stream);
 }
 
+namespace {
+// whether dX runs in a form that gradients share a launch with, and the estimate for it
+bool small_product(const CallCtx& c, bool aligned, size_t limit, double* us) {
+  if (aligned) return gemm_small_us(c.st, c.T, c.h, c.d, limit, us);
+  const GemmPlan pl = plan_gemm(c.st, c.T, c.h, c.d, rank_steps(c.st.rank, c.K), false, c.dtype, limit);
+  *us = pl.us;
+  return pl.small && !pl.packed;
+}
+}  // namespace
+
 // Calls whose gradients and dX leave most CUs idle each: up to 4 Mi activation elements, ranks up to 64 (higher ones take all
 // registers), and up to 32 where the aligned gradients could run, which are faster above (2000 x 256 -> 256, 16 tasks, rank 64
-// 18 against 24 us).  The sizes alone decide, so that the gradients of a call have the same bits whatever runs beside them.
-bool small_back(const CallCtx& c) {
+// 18 against 24 us); and dX in small tiles.
+// The sizes and the problem's own addresses decide, so that a group's gradients, and those of a call whose dX overlaps what they
+// read, have the bits of the shared launch.  (Without dX they run by themselves, in ranges of their own.)
+BackPlan plan_back(const CallCtx& c, bool aligned) {
+  const BackPlan apart{false, 0, c.scratch_bytes};
   const bool fast = c.dtype == MLORA_BF16 && c.h % 64 == 0 && c.d % 64 == 0;
-  return c.K > 0 && c.T > 0 && (long long)c.T * (c.h + c.d) <= 4 << 20 && c.ldz <= (fast ? 32 : 64);
+  if (c.K == 0 || c.T == 0 || (long long)c.T * (c.h + c.d) > kMostShared || c.ldz > (fast ? 32 : 64)) return apart;
+  double product;
+  if (!small_product(c, aligned, c.scratch_bytes, &product)) return apart;
+  const int ranges = best_grad_ranges(c, product, c.dtype == MLORA_F32 ? kLeastTokens : 2 * kLeastTokens);
+  const size_t left = c.scratch_bytes - (ranges > 1 ? grad_sum_bytes(c.st, ranges, c.d, c.h) : 0);
+  return small_product(c, aligned, left, &product) ? BackPlan{true, ranges, left} : apart;
 }
 
-hipError_t general_back(const CallCtx& c, bool aligned, const void* X, const void* W, const void* dY, const void* Z, const void* G,
+hipError_t general_back(const CallCtx& c, const BackPlan& bp, bool aligned, const void* X, const void* W, const void* dY, const void* Z, const void* G,
                         void* dX, const OutTable& dA, const OutTable& dB, int accumulate, float* scratch) {
   GradPlan gp;
-  plan_grads(c, dY, Z, dB, X, G, &dA, accumulate, true, scratch, c.scratch_bytes, &gp);
-  const size_t used = gp.splits > 1 ? grad_sum_bytes(c.st, gp.splits, c.d, c.h) : 0, left = c.scratch_bytes - used;
-  float* const partial = scratch + used / sizeof(float);
-  BackArgs p{gp.b, gp.a, gp.blocks_b, gp.blocks, 0};
+  plan_grads(c, dY, Z, dB, X, G, &dA, accumulate, bp.ranges, scratch, &gp);
+  const size_t left = bp.left;
+  float* const partial = scratch + (c.scratch_bytes - left) / sizeof(float);   // behind the gradients' sums
+  const BackArgs p{gp.b, gp.a, gp.blocks_b, gp.blocks, gp.blocks};
   const int nq = c.ldz <= 16 ? 1 : (c.ldz <= 32 ? 2 : 4);
   hipError_t e;
   gemmk::GemmArgs<1> r;

@@ -137,6 +137,13 @@ size_t scratch_bytes(const mlora_problem* p, const CallCtx& c) {
     most(use, gemm_partial_bytes(c.K, c.T, c.d, c.h));
     most(use, gemm_partial_bytes(c.K, c.T, c.h, c.d));
   }
+  if (c.K > 0 && c.ldz <= 64) {
+    // calls that run dX with the gradients, whose partial sums live side by side
+    const int64_t rows = kMostShared / (p->h + p->d);
+    const int t = (int)(p->T < rows ? p->T : rows);
+    const size_t product = mfma_chunks_ok(p) ? gemm_partial_bytes(c.K, t, c.h, c.d) : 0, general = general_dx_bytes(c.K, t, c.h, c.d, c.dtype);
+    most(use, (product > general ? product : general) + general_grad_bytes(c.st, t, c.h, c.d));
+  }
   const size_t room = z + reserve <= fixed ? fixed - z : 2 * fixed;
   use = use < room ? use : room;
   return use > reserve ? use : reserve;
@@ -233,11 +240,11 @@ hipError_t compute_G(const mlora_problem* p, const CallCtx& c, const void* X, co
 }
 
 // G, dB_k and dA_k, given Z
-// (with `skip_dA` the caller computes dA_k itself from G; `have_G`: G has been computed; `small`: the gradients of small calls
-// that want dX, which come from the general kernel whether or not they run with dX)
+// (with `skip_dA` the caller computes dA_k itself from G; `have_G`: G has been computed; `ranges`: 0, or those of a call whose
+// gradients share a launch with dX, so that they have the same bits where they don't)
 hipError_t adapter_grads_impl(const mlora_problem* p, const CallCtx& c, const void* X, const void* dY, const void* Z,
                               void* G, float* const* dA, float* const* dB, int accumulate, void* scratch,
-                              bool small, bool skip_dA = false, bool have_G = false) {
+                              int ranges, bool skip_dA = false, bool have_G = false) {
   OutTable ta, tb;
   grad_tables(p, dA, dB, &ta, &tb);
   float* partial = static_cast<float*>(scratch);
@@ -245,29 +252,34 @@ hipError_t adapter_grads_impl(const mlora_problem* p, const CallCtx& c, const vo
   const hipError_t e = have_G ? hipSuccess : compute_G(p, c, X, dY, Z, G, scratch);
   if (e != hipSuccess) return e;
   const OutTable* const a = skip_dA ? nullptr : &ta;
-  if (grads_aligned(p, X, dY, Z, G) && !small)
+  if (grads_aligned(p, X, dY, Z, G) && ranges == 0)
     return grads_mfma(c, (const bf16*)dY, (const bf16*)Z, tb, (const bf16*)X, (const bf16*)G, a, accumulate, partial, c.scratch_bytes);
-  return general_grads(c, dY, Z, tb, X, G, a, accumulate, small, partial, c.scratch_bytes);
+  return general_grads(c, dY, Z, tb, X, G, a, accumulate, ranges, partial);
+}
+
+// whether, and how, a call that wants dX runs it with the gradients
+BackPlan back_plan(const mlora_problem* p, const CallCtx& c, bool want_dX) {
+  return want_dX ? plan_back(c, mfma_gemm_applies(p)) : BackPlan{false, 0, c.scratch_bytes};
 }
 
 // G, dB_k, dA_k and (unless dX is NULL) dX, given Z
 hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X, const void* dY, const void* Z, void* G,
                          void* dX, float* const* dA, float* const* dB, int accumulate, void* scratch) {
-  const bool small = dX != nullptr && small_back(c);
+  const BackPlan bp = back_plan(p, c, dX != nullptr);
   bool have_G = false;
   const size_t bytes = (size_t)c.T * c.h * elem_size(p);
-  if (small && !overlap(X, bytes, dX, bytes) && !overlap(Z, (size_t)c.T * c.ldz * elem_size(p), dX, bytes)) {
+  if (bp.shared && !overlap(X, bytes, dX, bytes) && !overlap(Z, (size_t)c.T * c.ldz * elem_size(p), dX, bytes)) {
     // the products and the gradients of a small call in one launch (not where dX overwrites the X or Z that the gradients read)
     OutTable ta, tb;
     grad_tables(p, dA, dB, &ta, &tb);
     hipError_t e = compute_G(p, c, X, dY, Z, G, scratch);
     if (e != hipSuccess) return e;
     have_G = true;
-    e = general_back(c, mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G), X, p->W, dY, Z, G, dX, ta, tb,
+    e = general_back(c, bp, mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G), X, p->W, dY, Z, G, dX, ta, tb,
                      accumulate ? 1 : 0, static_cast<float*>(scratch));
     if (e != hipErrorNotSupported) return e;
   }
-  hipError_t e = adapter_grads_impl(p, c, X, dY, Z, G, dA, dB, accumulate, scratch, small, false, have_G);
+  hipError_t e = adapter_grads_impl(p, c, X, dY, Z, G, dA, dB, accumulate, scratch, bp.ranges, false, have_G);
   if (e == hipSuccess && dX != nullptr && p->T > 0) {
     float* partial = static_cast<float*>(scratch);
     if (mfma_gemm_applies(p) && aligned16(dY) && aligned16(dX) && aligned16(G))
@@ -279,12 +291,17 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
   return e;
 }
 
-// how the base product of Y (nn) or dX is cut up
-GemmForm product_form(const mlora_problem* p, const CallCtx& c, bool nn) {
+// how the base product of Y (nn) or dX is cut up within `room` bytes of scratch
+GemmForm product_form(const mlora_problem* p, const CallCtx& c, bool nn, size_t room) {
   const int N = nn ? c.d : c.h, Kd = nn ? c.h : c.d;
   const int* const rank = c.st.rank;
-  return mfma_gemm_applies(p) ? gemm_form(c.st, c.T, N, 1, &Kd, c.scratch_bytes)
-                              : general_gemm_form(c.st, c.T, N, 1, &Kd, &rank, nn, c.dtype, c.scratch_bytes);
+  return mfma_gemm_applies(p) ? gemm_form(c.st, c.T, N, 1, &Kd, room)
+                              : general_gemm_form(c.st, c.T, N, 1, &Kd, &rank, nn, c.dtype, room);
+}
+
+// token ranges of gradients that have a launch to themselves
+int grad_ranges_alone(const CallCtx& c, bool aligned) {
+  return c.K == 0 ? 1 : (aligned ? grad_splits(c.st, c.d, c.h, c.scratch_bytes) : general_grad_ranges(c));
 }
 
 // Whether the shared-input low-rank kernels (one pass over X for all projections) apply
@@ -590,7 +607,7 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
   for (int p = 0; p < P; ++p) fused = fused && aligned16(dY[p]) && aligned16(saved[p]) && aligned16(G[p]);
   for (int p = 0; p < P; ++p) {
     hipError_t e = adapter_grads_impl(ps[p], c[p], X, dY[p], saved[p], G[p], ps[0]->K > 0 ? dA[p] : nullptr,
-                                      ps[0]->K > 0 ? dB[p] : nullptr, accumulate, w, dX != nullptr && small_back(c[p]), fused);  // w: behind the last G_p
+                                      ps[0]->K > 0 ? dB[p] : nullptr, accumulate, w, back_plan(ps[p], c[p], dX != nullptr).ranges, fused);  // w: behind the last G_p
     if (e != hipSuccess) return hip_status(e);
   }
   if (fused) {
@@ -660,7 +677,8 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
   fill_ctx(p, nullptr, &c);
   const size_t room = c.scratch_bytes;
   const bool al = mfma_lowrank_applies(p);
-  const GemmForm y = product_form(p, c, true), dx = product_form(p, c, false);
+  const BackPlan bp = back_plan(p, c, true);
+  const GemmForm y = product_form(p, c, true, room), dx = product_form(p, c, false, bp.left);
   const RowsForm z = al && !general_rows_pay(c) ? rows_form(c.st, c.h, c.ldz, room) : general_rows_form(c, c.h);
   const RowsForm g = al ? rows_form(c.st, c.d, c.ldz, room) : general_rows_form(c, c.d);
   plan[MLORA_PLAN_Y] = y.form;
@@ -671,7 +689,7 @@ mlora_status mlora_kernel_plan(const mlora_problem* p, int32_t* plan) {
   plan[MLORA_PLAN_Z_PARTS] = z.parts;
   plan[MLORA_PLAN_G_ROWS] = g.rows;
   plan[MLORA_PLAN_G_PARTS] = g.parts;
-  plan[MLORA_PLAN_GRADS] = c.K == 0 ? 1 : (al && !small_back(c) ? grad_splits(c.st, c.d, c.h, room) : general_grad_ranges(c, small_back(c), room));
+  plan[MLORA_PLAN_GRADS] = bp.shared ? bp.ranges : grad_ranges_alone(c, al);
   return MLORA_OK;
 }
 
@@ -681,13 +699,16 @@ mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles) {
   if (tiles == nullptr) return MLORA_ERR_NULL;
   CallCtx c;
   fill_ctx(p, nullptr, &c);
-  const GemmForm y = product_form(p, c, true), dx = product_form(p, c, false);
+  const BackPlan bp = back_plan(p, c, true);
+  const GemmForm y = product_form(p, c, true, c.scratch_bytes), dx = product_form(p, c, false, bp.left);
   tiles[MLORA_PLAN_Y_WHOLE] = y.whole;
   tiles[MLORA_PLAN_Y_TILES] = y.tiles;
   tiles[MLORA_PLAN_DX_WHOLE] = dx.whole;
   tiles[MLORA_PLAN_DX_TILES] = dx.tiles;
   tiles[MLORA_PLAN_Y_ROWS] = y.rows;
   tiles[MLORA_PLAN_DX_ROWS] = dx.rows;
+  tiles[MLORA_PLAN_SHARED] = bp.shared ? 1 : 0;
+  tiles[MLORA_PLAN_GRADS_ALONE] = grad_ranges_alone(c, mfma_lowrank_applies(p));
   return MLORA_OK;
 }
 

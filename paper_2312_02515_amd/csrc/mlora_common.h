@@ -111,6 +111,8 @@ struct CallCtx {
 // `scratch` (`partial`) that they are given; 0 = none does.  The size functions give the most that T
 // rows or fewer use, whatever their split positions.
 size_t general_scratch_bytes(const SegTable& st, int T, int h, int d, int dtype);
+size_t general_grad_bytes(const SegTable& st, int T, int h, int d);     // the gradients' share of it
+size_t general_dx_bytes(int K, int T, int h, int d, int dtype);         // the input gradient's
 hipError_t general_Z(const CallCtx& c, const void* X, void* Z, float* scratch);      // Z = s x A
 hipError_t general_G(const CallCtx& c, const void* dY, void* G, float* scratch);     // G = s dy B^T
 // One operand pair of a base product: A [M, Kd], W [Kd, N] (nn) or [N, Kd], L [M, ldz] with
@@ -130,18 +132,26 @@ GemmForm general_gemm_form(const SegTable& st, int M, int N, int n, const int* K
                            size_t scratch_bytes);
 double general_rows_us(const CallCtx& c, int inner, double* block_bytes);
 RowsForm general_rows_form(const CallCtx& c, int inner);
-int general_grad_ranges(const CallCtx& c, bool small, size_t scratch_bytes);
+int general_grad_ranges(const CallCtx& c);
+double general_skinny_us(const SegTable& st, int M, int N, long long Kd, int dtype);
 // C = sum over the n <= MLORA_MAX_GROUP operand pairs of A op(W) + rows_k(L R_k)
 hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M, int N, bool nn, const SegTable& st,
                         float* scratch, size_t scratch_bytes, hipStream_t stream);
-// dB_k = Z^T dy_k and, unless dA is NULL, dA_k = x_k^T G (`small`: of a call that is small_back and wants dX)
+// dB_k = Z^T dy_k and, unless dA is NULL, dA_k = x_k^T G, in `ranges` token ranges (0: as many as suit the launch alone)
 hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G,
-                         const OutTable* dA, int accumulate, bool small, float* scratch, size_t scratch_bytes);
+                         const OutTable* dA, int accumulate, int ranges, float* scratch);
 
 // Small backward calls: dX (as in general_gemm, one operand pair; `aligned`: in the forms of gemm_mfma), dA_k and dB_k in
-// one launch, and one each for ranges to add.  hipErrorNotSupported, with nothing launched: not at these sizes.
-bool small_back(const CallCtx& c);
-hipError_t general_back(const CallCtx& c, bool aligned, const void* X, const void* W, const void* dY, const void* Z, const void* G,
+// one launch, and one each for ranges to add.
+constexpr long long kMostShared = 4 << 20;   // activation elements (X and dY) of such a call
+struct BackPlan {
+  bool shared;        // whether a call of these sizes runs so
+  int ranges;         // token ranges of the gradients (0: not shared)
+  size_t left;        // scratch for the product's ranges, behind the gradients' sums
+};
+BackPlan plan_back(const CallCtx& c, bool aligned);
+// hipErrorNotSupported, with nothing launched: buffers whose alignment takes dX to another form than the plan's
+hipError_t general_back(const CallCtx& c, const BackPlan& bp, bool aligned, const void* X, const void* W, const void* dY, const void* Z, const void* G,
                         void* dX, const OutTable& dA, const OutTable& dB, int accumulate, float* scratch);
 
 // gemm_mfma.hip : bf16 MFMA GEMM with the LoRA term as extra contraction steps

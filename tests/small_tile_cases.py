@@ -74,3 +74,37 @@ ROWS = [
     ("bf16", (219, 1920, 128, [22] * 9, [114, 5, 70, 128, 1, 99, 66, 8, 33], 2), {"Z_rows": 16, "Z_parts": 8}),
     ("bf16", (4458, 640, 128, [100] * 43, [123, 64, 7] * 14 + [97], 2), {"Z_rows": 16, "Z_parts": 1}),
 ]
+
+
+# Small backward calls, whose dX and gradients share a launch: every form of the product, with one range and several of
+# either (grads_alone: the gradients' ranges where they have a launch to themselves)
+SMALL_BACK = [(t, c, dict(w, shared=1)) for t, c, w in [
+    ("f32", (128, 256, 256, [60, 60], [8, 5], 4), {"dX": "skinny", "grads": 1}),
+    ("bf16", (400, 64, 64, [100, 0, 290], [16, 3, 8], 4), {"dX": "skinny", "grads": 1}),
+    ("bf16", (1001, 70, 514, [980], [40], 13), {"dX": "skinny", "grads": 7, "grads_alone": 11}),
+    ("f32", (714, 256, 64, [200, 300, 214], [8, 8, 8], 0), {"dX": "skinny", "grads": 4}),
+    ("f32", (571, 1088, 256, [100, 371, 100], [46, 4, 2], 0), {"dX": "64"}),
+    ("f32", (500, 700, 1001, [100, 390], [17, 4], 3), {"dX": "64", "dX_parts": 2, "grads": 5}),
+    ("f32", (900, 300, 1500, [880], [64], 3), {"dX": "64", "dX_parts": 6, "grads": 10}),
+    ("f32", (300, 2001, 501, [150, 140], [16, 3], 0), {"dX": "64", "grads": 1}),
+    ("f32", (500, 701, 701, [500], [16], 0), {"dX": "64", "dX_parts": 5, "grads": 6}),
+    ("bf16", (913, 1000, 1500, [300, 77, 513], [8, 10, 16], 5), {"dX": "64", "dX_parts": 1, "grads": 1}),
+    ("bf16", (1500, 999, 1500, [1400], [50], 5), {"dX": "64", "dX_parts": 1, "grads": 9}),
+    ("bf16", (913, 1024, 1536, [300, 77, 513], [8, 10, 16], 5), {"dX": "ring", "dX_parts": 1, "grads": 1, "grads_alone": 2}),
+    ("bf16", (300, 1216, 1984, [100, 190], [32, 5], 10), {"dX": "ring", "dX_parts": 1, "grads": 1}),
+    ("bf16", (60, 584, 4040, [37, 20], [12, 40], 1), {"dX": "ring", "dX_parts": 8, "grads": 1}),
+    # two blocks of gradients in one of the two-group ring, an odd number of them
+    ("bf16", (908, 768, 2624, [16, 8, 87, 48, 200, 15, 5, 100, 373, 28, 23, 5], [16, 3, 8] * 4, 0), {"dX": "ring", "dX_parts": 1, "grads": 1}),
+    ("bf16", (908, 768, 2496, [16, 8, 87, 48, 90, 15, 5, 90, 90, 28, 23], [16] * 11, 4), {"dX": "ring", "dX_parts": 1, "grads": 1}),
+    ("bf16", (1400, 2048, 192, [700, 691], [20, 8], 4), {"dX": "ring", "dX_parts": 1, "grads": 5, "grads_alone": 2}),
+]]
+# ... and calls of no more activation elements whose product runs in larger tiles: the gradients have their own launch, in
+# its ranges, as without dX
+APART = [(t, c, dict(w, shared=0)) for t, c, w in [
+    ("bf16", (512, 4096, 4096, [512], [16], 0), {"dX": "halves", "grads": 2, "grads_alone": 2}),
+    ("bf16", (256, 4096, 11008, [256], [16], 0), {"dX": "halves", "grads": 1, "grads_alone": 1}),
+    ("bf16", (300, 5120, 5120, [300], [8], 0), {"dX": "halves"}),
+    ("bf16", (150, 13824, 5120, [150], [8], 0), {"dX": "halves"}),
+    ("bf16", (4000, 901, 99, [1000] * 4, [40] * 4, 0), {"dX": "128", "grads": 11, "grads_alone": 11}),
+    ("bf16", (1000, 512, 512, [1000], [40], 0), {"grads": 3, "grads_alone": 3}),       # ranks above 32 in the aligned kernel
+]]

@@ -3,7 +3,7 @@ but not of 64), and low-rank products of few rows in contraction ranges, at the 
 import pytest
 import torch
 
-from tests.small_tile_cases import CASES, PACKED, ROWS
+from tests.small_tile_cases import APART, CASES, PACKED, ROWS, SMALL_BACK
 from tests.test_host_abi import mb  # noqa: F401  (a fixture)
 from tests.test_launch_plans import plan
 
@@ -95,29 +95,22 @@ def test_packed_group(dtype):
     check_group(ins, run_group(ins), TOL[dtype])
 
 
-# small backward calls, whose dX and gradients share a launch: every form of the product with one and several ranges of
-# either; overwriting, and adding to the gradients
-SMALL_BACK = [
-    (torch.float32, (128, 256, 256, [60, 60], [8, 5], 4)),                  # 16 x 64 tiles
-    (torch.bfloat16, (400, 64, 64, [100, 0, 290], [16, 3, 8], 4)),
-    (torch.bfloat16, (1001, 70, 514, [980], [40], 13)),                     # ... ranges of tokens
-    (torch.float32, (500, 700, 1001, [100, 390], [17, 4], 3)),              # 64 x 64 tiles
-    (torch.float32, (900, 300, 1500, [880], [64], 3)),                      # ... ranges of both
-    (torch.bfloat16, (913, 1000, 1500, [300, 77, 513], [8, 10, 16], 5)),
-    (torch.bfloat16, (1500, 999, 1500, [1400], [50], 5)),
-    (torch.bfloat16, (913, 1024, 1536, [300, 77, 513], [8, 10, 16], 5)),    # small aligned tiles
-    (torch.bfloat16, (300, 1216, 1984, [100, 190], [32, 5], 10)),
-    (torch.bfloat16, (60, 584, 4040, [37, 20], [12, 40], 1)),
-]
+@pytest.mark.parametrize("dtype,case,want", SMALL_BACK + APART)
+def test_small_backward_takes_its_form(mb, dtype, case, want):  # noqa: F811
+    T, h, d, tokens, ranks, lead = case
+    got = plan(mb, T, h, d, tokens, ranks, lead, f32=dtype == "f32")
+    assert {k: got[k] for k in want} == want
 
 
+# small backward calls, whose dX and gradients share a launch; overwriting, and adding to the gradients
 @pytest.mark.gpu
-@pytest.mark.parametrize("dtype,case", SMALL_BACK)
+@pytest.mark.parametrize("dtype,case", [(t, c) for t, c, _ in SMALL_BACK])
 def test_small_backward(dtype, case):
     from paper_2312_02515_amd import binding as hip
     from tests.parity_util import TOL, check_full, run_hip
     from tests.test_gpu_general import _inputs
     T, h, d, tokens, ranks, lead = case
+    dtype = torch.float32 if dtype == "f32" else torch.bfloat16
     inp = _inputs(T, h, d, tokens, ranks, dtype, lead=lead, seed=95)
     out = run_hip(inp)
     check_full(inp, out, TOL[dtype], label=f"small backward {case}")
