@@ -1112,6 +1112,17 @@ __global__ __launch_bounds__(256) void k_gen_grad(const GenGradArgs b, const Gen
   gen_grads_body<T, NQ>(b, a, blocks_b, gridDim.x, blockIdx.x);
 }
 
+// ... of two projections that share their input
+struct TwoGrads {
+  GenGradArgs b[2], a[2];
+  int blocks_b[2], blocks[2];
+};
+template <typename T, int NQ>
+__global__ __launch_bounds__(256) void k_gen_grad_two(const TwoGrads p) {
+  const int second = (int)blockIdx.x >= p.blocks[0] ? 1 : 0;
+  gen_grads_body<T, NQ>(p.b[second], p.a[second], p.blocks_b[second], p.blocks[second], (int)blockIdx.x - (second ? p.blocks[0] : 0));
+}
+
 // Both gradients (the first blocks, which take longest) and the input gradient's product in one launch: neither reads what the other
 // writes, each leaves most of the chip idle in a small call, and a launch costs 4 us.  Backward calls, two launches and the ranges'
 // reduction -> one, us: bf16 913 x 1000 -> 1500 (3 tasks) 28.9 -> 22.9, 1024 -> 1536 21.9 -> 16.4, 1000 x 3000 -> 1000 33.0 -> 26.0,
@@ -1640,6 +1651,59 @@ bool small_product(const CallCtx& c, bool aligned, size_t limit, double* us) {
   return pl.small && !pl.packed;
 }
 }  // namespace
+
+namespace {
+template <typename T>
+void launch_two(const TwoGrads& p, int ldz, hipStream_t s) {
+  const dim3 grid((unsigned)(p.blocks[0] + p.blocks[1]));
+  if (ldz <= 16) hipLaunchKernelGGL((k_gen_grad_two<T, 1>), grid, dim3(256), 0, s, p);
+  else if (ldz <= 32) hipLaunchKernelGGL((k_gen_grad_two<T, 2>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((k_gen_grad_two<T, 4>), grid, dim3(256), 0, s, p);
+}
+}  // namespace
+
+// The gradients of a group's projections, two to a launch where their sums fit the scratch together: a group's dX is a product of its
+// own, and the ranges that suit a shared launch are long ones.  A launch each in ranges of 64 tokens -> as here, a step, us:
+// bf16 500 x 701 -> 3 x 701 110 -> 102, 1000 x 500 -> 2 x 300 (4 tasks, rank 40) 60 -> 56; fp32 300 x 2001 -> 2001, 501 142 -> 139; a
+// launch each in the long ranges 120, 64, 149.
+hipError_t general_grads_group(int n, const GradItem* items, int accumulate, float* scratch, size_t scratch_bytes) {
+  for (int i = 0; i < n; ++i) {
+    const GradItem& x = items[i];
+    const CallCtx& c = *x.c;
+    auto sums = [](const GradItem& g) { return g.ranges > 1 ? grad_sum_bytes(g.c->st, g.ranges, g.c->d, g.c->h) : 0; };
+    const size_t first = sums(x);
+    hipError_t e;
+    if (i + 1 == n || c.ldz > 64 || items[i + 1].c->ldz > 64 || first + sums(items[i + 1]) > scratch_bytes) {
+      e = general_grads(c, x.dY, x.Z, *x.dB, x.X, x.G, x.dA, accumulate, x.ranges, scratch);
+      if (e != hipSuccess) return e;
+      continue;
+    }
+    const GradItem& y = items[++i];
+    TwoGrads p;
+    int ldz = 0;
+    for (int q = 0; q < 2; ++q) {
+      const GradItem& g = q ? y : x;
+      GradPlan gp;
+      plan_grads(*g.c, g.dY, g.Z, *g.dB, g.X, g.G, g.dA, accumulate, g.ranges, scratch + (q ? first / sizeof(float) : 0), &gp);
+      p.b[q] = gp.b;
+      p.a[q] = gp.a;
+      p.blocks_b[q] = gp.blocks_b;
+      p.blocks[q] = gp.blocks;
+      ldz = g.c->ldz > ldz ? g.c->ldz : ldz;
+    }
+    if (c.dtype == MLORA_F32) launch_two<float>(p, ldz, c.stream);
+    else launch_two<bf16>(p, ldz, c.stream);
+    e = hipGetLastError();
+    for (int q = 0; q < 2 && e == hipSuccess; ++q) {
+      const GradItem& g = q ? y : x;
+      if (g.ranges > 1)
+        e = grad_reduce(g.c->st, scratch + (q ? first / sizeof(float) : 0), g.ranges, g.c->d, *g.dB, g.dA != nullptr ? g.c->h : 0,
+                        g.dA != nullptr ? *g.dA : *g.dB, accumulate, c.stream);
+    }
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 // Calls whose gradients and dX leave most CUs idle each: up to 4 Mi activation elements, ranks up to 64 (higher ones take all
 // registers), and up to 32 where the aligned gradients could run, which are faster above (2000 x 256 -> 256, 16 tasks, rank 64

@@ -605,9 +605,28 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
   }
   bool fused = ps[0]->K > 0 && group_lowrank_applies(ps, P, X) && group_grads_pay(c[0].st, c[0].h);
   for (int p = 0; p < P; ++p) fused = fused && aligned16(dY[p]) && aligned16(saved[p]) && aligned16(G[p]);
+  size_t scratch = 0;   // what the size query reserved behind the last G_p, at w
+  for (int p = 0; p < P; ++p) scratch = c[p].scratch_bytes > scratch ? c[p].scratch_bytes : scratch;
+  // projections whose calls share a launch with dX, in their ranges: the gradients of a call have the same bits in a group
+  GradItem small[MLORA_MAX_GROUP];
+  OutTable tables[MLORA_MAX_GROUP][2];
+  int smalls = 0;
   for (int p = 0; p < P; ++p) {
-    hipError_t e = adapter_grads_impl(ps[p], c[p], X, dY[p], saved[p], G[p], ps[0]->K > 0 ? dA[p] : nullptr,
-                                      ps[0]->K > 0 ? dB[p] : nullptr, accumulate, w, back_plan(ps[p], c[p], dX != nullptr).ranges, fused);  // w: behind the last G_p
+    const int ranges = ps[0]->K > 0 ? back_plan(ps[p], c[p], dX != nullptr).ranges : 0;
+    hipError_t e;
+    if (ranges > 0) {
+      OutTable* t = tables[smalls];
+      grad_tables(ps[p], dA[p], dB[p], &t[0], &t[1]);
+      small[smalls++] = GradItem{&c[p], dY[p], saved[p], X, G[p], &t[1], fused ? nullptr : &t[0], ranges};
+      e = compute_G(ps[p], c[p], X, dY[p], saved[p], G[p], w);
+    } else {
+      e = adapter_grads_impl(ps[p], c[p], X, dY[p], saved[p], G[p], ps[0]->K > 0 ? dA[p] : nullptr,
+                             ps[0]->K > 0 ? dB[p] : nullptr, accumulate, w, 0, fused);
+    }
+    if (e != hipSuccess) return hip_status(e);
+  }
+  {
+    const hipError_t e = general_grads_group(smalls, small, accumulate ? 1 : 0, reinterpret_cast<float*>(w), scratch);
     if (e != hipSuccess) return hip_status(e);
   }
   if (fused) {
@@ -623,8 +642,6 @@ mlora_status mlora_lora_group_bwd(const mlora_problem* const* ps, int P, const v
   }
   if (dX == nullptr || ps[0]->T == 0) return MLORA_OK;
   hipError_t e = hipSuccess;
-  size_t scratch = 0;   // what the size query reserved behind the last G_p
-  for (int p = 0; p < P; ++p) scratch = c[p].scratch_bytes > scratch ? c[p].scratch_bytes : scratch;
   float* partial = reinterpret_cast<float*>(w);
   if (sum_kernel) {
     // one kernel: the P products accumulate in fp32 in the same output tile, dX is written once

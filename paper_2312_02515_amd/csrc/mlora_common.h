@@ -141,6 +141,15 @@ hipError_t general_gemm(int n, const GenOperands* ops, int dtype, void* C, int M
 hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const OutTable& dB, const void* X, const void* G,
                          const OutTable* dA, int accumulate, int ranges, float* scratch);
 
+// ... of a group's projections (same tasks and X), in `ranges` >= 1
+struct GradItem {
+  const CallCtx* c;
+  const void *dY, *Z, *X, *G;
+  const OutTable *dB, *dA;
+  int ranges;
+};
+hipError_t general_grads_group(int n, const GradItem* items, int accumulate, float* scratch, size_t scratch_bytes);
+
 // Small backward calls: dX (as in general_gemm, one operand pair; `aligned`: in the forms of gemm_mfma), dA_k and dB_k in
 // one launch, and one each for ranges to add.
 constexpr long long kMostShared = 4 << 20;   // activation elements (X and dY) of such a call

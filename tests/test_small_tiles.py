@@ -103,6 +103,40 @@ def test_small_backward_takes_its_form(mb, dtype, case, want):  # noqa: F811
 
 
 # small backward calls, whose dX and gradients share a launch; overwriting, and adding to the gradients
+# groups of such projections, whose gradients share launches in pairs: one range, several, projections in larger tiles
+# between them, ranks above the others'
+GROUPS = [
+    ("f32", 500, 300, [700, 120, 1001], [100, 0, 390], [[17, 4, 8], [3, 16, 1], [64, 9, 30]]),
+    ("bf16", 913, 999, [1500, 300], [300, 77, 513], [[8, 10, 16], [40, 3, 64]]),
+    ("bf16", 1300, 512, [512, 4096, 64, 128], [700, 590], [[8, 32], [16, 3], [20, 20], [1, 5]]),
+    ("bf16", 400, 704, [640, 5120, 128], [200, 196], [[8, 16], [16, 16], [9, 30]]),
+]
+
+
+@pytest.mark.parametrize("dtype,T,h,ds,tokens,ranks", GROUPS)
+def test_small_groups_share_launches(mb, dtype, T, h, ds, tokens, ranks):  # noqa: F811
+    plans = [plan(mb, T, h, d, tokens, r, 3, f32=dtype == "f32") for d, r in zip(ds, ranks)]
+    assert sum(p["shared"] for p in plans) > 1, [(p["shared"], p["grads"]) for p in plans]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,T,h,ds,tokens,ranks", GROUPS)
+def test_small_groups(dtype, T, h, ds, tokens, ranks):
+    """The gradients against the oracle, bit for bit those of single calls, and added to what is there."""
+    from tests.parity_util import TOL, run_hip
+    from tests.test_gpu_groups import _group_inputs, check_group, run_group
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    ins = _group_inputs(T, h, ds, tokens, ranks, dt, lead=3, seed=96)
+    out = run_group(ins)
+    check_group(ins, out, TOL[dt], label=f"small group {ds}")
+    acc = run_group(ins, accumulate=True, preset=(0.5, -1.5))
+    for p, i in enumerate(ins):
+        one = run_hip(i)
+        for k in range(len(tokens)):
+            assert torch.equal(one["dA"][k], out["dA"][p][k]) and torch.equal(one["dB"][k], out["dB"][p][k]), (p, k)
+            assert torch.equal(acc["dA"][p][k], out["dA"][p][k] + 0.5) and torch.equal(acc["dB"][p][k], out["dB"][p][k] - 1.5), (p, k)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,case", [(t, c) for t, c, _ in SMALL_BACK])
 def test_small_backward(dtype, case):
