@@ -130,7 +130,7 @@ void launch_halves(const gemmk::GemmArgs<NSEG>& a, bool packed, hipStream_t stre
 // that the rule takes lost, and with 7 % one, by 8 % (256 x 11008 -> 4096).  Half tiles -> small tiles, us of the call:
 //   100 x 4096 -> 4096  31 -> 25     32 x 4096 -> 11008  40 -> 28     100 x 8192 -> 8192  51 -> 42     8 x 2048 -> 8192  28 -> 19
 //   30 x 9752 -> 6144 (2 tasks)  72 -> 36     25 x 1824 -> 10296  34 -> 18     50 x 4896 -> 4072 (11 tasks)  50 -> 41
-//   2740 x 368 -> 1600 (84 tiles)  24.4 -> 21.6     3191 x 312 -> 1232 (65)  20.0 -> 18.1
+//   2740 x 368 -> 1600 (84 tiles)  24.4 -> 21.6     3191 x 312 -> 1232 (65; now the general kernel, 18.7)  20.0 -> 18.1
 //   4291 x 64 -> 1536 (1656 small tiles)  stays: a step 70.8 us, 73.0
 constexpr int kSmallTiles = 64, kMostTiles = 128, kMostSmallTiles = 5 * 256;
 struct Plan {
@@ -254,6 +254,15 @@ bool skinny(const SegTable& st, int M, int N, long long Kd) {
   return (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN) <= kSmallTiles && general_skinny(st, M, N, Kd, MLORA_BF16);
 }
 
+// Forward products whose features are no multiples of 64, between three and four small tiles per CU, seven contraction tiles
+// deep at most: the 64 x 64 tiles of the general kernel, of which a CU holds five.  Call, small tiles -> general, us: 641 x 200 -> 4504
+// 16.4 -> 14.7, 1527 x 240 -> 2136 (10 tasks) 18.2 -> 16.2, 700 x 136 -> 4504 15.8 -> 15.1, 1500 x 328 -> 2136 18.5 -> 17.6, 700 x 392 ->
+// 4504 19.7 -> 19.5; with 756 tiles (300 x 200 -> 8008) 13.5 and 14.2, beyond 1024 larger tiles are faster than either.
+bool general_forward(const SegTable& st, int M, int N, int Kd, const Plan& pl) {
+  const long long n = (virtual_rows(st, M) + 63) / 64 * ((N + 63) / 64);
+  return (N % 64 != 0 || Kd % 64 != 0) && pl.small > 0 && pl.parts == 1 && n > 3 * 256 && n <= 4 * 256 && Kd <= 7 * 64;
+}
+
 template <int NSEG>
 void fill_common(gemmk::GemmArgs<NSEG>* a, bf16* C, int M, int N, const SegTable& st) {
   a->C = C;
@@ -314,7 +323,7 @@ hipError_t launch_sum(const GemmOperands* ops, bf16* C, int M, int N, const SegT
 // C[M,N] = A[M,Kd] * (nn ? Bm[Kd,N] : Bm[N,Kd]^T) + rows_k( L[rows_k, :r_k] * (nn ? R_k[r_k,N] : R_k[N,r_k]^T) )
 hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, bool nn, const bf16* L, int ldz,
                      const SegTable& st, const PtrTable& R, float* scratch, size_t scratch_bytes, hipStream_t stream) {
-  if (skinny(st, M, N, Kd)) {
+  if (skinny(st, M, N, Kd) || (nn && general_forward(st, M, N, Kd, plan_gemm(st, M, N, (Kd + 63) / 64, 1, scratch_bytes)))) {
     const GenOperands o{A, Bm, L, Kd, ldz, st.rank, &R};
     return general_gemm(1, &o, MLORA_BF16, C, M, N, nn, st, scratch, scratch_bytes, stream);
   }
@@ -359,7 +368,7 @@ SmallForm gemm_small_nt(const bf16* A, const bf16* Bm, bf16* C, int M, int N, in
   return kRing;
 }
 
-GemmForm gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, size_t scratch_bytes) {
+GemmForm gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, bool nn, size_t scratch_bytes) {
   const long long mv = virtual_rows(st, M), total = (mv + BM - 1) / BM * ((N + BN - 1) / BN);
   long long kd = 0;
   int kt = 0;
@@ -370,6 +379,10 @@ GemmForm gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, size_
   auto tiles = [&](int rows) { return (int)((mv + rows - 1) / rows * ((N + 63) / 64)); };
   if (skinny(st, M, N, kd)) return GemmForm{MLORA_FORM_SKINNY, 1, tiles(16), tiles(16), 16};
   const Plan pl = plan_gemm(st, M, N, kt, n, scratch_bytes);
+  if (nn && general_forward(st, M, N, Kd[0], pl)) {
+    const int* const rank = st.rank;
+    return general_gemm_form(st, M, N, 1, Kd, &rank, true, MLORA_BF16, scratch_bytes);
+  }
   if (pl.small > 0) return GemmForm{MLORA_FORM_RING, pl.parts, tiles(64), tiles(64), 64};
   if (pl.packed) return GemmForm{MLORA_FORM_HALVES, pl.parts, 0, (M + BM - 1) / BM * ((N + BN - 1) / BN), BM / 2};
   const int form = pl.whole == total ? MLORA_FORM_WHOLE : (pl.whole == 0 ? MLORA_FORM_HALVES : MLORA_FORM_MIXED);

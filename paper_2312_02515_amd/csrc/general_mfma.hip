@@ -1664,7 +1664,7 @@ void launch_two(const TwoGrads& p, int ldz, hipStream_t s) {
 
 // The gradients of a group's projections, two to a launch where their sums fit the scratch together: a group's dX is a product of its
 // own, and the ranges that suit a shared launch are long ones.  A launch each in ranges of 64 tokens -> as here, a step, us:
-// bf16 500 x 701 -> 3 x 701 110 -> 102, 1000 x 500 -> 2 x 300 (4 tasks, rank 40) 60 -> 56; fp32 300 x 2001 -> 2001, 501 142 -> 139; a
+// bf16 500 x 701 -> 3 x 701 110 -> 109, 1000 x 500 -> 2 x 300 (4 tasks, rank 40) 60 -> 52; fp32 300 x 2001 -> 2001, 501 142 -> 138; a
 // launch each in the long ranges 120, 64, 149.
 hipError_t general_grads_group(int n, const GradItem* items, int accumulate, float* scratch, size_t scratch_bytes) {
   for (int i = 0; i < n; ++i) {

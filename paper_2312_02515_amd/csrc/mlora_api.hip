@@ -295,7 +295,7 @@ hipError_t backward_impl(const mlora_problem* p, const CallCtx& c, const void* X
 GemmForm product_form(const mlora_problem* p, const CallCtx& c, bool nn, size_t room) {
   const int N = nn ? c.d : c.h, Kd = nn ? c.h : c.d;
   const int* const rank = c.st.rank;
-  return mfma_gemm_applies(p) ? gemm_form(c.st, c.T, N, 1, &Kd, room)
+  return mfma_gemm_applies(p) ? gemm_form(c.st, c.T, N, 1, &Kd, nn, room)
                               : general_gemm_form(c.st, c.T, N, 1, &Kd, &rank, nn, c.dtype, room);
 }
 
@@ -745,7 +745,7 @@ mlora_status mlora_kernel_plan_group(const mlora_problem* const* ps, int P, int3
     al = al && mfma_gemm_applies(ps[p]);
     room = c[p].scratch_bytes > room ? c[p].scratch_bytes : room;
   }
-  const GemmForm f = al ? gemm_form(c[0].st, c[0].T, c[0].h, P, Kd, room)
+  const GemmForm f = al ? gemm_form(c[0].st, c[0].T, c[0].h, P, Kd, false, room)
                         : general_gemm_form(c[0].st, c[0].T, c[0].h, P, Kd, rank, false, c[0].dtype, room);
   plan[MLORA_PLAN_GROUP_DX] = f.form;
   plan[MLORA_PLAN_GROUP_DX_PARTS] = f.parts;

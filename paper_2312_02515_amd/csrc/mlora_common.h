@@ -168,7 +168,7 @@ bool gemm_mfma_ok(int M, int N, int Kd);
 hipError_t gemm_mfma(const bf16* A, const bf16* Bm, bf16* C, int M, int N, int Kd, bool nn, const bf16* L, int ldz,
                      const SegTable& st, const PtrTable& R, float* scratch, size_t scratch_bytes, hipStream_t stream);
 size_t gemm_partial_bytes(int K, int T, int N, int Kd);
-GemmForm gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, size_t scratch_bytes);
+GemmForm gemm_form(const SegTable& st, int M, int N, int n, const int* Kd, bool nn, size_t scratch_bytes);
 
 // One operand pair of a summed contraction (the input gradient of projections that share X):
 // A [M, Kd], Bm [N, Kd], L [M, ldz] with R_k [N, rank[k]].

@@ -24,6 +24,8 @@ CASES = [
     # ... more than 64 tiles of 256 x 256
     ((2740, 368, 1600, [230] * 11 + [201], [64, 9, 16] * 4, 4), {"Y_rows": 64}),
     ((3191, 1232, 312, [1600, 1560], [32, 17], 4), {"dX_rows": 64}),
+    # ... between three and four of them per CU: the general kernel's
+    ((641, 200, 4504, [200, 203, 231], [64, 9, 16], 3), {"Y_rows": 64, "Y": "64"}),
     # 16 x 64 tiles
     ((128, 256, 256, [60, 60], [8, 64], 4), {"Y_rows": 16, "dX_rows": 16}),
     # partial contraction tiles, one chunk more or less than a whole one; 64 x 64 tiles

@@ -96,8 +96,14 @@ def test_form_names(mb, dtype, sizes, form, rows):  # noqa: F811
     (700, 8200, 2056, [300, 400], [16, 16], dict(Y="halves", Y_parts=4)),
     # small tiles beyond 64 tiles of 256 x 256
     (2740, 368, 1600, [130, 123, 21, 273, 336, 190, 92, 125, 379, 551, 105, 415], [16, 64, 32] * 4, dict(Y="ring")),
-    (3191, 312, 1232, [1600, 1591], [32, 16], dict(Y="ring")),
+    (3191, 504, 1232, [1600, 1591], [32, 16], dict(Y="ring")),
     (3000, 512, 2944, [3000], [16], dict(Y="whole")),
+    # between three and four small tiles per CU: the general kernel's, unless the features are multiples of 64
+    (641, 200, 4504, [200, 200, 241], [64, 8, 16], dict(Y="64")),
+    (1500, 392, 2136, [500] * 3, [64, 16, 32], dict(Y="64")),
+    (1500, 456, 2136, [500] * 3, [64, 16, 32], dict(Y="ring")),
+    (641, 192, 4544, [200, 200, 241], [64, 8, 16], dict(Y="ring")),
+    (300, 200, 8008, [100] * 3, [64, 8, 16], dict(Y="ring")),
     (4291, 64, 1536, [656, 69, 1776, 1044, 16, 411, 319], [67, 3, 1, 5, 2, 81, 9], dict(Y="halves")),
 ])
 def test_plans_of_known_calls(mb, T, h, d, tokens, ranks, want):  # noqa: F811
