@@ -782,12 +782,12 @@ __device__ __forceinline__ float shared_sum(const float* red, int t) {
   return sum;
 }
 
-template <typename T, int VW, int RM, int NW, bool KMAJOR>
+template <typename T, int VW, int RM, int NW, bool KMAJOR, bool RANGES>
 __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, int hi, int sp, float* red) {
   const int r = a.rank[k];
   // this block's range, in whole runs of 64 contraction indices
   int c0 = 0, inner = a.inner;
-  if (a.parts > 1) {
+  if constexpr (RANGES) {
     const unsigned runs = (unsigned)(a.inner + 63) / 64;
     c0 = (int)(runs * (unsigned)sp / (unsigned)a.parts) * 64;
     const int c1 = (int)(runs * (unsigned)(sp + 1) / (unsigned)a.parts) * 64;
@@ -810,7 +810,7 @@ __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, i
                                          KMAJOR ? r : a.inner, 0, r, wave, lane);
   share_sums<VW, RM, NW>(acc, red, wave, lane);
   constexpr int FR = RM * VW * 256;
-  if (a.parts > 1) {
+  if constexpr (RANGES) {
     float* part = a.part + ((size_t)sp * (a.off[a.K] - a.off[0]) + lo - a.off[0]) * a.ldz;
     for (int t = tid; t < FR; t += NW * 64) {
       const float sum = shared_sum<FR, NW / 2>(red, t);
@@ -833,22 +833,23 @@ __device__ __forceinline__ void rows_body(const GenRowsArgs& a, int k, int lo, i
     for (int t = tid; t < (hi - lo) * pad; t += NW * 64) Out[(size_t)(lo + t / pad) * a.ldz + r + t % pad] = T(0.f);
 }
 
-template <typename T, int RM, int NW, bool KMAJOR>
+// RANGES: whether the contraction is cut (the code for it costs the others 0.2 to 0.3 us of a launch of 4.1)
+template <typename T, int RM, int NW, bool KMAJOR, bool RANGES>
 __global__ __launch_bounds__(NW * 64, 4) void k_gen_rows(const GenRowsArgs a) {
   extern __shared__ float red[];         // NW / 2 x RM x (groups of the largest rank) KiB
   int lo = 0, hi = 0;
   int block = blockIdx.x, sp = 0;
-  if (a.parts > 1) {
+  if constexpr (RANGES) {
     sp = block % a.parts;
     block /= a.parts;
   }
   const int k = rows_block<16 * RM>(a, a.b0 + block, &lo, &hi);
   if (k < 0) return;
   const int r = a.rank[k];
-  if (r <= 16) rows_body<T, 1, RM, NW, KMAJOR>(a, k, lo, hi, sp, red);
-  else if (r <= 32) rows_body<T, 2, RM, NW, KMAJOR>(a, k, lo, hi, sp, red);
-  else if (r <= 64) rows_body<T, 4, RM, NW, KMAJOR>(a, k, lo, hi, sp, red);
-  else if constexpr (RM == 1) rows_body<T, 8, RM, NW, KMAJOR>(a, k, lo, hi, sp, red);   // (two row groups: ranks up to 64)
+  if (r <= 16) rows_body<T, 1, RM, NW, KMAJOR, RANGES>(a, k, lo, hi, sp, red);
+  else if (r <= 32) rows_body<T, 2, RM, NW, KMAJOR, RANGES>(a, k, lo, hi, sp, red);
+  else if (r <= 64) rows_body<T, 4, RM, NW, KMAJOR, RANGES>(a, k, lo, hi, sp, red);
+  else if constexpr (RM == 1) rows_body<T, 8, RM, NW, KMAJOR, RANGES>(a, k, lo, hi, sp, red);   // (two row groups: ranks up to 64)
 }
 
 // Adds the contraction ranges of k_gen_rows in order, scales and rounds.  One thread per four columns of a row.
@@ -1216,8 +1217,9 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
   constexpr int most = 1 << 22;          // a launch holds fewer than 2^32 threads
   for (a.b0 = 0; a.b0 < blocks; a.b0 += most) {
     const dim3 grid((unsigned)(blocks - a.b0 < most ? blocks - a.b0 : most) * (unsigned)a.parts);
-    if (two) hipLaunchKernelGGL((k_gen_rows<T, 2, 8, KMAJOR>), grid, dim3(512), lds, c.stream, a);
-    else hipLaunchKernelGGL((k_gen_rows<T, 1, 8, KMAJOR>), grid, dim3(512), lds, c.stream, a);
+    if (two) hipLaunchKernelGGL((k_gen_rows<T, 2, 8, KMAJOR, false>), grid, dim3(512), lds, c.stream, a);
+    else if (a.parts > 1) hipLaunchKernelGGL((k_gen_rows<T, 1, 8, KMAJOR, true>), grid, dim3(512), lds, c.stream, a);
+    else hipLaunchKernelGGL((k_gen_rows<T, 1, 8, KMAJOR, false>), grid, dim3(512), lds, c.stream, a);
   }
   if (a.parts > 1) {
     const long long n = (long long)(c.st.off[c.K] - c.st.off[0]) * (c.ldz / 4);
