@@ -254,13 +254,29 @@ bool skinny(const SegTable& st, int M, int N, long long Kd) {
   return (virtual_rows(st, M) + BM - 1) / BM * ((N + BN - 1) / BN) <= kSmallTiles && general_skinny(st, M, N, Kd, MLORA_BF16);
 }
 
-// Forward products whose features are no multiples of 64, between three and four small tiles per CU, seven contraction tiles
-// deep at most: the 64 x 64 tiles of the general kernel, of which a CU holds five.  Call, small tiles -> general, us: 641 x 200 -> 4504
-// 16.4 -> 14.7, 1527 x 240 -> 2136 (10 tasks) 18.2 -> 16.2, 700 x 136 -> 4504 15.8 -> 15.1, 1500 x 328 -> 2136 18.5 -> 17.6, 700 x 392 ->
-// 4504 19.7 -> 19.5; with 756 tiles (300 x 200 -> 8008) 13.5 and 14.2, beyond 1024 larger tiles are faster than either.
+// Forward products whose features are no multiples of 64 that the general kernel runs: its tiles, of 64 x 64 or 128 x 128, fill the
+// chip where those of this file leave CUs idle.  Call, us, the plan above -> the general kernel:
+//   between three and four small tiles per CU, seven contraction tiles deep at most (a CU holds five of the general kernel's):
+//     641 x 200 -> 4504 16.4 -> 14.7, 1527 x 240 -> 2136 (10 tasks) 18.2 -> 16.2, 700 x 136 -> 4504 15.8 -> 15.1, 1500 x 328 -> 2136
+//     18.5 -> 17.6, 700 x 392 -> 4504 19.7 -> 19.5; with 756 tiles (300 x 200 -> 8008) 13.5 and 14.2, beyond 1024 larger tiles.
+//   ranks of 16 at most, one or two tiles of 128 x 128 per CU, two to five contraction tiles: of 26 calls none lost.  1826 x 152 -> 2128
+//     19.8 -> 12.6, 668 x 120 -> 8648 (10 tasks) 24.3 -> 16.0, 1500 x 136 -> 4504 21.6 -> 16.5, 10829 x 200 -> 328 21.7 -> 18.3,
+//     3002 x 256 -> 2248 18.1 -> 17.6; at rank 32 7163 x 272 -> 608 19.2 and 19.5, 17 contraction tiles at rank 64 35.0 and 39.3.
+//   ranks of 16 at most, whole tiles whose second round is no more than half full, two to eight contraction tiles: of 19 calls none lost.  1419 x 280 ->
+//     10808 48.6 -> 33.0, 13691 x 144 -> 1304 (10 tasks) 49.1 -> 37.7, 3000 x 152 -> 8008 45.9 -> 37.8, 2638 x 392 -> 7440 55.3 -> 45.5,
+//     2673 x 384 -> 8416 (10 tasks) 46.8 -> 46.6; with nine tiles 2636 x 536 -> 7840 55.4 and 59.7, 420 tiles of 256 x 256 59.4 and 64.4.
 bool general_forward(const SegTable& st, int M, int N, int Kd, const Plan& pl) {
-  const long long n = (virtual_rows(st, M) + 63) / 64 * ((N + 63) / 64);
-  return (N % 64 != 0 || Kd % 64 != 0) && pl.small > 0 && pl.parts == 1 && n > 3 * 256 && n <= 4 * 256 && Kd <= 7 * 64;
+  if ((N % 64 == 0 && Kd % 64 == 0) || pl.parts > 1 || pl.packed) return false;
+  const long long v = virtual_rows(st, M);
+  if (pl.small > 0) {
+    const long long n = (v + 63) / 64 * ((N + 63) / 64);
+    return n > 3 * 256 && n <= 4 * 256 && Kd <= 7 * 64;
+  }
+  int rmax = 0;
+  for (int k = 0; k < st.K; ++k) rmax = st.rank[k] > rmax ? st.rank[k] : rmax;
+  if (rmax > 16 || Kd <= 64) return false;
+  const long long whole = (v + BM - 1) / BM * ((N + BN - 1) / BN), quarters = (v + 127) / 128 * ((N + 127) / 128);
+  return (quarters > 256 && quarters <= 512 && Kd <= 5 * 64) || (pl.whole == whole && whole > 256 && whole <= 384 && Kd <= 8 * 64);
 }
 
 template <int NSEG>

@@ -26,6 +26,11 @@ CASES = [
     ((3191, 1232, 312, [1600, 1560], [32, 17], 4), {"dX_rows": 64}),
     # ... between three and four of them per CU: the general kernel's
     ((641, 200, 4504, [200, 203, 231], [64, 9, 16], 3), {"Y_rows": 64, "Y": "64"}),
+    # ... no more than two tiles of 128 x 128 per CU, or a second round of whole tiles half full at most: its larger tiles, to rank 16
+    ((2400, 152, 2128, [900, 33, 1450], [8, 16, 3], 3), {"Y": "128"}),
+    ((2400, 152, 2128, [900, 33, 1450], [8, 17, 3], 3), {"Y": "halves"}),
+    ((9268, 200, 1608, [4000, 33, 5000], [16, 8, 3], 20), {"Y": "128"}),
+    ((9268, 200, 1608, [4000, 33, 5000], [16, 8, 17], 20), {"Y": "whole"}),
     # 16 x 64 tiles
     ((128, 256, 256, [60, 60], [8, 64], 4), {"Y_rows": 16, "dX_rows": 16}),
     # partial contraction tiles, one chunk more or less than a whole one; 64 x 64 tiles
