@@ -60,7 +60,8 @@ void launch_whole(const gemmk::GemmArgs<NSEG>& a, int tiles, hipStream_t stream)
     }
   }
   // (without the code for partial contraction tiles where there are none: 16448 x 4096 -> 11008 forward, backward and
-  // gradients 2406 -> 2396 us, 22548 x 192 -> 8064 490 -> 485)
+  // gradients 2406 -> 2396 us, 22548 x 192 -> 8064 490 -> 485.  Ragged ranks, which run one form: 3072 x 4096 -> 4096 with it 235,
+  // without 234, 16000 x 5120 -> 13824 3347 and 3349)
   if (partial_tiles(a)) hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, NN, NSEG, false, true>), dim3(tiles), dim3(512), 0, stream, a);
   else hipLaunchKernelGGL((gemmk::k_gemm_mfma<2, 4, NN, NSEG, false, false>), dim3(tiles), dim3(512), 0, stream, a);
 }

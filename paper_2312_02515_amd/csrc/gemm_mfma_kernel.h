@@ -640,8 +640,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       issue_a(lc, stage_a(t));
       if (t < 2) issue_b(lc, stage_b(t));
     }
+    // (RAG: a LoRA tile's weight side is stored from registers, so that fewer than PER_TILE loads may stand behind tile 0)
     if (VT > 2 && HALF) wait_vmcnt<PER_TILE + LPA>();
-    else if (VT > 1) wait_vmcnt<PER_TILE>();
+    else if (VT > 1 && !(RAG && !HALF && base_tiles == 1)) wait_vmcnt<PER_TILE>();
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
 #pragma unroll

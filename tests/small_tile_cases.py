@@ -53,6 +53,9 @@ CASES = [
     ((9268, 1032, 184, [4000, 33, 5000], [64, 8, 16], 20), {"dX": "whole"}),
     ((9268, 632, 1032, [4000, 33, 5000], [64, 8, 16], 20), {"Y": "whole"}),
     ((9268, 1032, 632, [4000, 33, 5000], [64, 8, 20], 20), {"dX": "whole"}),
+    # ... a single base tile before the LoRA tiles of ranks that are no multiple of 8, waves without a weight row in the last column
+    ((17000, 264, 64, [9000, 33, 7900], [12, 5, 20], 20), {"dX": "whole"}),
+    ((17000, 264, 40, [9000, 33, 7900], [12, 5, 100], 20), {"dX": "whole"}),
 ]
 
 # Many tasks of few rows, whose rows are packed in pieces of 32 (half tiles, and 64 x 64 tiles of the general kernel): the
