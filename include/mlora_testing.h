@@ -76,15 +76,17 @@ mlora_status mlora_kernel_plan_tiles(const mlora_problem* p, int32_t* tiles);
 #define MLORA_PLAN_GROUP          5
 mlora_status mlora_kernel_plan_group(const mlora_problem* const* ps, int P, int32_t* plan);
 
-/* Measurement aid.  While enabled, every launch of the MFMA kernels by this process is bracketed
- * by a pair of HIP events recorded on the launch stream (at most 16384 launches are kept; the
- * events are created on first use and live until the process ends).  Returns the previous
- * setting. */
+/* Measurement aid.  While enabled, every launch of the MFMA kernels by this process, reductions
+ * of their ranges included, is bracketed by a pair of HIP events recorded on the launch stream
+ * (at most 16384 launches are kept; the events are created on first use and live until the
+ * process ends).  Returns the previous setting. */
 int mlora_profile_kernels(int enable);
 
 /* Kinds of kernels the measurement aid tells apart, and the unit their work is counted in. */
 #define MLORA_PROFILE_GEMM  0  /* base products with their LoRA steps; algorithmic flops
-                                  (2 M N K plus 2 t_k r_k N per task)                          */
+                                  (2 M N K plus 2 t_k r_k N per task).  The input gradient of a
+                                  small call runs in one launch with dA_k and dB_k, which are
+                                  counted here then, 2 t_k r_k (h + d) per task                */
 #define MLORA_PROFILE_ROWS  1  /* s x A and s dy B^T; algorithmic bytes (activation rows read
                                   once, result written once, adapter matrices read once)       */
 #define MLORA_PROFILE_GRAD  2  /* dA_k and dB_k; algorithmic bytes                             */

@@ -25,16 +25,6 @@ bool gemm_mfma_ok(int M, int N, int Kd) { return M >= 1 && (N % 8) == 0 && (Kd %
 namespace {
 
 template <int NSEG>
-double algorithmic_flops(const gemmk::GemmArgs<NSEG>& a) {
-  double f = 0;
-  for (int g = 0; g < NSEG; ++g) {
-    f += 2.0 * a.M * (double)a.N * a.Kd[g];
-    for (int k = 0; k < a.K; ++k) f += 2.0 * (a.off[k + 1] - a.off[k]) * (double)a.rank[g][k] * a.N;
-  }
-  return f;
-}
-
-template <int NSEG>
 bool ragged_ranks(const gemmk::GemmArgs<NSEG>& a) {
   for (int g = 0; g < NSEG; ++g)
     for (int k = 0; k < a.K; ++k)
@@ -303,7 +293,7 @@ hipError_t launch(gemmk::GemmArgs<NSEG>& a, float* scratch, size_t scratch_bytes
   a.t0 = pl.whole;
   a.parts = pl.parts;
   a.part = scratch;
-  const int slot = profile_begin(kProfileGemm, algorithmic_flops(a), stream);
+  const int slot = profile_begin(kProfileGemm, product_work(a), stream);
   if (pl.small > 0) {
     launch_ring<NSEG>(a, st, NN, pl.small, pl.parts, scratch, stream);
     const hipError_t e = hipGetLastError();

@@ -1193,6 +1193,25 @@ int gen_rows_parts(const CallCtx& c, int inner, size_t limit) {
   return p > 1 ? p : 1;
 }
 
+// algorithmic work of the launches below, as the timing of launches counts it (rows and gradients: bytes)
+template <typename T>
+double rows_work(const CallCtx& c, int inner) {
+  double b = (double)(c.st.off[c.K] - c.st.off[0]) * ((double)inner + c.ldz);
+  for (int k = 0; k < c.K; ++k) b += (double)c.st.rank[k] * inner;
+  return b * sizeof(T);
+}
+double grads_work(const CallCtx& c, bool both) {
+  const double wide = (double)c.d + (both ? c.h : 0), el = c.dtype == MLORA_F32 ? 4.0 : 2.0;
+  double b = (double)(c.st.off[c.K] - c.st.off[0]) * (wide + (both ? 2.0 : 1.0) * c.ldz) * el;
+  for (int k = 0; k < c.K; ++k) b += (double)c.st.rank[k] * wide * 4.0;
+  return b;
+}
+double grads_flops(const CallCtx& c) {
+  double f = 0;
+  for (int k = 0; k < c.K; ++k) f += 2.0 * (c.st.off[k + 1] - c.st.off[k]) * (double)c.st.rank[k] * ((double)c.h + c.d);
+  return f;
+}
+
 template <typename T, bool KMAJOR>
 hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const PtrTable& M, float* scratch) {
   if (c.K == 0 || c.T == 0 || row_blocks(c.st, 16) == 0) return hipSuccess;
@@ -1215,6 +1234,7 @@ hipError_t rows_t(const CallCtx& c, const void* In, int inner, void* Out, const 
   const int groups = c.ldz <= 16 ? 1 : (c.ldz <= 32 ? 2 : (c.ldz <= 64 ? 4 : 8));
   const unsigned lds = 4 * (two ? 2 : 1) * groups * 1024;
   constexpr int most = 1 << 22;          // a launch holds fewer than 2^32 threads
+  const Profiled timed(kProfileRows, rows_work<T>(c, inner), c.stream);
   for (a.b0 = 0; a.b0 < blocks; a.b0 += most) {
     const dim3 grid((unsigned)(blocks - a.b0 < most ? blocks - a.b0 : most) * (unsigned)a.parts);
     if (two) hipLaunchKernelGGL((k_gen_rows<T, 2, 8, KMAJOR, false>), grid, dim3(512), lds, c.stream, a);
@@ -1364,6 +1384,7 @@ hipError_t launch_gemm(GenGemmArgs<NSEG>& a, const GemmPlan& pl, float* scratch,
   a.parts = 1;
   a.t0 = a.units = pl.whole;
   const int tiles = pl.tiles_m * pl.tiles_n;
+  const Profiled timed(kProfileGemm, product_work(a), s);
   if (pl.skinny) {
     hipLaunchKernelGGL((k_gen_skinny<T, NN, NSEG>), dim3((unsigned)tiles), dim3(512), 0, s, a);
     return hipGetLastError();
@@ -1637,6 +1658,7 @@ hipError_t general_grads(const CallCtx& c, const void* dY, const void* Z, const 
   GradPlan p;
   // (planned for both outputs, so that the scratch suffices for either)
   plan_grads(c, dY, Z, dB, X, G, dA, accumulate, ranges > 0 ? ranges : general_grad_ranges(c), scratch, &p);
+  const Profiled timed(kProfileGrad, grads_work(c, dA != nullptr), c.stream);
   if (c.dtype == MLORA_F32) launch_grads<float>(p.b, p.a, p.blocks_b, p.blocks, c.ldz, c.stream);
   else launch_grads<bf16>(p.b, p.a, p.blocks_b, p.blocks, c.ldz, c.stream);
   const hipError_t e = hipGetLastError();
@@ -1693,6 +1715,7 @@ hipError_t general_grads_group(int n, const GradItem* items, int accumulate, flo
       p.blocks[q] = gp.blocks;
       ldz = g.c->ldz > ldz ? g.c->ldz : ldz;
     }
+    const Profiled timed(kProfileGrad, grads_work(*x.c, x.dA != nullptr) + grads_work(*y.c, y.dA != nullptr), c.stream);
     if (c.dtype == MLORA_F32) launch_two<float>(p, ldz, c.stream);
     else launch_two<bf16>(p, ldz, c.stream);
     e = hipGetLastError();
@@ -1739,6 +1762,7 @@ hipError_t general_back(const CallCtx& c, const BackPlan& bp, bool aligned, cons
                                  : kNotSmall;
   if (form == kRing) {
     ring_tiles(&r, c.st, parts, partial);
+    const Profiled timed(kProfileGemm, product_work(r) + grads_flops(c), c.stream);
     if (nq == 1) launch_back_ring<1>(r, groups, p, c.stream);
     else if (nq == 2) launch_back_ring<2>(r, groups, p, c.stream);
     else launch_back_ring<4>(r, groups, p, c.stream);
@@ -1770,6 +1794,7 @@ hipError_t general_back(const CallCtx& c, const BackPlan& bp, bool aligned, cons
     g.part = partial;
     g.t0 = 0;
     const bool f32 = c.dtype == MLORA_F32;
+    const Profiled timed(kProfileGemm, product_work(g) + grads_flops(c), c.stream);
     if (nq == 1) f32 ? launch_back<float, 1>(g, pl.skinny, p, c.stream) : launch_back<bf16, 1>(g, pl.skinny, p, c.stream);
     else if (nq == 2) f32 ? launch_back<float, 2>(g, pl.skinny, p, c.stream) : launch_back<bf16, 2>(g, pl.skinny, p, c.stream);
     else f32 ? launch_back<float, 4>(g, pl.skinny, p, c.stream) : launch_back<bf16, 4>(g, pl.skinny, p, c.stream);

@@ -188,6 +188,24 @@ enum { kProfileGemm = 0, kProfileRows = 1, kProfileGrad = 2, kProfileKinds = 3 }
 int profile_enable(int enable);
 int profile_begin(int kind, double units, hipStream_t stream);
 void profile_end(int slot, hipStream_t stream);
+// flops of a product with its LoRA terms, from a kernel's arguments
+template <typename Args>
+double product_work(const Args& a) {
+  double f = 0;
+  for (int g = 0; g < (int)(sizeof(a.Kd) / sizeof(a.Kd[0])); ++g) {
+    f += 2.0 * a.M * (double)a.N * a.Kd[g];
+    for (int k = 0; k < a.K; ++k) f += 2.0 * (a.off[k + 1] - a.off[k]) * (double)a.rank[g][k] * a.N;
+  }
+  return f;
+}
+struct Profiled {      // the launches of a scope
+  const int slot;
+  const hipStream_t stream;
+  Profiled(int kind, double units, hipStream_t s) : slot(profile_begin(kind, units, s)), stream(s) {}
+  ~Profiled() { profile_end(slot, stream); }
+  Profiled(const Profiled&) = delete;
+  Profiled& operator=(const Profiled&) = delete;
+};
 hipError_t profile_read(double* ms, double* units, int* launches);
 
 // w8_kernels.hip : column-wise absmax code of the frozen weight and its decoder

@@ -334,3 +334,37 @@ def test_one_workspace_for_every_batch(dtype):
         assert torch.equal(Y, ref["Y"]) and torch.equal(dX, ref["dX"])
         for k in range(len(ranks)):
             assert torch.equal(dA[k], ref["dA"][k]) and torch.equal(dB[k], ref["dB"][k])
+
+
+# aligned kernels; 16 x 64 tiles and a shared launch; small tiles in ranges; the general kernel's tiles, in fp32 and ranges
+@pytest.mark.parametrize("T,h,d,tokens,ranks,f32", [
+    (900, 2048, 5632, [256, 515], [8, 16], False),
+    (128, 256, 256, [60, 60], [8, 64], False),
+    (60, 584, 4040, [37, 20], [12, 40], False),
+    (300, 704, 70, [150, 100], [5, 16], False),
+    (300, 2001, 501, [150, 140], [16, 3], True),
+    (6, 4096, 4096, [2, 3], [16, 100], False),
+])
+def test_timed_launches(T, h, d, tokens, ranks, f32):
+    """Every launch of a call is timed, and its work counted once."""
+    inp = _inputs(T, h, d, tokens, ranks, torch.float32 if f32 else torch.bfloat16, lead=1, seed=97)
+    prob = mb.Problem(T, h, d, inp.W, inp.seg_offsets, inp.ranks, inp.scalings, inp.A, inp.B)
+    shared = prob.kernel_plan()["shared"]
+    run_hip(inp)
+    mb.profile_kernels_read()
+    mb.profile_kernels(True)
+    try:
+        run_hip(inp)
+    finally:
+        mb.profile_kernels(False)
+    got = mb.profile_kernels_read()
+    el, rows, r = (4 if f32 else 2), sum(tokens), sum(ranks)
+    lora = sum(t * k for t, k in zip(tokens, ranks))
+    assert got["gemm"][1] == 4 * T * h * d + 2 * lora * (h + d) * (2 if shared else 1)
+    assert (got["grad"][1] > 0) == (not shared) and got["gemm"][2] == 2 and got["rows"][2] >= 2
+    low = el * ((rows + r) * (h + d))
+    assert low < got["rows"][1] <= low + 2 * el * rows * 128
+    if not shared:
+        low = el * rows * (h + d) + 4 * r * (h + d)
+        assert low < got["grad"][1] <= low + 2 * el * rows * 128
+    assert all(got[k][0] > 0 for k in got if got[k][2])
