@@ -64,6 +64,9 @@ def test_small_tile_isolation(case):
     lo, hi = inp.seg_offsets[k], inp.seg_offsets[k + 1]
     inp.A[k].fill_(float("nan"))
     inp.B[k].fill_(float("inf"))
+    for big, value in ((inp.X, "nan"), (inp.dY, "inf")):
+        big[lo:hi:2] = float(value)
+        big[lo + 1:hi:2] = -float("inf")
     out = run_hip(inp)
     for name in ("Y", "dX"):
         a, b = ref[name].view(torch.int16), out[name].view(torch.int16)
