@@ -11,7 +11,8 @@ template <int NSEG>
 void launch_ring(gemmk::GemmArgs<NSEG> a, const SegTable& st, bool nn, int groups, int parts, float* scratch, hipStream_t s);
 
 // fills in the tile counts and ranges; adds the ranges (nothing to do for one)
-void ring_tiles(gemmk::GemmArgs<1>* a, const SegTable& st, int parts, float* scratch);
+template <int NSEG>
+void ring_tiles(gemmk::GemmArgs<NSEG>* a, const SegTable& st, int parts, float* scratch);
 template <int NSEG>
 void launch_ring_reduce(const gemmk::GemmArgs<NSEG>& a, hipStream_t s);
 

@@ -5,10 +5,10 @@
 namespace mlora {
 namespace {
 
-template <int G, int NS, bool NN, int NSEG>
+template <int G, bool NN, int NSEG>
 void launch_tile(const gemmk::GemmArgs<NSEG>& a, hipStream_t s) {
   const int units = a.tiles_m * a.tiles_n;
-  hipLaunchKernelGGL((ringk::k_gemm_ring<G, NS, NN, NSEG>), dim3((unsigned)(units * a.parts)), dim3(256 * G), 0, s, a);
+  hipLaunchKernelGGL((ringk::k_gemm_ring<G, NN, NSEG>), dim3((unsigned)(units * a.parts)), dim3(256 * G), 0, s, a);
   launch_ring_reduce(a, s);
 }
 
@@ -32,26 +32,24 @@ void launch_ring_reduce(const gemmk::GemmArgs<NSEG>& a, hipStream_t s) {
 }
 template void launch_ring_reduce<1>(const gemmk::GemmArgs<1>&, hipStream_t);
 
-void ring_tiles(gemmk::GemmArgs<1>* a, const SegTable& st, int parts, float* scratch) {
+template <int NSEG>
+void ring_tiles(gemmk::GemmArgs<NSEG>* a, const SegTable& st, int parts, float* scratch) {
   a->tiles_m = (int)((virtual_rows(st, a->M) + 63) / 64);
   a->tiles_n = (a->N + 63) / 64;
   a->t0 = 0;
   a->parts = parts;
   a->part = scratch;
 }
+template void ring_tiles<1>(gemmk::GemmArgs<1>*, const SegTable&, int, float*);
 
 template <int NSEG>
 void launch_ring(gemmk::GemmArgs<NSEG> a, const SegTable& st, bool nn, int groups, int parts, float* scratch, hipStream_t s) {
-  a.tiles_m = (int)((virtual_rows(st, a.M) + 63) / 64);
-  a.tiles_n = (a.N + 63) / 64;
-  a.t0 = 0;
-  a.parts = parts;
-  a.part = scratch;
+  ring_tiles(&a, st, parts, scratch);
   if constexpr (NSEG == 1) {
-    if (nn) return groups == 2 ? launch_tile<2, 3, true, 1>(a, s) : launch_tile<1, 3, true, 1>(a, s);
-    if (groups == 2) return launch_tile<2, 3, false, 1>(a, s);
+    if (nn) return groups == 2 ? launch_tile<2, true, 1>(a, s) : launch_tile<1, true, 1>(a, s);
+    if (groups == 2) return launch_tile<2, false, 1>(a, s);
   }
-  launch_tile<1, 3, false, NSEG>(a, s);
+  launch_tile<1, false, NSEG>(a, s);
 }
 template void launch_ring<1>(gemmk::GemmArgs<1>, const SegTable&, bool, int, int, float*, hipStream_t);
 template void launch_ring<2>(gemmk::GemmArgs<2>, const SegTable&, bool, int, int, float*, hipStream_t);

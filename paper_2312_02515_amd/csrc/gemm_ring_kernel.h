@@ -7,7 +7,7 @@
 //
 // Such calls are bound by latency, not by a rate: what a block does before, between and behind its MFMAs counts.
 // A block of one or two groups of 4 waves owns a 64 x 64 tile; the waves of a group split each contraction tile, and two
-// groups take every other one.  Contraction tiles of 64 come by direct global->LDS loads into a ring of NS stages per
+// groups take every other one.  Contraction tiles of 64 come by direct global->LDS loads into a ring of three stages (NS) per
 // group, NS - 1 tiles ahead of their use, with one barrier per tile; the loop is rolled (its code is fetched cold by
 // every launch).  The LoRA term is more contraction tiles from the same ring, of two slots of 32 ranks each, so that no
 // load of it is waited for at the end.
@@ -40,8 +40,9 @@ __device__ __forceinline__ Tile tile_of(int t, int tiles_m, int tiles_n) {
   return Tile{first + in_g % gm, in_g / gm};
 }
 
-template <int G, int NS> constexpr int kRingLds = G * NS * 2 * 64 * 128;
-template <int G, int NS, bool NN, int NSEG>
+constexpr int NS = 3;
+template <int G> constexpr int kRingLds = G * NS * 2 * 64 * 128;
+template <int G, bool NN, int NSEG>
 __device__ __forceinline__ void ring_body(const GemmArgs<NSEG>& ga, int bid, char* sm) {
   constexpr int BK = 64, BM = 64, BN = 64, NFR = 2;
   constexpr int ABYTES = BM * 128, SBYTES = 2 * ABYTES;
@@ -352,10 +353,10 @@ __device__ __forceinline__ void ring_body(const GemmArgs<NSEG>& ga, int bid, cha
   }
 }
 
-template <int G, int NS, bool NN, int NSEG>
+template <int G, bool NN, int NSEG>
 __global__ __launch_bounds__(256 * G, G == 1 ? 3 : 2) void k_gemm_ring(const GemmArgs<NSEG> ga) {
-  __shared__ __attribute__((aligned(1024))) char sm[kRingLds<G, NS>];
-  ring_body<G, NS, NN, NSEG>(ga, blockIdx.x, sm);
+  __shared__ __attribute__((aligned(1024))) char sm[kRingLds<G>];
+  ring_body<G, NN, NSEG>(ga, blockIdx.x, sm);
 }
 
 // Adds the contraction ranges in order and writes the rows: block = a quarter of each quadrant of a tile, a wave one of

@@ -1153,9 +1153,9 @@ __global__ __launch_bounds__(256) void k_gen_back_64(const GenGemmArgs<1> g, con
 }
 template <int G, int NQ>
 __global__ __launch_bounds__(256 * G, G == 1 ? 3 : 2) void k_gen_back_ring(const gemmk::GemmArgs<1> g, const BackArgs p) {
-  __shared__ __attribute__((aligned(1024))) char sm[ringk::kRingLds<G, 3>];
+  __shared__ __attribute__((aligned(1024))) char sm[ringk::kRingLds<G>];
   const int bid = blockIdx.x;
-  if (bid >= p.lead) return ringk::ring_body<G, 3, false, 1>(g, bid - p.lead, sm);
+  if (bid >= p.lead) return ringk::ring_body<G, false, 1>(g, bid - p.lead, sm);
   const int half = G == 1 ? 0 : (int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 8);
   const bool two = G == 2 && p.lead < p.blocks;      // neighbours: mostly of one task, which take as long
   if (two || half == 0) gen_grads_body<bf16, NQ>(p.b, p.a, p.blocks_b, p.blocks, two ? 2 * bid + half : bid);

@@ -95,11 +95,10 @@ __device__ __forceinline__ RowPiece packed_piece(int M, unsigned v0) {
 // ... the tasks of rows [row, row + n): k from first() on, as long as their rows begin inside
 struct TaskWalk {
   int off;                 // lane k: first row of task k (entries from K on: the end of the last one's rows)
-  int K;
 };
 template <typename Args>
 __device__ __forceinline__ TaskWalk task_walk(const Args& a) {
-  return TaskWalk{a.off[threadIdx.x & 63], a.K};
+  return TaskWalk{a.off[threadIdx.x & 63]};
 }
 __device__ __forceinline__ int task_begin(const TaskWalk& w, int k, int rows_end) {
   return k < 64 ? __builtin_amdgcn_readlane(w.off, k) : rows_end;
