@@ -384,7 +384,6 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
   // or A_k), fetched into the same LDS layouts by the same direct loads two tiles ahead, so the LoRA term
   // costs ceil(r_k / 32) more half tiles on the same accumulators and no exposed load latency.
   LoraTiles lora{0, 0};
-  if constexpr (!HALF) lora = lora_tiles<NFR>(ga, [&](int f) { return frag_task(f); });
   // what the load slots of a tile fetch: base tile kt of the current operand pair, or a LoRA tile.
   // `left`: contraction indices of the tile, fewer than 64 in the last one of features that are no multiple of 64
   struct LoadCtx {
@@ -609,7 +608,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
     set_operands(ga.A[sg], ga.Bm[sg], ga.Kd[sg]);
     abase += (size_t)k0 * (BK * 2);
     bbase += (size_t)k0 * bstep;
-    const int VT = base_tiles + (!HALF && sg == NSEG - 1 ? lora.n : 0);  // tiles of this pass: base tiles, then LoRA tiles
+    int VT = base_tiles;                     // tiles of this pass: base tiles, then (whole tiles, last pair) LoRA tiles
     auto ctx_of = [&](int v) {
       LoadCtx lc = base_ctx(v);
       lc.Kd = ga.Kd[sg];
@@ -633,8 +632,17 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void k_gemm_mfma(const GemmA
       else return u % 2 == 0 ? sB0 : sB1;
     };
     // whole tiles: tiles 0 and 1.  HALF: also the A side of tile 2.  The first reads need tile 0
+    // (the table of the LoRA tiles is made while tile 0, a base tile, is on its way: in front of it, every block paid for the table before
+    // its first load.  Call, us: 13358 x 384 -> 3392 159.6 -> 157.7 and 180.7 -> 178.2 (6 and 40 tasks), 22548 x 192 -> 8064 forward
+    // 184.8 -> 179.6, 8192 x 4096 -> 4096 437.9 -> 435.5)
 #pragma unroll(HALF ? 3 : 1)
     for (int t = 0; t < (HALF ? 3 : 2); ++t) {
+      if constexpr (!HALF) {
+        if (t == 1 && sg == NSEG - 1) {
+          lora = lora_tiles<NFR>(ga, [&](int f) { return frag_task(f); });
+          VT += lora.n;
+        }
+      }
       if (t >= VT) break;
       const LoadCtx lc = ctx_of(t);
       issue_a(lc, stage_a(t));
