@@ -1742,7 +1742,8 @@ BackPlan plan_back(const CallCtx& c, bool aligned) {
   double product;
   if (!small_product(c, aligned, c.scratch_bytes, &product)) return apart;
   const int ranges = best_grad_ranges(c, product, c.dtype == MLORA_F32 ? kLeastTokens : 2 * kLeastTokens);
-  const size_t left = c.scratch_bytes - (ranges > 1 ? grad_sum_bytes(c.st, ranges, c.d, c.h) : 0);
+  if (ranges == 1) return BackPlan{true, 1, c.scratch_bytes};
+  const size_t left = c.scratch_bytes - grad_sum_bytes(c.st, ranges, c.d, c.h);
   return small_product(c, aligned, left, &product) ? BackPlan{true, ranges, left} : apart;
 }
 
