@@ -235,11 +235,14 @@ const char* mlora_status_string(mlora_status s);
 /* hipError_t (as int) of the last HIP failure seen by this thread's calls; 0 if none. */
 int mlora_last_hip_error(void);
 
-/* Whether the calls run the fastest kernels for `p`, the aligned bf16 ones (direct-to-LDS loads) in
- * their whole-chunk form (bit mask), so that a caller can tell before it launches anything:
- *   0      they do everywhere,
+/* Whether `p` has the form that the fastest kernels take, the aligned bf16 ones (direct-to-LDS loads)
+ * in their whole-chunk form (bit mask), so that a caller can tell before it launches anything:
+ *   0      it has,
  *   bit 0  the two base products run other kernels,
  *   bit 1  the low-rank products do.
+ * Small calls run some launches in forms of their own whatever the answer, where those are faster
+ * (products in small tiles, dX and the gradients in one launch): mlora_kernel_plan (mlora_testing.h)
+ * tells which.
  * That form takes bf16 problems whose h and d are multiples of 64, whose ranks are multiples of 8 and
  * whose W, A_k, B_k are 16-byte aligned.  Where only a rank stands in the way, both bits are set and
  * the aligned kernels run in forms for ragged ranks, a little slower; with features that are multiples of
